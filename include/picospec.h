@@ -101,7 +101,10 @@ enum { PICOSPEC_LIMIT_MAX_K = 0, PICOSPEC_LIMIT_MAX_V = 1 };
  *          order whose probability sum reaches top_p, capped at k (a workload setting, not in the paper)
  *   idx [n_rows,k] int32, prob [n_rows,k] fp32, count [n_rows] int32, mass [n_rows] fp32,
  *   lse [n_rows] fp32             out
- *   workspace: unused (picospec_workspace_bytes(PICOSPEC_CALL_COMPRESS, ...) is 0); pass NULL.
+ *   workspace (optional): picospec_workspace_bytes(PICOSPEC_CALL_COMPRESS, ...) bytes; 0 for calls that have no use for one.
+ *              A call of few rows then spreads every row over many workgroups.  The records hold the same ids; the row's
+ *              sum is formed in another order, so probabilities, mass and lse agree to rounding.  NULL or a smaller one:
+ *              one workgroup per row.
  */
 int picospec_compress(const void* logits, int dtype, int64_t ld, int32_t n_rows, int32_t V,
                       float temperature, int32_t k, float top_p,
@@ -199,6 +202,14 @@ int picospec_sample_residual(const void* tgt_logits, int dtype, int64_t ld, int3
  */
 int picospec_row_stats(const void* logits, int dtype, int64_t ld, int32_t n_rows, int32_t V, float temperature,
                        float* row_max, float* row_sum, float* row_lse, void* stream);
+
+/*
+ * The same with an optional workspace of picospec_workspace_bytes(PICOSPEC_CALL_VERIFY, dtype, n_rows, V, 0) bytes: a call
+ * of up to 256 rows then spreads every row over many workgroups (the sums are formed in another order and agree to rounding).
+ */
+int picospec_row_stats_ws(const void* logits, int dtype, int64_t ld, int32_t n_rows, int32_t V, float temperature,
+                          float* row_max, float* row_sum, float* row_lse,
+                          void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * The downlink record (Eq. 4): picospec_compress of ONE target row per sequence, the row of its

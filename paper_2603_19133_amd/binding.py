@@ -19,13 +19,13 @@ F32, BF16 = 0, 1
 OK, EINVAL, EWORKSPACE, EDTYPE, EHIP, EUNSUPPORTED, ESCRATCH = 0, -1, -2, -3, -4, -5, -6
 FLAG_TOKEN_NOT_IN_SUPPORT, FLAG_NONFINITE, FLAG_RESIDUAL_EMPTY, FLAG_BAD_INPUT = 1, 2, 4, 8
 CALL_COMPRESS, CALL_SAMPLE_DRAFT, CALL_VERIFY, CALL_SAMPLE_RESIDUAL = 0, 1, 2, 3
-CALL_ROUND, CALL_VERIFY_SAMPLE = 6, 7
+CALL_COMPRESS_REJECTED, CALL_RESAMPLE_SPARSE, CALL_ROUND, CALL_VERIFY_SAMPLE = 4, 5, 6, 7
 LIMIT_MAX_K, LIMIT_MAX_V = 0, 1
 WIRE_FP32, WIRE_FP16, WIRE_BF16 = 0, 1, 2
 WIRE_BAD_HEADER, WIRE_BAD_BATCH, WIRE_CLAMPED, WIRE_TRUNCATED = 1, 2, 4, 8
 
 EXPORTS = ("picospec_round", "picospec_verify_sample", "picospec_verify_sample_static", "picospec_static_scratch_bytes", "picospec_compress", "picospec_sample_draft", "picospec_verify", "picospec_verify_range", "picospec_sample_residual",
-           "picospec_row_stats", "picospec_compress_rejected", "picospec_resample_sparse",
+           "picospec_row_stats", "picospec_row_stats_ws", "picospec_compress_rejected", "picospec_resample_sparse",
            "picospec_pack_downlink", "picospec_unpack_downlink", "picospec_pack_uplink", "picospec_unpack_uplink",
            "picospec_downlink_bytes_max", "picospec_uplink_bytes", "picospec_max_load_byte", "picospec_check_device", "picospec_probe_clock",
            "picospec_workspace_bytes", "picospec_limit", "picospec_strerror", "picospec_version")
@@ -55,6 +55,7 @@ lib.picospec_static_scratch_bytes.restype = _i64
 lib.picospec_sample_residual.argtypes = [_p, C.c_int, _i64, _i32, _f, _i32, _i32, _p, _p, _p, _p, _p, _p, _p, _p,
                                          _i32, C.c_int, _p, _p, _p, _p, _p, _sz, _p]
 lib.picospec_row_stats.argtypes = [_p, C.c_int, _i64, _i32, _i32, _f, _p, _p, _p, _p]
+lib.picospec_row_stats_ws.argtypes = [_p, C.c_int, _i64, _i32, _i32, _f, _p, _p, _p, _p, _sz, _p]
 lib.picospec_compress_rejected.argtypes = [_p, C.c_int, _i64, _i32, _f, _i32, _i32, _p, _p, _i32, _f,
                                            _p, _p, _p, _p, _p, _p, _sz, _p]
 lib.picospec_resample_sparse.argtypes = [_p, C.c_int, _i64, _i32, _f, _i32, _i32, _p, _p, _p, _p, _p, _p, _p, _p,
@@ -80,7 +81,7 @@ lib.picospec_limit.restype = _i64
 lib.picospec_strerror.argtypes = [C.c_int]
 lib.picospec_strerror.restype = C.c_char_p
 for _n in ("picospec_compress", "picospec_sample_draft", "picospec_verify", "picospec_sample_residual",
-           "picospec_row_stats", "picospec_compress_rejected", "picospec_resample_sparse", "picospec_version",
+           "picospec_row_stats", "picospec_row_stats_ws", "picospec_compress_rejected", "picospec_resample_sparse", "picospec_version",
            "picospec_pack_downlink", "picospec_unpack_downlink", "picospec_pack_uplink", "picospec_unpack_uplink",
            "picospec_verify_range", "picospec_round"):
     getattr(lib, _n).restype = C.c_int
@@ -149,15 +150,32 @@ def alloc_compressed(rows: int, k: int, device) -> Compressed:
     return Compressed(e(rows, k, dt=torch.int32), e(rows, k), e(rows, dt=torch.int32), e(rows), e(rows), k)
 
 
+def _scratch(which: int, dt: int, rows: int, V: int, k: int, device):
+    """Scratch of a compressing call of few rows (None where the call has no use for one)."""
+    n = lib.picospec_workspace_bytes(which, dt, rows, V, k)
+    return torch.empty(n, dtype=torch.uint8, device=device) if n else None
+
+
+_SPLIT_ROWS, _SPLIT_MIN_V = 256, 16384     # calls of up to this many target rows form their statistics from a table
+
+
+def _table(workspace, dt: int, rows: int, V: int, device):
+    """The workspace of a call of few target rows that was given none: the rows are then spread over many workgroups."""
+    if workspace is not None or not 0 < rows <= _SPLIT_ROWS or V < _SPLIT_MIN_V:
+        return workspace
+    return torch.empty(lib.picospec_workspace_bytes(CALL_VERIFY, dt, rows, V, 0), dtype=torch.uint8, device=device)
+
+
 def compress(logits: torch.Tensor, V: int, temperature: float, k: int, top_p: float = 0.0,
              out: Compressed | None = None) -> Compressed:
     """picospec_compress on [rows, >=V] fp32/bf16 device logits."""
     dt, ld = _logits_2d(logits)
     rows = logits.shape[0]
     out = out or alloc_compressed(rows, k, logits.device)
+    ws = _scratch(CALL_COMPRESS, dt, rows, V, k, logits.device)
     _check(lib.picospec_compress(_ptr(logits), dt, ld, rows, V, temperature, k, top_p,
                                  _ptr(out.idx), _ptr(out.prob), _ptr(out.count), _ptr(out.mass), _ptr(out.lse),
-                                 None, 0, _stream()))
+                                 _ptr(ws), _nbytes(ws), _stream()))
     return out
 
 
@@ -197,6 +215,7 @@ def verify(tgt_logits: torch.Tensor, V: int, temperature: float, seq_off: torch.
     dt, ld = _logits_2d(tgt_logits)
     B = seq_off.shape[0] - 1
     out = out or alloc_verified(B, n_draft, tgt_logits.device)
+    workspace = _table(workspace, dt, n_draft + B, V, tgt_logits.device)
     _check(lib.picospec_verify(_ptr(tgt_logits), dt, ld, V, temperature, B, n_draft, _ptr(seq_off), _ptr(draft_tok),
                                _ptr(q.idx) if q else None, _ptr(q.prob) if q else None,
                                _ptr(q.count) if q else None, _ptr(q.mass) if q else None,
@@ -216,6 +235,7 @@ def verify_range(tgt_logits: torch.Tensor, V: int, temperature: float, seq_off: 
     dt, ld = _logits_2d(tgt_logits)
     B = seq_off.shape[0] - 1
     out = out or alloc_verified(B, n_draft, tgt_logits.device)
+    workspace = _table(None, dt, n_draft + B, V, tgt_logits.device)
     _check(lib.picospec_verify_range(_ptr(tgt_logits), dt, ld, V, temperature, B, n_draft, _ptr(seq_off), _ptr(draft_tok),
                                      _ptr(q.idx) if q else None, _ptr(q.prob) if q else None,
                                      _ptr(q.count) if q else None, _ptr(q.mass) if q else None,
@@ -223,7 +243,7 @@ def verify_range(tgt_logits: torch.Tensor, V: int, temperature: float, seq_off: 
                                      _ptr(pos_begin), _ptr(pos_end), gamma_max,
                                      _ptr(out.n_accept), _ptr(out.p_tok), _ptr(out.q_tok),
                                      _ptr(out.tgt_max), _ptr(out.tgt_sum), _ptr(out.tgt_lse), _ptr(out.flags),
-                                     None, 0, _stream()))
+                                     _ptr(workspace), _nbytes(workspace), _stream()))
     return out
 
 
@@ -241,6 +261,10 @@ def round(draft_logits: torch.Tensor, tgt_logits: torch.Tensor, V: int, temperat
     q = q or alloc_compressed(n_draft, k, dev)
     ver = ver or alloc_verified(B, n_draft, dev)
     res = res or alloc_residual(B, dev)
+    split = lib.picospec_workspace_bytes(CALL_COMPRESS, dt, n_draft, V, k)
+    if split:                                 # few draft rows: the call's own buffer, the segment table and the split kernels' scratch
+        table = lib.picospec_workspace_bytes(CALL_ROUND, dt, n_draft + B, V, 0)
+        workspace = torch.empty((table + 15) // 16 * 16 + split, dtype=torch.uint8, device=dev)
     _check(lib.picospec_round(_ptr(draft_logits), _ptr(tgt_logits), dt, ld_d, ld_t, V, temperature, B, n_draft,
                               _ptr(seq_off), _ptr(draft_tok), k, top_p, renorm, _ptr(uniforms),
                               _ptr(q.idx), _ptr(q.prob), _ptr(q.count), _ptr(q.mass), _ptr(q.lse),
@@ -260,6 +284,7 @@ def verify_sample(tgt_logits: torch.Tensor, V: int, temperature: float, seq_off:
     dev = tgt_logits.device
     ver = ver or alloc_verified(B, n_draft, dev)
     res = res or alloc_residual(B, dev)
+    workspace = _table(workspace, dt, n_draft + B, V, dev)
     _check(lib.picospec_verify_sample(_ptr(tgt_logits), dt, ld, V, temperature, B, n_draft, _ptr(seq_off), _ptr(draft_tok),
                                       _ptr(q.idx), _ptr(q.prob), _ptr(q.count), _ptr(q.mass), q.k, renorm, _ptr(uniforms),
                                       _ptr(ver.n_accept), _ptr(ver.p_tok), _ptr(ver.q_tok),
@@ -323,7 +348,9 @@ def row_stats(logits: torch.Tensor, V: int, temperature: float):
     rows = logits.shape[0]
     e = lambda: torch.empty(rows, dtype=torch.float32, device=logits.device)
     mx, sm, ls = e(), e(), e()
-    _check(lib.picospec_row_stats(_ptr(logits), dt, ld, rows, V, temperature, _ptr(mx), _ptr(sm), _ptr(ls), _stream()))
+    ws = _table(None, dt, rows, V, logits.device)
+    _check(lib.picospec_row_stats_ws(_ptr(logits), dt, ld, rows, V, temperature, _ptr(mx), _ptr(sm), _ptr(ls),
+                                     _ptr(ws), _nbytes(ws), _stream()))
     return mx, sm, ls
 
 
@@ -333,9 +360,10 @@ def compress_rejected(tgt_logits: torch.Tensor, V: int, temperature: float, seq_
     dt, ld = _logits_2d(tgt_logits)
     B = seq_off.shape[0] - 1
     out = out or alloc_compressed(B, k, tgt_logits.device)
+    ws = _scratch(CALL_COMPRESS_REJECTED, dt, B, V, k, tgt_logits.device)
     _check(lib.picospec_compress_rejected(_ptr(tgt_logits), dt, ld, V, temperature, B, n_draft, _ptr(seq_off),
                                           _ptr(n_accept), k, top_p, _ptr(out.idx), _ptr(out.prob), _ptr(out.count),
-                                          _ptr(out.mass), _ptr(out.lse), None, 0, _stream()))
+                                          _ptr(out.mass), _ptr(out.lse), _ptr(ws), _nbytes(ws), _stream()))
     return out
 
 

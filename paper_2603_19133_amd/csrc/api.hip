@@ -25,12 +25,21 @@ int check_logits(const void* logits, int dtype, int64_t ld, int64_t rows, int32_
     return PICOSPEC_OK;
 }
 
-// The workspace is optional: a call that is given none works without it.  One that is too small is an error.
+// The workspace is optional: a call that is given none works without it.  One that does not hold the target rows' segment
+// table is an error (what picospec_workspace_bytes counts besides the table is scratch that a call can do without).
 int check_workspace(int which, int dtype, int64_t rows, int32_t V, int32_t k, const void* ws, size_t ws_bytes)
 {
     if (!ws) return PICOSPEC_OK;
+    if (which == PICOSPEC_CALL_ROUND) k = 0;
     if (((uintptr_t)ws & 15u) || ws_bytes < picospec_workspace_bytes(which, dtype, (int32_t)rows, V, k)) return PICOSPEC_EWORKSPACE;
     return PICOSPEC_OK;
+}
+
+// The compressing calls need no workspace; one that holds the split kernels' scratch lets a call of few rows spread every row
+// over several workgroups.  A smaller one is accepted and left alone.
+bool split_fits(int dtype, int64_t rows, int32_t V, int32_t k, const void* ws, size_t ws_bytes)
+{
+    return ws && split_plan(dtype, rows, V, k).parts > 0 && ws_bytes >= split_scratch_bytes(dtype, rows, V, k);
 }
 
 int hip_status(hipError_t e) { return e == hipSuccess ? PICOSPEC_OK : PICOSPEC_EHIP; }
@@ -57,6 +66,12 @@ int64_t max_load_end(int which, int V, int o)
         };
         sweep(CompressGeom<BF16, false>{});
         sweep(CompressGeom<BF16, true>{});
+        const int parts = split_parts(BF16, nq + 1);                            // ... and the split rows' blocks
+        for (int j = 0; j < kSplitElems / (256 * N); ++j)
+            for (int w = 0; w < 4; ++w)
+                for (int part = 0; part < parts; ++part)
+                    for (int lane = 0; lane < 64; ++lane)
+                        end = std::max(end, buffer_lane_read_end(size, (int64_t)split_block(j, w, part, parts) * 1024, (int64_t)lane * 16));
     } else {
         using G = ResidualGeom<BF16>;
         const int n_tiles = (L + kResidualTile - 1) / kResidualTile;
@@ -82,7 +97,10 @@ int picospec_compress(const void* logits, int dtype, int64_t ld, int32_t n_rows,
     if (k < 1 || k > V || std::isnan(top_p)) return PICOSPEC_EINVAL;
     if (k > kMaxK) return PICOSPEC_EUNSUPPORTED;
     if (n_rows > 0 && (!idx || !prob || !count || !mass || !lse)) return PICOSPEC_EINVAL;
-    if (int rc = check_workspace(PICOSPEC_CALL_COMPRESS, dtype, n_rows, V, k, workspace, workspace_bytes)) return rc;
+    if ((uintptr_t)workspace & 15u) return PICOSPEC_EWORKSPACE;
+    if (split_fits(dtype, n_rows, V, k, workspace, workspace_bytes))
+        return hip_status(launch_split_compress(logits, dtype, ld, n_rows, V, temperature, k, top_p, idx, prob, count,
+                                                mass, lse, nullptr, nullptr, workspace, (hipStream_t)stream));
     return hip_status(launch_compress(logits, dtype, ld, n_rows, V, temperature, k, top_p, idx, prob, count,
                                       mass, lse, nullptr, nullptr, (hipStream_t)stream));
 }
@@ -94,6 +112,20 @@ int picospec_row_stats(const void* logits, int dtype, int64_t ld, int32_t n_rows
     if (n_rows > 0 && (!row_max || !row_sum)) return PICOSPEC_EINVAL;
     return hip_status(launch_row_stats(logits, dtype, ld, n_rows, V, temperature, row_max, row_sum, row_lse,
                                        nullptr, (hipStream_t)stream));
+}
+
+int picospec_row_stats_ws(const void* logits, int dtype, int64_t ld, int32_t n_rows, int32_t V, float temperature,
+                          float* row_max, float* row_sum, float* row_lse, void* workspace, size_t workspace_bytes, void* stream)
+{
+    if (int rc = check_logits(logits, dtype, ld, n_rows, V, temperature)) return rc;
+    if (n_rows > 0 && (!row_max || !row_sum)) return PICOSPEC_EINVAL;
+    if (int rc = check_workspace(PICOSPEC_CALL_VERIFY, dtype, n_rows, V, 0, workspace, workspace_bytes)) return rc;
+    hipStream_t s = (hipStream_t)stream;
+    if (!workspace || !split_stats_serves(n_rows, V))
+        return hip_status(launch_row_stats(logits, dtype, ld, n_rows, V, temperature, row_max, row_sum, row_lse, nullptr, s));
+    if (hipError_t e = launch_row_stats_parts(logits, dtype, ld, n_rows, V, temperature, 0, 0, nullptr, nullptr, nullptr, workspace, s))
+        return hip_status(e);
+    return hip_status(launch_row_stats_finish(logits, dtype, ld, n_rows, V, temperature, workspace, row_max, row_sum, row_lse, s));
 }
 
 int picospec_compress_rejected(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float temperature,
@@ -109,7 +141,10 @@ int picospec_compress_rejected(const void* tgt_logits, int dtype, int64_t ld, in
     if (k < 1 || k > V || std::isnan(top_p)) return PICOSPEC_EINVAL;
     if (k > kMaxK) return PICOSPEC_EUNSUPPORTED;
     if (B > 0 && (!seq_off || !n_accept || !idx || !prob || !count || !mass || !lse)) return PICOSPEC_EINVAL;
-    if (int rc = check_workspace(PICOSPEC_CALL_COMPRESS_REJECTED, dtype, B, V, k, workspace, workspace_bytes)) return rc;
+    if ((uintptr_t)workspace & 15u) return PICOSPEC_EWORKSPACE;
+    if (split_fits(dtype, B, V, k, workspace, workspace_bytes))
+        return hip_status(launch_split_compress(tgt_logits, dtype, ld, B, V, temperature, k, top_p, idx, prob, count,
+                                                mass, lse, seq_off, n_accept, workspace, (hipStream_t)stream));
     return hip_status(launch_compress(tgt_logits, dtype, ld, B, V, temperature, k, top_p, idx, prob, count,
                                       mass, lse, seq_off, n_accept, (hipStream_t)stream));
 }
@@ -164,6 +199,29 @@ int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, 
     // its two streaming kernels go out as one as well; a round that fills the chip streams faster with each
     // kernel in its own launch shape.
     const bool small_round = rows + n_draft <= kRoundSmallRows;     // (bound by its launches: two of them)
+    // (a workspace that holds the split kernels' scratch behind the segment table: few draft rows are spread over many
+    //  workgroups, and with few target rows their statistics as well)
+    const size_t table_bytes = (round_seg_table_bytes(dtype, rows, V) + 15) / 16 * 16;
+    const bool split_draft = n_draft > 0 && workspace && workspace_bytes > table_bytes &&
+                             split_fits(dtype, n_draft, V, k, (char*)workspace + table_bytes, workspace_bytes - table_bytes);
+    const bool split_stats = split_draft && split_stats_serves(rows, V);
+    if (split_draft) {
+        void* const scratch = (char*)workspace + table_bytes;
+        hipError_t e = hipSuccess;
+        if (split_stats) {
+            e = launch_split_round(draft_logits, dtype, ld_draft, n_draft, V, temperature, k, top_p, q_idx, q_prob, q_count, q_mass,
+                                   q_lse, tgt_logits, ld_tgt, (int)rows, workspace, scratch, s);
+        } else {
+            e = launch_split_compress(draft_logits, dtype, ld_draft, n_draft, V, temperature, k, top_p, q_idx, q_prob, q_count,
+                                      q_mass, q_lse, nullptr, nullptr, scratch, s);
+            if (e == hipSuccess)
+                e = launch_row_stats(tgt_logits, dtype, ld_tgt, (int)rows, V, temperature, tgt_max, tgt_sum, tgt_lse, workspace, s);
+        }
+        if (e != hipSuccess) return hip_status(e);
+        return hip_status(launch_decide(tgt_logits, dtype, ld_tgt, V, temperature, B, seq_off, draft_tok, q_idx, q_prob,
+                                        q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok,
+                                        verify_flags, out_tok, resid_mass, residual_flags, workspace, rows, false, split_stats, s));
+    }
     if (small_round) {
         if (hipError_t e = launch_round_stream(draft_logits, dtype, ld_draft, n_draft, V, temperature, k, top_p, q_idx,
                                                q_prob, q_count, q_mass, q_lse, tgt_logits, ld_tgt, (int)rows,
@@ -177,8 +235,8 @@ int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, 
             return hip_status(e);
     }
     return hip_status(launch_decide(tgt_logits, dtype, ld_tgt, V, temperature, B, seq_off, draft_tok, q_idx, q_prob,
-                                    q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok,
-                                    verify_flags, out_tok, resid_mass, residual_flags, workspace, rows, small_round, s));
+                                    q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok,
+                                    verify_flags, out_tok, resid_mass, residual_flags, workspace, rows, small_round, false, s));
 }
 
 // ---- verification and draw on records that exist
@@ -203,11 +261,13 @@ int picospec_verify_sample(const void* tgt_logits, int dtype, int64_t ld, int32_
                   !resid_mass || !residual_flags)) return PICOSPEC_EINVAL;
     if (int rc = check_workspace(PICOSPEC_CALL_VERIFY_SAMPLE, dtype, rows, V, k, workspace, workspace_bytes)) return rc;
     hipStream_t s = (hipStream_t)stream;
-    if (hipError_t e = launch_row_stats(tgt_logits, dtype, ld, (int)rows, V, temperature, tgt_max, tgt_sum, tgt_lse, workspace, s))
+    const bool split = workspace && B > 0 && split_stats_serves(rows, V);
+    if (hipError_t e = split ? launch_row_stats_parts(tgt_logits, dtype, ld, (int)rows, V, temperature, 0, 0, nullptr, nullptr, nullptr, workspace, s)
+                             : launch_row_stats(tgt_logits, dtype, ld, (int)rows, V, temperature, tgt_max, tgt_sum, tgt_lse, workspace, s))
         return hip_status(e);
     return hip_status(launch_decide(tgt_logits, dtype, ld, V, temperature, B, seq_off, draft_tok, q_idx, q_prob,
-                                    q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok,
-                                    verify_flags, out_tok, resid_mass, residual_flags, workspace, rows, false, s));
+                                    q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok,
+                                    verify_flags, out_tok, resid_mass, residual_flags, workspace, rows, false, split, s));
 }
 
 // ---- wire messages
@@ -317,15 +377,19 @@ int verify_impl(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float 
     }
     if (int rc = check_workspace(PICOSPEC_CALL_VERIFY, dtype, rows, V, k, workspace, workspace_bytes)) return rc;
     hipStream_t s = (hipStream_t)stream;
-    const hipError_t e = ranged
+    const bool split = workspace && B > 0 && split_stats_serves(rows, V);
+    const hipError_t e = split
+        ? launch_row_stats_parts(tgt_logits, dtype, ld, (int)rows, V, temperature, B, gamma_max, ranged ? seq_off : nullptr,
+                                 pos_begin, pos_end, workspace, s)
+        : ranged
         ? launch_row_stats_range(tgt_logits, dtype, ld, V, temperature, B, gamma_max, seq_off, pos_begin, pos_end,
                                  tgt_max, tgt_sum, tgt_lse, s)
         : launch_row_stats(tgt_logits, dtype, ld, (int)rows, V, temperature, tgt_max, tgt_sum, tgt_lse, workspace, s);
     if (e != hipSuccess) return hip_status(e);
     return hip_status(launch_accept(tgt_logits, dtype, ld, V, temperature, B, seq_off, draft_tok, q_idx, q_prob,
-                                    q_count, q_mass, k, renorm, q_scalar, uniforms, tgt_max, tgt_sum,
+                                    q_count, q_mass, k, renorm, q_scalar, uniforms, tgt_max, tgt_sum, tgt_lse,
                                     n_accept, p_tok, q_tok, flags, ranged ? pos_begin : nullptr,
-                                    ranged ? pos_end : nullptr, s));
+                                    ranged ? pos_end : nullptr, split ? workspace : nullptr, ranged ? 0 : rows, s));
 }
 
 }  // namespace
@@ -382,13 +446,18 @@ int picospec_sample_residual(const void* tgt_logits, int dtype, int64_t ld, int3
 
 size_t picospec_workspace_bytes(int which_call, int dtype, int32_t rows, int32_t V, int32_t k)
 {
-    (void)k;
     if (rows < 0 || V < 1 || V > kMaxV) return 0;
-    switch (which_call) {                       // the calls that can keep the target rows' segment table
+    switch (which_call) {
+        case PICOSPEC_CALL_COMPRESS: case PICOSPEC_CALL_COMPRESS_REJECTED:      // (few rows: scratch of the split kernels)
+            return split_scratch_bytes(dtype, rows, V, k);
+        // the calls that can keep the target rows' segment table
         case PICOSPEC_CALL_VERIFY: case PICOSPEC_CALL_SAMPLE_RESIDUAL: case PICOSPEC_CALL_VERIFY_SAMPLE:
             return seg_table_bytes(dtype, rows, V);
         case PICOSPEC_CALL_ROUND:               // (a small round lays the table out for its own launch shape)
-            return round_seg_table_bytes(dtype, rows, V);
+        {
+            const size_t table = round_seg_table_bytes(dtype, rows, V), split = split_scratch_bytes(dtype, rows, V, k);
+            return split ? (table + 15) / 16 * 16 + split : table;
+        }
         default:
             return 0;                           // every other kernel keeps its intermediate state in LDS
     }

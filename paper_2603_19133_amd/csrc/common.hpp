@@ -95,12 +95,25 @@ __device__ __forceinline__ float wave_sum_last(float v) {
     return v;
 }
 
+// maximum over the 64 lanes, in every lane (NaN is skipped): a DPP operand per step and one lane read at the end.  (Written by
+// hand: the compiler spends two more instructions per step on moving the operand and on quieting NaN, in phases where every
+// wave of a workgroup does this once; the two wait states in front of each step are the DPP read's.)
 __device__ __forceinline__ float wave_max(float v) {
-    v = fmaxf(v, dpp<kDppQuadXor1>(v));
-    v = fmaxf(v, dpp<kDppQuadXor2>(v));
-    v = fmaxf(v, dpp<kDppRowHalfMirror>(v));
-    v = fmaxf(v, dpp<kDppRowMirror>(v));
-    return fmaxf(fmaxf(read_lane(v, 0), read_lane(v, 16)), fmaxf(read_lane(v, 32), read_lane(v, 48)));
+    asm("s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(v));
+    return read_lane(v, kWave - 1);
 }
 
 __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int o) {
@@ -473,6 +486,74 @@ __device__ __forceinline__ void row_stats_seg_row(
         row_max[row] = M;
         row_sum[row] = (float)S;
         if (row_lse) row_lse[row] = (float)((double)M * (double)inv_T + log(S));
+    }
+}
+
+// The segment table of part `part` of a row, and nothing else (calls of few rows, whose statistics are formed from the table):
+// a workgroup of four waves, each wave SPW consecutive segments of NV * 64 vectors whose loads are all in flight at once.
+// Entry: (sum of 2^(z c - r), m), m = the segment's largest logit and r = split_ref(m, c).
+__device__ __forceinline__ bool split_ref_fused(float m, float c) { return fabsf(m * c) < __builtin_huge_valf(); }
+// m c as the sums' reference: rounded to fp32 as in the fused form of their terms; exact where that overflows (a segment of
+// nothing but masked entries of the type's lowest value), whose terms are formed as (z - m) c
+__device__ __forceinline__ double split_ref(float m, float c) { return split_ref_fused(m, c) ? (double)(m * c) : (double)m * (double)c; }
+template <bool BF16, int NV, int SPW>
+__device__ __forceinline__ void row_stats_parts(
+    const int64_t row, const int part, const void* __restrict__ logits, int64_t ld, int V, float inv_T,
+    float2* __restrict__ seg, int seg_stride)
+{
+    constexpr int N = Vec<BF16>::N, E = NV * N;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const RowView rv = row_view<BF16>(logits, ld, row, V);
+    const int nq = (rv.L + N - 1) / N, n_seg = (nq + NV * kWave - 1) / (NV * kWave);
+    const float c = 1.4426950408889634f * inv_T;
+    const int s0 = (part * 4 + wave) * SPW;
+    // (the range rule of the other row kernels, rowspan.hpp: vectors behind the row read as zero and touch no memory)
+    const __amdgpu_buffer_rsrc_t row_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)rv.base, 0, nq * 16, 0x00020000);
+    uint4 raw[SPW][NV];
+#pragma unroll
+    for (int i = 0; i < SPW; ++i)
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(row_rsrc, lane * 16, ((s0 + i) * NV + j) * (kWave * 16), 2 /* non-temporal */);
+            raw[i][j] = make_uint4(t.x, t.y, t.z, t.w);
+        }
+    float2* const seg_row = seg + row * (int64_t)seg_stride;
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+        const int s = s0 + i;
+        if (s >= n_seg) return;                       // (uniform)
+        float v[E];
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            float t[N];
+            unpack<BF16>(raw[i][j], t);
+#pragma unroll
+            for (int e = 0; e < N; ++e) v[j * N + e] = t[e];
+        }
+        if (s == 0 || s + 1 == n_seg) {               // (elements outside the row)
+#pragma unroll
+            for (int j = 0; j < NV; ++j) {
+                const unsigned vm = vec_valid_mask<BF16>(rv, (s * NV + j) * kWave + lane);
+#pragma unroll
+                for (int e = 0; e < N; ++e) v[j * N + e] = (vm >> e) & 1u ? v[j * N + e] : kNegInf;
+            }
+        }
+        float bm = v[0];
+#pragma unroll
+        for (int e = 1; e < E; ++e) bm = fmaxf(bm, v[e]);
+        const float m = wave_max(bm);
+        float acc = 0.f;
+        if (split_ref_fused(m, c)) {                  // (uniform)
+            const float nr = -(m * c);
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc += __builtin_amdgcn_exp2f(fmaf(v[e], c, nr));
+        } else if (m > kNegInf) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc += exp_stream(v[e], m, c);
+        }
+        const float t = wave_sum_last(acc);
+        if (lane == kWave - 1) seg_row[s] = make_float2(t, m);
     }
 }
 

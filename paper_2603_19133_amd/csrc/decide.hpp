@@ -20,24 +20,66 @@ __device__ __forceinline__ bool clamp_range(const int32_t* pos_begin, const int3
     return rb != begin || re != end;
 }
 
+// The statistics of one target row from its segment table in the split layout (row_stats_parts_kernel): M = the largest of
+// the segments' maxima, S = their sums brought to M in fp64.  One wave, the result in every lane.
+template <bool BF16>
+__device__ __forceinline__ void row_stats_of_table(const float2* __restrict__ seg_row, int n_seg, float c, float& M, double& S) {
+    const int lane = threadIdx.x & (kWave - 1);
+    constexpr int kAhead = 5;                        // entries per lane in flight (rows of up to 320 segments: one trip)
+    float2 e[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+        e[u] = make_float2(0.f, kNegInf);
+        if (u * kWave < n_seg && u * kWave + lane < n_seg) e[u] = seg_row[u * kWave + lane];
+    }
+    float m = kNegInf;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) m = fmaxf(m, e[u].y);
+    for (int s = kAhead * kWave + lane; s < n_seg; s += kWave) m = fmaxf(m, seg_row[s].y);
+    M = wave_max(m);
+    auto term = [&](float2 t) { return t.x > 0.f || t.x != t.x ? (double)t.x * exp2_split(split_ref(t.y, c) - (double)M * (double)c) : 0.0; };
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) if (u * kWave < n_seg) s += term(e[u]);
+    for (int q = kAhead * kWave + lane; q < n_seg; q += kWave) s += term(seg_row[q]);
+    S = wave_sum(s);
+}
+
+struct SplitStats { double S; float M; };
+// tgt_lse of the positions rows.x .. rows.y - 1 from what accept_sequence<.., TABLE> left in LDS, by `n` threads from thread
+// `first` on (a logarithm in fp64: some hundred instructions that the deciding waves need not wait for).
+__device__ __forceinline__ void write_split_lse(const SplitStats* s_stats, int2 rows, int64_t t0, float inv_T, float* tgt_lse, int first, int n) {
+    for (int i = rows.x + (int)threadIdx.x - first; tgt_lse && i < min(rows.y, kSplitStatsRows); i += n)
+        tgt_lse[t0 + i] = (float)((double)s_stats[i].M * (double)inv_T + log(s_stats[i].S));
+}
+
 // One workgroup (16 waves) per sequence, one wave per draft position.  The wave looks the drafted
 // token up in the position's sparse record with 16-byte loads (four in flight per lane), front
-// first, and stops once it is found.
+// first, and stops once it is found.  What a position needs is asked for in two trips to memory: everything that depends
+// only on the position (token, uniform, statistics, the record's first 1024 ids), then the target's logit and the
+// record's probability of the token.
 // Returns the sequence's first rejected position (in every thread; a barrier stands behind the decision).
-template <bool BF16>
+// TABLE: the rows' statistics are not known yet; their sums stand in the segment table (split layout, at most kSplitStatsRows
+// target rows in the call): they are formed here and written to tgt_max / tgt_sum / tgt_lse.  s_stats (nullable, LDS): they
+// are left there by position as well, and tgt_lse is not written: the caller does that off the critical path
+// (write_split_lse), for the positions that come back in `rows`.
+template <bool BF16, bool TABLE = false>
 __device__ __forceinline__ int accept_sequence(
     const int b, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
     const float* __restrict__ q_scalar, const float* __restrict__ uniforms,
-    const float* __restrict__ tgt_max, const float* __restrict__ tgt_sum,
+    float* __restrict__ tgt_max, float* __restrict__ tgt_sum,
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok,
-    uint32_t* __restrict__ flags, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end)
+    uint32_t* __restrict__ flags, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end,
+    float* __restrict__ tgt_lse = nullptr, const SegHeader* __restrict__ table = nullptr, int seg_vecs = 0, int stride = 0,
+    int n_rows = 0, SplitStats* s_stats = nullptr, int2* rows = nullptr)
 {
     __shared__ int s_first;
     __shared__ unsigned s_flags;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);   // uniform: so are a position's addresses
     const int d0 = seq_off[b];
     int g = seq_off[b + 1] - d0;
     unsigned fl = 0;
@@ -47,66 +89,115 @@ __device__ __forceinline__ int accept_sequence(
     if (tid == 0) { s_first = end; s_flags = 0; }
     __syncthreads();
     const int64_t t0 = (int64_t)d0 + b;
+    const float c = 1.4426950408889634f * inv_T;
     const double cd = 1.4426950408889634 * (double)inv_T;
+    auto nonfinite = [](float M, float S) { return !(fabsf(M) < __builtin_huge_valf()) || !(S > 0.f) || !(S < __builtin_huge_valf()); };
 
     // every target row of the range must have finite statistics
-    for (int t = begin + tid; t <= end; t += kThreads) {
-        float M = tgt_max[t0 + t], S = tgt_sum[t0 + t];
-        if (!(fabsf(M) < __builtin_huge_valf()) || !(S > 0.f) || !(S < __builtin_huge_valf())) fl |= 2u;
+    if constexpr (!TABLE) {
+        for (int t = begin + tid; t <= end; t += kThreads)
+            if (nonfinite(tgt_max[t0 + t], tgt_sum[t0 + t])) fl |= 2u;
     }
 
-    for (int i = begin + wave; i < end; i += kWaves) {
-        const int64_t rd = (int64_t)d0 + i, rt = t0 + i;
-        const int x = draft_tok[rd];
-        const bool bad = x < 0 || x >= V;
-        // everything the decision needs besides qhat is asked for now (every lane the same address), so that it
-        // arrives while the record is scanned instead of after it
-        const float M_t = tgt_max[rt], S_t = tgt_sum[rt], u_t = uniforms[rt];
-        const float z_t = bad ? 0.f : logit_at<BF16>(tgt_logits, ld, rt, x);
-        const float mass_d = (!q_scalar && renorm) ? q_mass[rd] : 1.f;
+    // (TABLE: the row behind the last position as well, and, by the last sequence's workgroup, rows of the call behind the
+    //  last sequence: n_draft may be larger than seq_off[B], as for a batch that an uplink message clamped)
+    int rows_end = end;                               // positions begin .. rows_end - 1
+    if constexpr (TABLE) rows_end = (b + 1 == (int)gridDim.x && n_rows > 0) ? max(end + 1, (int)(n_rows - t0)) : end + 1;
+    for (int i = begin + wave; i < rows_end; i += kWaves) {
+        const int64_t rt = t0 + i;
+        const bool decides = !TABLE || i < end;       // (the row behind the last position has statistics only)
+        const int64_t rd = (int64_t)d0 + (decides ? i : 0);
+        int x = -1, cnt = 0;
+        float u_t = 0.f, mass_d = 1.f, M_t = 0.f, S_t = 1.f;
         double qh = 0.0;
-        if (q_scalar) {
-            qh = (double)q_scalar[rd];
-        } else {
-            int cnt = q_count[rd];
+        const int32_t* ids = q_idx;
+        const bool ids_aligned = !q_scalar && ((((uintptr_t)(q_idx + rd * k)) & 15u) == 0);
+        int4 q4[4];                                   // the record's first 1024 ids (512 where it is off the 16-byte boundary)
+        if (decides) {
+            x = draft_tok[rd];
+            u_t = uniforms[rt];
+            if (!TABLE) { M_t = tgt_max[rt]; S_t = tgt_sum[rt]; }
+            if (q_scalar) {
+                qh = (double)q_scalar[rd];
+            } else {
+                cnt = q_count[rd];
+                if (renorm) mass_d = q_mass[rd];
+                ids = q_idx + rd * k;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int s = u * kWave + lane;
+                    if (ids_aligned) { if (s < (k >> 2)) q4[u] = reinterpret_cast<const int4*>(ids)[s]; }
+                    else { if (s < k) q4[u].x = ids[s]; if (s + 4 * kWave < k) q4[u].y = ids[s + 4 * kWave]; }
+                }
+            }
+        }
+        if constexpr (TABLE) {
+            const RowView rv = row_view<BF16>(tgt_logits, ld, rt, V);
+            const int nq = (rv.L + Vec<BF16>::N - 1) / Vec<BF16>::N, n_seg = (nq + seg_vecs - 1) / seg_vecs;
+            double S;
+            row_stats_of_table<BF16>(reinterpret_cast<const float2*>(table + 1) + rt * (int64_t)stride, n_seg, c, M_t, S);
+            S_t = (float)S;
+            if (lane == 0) {
+                tgt_max[rt] = M_t;
+                tgt_sum[rt] = S_t;
+                if (s_stats && i < kSplitStatsRows) s_stats[i] = SplitStats{S, M_t};
+                else if (tgt_lse) tgt_lse[rt] = (float)((double)M_t * (double)inv_T + log(S));
+                if (i <= end && nonfinite(M_t, S_t)) fl |= 2u;
+            }
+            if (!decides) continue;
+        }
+        const bool bad = x < 0 || x >= V;
+        const float z_t = bad ? 0.f : logit_at<BF16>(tgt_logits, ld, rt, x);
+        if (!q_scalar) {
             cnt = cnt < 0 ? 0 : (cnt > k ? k : cnt);
-            const int32_t* ids = q_idx + rd * k;
             int slot = -1;
             // The record is ordered by probability and the token was drawn from it, so it sits near the
             // front more often than not: the scan goes in rounds of 1024 ids and stops at the round
             // that holds it.
-            if ((((uintptr_t)ids) & 15u) == 0) {
+            if (ids_aligned) {
                 const int4* ids4 = reinterpret_cast<const int4*>(ids);
                 const int n4 = cnt >> 2;
-                for (int s0 = 0; s0 < n4; s0 += 4 * kWave) {
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int s = s0 + u * kWave + lane;
-                        if (s < n4) {
-                            const int4 q = ids4[s];
-                            if (q.x == x) slot = 4 * s;
-                            if (q.y == x) slot = 4 * s + 1;
-                            if (q.z == x) slot = 4 * s + 2;
-                            if (q.w == x) slot = 4 * s + 3;
-                        }
+                auto look = [&](int s, const int4& q) {
+                    if (s < n4) {
+                        if (q.x == x) slot = 4 * s;
+                        if (q.y == x) slot = 4 * s + 1;
+                        if (q.z == x) slot = 4 * s + 2;
+                        if (q.w == x) slot = 4 * s + 3;
                     }
-                    if (__ballot(slot >= 0)) break;
-                }
+                };
+#pragma unroll
+                for (int u = 0; u < 4; ++u) look(u * kWave + lane, q4[u]);
+                if (!__ballot(slot >= 0))
+                    for (int s0 = 4 * kWave; s0 < n4; s0 += 4 * kWave) {
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int s = s0 + u * kWave + lane;
+                            if (s < n4) look(s, ids4[s]);
+                        }
+                        if (__ballot(slot >= 0)) break;
+                    }
                 if (!__ballot(slot >= 0))
                     for (int s = 4 * n4 + lane; s < cnt; s += kWave)
                         if (ids[s] == x) slot = s;
             } else {
-                for (int s0 = 0; s0 < cnt; s0 += 8 * kWave) {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int s = s0 + u * kWave + lane;
-                        if (s < cnt && ids[s] == x) slot = s;
-                    }
-                    if (__ballot(slot >= 0)) break;
+                for (int u = 0; u < 4; ++u) {
+                    const int s = u * kWave + lane;
+                    if (s < cnt && q4[u].x == x) slot = s;
+                    if (s + 4 * kWave < cnt && q4[u].y == x) slot = s + 4 * kWave;
                 }
-            }
+                if (!__ballot(slot >= 0))
+                    for (int s0 = 8 * kWave; s0 < cnt; s0 += 8 * kWave) {
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) slot = max(slot, __shfl_xor(slot, o, kWave));
+                        for (int u = 0; u < 8; ++u) {
+                            const int s = s0 + u * kWave + lane;
+                            if (s < cnt && ids[s] == x) slot = s;
+                        }
+                        if (__ballot(slot >= 0)) break;
+                    }
+            }
+            const unsigned long long found = __ballot(slot >= 0);    // (one lane: the ids of a record are distinct)
+            slot = found ? __builtin_amdgcn_readlane(slot, 63 - __clzll((long long)found)) : -1;
             if (slot >= 0 && !bad) {
                 qh = (double)q_prob[rd * k + slot];
                 if (renorm) qh /= (double)mass_d;
@@ -128,6 +219,7 @@ __device__ __forceinline__ int accept_sequence(
         }
     }
     if (fl) atomicOr(&s_flags, fl);
+    if (rows) *rows = make_int2(begin, rows_end);
     __syncthreads();
     const int first = s_first;
     if (tid == 0) {
@@ -427,9 +519,13 @@ struct __align__(16) SegResidualShared {
     double red[2 * kWaves];
     double before;
     int seg_pick, seg_last;
+    int tok, last_tok;                         // first id behind the crossing, last id with mass
 };
 
-template <bool BF16>
+// s_stats (nullable): the target rows' statistics by position, left in LDS by accept_sequence<.., TABLE>.
+// RT: threads (whole waves from thread 0 on) that run this, at least k / 4: every wave more is one more that goes through the
+// chain of scans and barriers, four instructions' time each once a SIMD holds several (residual_seg_threads).
+template <bool BF16, int RT>
 __device__ __forceinline__ void residual_seg_sequence(
     const int b, const int j_in, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const float* __restrict__ tgt_max, const SegHeader* __restrict__ table,
@@ -437,12 +533,14 @@ __device__ __forceinline__ void residual_seg_sequence(
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
     const float* __restrict__ uniforms,
-    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ flags)
+    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ flags, const SplitStats* s_stats = nullptr)
 {
     __shared__ SegResidualShared sh;
     constexpr int N = Vec<BF16>::N;
-    constexpr int SP = kMaxK / kThreads;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    constexpr int SP = RT == kThreads ? kMaxK / kThreads : (RT == 512 ? 4 : 2);
+    constexpr int RW = RT / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int d0 = seq_off[b];
     int g = seq_off[b + 1] - d0;
     unsigned fl = 0;
@@ -461,7 +559,7 @@ __device__ __forceinline__ void residual_seg_sequence(
     // (checked below), the target row's maximum, the record's count and mass, this thread's entries of the record and
     // its entries of the segment table.
     const SegHeader hd = *table;
-    const float M = tgt_max[rt];
+    const float M = s_stats ? s_stats[min(j, kSplitStatsRows - 1)].M : tgt_max[rt];
     int cnt = 0;
     float mass_d = 1.f;
     int my_id[SP];
@@ -471,7 +569,7 @@ __device__ __forceinline__ void residual_seg_sequence(
         if (renorm) mass_d = q_mass[rd];
 #pragma unroll
         for (int z = 0; z < SP; ++z) {
-            const int sl = z * kThreads + tid;
+            const int sl = z * RT + tid;
             my_id[z] = -1;
             my_p[z] = 0.f;
             if (sl < k) { my_id[z] = q_idx[rd * k + sl]; my_p[z] = q_prob[rd * k + sl]; }
@@ -482,10 +580,10 @@ __device__ __forceinline__ void residual_seg_sequence(
         for (int z = 0; z < SP; ++z) { my_id[z] = -1; my_p[z] = 0.f; }
     }
     const bool table_ok = n_seg <= stride && n_seg <= kMaxSegTable && seg_elems <= kMaxSegElems;
-    float2 my_seg[(kMaxSegTable + kThreads - 1) / kThreads];
+    float2 my_seg[(kMaxSegTable + RT - 1) / RT];
 #pragma unroll
-    for (int u = 0; u < (kMaxSegTable + kThreads - 1) / kThreads; ++u) {
-        const int sg = u * kThreads + tid;
+    for (int u = 0; u < (kMaxSegTable + RT - 1) / RT; ++u) {
+        const int sg = u * RT + tid;
         my_seg[u] = make_float2(0.f, 0.f);
         if (table_ok && sg < n_seg) my_seg[u] = seg_row[sg];
     }
@@ -493,14 +591,14 @@ __device__ __forceinline__ void residual_seg_sequence(
     float my_z[SP];
 #pragma unroll
     for (int z = 0; z < SP; ++z) {
-        const int sl = z * kThreads + tid;
+        const int sl = z * RT + tid;
         if (!(sl < cnt && my_id[z] >= 0 && my_id[z] < V)) my_id[z] = -1;
         my_z[z] = my_id[z] >= 0 ? logit_at<BF16>(tgt_logits, ld, rt, my_id[z]) : 0.f;
     }
     const float c = 1.4426950408889634f * inv_T;
     const double cd = 1.4426950408889634 * (double)inv_T;
     const double q_scale = 1.0 / (double)mass_d;
-    if (!table_ok || hd.magic != kSegMagic || rt >= hd.rows || hd.stride != stride || hd.seg_vecs != seg_vecs) {
+    if (!table_ok || (hd.magic != kSegMagic && hd.magic != kSegMagicSplit) || rt >= hd.rows || hd.stride != stride || hd.seg_vecs != seg_vecs) {
         if (tid == 0) { out_tok[b] = 0; resid_mass[b] = 0.f; flags[b] = fl | 8u; }     // (not the table of these rows)
         return;
     }
@@ -508,11 +606,13 @@ __device__ __forceinline__ void residual_seg_sequence(
     // P of every segment, up to the common factor 1 / S
     double part = 0.0;
 #pragma unroll
-    for (int u = 0; u < (kMaxSegTable + kThreads - 1) / kThreads; ++u) {
-        const int sg = u * kThreads + tid;
+    for (int u = 0; u < (kMaxSegTable + RT - 1) / RT; ++u) {
+        const int sg = u * RT + tid;
         if (sg < n_seg) {
             const float2 e = my_seg[u];
-            const double p = e.x > 0.f ? (double)e.x * exp2_split((double)e.y - (double)M * (double)c) : 0.0;
+            // (the split layout keeps the segment's maximum, the other one its reference exponent)
+            const double up = (hd.magic == kSegMagicSplit ? split_ref(e.y, c) : (double)e.y) - (double)M * (double)c;
+            const double p = e.x > 0.f ? (double)e.x * exp2_split(up) : 0.0;
             sh.pseg[sg] = p;
             sh.tfix[sg] = 0ull;
             part += p;
@@ -524,7 +624,7 @@ __device__ __forceinline__ void residual_seg_sequence(
     __syncthreads();
     double S = 0.0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) S += sh.red[w];
+    for (int w = 0; w < RW; ++w) S += sh.red[w];
     const double invS = 1.0 / S;
     __syncthreads();
 
@@ -544,7 +644,7 @@ __device__ __forceinline__ void residual_seg_sequence(
     __syncthreads();
 
     // residual mass of every segment, the total, and the segment in which the cumulative residual crosses u R
-    const int per = (n_seg + kThreads - 1) / kThreads;        // contiguous segments per thread
+    const int per = (n_seg + RT - 1) / RT;        // contiguous segments per thread
     const int s0 = min(n_seg, tid * per), s1 = min(n_seg, s0 + per);
     double R = 0.0, mine = 0.0;
     for (int attempt = 0; attempt < 2; ++attempt) {
@@ -560,7 +660,7 @@ __device__ __forceinline__ void residual_seg_sequence(
         __syncthreads();
         R = 0.0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) R += sh.red[w];
+        for (int w = 0; w < RW; ++w) R += sh.red[w];
         if (R > 0.0 || !has_q) break;
         fl |= 4u;                                              // P == qhat numerically: draw from P itself
         has_q = false;
@@ -573,11 +673,11 @@ __device__ __forceinline__ void residual_seg_sequence(
     const double target = (double)uniforms[(int64_t)d0 + b + g] * R;
     const double incl = wave_scan_incl(mine);
     __syncthreads();
-    if (lane == kWave - 1) sh.red[kWaves + wave] = incl;
+    if (lane == kWave - 1) sh.red[RW + wave] = incl;
     __syncthreads();
     double cum = incl - mine;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) if (w < wave) cum += sh.red[kWaves + w];
+    for (int w = 0; w < RW; ++w) if (w < wave) cum += sh.red[RW + w];
     int my_pick = 0x7FFFFFFF, my_last = -1;
     for (int s = s0; s < s1; ++s) {
         const double v = seg_mass(s);
@@ -588,13 +688,20 @@ __device__ __forceinline__ void residual_seg_sequence(
     if (my_pick != 0x7FFFFFFF) atomicMin(&sh.seg_pick, my_pick);
     if (my_last >= 0) atomicMax(&sh.seg_last, my_last);
     __syncthreads();
-    int pick = sh.seg_pick;
+    int pick = __builtin_amdgcn_readfirstlane(sh.seg_pick);
     const bool crossed = pick != 0x7FFFFFFF;
-    if (!crossed) pick = max(sh.seg_last, 0);                 // rounding: last segment with mass
+    if (!crossed) pick = max(__builtin_amdgcn_readfirstlane(sh.seg_last), 0);     // rounding: last segment with mass
     if (crossed && my_pick == pick) sh.before = cum;          // exactly one thread owns the chosen segment
     const int seg_vec = pick * seg_vecs;                      // first vector of the segment
     const int seg_lo = seg_vec * N - rv.o;                    // id of its first element
-    for (int i = tid; i < seg_elems; i += kThreads) sh.qimg[i] = 0.f;
+    // Wave w reads the segment's vectors w * 64 + lane (a segment has at most four times 64 of them); the loads are on their
+    // way while the record's entries are laid out.
+    static_assert(RW >= 4 && kMaxSegElems <= 4 * kWave * 8, "one wave per 64 vectors of the segment");
+    const bool reads = wave * kWave < seg_vecs;               // (uniform)
+    const int ql = wave * kWave + lane, q = seg_vec + ql;
+    uint4 raw = make_uint4(0, 0, 0, 0);
+    if (reads && vec_in_row<BF16>(rv, q)) raw = load16_stream(rv.base + q);
+    for (int i = tid; i < seg_elems; i += RT) sh.qimg[i] = 0.f;
     __syncthreads();
     if (has_q) {
 #pragma unroll
@@ -603,61 +710,56 @@ __device__ __forceinline__ void residual_seg_sequence(
             if (my_id[z] >= 0 && off >= 0 && off < seg_elems) sh.qimg[off] = my_q[z];
         }
     }
+    if (tid == 0) { sh.tok = 0x7FFFFFFF; sh.last_tok = -1; }
     __syncthreads();
 
-    // read that one segment and name the token (wave 0): ids ascend with (jv, lane, element)
-    if (wave == 0) {
+    // the token: ids ascend with (wave, lane, element)
+    double r[N], sum = 0.0, inc = 0.0;
+    if (reads) {
         const double kappa = -(double)M * cd - log2(S);
+        float v[N];
+        unpack<BF16>(raw, v);
+        const unsigned vm = vec_valid_mask<BF16>(rv, q);
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            const double d = exp2_split((double)v[e] * cd + kappa) - (double)sh.qimg[ql * N + e];
+            r[e] = ((vm >> e) & 1u) && d > 0.0 ? d : 0.0;
+            sum += r[e];
+        }
+        inc = wave_scan_incl(sum);
+        if (lane == kWave - 1) sh.red[wave] = inc;
+    }
+    __syncthreads();
+    if (reads) {
         double base = sh.before;
-        int tok = -1, last_tok = -1;
-        for (int jv = 0; jv * kWave < seg_vecs; ++jv) {
-            const int ql = jv * kWave + lane, q = seg_vec + ql;
-            uint4 raw = make_uint4(0, 0, 0, 0);
-            if (vec_in_row<BF16>(rv, q)) raw = load16_stream(rv.base + q);
-            float v[N];
-            unpack<BF16>(raw, v);
-            const unsigned vm = vec_valid_mask<BF16>(rv, q);
-            double r[N], sum = 0.0;
+        for (int w = 0; w < wave; ++w) base += sh.red[w];
+        const unsigned long long hit = crossed ? __ballot(base + inc > target) : 0ull;
+        if (hit && lane == __ffsll((long long)hit) - 1) {
+            double cu = base + inc - sum;
+            int t = -1;
 #pragma unroll
             for (int e = 0; e < N; ++e) {
-                const double d = exp2_split((double)v[e] * cd + kappa) - (double)sh.qimg[ql * N + e];
-                r[e] = ((vm >> e) & 1u) && d > 0.0 ? d : 0.0;
-                sum += r[e];
+                cu += r[e];
+                if (t < 0 && cu > target) t = seg_lo + ql * N + e;
             }
-            const double inc = wave_scan_incl(sum);
-            const unsigned long long hit = (crossed && tok < 0) ? __ballot(base + inc > target) : 0ull;
-            if (hit) {
-                const int owner = __ffsll((long long)hit) - 1;
-                int t = -1;
-                if (lane == owner) {
-                    double cu = base + inc - sum;
-#pragma unroll
-                    for (int e = 0; e < N; ++e) {
-                        cu += r[e];
-                        if (t < 0 && cu > target) t = seg_lo + ql * N + e;
-                    }
-                    if (t < 0) t = seg_lo + ql * N + N - 1;
-                }
-                tok = __shfl(t, owner, kWave);
-            }
-            const unsigned long long any = __ballot(sum > 0.0);   // rounding fallback: the last id of the segment with mass
-            if (any) {
-                const int owner = 63 - __clzll((long long)any);
-                int t = -1;
-                if (lane == owner) {
-#pragma unroll
-                    for (int e = 0; e < N; ++e) if (r[e] > 0.0) t = seg_lo + ql * N + e;
-                }
-                last_tok = __shfl(t, owner, kWave);
-            }
-            base += __shfl(inc, kWave - 1, kWave);
+            if (t < 0) t = seg_lo + ql * N + N - 1;
+            atomicMin(&sh.tok, t);
         }
-        if (tok < 0) tok = last_tok >= 0 ? last_tok : min(max(seg_lo, 0), V - 1);
-        if (lane == 0) {
-            out_tok[b] = tok;
-            resid_mass[b] = (fl & 4u) ? 0.f : (float)R;
-            flags[b] = fl;
+        const unsigned long long any = __ballot(sum > 0.0);   // rounding fallback: the last id of the segment with mass
+        if (any && lane == 63 - __clzll((long long)any)) {
+            int t = -1;
+#pragma unroll
+            for (int e = 0; e < N; ++e) if (r[e] > 0.0) t = seg_lo + ql * N + e;
+            atomicMax(&sh.last_tok, t);
         }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int tok = sh.tok;
+        if (tok == 0x7FFFFFFF) tok = sh.last_tok >= 0 ? sh.last_tok : min(max(seg_lo, 0), V - 1);
+        out_tok[b] = tok;
+        resid_mass[b] = (fl & 4u) ? 0.f : (float)R;
+        flags[b] = fl;
     }
 }
 

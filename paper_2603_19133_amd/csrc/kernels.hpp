@@ -39,6 +39,37 @@ __host__ __device__ inline int optimistic_rank(int k, int V, int m, int cap, flo
     return 0;
 }
 
+// The compression of few rows over many workgroups (split.hip): how a row is split, how many of its elements a workgroup
+// hands on (its `rank` largest and what shares the threshold's bin), and how many slots a wave's list has.
+// parts = 0: the call is not split.  Lines of the rule:
+//   * rows: up to kSplitMaxRows rows; beyond that one workgroup per row fills the chip by itself.
+//   * the margin of the rank is optimistic_rank's (4.5 standard deviations of the share of the k largest that falls to one
+//     workgroup); its lists together must fit the candidate buffer of the finishing kernel with room to spare.
+//   * a list holds the rank, a crowded pivot bin and some slack.
+constexpr int kSplitMaxRows = 256;
+constexpr int kSplitMinV = 16384;                // (two workgroups per row)
+constexpr int kSplitNarrowRank = 240;            // ranks for which 256 elements above the histogram's lower end suffice
+constexpr int kSplitMaxParts = 64;               // lists per row (one per lane of a finishing wave): rows of up to half a million elements
+struct SplitPlan { int parts, rank, cap; };
+inline SplitPlan split_plan(int dtype, int64_t rows, int V, int k) {
+    const SplitPlan none{0, 0, 0};
+    if (rows < 1 || rows > kSplitMaxRows || V < kSplitMinV || k < 1 || k > kMaxK) return none;
+    const int esz = dtype == 1 ? 2 : 4;
+    const int nq = (int)(((int64_t)V * esz + 15) / 16) + 1;                  // (a row off the 16-byte boundary spans one vector more)
+    const int parts = split_parts(dtype == 1, nq);
+    if (parts < 2 || parts > kSplitMaxParts) return none;
+    const float f = 1.f / (float)parts, lam = (float)k * f;
+    const int rank = (int)ceilf(lam + 4.5f * sqrtf(lam * (1.f - f)) + 6.75f);
+    if (rank > V / parts / 2 || (float)parts * (float)rank > 7000.f) return none;
+    const float m = (float)(rank + (rank / 8 > 16 ? rank / 8 : 16));         // with a crowded pivot bin
+    const int cap = ((int)ceilf(m + 2.f * sqrtf(m)) + 7) / 8 * 8;
+    return SplitPlan{parts, rank, cap};
+}
+inline size_t split_scratch_bytes(int dtype, int64_t rows, int V, int k) {
+    const SplitPlan p = split_plan(dtype, rows, V, k);
+    return (size_t)rows * (size_t)p.parts * (32 + 8 * (size_t)p.cap);
+}
+
 // Kernels whose dynamic LDS exceeds the 64 KB default need their limit raised once per device and kernel.
 // `done` is the caller's per-device record for that kernel; the current device's ordinal comes back in `dev`.
 // The record is atomic and the attribute call idempotent: two threads that meet here on a kernel's first use
@@ -62,6 +93,17 @@ inline hipError_t raise_lds_limit_once(const void* kernel, size_t bytes, DeviceF
 hipError_t launch_compress(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
                            int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass,
                            float* lse, const int32_t* seq_off, const int32_t* n_accept, hipStream_t stream);
+
+// the same in two launches that spread every row over several workgroups (split_plan(...).parts > 0); scratch holds
+// split_scratch_bytes(...) bytes on a 16-byte boundary
+hipError_t launch_split_compress(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
+                                 int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass,
+                                 float* lse, const int32_t* seq_off, const int32_t* n_accept, void* scratch, hipStream_t stream);
+
+// ... and besides it, in the first of the two launches, the target rows' segment table in the split layout
+hipError_t launch_split_round(const void* draft_logits, int dtype, int64_t ld_d, int n_draft, int V, float temperature,
+                              int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass, float* lse,
+                              const void* tgt_logits, int64_t ld_t, int n_target, void* seg_table, void* scratch, hipStream_t stream);
 
 // the draft rows' compression and the target rows' statistics in one launch (small rounds)
 hipError_t launch_round_stream(const void* draft_logits, int dtype, int64_t ld_d, int n_draft, int V, float temperature,
@@ -107,7 +149,18 @@ inline StatsShape round_stats_shape(int dtype, int V) {
 }
 // bytes of the segment table of `rows` rows (16-byte header in front: see SegHeader)
 struct SegHeader { int32_t magic, seg_vecs, stride, rows; };
-constexpr int32_t kSegMagic = 0x53454731;
+constexpr int32_t kSegMagic = 0x53454731;        // entries (sum of 2^(z c - r), r)
+constexpr int32_t kSegMagicSplit = 0x53454732;   // split layout: entries (sum of 2^(z c - r), m), m = the segment's largest logit, r = m c (split_ref)
+// Calls of few target rows spread every row's statistics over many workgroups: each wave leaves the entries of a few
+// segments, nothing else, and the kernel that needs the statistics forms them from the row's table.  A row's workgroup is
+// bound by its own vector ALUs (90 rows of 151,936 fp32: 17.8 us at one row per CU); up to one row per CU leaves room for that.
+constexpr int kSplitStatsRows = 256;
+constexpr int kStatsSpwF32 = 2, kStatsSpwBF16 = 4;   // segments per wave: eight loads in flight per lane
+inline int stats_parts(int dtype, int stride) {      // workgroups of four waves per row
+    const int per = 4 * (dtype == 1 ? kStatsSpwBF16 : kStatsSpwF32);
+    return (stride + per - 1) / per;
+}
+inline bool split_stats_serves(int64_t rows, int V) { return rows >= 1 && rows <= kSplitStatsRows && V >= kSplitMinV; }
 inline size_t seg_table_bytes(int dtype, int64_t rows, int V) {
     return sizeof(SegHeader) + (size_t)rows * (size_t)stats_shape(dtype, rows, V).stride * 8;
 }
@@ -121,6 +174,14 @@ inline size_t round_seg_table_bytes(int dtype, int64_t rows, int V) {
 hipError_t launch_row_stats(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
                             float* row_max, float* row_sum, float* row_lse, void* seg_table, hipStream_t stream);
 
+// the table of the rows alone, in the split layout (split_stats_serves): seq_off == nullptr: rows 0 .. n_rows - 1; else the
+// target rows pos_begin[b]..pos_end[b] of every sequence (nullable: 0 / gamma_b)
+hipError_t launch_row_stats_parts(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature, int B, int gamma_max, const int32_t* seq_off, const int32_t* pos_begin, const int32_t* pos_end,
+                                  void* seg_table, hipStream_t stream);
+// ... and the statistics from it
+hipError_t launch_row_stats_finish(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
+                                   const void* seg_table, float* row_max, float* row_sum, float* row_lse, hipStream_t stream);
+
 // the same for the target rows pos_begin[b]..pos_end[b] of every sequence only (nullable: 0 / gamma_b)
 hipError_t launch_row_stats_range(const void* logits, int dtype, int64_t ld, int V, float temperature, int B,
                                   int gamma_max, const int32_t* seq_off, const int32_t* pos_begin,
@@ -131,9 +192,14 @@ hipError_t launch_accept(const void* tgt_logits, int dtype, int64_t ld, int V, f
                          int B, const int32_t* seq_off, const int32_t* draft_tok,
                          const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
                          int k, int renorm, const float* q_scalar, const float* uniforms,
-                         const float* tgt_max, const float* tgt_sum,
+                         float* tgt_max, float* tgt_sum, float* tgt_lse,
                          int32_t* n_accept, float* p_tok, float* q_tok, uint32_t* flags,
-                         const int32_t* pos_begin, const int32_t* pos_end, hipStream_t stream);
+                         const int32_t* pos_begin, const int32_t* pos_end,
+                         const void* split_table, int64_t n_rows, hipStream_t stream);
+
+// threads of the draw from the segment table: a thread holds two record entries of records of up to 512 entries, four of
+// longer ones
+inline int residual_seg_threads(int k) { return k <= 512 ? 256 : k <= 2048 ? 512 : 1024; }
 
 hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
                            int B, const int32_t* seq_off, const int32_t* n_accept,
@@ -142,16 +208,18 @@ hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V,
                            int k, int renorm, const float* uniforms,
                            int32_t* out_tok, float* resid_mass, uint32_t* flags, const void* seg_table, int64_t n_rows, hipStream_t stream);
 
-// acceptance and residual draw of every sequence in one launch; seg_table (nullable, also in launch_residual): the
+// (launch_accept: split_table non-null: the rows' statistics are formed from that table, tgt_max / tgt_sum / tgt_lse written)
+// acceptance and residual draw of every sequence in one launch; split_table: the table holds the split layout, and the rows'
+// statistics are formed from it and written; seg_table (nullable, also in launch_residual): the
 // table of the n_rows target rows from launch_row_stats (small_round_table: from launch_round_stream, whose layout
 // differs), with which the draw does not stream its row again
 hipError_t launch_decide(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
                          int B, const int32_t* seq_off, const int32_t* draft_tok,
                          const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
-                         int k, int renorm, const float* uniforms, const float* tgt_max, const float* tgt_sum,
+                         int k, int renorm, const float* uniforms, float* tgt_max, float* tgt_sum, float* tgt_lse,
                          int32_t* n_accept, float* p_tok, float* q_tok, uint32_t* flags,
                          int32_t* out_tok, float* resid_mass, uint32_t* res_flags, const void* seg_table, int64_t n_rows,
-                         bool small_round_table, hipStream_t stream);
+                         bool small_round_table, bool split_table, hipStream_t stream);
 
 hipError_t launch_resample_sparse(const void* draft_logits, int dtype, int64_t ld, int V, float temperature,
                                   int B, const int32_t* seq_off, const int32_t* n_accept,

@@ -38,7 +38,7 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
-    const float* __restrict__ uniforms, const float* __restrict__ tgt_max, const float* __restrict__ tgt_sum,
+    const float* __restrict__ uniforms, float* __restrict__ tgt_max, float* __restrict__ tgt_sum,
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
     int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags)
 {
@@ -50,8 +50,8 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(
 }
 
 // The same two kernels with the target rows' segment table at hand (no second pass over a row).
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void residual_seg_kernel(
+template <bool BF16, int RT>
+__global__ __launch_bounds__(RT) void residual_seg_kernel(
     const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept,
     const float* __restrict__ tgt_max, const SegHeader* __restrict__ table, int seg_vecs, int stride,
@@ -60,26 +60,41 @@ __global__ __launch_bounds__(kThreads) void residual_seg_kernel(
     const float* __restrict__ uniforms,
     int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ flags)
 {
-    residual_seg_sequence<BF16>(blockIdx.x, n_accept[blockIdx.x], tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
+    residual_seg_sequence<BF16, RT>(blockIdx.x, n_accept[blockIdx.x], tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
                                 q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags);
 }
 
-template <bool BF16>
+// SPLIT: the table stands in the split layout, and the rows' statistics are formed here.
+template <bool BF16, bool SPLIT, int RT>
 __global__ __launch_bounds__(kThreads) void decide_seg_kernel(
     const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
-    const float* __restrict__ uniforms, const float* __restrict__ tgt_max, const float* __restrict__ tgt_sum,
+    const float* __restrict__ uniforms, float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
     const SegHeader* __restrict__ table, int seg_vecs, int stride,
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
-    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags)
+    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags, int n_rows)
 {
-    const int first = accept_sequence<BF16>(blockIdx.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
-                                            q_count, q_mass, k, renorm, nullptr, uniforms, tgt_max, tgt_sum,
-                                            n_accept, p_tok, q_tok, flags, nullptr, nullptr);
-    residual_seg_sequence<BF16>(blockIdx.x, first, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
-                                q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, res_flags);
+    __shared__ SplitStats s_stats[SPLIT ? kSplitStatsRows : 1];
+    int2 rows = make_int2(0, 0);
+    const int first = accept_sequence<BF16, SPLIT>(blockIdx.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
+                                                   q_count, q_mass, k, renorm, nullptr, uniforms, tgt_max, tgt_sum,
+                                                   n_accept, p_tok, q_tok, flags, nullptr, nullptr,
+                                                   tgt_lse, table, seg_vecs, stride, n_rows, SPLIT ? s_stats : nullptr, &rows);
+    const int64_t t0 = (int64_t)seq_off[blockIdx.x] + blockIdx.x;
+    // the waves that the draw has no use for write the log-sum-exps and end here (a barrier waits for those that are left)
+    if (RT < kThreads) {
+        if (__builtin_amdgcn_readfirstlane(threadIdx.x / kWave) >= RT / kWave) {
+            if (SPLIT) write_split_lse(s_stats, rows, t0, inv_T, tgt_lse, RT, kThreads - RT);
+            return;
+        }
+    } else if (SPLIT) {
+        write_split_lse(s_stats, rows, t0, inv_T, tgt_lse, 0, kThreads);
+    }
+    residual_seg_sequence<BF16, RT>(blockIdx.x, first, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
+                                    q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, res_flags,
+                                    SPLIT ? s_stats : nullptr);
 }
 
 }  // namespace
@@ -95,8 +110,13 @@ hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V,
         if (B == 0) return hipSuccess;
         const float it = 1.0f / temperature;
         const StatsShape sh = stats_shape(dtype, n_rows, V);
-        if (dtype == 1) hipLaunchKernelGGL(residual_seg_kernel<true>, dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, it, seq_off, n_accept, tgt_max, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags);
-        else            hipLaunchKernelGGL(residual_seg_kernel<false>, dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, it, seq_off, n_accept, tgt_max, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags);
+#define PICOSPEC_RESIDUAL(BF, RT) \
+        hipLaunchKernelGGL((residual_seg_kernel<BF, RT>), dim3(B), dim3(RT), 0, stream, tgt_logits, ld, V, it, seq_off, n_accept, tgt_max, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags)
+#define PICOSPEC_RESIDUAL_RT(BF) \
+        switch (residual_seg_threads(k)) { case 256: PICOSPEC_RESIDUAL(BF, 256); break; case 512: PICOSPEC_RESIDUAL(BF, 512); break; default: PICOSPEC_RESIDUAL(BF, 1024); }
+        if (dtype == 1) { PICOSPEC_RESIDUAL_RT(true) } else { PICOSPEC_RESIDUAL_RT(false) }
+#undef PICOSPEC_RESIDUAL_RT
+#undef PICOSPEC_RESIDUAL
         return hipGetLastError();
     }
     static DeviceFlags limit_raised[2] = {};
@@ -119,17 +139,23 @@ hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V,
 hipError_t launch_decide(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
                          int B, const int32_t* seq_off, const int32_t* draft_tok,
                          const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
-                         int k, int renorm, const float* uniforms, const float* tgt_max, const float* tgt_sum,
+                         int k, int renorm, const float* uniforms, float* tgt_max, float* tgt_sum, float* tgt_lse,
                          int32_t* n_accept, float* p_tok, float* q_tok, uint32_t* flags,
                          int32_t* out_tok, float* resid_mass, uint32_t* res_flags, const void* seg_table, int64_t n_rows,
-                         bool small_round_table, hipStream_t stream)
+                         bool small_round_table, bool split_table, hipStream_t stream)
 {
     if (seg_table) {
         if (B == 0) return hipSuccess;
         const float it = 1.0f / temperature;
         const StatsShape sh = small_round_table ? round_stats_shape(dtype, V) : stats_shape(dtype, n_rows, V);
-        if (dtype == 1) hipLaunchKernelGGL(decide_seg_kernel<true>, dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, it, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags);
-        else            hipLaunchKernelGGL(decide_seg_kernel<false>, dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, it, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags);
+#define PICOSPEC_DECIDE(BF, SP, RT) \
+        hipLaunchKernelGGL((decide_seg_kernel<BF, SP, RT>), dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, it, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags, (int)n_rows)
+#define PICOSPEC_DECIDE_RT(BF, SP) \
+        switch (residual_seg_threads(k)) { case 256: PICOSPEC_DECIDE(BF, SP, 256); break; case 512: PICOSPEC_DECIDE(BF, SP, 512); break; default: PICOSPEC_DECIDE(BF, SP, 1024); }
+        if (split_table) { if (dtype == 1) { PICOSPEC_DECIDE_RT(true, true) } else { PICOSPEC_DECIDE_RT(false, true) } }
+        else             { if (dtype == 1) { PICOSPEC_DECIDE_RT(true, false) } else { PICOSPEC_DECIDE_RT(false, false) } }
+#undef PICOSPEC_DECIDE_RT
+#undef PICOSPEC_DECIDE
         return hipGetLastError();
     }
     static DeviceFlags limit_raised[2] = {};

@@ -52,6 +52,17 @@ struct CompressGeom {
     __host__ __device__ static int group_first(int sub, int j) { return sub * SUB_VECS + j * kCompressThreads; }
 };
 
+// Rows split over several workgroups (split.hip): a workgroup of four waves holds kSplitElems elements, as 1 KB
+// blocks (64 vectors, one per lane) taken evenly from the whole row.
+constexpr int kSplitElems = 8192;
+// block j of wave `wave` of workgroup `part` of P
+__host__ __device__ inline int split_block(int j, int wave, int part, int P) { return (j * 4 + wave) * P + part; }
+// workgroups of a row of `nq` vectors
+__host__ __device__ inline int split_parts(bool bf16, int nq) {
+    const int n_blocks = (nq + 63) / 64, per = kSplitElems / (64 * (bf16 ? 8 : 4));
+    return (n_blocks + per - 1) / per;
+}
+
 template <bool BF16>
 struct ResidualGeom {
     static constexpr int N = BF16 ? 8 : 4;

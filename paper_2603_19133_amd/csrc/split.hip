@@ -1,0 +1,400 @@
+// Sparse Top-K compression of few rows (paper Section 3.3, Eq. 4): a call that leaves most of the chip idle spreads every
+// row over many small workgroups and finishes it in a second launch.
+//
+// One workgroup per row (compress_row.hpp) is a chain of phases on one CU: 25 us for a bf16 row of 128,256 whatever k is, of
+// which 13 us are the streaming of the row by eight waves and the rest serial phases that issue one instruction per wave
+// every eight to ten cycles with two waves on a SIMD.  Here
+//   * split_select_kernel: P = V / 8192 workgroups of four waves per row.  A workgroup takes every P-th block of 1 KB of the
+//     row (so that each sees the whole row evenly: logits trend with the vocabulary id) and holds its 8192 elements in
+//     registers: one trip to memory, nothing read twice, no sample.  A histogram over the upper part of its values finds a
+//     threshold with at least `rank` of its elements above it; rank is optimistic_rank's bound for a share of 1 / P of the
+//     row's k largest, so the elements above it hold the row's top k but for a chance of some 1e-6.  The workgroup writes
+//     them to a list of its own in the scratch, and its share of the statistics in front of it.
+//   * split_finish_kernel: one workgroup per row gathers the lists (about k plus the ranks' margins), orders them and writes
+//     the record with the code of the unsplit kernels.  The answer is exact iff the k-th value lies above every workgroup's
+//     threshold, which is tested; a row that fails it (or whose lists overflow) is compressed from the start by the general
+//     code in the same workgroup.
+#include "compress_row.hpp"
+
+namespace picospec {
+
+namespace {
+
+constexpr int kSplitThreads = 256, kSplitWaves = kSplitThreads / kWave;
+constexpr int kSplitBins = 512;                // histogram of a workgroup's values: eight bins per lane in the pivot scan
+constexpr int kImageVecs = 4;                  // vectors per lane that pass through LDS at a time
+template <bool BF16> struct SplitGeom {
+    using elem_t = typename std::conditional<BF16, uint16_t, uint32_t>::type;
+    static constexpr int N = Vec<BF16>::N;
+    static constexpr int NV = kSplitElems / (kSplitThreads * N);           // vectors per lane
+    static constexpr int E = NV * N;                                  // elements per lane
+    static_assert(NV % kImageVecs == 0 && E == 32, "one bit of a word per element");
+};
+
+// What a workgroup leaves of its share of the row; its list of (value, id) pairs stands in an array of its own.
+struct __align__(16) SplitHead {
+    float mx, tau, r;                          // largest value; threshold (every element above it is in the list); reference exponent
+    int count;                                 // entries of the list (more than the list holds: the row is given up)
+    double s;                                  // sum of 2^(z c - r) over the share
+    double unused;
+};
+static_assert(sizeof(SplitHead) == 32, "two 16-byte loads");
+
+// Workgroup `part` of the P workgroups of row `row` of the call.
+template <bool BF16>
+__device__ __forceinline__ void split_select(
+    const int64_t row, const int part, const int P,
+    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int rank, int cap, int narrow,
+    SplitHead* __restrict__ heads, uint2* __restrict__ lists,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
+{
+    using G = SplitGeom<BF16>;
+    constexpr int N = G::N, NV = G::NV, E = G::E;
+    __shared__ __align__(16) unsigned hist[kSplitBins + kWave];       // (behind the bins: a slot per lane for what lies below them)
+    __shared__ __align__(16) unsigned image[4 * kImageVecs * kSplitThreads];
+    __shared__ float red[2 * kSplitWaves];
+    __shared__ double wave_s[kSplitWaves];
+    __shared__ int wave_held[kSplitWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    int64_t in_row = row;
+    if (seq_off) {
+        const int d0 = seq_off[row], g = max(seq_off[row + 1] - d0, 0);
+        in_row = (int64_t)d0 + row + min(max(n_accept[row], 0), g);
+    }
+    const RowView rv = row_view<BF16>(logits, ld, in_row, V);
+    const int nq = (rv.L + N - 1) / N;
+    const int n_blocks = (nq + kWave - 1) / kWave;
+    const float c = 1.4426950408889634f * inv_T;
+    // (the same range rule as the other row kernels, rowspan.hpp: vectors behind the row read as zero and touch no memory)
+    const __amdgpu_buffer_rsrc_t row_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)rv.base, 0, nq * 16, 0x00020000);
+    uint4 raw[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(row_rsrc, lane * 16, split_block(j, wave, part, P) * (kWave * 16), 2 /* non-temporal */);
+        raw[j] = make_uint4(t.x, t.y, t.z, t.w);
+    }
+    *reinterpret_cast<uint2*>(&hist[2 * tid]) = make_uint2(0u, 0u);
+    static_assert(kSplitBins == 2 * kSplitThreads, "one store clears the histogram");
+    float v[E];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        float t[N];
+        unpack<BF16>(raw[j], t);
+#pragma unroll
+        for (int e = 0; e < N; ++e) v[j * N + e] = t[e];
+    }
+    // elements outside the row (in front of its first, behind its last) count as masked ones: -inf.  Only the row's first and
+    // last blocks hold any.
+    if ((part == 0 && wave == 0) || split_block(NV - 1, wave, part, P) >= n_blocks - 1) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const unsigned vm = vec_valid_mask<BF16>(rv, split_block(j, wave, part, P) * kWave + lane);
+#pragma unroll
+            for (int e = 0; e < N; ++e) v[j * N + e] = (vm >> e) & 1u ? v[j * N + e] : kNegInf;
+        }
+    }
+    float bm = kNegInf;
+#pragma unroll
+    for (int e = 0; e < E; ++e) bm = fmaxf(bm, v[e]);
+    // Lower end of the histogram: at least `rank` elements must lie at or above it.  narrow: the smallest of the lanes' largest
+    // values will do (256 elements at or above it); else the smallest value above -inf.
+    float bl = bm;
+    if (!narrow) {
+        bl = __builtin_huge_valf();
+#pragma unroll
+        for (int e = 0; e < E; ++e) bl = fminf(bl, v[e] > kNegInf ? v[e] : __builtin_huge_valf());
+    }
+    if (!(bl > kNegInf)) bl = __builtin_huge_valf();
+    const float wm = wave_max(bm), wl = -wave_max(-bl);
+    if (lane == 0) { red[wave] = wm; red[kSplitWaves + wave] = wl; }
+    __syncthreads();
+    float hi = red[0], lo = red[kSplitWaves];
+#pragma unroll
+    for (int w = 1; w < kSplitWaves; ++w) { hi = fmaxf(hi, red[w]); lo = fminf(lo, red[kSplitWaves + w]); }
+    const float mx = hi;
+    // the share's softmax sum, against an integer reference exponent
+    const float ref = hi > kNegInf ? ceilf(hi * c) : 0.f;
+    float acc = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc += __builtin_amdgcn_exp2f(fmaf(v[e], c, -ref));   // (masked: 2^-inf = 0)
+
+    // ---- threshold: a linear histogram of [lo, hi], refined inside the pivot bin while that is crowded (outliers)
+    float tau = kNegInf;
+    const bool finite = hi > kNegInf && hi < __builtin_huge_valf();
+    if (finite) {
+        int need = rank;
+        for (int pass = 0; pass < 3; ++pass) {
+            const float width = (hi - lo) * (1.0f / (float)kSplitBins);
+            const float scale = __builtin_amdgcn_rcpf(width);
+            if (!(hi > lo) || !(scale < __builtin_huge_valf()) || !(width < __builtin_huge_valf())) { if (hi >= lo) tau = float_below(lo); break; }   // one value (or too close to tell apart)
+            if (pass > 0) {
+                __syncthreads();
+                *reinterpret_cast<uint2*>(&hist[2 * tid]) = make_uint2(0u, 0u);
+                __syncthreads();
+            }
+            const float top = hi * scale;
+            // bin 0 holds the largest values; what lies below lo goes to the lane's own slot behind the bins
+            auto bin_of = [&](float x) {
+                unsigned b;
+                asm("v_cvt_u32_f32 %0, %1" : "=v"(b) : "v"(fmaf(x, -scale, top)));     // (saturates: below 0 and NaN 0, large 2^32 - 1)
+                return b;
+            };
+            if (pass == 0) {                     // (nothing lies above hi)
+#pragma unroll
+                for (int e = 0; e < E; ++e) atomicAdd(&hist[min(bin_of(v[e]), (unsigned)(kSplitBins + lane))], 1u);
+            } else {
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    if (v[e] >= lo && v[e] <= hi) atomicAdd(&hist[min(bin_of(v[e]), (unsigned)(kSplitBins - 1))], 1u);
+            }
+            __syncthreads();
+            // every wave scans the bins for itself: eight consecutive ones per lane
+            const uint4 h0 = *reinterpret_cast<const uint4*>(&hist[8 * lane]), h1 = *reinterpret_cast<const uint4*>(&hist[8 * lane + 4]);
+            const int h[8] = {(int)h0.x, (int)h0.y, (int)h0.z, (int)h0.w, (int)h1.x, (int)h1.y, (int)h1.z, (int)h1.w};
+            const int loc = ((h[0] + h[1]) + (h[2] + h[3])) + ((h[4] + h[5]) + (h[6] + h[7]));
+            const int incl = wave_scan_incl(loc);
+            const unsigned long long reach = __ballot(incl >= need);
+            if (!reach) break;                   // fewer than `need` elements above -inf (a masked row): tau stays -inf, all of them are listed
+            const int owner = __ffsll((long long)reach) - 1;
+            // (the walk through the owner's eight bins in scalar registers)
+            int before = read_lane(incl - loc, owner), bin = 8 * owner, cnt = read_lane(h[0], owner);
+#pragma unroll
+            for (int u = 1; u < 8; ++u) {
+                const int next = read_lane(h[u], owner);
+                if (before + cnt < need && bin == 8 * owner + u - 1) { before += cnt; ++bin; cnt = next; }
+            }
+            const float edge = hi - ((float)(bin + 1) + 0.02f) * width;    // below every element of the bins up to the pivot
+            tau = float_below(edge);
+            if (cnt <= max(16, rank >> 3)) break;
+            hi = hi - ((float)bin - 0.02f) * width;
+            lo = fmaxf(lo, edge);
+            need -= before;
+        }
+    }
+
+    // ---- the list: the elements above the threshold, in any order.  A lane marks its elements in a word, a scan over the
+    //      counts gives it its slots, and it takes the few it marked from the image.
+    unsigned marks = 0;                          // bit 31 - e: element e
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        asm("v_cmp_gt_f32_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(marks) : "v"(v[e]), "v"(tau) : "vcc");
+    const int mine = __popc(marks);
+    const int incl = wave_scan_incl(mine);
+    const double ws = wave_sum((double)acc);
+    if (lane == kWave - 1) { wave_held[wave] = incl; wave_s[wave] = ws; }
+    __syncthreads();
+    int at = incl - mine, held = 0;
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; ++w) { at += w < wave ? wave_held[w] : 0; held += wave_held[w]; }
+    const int64_t list = row * P + part;
+    uint2* const out = lists + list * cap;
+    const typename G::elem_t* const my_image = reinterpret_cast<const typename G::elem_t*>(image) + tid * N;
+    const int first_block = wave * P + part;
+    if (held <= cap) {
+        // (a lane's vectors go through LDS four at a time, so that it picks its marked elements by a computed address)
+#pragma unroll
+        for (int j0 = 0; j0 < NV; j0 += kImageVecs) {
+#pragma unroll
+            for (int j = 0; j < kImageVecs; ++j) {
+                unsigned* const dst = &image[(j * kSplitThreads + tid) * 4];
+                if constexpr (BF16) {                // (packed again: the vectors as they were read would hold registers throughout)
+                    unsigned p[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        p[q] = __builtin_amdgcn_perm(__float_as_uint(v[(j0 + j) * N + 2 * q + 1]), __float_as_uint(v[(j0 + j) * N + 2 * q]), 0x07060302u);
+                    *reinterpret_cast<uint4*>(dst) = make_uint4(p[0], p[1], p[2], p[3]);
+                } else *reinterpret_cast<float4*>(dst) = make_float4(v[(j0 + j) * N], v[(j0 + j) * N + 1], v[(j0 + j) * N + 2], v[(j0 + j) * N + 3]);
+            }
+            constexpr int kPer = kImageVecs * N;     // elements per batch
+            unsigned m = (marks << (j0 * N)) & (0xFFFFFFFFu << (E - kPer));
+            while (m) {
+                const int e = __clz((int)m);
+                m &= ~(0x80000000u >> e);
+                const int j = e / N, el = e % N;
+                const unsigned bits = (unsigned)my_image[j * (kSplitThreads * N) + el] << (BF16 ? 16 : 0);
+                const int x = ((first_block + (j0 + j) * (kSplitWaves * P)) * kWave + lane) * N - rv.o + el;
+                out[at++] = make_uint2(bits, (unsigned)x);
+            }
+        }
+    }
+    if (tid == 0) {
+        // (+inf in the row: given up, as by the other kernels' first pass)
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < kSplitWaves; ++w) s += wave_s[w];
+        SplitHead h{mx, tau, ref, finite || !(mx > kNegInf) ? held : cap + 1, s, 0.0};
+        uint4* dst = reinterpret_cast<uint4*>(heads + list);
+        const uint4* src = reinterpret_cast<const uint4*>(&h);
+        dst[0] = src[0];
+        dst[1] = src[1];
+    }
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kSplitThreads) void split_select_kernel(
+    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int rank, int cap, int narrow,
+    SplitHead* __restrict__ heads, uint2* __restrict__ lists,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
+{
+    split_select<BF16>(blockIdx.y, (int)blockIdx.x, (int)gridDim.x, logits, ld, V, inv_T, rank, cap, narrow, heads, lists, seq_off, n_accept);
+}
+
+// A small round's draft rows and, in the same launch, the segment tables of its target rows: workgroups (x, y) with
+// y < n_draft and x < parts select, those with y >= n_draft and x < stats_per_row sum.
+template <bool BF16>
+__global__ __launch_bounds__(kSplitThreads) void split_round_kernel(
+    const void* __restrict__ draft_logits, int64_t ld_d, int n_draft, int V, float inv_T, int rank, int cap, int narrow,
+    SplitHead* __restrict__ heads, uint2* __restrict__ lists, int parts,
+    const void* __restrict__ tgt_logits, int64_t ld_t, int stats_per_row, SegHeader* __restrict__ header, int seg_stride)
+{
+    constexpr int NV = BF16 ? 2 : 4;
+    const int x = blockIdx.x, y = blockIdx.y;
+    if (y < n_draft) {
+        if (x < parts) split_select<BF16>(y, x, parts, draft_logits, ld_d, V, inv_T, rank, cap, narrow, heads, lists, nullptr, nullptr);
+        return;
+    }
+    if (y == n_draft && x == 0 && threadIdx.x == 0)
+        *header = SegHeader{kSegMagicSplit, NV * kWave, seg_stride, (int32_t)gridDim.y - n_draft};
+    if (x < stats_per_row)
+        row_stats_parts<BF16, NV, BF16 ? kStatsSpwBF16 : kStatsSpwF32>(y - n_draft, x, tgt_logits, ld_t, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kT, 4) void split_finish_kernel(
+    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
+    int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
+    float* __restrict__ mass, float* __restrict__ lse,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept,
+    const SplitHead* __restrict__ heads, const uint2* __restrict__ lists, int n_lists, int cap)
+{
+    using SH = CompressShared<kCapBig>;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    SH& sh = *reinterpret_cast<SH*>(smem_raw);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int64_t row = blockIdx.x;
+    const SplitHead* const head = heads + row * n_lists;
+    const uint2* const list = lists + row * n_lists * (int64_t)cap;
+    const float c = 1.4426950408889634f * inv_T;
+    // ---- Everything is asked for at once: the lists' heads (by every wave for itself, one per lane) and the first kAhead * kT
+    //      slots of the row's lists, whatever those turn out to hold.  Slot f of the row's array: position f mod cap of list
+    //      f / cap.
+    constexpr int kAhead = 8;
+    const int n_slots = n_lists * cap;
+    const float per_list = 1.0f / (float)cap;
+    uint4 h = make_uint4(0xFF800000u, 0xFF800000u, 0xFF800000u, 0u);
+    double s = 0.0;
+    if (lane < n_lists) {
+        h = *reinterpret_cast<const uint4*>(head + lane);
+        s = head[lane].s;
+    }
+    uint2 e[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+        e[u] = make_uint2(0u, 0u);
+        if (u * kT < n_slots && u * kT + tid < n_slots) e[u] = list[u * kT + tid];
+    }
+    const float mx = __uint_as_float(h.x), tau = __uint_as_float(h.y), ref = mx > kNegInf ? __uint_as_float(h.z) : kNegInf;
+    const int held = (int)h.w;
+    const float M = wave_max(mx), T = wave_max(tau), R = wave_max(ref);
+    const float low = -wave_max(lane < n_lists ? -tau : kNegInf);
+    const bool over = __ballot(held > cap) != 0ull;
+    const int incl = wave_scan_incl(held), total = read_lane(incl, kWave - 1);
+    const int first = incl - held;               // first slot, in the ordering's buffer, of list `lane`
+    double S = wave_sum(ref > kNegInf ? ldexp(s, max((int)(ref - R), -2000)) : 0.0);     // (whole exponents: exact)
+    S *= exp2_split((double)R - (double)M * (double)c);
+
+    RowSelection sel{total, total < k, true, M, S, short_key<BF16>(__float_as_uint(low)), short_key<BF16>(__float_as_uint(M))};
+    bool ok = !over && total <= SH::kCap && total >= 1 && M > kNegInf && M < __builtin_huge_valf() && S > 0.0 && S < 1e300 &&
+              (total >= k || T == kNegInf);      // (a threshold of -inf: every entry above -inf is listed)
+    if (ok) {
+        auto take = [&](int f, uint2 t) {
+            const int l = (int)(((float)f + 0.5f) * per_list), q = f - l * cap;     // (f < 2^15: exact)
+            const int n = __shfl(held, l, kWave), s0 = __shfl(first, l, kWave);
+            if (f < n_slots && q < n) { sh.cand_val[s0 + q] = t.x; sh.cand_id[s0 + q] = t.y; }
+        };
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) if (u * kT < n_slots) take(u * kT + tid, e[u]);
+        for (int f0 = kAhead * kT; f0 < n_slots; f0 += kT) take(f0 + tid, f0 + tid < n_slots ? list[f0 + tid] : make_uint2(0u, 0u));
+        order_prepare(sh, total);
+        if (tid == kT - 1) lse[row] = (float)((double)M * (double)inv_T + log(S));
+        __syncthreads();
+    }
+    const uint32_t key_T = short_key<BF16>(__float_as_uint(T));
+    const uint64_t* sorted;
+    int n;
+    for (;;) {
+        if (!ok) sel = select_row<BF16, false, false>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept);
+        n = min(sel.n_held, k);
+        if (sel.n_held <= kT)          sorted = order_top_k<BF16, 1, 1024, 128>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+        else if (sel.n_held <= 2 * kT) sorted = order_top_k<BF16, 2, 2048, 256>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+        else if (sel.n_held <= 4 * kT) sorted = order_top_k<BF16, 4>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+        else if (sel.n_held <= 8 * kT) sorted = order_top_k<BF16, 8>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+        else                           sorted = order_top_k<BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+        // the lists hold every element above T: they hold the top k iff the k-th lies above it
+        // (bf16: the short key of a T between two values is that of the lower one)
+        if (!ok || T == kNegInf || (uint32_t)(sorted[n - 1] >> kIdBits) > key_T) break;
+        ok = false;
+        __syncthreads();
+    }
+    emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass, u32x4_t{0u, 0u, 0u, 0u});
+}
+
+}  // namespace
+
+namespace {
+
+hipError_t launch_split_finish(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
+                               int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass, float* lse,
+                               const int32_t* seq_off, const int32_t* n_accept, const SplitPlan& p, const SplitHead* heads,
+                               const uint2* lists, hipStream_t stream)
+{
+    static DeviceFlags limit_raised[2] = {};
+    const int bf = dtype == 1;
+    const size_t smem = sizeof(CompressShared<kCapBig>);
+    int dev = 0;
+    const void* const finish = bf ? (const void*)split_finish_kernel<true> : (const void*)split_finish_kernel<false>;
+    if (hipError_t e = raise_lds_limit_once(finish, smem, limit_raised[bf], dev)) return e;
+    const float inv_T = 1.0f / temperature;
+    if (bf) hipLaunchKernelGGL(split_finish_kernel<true>, dim3(n_rows), dim3(kT), smem, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, heads, lists, p.parts, p.cap);
+    else    hipLaunchKernelGGL(split_finish_kernel<false>, dim3(n_rows), dim3(kT), smem, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, heads, lists, p.parts, p.cap);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_split_compress(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
+                                 int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass,
+                                 float* lse, const int32_t* seq_off, const int32_t* n_accept, void* scratch, hipStream_t stream)
+{
+    const SplitPlan p = split_plan(dtype, n_rows, V, k);
+    const float inv_T = 1.0f / temperature;
+    SplitHead* const heads = (SplitHead*)scratch;
+    uint2* const lists = (uint2*)(heads + (size_t)n_rows * p.parts);
+    const int narrow = p.rank <= kSplitNarrowRank;
+    const dim3 grid(p.parts, n_rows);
+    if (dtype == 1) hipLaunchKernelGGL(split_select_kernel<true>, grid, dim3(kSplitThreads), 0, stream, logits, ld, V, inv_T, p.rank, p.cap, narrow, heads, lists, seq_off, n_accept);
+    else            hipLaunchKernelGGL(split_select_kernel<false>, grid, dim3(kSplitThreads), 0, stream, logits, ld, V, inv_T, p.rank, p.cap, narrow, heads, lists, seq_off, n_accept);
+    if (hipError_t e = hipGetLastError()) return e;
+    return launch_split_finish(logits, dtype, ld, n_rows, V, temperature, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, p, heads, lists, stream);
+}
+
+hipError_t launch_split_round(const void* draft_logits, int dtype, int64_t ld_d, int n_draft, int V, float temperature,
+                              int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass, float* lse,
+                              const void* tgt_logits, int64_t ld_t, int n_target, void* seg_table, void* scratch, hipStream_t stream)
+{
+    const SplitPlan p = split_plan(dtype, n_draft, V, k);
+    const StatsShape sh = stats_shape(dtype, n_target, V);
+    const int per_row = stats_parts(dtype, sh.stride);
+    const float inv_T = 1.0f / temperature;
+    SplitHead* const heads = (SplitHead*)scratch;
+    uint2* const lists = (uint2*)(heads + (size_t)n_draft * p.parts);
+    const int narrow = p.rank <= kSplitNarrowRank;
+    const dim3 grid(p.parts > per_row ? p.parts : per_row, n_draft + n_target);
+    if (dtype == 1) hipLaunchKernelGGL(split_round_kernel<true>, grid, dim3(kSplitThreads), 0, stream, draft_logits, ld_d, n_draft, V, inv_T, p.rank, p.cap, narrow, heads, lists, p.parts, tgt_logits, ld_t, per_row, (SegHeader*)seg_table, sh.stride);
+    else            hipLaunchKernelGGL(split_round_kernel<false>, grid, dim3(kSplitThreads), 0, stream, draft_logits, ld_d, n_draft, V, inv_T, p.rank, p.cap, narrow, heads, lists, p.parts, tgt_logits, ld_t, per_row, (SegHeader*)seg_table, sh.stride);
+    if (hipError_t e = hipGetLastError()) return e;
+    return launch_split_finish(draft_logits, dtype, ld_d, n_draft, V, temperature, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr, p, heads, lists, stream);
+}
+
+}  // namespace picospec

@@ -47,20 +47,65 @@ __global__ __launch_bounds__(THREADS) void row_stats_range_kernel(
     row_stats_row<BF16, NV, THREADS>((int64_t)d0 + b + t, logits, ld, V, inv_T, row_max, row_sum, row_lse);
 }
 
-// picospec_verify's second kernel: one workgroup per sequence (accept_sequence, decide.hpp).
+// Few rows: the segment tables alone (split layout).  grid: (workgroups per row, rows), or (.., gamma_max + 1, B) for the
+// target rows of a range of positions.
+template <bool BF16, int NV, int SPW>
+__global__ __launch_bounds__(256) void row_stats_parts_kernel(
+    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int n_rows, int seg_stride,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end,
+    SegHeader* __restrict__ header)
+{
+    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
+        *header = SegHeader{kSegMagicSplit, NV * kWave, seg_stride, n_rows};
+    int64_t row = blockIdx.y;
+    if (seq_off) {                                    // position t of sequence b, or nothing
+        const int b = blockIdx.z, t = blockIdx.y, d0 = seq_off[b];
+        const int g = max(seq_off[b + 1] - d0, 0);
+        int begin, end;
+        clamp_range(pos_begin, pos_end, b, g, begin, end);
+        if (t < begin || t > end) return;
+        row = (int64_t)d0 + b + t;
+    }
+    row_stats_parts<BF16, NV, SPW>(row, (int)blockIdx.x, logits, ld, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
+}
+
+// The statistics of rows whose table stands in the split layout: one wave per row.
 template <bool BF16>
+__global__ __launch_bounds__(256) void row_stats_finish_kernel(
+    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int n_rows, const SegHeader* __restrict__ header,
+    int seg_vecs, int seg_stride, float* __restrict__ row_max, float* __restrict__ row_sum, float* __restrict__ row_lse)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+    if (row >= n_rows) return;
+    const RowView rv = row_view<BF16>(logits, ld, row, V);
+    const int nq = (rv.L + Vec<BF16>::N - 1) / Vec<BF16>::N, n_seg = (nq + seg_vecs - 1) / seg_vecs;
+    float M;
+    double S;
+    row_stats_of_table<BF16>(reinterpret_cast<const float2*>(header + 1) + row * (int64_t)seg_stride, n_seg, 1.4426950408889634f * inv_T, M, S);
+    if (lane == 0) {
+        row_max[row] = M;
+        row_sum[row] = (float)S;
+        if (row_lse) row_lse[row] = (float)((double)M * (double)inv_T + log(S));
+    }
+}
+
+// picospec_verify's second kernel: one workgroup per sequence (accept_sequence, decide.hpp).
+template <bool BF16, bool TABLE>
 __global__ __launch_bounds__(kThreads) void accept_kernel(
     const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T, int B,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
     const float* __restrict__ q_scalar, const float* __restrict__ uniforms,
-    const float* __restrict__ tgt_max, const float* __restrict__ tgt_sum,
+    float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok,
-    uint32_t* __restrict__ flags, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end)
+    uint32_t* __restrict__ flags, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end,
+    const SegHeader* __restrict__ table, int seg_vecs, int stride, int n_rows)
 {
-    accept_sequence<BF16>(blockIdx.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k,
-                          renorm, q_scalar, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok, flags, pos_begin, pos_end);
+    accept_sequence<BF16, TABLE>(blockIdx.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k,
+                                 renorm, q_scalar, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok, flags, pos_begin, pos_end,
+                                 tgt_lse, table, seg_vecs, stride, n_rows);
 }
 
 }  // namespace
@@ -101,18 +146,47 @@ hipError_t launch_row_stats(const void* logits, int dtype, int64_t ld, int n_row
     return hipGetLastError();
 }
 
+hipError_t launch_row_stats_parts(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature, int B, int gamma_max, const int32_t* seq_off, const int32_t* pos_begin, const int32_t* pos_end,
+                                  void* seg_table, hipStream_t stream)
+{
+    if (n_rows == 0 || (seq_off && B == 0)) return hipSuccess;
+    const float inv_T = 1.0f / temperature;
+    const StatsShape sh = stats_shape(dtype, n_rows, V);      // (fp32 NV = 4, bf16 NV = 2 at the row counts that are split)
+    const dim3 grid(stats_parts(dtype, sh.stride), seq_off ? gamma_max + 1 : n_rows, seq_off ? B : 1);
+    if (dtype == 1) hipLaunchKernelGGL((row_stats_parts_kernel<true, 2, kStatsSpwBF16>), grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, (SegHeader*)seg_table);
+    else            hipLaunchKernelGGL((row_stats_parts_kernel<false, 4, kStatsSpwF32>), grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, (SegHeader*)seg_table);
+    return hipGetLastError();
+}
+
+hipError_t launch_row_stats_finish(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
+                                   const void* seg_table, float* row_max, float* row_sum, float* row_lse, hipStream_t stream)
+{
+    if (n_rows == 0) return hipSuccess;
+    const float inv_T = 1.0f / temperature;
+    const StatsShape sh = stats_shape(dtype, n_rows, V);
+    const dim3 grid((n_rows + 3) / 4);
+    if (dtype == 1) hipLaunchKernelGGL(row_stats_finish_kernel<true>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, row_max, row_sum, row_lse);
+    else            hipLaunchKernelGGL(row_stats_finish_kernel<false>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, row_max, row_sum, row_lse);
+    return hipGetLastError();
+}
+
 hipError_t launch_accept(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
                          int B, const int32_t* seq_off, const int32_t* draft_tok,
                          const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
                          int k, int renorm, const float* q_scalar, const float* uniforms,
-                         const float* tgt_max, const float* tgt_sum,
+                         float* tgt_max, float* tgt_sum, float* tgt_lse,
                          int32_t* n_accept, float* p_tok, float* q_tok, uint32_t* flags,
-                         const int32_t* pos_begin, const int32_t* pos_end, hipStream_t stream)
+                         const int32_t* pos_begin, const int32_t* pos_end,
+                         const void* split_table, int64_t n_rows, hipStream_t stream)
 {
     if (B == 0) return hipSuccess;
     const float inv_T = 1.0f / temperature;
-    if (dtype == 1) hipLaunchKernelGGL(accept_kernel<true>, dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, inv_T, B, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, q_scalar, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok, flags, pos_begin, pos_end);
-    else            hipLaunchKernelGGL(accept_kernel<false>, dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, inv_T, B, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, q_scalar, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok, flags, pos_begin, pos_end);
+    const StatsShape sh = stats_shape(dtype, n_rows, V);
+#define PICOSPEC_ACCEPT(BF, TA) \
+    hipLaunchKernelGGL((accept_kernel<BF, TA>), dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, inv_T, B, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, q_scalar, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok, flags, pos_begin, pos_end, (const SegHeader*)split_table, sh.seg_vecs, sh.stride, (pos_begin || pos_end) ? 0 : (int)n_rows)
+    if (split_table) { if (dtype == 1) PICOSPEC_ACCEPT(true, true); else PICOSPEC_ACCEPT(false, true); }
+    else             { if (dtype == 1) PICOSPEC_ACCEPT(true, false); else PICOSPEC_ACCEPT(false, false); }
+#undef PICOSPEC_ACCEPT
     return hipGetLastError();
 }
 

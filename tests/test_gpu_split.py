@@ -1,0 +1,158 @@
+"""Calls of few rows, whose rows are spread over many workgroups: the compression and the target rows' statistics against the
+oracle at the edges of the rule and of its parts (two parts, a part with one block, the longest rows, the most rows), and
+against the same calls with one workgroup per row."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2603_19133_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ps():
+    from paper_2603_19133_amd import binding
+    return binding
+
+
+@pytest.fixture(scope="module")
+def pu():
+    import parity_util
+    return parity_util
+
+
+def _announce(*a):
+    print("[case]", *a, flush=True)
+
+
+def _unsplit(ps, z, V, T, k, top_p=0.0):
+    """picospec_compress without a workspace: one workgroup per row."""
+    out = ps.alloc_compressed(z.shape[0], k, z.device)
+    p = lambda t: t.data_ptr()
+    ps._check(ps.lib.picospec_compress(p(z), ps._dtype_code(z), z.stride(0), z.shape[0], V, T, k, top_p, p(out.idx), p(out.prob),
+                                       p(out.count), p(out.mass), p(out.lse), None, 0, torch.cuda.current_stream().cuda_stream))
+    return out
+
+
+def _rows(rng, pattern, R, V):
+    z = rng.standard_normal((R, V)) * 3
+    if pattern == "trend":
+        z = z + np.linspace(6, -6, V)
+    elif pattern == "few_values":
+        z = np.round(z)
+    elif pattern == "one_value":
+        z = np.full((R, V), -0.5)
+    elif pattern == "outlier":
+        z[:, V // 3] = 1e4
+    elif pattern == "masked":
+        z = np.where(rng.random((R, V)) < 0.97, -np.inf, z)
+    elif pattern == "masked_lowest":
+        z = np.where(rng.random((R, V)) < 0.9, np.finfo(np.float32).min, z)
+    elif pattern == "masked_to_a_few":
+        z = np.where(rng.random((R, V)) < 0.9999, -np.inf, z)
+    elif pattern == "periodic":                  # one workgroup's blocks hold all of the large values
+        z = z + 8.0 * ((np.arange(V) // 256) % 64 == 5)
+    elif pattern == "plus_inf":
+        z[:, 7] = np.inf
+    return z.astype(np.float32)
+
+
+# 8192 elements per workgroup: two parts, a block more, the longest row of 64 parts and the first that is not split
+@pytest.mark.parametrize("V,R,k", [(16383, 2, 64), (16384, 2, 64), (16385, 3, 1), (16640, 2, 500), (24576, 256, 32), (24577, 257, 32),
+                                   (50001, 4, 4096), (128256, 2, 10), (151936, 3, 1024), (152064, 1, 4096), (524288 - 64, 1, 4000),
+                                   (524289, 1, 100)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_sizes_match_the_oracle_and_one_workgroup_per_row(gpu, pu, ps, V, R, k, dtype):
+    _announce("split sizes", V, R, k, dtype)
+    z = _rows(np.random.default_rng(V + k), "normal", R, V)
+    stored = z if dtype == "f32" else W.to_bf16_bits(z)
+    dev = pu.to_device(stored, gpu)
+    g, u = ps.compress(dev, V, 0.9, k), _unsplit(ps, dev, V, 0.9, k)
+    torch.cuda.synchronize()
+    n = min(R, 4)
+    pu.compare_compress(ps.Compressed(g.idx[:n], g.prob[:n], g.count[:n], g.mass[:n], g.lse[:n], k), oracle.compress(stored[:n], V, 0.9, k), 0.0)
+    assert torch.equal(g.idx, u.idx) and torch.equal(g.count, u.count)
+    pu.assert_close(pu.n(g.prob), pu.n(u.prob).astype(np.float64), 1e-6, "prob", atol=1e-38)
+
+
+@pytest.mark.parametrize("pattern", ["trend", "few_values", "one_value", "outlier", "masked", "masked_lowest", "masked_to_a_few", "periodic"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("k,top_p", [(40, 0.0), (2000, 0.9)])
+def test_patterns_match_the_oracle(gpu, pu, ps, pattern, dtype, k, top_p):
+    _announce("split patterns", pattern, dtype, k, top_p)
+    V, R, shift = 40003, 3, 1                    # rows off the 16-byte boundary
+    z = _rows(np.random.default_rng(k), pattern, R, V + shift)
+    stored = z if dtype == "f32" else W.to_bf16_bits(z)
+    g = ps.compress(pu.to_device(stored, gpu)[:, shift:], V, 1.1, k, top_p)
+    torch.cuda.synchronize()
+    pu.compare_compress(g, oracle.compress(np.ascontiguousarray(stored[:, shift:]), V, 1.1, k, top_p), top_p)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_infinities_and_nan_as_with_one_workgroup_per_row(gpu, ps, dtype):
+    _announce("split infinities", dtype)
+    V, k = 30000, 20
+    z = torch.from_numpy(_rows(np.random.default_rng(3), "plus_inf", 4, V)).to(gpu).to(dtype)
+    z[1] = float("-inf")
+    z[2, 5] = float("nan")
+    z[2, 7] = 0.0
+    z[3] = torch.finfo(dtype).min
+    g, u = ps.compress(z, V, 1.0, k), _unsplit(ps, z, V, 1.0, k)
+    torch.cuda.synchronize()
+    for r in (0, 1, 3):                          # (the entries of a row with a NaN are whatever they are; the statistics are NaN)
+        assert torch.equal(g.idx[r], u.idx[r]) and torch.equal(g.count[r], u.count[r])
+        assert torch.allclose(g.prob[r], u.prob[r], rtol=1e-6, atol=0, equal_nan=True)
+    assert torch.allclose(g.lse, u.lse, rtol=1e-6, atol=0, equal_nan=True)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V,R,T", [(16384, 3, 1.0), (33001, 256, 0.7), (128256, 5, 0.05), ((1 << 20) - 5, 2, 1.0)])
+def test_row_statistics(gpu, pu, ps, dtype, V, R, T):
+    _announce("split statistics", dtype, V, R, T)
+    g = torch.Generator(device=gpu)
+    g.manual_seed(V)
+    z = (torch.randn((R, V + 3), device=gpu, generator=g) * 4).to(dtype)[:, 1:V + 1]
+    z[0, : V // 2] = torch.finfo(dtype).min     # whole segments of masked entries, by the type's lowest value and by -inf
+    z[1, V // 2:] = float("-inf")
+    mx, sm, lse = ps.row_stats(z, V, T)
+    x = z.double().cpu()
+    m = x.max(1).values
+    s = torch.exp((x - m[:, None]) / T).sum(1)
+    assert torch.equal(mx.double().cpu(), m)
+    pu.assert_close(pu.n(sm), s.numpy(), pu.RTOL, "sum")
+    pu.assert_close(pu.n(lse), (m / T + torch.log(s)).numpy(), pu.RTOL_LSE, "lse", atol=2e-6)
+
+
+@pytest.mark.parametrize("rows", ["all_lowest", "all_neg_inf", "nan", "plus_inf"])
+def test_statistics_of_degenerate_rows(gpu, ps, rows):
+    """What a row of nothing but masked entries, or with a NaN or an infinity in it, gave before it gives with its statistics
+    spread over many workgroups."""
+    _announce("split degenerate statistics", rows)
+    V = 20000
+    z = torch.randn((2, V), device=gpu)
+    z[1] = {"all_lowest": torch.finfo(torch.float32).min, "all_neg_inf": float("-inf")}.get(rows, 0.0)
+    if rows == "nan":
+        z[1, 9] = float("nan")
+    if rows == "plus_inf":
+        z[1, 9] = float("inf")
+    got = ps.row_stats(z, V, 1.0)
+    want = [torch.empty(2, device=gpu) for _ in range(3)]
+    ps._check(ps.lib.picospec_row_stats(z.data_ptr(), ps.F32, V, 2, V, 1.0, *[t.data_ptr() for t in want],
+                                        torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        assert torch.allclose(a, b, rtol=1e-6, atol=0, equal_nan=True), (a, b)
+
+
+def test_rows_behind_the_last_sequence_keep_their_statistics(gpu, ps):
+    """n_draft may be larger than seq_off[B] (a batch that an uplink message clamped): all n_draft + B rows get statistics."""
+    _announce("split statistics behind the last sequence")
+    V, B, N = 20000, 2, 7
+    tgt = torch.randn((N + B, V), device=gpu)
+    off = torch.tensor([0, 2, 4], dtype=torch.int32, device=gpu)
+    tok = torch.zeros(N, dtype=torch.int32, device=gpu)
+    v = ps.verify(tgt, V, 1.0, off, N, tok, None, torch.rand(N + B, device=gpu), q_scalar=torch.rand(N, device=gpu))
+    assert torch.equal(v.tgt_max, tgt.max(1).values)
+    assert torch.allclose(v.tgt_lse, torch.logsumexp(tgt, 1), rtol=1e-5)

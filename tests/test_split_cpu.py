@@ -1,0 +1,83 @@
+"""The rule by which a call's rows are split over workgroups, and the split kernels' code, without a GPU."""
+import os
+import re
+import subprocess
+import tempfile
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2603_19133_amd import binding
+    return binding
+
+
+def test_scratch_is_asked_for_where_rows_are_split_only(B):
+    f = B.workspace_bytes
+    for dt in (B.F32, B.BF16):
+        assert f(B.CALL_COMPRESS, dt, 1, 16384, 64) > 0 and f(B.CALL_COMPRESS, dt, 256, 151936, 4096) > 0
+        assert f(B.CALL_COMPRESS, dt, 257, 151936, 64) == 0          # the rows fill the chip by themselves
+        assert f(B.CALL_COMPRESS, dt, 4, 16383, 64) == 0             # too short to split
+        assert f(B.CALL_COMPRESS, dt, 1, 1 << 20, 64) == 0           # more lists than a finishing wave has lanes
+        assert f(B.CALL_COMPRESS, dt, 0, 32000, 64) == 0
+        sizes = [f(B.CALL_COMPRESS, dt, r, 40000, 100) for r in range(1, 257)]
+        assert all(b > a for a, b in zip(sizes, sizes[1:]))
+        # a round's workspace without k is its segment table; with k it holds the scratch of up to that many draft rows as well
+        table = f(B.CALL_ROUND, dt, 20, 32000, 0)
+        assert f(B.CALL_ROUND, dt, 20, 32000, 64) >= table + f(B.CALL_COMPRESS, dt, 20, 32000, 64)
+
+
+FAKE = 0x1000
+
+
+def test_a_smaller_workspace_is_accepted_and_a_misaligned_one_is_not(B):
+    """Both calls fail later checks of theirs in no case: no rows, nothing is launched (the calls return before that only where the
+    workspace is refused)."""
+    call = lambda ws, n: B.lib.picospec_compress(None, B.F32, 100, 0, 100, 1.0, 10, 0.0, None, None, None, None, None, ws, n, None)
+    assert call(FAKE + 4, 1 << 20) == B.EWORKSPACE
+    rs = lambda ws, n, rows=2: B.lib.picospec_row_stats_ws(FAKE, B.F32, 100, rows, 100, 1.0, FAKE, FAKE, None, ws, n, None)
+    assert rs(FAKE + 4, 1 << 20) == B.EWORKSPACE and rs(FAKE, 16) == B.EWORKSPACE
+    assert B.lib.picospec_row_stats_ws(FAKE, B.F32, 100, 2, 100, 0.0, FAKE, FAKE, None, None, 0, None) == B.EINVAL
+    assert B.lib.picospec_row_stats_ws(FAKE, B.F32, 100, 2, 100, 1.0, None, FAKE, None, None, 0, None) == B.EINVAL
+    assert B.lib.picospec_row_stats_ws(FAKE, 9, 100, 2, 100, 1.0, FAKE, FAKE, None, None, 0, None) == B.EDTYPE
+
+
+def test_split_kernels_keep_claimed_slots_in_registers():
+    """The finishing kernel holds the general compression for the rows it gives up, with that code's hand-issued LDS atomics: no
+    scratch access may stand between one of them and the wait that follows (see the same test of the compress kernels)."""
+    from paper_2603_19133_amd import build as bld
+    if not os.path.exists(bld.HIPCC):
+        pytest.skip("hipcc not found")
+    flags = [f for f in bld.FLAGS if f not in ("-shared", "-fPIC")]
+    with tempfile.TemporaryDirectory() as tmp:
+        asm = os.path.join(tmp, "split.s")
+        out = subprocess.run([bld.HIPCC, *flags, "-S", "--cuda-device-only", "-o", asm, os.path.join(bld.CSRC, "split.hip")],
+                             capture_output=True, text=True)
+        assert out.returncode == 0, out.stderr[-2000:]
+        lines = open(asm).read().split("\n")
+    seen, name, pending, by_hand = {}, None, False, False
+    for line in lines:
+        m = re.match(r"^(_ZN8picospec\S+):", line)
+        if m:
+            name, pending, by_hand = m.group(1), False, False
+            seen[name] = dict(atomics=0, scratch=0, in_window=0)
+            continue
+        if name is None:
+            continue
+        ins = line.strip()
+        if ins.startswith(";;#ASMSTART") or ins.startswith(";;#ASMEND"):
+            by_hand = ins.startswith(";;#ASMSTART")
+        elif ins.startswith("s_endpgm"):
+            name = None
+        elif ins.startswith("ds_add_rtn") and by_hand:
+            seen[name]["atomics"] += 1
+            pending = True
+        elif ins.startswith("s_waitcnt") and "lgkmcnt(0)" in ins:
+            pending = False
+        elif ins.startswith("scratch_"):
+            seen[name]["scratch"] += 1
+            seen[name]["in_window"] += pending
+    assert sum(v["atomics"] >= 8 for v in seen.values()) == 2, seen          # the finishing kernel, both types
+    assert all(v["in_window"] == 0 for v in seen.values()), seen
+    assert all(v["scratch"] == 0 for k, v in seen.items() if "select" in k or "split_round" in k), seen
