@@ -1,4 +1,5 @@
-"""Builds libpicospec.so (gfx950) in-tree with hipcc.  Run as ``python -m paper_2603_19133_amd.build``."""
+"""Builds libpicospec.so (gfx950, hipcc) and the native part of the Python binding (_native.so, host compiler) in-tree.
+Run as ``python -m paper_2603_19133_amd.build``."""
 from __future__ import annotations
 
 import os
@@ -8,6 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpicospec.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.hip", "compress.hip", "split.hip", "verify.hip", "residual.hip", "downlink.hip", "wire.hip", "selfcheck.hip", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 instructions are switched off (scalar fp32 code only); the compiler's rewrite of
@@ -35,5 +37,27 @@ def build(verbose: bool = False, extra: list[str] | None = None, out: str | None
     return out
 
 
+def build_native(verbose: bool = False) -> str:
+    """Compiles the binding's extension module against the torch that is installed; links libpicospec.so, which must be built."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f"-I{p}" for p in (*include_paths(), sysconfig.get_paths()["include"])],
+           "-o", NATIVE, os.path.join(CSRC, "native.cpp"),
+           f"-L{HERE}", "-l:libpicospec.so", "-Wl,-rpath,$ORIGIN", f"-L{torch_lib}", f"-Wl,-rpath,{torch_lib}",
+           "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed:\n{res.stderr}")
+    return NATIVE
+
+
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_native(verbose=True))
