@@ -1167,37 +1167,51 @@ __device__ __forceinline__ void emit_row(
             }
         }
     } else {
-        for (int j0 = 0; j0 < k; j0 += kT) {   // keep a slot iff the probability before it has not reached top_p
-            const int slot = j0 + tid;
-            int id = -1;
-            float pr = 0.f;
-            if (slot < n) emit_value(slot, id, pr);
-            const double mine = (double)pr;
+        // keep a slot iff the probability in front of it has not reached top_p.  Four consecutive slots per thread, so that one
+        // scan over the workgroup covers 2048 slots (one slot per thread took a scan and two barriers per 512).
+        for (int j0 = 0; j0 < k; j0 += 4 * kT) {
+            const int s0 = j0 + 4 * tid;
+            int id[4] = {-1, -1, -1, -1};
+            float pr[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) if (s0 + e < n) emit_value(s0 + e, id[e], pr[e]);
+            const double mine = (((double)pr[0] + (double)pr[1]) + (double)pr[2]) + (double)pr[3];
             const double incl = wave_scan_incl(mine);
             if (lane == kWave - 1) sh.red[wave] = incl;
             __syncthreads();
-            double before = carry, tot = 0.0;
+            double before = carry + incl - mine, tot = 0.0;
 #pragma unroll
             for (int w = 0; w < kW; ++w) { const double t = sh.red[w]; if (w < wave) before += t; tot += t; }
-            __syncthreads();
-            const bool keep = slot < n && (before + incl - mine) < (double)top_p;
             carry += tot;
-            if (slot < k) {
-                idx_row[slot] = keep ? id : -1;
-                prob_row[slot] = keep ? pr : 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool keep = s0 + e < n && before < (double)top_p;
+                before += (double)pr[e];
+                if (keep) { my_mass += (double)pr[e]; ++my_count; } else { id[e] = -1; pr[e] = 0.f; }
             }
-            if (keep) { my_mass += (double)pr; ++my_count; }
+            if (rows_aligned) {
+                typedef int i32x4_t __attribute__((ext_vector_type(4)));
+                typedef float f32x4_t __attribute__((ext_vector_type(4)));
+                if (s0 < k) {
+                    __builtin_nontemporal_store(i32x4_t{id[0], id[1], id[2], id[3]}, reinterpret_cast<i32x4_t*>(idx_row + s0));
+                    __builtin_nontemporal_store(f32x4_t{pr[0], pr[1], pr[2], pr[3]}, reinterpret_cast<f32x4_t*>(prob_row + s0));
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) if (s0 + e < k) { idx_row[s0 + e] = id[e]; prob_row[s0 + e] = pr[e]; }
+            }
+            if (j0 + 4 * kT < k) __syncthreads();  // (the waves' sums are written again)
         }
     }
     const double wm = wave_sum(my_mass);
     const int wc = wave_sum(my_count);
-    if (lane == 0) { sh.red[wave] = wm; sh.wtot[wave] = wc; }
+    if (lane == 0) { sh.red[kW + wave] = wm; sh.wtot[wave] = wc; }     // (the first kW words may still be read)
     __syncthreads();
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));                  // (nothing of this is held from the top of the kernel)
     if (t < kWave) {                             // the eight waves' sums, in eight lanes
         static_assert(kW == 8, "three steps add the waves' sums");
-        double tm = t < kW ? sh.red[t] : 0.0;
+        double tm = t < kW ? sh.red[kW + t] : 0.0;
         int tc = t < kW ? sh.wtot[t] : 0;
         tm += dpp<kDppQuadXor1>(tm); tc += dpp<kDppQuadXor1>(tc);
         tm += dpp<kDppQuadXor2>(tm); tc += dpp<kDppQuadXor2>(tc);
