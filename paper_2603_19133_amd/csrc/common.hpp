@@ -182,14 +182,14 @@ __device__ __forceinline__ double exp_emit(float x, float m, double c) {
     if (!(a > -1100.0)) return 0.0;               // also catches x = -inf
     double n = rint(a);
     float f = (float)(a - n);                     // |f| <= 0.5, exact difference
-    return ldexp((double)exp2f(f), (int)n);
+    return ldexp((double)__builtin_amdgcn_exp2f(f), (int)n);   // (no scaling for tiny results is needed at |f| <= 0.5)
 }
 
 // 2^a for a double exponent of any magnitude (split into integer and fraction as in exp_emit).
 __device__ __forceinline__ double exp2_split(double a) {
     if (!(a > -1100.0)) return 0.0;
     double n = rint(a);
-    return ldexp((double)exp2f((float)(a - n)), (int)n);
+    return ldexp((double)__builtin_amdgcn_exp2f((float)(a - n)), (int)n);
 }
 
 // ---------------------------------------------------------------- row streaming

@@ -12,10 +12,10 @@ __global__ __launch_bounds__(kT, SMALL ? 6 : 4) void compress_kernel(
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
     int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
     float* __restrict__ mass, float* __restrict__ lse,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int ahead)
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int ahead, int rank_opt)
 {
     compress_row<BF16, SMALL, FAST>(blockIdx.x, (int)gridDim.x, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse,
-                                    seq_off, n_accept, ahead);
+                                    seq_off, n_accept, ahead, rank_opt);
 }
 
 // The rows that the small variant marked with count = kRetryRow, through the general code: a few workgroups, each
@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kT, 4) void compress_retry_kernel(
     const void* __restrict__ logits, int64_t ld, int n_rows, int V, float inv_T, int k, float top_p,
     int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
     float* __restrict__ mass, float* __restrict__ lse,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int rank_opt)
 {
     __shared__ int marked[kT];
     __shared__ int n_marked;
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kT, 4) void compress_retry_kernel(
         for (int i = 0; i < n; ++i) {
             const int row = marked[i];
             compress_row<BF16, false, false>(row, n_rows, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse,
-                                      seq_off, n_accept, 0);
+                                      seq_off, n_accept, 0, rank_opt);
             __syncthreads();                     // (the row's last reads of LDS are done before the next one resets it)
         }
         __syncthreads();
@@ -59,11 +59,11 @@ __global__ __launch_bounds__(kT, 2) void round_stream_kernel(
     float* __restrict__ mass, float* __restrict__ lse,
     const void* __restrict__ tgt_logits, int64_t ld_t,
     float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
-    SegHeader* __restrict__ seg_header, int seg_stride)
+    SegHeader* __restrict__ seg_header, int seg_stride, int rank_opt)
 {
     if ((int)blockIdx.x < n_draft) {
         compress_row<BF16, false, false>(blockIdx.x, n_draft, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse,
-                                  nullptr, nullptr, 0);
+                                  nullptr, nullptr, 0, rank_opt);
     } else if (seg_header) {
         // with the target rows' segment table (the draw then needs no second pass over its row); the row's table is
         // staged in the LDS that a compressing workgroup uses for its candidates
@@ -240,10 +240,11 @@ hipError_t launch_compress(const void* logits, int dtype, int64_t ld, int n_rows
     // (no look-ahead with a row map: the next row is not known from the row number)
     const int ahead = (!seq_off && cus > 0) ? (small ? 3 : 2) * cus : 0;
     const float inv_T = 1.0f / temperature;
+    const int rank_opt = compress_rank(k, V, small);
 #define PICOSPEC_COMPRESS(BF, SM, FA, SMEM) \
-    hipLaunchKernelGGL((compress_kernel<BF, SM, FA>), dim3(n_rows), dim3(kT), SMEM, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, ahead)
+    hipLaunchKernelGGL((compress_kernel<BF, SM, FA>), dim3(n_rows), dim3(kT), SMEM, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, ahead, rank_opt)
 #define PICOSPEC_RETRY(BF) \
-    hipLaunchKernelGGL((compress_retry_kernel<BF>), dim3(min(64, (n_rows + kT - 1) / kT)), dim3(kT), smem_big, stream, logits, ld, n_rows, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept)
+    hipLaunchKernelGGL((compress_retry_kernel<BF>), dim3(min(64, (n_rows + kT - 1) / kT)), dim3(kT), smem_big, stream, logits, ld, n_rows, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, compress_rank(k, V, false))
     if (small) {
         PICOSPEC_COMPRESS(true, true, true, smem_small);
     } else if (fast) {
@@ -280,8 +281,8 @@ hipError_t launch_round_stream(const void* draft_logits, int dtype, int64_t ld_d
     if (n_target == 0) seg_table = nullptr;
     SegHeader* const header = (SegHeader*)seg_table;
     const int stride = round_stats_shape(dtype, V).stride;
-    if (which) hipLaunchKernelGGL(b16, dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, header, stride);
-    else       hipLaunchKernelGGL(f32, dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, header, stride);
+    if (which) hipLaunchKernelGGL(b16, dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, header, stride, compress_rank(k, V, false));
+    else       hipLaunchKernelGGL(f32, dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, header, stride, compress_rank(k, V, false));
     return hipGetLastError();
 }
 

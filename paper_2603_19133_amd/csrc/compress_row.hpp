@@ -95,6 +95,11 @@ struct __align__(16) CompressShared {
 static_assert(sizeof(CompressShared<kCapBig>) <= 80 * 1024, "two workgroups share the 160 KB of LDS of a gfx950 CU");
 static_assert(sizeof(CompressShared<kCapSmall>) <= 160 * 1024 / 3, "three workgroups of the small variant share a CU's LDS");
 
+// The optimistic pass's rank for a call (0: the careful pass takes its rows), with the buffer of the kernel that runs it.
+inline int compress_rank(int k, int V, bool small) {
+    return V > kCompressSample - 8 ? optimistic_rank(k, V, kCompressSample, small ? kCapSmall : kCapBig) : 0;
+}
+
 template <bool BF16>
 __device__ __forceinline__ uint32_t short_key(uint32_t bits) {
     uint32_t key = key_of_bits(bits);
@@ -482,11 +487,13 @@ __device__ __forceinline__ int sample_vec_of(int j, int n_vec, const uint4* base
 // FAST: the optimistic pass only (what the careful pass keeps alive across it costs registers, those that the third
 // workgroup needs among them): a row whose pass fails, or to which it does not apply, gets count = kRetryRow and
 // nothing else, and a second, small launch that runs the general code on the marked rows takes it.
+// rank_opt: compress_rank() of the call, from the host (its square roots are a hundred instructions that every wave of every
+// row would spend on the same number).
 template <bool BF16, bool SMALL, bool FAST>
 __device__ __forceinline__ RowSelection select_row(
     CompressShared<SMALL ? kCapSmall : kCapBig>& sh, const int64_t row,
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float* __restrict__ lse,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, const int rank_opt)
 {
     using SH = CompressShared<SMALL ? kCapSmall : kCapBig>;
     constexpr int kCap = SH::kCap;
@@ -567,9 +574,16 @@ __device__ __forceinline__ RowSelection select_row(
         for (int j = 0; j < NV0; ++j) {
             float t[N];
             unpack<BF16>(src[j], t);
-            const unsigned vm = vec_valid_mask<BF16>(rv, sample_vec(j));
 #pragma unroll
-            for (int e = 0; e < N; ++e) v[j * N + e] = (vm >> e) & 1u ? t[e] : qnan;
+            for (int e = 0; e < N; ++e) v[j * N + e] = t[e];
+        }
+        if (rv.o > 0 || rv.L % N != 0) {         // (uniform; a row that begins and ends on vector edges has no such element)
+#pragma unroll
+            for (int j = 0; j < NV0; ++j) {
+                const unsigned vm = vec_valid_mask<BF16>(rv, sample_vec(j));
+#pragma unroll
+                for (int e = 0; e < N; ++e) v[j * N + e] = (vm >> e) & 1u ? v[j * N + e] : qnan;
+            }
         }
     };
     // Running softmax sum of this thread: s = sum 2^(v*c - r) with an integer reference exponent
@@ -674,9 +688,8 @@ __device__ __forceinline__ RowSelection select_row(
     // that they stay straight-line code (predication by EXEC, no branches for the compiler to lay
     // out): claim_asm forms the lane mask, claims under it and hands the mask on; put_asm waits for
     // the claimed slots and writes under the same masks.  The counter
-    // starts at the LDS address of cand_val and counts bytes (4 per candidate), so that a claimed slot, clamped,
-    // is the address to write to; slots behind the buffer's end fall onto its last one: once the count has
-    // passed the end the pass is lost anyway.
+    // starts at the LDS address of cand_val and counts bytes (4 per candidate), so that a claimed slot
+    // is the address to write to.
     typedef __attribute__((address_space(3))) unsigned lds_u32;
     const unsigned cnt_addr = (unsigned)(uintptr_t)(lds_u32*)&sh.cnt;
     const unsigned val_addr = (unsigned)(uintptr_t)(lds_u32*)&sh.cand_val[0];
@@ -693,7 +706,7 @@ __device__ __forceinline__ RowSelection select_row(
                          "s_and_saveexec_b64 %[sv], %[m]\n\t"
                          "ds_add_rtn_u32 %[slot], %[ca], %[four]\n\t"
                          "s_mov_b64 exec, %[sv]"
-                         : [slot] "=&v"(slot[e]), [m] "=&s"(passed[e]), [sv] "=&s"(saved)
+                         : [slot] "+v"(slot[e]), [m] "=&s"(passed[e]), [sv] "=&s"(saved)
                          : [x] "v"(v[e]), [t] "v"(tau), [ca] "v"(ca), [four] "v"(four)
                          : "memory", "scc");
         }
@@ -711,16 +724,20 @@ __device__ __forceinline__ RowSelection select_row(
             asm volatile("" : "+v"(slot[8]), "+v"(slot[9]), "+v"(slot[10]), "+v"(slot[11]),
                          "+v"(slot[12]), "+v"(slot[13]), "+v"(slot[14]), "+v"(slot[15]));
         }
-        // eight columns at a time: their addresses and ids first (every lane, back to back), then only the write
-        // under each column's mask
+        // A slot behind the buffer's end: the pass is lost, nothing is written any more (the counter says so at the end).  Looked
+        // at once per sub-tile and wave; a lane that claimed nothing holds its last claim, or the buffer's start.
+        unsigned top = (unsigned)slot[0];
+#pragma unroll
+        for (int i = 1; i < NVV * N; ++i) top = max(top, (unsigned)slot[i]);
+        if (__ballot(top > last_slot)) return;
+        // eight columns at a time: their ids first (every lane, back to back), then only the write under each column's mask
         static_assert((NVV * N) % 8 == 0, "writes go in blocks of eight columns");
 #pragma unroll
         for (int i0 = 0; i0 < NVV * N; i0 += 8) {
-            unsigned at[8], id[8];
+            unsigned id[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int i = i0 + u;
-                                at[u] = min((unsigned)slot[i], last_slot);
                 id[u] = (unsigned)(x0 + (i / N) * kT * N + i % N);
             }
 #pragma unroll
@@ -730,7 +747,7 @@ __device__ __forceinline__ RowSelection select_row(
                              "ds_write2st64_b32 %[at], %[x], %[id] offset1:%c[o1]\n\t"
                              "s_mov_b64 exec, %[sv]"
                              : [sv] "=&s"(saved)
-                             : [m] "s"(passed[i0 + u]), [at] "v"(at[u]), [id] "v"(id[u]), [x] "v"(v[i0 + u]), [o1] "n"(kCap / 64)
+                             : [m] "s"(passed[i0 + u]), [at] "v"(slot[i0 + u]), [id] "v"(id[u]), [x] "v"(v[i0 + u]), [o1] "n"(kCap / 64)
                              : "memory", "scc");
             }
         }
@@ -739,7 +756,7 @@ __device__ __forceinline__ RowSelection select_row(
                   "ds_write2st64 offset1 reaches cand_id from cand_val");
 
     const bool more = n_sub > T0;                // the row goes on behind the sample
-    const int r_opt = more ? optimistic_rank(k, V, SAMPLE, kCap) : 0;
+    const int r_opt = more ? rank_opt : 0;
     float M = kNegInf;
     double S = 0.0;
     uint32_t key_lo = 0, key_hi = 0;
@@ -785,16 +802,29 @@ __device__ __forceinline__ RowSelection select_row(
                 unpack_vecs(nv0_t{}, tid, &rb[0][0], v, true);
                 bm = add_stats(e0_t{}, v, true);
             }
+            const int target = optimistic ? r_opt : k;
+            bool have_tau = false;
+            // Lower end of the values that the optimistic pass's histogram looks at.  Usually (ranks up to kT - 32) the smallest
+            // of the threads' largest values: every thread holds an element at or above it, so at least kT of the sample's
+            // are, and two thirds of the sample - the crowded middle of the distribution, where rows of 16-bit values put
+            // dozens of elements on one value and an LDS atomic waits for as many others - are left out.  A row that is mostly
+            // masked, or all one value, takes the smallest value above -inf instead.
+            bool narrow = optimistic && target <= kT - 32;
+            for (;;) {
             // smallest value of the sample; the optimistic pass leaves masked vocabulary entries (-inf) out of it,
             // so that the value range it bins is that of the entries a threshold can fall between
             float bn = __builtin_huge_valf();
             bool saw_masked = false;             // (an element in front of or behind the row counts as one: it only costs a
                                                  //  constant row that is cut at both ends a pass that fails)
+            if (narrow) {
+                bn = bm > kNegInf ? bm : bn;
+            } else {
 #pragma unroll
-            for (int e = 0; e < E0; ++e) {
-                const bool above = v[e] > kNegInf;
-                bn = fminf(bn, (optimistic && !above) ? __builtin_huge_valf() : v[e]);
-                saw_masked |= !above;
+                for (int e = 0; e < E0; ++e) {
+                    const bool above = v[e] > kNegInf;
+                    bn = fminf(bn, (optimistic && !above) ? __builtin_huge_valf() : v[e]);
+                    saw_masked |= !above;
+                }
             }
             // key range of the sample
             const float wmax = wave_max(bm), wmin = -wave_max(-bn);
@@ -804,7 +834,6 @@ __device__ __forceinline__ RowSelection select_row(
                 sh.wkey[kW + wave] = short_key<BF16>(__float_as_uint(wmin));
                 sh.wkey[2 * kW + wave] = wave_masked;
             }
-            const int target = optimistic ? r_opt : k;
             const bool one_pass = optimistic && more && n0 > target;
             if (one_pass) zero_hist(sh);         // (for the histogram below: the barrier of the key range serves it too)
             __syncthreads();
@@ -812,7 +841,7 @@ __device__ __forceinline__ RowSelection select_row(
             unsigned masked = 0;
 #pragma unroll
             for (int w = 0; w < kW; ++w) { key_hi = max(key_hi, sh.wkey[w]); key_lo = min(key_lo, sh.wkey[kW + w]); masked |= sh.wkey[2 * kW + w]; }
-            bool have_tau = false;
+            bool again = false;
             if (one_pass) {
                 // Optimistic pass: the threshold only has to be about right (the count at the end of the row
                 // decides), so one histogram pass over a linear scale of the sample's value range does: bin
@@ -825,10 +854,12 @@ __device__ __forceinline__ RowSelection select_row(
                     const float scale = 1.0f / width;
 #pragma unroll
                     for (int e = 0; e < E0; ++e)
-                        if (v[e] > kNegInf) atomicAdd(&sh.hist[min((int)((vmax - v[e]) * scale), kBins - 1)], 1u);
+                        if (v[e] >= vmin) atomicAdd(&sh.hist[min((int)((vmax - v[e]) * scale), kBins - 1)], 1u);
                     __syncthreads();
                     const int n_finite = find_pivot_bin(sh, target);
-                    if (n_finite < target) {
+                    if (n_finite < target && narrow) {
+                        again = true;
+                    } else if (n_finite < target) {
                         // A row that is mostly masked: fewer entries above -inf than the rank aimed at.  Every one
                         // of them becomes a candidate (there are about n_finite * V / SAMPLE, which fits); should
                         // the row hold fewer than k, masked entries fill the record up in id order at the end.
@@ -846,6 +877,9 @@ __device__ __forceinline__ RowSelection select_row(
                         }
                     }
                     __syncthreads();             // (the histogram and the pivot words are reused below)
+                } else if (narrow && vmax < __builtin_huge_valf()) {
+                    again = true;
+                    __syncthreads();
                 } else if (masked && !(vmax > vmin) && vmax < __builtin_huge_valf()) {
                     // masked entries and at most one value above -inf in the whole sample (a vocabulary mask that
                     // leaves a handful of ids): every entry above -inf becomes a candidate
@@ -855,6 +889,9 @@ __device__ __forceinline__ RowSelection select_row(
                     key_lo = short_key<BF16>(0xFF800000u);
                     __syncthreads();
                 }
+            }
+            if (!again) break;                   // (uniform)
+            narrow = false;
             }
             if (!have_tau && more && n0 > target && key_hi > key_lo) {
                 // two histogram passes over the keys in registers: a key with >= target elements of the sample at or above it
@@ -906,9 +943,11 @@ __device__ __forceinline__ RowSelection select_row(
             if (applies) {
 #pragma unroll
                 for (int t = 0; t < T0; ++t) load_sub(RING - T0 + t, rb[t]);
+                int slot[ES];                    // per column: this lane's last claim
+#pragma unroll
+                for (int e = 0; e < ES; ++e) slot[e] = (int)val_addr;
                 auto full = [&](int sub, uint4 (&buf)[SV]) {        // a sub-tile wholly inside the row
                     float v[ES];
-                    int slot[ES];
                     unsigned long long passed[ES];
                     unpack_vecs(sv_t{}, 0, buf, v, false);
                     claim_asm(es_t{}, v, tau, slot, passed);
@@ -919,7 +958,6 @@ __device__ __forceinline__ RowSelection select_row(
                 auto ragged = [&](int sub, uint4 (&buf)[SV]) {      // the last sub-tiles: what lies behind the row is masked
                     if (sub < n_sub) {
                         float v[ES];
-                        int slot[ES];
                         unsigned long long passed[ES];
                         const bool edge = sub + 1 == n_sub;
                         unpack_vecs(sv_t{}, sub * (kT * SV) + tid, buf, v, edge);
@@ -930,11 +968,10 @@ __device__ __forceinline__ RowSelection select_row(
                 };
                 {   // sub-tile 0 may begin in front of the row (rows off the 16-byte boundary): masked like an edge
                     float v[ES];
-                    int slot[ES];
                     unsigned long long passed[ES];
-                    unpack_vecs(sv_t{}, tid, rb[T0], v, true);
+                    unpack_vecs(sv_t{}, tid, rb[T0], v, rv.o > 0);
                     claim_asm(es_t{}, v, tau, slot, passed);
-                    add_sum(es_t{}, v, true, nr);
+                    add_sum(es_t{}, v, rv.o > 0, nr);
                     put_asm(sv_t{}, v, slot, passed, tid * N - rv.o);
                     load_sub(RING, rb[T0]);
                 }
@@ -1227,12 +1264,12 @@ __device__ __forceinline__ void compress_row(
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
     int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
     float* __restrict__ mass, float* __restrict__ lse,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int ahead)
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int ahead, int rank_opt)
 {
     using SH = CompressShared<SMALL ? kCapSmall : kCapBig>;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     SH& sh = *reinterpret_cast<SH*>(smem_raw);
-    const RowSelection sel = select_row<BF16, SMALL, FAST>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept);
+    const RowSelection sel = select_row<BF16, SMALL, FAST>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, rank_opt);
     if (FAST && !sel.done) {                     // (uniform: the verdict was read from LDS behind a barrier)
         if (threadIdx.x == 0) count[row] = kRetryRow;
         return;
@@ -1250,7 +1287,7 @@ __device__ __forceinline__ void compress_row(
         constexpr int NV0 = kCompressSample / (kT * N), PIECES = NV0 * (kT / 8);
         const RowView nv = row_view<BF16>(logits, ld, row + ahead, V);
         const int nq2 = (nv.L + N - 1) / N;
-        const bool spread = V > kCompressSample && optimistic_rank(k, V, kCompressSample, SH::kCap) > 0;
+        const bool spread = V > kCompressSample && rank_opt > 0;
         const int n_spread = (spread && nq2 >= 8 * PIECES + 8) ? NV0 : 0;
 #pragma unroll
         for (int j = 0; j < RING * SV; ++j) {

@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
     int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
     float* __restrict__ mass, float* __restrict__ lse,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept,
-    const SplitHead* __restrict__ heads, const uint2* __restrict__ lists, int n_lists, int cap)
+    const SplitHead* __restrict__ heads, const uint2* __restrict__ lists, int n_lists, int cap, int rank_opt)
 {
     using SH = CompressShared<kCapBig>;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
     const uint64_t* sorted;
     int n;
     for (;;) {
-        if (!ok) sel = select_row<BF16, false, false>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept);
+        if (!ok) sel = select_row<BF16, false, false>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, rank_opt);
         n = min(sel.n_held, k);
         if (sel.n_held <= kT)          sorted = order_top_k<BF16, 1, 1024, 128>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
         else if (sel.n_held <= 2 * kT) sorted = order_top_k<BF16, 2, 2048, 256>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
@@ -356,8 +356,8 @@ hipError_t launch_split_finish(const void* logits, int dtype, int64_t ld, int n_
     const void* const finish = bf ? (const void*)split_finish_kernel<true> : (const void*)split_finish_kernel<false>;
     if (hipError_t e = raise_lds_limit_once(finish, smem, limit_raised[bf], dev)) return e;
     const float inv_T = 1.0f / temperature;
-    if (bf) hipLaunchKernelGGL(split_finish_kernel<true>, dim3(n_rows), dim3(kT), smem, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, heads, lists, p.parts, p.cap);
-    else    hipLaunchKernelGGL(split_finish_kernel<false>, dim3(n_rows), dim3(kT), smem, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, heads, lists, p.parts, p.cap);
+    if (bf) hipLaunchKernelGGL(split_finish_kernel<true>, dim3(n_rows), dim3(kT), smem, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, heads, lists, p.parts, p.cap, compress_rank(k, V, false));
+    else    hipLaunchKernelGGL(split_finish_kernel<false>, dim3(n_rows), dim3(kT), smem, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, heads, lists, p.parts, p.cap, compress_rank(k, V, false));
     return hipGetLastError();
 }
 
