@@ -42,18 +42,23 @@ __host__ __device__ inline int optimistic_rank(int k, int V, int m, int cap, flo
 // The compression of few rows over many workgroups (split.hip): how a row is split, how many of its elements a workgroup
 // hands on (its `rank` largest and what shares the threshold's bin), and how many slots a wave's list has.
 // parts = 0: the call is not split.  Lines of the rule:
-//   * rows: up to kSplitMaxRows rows; beyond that one workgroup per row fills the chip by itself.
+//   * rows (split_max_rows): with one workgroup per row a call takes the time of one row as long as every row has a CU of its
+//     own; split, the first launch's time grows with the rows from about 40 rows on, and the second one's with k.  Measured,
+//     unsplit / split, us, fp32 (bf16) of 151,936: k = 64: 128 rows 28.2 / 23.8 (29.2 / 21.4), 192: 29.8 / 29.8 (29.1 / 25.8);
+//     k = 1024: 96 rows 29.7 / 24.4, 128: 29.6 / 27.2, 160: 29.8 / 30.3; k = 4096: 48 rows 35.4 / 29.9, 96: 35.6 / 36.1.
+//   * V: two workgroups' worth, and eight times k (V = 20,000, k = 4096, 48 rows: 23.2 / 24.1).
 //   * the margin of the rank is optimistic_rank's (4.5 standard deviations of the share of the k largest that falls to one
 //     workgroup); its lists together must fit the candidate buffer of the finishing kernel with room to spare.
 //   * a list holds the rank, a crowded pivot bin and some slack.
-constexpr int kSplitMaxRows = 256;
+constexpr int kSplitMaxRows = 192;
+inline int split_max_rows(int k) { return k <= 256 ? kSplitMaxRows : k <= 1024 ? 128 : 80; }
 constexpr int kSplitMinV = 16384;                // (two workgroups per row)
 constexpr int kSplitNarrowRank = 240;            // ranks for which 256 elements above the histogram's lower end suffice
 constexpr int kSplitMaxParts = 64;               // lists per row (one per lane of a finishing wave): rows of up to half a million elements
 struct SplitPlan { int parts, rank, cap; };
 inline SplitPlan split_plan(int dtype, int64_t rows, int V, int k) {
     const SplitPlan none{0, 0, 0};
-    if (rows < 1 || rows > kSplitMaxRows || V < kSplitMinV || k < 1 || k > kMaxK) return none;
+    if (rows < 1 || V < kSplitMinV || k < 1 || k > kMaxK || rows > split_max_rows(k) || V / 8 < k) return none;
     const int esz = dtype == 1 ? 2 : 4;
     const int nq = (int)(((int64_t)V * esz + 15) / 16) + 1;                  // (a row off the 16-byte boundary spans one vector more)
     const int parts = split_parts(dtype == 1, nq);

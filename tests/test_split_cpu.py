@@ -16,12 +16,15 @@ def B():
 def test_scratch_is_asked_for_where_rows_are_split_only(B):
     f = B.workspace_bytes
     for dt in (B.F32, B.BF16):
-        assert f(B.CALL_COMPRESS, dt, 1, 16384, 64) > 0 and f(B.CALL_COMPRESS, dt, 256, 151936, 4096) > 0
-        assert f(B.CALL_COMPRESS, dt, 257, 151936, 64) == 0          # the rows fill the chip by themselves
+        for rows, k in ((192, 256), (128, 1024), (80, 4096)):        # more rows fill the chip by themselves
+            assert f(B.CALL_COMPRESS, dt, 1, 151936, k) > 0 and f(B.CALL_COMPRESS, dt, rows, 151936, k) > 0
+            assert f(B.CALL_COMPRESS, dt, rows + 1, 151936, k) == 0
+        assert f(B.CALL_COMPRESS, dt, 1, 16384, 64) > 0
+        assert f(B.CALL_COMPRESS, dt, 2, 32767, 4096) == 0           # a record of more than an eighth of the row
         assert f(B.CALL_COMPRESS, dt, 4, 16383, 64) == 0             # too short to split
         assert f(B.CALL_COMPRESS, dt, 1, 1 << 20, 64) == 0           # more lists than a finishing wave has lanes
         assert f(B.CALL_COMPRESS, dt, 0, 32000, 64) == 0
-        sizes = [f(B.CALL_COMPRESS, dt, r, 40000, 100) for r in range(1, 257)]
+        sizes = [f(B.CALL_COMPRESS, dt, r, 40000, 100) for r in range(1, 193)]
         assert all(b > a for a, b in zip(sizes, sizes[1:]))
         # a round's workspace without k is its segment table; with k it holds the scratch of up to that many draft rows as well
         table = f(B.CALL_ROUND, dt, 20, 32000, 0)
