@@ -79,7 +79,8 @@ __global__ __launch_bounds__(kT, 2) void round_stream_kernel(
     }
 }
 
-// The drafter's draw: inverse CDF over the used slots, one wave per row.
+// The drafter's draw from a record of any length: inverse CDF over the used slots, one wave per row.  (Records beyond kMaxK:
+// they do not come from this library's compression.)
 __global__ __launch_bounds__(256) void sample_draft_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ prob, const int32_t* __restrict__ count,
     const float* __restrict__ mass, int k, int n_rows, const float* __restrict__ uniforms,
@@ -121,74 +122,101 @@ __global__ __launch_bounds__(256) void sample_draft_kernel(
     }
 }
 
-// The same draw for records whose rows start on 16-byte boundaries (k a multiple of 4): the wave reads the row
-// with 16-byte loads, 1 KB per instruction, and keeps it in registers; lane l of load i owns the four slots
-// 4 * (64 i + l) ..., so a chunk of 256 slots is summed by a wave scan and the chunks by a running carry.
-template <int CHUNKS>
+// The same draw for records of up to CHUNKS * 256 slots: the wave reads the row in 16-byte pieces, 1 KB per instruction
+// (global loads need four-byte alignment only; the last piece of a row whose length is no multiple of four goes slot by
+// slot), and keeps it in registers; lane l of piece i owns the four slots 4 * (64 i + l) ..., so a chunk of 256 slots is summed
+// by a wave scan and the chunks by a running carry.  What depends on the row alone - count, mass, uniform, probabilities, and
+// with IDS the ids - is asked for in one trip to memory; IDS spares the trip for the drawn id, at the price of reading as many
+// bytes again: for calls that are bound by their trips.
+template <int CHUNKS, bool IDS>
 __global__ __launch_bounds__(256) void sample_draft_vec_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ prob, const int32_t* __restrict__ count,
     const float* __restrict__ mass, int k, int n_rows, const float* __restrict__ uniforms,
     int32_t* __restrict__ tok, float* __restrict__ q_scalar)
 {
+    struct __attribute__((packed, aligned(4))) Four { uint32_t w[4]; };
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     if (row >= n_rows) return;
     const float* p = prob + row * k;
+    const int32_t* ids = idx + row * k;
     int cnt = count[row];
-    cnt = cnt < 0 ? 0 : (cnt > k ? k : cnt);
-    if (cnt == 0) { if (lane == 0) { tok[row] = -1; if (q_scalar) q_scalar[row] = 0.f; } return; }
-    const float4* p4 = reinterpret_cast<const float4*>(p);
-    float4 v[CHUNKS];
-    double incl[CHUNKS];                      // inclusive sum over the chunk up to and including this lane's four
-    double carry[CHUNKS + 1];                 // sum of the chunks in front
-    carry[0] = 0.0;
+    const float mass_row = mass[row], u = uniforms[row];
+    Four v[CHUNKS], t[IDS ? CHUNKS : 1] = {};
 #pragma unroll
     for (int i = 0; i < CHUNKS; ++i) {
         const int s0 = 4 * (i * kWave + lane);
-        v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (s0 < cnt) v[i] = p4[i * kWave + lane];
-        if (s0 + 1 >= cnt) v[i].y = 0.f;      // slots behind the count carry no weight
-        if (s0 + 2 >= cnt) v[i].z = 0.f;
-        if (s0 + 3 >= cnt) v[i].w = 0.f;
+        v[i] = Four{{0u, 0u, 0u, 0u}};
+        if constexpr (IDS) t[i] = v[i];
+        if (s0 + 4 <= k) {
+            v[i] = *reinterpret_cast<const Four*>(p + s0);
+            if constexpr (IDS) t[i] = *reinterpret_cast<const Four*>(ids + s0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (s0 + e < k) {
+                    v[i].w[e] = __float_as_uint(p[s0 + e]);
+                    if constexpr (IDS) t[i].w[e] = (uint32_t)ids[s0 + e];
+                }
+        }
     }
+    cnt = cnt < 0 ? 0 : (cnt > k ? k : cnt);
+    if (cnt == 0) { if (lane == 0) { tok[row] = -1; if (q_scalar) q_scalar[row] = 0.f; } return; }
+    double incl[CHUNKS];                      // inclusive sum over the chunk up to and including this lane's four
+    double carry[CHUNKS + 1];                 // sum of the chunks in front
+    carry[0] = 0.0;
+    auto weight = [&](int i, int e) { return (double)__uint_as_float(v[i].w[e]); };
 #pragma unroll
     for (int i = 0; i < CHUNKS; ++i) {
-        const double mine = (((double)v[i].x + (double)v[i].y) + (double)v[i].z) + (double)v[i].w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[i].w[e] = 4 * (i * kWave + lane) + e < cnt ? v[i].w[e] : 0u;   // slots behind the count carry no weight
+        const double mine = ((weight(i, 0) + weight(i, 1)) + weight(i, 2)) + weight(i, 3);
         incl[i] = wave_scan_incl(mine);
         carry[i + 1] = carry[i] + read_lane(incl[i], kWave - 1);
     }
-    const double target = (double)uniforms[row] * carry[CHUNKS];
-    int pick = -1;
+    const double target = (double)u * carry[CHUNKS];
+    // the chunk and the lane in which the cumulative weight crosses the target (uniform across the wave), then the lane's slot
+    int chunk = -1, owner = 0;
+    Four w = v[0], id = t[0];
+    double upto = 0.0;
 #pragma unroll
     for (int i = 0; i < CHUNKS; ++i) {
-        if (pick < 0) {                       // (uniform across the wave)
-            const unsigned long long ball = __ballot(carry[i] + incl[i] > target);
-            if (ball) {
-                const int owner = __ffsll((long long)ball) - 1;
-                int mine_pick = -1;
-                if (lane == owner) {
-                    const double w4[4] = {(double)v[i].x, (double)v[i].y, (double)v[i].z, (double)v[i].w};
-                    double cum = carry[i] + incl[i] - ((((double)v[i].x + (double)v[i].y) + (double)v[i].z) + (double)v[i].w);
-                    mine_pick = 4 * (i * kWave + lane) + 3;
-#pragma unroll
-                    for (int e = 3; e >= 0; --e) {   // first slot of the four whose cumulative weight exceeds the target
-                        double upto = cum;
-#pragma unroll
-                        for (int f = 0; f <= e; ++f) upto += w4[f];
-                        if (upto > target) mine_pick = 4 * (i * kWave + lane) + e;
-                    }
-                }
-                pick = __shfl(mine_pick, owner, kWave);
-            }
+        const unsigned long long ball = chunk < 0 ? __ballot(carry[i] + incl[i] > target) : 0ull;
+        if (ball) {
+            chunk = i;
+            owner = __ffsll((long long)ball) - 1;
+            w = v[i];
+            if constexpr (IDS) id = t[i];
+            upto = carry[i] + incl[i] - (((weight(i, 0) + weight(i, 1)) + weight(i, 2)) + weight(i, 3));
         }
     }
-    if (pick < 0 || pick >= cnt) {            // rounding: the last slot with weight
-        if (lane == 0) { pick = cnt - 1; while (pick > 0 && !(p[pick] > 0.f)) --pick; }
-        pick = __shfl(pick, 0, kWave);
+    int pick = -1;
+    uint32_t pick_w = 0u, pick_id = 0u;
+    if (chunk >= 0) {
+        int at = 3;                           // first slot of the lane's four whose cumulative weight exceeds the target
+        bool found = false;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            upto += (double)__uint_as_float(w.w[e]);
+            if (!found && upto > target) { at = e; found = true; }
+        }
+        uint32_t x = w.w[0], y = id.w[0];
+#pragma unroll
+        for (int e = 1; e < 4; ++e) { x = at == e ? w.w[e] : x; y = at == e ? id.w[e] : y; }
+        pick = 4 * (chunk * kWave + owner) + __builtin_amdgcn_readlane(at, owner);
+        pick_w = (uint32_t)__builtin_amdgcn_readlane((int)x, owner);
+        pick_id = (uint32_t)__builtin_amdgcn_readlane((int)y, owner);
     }
     if (lane == 0) {
-        tok[row] = idx[row * k + pick];
-        if (q_scalar) q_scalar[row] = p[pick] / mass[row];
+        bool known = true;
+        if (pick < 0 || pick >= cnt) {        // rounding: the last slot with weight
+            pick = cnt - 1;
+            while (pick > 0 && !(p[pick] > 0.f)) --pick;
+            pick_w = __float_as_uint(p[pick]);
+            known = false;
+        }
+        tok[row] = IDS && known ? (int32_t)pick_id : ids[pick];
+        if (q_scalar) q_scalar[row] = __uint_as_float(pick_w) / mass_row;
     }
 }
 
@@ -293,14 +321,16 @@ hipError_t launch_sample_draft(const int32_t* idx, const float* prob, const int3
     if (n_rows == 0) return hipSuccess;
     const int rows_per_block = 256 / kWave;
     const dim3 grid((n_rows + rows_per_block - 1) / rows_per_block);
-    if ((k & 3) == 0 && k <= 16 * 256 && (((uintptr_t)prob) & 15u) == 0) {
-        // rows on 16-byte boundaries: the row in registers, as many 256-slot chunks as k needs
-#define PICOSPEC_SAMPLE_DRAFT(C) \
-        hipLaunchKernelGGL(sample_draft_vec_kernel<C>, grid, dim3(256), 0, stream, idx, prob, count, mass, k, n_rows, uniforms, tok, q_scalar)
-        if (k <= 256)       PICOSPEC_SAMPLE_DRAFT(1);
-        else if (k <= 1024) PICOSPEC_SAMPLE_DRAFT(4);
-        else if (k <= 2048) PICOSPEC_SAMPLE_DRAFT(8);
-        else                PICOSPEC_SAMPLE_DRAFT(16);
+    if (k <= kMaxK) {
+        // the row in registers, as many 256-slot chunks as k needs; up to 512 rows (two waves per CU) the ids as well: such calls
+        // wait for their trips to memory (64 rows of 1024: 5.2 us with a trip of its own for the drawn id)
+        const bool few = n_rows <= 512;
+#define PICOSPEC_SAMPLE_DRAFT(C, I) \
+        hipLaunchKernelGGL((sample_draft_vec_kernel<C, I>), grid, dim3(256), 0, stream, idx, prob, count, mass, k, n_rows, uniforms, tok, q_scalar)
+        if (k <= 256)       { if (few) PICOSPEC_SAMPLE_DRAFT(1, true); else PICOSPEC_SAMPLE_DRAFT(1, false); }
+        else if (k <= 1024) { if (few) PICOSPEC_SAMPLE_DRAFT(4, true); else PICOSPEC_SAMPLE_DRAFT(4, false); }
+        else if (k <= 2048) PICOSPEC_SAMPLE_DRAFT(8, false);
+        else                PICOSPEC_SAMPLE_DRAFT(16, false);
 #undef PICOSPEC_SAMPLE_DRAFT
         static_assert(kMaxK <= 16 * 256, "sixteen chunks hold the longest record");
         return hipGetLastError();

@@ -60,8 +60,8 @@ def _rows(rng, pattern, R, V):
 
 
 # 8192 elements per workgroup: two parts, a block more, the longest row of 64 parts and the first that is not split
-@pytest.mark.parametrize("V,R,k", [(16383, 2, 64), (16384, 2, 64), (16385, 3, 1), (16640, 2, 500), (24576, 256, 32), (24577, 257, 32),
-                                   (50001, 4, 4096), (128256, 2, 10), (151936, 3, 1024), (152064, 1, 4096), (524288 - 64, 1, 4000),
+@pytest.mark.parametrize("V,R,k", [(16383, 2, 64), (16384, 2, 64), (16385, 3, 1), (16640, 2, 500), (24576, 192, 32), (24577, 193, 32),
+                                   (50001, 4, 4096), (40000, 128, 1024), (40000, 80, 4096), (40000, 81, 4096), (32767, 2, 4096), (128256, 2, 10), (151936, 3, 1024), (152064, 1, 4096), (524288 - 64, 1, 4000),
                                    (524289, 1, 100)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_sizes_match_the_oracle_and_one_workgroup_per_row(gpu, pu, ps, V, R, k, dtype):
@@ -156,3 +156,28 @@ def test_rows_behind_the_last_sequence_keep_their_statistics(gpu, ps):
     v = ps.verify(tgt, V, 1.0, off, N, tok, None, torch.rand(N + B, device=gpu), q_scalar=torch.rand(N, device=gpu))
     assert torch.equal(v.tgt_max, tgt.max(1).values)
     assert torch.allclose(v.tgt_lse, torch.logsumexp(tgt, 1), rtol=1e-5)
+
+
+@pytest.mark.parametrize("k", [1, 3, 10, 255, 256, 257, 777, 1021, 1024, 1025, 2047, 2049, 4093, 4096])
+@pytest.mark.parametrize("R", [1, 5, 513])
+def test_draw_from_records_of_every_length(gpu, pu, ps, k, R):
+    """The drafter's draw against the oracle: pieces of four slots, the last one cut, counts of 1 to k, up to 512 rows and more."""
+    _announce("draw", k, R)
+    rng = np.random.default_rng(k * 1000 + R)
+    p = np.sort(rng.random((R, k)).astype(np.float32) ** 4, axis=1)[:, ::-1].copy()
+    cnt = rng.integers(1, k + 1, R).astype(np.int32)
+    cnt[0] = k
+    p[np.arange(k)[None, :] >= cnt[:, None]] = 0
+    ids = rng.integers(0, 1 << 20, (R, k)).astype(np.int32)
+    mass = p.astype(np.float64).sum(1).astype(np.float32)
+    u = rng.random(R, dtype=np.float32)
+    q = oracle.Compressed(ids, p.astype(np.float64), cnt, mass.astype(np.float64), mass.astype(np.float64), np.ones(R), k)
+    tok, slot, margin = oracle.sample_draft(q, u)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(gpu)
+    g_tok, g_q = ps.sample_draft(ps.Compressed(d(ids), d(p), d(cnt), d(mass), d(mass), k), d(u))
+    torch.cuda.synchronize()
+    # (fp64 sums in another order: a uniform within 1e-12 of a step is the only way to differ)
+    sure = margin > 1e-12
+    assert sure.mean() > 0.99 and np.array_equal(pu.n(g_tok)[sure], tok[sure])
+    want = p[np.arange(R), slot].astype(np.float64) / mass
+    pu.assert_close(pu.n(g_q)[sure], want[sure], pu.RTOL, "q_scalar", atol=1e-37)
