@@ -156,16 +156,25 @@ inline StatsShape round_stats_shape(int dtype, int V) {
 struct SegHeader { int32_t magic, seg_vecs, stride, rows; };
 constexpr int32_t kSegMagic = 0x53454731;        // entries (sum of 2^(z c - r), r)
 constexpr int32_t kSegMagicSplit = 0x53454732;   // split layout: entries (sum of 2^(z c - r), m), m = the segment's largest logit, r = m c (split_ref)
-// Calls of few target rows spread every row's statistics over many workgroups: each wave leaves the entries of a few
-// segments, nothing else, and the kernel that needs the statistics forms them from the row's table.  A row's workgroup is
-// bound by its own vector ALUs (90 rows of 151,936 fp32: 17.8 us at one row per CU); up to one row per CU leaves room for that.
-constexpr int kSplitStatsRows = 256;
-constexpr int kStatsSpwF32 = 2, kStatsSpwBF16 = 4;   // segments per wave: eight loads in flight per lane
-inline int stats_parts(int dtype, int stride) {      // workgroups of four waves per row
-    const int per = 4 * (dtype == 1 ? kStatsSpwBF16 : kStatsSpwF32);
-    return (stride + per - 1) / per;
+// Calls whose rows do not fill the CUs with one workgroup per row spread every row's statistics over many workgroups: each wave
+// leaves the entries of two segments of 256 vectors, nothing else, and the kernel that needs the statistics forms them from the
+// row's table.  One workgroup per row is bound by the vector ALUs of one CU and by the rows of its last generation.
+constexpr int kSplitStatsPositions = 256;            // ... of a sequence that the deciding workgroup keeps in LDS
+constexpr int kSplitStatsNV = 4, kSplitStatsSpw = 2; // vectors per lane and segment, segments per wave: eight loads in flight per lane
+inline StatsShape split_stats_shape(int dtype, int V) {
+    const int esz = dtype == 1 ? 2 : 4;
+    const int64_t nq_max = ((int64_t)V * esz + 15) / 16 + 1;
+    return StatsShape{256, kSplitStatsNV, 64 * kSplitStatsNV, (int)((nq_max + 64 * kSplitStatsNV - 1) / (64 * kSplitStatsNV))};
 }
-inline bool split_stats_serves(int64_t rows, int V) { return rows >= 1 && rows <= kSplitStatsRows && V >= kSplitMinV; }
+inline int split_stats_parts(int stride) { return (stride + 4 * kSplitStatsSpw - 1) / (4 * kSplitStatsSpw); }   // workgroups of four waves per row
+// Where: a row per CU has no last generation to shorten when it is full or nearly so (256 rows x 151 936: 19.3 us per row, 20.0
+// spread, bf16 verification; 512: 31.6, 30.3), and gains most just behind one (128: 17.8, 14.1; 384: 28.4, 25.1; fp32 128: 20.8,
+// 19.1; 384: 43.4, 42.0).  From some generations on there is nothing left to gain (768: 42.3, 41.0; 1024: 51.8, 50.9; fp32
+// 768: 74.3, 76.3), nor below kSplitMinV, where a row is a few segments.
+constexpr int kSplitStatsRowsF32 = 512, kSplitStatsRowsBF16 = 1024;
+inline bool split_stats_serves(int dtype, int64_t rows, int V) {
+    return rows >= 1 && rows <= (dtype == 1 ? kSplitStatsRowsBF16 : kSplitStatsRowsF32) && (rows - 1) % 256 < 224 && V >= kSplitMinV;
+}
 inline size_t seg_table_bytes(int dtype, int64_t rows, int V) {
     return sizeof(SegHeader) + (size_t)rows * (size_t)stats_shape(dtype, rows, V).stride * 8;
 }

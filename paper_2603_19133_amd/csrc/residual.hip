@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kThreads) void decide_seg_kernel(
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
     int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags, int n_rows)
 {
-    __shared__ SplitStats s_stats[SPLIT ? kSplitStatsRows : 1];
+    __shared__ SplitStats s_stats[SPLIT ? kSplitStatsPositions : 1];
     int2 rows = make_int2(0, 0);
     const int first = accept_sequence<BF16, SPLIT>(blockIdx.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
                                                    q_count, q_mass, k, renorm, nullptr, uniforms, tgt_max, tgt_sum,
@@ -109,7 +109,7 @@ hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V,
     if (seg_table) {
         if (B == 0) return hipSuccess;
         const float it = 1.0f / temperature;
-        const StatsShape sh = stats_shape(dtype, n_rows, V);
+        const StatsShape sh = split_stats_serves(dtype, n_rows, V) ? split_stats_shape(dtype, V) : stats_shape(dtype, n_rows, V);   // (as the verification laid it out)
 #define PICOSPEC_RESIDUAL(BF, RT) \
         hipLaunchKernelGGL((residual_seg_kernel<BF, RT>), dim3(B), dim3(RT), 0, stream, tgt_logits, ld, V, it, seq_off, n_accept, tgt_max, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags)
 #define PICOSPEC_RESIDUAL_RT(BF) \
@@ -147,7 +147,7 @@ hipError_t launch_decide(const void* tgt_logits, int dtype, int64_t ld, int V, f
     if (seg_table) {
         if (B == 0) return hipSuccess;
         const float it = 1.0f / temperature;
-        const StatsShape sh = small_round_table ? round_stats_shape(dtype, V) : stats_shape(dtype, n_rows, V);
+        const StatsShape sh = split_table ? split_stats_shape(dtype, V) : small_round_table ? round_stats_shape(dtype, V) : stats_shape(dtype, n_rows, V);
 #define PICOSPEC_DECIDE(BF, SP, RT) \
         hipLaunchKernelGGL((decide_seg_kernel<BF, SP, RT>), dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, it, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags, (int)n_rows)
 #define PICOSPEC_DECIDE_RT(BF, SP) \

@@ -248,16 +248,15 @@ __global__ __launch_bounds__(kSplitThreads) void split_round_kernel(
     SplitHead* __restrict__ heads, uint2* __restrict__ lists, int parts,
     const void* __restrict__ tgt_logits, int64_t ld_t, int stats_per_row, SegHeader* __restrict__ header, int seg_stride)
 {
-    constexpr int NV = BF16 ? 2 : 4;
     const int x = blockIdx.x, y = blockIdx.y;
     if (y < n_draft) {
         if (x < parts) split_select<BF16>(y, x, parts, draft_logits, ld_d, V, inv_T, rank, cap, narrow, heads, lists, nullptr, nullptr);
         return;
     }
     if (y == n_draft && x == 0 && threadIdx.x == 0)
-        *header = SegHeader{kSegMagicSplit, NV * kWave, seg_stride, (int32_t)gridDim.y - n_draft};
+        *header = SegHeader{kSegMagicSplit, kSplitStatsNV * kWave, seg_stride, (int32_t)gridDim.y - n_draft};
     if (x < stats_per_row)
-        row_stats_parts<BF16, NV, BF16 ? kStatsSpwBF16 : kStatsSpwF32>(y - n_draft, x, tgt_logits, ld_t, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
+        row_stats_parts<BF16, kSplitStatsNV, kSplitStatsSpw>(y - n_draft, x, tgt_logits, ld_t, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
 }
 
 template <bool BF16>
@@ -384,8 +383,8 @@ hipError_t launch_split_round(const void* draft_logits, int dtype, int64_t ld_d,
                               const void* tgt_logits, int64_t ld_t, int n_target, void* seg_table, void* scratch, hipStream_t stream)
 {
     const SplitPlan p = split_plan(dtype, n_draft, V, k);
-    const StatsShape sh = stats_shape(dtype, n_target, V);
-    const int per_row = stats_parts(dtype, sh.stride);
+    const StatsShape sh = split_stats_shape(dtype, V);
+    const int per_row = split_stats_parts(sh.stride);
     const float inv_T = 1.0f / temperature;
     SplitHead* const heads = (SplitHead*)scratch;
     uint2* const lists = (uint2*)(heads + (size_t)n_draft * p.parts);

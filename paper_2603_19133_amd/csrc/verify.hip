@@ -49,14 +49,14 @@ __global__ __launch_bounds__(THREADS) void row_stats_range_kernel(
 
 // Few rows: the segment tables alone (split layout).  grid: (workgroups per row, rows), or (.., gamma_max + 1, B) for the
 // target rows of a range of positions.
-template <bool BF16, int NV, int SPW>
+template <bool BF16>
 __global__ __launch_bounds__(256) void row_stats_parts_kernel(
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int n_rows, int seg_stride,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end,
     SegHeader* __restrict__ header)
 {
     if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
-        *header = SegHeader{kSegMagicSplit, NV * kWave, seg_stride, n_rows};
+        *header = SegHeader{kSegMagicSplit, kSplitStatsNV * kWave, seg_stride, n_rows};
     int64_t row = blockIdx.y;
     if (seq_off) {                                    // position t of sequence b, or nothing
         const int b = blockIdx.z, t = blockIdx.y, d0 = seq_off[b];
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void row_stats_parts_kernel(
         if (t < begin || t > end) return;
         row = (int64_t)d0 + b + t;
     }
-    row_stats_parts<BF16, NV, SPW>(row, (int)blockIdx.x, logits, ld, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
+    row_stats_parts<BF16, kSplitStatsNV, kSplitStatsSpw>(row, (int)blockIdx.x, logits, ld, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
 }
 
 // The statistics of rows whose table stands in the split layout: one wave per row.
@@ -151,10 +151,10 @@ hipError_t launch_row_stats_parts(const void* logits, int dtype, int64_t ld, int
 {
     if (n_rows == 0 || (seq_off && B == 0)) return hipSuccess;
     const float inv_T = 1.0f / temperature;
-    const StatsShape sh = stats_shape(dtype, n_rows, V);      // (fp32 NV = 4, bf16 NV = 2 at the row counts that are split)
-    const dim3 grid(stats_parts(dtype, sh.stride), seq_off ? gamma_max + 1 : n_rows, seq_off ? B : 1);
-    if (dtype == 1) hipLaunchKernelGGL((row_stats_parts_kernel<true, 2, kStatsSpwBF16>), grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, (SegHeader*)seg_table);
-    else            hipLaunchKernelGGL((row_stats_parts_kernel<false, 4, kStatsSpwF32>), grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, (SegHeader*)seg_table);
+    const StatsShape sh = split_stats_shape(dtype, V);
+    const dim3 grid(split_stats_parts(sh.stride), seq_off ? gamma_max + 1 : n_rows, seq_off ? B : 1);
+    if (dtype == 1) hipLaunchKernelGGL(row_stats_parts_kernel<true>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, (SegHeader*)seg_table);
+    else            hipLaunchKernelGGL(row_stats_parts_kernel<false>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, (SegHeader*)seg_table);
     return hipGetLastError();
 }
 
@@ -163,7 +163,7 @@ hipError_t launch_row_stats_finish(const void* logits, int dtype, int64_t ld, in
 {
     if (n_rows == 0) return hipSuccess;
     const float inv_T = 1.0f / temperature;
-    const StatsShape sh = stats_shape(dtype, n_rows, V);
+    const StatsShape sh = split_stats_shape(dtype, V);
     const dim3 grid((n_rows + 3) / 4);
     if (dtype == 1) hipLaunchKernelGGL(row_stats_finish_kernel<true>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, row_max, row_sum, row_lse);
     else            hipLaunchKernelGGL(row_stats_finish_kernel<false>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, row_max, row_sum, row_lse);
@@ -181,7 +181,7 @@ hipError_t launch_accept(const void* tgt_logits, int dtype, int64_t ld, int V, f
 {
     if (B == 0) return hipSuccess;
     const float inv_T = 1.0f / temperature;
-    const StatsShape sh = stats_shape(dtype, n_rows, V);
+    const StatsShape sh = split_stats_shape(dtype, V);
 #define PICOSPEC_ACCEPT(BF, TA) \
     hipLaunchKernelGGL((accept_kernel<BF, TA>), dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, inv_T, B, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, q_scalar, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok, flags, pos_begin, pos_end, (const SegHeader*)split_table, sh.seg_vecs, sh.stride, (pos_begin || pos_end) ? 0 : (int)n_rows)
     if (split_table) { if (dtype == 1) PICOSPEC_ACCEPT(true, true); else PICOSPEC_ACCEPT(false, true); }

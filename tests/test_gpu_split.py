@@ -158,6 +158,36 @@ def test_rows_behind_the_last_sequence_keep_their_statistics(gpu, ps):
     assert torch.allclose(v.tgt_lse, torch.logsumexp(tgt, 1), rtol=1e-5)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("R", [224, 225, 257, 300, 480, 481, 992, 993])
+def test_long_sequences_on_either_side_of_the_rule(gpu, ps, monkeypatch, R, dtype):
+    """One sequence of R - 1 drafts, rejected at its last or its first but two: the edges of the rule by rows, and positions behind
+    those whose statistics the deciding workgroup keeps in LDS."""
+    _announce("split statistics of long sequences", R, dtype)
+    V, k, T, N = 16384, 64, 0.9, R - 1
+    g = torch.Generator(device=gpu)
+    g.manual_seed(R)
+    tgt = (torch.randn((R, V), device=gpu, generator=g) * 2).to(dtype)
+    q = ps.compress(tgt[:N].contiguous(), V, T, k)               # (mass < 1: q > p on every entry of the record)
+    off = torch.tensor([0, N], dtype=torch.int32, device=gpu)
+    tok = q.idx[:, 0].contiguous()
+    for reject in (N - 1, 2):
+        u = torch.zeros(R, device=gpu)
+        u[reject], u[-1] = 0.9999999, 0.37
+        res = []
+        for split in (True, False):
+            if not split:
+                monkeypatch.setattr(ps, "_split_stats", lambda *a: False)
+            res.append(ps.verify_sample(tgt, V, T, off, N, tok, q, u))
+            monkeypatch.undo()
+        (v, r), (v0, r0) = res
+        assert int(v.n_accept[0]) == reject and int(v0.n_accept[0]) == reject and not v.flags.any() and not r.flags.any()
+        assert torch.equal(v.tgt_max, tgt.float().max(1).values)
+        assert torch.allclose(v.tgt_lse.double(), torch.logsumexp(tgt.double() / T, 1), rtol=1e-6, atol=2e-6)
+        assert torch.allclose(v.p_tok, v0.p_tok, rtol=2e-6, atol=0)
+        assert torch.equal(r.out_tok, r0.out_tok) and torch.allclose(r.resid_mass, r0.resid_mass, rtol=1e-5, atol=1e-7)
+
+
 @pytest.mark.parametrize("k", [1, 3, 10, 255, 256, 257, 777, 1021, 1024, 1025, 2047, 2049, 4093, 4096])
 @pytest.mark.parametrize("R", [1, 5, 513])
 def test_draw_from_records_of_every_length(gpu, pu, ps, k, R):
