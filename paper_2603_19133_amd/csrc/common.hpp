@@ -489,9 +489,16 @@ __device__ __forceinline__ void row_stats_seg_row(
     }
 }
 
+// f(FROM) + .. + f(FROM + N - 1) by halves: as many additions as one after the other, log2(N) roundings deep instead of N
+template <int FROM, int N, typename F>
+__device__ __forceinline__ float tree_sum(const F& f) {
+    if constexpr (N == 1) return f(FROM);
+    else return tree_sum<FROM, N / 2>(f) + tree_sum<FROM + N / 2, N / 2>(f);
+}
+
 // The segment table of part `part` of a row, and nothing else (calls of few rows, whose statistics are formed from the table):
 // a workgroup of four waves, each wave SPW consecutive segments of NV * 64 vectors whose loads are all in flight at once.
-// Entry: (sum of 2^(z c - r), m), m = the segment's largest logit and r = split_ref(m, c).
+// Entry: (sum of 2^(z c - r), m), m = the segment's largest logit and r = split_ref(m, c).  The lanes' sums are added in fp64.
 __device__ __forceinline__ bool split_ref_fused(float m, float c) { return fabsf(m * c) < __builtin_huge_valf(); }
 // m c as the sums' reference: rounded to fp32 as in the fused form of their terms; exact where that overflows (a segment of
 // nothing but masked entries of the type's lowest value), whose terms are formed as (z - m) c
@@ -546,14 +553,12 @@ __device__ __forceinline__ void row_stats_parts(
         float acc = 0.f;
         if (split_ref_fused(m, c)) {                  // (uniform)
             const float nr = -(m * c);
-#pragma unroll
-            for (int e = 0; e < E; ++e) acc += __builtin_amdgcn_exp2f(fmaf(v[e], c, nr));
+            acc = tree_sum<0, E>([&](int e) { return __builtin_amdgcn_exp2f(fmaf(v[e], c, nr)); });
         } else if (m > kNegInf) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) acc += exp_stream(v[e], m, c);
+            acc = tree_sum<0, E>([&](int e) { return exp_stream(v[e], m, c); });
         }
-        const float t = wave_sum_last(acc);
-        if (lane == kWave - 1) seg_row[s] = make_float2(t, m);
+        const float t = (float)wave_sum((double)acc);
+        if (lane == 0) seg_row[s] = make_float2(t, m);
     }
 }
 
