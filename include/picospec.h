@@ -188,6 +188,19 @@ int picospec_sample_residual(const void* tgt_logits, int dtype, int64_t ld, int3
                              void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * The same where no verification left a table: the workspace (optional, of the same size) is scratch, whatever it holds.  A call
+ * of up to 1024 sequences and records of up to 1024 entries then forms the table of the rows it draws from, every row spread over many workgroups, in a launch of
+ * its own (the sums are formed in another order and agree to rounding).
+ */
+int picospec_sample_residual_ws(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float temperature,
+                                int32_t B, int32_t n_draft, const int32_t* seq_off, const int32_t* n_accept,
+                                const float* tgt_max, const float* tgt_sum,
+                                const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
+                                int32_t k, int renorm, const float* uniforms,
+                                int32_t* out_tok, float* resid_mass, uint32_t* flags,
+                                void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * ---- The paper's own direction of the sparse record (Section 3.3, last part) -------------------
  * The edge uplinks the scalars q_1..q_gamma (picospec_verify with q_scalar), the cloud verifies,
  * and only on a rejection at position j it sends the Top-K record of the TARGET distribution P_j

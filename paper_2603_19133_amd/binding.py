@@ -25,7 +25,7 @@ LIMIT_MAX_K, LIMIT_MAX_V = 0, 1
 WIRE_FP32, WIRE_FP16, WIRE_BF16 = 0, 1, 2
 WIRE_BAD_HEADER, WIRE_BAD_BATCH, WIRE_CLAMPED, WIRE_TRUNCATED = 1, 2, 4, 8
 
-EXPORTS = ("picospec_round", "picospec_verify_sample", "picospec_verify_sample_static", "picospec_static_scratch_bytes", "picospec_compress", "picospec_sample_draft", "picospec_verify", "picospec_verify_range", "picospec_sample_residual",
+EXPORTS = ("picospec_round", "picospec_verify_sample", "picospec_verify_sample_static", "picospec_static_scratch_bytes", "picospec_compress", "picospec_sample_draft", "picospec_verify", "picospec_verify_range", "picospec_sample_residual", "picospec_sample_residual_ws",
            "picospec_row_stats", "picospec_row_stats_ws", "picospec_compress_rejected", "picospec_resample_sparse",
            "picospec_pack_downlink", "picospec_unpack_downlink", "picospec_pack_uplink", "picospec_unpack_uplink",
            "picospec_downlink_bytes_max", "picospec_uplink_bytes", "picospec_max_load_byte", "picospec_check_device", "picospec_probe_clock",
@@ -61,6 +61,7 @@ lib.picospec_static_scratch_bytes.argtypes = []
 lib.picospec_static_scratch_bytes.restype = _i64
 lib.picospec_sample_residual.argtypes = [_p, C.c_int, _i64, _i32, _f, _i32, _i32, _p, _p, _p, _p, _p, _p, _p, _p,
                                          _i32, C.c_int, _p, _p, _p, _p, _p, _sz, _p]
+lib.picospec_sample_residual_ws.argtypes = lib.picospec_sample_residual.argtypes
 lib.picospec_row_stats.argtypes = [_p, C.c_int, _i64, _i32, _i32, _f, _p, _p, _p, _p]
 lib.picospec_row_stats_ws.argtypes = [_p, C.c_int, _i64, _i32, _i32, _f, _p, _p, _p, _p, _sz, _p]
 lib.picospec_compress_rejected.argtypes = [_p, C.c_int, _i64, _i32, _f, _i32, _i32, _p, _p, _i32, _f,
@@ -87,7 +88,7 @@ lib.picospec_limit.argtypes = [C.c_int]
 lib.picospec_limit.restype = _i64
 lib.picospec_strerror.argtypes = [C.c_int]
 lib.picospec_strerror.restype = C.c_char_p
-for _n in ("picospec_compress", "picospec_sample_draft", "picospec_verify", "picospec_sample_residual",
+for _n in ("picospec_compress", "picospec_sample_draft", "picospec_verify", "picospec_sample_residual", "picospec_sample_residual_ws",
            "picospec_row_stats", "picospec_row_stats_ws", "picospec_compress_rejected", "picospec_resample_sparse", "picospec_version",
            "picospec_pack_downlink", "picospec_unpack_downlink", "picospec_pack_uplink", "picospec_unpack_uplink",
            "picospec_verify_range", "picospec_round"):
@@ -307,6 +308,11 @@ def static_scratch_bytes() -> int:
     return int(lib.picospec_static_scratch_bytes())
 
 
+def _residual_split(dt: int, B: int, V: int, k: int) -> bool:
+    """Whether a draw that is given no table makes one of the rows it draws from (residual_split_serves in csrc/kernels.hpp)."""
+    return 0 < B <= 1024 and k <= 1024 and V * (2 if dt == 1 else 4) > 65536 and (k <= 256 or B <= 128 or B > 256)
+
+
 def sample_residual(tgt_logits: torch.Tensor, V: int, temperature: float, seq_off: torch.Tensor, n_draft: int,
                     ver: Verified, q: Compressed, uniforms: torch.Tensor, renorm: int = 1,
                     out: Residual | None = None, n_accept: torch.Tensor | None = None,
@@ -316,10 +322,13 @@ def sample_residual(tgt_logits: torch.Tensor, V: int, temperature: float, seq_of
     dt, ld, _ = _logits_2d(tgt_logits)
     B = seq_off.shape[0] - 1
     out = out or alloc_residual(B, tgt_logits.device)
-    _check(_nat.sample_residual(tgt_logits, dt, ld, V, temperature, B, n_draft, seq_off,
-                              ver.n_accept if n_accept is None else n_accept, ver.tgt_max, ver.tgt_sum,
-                              q.idx, q.prob, q.count, q.mass, q.k, renorm, uniforms, out.out_tok, out.resid_mass, out.flags,
-                              workspace, _stream()))
+    call = _nat.sample_residual
+    if workspace is None and _residual_split(dt, B, V, q.k):
+        call, workspace = _nat.sample_residual_ws, _nat.scratch(tgt_logits, CALL_SAMPLE_RESIDUAL, dt, n_draft + B, V, 0)
+    _check(call(tgt_logits, dt, ld, V, temperature, B, n_draft, seq_off,
+                ver.n_accept if n_accept is None else n_accept, ver.tgt_max, ver.tgt_sum,
+                q.idx, q.prob, q.count, q.mass, q.k, renorm, uniforms, out.out_tok, out.resid_mass, out.flags,
+                workspace, _stream()))
     return out
 
 

@@ -423,13 +423,14 @@ int picospec_verify_range(const void* tgt_logits, int dtype, int64_t ld, int32_t
                        true, pos_begin, pos_end, gamma_max, workspace, workspace_bytes, stream);
 }
 
-int picospec_sample_residual(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float temperature,
+namespace {
+int sample_residual_impl(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float temperature,
                              int32_t B, int32_t n_draft, const int32_t* seq_off, const int32_t* n_accept,
                              const float* tgt_max, const float* tgt_sum,
                              const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
                              int32_t k, int renorm, const float* uniforms,
                              int32_t* out_tok, float* resid_mass, uint32_t* flags,
-                             void* workspace, size_t workspace_bytes, void* stream)
+                             void* workspace, size_t workspace_bytes, bool own_table, void* stream)
 {
     if (B < 0 || n_draft < 0) return PICOSPEC_EINVAL;
     const int64_t rows = (int64_t)n_draft + B;
@@ -441,9 +442,38 @@ int picospec_sample_residual(const void* tgt_logits, int dtype, int64_t ld, int3
     if (n_draft > 0 && (k < 1 || !q_idx || !q_prob || !q_count || !q_mass)) return PICOSPEC_EINVAL;
     if (n_draft > 0 && k > kMaxK) return PICOSPEC_EUNSUPPORTED;   // records come from picospec_compress
     if (int rc = check_workspace(PICOSPEC_CALL_SAMPLE_RESIDUAL, dtype, rows, V, k, workspace, workspace_bytes)) return rc;
+    if (own_table && workspace && residual_split_serves(dtype, B, V, k))
+        return hip_status(launch_residual_split(tgt_logits, dtype, ld, V, temperature, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass, k,
+                                                renorm, uniforms, out_tok, resid_mass, flags, workspace, rows, (hipStream_t)stream));
+    if (own_table) workspace = nullptr;
     return hip_status(launch_residual(tgt_logits, dtype, ld, V, temperature, B, seq_off, n_accept, tgt_max, tgt_sum,
                                       q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass,
                                       flags, workspace, rows, (hipStream_t)stream));
+}
+}  // namespace
+
+int picospec_sample_residual(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float temperature,
+                             int32_t B, int32_t n_draft, const int32_t* seq_off, const int32_t* n_accept,
+                             const float* tgt_max, const float* tgt_sum,
+                             const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
+                             int32_t k, int renorm, const float* uniforms,
+                             int32_t* out_tok, float* resid_mass, uint32_t* flags,
+                             void* workspace, size_t workspace_bytes, void* stream)
+{
+    return sample_residual_impl(tgt_logits, dtype, ld, V, temperature, B, n_draft, seq_off, n_accept, tgt_max, tgt_sum, q_idx, q_prob, q_count,
+                                q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, workspace, workspace_bytes, false, stream);
+}
+
+int picospec_sample_residual_ws(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float temperature,
+                             int32_t B, int32_t n_draft, const int32_t* seq_off, const int32_t* n_accept,
+                             const float* tgt_max, const float* tgt_sum,
+                             const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
+                             int32_t k, int renorm, const float* uniforms,
+                             int32_t* out_tok, float* resid_mass, uint32_t* flags,
+                             void* workspace, size_t workspace_bytes, void* stream)
+{
+    return sample_residual_impl(tgt_logits, dtype, ld, V, temperature, B, n_draft, seq_off, n_accept, tgt_max, tgt_sum, q_idx, q_prob, q_count,
+                                q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, workspace, workspace_bytes, true, stream);
 }
 
 size_t picospec_workspace_bytes(int which_call, int dtype, int32_t rows, int32_t V, int32_t k)

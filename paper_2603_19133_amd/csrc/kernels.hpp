@@ -175,6 +175,17 @@ constexpr int kSplitStatsRowsF32 = 512, kSplitStatsRowsBF16 = 1024;
 inline bool split_stats_serves(int dtype, int64_t rows, int V) {
     return rows >= 1 && rows <= (dtype == 1 ? kSplitStatsRowsBF16 : kSplitStatsRowsF32) && (rows - 1) % 256 < 224 && V >= kSplitMinV;
 }
+// Where a draw that was given no table makes one of the rows it draws from (one workgroup per row passes over its row twice, and
+// is bound by the vector ALUs of one CU): 24 sequences x 33 001 fp32, k = 70: 17.0 -> 11.8 us; 64 x 151 936, k = 64: fp32 29.5 ->
+// 15.4, bf16 24.7 -> 13.2; 512: 73.4 -> 54.7, 50.4 -> 32.2; 1024: 139 -> 105, 98.7 -> 56.7.  The draw from a table gathers one logit per
+// record entry: long records cost more than the second pass (256 x 151 936 bf16, k = 4096: 28.0, 37.8), and so do those of up to
+// 1024 entries where the pass has the chip filled once (256 x 64 000 bf16, k = 1024: 17.8, 19.2); on rows of up to 64 KB the
+// pass is as fast as the second launch (256 x 16 384 bf16, k = 64: 10.8, 12.3).
+constexpr int kResidualSplitSeqs = 1024, kResidualSplitK = 1024;
+inline bool residual_split_serves(int dtype, int64_t B, int V, int k) {
+    if (B < 1 || B > kResidualSplitSeqs || k > kResidualSplitK || (int64_t)V * (dtype == 1 ? 2 : 4) <= 65536) return false;
+    return k <= 256 || B <= 128 || B > 256;
+}
 inline size_t seg_table_bytes(int dtype, int64_t rows, int V) {
     return sizeof(SegHeader) + (size_t)rows * (size_t)stats_shape(dtype, rows, V).stride * 8;
 }
@@ -191,7 +202,7 @@ hipError_t launch_row_stats(const void* logits, int dtype, int64_t ld, int n_row
 // the table of the rows alone, in the split layout (split_stats_serves): seq_off == nullptr: rows 0 .. n_rows - 1; else the
 // target rows pos_begin[b]..pos_end[b] of every sequence (nullable: 0 / gamma_b)
 hipError_t launch_row_stats_parts(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature, int B, int gamma_max, const int32_t* seq_off, const int32_t* pos_begin, const int32_t* pos_end,
-                                  void* seg_table, hipStream_t stream);
+                                  void* seg_table, hipStream_t stream, const int32_t* n_accept = nullptr);   // n_accept: every sequence's row at that position only
 // ... and the statistics from it
 hipError_t launch_row_stats_finish(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
                                    const void* seg_table, float* row_max, float* row_sum, float* row_lse, hipStream_t stream);
@@ -221,6 +232,13 @@ hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V,
                            const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
                            int k, int renorm, const float* uniforms,
                            int32_t* out_tok, float* resid_mass, uint32_t* flags, const void* seg_table, int64_t n_rows, hipStream_t stream);
+// the same with a scratch table of its own (residual_split_serves): one launch spreads the sequences' rows at n_accept over
+// many workgroups, and the draw reads their segments
+hipError_t launch_residual_split(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
+                                 int B, const int32_t* seq_off, const int32_t* n_accept, const float* tgt_max,
+                                 const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
+                                 int k, int renorm, const float* uniforms,
+                                 int32_t* out_tok, float* resid_mass, uint32_t* flags, void* scratch, int64_t n_rows, hipStream_t stream);
 
 // (launch_accept: split_table non-null: the rows' statistics are formed from that table, tgt_max / tgt_sum / tgt_lse written)
 // acceptance and residual draw of every sequence in one launch; split_table: the table holds the split layout, and the rows'

@@ -155,12 +155,13 @@ PyObject* n_verify_sample_static(PyObject*, PyObject* const* v, Py_ssize_t n) {
     });
 }
 
+template <auto CALL>
 PyObject* n_sample_residual(PyObject*, PyObject* const* v, Py_ssize_t n) {
     return enter(v, n, [](Args& a) {
         auto t = target(a); auto na = a.ptr<int32_t>(); auto mx = a.ptr<float>(); auto sm = a.ptr<float>(); auto q = records(a); auto renorm = a.i32();
         auto uni = a.ptr<float>(); auto d = draw(a); auto ws = a.buffer(); auto s = a.stream();
-        return [=] { return picospec_sample_residual(t.z, t.dt, t.ld, t.V, t.T, t.B, t.N, t.off, na, mx, sm, q.idx, q.prob, q.count, q.mass, q.k, renorm, uni,
-                                                     d.tok, d.mass, d.fl, ws.p, ws.bytes, s); };
+        return [=] { return CALL(t.z, t.dt, t.ld, t.V, t.T, t.B, t.N, t.off, na, mx, sm, q.idx, q.prob, q.count, q.mass, q.k, renorm, uni,
+                                 d.tok, d.mass, d.fl, ws.p, ws.bytes, s); };
     });
 }
 
@@ -311,7 +312,7 @@ PyObject* n_empty(PyObject*, PyObject* const* v, Py_ssize_t n) {
 PyMethodDef methods[] = {
     FAST("compress", n_compress), FAST("sample_draft", n_sample_draft), FAST("verify", n_verify), FAST("verify_range", n_verify_range),
     FAST("round", n_round), FAST("verify_sample", n_verify_sample), FAST("verify_sample_static", n_verify_sample_static),
-    FAST("sample_residual", n_sample_residual), FAST("row_stats", n_row_stats), FAST("compress_rejected", n_compress_rejected),
+    FAST("sample_residual", n_sample_residual<picospec_sample_residual>), FAST("sample_residual_ws", n_sample_residual<picospec_sample_residual_ws>), FAST("row_stats", n_row_stats), FAST("compress_rejected", n_compress_rejected),
     FAST("resample_sparse", n_resample_sparse), FAST("pack_downlink", n_pack_downlink), FAST("unpack_downlink", n_unpack_downlink),
     FAST("pack_uplink", n_pack_uplink), FAST("unpack_uplink", n_unpack_uplink), FAST("scratch", n_scratch), FAST("round_scratch", n_round_scratch), FAST("empty", n_empty),
     {"rows2d", (PyCFunction)n_rows2d, METH_O, nullptr},

@@ -99,6 +99,33 @@ __global__ __launch_bounds__(kThreads) void decide_seg_kernel(
 
 }  // namespace
 
+static hipError_t launch_residual_seg(const void* tgt_logits, int dtype, int64_t ld, int V, float it, int B, const int32_t* seq_off,
+                                      const int32_t* n_accept, const float* tgt_max, const int32_t* q_idx, const float* q_prob,
+                                      const int32_t* q_count, const float* q_mass, int k, int renorm, const float* uniforms,
+                                      int32_t* out_tok, float* resid_mass, uint32_t* flags, const void* seg_table, const StatsShape& sh, hipStream_t stream)
+{
+#define PICOSPEC_RESIDUAL(BF, RT) \
+    hipLaunchKernelGGL((residual_seg_kernel<BF, RT>), dim3(B), dim3(RT), 0, stream, tgt_logits, ld, V, it, seq_off, n_accept, tgt_max, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags)
+#define PICOSPEC_RESIDUAL_RT(BF) \
+    switch (residual_seg_threads(k)) { case 256: PICOSPEC_RESIDUAL(BF, 256); break; case 512: PICOSPEC_RESIDUAL(BF, 512); break; default: PICOSPEC_RESIDUAL(BF, 1024); }
+    if (dtype == 1) { PICOSPEC_RESIDUAL_RT(true) } else { PICOSPEC_RESIDUAL_RT(false) }
+#undef PICOSPEC_RESIDUAL_RT
+#undef PICOSPEC_RESIDUAL
+    return hipGetLastError();
+}
+
+hipError_t launch_residual_split(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
+                                 int B, const int32_t* seq_off, const int32_t* n_accept, const float* tgt_max,
+                                 const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
+                                 int k, int renorm, const float* uniforms,
+                                 int32_t* out_tok, float* resid_mass, uint32_t* flags, void* scratch, int64_t n_rows, hipStream_t stream)
+{
+    if (hipError_t e = launch_row_stats_parts(tgt_logits, dtype, ld, (int)n_rows, V, temperature, B, 0, seq_off, nullptr, nullptr, scratch, stream, n_accept))
+        return e;
+    return launch_residual_seg(tgt_logits, dtype, ld, V, 1.0f / temperature, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass,
+                               k, renorm, uniforms, out_tok, resid_mass, flags, scratch, split_stats_shape(dtype, V), stream);
+}
+
 hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
                            int B, const int32_t* seq_off, const int32_t* n_accept,
                            const float* tgt_max, const float* tgt_sum,
@@ -108,16 +135,9 @@ hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V,
 {
     if (seg_table) {
         if (B == 0) return hipSuccess;
-        const float it = 1.0f / temperature;
         const StatsShape sh = split_stats_serves(dtype, n_rows, V) ? split_stats_shape(dtype, V) : stats_shape(dtype, n_rows, V);   // (as the verification laid it out)
-#define PICOSPEC_RESIDUAL(BF, RT) \
-        hipLaunchKernelGGL((residual_seg_kernel<BF, RT>), dim3(B), dim3(RT), 0, stream, tgt_logits, ld, V, it, seq_off, n_accept, tgt_max, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags)
-#define PICOSPEC_RESIDUAL_RT(BF) \
-        switch (residual_seg_threads(k)) { case 256: PICOSPEC_RESIDUAL(BF, 256); break; case 512: PICOSPEC_RESIDUAL(BF, 512); break; default: PICOSPEC_RESIDUAL(BF, 1024); }
-        if (dtype == 1) { PICOSPEC_RESIDUAL_RT(true) } else { PICOSPEC_RESIDUAL_RT(false) }
-#undef PICOSPEC_RESIDUAL_RT
-#undef PICOSPEC_RESIDUAL
-        return hipGetLastError();
+        return launch_residual_seg(tgt_logits, dtype, ld, V, 1.0f / temperature, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass,
+                                   k, renorm, uniforms, out_tok, resid_mass, flags, seg_table, sh, stream);
     }
     static DeviceFlags limit_raised[2] = {};
     const size_t smem = sizeof(ResidualShared);

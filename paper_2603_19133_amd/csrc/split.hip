@@ -115,9 +115,7 @@ __device__ __forceinline__ void split_select(
     const float mx = hi;
     // the share's softmax sum, against an integer reference exponent
     const float ref = hi > kNegInf ? ceilf(hi * c) : 0.f;
-    float acc = 0.f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc += __builtin_amdgcn_exp2f(fmaf(v[e], c, -ref));   // (masked: 2^-inf = 0)
+    const float acc = tree_sum<0, E>([&](int e) { return __builtin_amdgcn_exp2f(fmaf(v[e], c, -ref)); });   // (masked: 2^-inf = 0)
 
     // ---- threshold: a linear histogram of [lo, hi], refined inside the pivot bin while that is crowded (outliers)
     float tau = kNegInf;

@@ -48,23 +48,29 @@ __global__ __launch_bounds__(THREADS) void row_stats_range_kernel(
 }
 
 // Few rows: the segment tables alone (split layout).  grid: (workgroups per row, rows), or (.., gamma_max + 1, B) for the
-// target rows of a range of positions.
+// target rows of a range of positions, or (.., 1, B) for every sequence's row at n_accept.
 template <bool BF16>
 __global__ __launch_bounds__(256) void row_stats_parts_kernel(
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int n_rows, int seg_stride,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end,
-    SegHeader* __restrict__ header)
+    const int32_t* __restrict__ n_accept, SegHeader* __restrict__ header)
 {
     if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
         *header = SegHeader{kSegMagicSplit, kSplitStatsNV * kWave, seg_stride, n_rows};
     int64_t row = blockIdx.y;
     if (seq_off) {                                    // position t of sequence b, or nothing
-        const int b = blockIdx.z, t = blockIdx.y, d0 = seq_off[b];
+        const int b = blockIdx.z, d0 = seq_off[b];
         const int g = max(seq_off[b + 1] - d0, 0);
-        int begin, end;
-        clamp_range(pos_begin, pos_end, b, g, begin, end);
-        if (t < begin || t > end) return;
+        int t = blockIdx.y;
+        if (n_accept) {
+            t = min(max(n_accept[b], 0), g);          // (as the draw takes it)
+        } else {
+            int begin, end;
+            clamp_range(pos_begin, pos_end, b, g, begin, end);
+            if (t < begin || t > end) return;
+        }
         row = (int64_t)d0 + b + t;
+        if (n_accept && (row < 0 || row >= n_rows)) return;
     }
     row_stats_parts<BF16, kSplitStatsNV, kSplitStatsSpw>(row, (int)blockIdx.x, logits, ld, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
 }
@@ -147,14 +153,14 @@ hipError_t launch_row_stats(const void* logits, int dtype, int64_t ld, int n_row
 }
 
 hipError_t launch_row_stats_parts(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature, int B, int gamma_max, const int32_t* seq_off, const int32_t* pos_begin, const int32_t* pos_end,
-                                  void* seg_table, hipStream_t stream)
+                                  void* seg_table, hipStream_t stream, const int32_t* n_accept)
 {
     if (n_rows == 0 || (seq_off && B == 0)) return hipSuccess;
     const float inv_T = 1.0f / temperature;
     const StatsShape sh = split_stats_shape(dtype, V);
-    const dim3 grid(split_stats_parts(sh.stride), seq_off ? gamma_max + 1 : n_rows, seq_off ? B : 1);
-    if (dtype == 1) hipLaunchKernelGGL(row_stats_parts_kernel<true>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, (SegHeader*)seg_table);
-    else            hipLaunchKernelGGL(row_stats_parts_kernel<false>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, (SegHeader*)seg_table);
+    const dim3 grid(split_stats_parts(sh.stride), n_accept ? 1 : seq_off ? gamma_max + 1 : n_rows, seq_off ? B : 1);
+    if (dtype == 1) hipLaunchKernelGGL(row_stats_parts_kernel<true>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, n_accept, (SegHeader*)seg_table);
+    else            hipLaunchKernelGGL(row_stats_parts_kernel<false>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, n_accept, (SegHeader*)seg_table);
     return hipGetLastError();
 }
 

@@ -188,6 +188,56 @@ def test_long_sequences_on_either_side_of_the_rule(gpu, ps, monkeypatch, R, dtyp
         assert torch.equal(r.out_tok, r0.out_tok) and torch.allclose(r.resid_mass, r0.resid_mass, rtol=1e-5, atol=1e-7)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V,B,k", [(16385, 1, 1), (33001, 24, 70), (128256, 3, 1024), (40000, 2, 1025), (32768, 2, 5), (33000, 129, 257), (33000, 257, 257), (33000, 1024, 10), (33000, 1025, 10)])
+def test_draw_without_a_table_makes_one(gpu, pu, ps, V, B, k, dtype):
+    """The correction draw of few sequences from a table that it forms itself: against the oracle, at first rejections from
+    the first position to the bonus row, with one out of range (clamped and flagged, as without the table)."""
+    _announce("draw with a table of its own", V, B, k, dtype)
+    T, g = 0.9, torch.Generator(device=gpu)
+    g.manual_seed(V + B)
+    gam = torch.tensor([b % 3 for b in range(B)], dtype=torch.int32)
+    gam[0] = 2
+    off = torch.zeros(B + 1, dtype=torch.int32)
+    off[1:] = gam.cumsum(0)
+    N = int(off[-1])
+    tgt = (torch.randn((N + B, V + 1), device=gpu, generator=g) * 2).to(dtype)[:, 1:]     # (rows off the 16-byte boundary)
+    rows = [int(off[b]) + b + i for b in range(B) for i in range(int(gam[b]))]
+    draft = (tgt[rows].float() + torch.randn((N, V), device=gpu, generator=g)).to(dtype)
+    q = ps.compress(draft, V, T, k)
+    u = torch.rand(N + B, device=gpu, generator=g)
+    tok = q.idx[:, 0].contiguous()
+    ver = ps.verify(tgt, V, T, off.to(gpu), N, tok, q, u)
+    na = torch.tensor([b % (int(gam[b]) + 1) for b in range(B)], dtype=torch.int32)
+    if B > 1:
+        na[1] = 9
+    d = lambda t: t.to(gpu)
+    got = ps.sample_residual(tgt, V, T, d(off), N, ver, q, u, n_accept=d(na))
+    plain = ps.alloc_residual(B, tgt.device)
+    p = lambda t: t.data_ptr()
+    o_d, na_d = d(off), d(na)
+    ps._check(ps.lib.picospec_sample_residual(p(tgt), ps._dtype_code(tgt), tgt.stride(0), V, T, B, N, p(o_d), p(na_d), p(ver.tgt_max), p(ver.tgt_sum),
+                                              p(q.idx), p(q.prob), p(q.count), p(q.mass), k, 1, p(u), p(plain.out_tok), p(plain.resid_mass), p(plain.flags),
+                                              None, 0, torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert torch.equal(got.flags, plain.flags) and int(got.flags.sum()) == (8 if B > 1 else 0)
+    # two fp32 sums of the row: the mass agrees to their rounding, and the token unless the uniform falls within it of a step
+    assert torch.allclose(got.resid_mass, plain.resid_mass, rtol=1e-5, atol=1e-6)
+    assert (got.out_tok != plain.out_tok).sum().item() <= B // 200
+    for b in range(min(B, 4)):
+        j = min(int(na[b]), int(gam[b]))
+        r = int(off[b]) + b + j
+        pr = torch.softmax(tgt[r].double() / T, 0)
+        if j < int(gam[b]):
+            i, n = int(off[b]) + j, int(q.count[int(off[b]) + j])
+            pr[q.idx[i, :n].long()] -= q.prob[i, :n].double() / q.mass[i].double()
+        res = pr.clamp_min(0).cpu()
+        cum = res.cumsum(0) / res.sum()
+        x, uu = int(got.out_tok[b]), float(u[int(off[b]) + b + int(gam[b])])
+        assert abs(float(got.resid_mass[b]) - float(res.sum())) < 2e-6 * max(1.0, float(res.sum()))
+        assert float(cum[x]) > uu - 1e-5 and (x == 0 or float(cum[x - 1]) < uu + 1e-5)
+
+
 @pytest.mark.parametrize("k", [1, 3, 10, 255, 256, 257, 777, 1021, 1024, 1025, 2047, 2049, 4093, 4096])
 @pytest.mark.parametrize("R", [1, 5, 513])
 def test_draw_from_records_of_every_length(gpu, pu, ps, k, R):
