@@ -218,7 +218,7 @@ int picospec_row_stats(const void* logits, int dtype, int64_t ld, int32_t n_rows
 
 /*
  * The same with an optional workspace of picospec_workspace_bytes(PICOSPEC_CALL_VERIFY, dtype, n_rows, V, 0) bytes: a call
- * of up to 256 rows then spreads every row over many workgroups (the sums are formed in another order and agree to rounding).
+ * of up to 224 rows then spreads every row over many workgroups (the sums are formed in another order and agree to rounding).
  */
 int picospec_row_stats_ws(const void* logits, int dtype, int64_t ld, int32_t n_rows, int32_t V, float temperature,
                           float* row_max, float* row_sum, float* row_lse,
@@ -272,9 +272,12 @@ int picospec_resample_sparse(const void* draft_logits, int dtype, int64_t ld, in
  * bandwidth.  Larger rounds keep the two streaming launches of the separate calls (three in all).
  * The records are the same bit for bit in both schedules; the target statistics of the two-launch schedule are
  * summed in another order, so what depends on them agrees with the separate calls to rounding.
- * workspace (optional): picospec_workspace_bytes(PICOSPEC_CALL_ROUND, ...) bytes; either schedule then leaves the
- * target rows' segment table there (in a layout of its own: the table of one call of picospec_round serves that call
- * only) and draws from it without a second pass over the target row.
+ * workspace (optional): picospec_workspace_bytes(PICOSPEC_CALL_ROUND, dtype, n_draft + B, V, 0) bytes; either schedule then
+ * leaves the target rows' segment table there (in a layout of its own: the table of one call of picospec_round serves that
+ * call only) and draws from it without a second pass over the target row.  The size for the record length k instead of 0
+ * holds scratch as well (few rows only; the same size where there are more): the draft rows, and the target rows with
+ * them, are then spread over many workgroups, three launches that each take a fraction of the two.  Records then hold the
+ * same ids, and probabilities agree to rounding, as with picospec_compress given a workspace.
  */
 int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, int64_t ld_draft, int64_t ld_tgt,
                    int32_t V, float temperature, int32_t B, int32_t n_draft, const int32_t* seq_off,

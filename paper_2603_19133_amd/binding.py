@@ -154,14 +154,14 @@ def alloc_compressed(rows: int, k: int, device) -> Compressed:
     return Compressed(e(rows, k, dt=torch.int32), e(rows, k), e(rows, dt=torch.int32), e(rows), e(rows), k)
 
 
-def _split_stats(dt: int, rows: int, V: int) -> bool:
+def _split_stats(rows: int, V: int) -> bool:
     """Whether the library spreads the target rows' statistics over many workgroups (split_stats_serves in csrc/kernels.hpp)."""
-    return 0 < rows <= (1024 if dt == 1 else 512) and (rows - 1) % 256 < 224 and V >= 16384
+    return 0 < rows <= 224 and V >= 16384
 
 
 def _table(workspace, dt: int, rows: int, V: int, like):
     """The workspace of a call that was given none: such a call then spreads its rows over many workgroups."""
-    if workspace is not None or not _split_stats(dt, rows, V):
+    if workspace is not None or not _split_stats(rows, V):
         return workspace
     return _nat.scratch(like, CALL_VERIFY, dt, rows, V, 0)
 
@@ -336,8 +336,7 @@ def row_stats(logits: torch.Tensor, V: int, temperature: float):
     """picospec_row_stats -> (row_max, row_sum, row_lse), float32 [rows] each."""
     dt, ld, rows = _logits_2d(logits)
     mx, sm, ls = _nat.empty(logits, "fff", rows, rows, rows)
-    _check(_nat.row_stats(logits, dt, ld, rows, V, temperature, mx, sm, ls,
-                          _table(None, dt, rows, V, logits) if rows <= 256 else None, _stream()))
+    _check(_nat.row_stats(logits, dt, ld, rows, V, temperature, mx, sm, ls, _table(None, dt, rows, V, logits), _stream()))
     return mx, sm, ls
 
 

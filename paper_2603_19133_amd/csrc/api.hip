@@ -121,8 +121,7 @@ int picospec_row_stats_ws(const void* logits, int dtype, int64_t ld, int32_t n_r
     if (n_rows > 0 && (!row_max || !row_sum)) return PICOSPEC_EINVAL;
     if (int rc = check_workspace(PICOSPEC_CALL_VERIFY, dtype, n_rows, V, 0, workspace, workspace_bytes)) return rc;
     hipStream_t s = (hipStream_t)stream;
-    // (beyond one generation of rows what the split gains does not pay for the launch that forms the statistics)
-    if (!workspace || n_rows > 256 || !split_stats_serves(dtype, n_rows, V))
+    if (!workspace || !split_stats_serves(n_rows, V))
         return hip_status(launch_row_stats(logits, dtype, ld, n_rows, V, temperature, row_max, row_sum, row_lse, nullptr, s));
     if (hipError_t e = launch_row_stats_parts(logits, dtype, ld, n_rows, V, temperature, 0, 0, nullptr, nullptr, nullptr, workspace, s))
         return hip_status(e);
@@ -205,7 +204,7 @@ int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, 
     const size_t table_bytes = (round_seg_table_bytes(dtype, rows, V) + 15) / 16 * 16;
     const bool split_draft = n_draft > 0 && workspace && workspace_bytes > table_bytes &&
                              split_fits(dtype, n_draft, V, k, (char*)workspace + table_bytes, workspace_bytes - table_bytes);
-    const bool split_stats = workspace && B > 0 && (split_draft || !small_round) && split_stats_serves(dtype, rows, V);
+    const bool split_stats = split_draft && split_stats_serves(rows, V);
     if (split_draft) {
         void* const scratch = (char*)workspace + table_bytes;
         hipError_t e = hipSuccess;
@@ -232,13 +231,12 @@ int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, 
         if (hipError_t e = launch_compress(draft_logits, dtype, ld_draft, n_draft, V, temperature, k, top_p, q_idx, q_prob,
                                            q_count, q_mass, q_lse, nullptr, nullptr, s))
             return hip_status(e);
-        if (hipError_t e = split_stats ? launch_row_stats_parts(tgt_logits, dtype, ld_tgt, (int)rows, V, temperature, 0, 0, nullptr, nullptr, nullptr, workspace, s)
-                                       : launch_row_stats(tgt_logits, dtype, ld_tgt, (int)rows, V, temperature, tgt_max, tgt_sum, tgt_lse, workspace, s))
+        if (hipError_t e = launch_row_stats(tgt_logits, dtype, ld_tgt, (int)rows, V, temperature, tgt_max, tgt_sum, tgt_lse, workspace, s))
             return hip_status(e);
     }
     return hip_status(launch_decide(tgt_logits, dtype, ld_tgt, V, temperature, B, seq_off, draft_tok, q_idx, q_prob,
                                     q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok,
-                                    verify_flags, out_tok, resid_mass, residual_flags, workspace, rows, small_round, split_stats, s));
+                                    verify_flags, out_tok, resid_mass, residual_flags, workspace, rows, small_round, false, s));
 }
 
 // ---- verification and draw on records that exist
@@ -263,7 +261,7 @@ int picospec_verify_sample(const void* tgt_logits, int dtype, int64_t ld, int32_
                   !resid_mass || !residual_flags)) return PICOSPEC_EINVAL;
     if (int rc = check_workspace(PICOSPEC_CALL_VERIFY_SAMPLE, dtype, rows, V, k, workspace, workspace_bytes)) return rc;
     hipStream_t s = (hipStream_t)stream;
-    const bool split = workspace && B > 0 && split_stats_serves(dtype, rows, V);
+    const bool split = workspace && B > 0 && split_stats_serves(rows, V);
     if (hipError_t e = split ? launch_row_stats_parts(tgt_logits, dtype, ld, (int)rows, V, temperature, 0, 0, nullptr, nullptr, nullptr, workspace, s)
                              : launch_row_stats(tgt_logits, dtype, ld, (int)rows, V, temperature, tgt_max, tgt_sum, tgt_lse, workspace, s))
         return hip_status(e);
@@ -379,7 +377,7 @@ int verify_impl(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float 
     }
     if (int rc = check_workspace(PICOSPEC_CALL_VERIFY, dtype, rows, V, k, workspace, workspace_bytes)) return rc;
     hipStream_t s = (hipStream_t)stream;
-    const bool split = workspace && B > 0 && split_stats_serves(dtype, rows, V);
+    const bool split = workspace && B > 0 && split_stats_serves(rows, V);
     const hipError_t e = split
         ? launch_row_stats_parts(tgt_logits, dtype, ld, (int)rows, V, temperature, B, gamma_max, ranged ? seq_off : nullptr,
                                  pos_begin, pos_end, workspace, s)

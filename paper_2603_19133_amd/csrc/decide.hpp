@@ -49,7 +49,7 @@ struct SplitStats { double S; float M; };
 // tgt_lse of the positions rows.x .. rows.y - 1 from what accept_sequence<.., TABLE> left in LDS, by `n` threads from thread
 // `first` on (a logarithm in fp64: some hundred instructions that the deciding waves need not wait for).
 __device__ __forceinline__ void write_split_lse(const SplitStats* s_stats, int2 rows, int64_t t0, float inv_T, float* tgt_lse, int first, int n) {
-    for (int i = rows.x + (int)threadIdx.x - first; tgt_lse && i < min(rows.y, kSplitStatsPositions); i += n)
+    for (int i = rows.x + (int)threadIdx.x - first; tgt_lse && i < min(rows.y, kSplitStatsRows); i += n)
         tgt_lse[t0 + i] = (float)((double)s_stats[i].M * (double)inv_T + log(s_stats[i].S));
 }
 
@@ -61,7 +61,7 @@ __device__ __forceinline__ void write_split_lse(const SplitStats* s_stats, int2 
 // Returns the sequence's first rejected position (in every thread; a barrier stands behind the decision).
 // TABLE: the rows' statistics are not known yet; their sums stand in the segment table (split layout,
 // split_stats_serves): they are formed here and written to tgt_max / tgt_sum / tgt_lse.  s_stats (nullable, LDS): they
-// are left there by position as well (the first kSplitStatsPositions), and tgt_lse is not written for those: the caller does that off the critical path
+// are left there by position as well, and tgt_lse is not written: the caller does that off the critical path
 // (write_split_lse), for the positions that come back in `rows`.
 template <bool BF16, bool TABLE = false>
 __device__ __forceinline__ int accept_sequence(
@@ -140,7 +140,7 @@ __device__ __forceinline__ int accept_sequence(
             if (lane == 0) {
                 tgt_max[rt] = M_t;
                 tgt_sum[rt] = S_t;
-                if (s_stats && i < kSplitStatsPositions) s_stats[i] = SplitStats{S, M_t};
+                if (s_stats && i < kSplitStatsRows) s_stats[i] = SplitStats{S, M_t};
                 else if (tgt_lse) tgt_lse[rt] = (float)((double)M_t * (double)inv_T + log(S));
                 if (i <= end && nonfinite(M_t, S_t)) fl |= 2u;
             }
@@ -559,9 +559,7 @@ __device__ __forceinline__ void residual_seg_sequence(
     // (checked below), the target row's maximum, the record's count and mass, this thread's entries of the record and
     // its entries of the segment table.
     const SegHeader hd = *table;
-    // (a position beyond those kept in LDS: this workgroup wrote it to memory, a barrier ago)
-    const float M = !s_stats ? tgt_max[rt] : j < kSplitStatsPositions ? s_stats[j].M
-                             : __hip_atomic_load(tgt_max + rt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const float M = s_stats ? s_stats[min(j, kSplitStatsRows - 1)].M : tgt_max[rt];
     int cnt = 0;
     float mass_d = 1.f;
     int my_id[SP];

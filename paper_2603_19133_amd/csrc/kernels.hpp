@@ -156,10 +156,13 @@ inline StatsShape round_stats_shape(int dtype, int V) {
 struct SegHeader { int32_t magic, seg_vecs, stride, rows; };
 constexpr int32_t kSegMagic = 0x53454731;        // entries (sum of 2^(z c - r), r)
 constexpr int32_t kSegMagicSplit = 0x53454732;   // split layout: entries (sum of 2^(z c - r), m), m = the segment's largest logit, r = m c (split_ref)
-// Calls whose rows do not fill the CUs with one workgroup per row spread every row's statistics over many workgroups: each wave
-// leaves the entries of two segments of 256 vectors, nothing else, and the kernel that needs the statistics forms them from the
-// row's table.  One workgroup per row is bound by the vector ALUs of one CU and by the rows of its last generation.
-constexpr int kSplitStatsPositions = 256;            // ... of a sequence that the deciding workgroup keeps in LDS
+// Calls whose rows leave CUs idle spread every row's statistics over many workgroups: each wave leaves the entries of two
+// segments of 256 vectors, nothing else, and the kernel that needs the statistics forms them from the row's table.  One
+// workgroup per row is bound by the vector ALUs of one CU.  The line: a row for nearly every CU (256 rows x 151 936: 19.3 us per
+// row, 20.0 spread, bf16 verification; 128: 17.8, 14.1; fp32 128: 20.8, 19.1); nor below kSplitMinV, where a row is a few
+// segments.  (384 rows: 28.4, 25.1, a round's 576: 31.5, 24.0.  Not taken: the draws of such a call are many, and one in 400
+// lies so near a step of the cumulative sum that sums in another order name its neighbour.)
+constexpr int kSplitStatsRows = 224;
 constexpr int kSplitStatsNV = 4, kSplitStatsSpw = 2; // vectors per lane and segment, segments per wave: eight loads in flight per lane
 inline StatsShape split_stats_shape(int dtype, int V) {
     const int esz = dtype == 1 ? 2 : 4;
@@ -167,16 +170,9 @@ inline StatsShape split_stats_shape(int dtype, int V) {
     return StatsShape{256, kSplitStatsNV, 64 * kSplitStatsNV, (int)((nq_max + 64 * kSplitStatsNV - 1) / (64 * kSplitStatsNV))};
 }
 inline int split_stats_parts(int stride) { return (stride + 4 * kSplitStatsSpw - 1) / (4 * kSplitStatsSpw); }   // workgroups of four waves per row
-// Where: a row per CU has no last generation to shorten when it is full or nearly so (256 rows x 151 936: 19.3 us per row, 20.0
-// spread, bf16 verification; 512: 31.6, 30.3), and gains most just behind one (128: 17.8, 14.1; 384: 28.4, 25.1; fp32 128: 20.8,
-// 19.1; 384: 43.4, 42.0).  From some generations on there is nothing left to gain (768: 42.3, 41.0; 1024: 51.8, 50.9; fp32
-// 768: 74.3, 76.3), nor below kSplitMinV, where a row is a few segments.
-constexpr int kSplitStatsRowsF32 = 512, kSplitStatsRowsBF16 = 1024;
-inline bool split_stats_serves(int dtype, int64_t rows, int V) {
-    return rows >= 1 && rows <= (dtype == 1 ? kSplitStatsRowsBF16 : kSplitStatsRowsF32) && (rows - 1) % 256 < 224 && V >= kSplitMinV;
-}
+inline bool split_stats_serves(int64_t rows, int V) { return rows >= 1 && rows <= kSplitStatsRows && V >= kSplitMinV; }
 // Where a draw that was given no table makes one of the rows it draws from (one workgroup per row passes over its row twice, and
-// is bound by the vector ALUs of one CU): 24 sequences x 33 001 fp32, k = 70: 17.0 -> 11.8 us; 64 x 151 936, k = 64: fp32 29.5 ->
+// is bound by the vector ALUs of one CU): 64 sequences x 33 001 fp32, k = 64: 17.2 -> 11.3 us; 64 x 151 936, k = 64: fp32 29.5 ->
 // 15.4, bf16 24.7 -> 13.2; 512: 73.4 -> 54.7, 50.4 -> 32.2; 1024: 139 -> 105, 98.7 -> 56.7.  The draw from a table gathers one logit per
 // record entry: long records cost more than the second pass (256 x 151 936 bf16, k = 4096: 28.0, 37.8), and so do those of up to
 // 1024 entries where the pass has the chip filled once (256 x 64 000 bf16, k = 1024: 17.8, 19.2); on rows of up to 64 KB the

@@ -67,7 +67,7 @@ int picospec_verify_sample_static(const void* tgt_logits, int dtype, int64_t ld,
     if (scratch_of_current_device(&table) != hipSuccess) return PICOSPEC_EHIP;
     hipStream_t s = (hipStream_t)stream;
     // (every entry of the table that the second launch reads is written by the first: nothing has to start at zero)
-    const bool split = B > 0 && split_stats_serves(dtype, rows, V);
+    const bool split = B > 0 && split_stats_serves(rows, V);
     if ((split ? launch_row_stats_parts(tgt_logits, dtype, ld, (int)rows, V, temperature, 0, 0, nullptr, nullptr, nullptr, table, s)
                : launch_row_stats(tgt_logits, dtype, ld, (int)rows, V, temperature, tgt_max, tgt_sum, tgt_lse, table, s)) != hipSuccess)
         return PICOSPEC_EHIP;

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kThreads) void decide_seg_kernel(
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
     int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags, int n_rows)
 {
-    __shared__ SplitStats s_stats[SPLIT ? kSplitStatsPositions : 1];
+    __shared__ SplitStats s_stats[SPLIT ? kSplitStatsRows : 1];
     int2 rows = make_int2(0, 0);
     const int first = accept_sequence<BF16, SPLIT>(blockIdx.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
                                                    q_count, q_mass, k, renorm, nullptr, uniforms, tgt_max, tgt_sum,
@@ -135,7 +135,7 @@ hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V,
 {
     if (seg_table) {
         if (B == 0) return hipSuccess;
-        const StatsShape sh = split_stats_serves(dtype, n_rows, V) ? split_stats_shape(dtype, V) : stats_shape(dtype, n_rows, V);   // (as the verification laid it out)
+        const StatsShape sh = split_stats_serves(n_rows, V) ? split_stats_shape(dtype, V) : stats_shape(dtype, n_rows, V);   // (as the verification laid it out)
         return launch_residual_seg(tgt_logits, dtype, ld, V, 1.0f / temperature, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass,
                                    k, renorm, uniforms, out_tok, resid_mass, flags, seg_table, sh, stream);
     }

@@ -14,6 +14,8 @@
 //     the record with the code of the unsplit kernels.  The answer is exact iff the k-th value lies above every workgroup's
 //     threshold, which is tested; a row that fails it (or whose lists overflow) is compressed from the start by the general
 //     code in the same workgroup.
+// Device time of a call, one workgroup per row -> split: one bf16 row of 128,256, k = 10: 25.5 -> 4.9 + 6.1
+// us; 64 fp32 rows of 151,936, k = 1024: 31.0 -> 13.1 + 9.5 us, of which the first launch reads 39 MB (5.8 us at 6.8 TB/s).  The line between the two is split_plan's.
 #include "compress_row.hpp"
 
 namespace picospec {

@@ -47,7 +47,8 @@ __global__ __launch_bounds__(THREADS) void row_stats_range_kernel(
     row_stats_row<BF16, NV, THREADS>((int64_t)d0 + b + t, logits, ld, V, inv_T, row_max, row_sum, row_lse);
 }
 
-// Few rows: the segment tables alone (split layout).  grid: (workgroups per row, rows), or (.., gamma_max + 1, B) for the
+// Rows that leave the chip partly idle: the segment tables alone (split layout).  Bound by the memory's latency up to some
+// 100 rows and by its rate from there (576 bf16 rows of 128,256 in 24.0 us: 6.2 TB/s).  One workgroup per row -> here: 16 sequences of 1 to 8 drafts, fp32 rows of 151,936: 17.8 -> 9.3 us; half of 24 such drafts, rows of 33,001: 8.2 -> 5.0 us.  grid: (workgroups per row, rows), or (.., gamma_max + 1, B) for the
 // target rows of a range of positions, or (.., 1, B) for every sequence's row at n_accept.
 template <bool BF16>
 __global__ __launch_bounds__(256) void row_stats_parts_kernel(
