@@ -259,7 +259,7 @@ def round(draft_logits: torch.Tensor, tgt_logits: torch.Tensor, V: int, temperat
     _check(_nat.round(draft_logits, tgt_logits, dt, ld_d, ld_t, V, temperature, B, n_draft, seq_off, draft_tok, k, top_p, renorm,
                     uniforms, q.idx, q.prob, q.count, q.mass, q.lse,
                     ver.n_accept, ver.p_tok, ver.q_tok, ver.tgt_max, ver.tgt_sum, ver.tgt_lse, ver.flags,
-                    res.out_tok, res.resid_mass, res.flags, workspace if own is None else own, _stream()))
+                    res.out_tok, res.resid_mass, res.flags, workspace, own, _stream()))
     return q, ver, res
 
 

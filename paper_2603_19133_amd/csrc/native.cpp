@@ -131,7 +131,9 @@ PyObject* n_round(PyObject*, PyObject* const* v, Py_ssize_t n) {
         auto zd = a.ptr(), zt = a.ptr(); auto dt = a.i32(); auto ldd = a.i64(), ldt = a.i64(); auto V = a.i32(); auto T = a.f32(); auto B = a.i32(), N = a.i32();
         auto off = a.ptr<int32_t>(); auto tok = a.ptr<int32_t>(); auto k = a.i32(); auto top_p = a.f32(); auto renorm = a.i32(); auto uni = a.ptr<float>();
         auto idx = a.ptr<int32_t>(); auto prob = a.ptr<float>(); auto count = a.ptr<int32_t>(); auto mass = a.ptr<float>(); auto lse = a.ptr<float>();
-        auto o = verdict(a); auto d = draw(a); auto ws = a.buffer(); auto s = a.stream();
+        auto o = verdict(a); auto d = draw(a); auto ws = a.buffer(), own = a.buffer(); auto s = a.stream();
+        // (the call's own buffer in the place of the caller's, unless the library would refuse the caller's: it still does)
+        if (own.p && !(ws.p && (((uintptr_t)ws.p & 15u) || ws.bytes < picospec_workspace_bytes(PICOSPEC_CALL_ROUND, dt, N + B, V, 0)))) ws = own;
         return [=] { return picospec_round(zd, zt, dt, ldd, ldt, V, T, B, N, off, tok, k, top_p, renorm, uni, idx, prob, count, mass, lse,
                                            o.n, o.p, o.q, o.mx, o.sm, o.lse, o.fl, d.tok, d.mass, d.fl, ws.p, ws.bytes, s); };
     });

@@ -261,3 +261,21 @@ def test_draw_from_records_of_every_length(gpu, pu, ps, k, R):
     assert sure.mean() > 0.99 and np.array_equal(pu.n(g_tok)[sure], tok[sure])
     want = p[np.arange(R), slot].astype(np.float64) / mass
     pu.assert_close(pu.n(g_q)[sure], want[sure], pu.RTOL, "q_scalar", atol=1e-37)
+
+
+def test_a_workspace_that_is_refused_stays_refused(gpu, ps):
+    """Calls that bring a buffer of their own still look at the one they are given."""
+    _announce("refused workspace")
+    V, k = 20000, 8
+    d, t = torch.randn((2, V), device=gpu), torch.randn((3, V), device=gpu)
+    off = torch.tensor([0, 2], dtype=torch.int32, device=gpu)
+    tok, u = torch.zeros(2, dtype=torch.int32, device=gpu), torch.rand(3, device=gpu)
+    good = torch.empty(ps.workspace_bytes(ps.CALL_ROUND, ps.F32, 3, V, 0) + 16, dtype=torch.uint8, device=gpu)
+    q, v, _ = ps.round(d, t, V, 1.0, off, 2, tok, k, u, workspace=good)
+    for bad in (good[:64], good[8:]):
+        for call in (lambda: ps.round(d, t, V, 1.0, off, 2, tok, k, u, workspace=bad), lambda: ps.verify(t, V, 1.0, off, 2, tok, q, u, workspace=bad),
+                     lambda: ps.verify_sample(t, V, 1.0, off, 2, tok, q, u, workspace=bad),
+                     lambda: ps.sample_residual(t, V, 1.0, off, 2, v, q, u, workspace=bad)):
+            with pytest.raises(ps.PicoSpecError) as e:
+                call()
+            assert e.value.code == ps.EWORKSPACE
