@@ -498,7 +498,8 @@ __device__ __forceinline__ float tree_sum(const F& f) {
 
 // The segment table of part `part` of a row, and nothing else (calls of few rows, whose statistics are formed from the table):
 // a workgroup of four waves, each wave SPW consecutive segments of NV * 64 vectors whose loads are all in flight at once.
-// Entry: (sum of 2^(z c - r), m), m = the segment's largest logit and r = split_ref(m, c).  The lanes' sums are added in fp64.
+// Entry: (sum of 2^(z c - r), m), m = the segment's largest logit and r = split_ref(m, c); a NaN in the segment makes its sum NaN.
+// The lanes' sums are added in fp64.
 __device__ __forceinline__ bool split_ref_fused(float m, float c) { return fabsf(m * c) < __builtin_huge_valf(); }
 // m c as the sums' reference: rounded to fp32 as in the fused form of their terms; exact where that overflows (a segment of
 // nothing but masked entries of the type's lowest value), whose terms are formed as (z - m) c
@@ -550,15 +551,17 @@ __device__ __forceinline__ void row_stats_parts(
 #pragma unroll
         for (int e = 1; e < E; ++e) bm = fmaxf(bm, v[e]);
         const float m = wave_max(bm);
-        float acc = 0.f;
+        float acc;
         if (split_ref_fused(m, c)) {                  // (uniform)
             const float nr = -(m * c);
             acc = tree_sum<0, E>([&](int e) { return __builtin_amdgcn_exp2f(fmaf(v[e], c, nr)); });
-        } else if (m > kNegInf) {
-            acc = tree_sum<0, E>([&](int e) { return exp_stream(v[e], m, c); });
+        } else {
+            // (no value above -inf: the sum is 0, or NaN if the segment holds one - the maxima skip NaN, so only the sum can carry it)
+            const float ref = m > kNegInf ? m : 0.f;
+            acc = tree_sum<0, E>([&](int e) { return exp_stream(v[e], ref, c); });
         }
         const float t = (float)wave_sum((double)acc);
-        if (lane == 0) seg_row[s] = make_float2(t, m);
+        if (lane == 0) seg_row[s] = make_float2(t, m > kNegInf ? m : kNegInf);
     }
 }
 

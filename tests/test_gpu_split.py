@@ -279,3 +279,39 @@ def test_a_workspace_that_is_refused_stays_refused(gpu, ps):
             with pytest.raises(ps.PicoSpecError) as e:
                 call()
             assert e.value.code == ps.EWORKSPACE
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("where", ["whole_segment", "among_masked", "last_segment", "masked_row"])
+def test_nan_in_a_segment_without_a_finite_value_is_flagged(gpu, ps, dtype, where):
+    """A segment (256 vectors of 16 bytes) that holds NaN and nothing above -inf: the row's log-sum-exp is not finite, with its
+    statistics spread over many workgroups as with one workgroup per row."""
+    _announce("NaN in a segment without a finite value", dtype, where)
+    seg = 1024 if dtype == torch.float32 else 2048
+    V, B = 20 * seg + 3, 3
+    tgt = torch.randn((2 * B, V), device=gpu).to(dtype)          # one draft per sequence: rows 2 b and 2 b + 1
+    bad = 3                                      # (the second row of sequence 1)
+    if where == "whole_segment":
+        tgt[bad, 4 * seg:5 * seg] = float("nan")
+    elif where == "among_masked":
+        tgt[bad, 4 * seg:5 * seg] = float("-inf")
+        tgt[bad, 4 * seg + 777] = float("nan")
+    elif where == "last_segment":
+        tgt[bad, 20 * seg:] = float("nan")
+    else:
+        tgt[bad] = float("-inf")
+        tgt[bad, 12] = 1.0
+        tgt[bad, 7 * seg + 5] = float("nan")
+    base = torch.zeros((2 * B, (V + 7) // 8 * 8), dtype=dtype, device=gpu)   # (rows on the 16-byte boundary: a segment is whole ids)
+    base[:, :V] = tgt
+    z = base[:, :V]
+    off = torch.arange(B + 1, dtype=torch.int32, device=gpu)
+    tok, u = torch.zeros(B, dtype=torch.int32, device=gpu), torch.rand(2 * B, device=gpu)
+    q = ps.compress(torch.randn((B, V), device=gpu).to(dtype), V, 1.0, 8)
+    ws = ps.alloc_workspace(dtype, 2 * B, V, gpu)
+    for ver in (ps.verify(z, V, 1.0, off, B, tok, q, u, workspace=ws), ps.verify_sample(z, V, 1.0, off, B, tok, q, u, workspace=ws)[0],
+                ps.verify_range(z, V, 1.0, off, B, tok, q, u, None, None, 1)):
+        torch.cuda.synchronize()
+        assert [bool(f & ps.FLAG_NONFINITE) for f in ver.flags.tolist()] == [False, True, False], (ver.flags, ver.tgt_sum)
+        assert ver.tgt_sum.isnan().tolist() == [r == bad for r in range(2 * B)] and ver.tgt_lse.isnan().tolist() == ver.tgt_sum.isnan().tolist()
+    assert ps.row_stats(z, V, 1.0)[1].isnan().tolist() == [r == bad for r in range(2 * B)]
