@@ -219,11 +219,12 @@ __device__ __forceinline__ void split_select(
         }
     }
     if (tid == 0) {
-        // (+inf in the row: given up, as by the other kernels' first pass)
+        // (+inf in the row: given up, as by the other kernels' first pass; so is a share of NaN and nothing above -inf, whose sum the
+        //  finishing kernel leaves out with its reference: any other NaN it finds in the row's sum)
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < kSplitWaves; ++w) s += wave_s[w];
-        SplitHead h{mx, tau, ref, finite || !(mx > kNegInf) ? held : cap + 1, s, 0.0};
+        SplitHead h{mx, tau, ref, finite || (!(mx > kNegInf) && s == s) ? held : cap + 1, s, 0.0};
         uint4* dst = reinterpret_cast<uint4*>(heads + list);
         const uint4* src = reinterpret_cast<const uint4*>(&h);
         dst[0] = src[0];

@@ -315,3 +315,22 @@ def test_nan_in_a_segment_without_a_finite_value_is_flagged(gpu, ps, dtype, wher
         assert [bool(f & ps.FLAG_NONFINITE) for f in ver.flags.tolist()] == [False, True, False], (ver.flags, ver.tgt_sum)
         assert ver.tgt_sum.isnan().tolist() == [r == bad for r in range(2 * B)] and ver.tgt_lse.isnan().tolist() == ver.tgt_sum.isnan().tolist()
     assert ps.row_stats(z, V, 1.0)[1].isnan().tolist() == [r == bad for r in range(2 * B)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("others", ["masked", "nan"])
+def test_nan_in_a_share_without_a_finite_value_reaches_the_record(gpu, ps, dtype, others):
+    """The blocks of one workgroup's share of a row (every P-th kilobyte) hold a NaN and nothing above -inf: the row's sum is NaN as
+    with one workgroup per row."""
+    _announce("NaN in a share without a finite value", dtype, others)
+    P, blk, k = 5, 256 if dtype == torch.float32 else 512, 24
+    V = 8192 * P - 8                             # (a row is split as if it spanned a vector more)
+    z = torch.randn((3, V), device=gpu)
+    share = (torch.arange(V, device=gpu) // blk) % P == 3
+    z[1, share] = float("-inf") if others == "masked" else float("nan")
+    z[1, 3 * blk + 100] = float("nan")
+    z = z.to(dtype)
+    g, u = ps.compress(z, V, 1.0, k), _unsplit(ps, z, V, 1.0, k)
+    torch.cuda.synchronize()
+    assert g.lse.isnan().tolist() == u.lse.isnan().tolist() == [False, True, False]
+    assert g.mass.isnan().tolist() == u.mass.isnan().tolist()
