@@ -176,22 +176,9 @@ __device__ __forceinline__ void split_select(
     // ---- the list: the elements above the threshold, in any order.  A lane marks its elements in a word, a scan over the
     //      counts gives it its slots, and it takes the few it marked from the image.
     unsigned marks = 0;                          // bit 31 - e: element e
-    // (shifted in as the carry of marks + marks.  gfx950 asks for two wait states between a vector instruction that writes a
-    //  scalar register and one that reads it, and the compiler does not look into this: four compares, then four additions)
+    // (the sign of tau - v, shifted in; -inf below a threshold of -inf gives the positive NaN)
 #pragma unroll
-    for (int e = 0; e < E; e += 4) {
-        unsigned long long m0, m1, m2, m3;
-        asm("v_cmp_gt_f32_e64 %1, %5, %9\n\t"
-            "v_cmp_gt_f32_e64 %2, %6, %9\n\t"
-            "v_cmp_gt_f32_e64 %3, %7, %9\n\t"
-            "v_cmp_gt_f32_e64 %4, %8, %9\n\t"
-            "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\t"
-            "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
-            "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"
-            "v_addc_co_u32_e64 %0, vcc, %0, %0, %4"
-            : "+v"(marks), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
-            : "v"(v[e]), "v"(v[e + 1]), "v"(v[e + 2]), "v"(v[e + 3]), "v"(tau) : "vcc");
-    }
+    for (int e = 0; e < E; ++e) marks = __builtin_amdgcn_alignbit(marks, __float_as_uint(tau - v[e]), 31);
     const int mine = __popc(marks);
     const int incl = wave_scan_incl(mine);
     const double ws = wave_sum((double)acc);
