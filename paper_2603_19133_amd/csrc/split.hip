@@ -119,57 +119,88 @@ __device__ __forceinline__ void split_select(
     const float ref = hi > kNegInf ? ceilf(hi * c) : 0.f;
     const float acc = tree_sum<0, E>([&](int e) { return __builtin_amdgcn_exp2f(fmaf(v[e], c, -ref)); });   // (masked: 2^-inf = 0)
 
-    // ---- threshold: a linear histogram of [lo, hi], refined inside the pivot bin while that is crowded (outliers)
+    // ---- threshold: a linear histogram of [lo, hi]; a pivot bin that is crowded is refined over the keys (the order-preserving
+    //      integers) of its values.  A linear scale that outliers or masked entries of a finite value stretch (the type's
+    //      lowest, -1e9) holds all that matters in one bin however often it is cut; the keys of two values of one binade lie
+    //      2^23 apart at most, so three passes of nine bits resolve any bin.
     float tau = kNegInf;
     const bool finite = hi > kNegInf && hi < __builtin_huge_valf();
-    if (finite) {
+    int bin, before, cnt;                        // the pivot bin of a pass, elements in the bins in front of it and in it
+    const int crowd = max(16, rank >> 3);
+    // every wave scans the bins for itself, eight consecutive ones per lane; false: fewer than `need` elements in all of them
+    auto find_pivot = [&](int need) {
+        const uint4 h0 = *reinterpret_cast<const uint4*>(&hist[8 * lane]), h1 = *reinterpret_cast<const uint4*>(&hist[8 * lane + 4]);
+        const int h[8] = {(int)h0.x, (int)h0.y, (int)h0.z, (int)h0.w, (int)h1.x, (int)h1.y, (int)h1.z, (int)h1.w};
+        const int loc = ((h[0] + h[1]) + (h[2] + h[3])) + ((h[4] + h[5]) + (h[6] + h[7]));
+        const int incl = wave_scan_incl(loc);
+        const unsigned long long reach = __ballot(incl >= need);
+        if (!reach) return false;
+        const int owner = __ffsll((long long)reach) - 1;
+        // (the walk through the owner's eight bins in scalar registers)
+        before = read_lane(incl - loc, owner); bin = 8 * owner; cnt = read_lane(h[0], owner);
+#pragma unroll
+        for (int u = 1; u < 8; ++u) {
+            const int next = read_lane(h[u], owner);
+            if (before + cnt < need && bin == 8 * owner + u - 1) { before += cnt; ++bin; cnt = next; }
+        }
+        return true;
+    };
+    if (finite && !(hi > lo)) {
+        if (hi == lo) tau = float_below(lo);     // one value
+    } else if (finite) {
         int need = rank;
-        for (int pass = 0; pass < 3; ++pass) {
-            const float width = (hi - lo) * (1.0f / (float)kSplitBins);
-            const float scale = __builtin_amdgcn_rcpf(width);
-            if (!(hi > lo) || !(scale < __builtin_huge_valf()) || !(width < __builtin_huge_valf())) { if (hi >= lo) tau = float_below(lo); break; }   // one value (or too close to tell apart)
-            if (pass > 0) {
+        bool open = true;                        // the threshold is not fine enough yet
+        bool counted = false;                    // the histogram holds a pass
+        uint32_t top = key_of_bits(__float_as_uint(hi)), bottom = key_of_bits(__float_as_uint(lo));
+        const float width = (hi - lo) * (1.0f / (float)kSplitBins);
+        const float scale = __builtin_amdgcn_rcpf(width);
+        if (scale < __builtin_huge_valf() && width < __builtin_huge_valf()) {
+            const float at0 = hi * scale;
+            // bin 0 holds the largest values; what lies below lo goes to the lane's own slot behind the bins
+            auto bin_of = [&](float x) {
+                unsigned b;
+                asm("v_cvt_u32_f32 %0, %1" : "=v"(b) : "v"(fmaf(x, -scale, at0)));     // (saturates: below 0 and NaN 0, large 2^32 - 1)
+                return b;
+            };
+#pragma unroll
+            for (int e = 0; e < E; ++e) atomicAdd(&hist[min(bin_of(v[e]), (unsigned)(kSplitBins + lane))], 1u);
+            __syncthreads();
+            counted = true;
+            if (!find_pivot(need)) open = false; // fewer than `need` elements above -inf (a masked row): tau stays -inf, all of them are listed
+            else {
+                const float edge = hi - ((float)(bin + 1) + 0.02f) * width;    // below every element of the bins up to the pivot
+                tau = float_below(edge);
+                open = cnt > crowd;
+                need -= before;
+                top = min(top, key_of_bits(__float_as_uint(hi - ((float)bin - 0.02f) * width)));
+                bottom = max(bottom, key_of_bits(__float_as_uint(edge)));
+            }
+        }
+        for (int pass = 0; open && pass < 4; ++pass) {       // (a pass too many for the widest bin: one bin is one value by then)
+            if (counted) {
                 __syncthreads();
                 *reinterpret_cast<uint2*>(&hist[2 * tid]) = make_uint2(0u, 0u);
                 __syncthreads();
             }
-            const float top = hi * scale;
-            // bin 0 holds the largest values; what lies below lo goes to the lane's own slot behind the bins
-            auto bin_of = [&](float x) {
-                unsigned b;
-                asm("v_cvt_u32_f32 %0, %1" : "=v"(b) : "v"(fmaf(x, -scale, top)));     // (saturates: below 0 and NaN 0, large 2^32 - 1)
-                return b;
-            };
-            if (pass == 0) {                     // (nothing lies above hi)
+            const uint32_t span = top - bottom;
+            const int shift = max(0, 23 - (int)__clz((int)span));              // span >> shift < 2^9 = kSplitBins
+            static_assert(kSplitBins == 1 << 9, "a bin for every value of nine bits");
 #pragma unroll
-                for (int e = 0; e < E; ++e) atomicAdd(&hist[min(bin_of(v[e]), (unsigned)(kSplitBins + lane))], 1u);
-            } else {
-#pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (v[e] >= lo && v[e] <= hi) atomicAdd(&hist[min(bin_of(v[e]), (unsigned)(kSplitBins - 1))], 1u);
+            for (int e = 0; e < E; ++e) {
+                uint32_t bits = __float_as_uint(v[e]);
+                asm volatile("" : "+v"(bits));                       // (the keys are formed in each pass, not held from in front of the loop)
+                const uint32_t d = top - key_of_bits(bits);          // (keys above top wrap far above span)
+                if (d <= span) atomicAdd(&hist[d >> shift], 1u);
             }
             __syncthreads();
-            // every wave scans the bins for itself: eight consecutive ones per lane
-            const uint4 h0 = *reinterpret_cast<const uint4*>(&hist[8 * lane]), h1 = *reinterpret_cast<const uint4*>(&hist[8 * lane + 4]);
-            const int h[8] = {(int)h0.x, (int)h0.y, (int)h0.z, (int)h0.w, (int)h1.x, (int)h1.y, (int)h1.z, (int)h1.w};
-            const int loc = ((h[0] + h[1]) + (h[2] + h[3])) + ((h[4] + h[5]) + (h[6] + h[7]));
-            const int incl = wave_scan_incl(loc);
-            const unsigned long long reach = __ballot(incl >= need);
-            if (!reach) break;                   // fewer than `need` elements above -inf (a masked row): tau stays -inf, all of them are listed
-            const int owner = __ffsll((long long)reach) - 1;
-            // (the walk through the owner's eight bins in scalar registers)
-            int before = read_lane(incl - loc, owner), bin = 8 * owner, cnt = read_lane(h[0], owner);
-#pragma unroll
-            for (int u = 1; u < 8; ++u) {
-                const int next = read_lane(h[u], owner);
-                if (before + cnt < need && bin == 8 * owner + u - 1) { before += cnt; ++bin; cnt = next; }
-            }
-            const float edge = hi - ((float)(bin + 1) + 0.02f) * width;    // below every element of the bins up to the pivot
-            tau = float_below(edge);
-            if (cnt <= max(16, rank >> 3)) break;
-            hi = hi - ((float)bin - 0.02f) * width;
-            lo = fmaxf(lo, edge);
+            counted = true;
+            if (!find_pivot(need)) break;        // (the linear bins' margins: tau as it stands has them)
+            const uint32_t last = min(span, ((uint32_t)(bin + 1) << shift) - 1u);
+            tau = float_below(__uint_as_float(bits_of_key(top - last)));
+            open = cnt > crowd && shift > 0;
             need -= before;
+            bottom = top - last;
+            top -= (uint32_t)bin << shift;
         }
     }
 

@@ -334,3 +334,34 @@ def test_nan_in_a_share_without_a_finite_value_reaches_the_record(gpu, ps, dtype
     torch.cuda.synchronize()
     assert g.lse.isnan().tolist() == u.lse.isnan().tolist() == [False, True, False]
     assert g.mass.isnan().tolist() == u.mass.isnan().tolist()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("k,share", [(10, 0.9), (1024, 0.5), (1024, 0.9)])
+@pytest.mark.parametrize("mask", ["lowest", "-1e9"])
+def test_masks_of_a_finite_value_are_compressed_once(gpu, ps, dtype, mask, k, share):
+    """Rows masked by the type's lowest value or by -1e9: every workgroup's list holds what it found, so no row is compressed a
+    second time from the start (which costs more than one workgroup per row)."""
+    _announce("split finite masks", dtype, mask, k, share)
+    V, R = 32000, 3
+    g = torch.Generator(device=gpu)
+    g.manual_seed(k)
+    z = torch.randn((R, V), device=gpu, generator=g) * 3
+    hidden = torch.rand((R, V), device=gpu, generator=g) < share
+    z[hidden] = {"lowest": torch.finfo(dtype).min, "-1e9": -1e9}[mask]
+    z = z.to(dtype)
+    n = ps.workspace_bytes(ps.CALL_COMPRESS, ps._dtype_code(z), R, V, k)
+    ws = torch.zeros(n, dtype=torch.uint8, device=gpu)
+    out = ps.alloc_compressed(R, k, gpu)
+    p = lambda t: t.data_ptr()
+    ps._check(ps.lib.picospec_compress(p(z), ps._dtype_code(z), V, R, V, 1.0, k, 0.0, p(out.idx), p(out.prob), p(out.count), p(out.mass),
+                                       p(out.lse), p(ws), n, torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    u = _unsplit(ps, z, V, 1.0, k)
+    assert torch.equal(out.idx, u.idx) and torch.allclose(out.prob, u.prob, rtol=1e-6, atol=1e-38)
+    # the scratch begins with a 32-byte head per share (its fourth word the entries found), lists of `cap` pairs follow
+    vecs = (V * z.element_size() + 15) // 16 + 1
+    parts = -(-(-(-vecs // 64)) // (8192 * z.element_size() // 1024))
+    cap = (n // (R * parts) - 32) // 8
+    found = ws.view(torch.int32)[:R * parts * 8].view(R * parts, 8)[:, 3]
+    assert cap > 8 and int(found.max()) <= cap and int(found.view(R, parts).sum(1).min()) >= k, (cap, found)
