@@ -828,7 +828,8 @@ __device__ __forceinline__ RowSelection select_row(
             }
             // key range of the sample
             const float wmax = wave_max(bm), wmin = -wave_max(-bn);
-            const unsigned wave_masked = __ballot(saw_masked) != 0ull;
+            // (narrow: threads with an element above -inf)
+            const unsigned wave_masked = narrow ? (unsigned)__popcll(__ballot(bm > kNegInf)) : __ballot(saw_masked) != 0ull;
             if (lane == 0) {
                 sh.wkey[wave] = short_key<BF16>(__float_as_uint(wmax));
                 sh.wkey[kW + wave] = short_key<BF16>(__float_as_uint(wmin));
@@ -840,9 +841,14 @@ __device__ __forceinline__ RowSelection select_row(
             key_hi = 0; key_lo = 0xFFFFFFFFu;
             unsigned masked = 0;
 #pragma unroll
-            for (int w = 0; w < kW; ++w) { key_hi = max(key_hi, sh.wkey[w]); key_lo = min(key_lo, sh.wkey[kW + w]); masked |= sh.wkey[2 * kW + w]; }
+            for (int w = 0; w < kW; ++w) { key_hi = max(key_hi, sh.wkey[w]); key_lo = min(key_lo, sh.wkey[kW + w]); masked += sh.wkey[2 * kW + w]; }
             bool again = false;
-            if (one_pass) {
+            if (one_pass && narrow && (int)masked < target) {
+                // a row masked so far that fewer threads than the rank hold anything above -inf: hardly a histogram from there
+                // reaches it, so none is formed (300 fp32 rows of 50,001, 99 % at -inf, k = 1024: 31.3 -> 30.7 us)
+                again = true;
+                __syncthreads();
+            } else if (one_pass) {
                 // Optimistic pass: the threshold only has to be about right (the count at the end of the row
                 // decides), so one histogram pass over a linear scale of the sample's value range does: bin
                 // 0 holds the largest values.  A crowded pivot bin (a value range stretched by outliers)
