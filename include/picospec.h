@@ -87,7 +87,7 @@ enum {
 
 enum { PICOSPEC_CALL_COMPRESS = 0, PICOSPEC_CALL_SAMPLE_DRAFT = 1, PICOSPEC_CALL_VERIFY = 2, PICOSPEC_CALL_SAMPLE_RESIDUAL = 3,
        PICOSPEC_CALL_COMPRESS_REJECTED = 4, PICOSPEC_CALL_RESAMPLE_SPARSE = 5, PICOSPEC_CALL_ROUND = 6,
-       PICOSPEC_CALL_VERIFY_SAMPLE = 7 };
+       PICOSPEC_CALL_VERIFY_SAMPLE = 7, PICOSPEC_CALL_ROW_STATS = 8 };
 enum { PICOSPEC_LIMIT_MAX_K = 0, PICOSPEC_LIMIT_MAX_V = 1 };
 
 /*
@@ -437,6 +437,12 @@ int picospec_probe_clock(uint64_t* ticks, void* stream);
 /* host: bytes of the optional device workspace of the given call for (dtype, rows, V, k), rows = n_draft + B for the
  * calls that take target rows; 0 if the call has no use for one. */
 size_t picospec_workspace_bytes(int which_call, int dtype, int32_t rows, int32_t V, int32_t k);
+
+/* host: bytes of device memory with which the given call spreads its rows over many workgroups, where its caller has brought
+ * no workspace; 0 where one workgroup per row is as fast and the call takes NULL.  n_draft and B as the call's own (0 draft rows
+ * or 0 sequences where it has none: n_draft = n_rows, B = 0 for picospec_compress and picospec_row_stats_ws).  The rules by
+ * which calls are spread stand in the library only: a caller that keeps its buffers asks here which call has a use for one. */
+size_t picospec_scratch_bytes(int which_call, int dtype, int32_t n_draft, int32_t B, int32_t V, int32_t k);
 
 /* host: largest supported k (PICOSPEC_LIMIT_MAX_K) or V (PICOSPEC_LIMIT_MAX_V); -1 for an unknown id. */
 int64_t picospec_limit(int which);

@@ -20,7 +20,7 @@ F32, BF16 = 0, 1
 OK, EINVAL, EWORKSPACE, EDTYPE, EHIP, EUNSUPPORTED, ESCRATCH = 0, -1, -2, -3, -4, -5, -6
 FLAG_TOKEN_NOT_IN_SUPPORT, FLAG_NONFINITE, FLAG_RESIDUAL_EMPTY, FLAG_BAD_INPUT = 1, 2, 4, 8
 CALL_COMPRESS, CALL_SAMPLE_DRAFT, CALL_VERIFY, CALL_SAMPLE_RESIDUAL = 0, 1, 2, 3
-CALL_COMPRESS_REJECTED, CALL_RESAMPLE_SPARSE, CALL_ROUND, CALL_VERIFY_SAMPLE = 4, 5, 6, 7
+CALL_COMPRESS_REJECTED, CALL_RESAMPLE_SPARSE, CALL_ROUND, CALL_VERIFY_SAMPLE, CALL_ROW_STATS = 4, 5, 6, 7, 8
 LIMIT_MAX_K, LIMIT_MAX_V = 0, 1
 WIRE_FP32, WIRE_FP16, WIRE_BF16 = 0, 1, 2
 WIRE_BAD_HEADER, WIRE_BAD_BATCH, WIRE_CLAMPED, WIRE_TRUNCATED = 1, 2, 4, 8
@@ -29,7 +29,7 @@ EXPORTS = ("picospec_round", "picospec_verify_sample", "picospec_verify_sample_s
            "picospec_row_stats", "picospec_row_stats_ws", "picospec_compress_rejected", "picospec_resample_sparse",
            "picospec_pack_downlink", "picospec_unpack_downlink", "picospec_pack_uplink", "picospec_unpack_uplink",
            "picospec_downlink_bytes_max", "picospec_uplink_bytes", "picospec_max_load_byte", "picospec_check_device", "picospec_probe_clock",
-           "picospec_workspace_bytes", "picospec_limit", "picospec_strerror", "picospec_version")
+           "picospec_workspace_bytes", "picospec_scratch_bytes", "picospec_limit", "picospec_strerror", "picospec_version")
 
 if not os.path.exists(LIB_PATH):
     raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2603_19133_amd.build` "
@@ -84,6 +84,8 @@ lib.picospec_probe_clock.argtypes = [_p, _p]
 lib.picospec_probe_clock.restype = C.c_int
 lib.picospec_workspace_bytes.argtypes = [C.c_int, C.c_int, _i32, _i32, _i32]
 lib.picospec_workspace_bytes.restype = _sz
+lib.picospec_scratch_bytes.argtypes = [C.c_int, C.c_int, _i32, _i32, _i32, _i32]
+lib.picospec_scratch_bytes.restype = _sz
 lib.picospec_limit.argtypes = [C.c_int]
 lib.picospec_limit.restype = _i64
 lib.picospec_strerror.argtypes = [C.c_int]
@@ -154,16 +156,16 @@ def alloc_compressed(rows: int, k: int, device) -> Compressed:
     return Compressed(e(rows, k, dt=torch.int32), e(rows, k), e(rows, dt=torch.int32), e(rows), e(rows), k)
 
 
-def _split_stats(rows: int, V: int) -> bool:
-    """Whether the library spreads the target rows' statistics over many workgroups (split_stats_serves in csrc/kernels.hpp)."""
-    return 0 < rows <= 224 and V >= 16384
+def _split_stats(which: int, dt: int, n_draft: int, B: int, V: int) -> bool:
+    """Whether the library has a use for a table of its own in a call that was given none."""
+    return _nat.scratch_bytes(which, dt, n_draft, B, V, 0) > 0
 
 
-def _table(workspace, dt: int, rows: int, V: int, like):
+def _table(workspace, which: int, dt: int, n_draft: int, B: int, V: int, like):
     """The workspace of a call that was given none: such a call then spreads its rows over many workgroups."""
-    if workspace is not None or not _split_stats(rows, V):
+    if workspace is not None or not _split_stats(which, dt, n_draft, B, V):
         return workspace
-    return _nat.scratch(like, CALL_VERIFY, dt, rows, V, 0)
+    return _nat.scratch(like, which, dt, n_draft, B, V, 0)
 
 
 def compress(logits: torch.Tensor, V: int, temperature: float, k: int, top_p: float = 0.0,
@@ -172,7 +174,7 @@ def compress(logits: torch.Tensor, V: int, temperature: float, k: int, top_p: fl
     dt, ld, rows = _logits_2d(logits)
     out = out or alloc_compressed(rows, k, logits.device)
     _check(_nat.compress(logits, dt, ld, rows, V, temperature, k, top_p, out.idx, out.prob, out.count, out.mass, out.lse,
-                       _nat.scratch(logits, CALL_COMPRESS, dt, rows, V, k), _stream()))
+                       _nat.scratch(logits, CALL_COMPRESS, dt, rows, 0, V, k), _stream()))
     return out
 
 
@@ -216,7 +218,7 @@ def verify(tgt_logits: torch.Tensor, V: int, temperature: float, seq_off: torch.
     rec = (q.idx, q.prob, q.count, q.mass, q.k) if q else _NO_RECORDS
     _check(_nat.verify(tgt_logits, dt, ld, V, temperature, B, n_draft, seq_off, draft_tok, *rec, renorm, q_scalar, uniforms,
                      out.n_accept, out.p_tok, out.q_tok, out.tgt_max, out.tgt_sum, out.tgt_lse, out.flags,
-                     _table(workspace, dt, n_draft + B, V, tgt_logits), _stream()))
+                     _table(workspace, CALL_VERIFY, dt, n_draft, B, V, tgt_logits), _stream()))
     return out
 
 
@@ -236,7 +238,7 @@ def verify_range(tgt_logits: torch.Tensor, V: int, temperature: float, seq_off: 
     _check(_nat.verify_range(tgt_logits, dt, ld, V, temperature, B, n_draft, seq_off, draft_tok, *rec, renorm, q_scalar, uniforms,
                            pos_begin, pos_end, gamma_max,
                            out.n_accept, out.p_tok, out.q_tok, out.tgt_max, out.tgt_sum, out.tgt_lse, out.flags,
-                           _table(None, dt, n_draft + B, V, tgt_logits), _stream()))
+                           _table(None, CALL_VERIFY, dt, n_draft, B, V, tgt_logits), _stream()))
     return out
 
 
@@ -255,7 +257,7 @@ def round(draft_logits: torch.Tensor, tgt_logits: torch.Tensor, V: int, temperat
     ver = ver or alloc_verified(B, n_draft, dev)
     res = res or alloc_residual(B, dev)
     # few draft rows: the call's own buffer, the segment table and the split kernels' scratch
-    own = _nat.round_scratch(tgt_logits, dt, n_draft, B, V, k)
+    own = _nat.scratch(tgt_logits, CALL_ROUND, dt, n_draft, B, V, k)
     _check(_nat.round(draft_logits, tgt_logits, dt, ld_d, ld_t, V, temperature, B, n_draft, seq_off, draft_tok, k, top_p, renorm,
                     uniforms, q.idx, q.prob, q.count, q.mass, q.lse,
                     ver.n_accept, ver.p_tok, ver.q_tok, ver.tgt_max, ver.tgt_sum, ver.tgt_lse, ver.flags,
@@ -275,7 +277,7 @@ def verify_sample(tgt_logits: torch.Tensor, V: int, temperature: float, seq_off:
     _check(_nat.verify_sample(tgt_logits, dt, ld, V, temperature, B, n_draft, seq_off, draft_tok,
                             q.idx, q.prob, q.count, q.mass, q.k, renorm, uniforms,
                             ver.n_accept, ver.p_tok, ver.q_tok, ver.tgt_max, ver.tgt_sum, ver.tgt_lse, ver.flags,
-                            res.out_tok, res.resid_mass, res.flags, _table(workspace, dt, n_draft + B, V, tgt_logits), _stream()))
+                            res.out_tok, res.resid_mass, res.flags, _table(workspace, CALL_VERIFY_SAMPLE, dt, n_draft, B, V, tgt_logits), _stream()))
     return ver, res
 
 
@@ -308,11 +310,6 @@ def static_scratch_bytes() -> int:
     return int(lib.picospec_static_scratch_bytes())
 
 
-def _residual_split(dt: int, B: int, V: int, k: int) -> bool:
-    """Whether a draw that is given no table makes one of the rows it draws from (residual_split_serves in csrc/kernels.hpp)."""
-    return 0 < B <= 1024 and k <= 1024 and V * (2 if dt == 1 else 4) > 65536 and (k <= 256 or B <= 128 or B > 256)
-
-
 def sample_residual(tgt_logits: torch.Tensor, V: int, temperature: float, seq_off: torch.Tensor, n_draft: int,
                     ver: Verified, q: Compressed, uniforms: torch.Tensor, renorm: int = 1,
                     out: Residual | None = None, n_accept: torch.Tensor | None = None,
@@ -323,8 +320,10 @@ def sample_residual(tgt_logits: torch.Tensor, V: int, temperature: float, seq_of
     B = seq_off.shape[0] - 1
     out = out or alloc_residual(B, tgt_logits.device)
     call = _nat.sample_residual
-    if workspace is None and _residual_split(dt, B, V, q.k):
-        call, workspace = _nat.sample_residual_ws, _nat.scratch(tgt_logits, CALL_SAMPLE_RESIDUAL, dt, n_draft + B, V, 0)
+    if workspace is None:                        # (the draw may make a table of the rows it draws from)
+        workspace = _nat.scratch(tgt_logits, CALL_SAMPLE_RESIDUAL, dt, n_draft, B, V, q.k)
+        if workspace is not None:
+            call = _nat.sample_residual_ws
     _check(call(tgt_logits, dt, ld, V, temperature, B, n_draft, seq_off,
                 ver.n_accept if n_accept is None else n_accept, ver.tgt_max, ver.tgt_sum,
                 q.idx, q.prob, q.count, q.mass, q.k, renorm, uniforms, out.out_tok, out.resid_mass, out.flags,
@@ -336,7 +335,7 @@ def row_stats(logits: torch.Tensor, V: int, temperature: float):
     """picospec_row_stats -> (row_max, row_sum, row_lse), float32 [rows] each."""
     dt, ld, rows = _logits_2d(logits)
     mx, sm, ls = _nat.empty(logits, "fff", rows, rows, rows)
-    _check(_nat.row_stats(logits, dt, ld, rows, V, temperature, mx, sm, ls, _table(None, dt, rows, V, logits), _stream()))
+    _check(_nat.row_stats(logits, dt, ld, rows, V, temperature, mx, sm, ls, _table(None, CALL_ROW_STATS, dt, rows, 0, V, logits), _stream()))
     return mx, sm, ls
 
 
@@ -348,7 +347,7 @@ def compress_rejected(tgt_logits: torch.Tensor, V: int, temperature: float, seq_
     out = out or alloc_compressed(B, k, tgt_logits.device)
     _check(_nat.compress_rejected(tgt_logits, dt, ld, V, temperature, B, n_draft, seq_off, n_accept, k, top_p,
                                 out.idx, out.prob, out.count, out.mass, out.lse,
-                                _nat.scratch(tgt_logits, CALL_COMPRESS_REJECTED, dt, B, V, k), _stream()))
+                                _nat.scratch(tgt_logits, CALL_COMPRESS_REJECTED, dt, n_draft, B, V, k), _stream()))
     return out
 
 
@@ -438,6 +437,10 @@ def max_load_byte(which: int, dtype: int, V: int, misalign_bytes: int) -> int:
 
 def workspace_bytes(which: int, dtype: int, rows: int, V: int, k: int) -> int:
     return int(lib.picospec_workspace_bytes(which, dtype, rows, V, k))
+
+
+def scratch_bytes(which: int, dtype: int, n_draft: int, B: int, V: int, k: int) -> int:
+    return int(lib.picospec_scratch_bytes(which, dtype, n_draft, B, V, k))
 
 
 def limit(which: int) -> int:

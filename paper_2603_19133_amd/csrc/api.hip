@@ -493,6 +493,26 @@ size_t picospec_workspace_bytes(int which_call, int dtype, int32_t rows, int32_t
     }
 }
 
+size_t picospec_scratch_bytes(int which_call, int dtype, int32_t n_draft, int32_t B, int32_t V, int32_t k)
+{
+    const int64_t rows = (int64_t)n_draft + B;
+    if ((dtype != PICOSPEC_F32 && dtype != PICOSPEC_BF16) || n_draft < 0 || B < 0 || rows > INT32_MAX || V < 1 || V > kMaxV) return 0;
+    switch (which_call) {
+        case PICOSPEC_CALL_COMPRESS: return split_scratch_bytes(dtype, n_draft, V, k);
+        case PICOSPEC_CALL_COMPRESS_REJECTED: return split_scratch_bytes(dtype, B, V, k);
+        case PICOSPEC_CALL_VERIFY: case PICOSPEC_CALL_VERIFY_SAMPLE: case PICOSPEC_CALL_ROW_STATS:
+            return split_stats_serves(rows, V) ? seg_table_bytes(dtype, rows, V) : 0;
+        case PICOSPEC_CALL_SAMPLE_RESIDUAL:
+            return residual_split_serves(dtype, B, V, k) ? seg_table_bytes(dtype, rows, V) : 0;
+        case PICOSPEC_CALL_ROUND:
+        {
+            const size_t split = split_scratch_bytes(dtype, n_draft, V, k);
+            return split ? (round_seg_table_bytes(dtype, rows, V) + 15) / 16 * 16 + split : 0;
+        }
+        default: return 0;
+    }
+}
+
 int64_t picospec_max_load_byte(int which_call, int dtype, int32_t V, int32_t misalign_bytes)
 {
     if (which_call != PICOSPEC_CALL_COMPRESS && which_call != PICOSPEC_CALL_SAMPLE_RESIDUAL) return -1;

@@ -244,16 +244,14 @@ PyObject* n_rows2d(PyObject*, PyObject* o) {
 
 at::TensorOptions like(PyObject* o, at::ScalarType type) { return at::TensorOptions().dtype(type).device(THPVariable_Unpack(o).device()); }
 
-// scratch(like, which, dtype, rows, V, k) -> uint8 tensor of picospec_workspace_bytes(...) bytes, None where that is 0
-PyObject* n_scratch(PyObject*, PyObject* const* v, Py_ssize_t n) {
+// scratch_bytes(which, dtype, n_draft, B, V, k) -> picospec_scratch_bytes(...)
+PyObject* n_scratch_bytes(PyObject*, PyObject* const* v, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     try {
-        if (n != 6 || !THPVariable_Check(v[0])) throw BadArgument("scratch(tensor, which, dtype, rows, V, k)");
-        Args a{v, n, 1};
-        const int which = a.i32(), dt = a.i32(), rows = a.i32(), V = a.i32(), k = a.i32();
-        const size_t bytes = picospec_workspace_bytes(which, dt, rows, V, k);
-        if (!bytes) Py_RETURN_NONE;
-        return THPVariable_Wrap(at::empty({(int64_t)bytes}, like(v[0], at::kByte)));
+        Args a{v, n};
+        const int which = a.i32(), dt = a.i32(), N = a.i32(), B = a.i32(), V = a.i32(), k = a.i32();
+        a.done();
+        return PyLong_FromSize_t(picospec_scratch_bytes(which, dt, N, B, V, k));
     } catch (const BadArgument& e) {
         if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, e.what());
         return nullptr;
@@ -261,18 +259,16 @@ PyObject* n_scratch(PyObject*, PyObject* const* v, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// round_scratch(like, dtype, n_draft, B, V, k) -> the workspace with which picospec_round spreads its draft rows over many
-// workgroups (the segment table and, behind it, the split kernels' scratch); None where the draft rows are not split
-PyObject* n_round_scratch(PyObject*, PyObject* const* v, Py_ssize_t n) {
+// scratch(like, which, dtype, n_draft, B, V, k) -> uint8 tensor of picospec_scratch_bytes(...) bytes, None where that is 0
+PyObject* n_scratch(PyObject*, PyObject* const* v, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     try {
-        if (n != 6 || !THPVariable_Check(v[0])) throw BadArgument("round_scratch(tensor, dtype, n_draft, B, V, k)");
+        if (n != 7 || !THPVariable_Check(v[0])) throw BadArgument("scratch(tensor, which, dtype, n_draft, B, V, k)");
         Args a{v, n, 1};
-        const int dt = a.i32(), N = a.i32(), B = a.i32(), V = a.i32(), k = a.i32();
-        const size_t split = picospec_workspace_bytes(PICOSPEC_CALL_COMPRESS, dt, N, V, k);
-        if (!split) Py_RETURN_NONE;
-        const size_t table = (picospec_workspace_bytes(PICOSPEC_CALL_ROUND, dt, N + B, V, 0) + 15) / 16 * 16;
-        return THPVariable_Wrap(at::empty({(int64_t)(table + split)}, like(v[0], at::kByte)));
+        const int which = a.i32(), dt = a.i32(), N = a.i32(), B = a.i32(), V = a.i32(), k = a.i32();
+        const size_t bytes = picospec_scratch_bytes(which, dt, N, B, V, k);
+        if (!bytes) Py_RETURN_NONE;
+        return THPVariable_Wrap(at::empty({(int64_t)bytes}, like(v[0], at::kByte)));
     } catch (const BadArgument& e) {
         if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, e.what());
         return nullptr;
@@ -316,7 +312,7 @@ PyMethodDef methods[] = {
     FAST("round", n_round), FAST("verify_sample", n_verify_sample), FAST("verify_sample_static", n_verify_sample_static),
     FAST("sample_residual", n_sample_residual<picospec_sample_residual>), FAST("sample_residual_ws", n_sample_residual<picospec_sample_residual_ws>), FAST("row_stats", n_row_stats), FAST("compress_rejected", n_compress_rejected),
     FAST("resample_sparse", n_resample_sparse), FAST("pack_downlink", n_pack_downlink), FAST("unpack_downlink", n_unpack_downlink),
-    FAST("pack_uplink", n_pack_uplink), FAST("unpack_uplink", n_unpack_uplink), FAST("scratch", n_scratch), FAST("round_scratch", n_round_scratch), FAST("empty", n_empty),
+    FAST("pack_uplink", n_pack_uplink), FAST("unpack_uplink", n_unpack_uplink), FAST("scratch_bytes", n_scratch_bytes), FAST("scratch", n_scratch), FAST("empty", n_empty),
     {"rows2d", (PyCFunction)n_rows2d, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -84,3 +84,23 @@ def test_split_kernels_keep_claimed_slots_in_registers():
     assert sum(v["atomics"] >= 8 for v in seen.values()) == 2, seen          # the finishing kernel, both types
     assert all(v["in_window"] == 0 for v in seen.values()), seen
     assert all(v["scratch"] == 0 for k, v in seen.items() if "select" in k or "split_round" in k), seen
+
+
+def test_the_binding_asks_the_library_for_its_scratch(B):
+    """One copy of the rules: what the binding allocates is what picospec_scratch_bytes says, 0 where a call has no use for it."""
+    f, w = B.scratch_bytes, B.workspace_bytes
+    for dt in (B.F32, B.BF16):
+        for rows in (0, 1, 8, 64, 80, 128, 129, 192, 193, 224, 225, 1000):
+            for V in (4096, 16383, 16384, 33001, 151936):
+                for k in (10, 1024, 4096):
+                    assert f(B.CALL_COMPRESS, dt, rows, 0, V, k) == f(B.CALL_COMPRESS_REJECTED, dt, 7, rows, V, k) == w(B.CALL_COMPRESS, dt, rows, V, k)
+                    for which in (B.CALL_VERIFY, B.CALL_VERIFY_SAMPLE, B.CALL_ROW_STATS):
+                        n = f(which, dt, rows, 0, V, k)
+                        assert n in (0, w(B.CALL_VERIFY, dt, rows, V, 0)) and B._split_stats(which, dt, rows, 0, V) == (n > 0)
+                    # a round's is its table and, behind it, the scratch of its draft rows
+                    n = f(B.CALL_ROUND, dt, rows, 3, V, k)
+                    assert n == 0 or n == -(-w(B.CALL_ROUND, dt, rows + 3, V, 0) // 16) * 16 + w(B.CALL_COMPRESS, dt, rows, V, k)
+    assert f(B.CALL_SAMPLE_RESIDUAL, B.F32, 8, 8, 151936, 64) > 0 and f(B.CALL_SAMPLE_RESIDUAL, B.F32, 8, 8, 4096, 64) == 0
+    for bad in ((B.CALL_VERIFY, 7, 8, 1, 151936), (B.CALL_VERIFY, B.F32, -1, 1, 151936), (B.CALL_VERIFY, B.F32, 8, 1, 0),
+                (B.CALL_VERIFY, B.F32, 8, 1, (1 << 20) + 1), (B.CALL_VERIFY, B.F32, 2 ** 31 - 1, 1, 151936), (B.CALL_SAMPLE_DRAFT, B.F32, 8, 1, 151936)):
+        assert f(*bad, 64) == 0
