@@ -276,7 +276,8 @@ int picospec_resample_sparse(const void* draft_logits, int dtype, int64_t ld, in
  * leaves the target rows' segment table there (in a layout of its own: the table of one call of picospec_round serves that
  * call only) and draws from it without a second pass over the target row.  The size for the record length k instead of 0
  * holds scratch as well (few rows only; the same size where there are more): the draft rows, and the target rows with
- * them, are then spread over many workgroups, three launches that each take a fraction of the two.  Records then hold the
+ * them, are then spread over many workgroups where that is faster (picospec_scratch_bytes says where, and how many bytes the
+ * call needs by its own n_draft), three launches that each take a fraction of the two.  Records then hold the
  * same ids, and probabilities agree to rounding, as with picospec_compress given a workspace.
  */
 int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, int64_t ld_draft, int64_t ld_tgt,

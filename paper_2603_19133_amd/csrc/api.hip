@@ -202,7 +202,7 @@ int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, 
     // (a workspace that holds the split kernels' scratch behind the segment table: few draft rows are spread over many
     //  workgroups, and with few target rows their statistics as well)
     const size_t table_bytes = (round_seg_table_bytes(dtype, rows, V) + 15) / 16 * 16;
-    const bool split_draft = n_draft > 0 && workspace && workspace_bytes > table_bytes &&
+    const bool split_draft = n_draft > 0 && workspace && workspace_bytes > table_bytes && round_split_serves(dtype, n_draft, rows, V, k) &&
                              split_fits(dtype, n_draft, V, k, (char*)workspace + table_bytes, workspace_bytes - table_bytes);
     const bool split_stats = split_draft && split_stats_serves(rows, V);
     if (split_draft) {
@@ -506,8 +506,8 @@ size_t picospec_scratch_bytes(int which_call, int dtype, int32_t n_draft, int32_
             return residual_split_serves(dtype, B, V, k) ? seg_table_bytes(dtype, rows, V) : 0;
         case PICOSPEC_CALL_ROUND:
         {
-            const size_t split = split_scratch_bytes(dtype, n_draft, V, k);
-            return split ? (round_seg_table_bytes(dtype, rows, V) + 15) / 16 * 16 + split : 0;
+            if (!round_split_serves(dtype, n_draft, rows, V, k)) return 0;
+            return (round_seg_table_bytes(dtype, rows, V) + 15) / 16 * 16 + split_scratch_bytes(dtype, n_draft, V, k);
         }
         default: return 0;
     }

@@ -171,6 +171,23 @@ inline StatsShape split_stats_shape(int dtype, int V) {
 }
 inline int split_stats_parts(int stride) { return (stride + 4 * kSplitStatsSpw - 1) / (4 * kSplitStatsSpw); }   // workgroups of four waves per row
 inline bool split_stats_serves(int64_t rows, int V) { return rows >= 1 && rows <= kSplitStatsRows && V >= kSplitMinV; }
+// Whether a round spreads its draft rows (with scratch at hand): where picospec_compress would (the records of a round are then
+// those of a call of its own, bit for bit), unless the launch that otherwise streams the draft and the target rows at once, and
+// hides most of the drafts' serial phases, is faster.  us, one launch for both / spread:
+//   * rounds beyond kRoundSmallRows, which launch their streams one after the other: always (64 + 450 sequences of 16,384 fp32,
+//     k = 64: 34.6 / 31.9; 16 + 500 of 151,936, k = 4096: 117.6 / 108.5);
+//   * smaller rounds whose statistics are spread with them: up to 48 drafts for the longest records (48 and 48 of 151,936 fp32, k =
+//     4096: 52.6 / 53.1, 64 and 64: 53.6 / 58.0, bf16 of 64,000 80 and 80: 41.3 / 45.7), else always (192 and 32, k = 256: 64.0 / 58.3;
+//     80 and 20, k = 2048: 44.8 / 44.8, k = 1024: 40.5 / 40.0; the other way by up to 8 % around 200 rows of 64,000 in all);
+//   * with more target rows than that four launches stand against two (128 + 128 of 151,936 fp32, k = 64: 53.6 / 58.6; 20 + 300, k =
+//     4096: 65.5 / 87.9), but for bf16 rows of 192 KB and more, bound by the vector ALUs of their CUs, where the one launch no
+//     longer has a CU for every row (160 + 80 of 100,000, k = 64: 41.7 / 40.9, of 151,936: 52.4 / 47.3, 192 + 64: 53.6 / 50.5).
+inline bool round_split_serves(int dtype, int64_t n_draft, int64_t rows, int V, int k) {
+    if (split_plan(dtype, n_draft, V, k).parts == 0) return false;
+    if (n_draft + rows > kRoundSmallRows) return true;
+    if (split_stats_serves(rows, V)) return k <= 2048 || n_draft <= 48;
+    return dtype == 1 && V >= 96 * 1024 && n_draft >= 160 && rows <= 256;
+}
 // Where a draw that was given no table makes one of the rows it draws from (one workgroup per row passes over its row twice, and
 // is bound by the vector ALUs of one CU): 64 sequences x 33 001 fp32, k = 64: 17.2 -> 11.3 us; 64 x 151 936, k = 64: fp32 29.5 ->
 // 15.4, bf16 24.7 -> 13.2; 512: 73.4 -> 54.7, 50.4 -> 32.2; 1024: 139 -> 105, 98.7 -> 56.7.  The draw from a table gathers one logit per

@@ -104,3 +104,16 @@ def test_the_binding_asks_the_library_for_its_scratch(B):
     for bad in ((B.CALL_VERIFY, 7, 8, 1, 151936), (B.CALL_VERIFY, B.F32, -1, 1, 151936), (B.CALL_VERIFY, B.F32, 8, 1, 0),
                 (B.CALL_VERIFY, B.F32, 8, 1, (1 << 20) + 1), (B.CALL_VERIFY, B.F32, 2 ** 31 - 1, 1, 151936), (B.CALL_SAMPLE_DRAFT, B.F32, 8, 1, 151936)):
         assert f(*bad, 64) == 0
+
+
+def test_a_round_spreads_its_drafts_only_where_that_was_faster(B):
+    """By (drafts, sequences, V, k) as measured against the one launch for both streams: slower ones keep it, whatever the caller's
+    buffer."""
+    f = lambda dt, n, b, V, k: B.scratch_bytes(B.CALL_ROUND, dt, n, b, V, k) > 0
+    for dt in (B.F32, B.BF16):
+        for n, b, k in ((20, 300, 64), (20, 300, 4096), (64, 300, 4096), (128, 128, 1024), (128, 128, 64), (80, 80, 4096), (49, 10, 4096)):
+            assert not f(dt, n, b, 64000, k), (n, b, k)
+        for n, b, k in ((4, 1, 64), (64, 8, 256), (80, 20, 1024), (80, 20, 2048), (48, 3, 4096), (192, 32, 64), (64, 450, 64), (16, 500, 4096)):
+            assert f(dt, n, b, 151936, k), (n, b, k)
+    assert f(B.BF16, 160, 80, 151936, 64) and not f(B.F32, 160, 80, 151936, 64) and not f(B.BF16, 160, 80, 64000, 64)
+    assert not f(B.BF16, 0, 4, 151936, 64) and not f(B.BF16, 193, 4, 151936, 64)
