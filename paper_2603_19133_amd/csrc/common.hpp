@@ -300,7 +300,7 @@ __device__ __forceinline__ void block_softmax_stats(float m, float s, float c, d
     float bm = kNegInf;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) bm = fmaxf(bm, (float)sh[w]);
-    float scaled = (m == kNegInf) ? 0.f : s * __builtin_amdgcn_exp2f((m - bm) * c);
+    float scaled = (m == kNegInf) ? s : s * __builtin_amdgcn_exp2f((m - bm) * c);    // (nothing above -inf: s is 0, or NaN if a NaN was among it)
     double ws = wave_sum((double)scaled);
     if (lane == 0) sh[WAVES + wave] = ws;
     __syncthreads();
@@ -475,7 +475,7 @@ __device__ __forceinline__ void row_stats_seg_row(
     float M = kNegInf;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) M = fmaxf(M, (float)red[w]);
-    const double mine = r_w == kNegInf ? 0.0 : (double)s * exp2_split((double)r_w - (double)M * (double)c);
+    const double mine = r_w == kNegInf ? (double)s : (double)s * exp2_split((double)r_w - (double)M * (double)c);   // (r_w = -inf: s is 0 or NaN)
     const double ws = wave_sum(mine);
     if (lane == 0) red[WAVES + wave] = ws;
     __syncthreads();

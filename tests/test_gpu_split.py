@@ -315,6 +315,18 @@ def test_nan_in_a_segment_without_a_finite_value_is_flagged(gpu, ps, dtype, wher
         assert [bool(f & ps.FLAG_NONFINITE) for f in ver.flags.tolist()] == [False, True, False], (ver.flags, ver.tgt_sum)
         assert ver.tgt_sum.isnan().tolist() == [r == bad for r in range(2 * B)] and ver.tgt_lse.isnan().tolist() == ver.tgt_sum.isnan().tolist()
     assert ps.row_stats(z, V, 1.0)[1].isnan().tolist() == [r == bad for r in range(2 * B)]
+    # one workgroup per row, without and with the table of its own layout
+    out, p = ps.alloc_verified(B, B, gpu), lambda t: t.data_ptr()
+    ps._check(ps.lib.picospec_verify(p(z), ps._dtype_code(z), z.stride(0), V, 1.0, B, B, p(off), p(tok), p(q.idx), p(q.prob), p(q.count), p(q.mass), 8, 1,
+                                     None, p(u), p(out.n_accept), p(out.p_tok), p(out.q_tok), p(out.tgt_max), p(out.tgt_sum), p(out.tgt_lse),
+                                     p(out.flags), None, 0, torch.cuda.current_stream().cuda_stream))
+    many = z.repeat(40, 1) if z.stride(0) == V else torch.cat([base] * 40)[:, :V]       # (240 rows: more than are spread)
+    off40 = torch.arange(40 * B + 1, dtype=torch.int32, device=gpu)
+    tab = ps.verify(many, V, 1.0, off40, 40 * B, tok.repeat(40), None, u.repeat(40), q_scalar=u.repeat(40)[:40 * B].contiguous(),
+                    workspace=ps.alloc_workspace(dtype, 80 * B, V, gpu))
+    torch.cuda.synchronize()
+    assert [bool(f & ps.FLAG_NONFINITE) for f in out.flags.tolist()] == [False, True, False], out.flags
+    assert [bool(f & ps.FLAG_NONFINITE) for f in tab.flags.tolist()] == [False, True, False] * 40, tab.flags
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
@@ -365,3 +377,26 @@ def test_masks_of_a_finite_value_are_compressed_once(gpu, ps, dtype, mask, k, sh
     cap = (n // (R * parts) - 32) // 8
     found = ws.view(torch.int32)[:R * parts * 8].view(R * parts, 8)[:, 3]
     assert cap > 8 and int(found.max()) <= cap and int(found.view(R, parts).sum(1).min()) >= k, (cap, found)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V,R,T", [(16384, 4, 1.0), (33001, 224, 0.7), (64000, 64, 1.0), (128256, 128, 0.05), ((1 << 20) - 5, 2, 1.0)])
+def test_target_statistics_in_a_given_workspace(gpu, pu, ps, dtype, V, R, T):
+    """The statistics from the split table wherever a verification is given one, whole segments masked among them, against 64 bits;
+    and row_stats of the same rows, which takes the table or one workgroup per row by its own rule."""
+    _announce("split statistics in a given workspace", dtype, V, R, T)
+    g = torch.Generator(device=gpu)
+    g.manual_seed(V)
+    z = (torch.randn((R, V + 3), device=gpu, generator=g) * 4).to(dtype)[:, 1:V + 1]
+    z[0, : V // 2] = torch.finfo(dtype).min
+    z[1, V // 2:] = float("-inf")
+    off = torch.tensor([0, R - 1], dtype=torch.int32, device=gpu)
+    tok, u = torch.zeros(R - 1, dtype=torch.int32, device=gpu), torch.rand(R, device=gpu, generator=g)
+    ver = ps.verify(z, V, T, off, R - 1, tok, None, u, q_scalar=torch.rand(R - 1, device=gpu, generator=g), workspace=ps.alloc_workspace(dtype, R, V, gpu))
+    x = z.double().cpu()
+    m = x.max(1).values
+    s = torch.exp((x - m[:, None]) / T).sum(1)
+    for mx, sm, lse in ((ver.tgt_max, ver.tgt_sum, ver.tgt_lse), ps.row_stats(z, V, T)):
+        assert torch.equal(mx.double().cpu(), m)
+        pu.assert_close(pu.n(sm), s.numpy(), pu.RTOL, "sum")
+        pu.assert_close(pu.n(lse), (m / T + torch.log(s)).numpy(), pu.RTOL_LSE, "lse", atol=2e-6)
