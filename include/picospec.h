@@ -218,7 +218,8 @@ int picospec_row_stats(const void* logits, int dtype, int64_t ld, int32_t n_rows
 
 /*
  * The same with an optional workspace of picospec_workspace_bytes(PICOSPEC_CALL_VERIFY, dtype, n_rows, V, 0) bytes: a call
- * of up to 224 rows then spreads every row over many workgroups (the sums are formed in another order and agree to rounding).
+ * of few long rows then spreads every row over many workgroups where that is faster (picospec_scratch_bytes; the sums are formed
+ * in another order and agree to rounding).
  */
 int picospec_row_stats_ws(const void* logits, int dtype, int64_t ld, int32_t n_rows, int32_t V, float temperature,
                           float* row_max, float* row_sum, float* row_lse,

@@ -121,7 +121,7 @@ int picospec_row_stats_ws(const void* logits, int dtype, int64_t ld, int32_t n_r
     if (n_rows > 0 && (!row_max || !row_sum)) return PICOSPEC_EINVAL;
     if (int rc = check_workspace(PICOSPEC_CALL_VERIFY, dtype, n_rows, V, 0, workspace, workspace_bytes)) return rc;
     hipStream_t s = (hipStream_t)stream;
-    if (!workspace || !split_stats_serves(n_rows, V))
+    if (!workspace || !row_stats_split_serves(dtype, n_rows, V))
         return hip_status(launch_row_stats(logits, dtype, ld, n_rows, V, temperature, row_max, row_sum, row_lse, nullptr, s));
     if (hipError_t e = launch_row_stats_parts(logits, dtype, ld, n_rows, V, temperature, 0, 0, nullptr, nullptr, nullptr, workspace, s))
         return hip_status(e);
@@ -500,8 +500,9 @@ size_t picospec_scratch_bytes(int which_call, int dtype, int32_t n_draft, int32_
     switch (which_call) {
         case PICOSPEC_CALL_COMPRESS: return split_scratch_bytes(dtype, n_draft, V, k);
         case PICOSPEC_CALL_COMPRESS_REJECTED: return split_scratch_bytes(dtype, B, V, k);
-        case PICOSPEC_CALL_VERIFY: case PICOSPEC_CALL_VERIFY_SAMPLE: case PICOSPEC_CALL_ROW_STATS:
-            return split_stats_serves(rows, V) ? seg_table_bytes(dtype, rows, V) : 0;
+        case PICOSPEC_CALL_VERIFY: return verify_scratch_serves(dtype, rows, V) ? seg_table_bytes(dtype, rows, V) : 0;
+        case PICOSPEC_CALL_VERIFY_SAMPLE: return split_stats_serves(rows, V) ? seg_table_bytes(dtype, rows, V) : 0;
+        case PICOSPEC_CALL_ROW_STATS: return row_stats_split_serves(dtype, rows, V) ? seg_table_bytes(dtype, rows, V) : 0;
         case PICOSPEC_CALL_SAMPLE_RESIDUAL:
             return residual_split_serves(dtype, B, V, k) ? seg_table_bytes(dtype, rows, V) : 0;
         case PICOSPEC_CALL_ROUND:

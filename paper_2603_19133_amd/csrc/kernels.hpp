@@ -171,6 +171,23 @@ inline StatsShape split_stats_shape(int dtype, int V) {
 }
 inline int split_stats_parts(int stride) { return (stride + 4 * kSplitStatsSpw - 1) / (4 * kSplitStatsSpw); }   // workgroups of four waves per row
 inline bool split_stats_serves(int64_t rows, int V) { return rows >= 1 && rows <= kSplitStatsRows && V >= kSplitMinV; }
+// Calls that are given no workspace and would need one for their statistics alone.  A verification without a draw gains less
+// (its second launch is there either way; the draw that the table serves is another call's), row_stats pays a second launch.  us, one
+// workgroup per row / spread, device time:
+//   * verification, fp32: rows of 16,384: 9.4 / 10.6 (160 rows), 20,000: 10.6 / 9.8 (64), 10.8 / 11.0 (192), 32,000: 10.9 / 10.5 (128),
+//     12.0 / 12.3 (224), 64,000: 13.6 / 12.9 (128), 14.5 / 14.8 (192), 151,936: 22.5 / 21.9 (160), 24.4 / 24.7 (192);
+//     bf16: 16,384: 9.6 / 10.9 (160), 20,000: 10.2 / 9.8 (128), 10.3 / 10.5 (224), 32,000: 10.3 / 10.7 (160), 64,000: 12.6 / 12.3 (192),
+//     151,936: 18.6 / 16.8 (192), 18.7 / 18.3 (224);
+//   * row_stats: fp32: 32,000: 6.5 / 8.1 (64), 64,000: 9.2 / 8.4 (64), 9.4 / 10.2 (128), 151,936: 17.4 / 16.9 (128), 18.6 / 19.6 (160);
+//     bf16: 64,000: 8.1 / 8.3 (64), 151,936: 14.5 / 13.4 (160), 14.6 / 14.8 (192).
+inline bool verify_scratch_serves(int dtype, int64_t rows, int V) {
+    if (!split_stats_serves(rows, V) || V < 20000) return false;
+    return rows <= (dtype != 1 ? 160 : V >= 64000 ? kSplitStatsRows : 128);
+}
+inline bool row_stats_split_serves(int dtype, int64_t rows, int V) {
+    const int64_t row_bytes = (int64_t)V * (dtype == 1 ? 2 : 4);
+    return split_stats_serves(rows, V) && row_bytes >= 250000 && rows <= (dtype == 1 ? 160 : row_bytes >= 500000 ? 128 : 64);
+}
 // Whether a round spreads its draft rows (with scratch at hand): where picospec_compress would (the records of a round are then
 // those of a call of its own, bit for bit), unless the launch that otherwise streams the draft and the target rows at once, and
 // hides most of the drafts' serial phases, is faster.  us, one launch for both / spread:

@@ -117,3 +117,14 @@ def test_a_round_spreads_its_drafts_only_where_that_was_faster(B):
             assert f(dt, n, b, 151936, k), (n, b, k)
     assert f(B.BF16, 160, 80, 151936, 64) and not f(B.F32, 160, 80, 151936, 64) and not f(B.BF16, 160, 80, 64000, 64)
     assert not f(B.BF16, 0, 4, 151936, 64) and not f(B.BF16, 193, 4, 151936, 64)
+
+
+def test_statistics_are_spread_without_a_workspace_only_where_that_was_faster(B):
+    f = lambda which, dt, rows, V: B.scratch_bytes(which, dt, rows, 0, V, 0) > 0
+    for V, f32, bf16 in ((16384, 0, 0), (20000, 160, 128), (32000, 160, 128), (64000, 160, 224), (151936, 160, 224)):
+        for dt, most in ((B.F32, f32), (B.BF16, bf16)):
+            assert f(B.CALL_VERIFY, dt, most or 1, V) == (most > 0) and not f(B.CALL_VERIFY, dt, most + 1, V)
+            assert f(B.CALL_VERIFY_SAMPLE, dt, 224, V) and not f(B.CALL_VERIFY_SAMPLE, dt, 225, V)       # (the draw works from the table)
+    for V, f32, bf16 in ((32000, 0, 0), (62500, 64, 0), (64000, 64, 0), (128256, 128, 160), (151936, 128, 160)):
+        for dt, most in ((B.F32, f32), (B.BF16, bf16)):
+            assert f(B.CALL_ROW_STATS, dt, most or 1, V) == (most > 0) and not f(B.CALL_ROW_STATS, dt, most + 1, V)
