@@ -389,7 +389,7 @@ int verify_impl(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float 
     return hip_status(launch_accept(tgt_logits, dtype, ld, V, temperature, B, seq_off, draft_tok, q_idx, q_prob,
                                     q_count, q_mass, k, renorm, q_scalar, uniforms, tgt_max, tgt_sum, tgt_lse,
                                     n_accept, p_tok, q_tok, flags, ranged ? pos_begin : nullptr,
-                                    ranged ? pos_end : nullptr, split ? workspace : nullptr, ranged ? 0 : rows, s));
+                                    ranged ? pos_end : nullptr, split ? workspace : nullptr, rows, !ranged, s));
 }
 
 }  // namespace

@@ -74,7 +74,7 @@ __device__ __forceinline__ int accept_sequence(
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok,
     uint32_t* __restrict__ flags, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end,
     float* __restrict__ tgt_lse = nullptr, const SegHeader* __restrict__ table = nullptr, int seg_vecs = 0, int stride = 0,
-    int n_rows = 0, SplitStats* s_stats = nullptr, int2* rows = nullptr)
+    int n_rows = 0, bool all_rows = false, SplitStats* s_stats = nullptr, int2* rows = nullptr)
 {
     __shared__ int s_first;
     __shared__ unsigned s_flags;
@@ -99,13 +99,22 @@ __device__ __forceinline__ int accept_sequence(
             if (nonfinite(tgt_max[t0 + t], tgt_sum[t0 + t])) fl |= 2u;
     }
 
-    // (TABLE: the row behind the last position as well, and, by the last sequence's workgroup, rows of the call behind the
-    //  last sequence: n_draft may be larger than seq_off[B], as for a batch that an uplink message clamped)
-    int rows_end = end;                               // positions begin .. rows_end - 1
-    if constexpr (TABLE) rows_end = (b + 1 == (int)gridDim.x && n_rows > 0) ? max(end + 1, (int)(n_rows - t0)) : end + 1;
-    for (int i = begin + wave; i < rows_end; i += kWaves) {
+    // (TABLE: the row behind the last position as well, and, where all of the call's rows get statistics, by the first and the last
+    //  sequence's workgroup those in front of the first and behind the last sequence: seq_off may start above 0, and n_draft may be
+    //  larger than seq_off[B], as for a batch that an uplink message clamped)
+    int rows_begin = begin, rows_end = end;           // positions rows_begin .. rows_end - 1
+    if constexpr (TABLE) {
+        rows_begin = all_rows && b == 0 ? min(begin, -(int)t0) : begin;
+        rows_end = all_rows && b + 1 == (int)gridDim.x ? max(end + 1, (int)(n_rows - t0)) : end + 1;
+    }
+    for (int i = rows_begin + wave; i < rows_end; i += kWaves) {
         const int64_t rt = t0 + i;
-        const bool decides = !TABLE || i < end;       // (the row behind the last position has statistics only)
+        const bool decides = !TABLE || (i >= begin && i < end);       // (the other rows have statistics only)
+        if (TABLE && (rt < 0 || rt >= n_rows)) {      // (offsets that leave the call's rows: nothing is written for such a row)
+            fl |= 8u;
+            if (decides && lane == 0) atomicMin(&s_first, i);
+            continue;
+        }
         const int64_t rd = (int64_t)d0 + (decides ? i : 0);
         int x = -1, cnt = 0;
         float u_t = 0.f, mass_d = 1.f, M_t = 0.f, S_t = 1.f;
@@ -140,9 +149,9 @@ __device__ __forceinline__ int accept_sequence(
             if (lane == 0) {
                 tgt_max[rt] = M_t;
                 tgt_sum[rt] = S_t;
-                if (s_stats && i < kSplitStatsRows) s_stats[i] = SplitStats{S, M_t};
+                if (s_stats && i >= begin && i < kSplitStatsRows) s_stats[i] = SplitStats{S, M_t};
                 else if (tgt_lse) tgt_lse[rt] = (float)((double)M_t * (double)inv_T + log(S));
-                if (i <= end && nonfinite(M_t, S_t)) fl |= 2u;
+                if (i >= begin && i <= end && nonfinite(M_t, S_t)) fl |= 2u;
             }
             if (!decides) continue;
         }

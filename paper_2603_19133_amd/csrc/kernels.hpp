@@ -250,7 +250,7 @@ hipError_t launch_accept(const void* tgt_logits, int dtype, int64_t ld, int V, f
                          float* tgt_max, float* tgt_sum, float* tgt_lse,
                          int32_t* n_accept, float* p_tok, float* q_tok, uint32_t* flags,
                          const int32_t* pos_begin, const int32_t* pos_end,
-                         const void* split_table, int64_t n_rows, hipStream_t stream);
+                         const void* split_table, int64_t n_rows, bool all_rows, hipStream_t stream);
 
 // threads of the draw from the segment table: a thread holds two record entries of records of up to 512 entries, four of
 // longer ones
@@ -270,7 +270,8 @@ hipError_t launch_residual_split(const void* tgt_logits, int dtype, int64_t ld, 
                                  int k, int renorm, const float* uniforms,
                                  int32_t* out_tok, float* resid_mass, uint32_t* flags, void* scratch, int64_t n_rows, hipStream_t stream);
 
-// (launch_accept: split_table non-null: the rows' statistics are formed from that table, tgt_max / tgt_sum / tgt_lse written)
+// (launch_accept: split_table non-null: the rows' statistics are formed from that table, tgt_max / tgt_sum / tgt_lse written;
+// all_rows: those of all n_rows rows of the call, else of the sequences' positions in the range)
 // acceptance and residual draw of every sequence in one launch; split_table: the table holds the split layout, and the rows'
 // statistics are formed from it and written; seg_table (nullable, also in launch_residual): the
 // table of the n_rows target rows from launch_row_stats (small_round_table: from launch_round_stream, whose layout

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kThreads) void decide_seg_kernel(
     const int first = accept_sequence<BF16, SPLIT>(blockIdx.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
                                                    q_count, q_mass, k, renorm, nullptr, uniforms, tgt_max, tgt_sum,
                                                    n_accept, p_tok, q_tok, flags, nullptr, nullptr,
-                                                   tgt_lse, table, seg_vecs, stride, n_rows, SPLIT ? s_stats : nullptr, &rows);
+                                                   tgt_lse, table, seg_vecs, stride, n_rows, true, SPLIT ? s_stats : nullptr, &rows);
     const int64_t t0 = (int64_t)seq_off[blockIdx.x] + blockIdx.x;
     // the waves that the draw has no use for write the log-sum-exps and end here (a barrier waits for those that are left)
     if (RT < kThreads) {

@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256) void row_stats_parts_kernel(
             if (t < begin || t > end) return;
         }
         row = (int64_t)d0 + b + t;
-        if (n_accept && (row < 0 || row >= n_rows)) return;
+        if (row < 0 || row >= n_rows) return;           // (offsets that leave the call's rows)
     }
     row_stats_parts<BF16, kSplitStatsNV, kSplitStatsSpw>(row, (int)blockIdx.x, logits, ld, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
 }
@@ -108,11 +108,11 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(
     float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok,
     uint32_t* __restrict__ flags, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end,
-    const SegHeader* __restrict__ table, int seg_vecs, int stride, int n_rows)
+    const SegHeader* __restrict__ table, int seg_vecs, int stride, int n_rows, bool all_rows)
 {
     accept_sequence<BF16, TABLE>(blockIdx.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k,
                                  renorm, q_scalar, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok, flags, pos_begin, pos_end,
-                                 tgt_lse, table, seg_vecs, stride, n_rows);
+                                 tgt_lse, table, seg_vecs, stride, n_rows, all_rows);
 }
 
 }  // namespace
@@ -184,13 +184,13 @@ hipError_t launch_accept(const void* tgt_logits, int dtype, int64_t ld, int V, f
                          float* tgt_max, float* tgt_sum, float* tgt_lse,
                          int32_t* n_accept, float* p_tok, float* q_tok, uint32_t* flags,
                          const int32_t* pos_begin, const int32_t* pos_end,
-                         const void* split_table, int64_t n_rows, hipStream_t stream)
+                         const void* split_table, int64_t n_rows, bool all_rows, hipStream_t stream)
 {
     if (B == 0) return hipSuccess;
     const float inv_T = 1.0f / temperature;
     const StatsShape sh = split_stats_shape(dtype, V);
 #define PICOSPEC_ACCEPT(BF, TA) \
-    hipLaunchKernelGGL((accept_kernel<BF, TA>), dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, inv_T, B, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, q_scalar, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok, flags, pos_begin, pos_end, (const SegHeader*)split_table, sh.seg_vecs, sh.stride, (pos_begin || pos_end) ? 0 : (int)n_rows)
+    hipLaunchKernelGGL((accept_kernel<BF, TA>), dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, inv_T, B, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, q_scalar, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok, flags, pos_begin, pos_end, (const SegHeader*)split_table, sh.seg_vecs, sh.stride, (int)n_rows, all_rows)
     if (split_table) { if (dtype == 1) PICOSPEC_ACCEPT(true, true); else PICOSPEC_ACCEPT(false, true); }
     else             { if (dtype == 1) PICOSPEC_ACCEPT(true, false); else PICOSPEC_ACCEPT(false, false); }
 #undef PICOSPEC_ACCEPT

@@ -400,3 +400,35 @@ def test_target_statistics_in_a_given_workspace(gpu, pu, ps, dtype, V, R, T):
         assert torch.equal(mx.double().cpu(), m)
         pu.assert_close(pu.n(sm), s.numpy(), pu.RTOL, "sum")
         pu.assert_close(pu.n(lse), (m / T + torch.log(s)).numpy(), pu.RTOL_LSE, "lse", atol=2e-6)
+
+
+def test_rows_in_front_of_the_first_sequence_keep_their_statistics(gpu, ps):
+    """seq_off may start above 0: all n_draft + B rows get statistics, as with one workgroup per row."""
+    _announce("split statistics in front of the first sequence")
+    V, B, N = 20000, 2, 7
+    tgt = torch.randn((N + B, V), device=gpu)
+    off = torch.tensor([3, 4, 6], dtype=torch.int32, device=gpu)
+    tok, u = torch.zeros(N, dtype=torch.int32, device=gpu), torch.rand(N + B, device=gpu)
+    q = ps.compress(torch.randn((N, V), device=gpu), V, 1.0, 8)
+    for v in (ps.verify(tgt, V, 1.0, off, N, tok, None, u, q_scalar=torch.rand(N, device=gpu)), ps.verify_sample(tgt, V, 1.0, off, N, tok, q, u)[0]):
+        assert torch.equal(v.tgt_max, tgt.max(1).values)
+        assert torch.allclose(v.tgt_lse, torch.logsumexp(tgt, 1), rtol=1e-5)
+        assert not (v.flags & (ps.FLAG_BAD_INPUT | ps.FLAG_NONFINITE)).any()
+
+
+def test_offsets_beyond_the_rows_write_nothing_behind_them(gpu, ps):
+    """A negative gamma_b is flagged; the sequence it belongs to may start behind the call's rows, and what is behind those rows'
+    entries of the outputs stays as it was."""
+    _announce("split statistics, offsets beyond the rows")
+    V, B, N, room = 20000, 3, 3, 12
+    tgt = torch.randn((room, V), device=gpu)                      # (rows behind the call's six exist: nothing is read out of range)
+    off = torch.tensor([0, 5, 2, 3], dtype=torch.int32, device=gpu)
+    tok, u, qs = torch.zeros(room, dtype=torch.int32, device=gpu), torch.rand(room, device=gpu), torch.rand(room, device=gpu)
+    out = ps.alloc_verified(B, room, gpu)
+    for t in (out.tgt_max, out.tgt_sum, out.tgt_lse):
+        t.fill_(-7.0)
+    ps.verify(tgt, V, 1.0, off, N, tok, None, u, q_scalar=qs, out=out)
+    torch.cuda.synchronize()
+    for t in (out.tgt_max, out.tgt_sum, out.tgt_lse):
+        assert (t[:N + B] != -7.0).all() and (t[N + B:] == -7.0).all()
+    assert int(out.flags[1]) & ps.FLAG_BAD_INPUT
