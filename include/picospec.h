@@ -411,7 +411,8 @@ int picospec_unpack_uplink(const void* wire, int64_t wire_bytes, int32_t B, int3
  * misalign_bytes (0..15, a multiple of the element size) above a 16-byte boundary, the end (exclusive), in bytes
  * from the row's first byte, of the highest byte that the row loads of picospec_compress (which_call =
  * PICOSPEC_CALL_COMPRESS; also picospec_compress_rejected and picospec_round) or of picospec_sample_residual
- * (PICOSPEC_CALL_SAMPLE_RESIDUAL) can address, look-ahead loads behind the row included.  The library guarantees
+ * (PICOSPEC_CALL_SAMPLE_RESIDUAL; also the spread statistics of every call that takes target rows) can address, look-ahead
+ * loads behind the row included.  The library guarantees
  * that this lies inside the aligned 16-byte block that holds the row's last byte (a block that holds a valid byte
  * cannot leave that byte's page); the function evaluates the kernels' own addressing rule over every lane, so a test
  * can hold the library to it without a GPU.  The rule rests on one property of the device's buffer loads, which

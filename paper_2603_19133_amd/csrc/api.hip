@@ -66,7 +66,7 @@ int64_t max_load_end(int which, int V, int o)
         };
         sweep(CompressGeom<BF16, false>{});
         sweep(CompressGeom<BF16, true>{});
-        const int parts = split_parts(BF16, nq + 1);                            // ... and the split rows' blocks
+        const int parts = split_parts(BF16, row_vecs_max(BF16, V));            // ... and the split rows' blocks, of as many workgroups as are launched
         for (int j = 0; j < kSplitElems / (256 * N); ++j)
             for (int w = 0; w < 4; ++w)
                 for (int part = 0; part < parts; ++part)
@@ -80,6 +80,13 @@ int64_t max_load_end(int which, int V, int o)
                 for (int jv = 0; jv < G::NV; ++jv)
                     for (int lane = 0; lane < 64; ++lane)
                         end = std::max(end, buffer_lane_read_end(size, (int64_t)G::group_first(it, w, jv) * 16, (int64_t)lane * 16));
+        const int parts = stats_parts(stats_segments(row_vecs_max(BF16, V)));    // ... and the segments of rows whose statistics are spread
+        for (int part = 0; part < parts; ++part)
+            for (int w = 0; w < 4; ++w)
+                for (int i = 0; i < kSplitStatsSpw; ++i)
+                    for (int j = 0; j < kSplitStatsNV; ++j)
+                        for (int lane = 0; lane < 64; ++lane)
+                            end = std::max(end, buffer_lane_read_end(size, (int64_t)stats_group_first(stats_segment(part, w, i), j) * 16, (int64_t)lane * 16));
     }
     return end;
 }

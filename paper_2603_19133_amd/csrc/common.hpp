@@ -7,6 +7,8 @@
 
 #include <type_traits>
 
+#include "rowspan.hpp"
+
 namespace picospec {
 
 constexpr int kWave = 64;
@@ -504,18 +506,17 @@ __device__ __forceinline__ bool split_ref_fused(float m, float c) { return fabsf
 // m c as the sums' reference: rounded to fp32 as in the fused form of their terms; exact where that overflows (a segment of
 // nothing but masked entries of the type's lowest value), whose terms are formed as (z - m) c
 __device__ __forceinline__ double split_ref(float m, float c) { return split_ref_fused(m, c) ? (double)(m * c) : (double)m * (double)c; }
-template <bool BF16, int NV, int SPW>
+template <bool BF16>
 __device__ __forceinline__ void row_stats_parts(
     const int64_t row, const int part, const void* __restrict__ logits, int64_t ld, int V, float inv_T,
     float2* __restrict__ seg, int seg_stride)
 {
-    constexpr int N = Vec<BF16>::N, E = NV * N;
+    constexpr int NV = kSplitStatsNV, SPW = kSplitStatsSpw, N = Vec<BF16>::N, E = NV * N;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const RowView rv = row_view<BF16>(logits, ld, row, V);
-    const int nq = (rv.L + N - 1) / N, n_seg = (nq + NV * kWave - 1) / (NV * kWave);
+    const int nq = (rv.L + N - 1) / N, n_seg = stats_segments(nq);
     const float c = 1.4426950408889634f * inv_T;
-    const int s0 = (part * 4 + wave) * SPW;
     // (the range rule of the other row kernels, rowspan.hpp: vectors behind the row read as zero and touch no memory)
     const __amdgpu_buffer_rsrc_t row_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)rv.base, 0, nq * 16, 0x00020000);
     uint4 raw[SPW][NV];
@@ -523,13 +524,13 @@ __device__ __forceinline__ void row_stats_parts(
     for (int i = 0; i < SPW; ++i)
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(row_rsrc, lane * 16, ((s0 + i) * NV + j) * (kWave * 16), 2 /* non-temporal */);
+            const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(row_rsrc, lane * 16, stats_group_first(stats_segment(part, wave, i), j) * 16, 2 /* non-temporal */);
             raw[i][j] = make_uint4(t.x, t.y, t.z, t.w);
         }
     float2* const seg_row = seg + row * (int64_t)seg_stride;
 #pragma unroll
     for (int i = 0; i < SPW; ++i) {
-        const int s = s0 + i;
+        const int s = stats_segment(part, wave, i);
         if (s >= n_seg) return;                       // (uniform)
         float v[E];
 #pragma unroll
@@ -542,7 +543,7 @@ __device__ __forceinline__ void row_stats_parts(
         if (s == 0 || s + 1 == n_seg) {               // (elements outside the row)
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
-                const unsigned vm = vec_valid_mask<BF16>(rv, (s * NV + j) * kWave + lane);
+                const unsigned vm = vec_valid_mask<BF16>(rv, stats_group_first(s, j) + lane);
 #pragma unroll
                 for (int e = 0; e < N; ++e) v[j * N + e] = (vm >> e) & 1u ? v[j * N + e] : kNegInf;
             }

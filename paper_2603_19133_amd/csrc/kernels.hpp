@@ -40,7 +40,7 @@ __host__ __device__ inline int optimistic_rank(int k, int V, int m, int cap, flo
 }
 
 // The compression of few rows over many workgroups (split.hip): how a row is split, how many of its elements a workgroup
-// hands on (its `rank` largest and what shares the threshold's bin), and how many slots a wave's list has.
+// hands on (its `rank` largest and what shares the threshold's bin), and how many slots its list has.
 // parts = 0: the call is not split.  Lines of the rule:
 //   * rows (split_max_rows): with one workgroup per row a call takes the time of one row as long as every row has a CU of its
 //     own; split, the first launch's time grows with the rows from about 40 rows on, and the second one's with k.  Measured,
@@ -59,9 +59,7 @@ struct SplitPlan { int parts, rank, cap; };
 inline SplitPlan split_plan(int dtype, int64_t rows, int V, int k) {
     const SplitPlan none{0, 0, 0};
     if (rows < 1 || V < kSplitMinV || k < 1 || k > kMaxK || rows > split_max_rows(k) || V / 8 < k) return none;
-    const int esz = dtype == 1 ? 2 : 4;
-    const int nq = (int)(((int64_t)V * esz + 15) / 16) + 1;                  // (a row off the 16-byte boundary spans one vector more)
-    const int parts = split_parts(dtype == 1, nq);
+    const int parts = split_parts(dtype == 1, row_vecs_max(dtype == 1, V));
     if (parts < 2 || parts > kSplitMaxParts) return none;
     const float f = 1.f / (float)parts, lam = (float)k * f;
     const int rank = (int)ceilf(lam + 4.5f * sqrtf(lam * (1.f - f)) + 6.75f);
@@ -163,13 +161,9 @@ constexpr int32_t kSegMagicSplit = 0x53454732;   // split layout: entries (sum o
 // segments.  (384 rows: 28.4, 25.1, a round's 576: 31.5, 24.0.  Not taken: the draws of such a call are many, and one in 400
 // lies so near a step of the cumulative sum that sums in another order name its neighbour.)
 constexpr int kSplitStatsRows = 224;
-constexpr int kSplitStatsNV = 4, kSplitStatsSpw = 2; // vectors per lane and segment, segments per wave: eight loads in flight per lane
 inline StatsShape split_stats_shape(int dtype, int V) {
-    const int esz = dtype == 1 ? 2 : 4;
-    const int64_t nq_max = ((int64_t)V * esz + 15) / 16 + 1;
-    return StatsShape{256, kSplitStatsNV, 64 * kSplitStatsNV, (int)((nq_max + 64 * kSplitStatsNV - 1) / (64 * kSplitStatsNV))};
+    return StatsShape{256, kSplitStatsNV, 64 * kSplitStatsNV, stats_segments(row_vecs_max(dtype == 1, V))};
 }
-inline int split_stats_parts(int stride) { return (stride + 4 * kSplitStatsSpw - 1) / (4 * kSplitStatsSpw); }   // workgroups of four waves per row
 inline bool split_stats_serves(int64_t rows, int V) { return rows >= 1 && rows <= kSplitStatsRows && V >= kSplitMinV; }
 // Calls that are given no workspace and would need one for their statistics alone.  A verification without a draw gains less
 // (its second launch is there either way; the draw that the table serves is another call's), row_stats pays a second launch.  us, one

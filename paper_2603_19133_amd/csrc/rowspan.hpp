@@ -63,6 +63,19 @@ __host__ __device__ inline int split_parts(bool bf16, int nq) {
     return (n_blocks + per - 1) / per;
 }
 
+// Statistics of rows spread over several workgroups (row_stats_parts in common.hpp): a segment is kSplitStatsNV groups of 64
+// vectors, and each of a workgroup's four waves takes kSplitStatsSpw consecutive segments, eight loads in flight per lane.
+constexpr int kSplitStatsNV = 4, kSplitStatsSpw = 2;
+// segment i of wave `wave` of workgroup `part`
+__host__ __device__ inline int stats_segment(int part, int wave, int i) { return (part * 4 + wave) * kSplitStatsSpw + i; }
+// first vector of group j of a segment
+__host__ __device__ inline int stats_group_first(int seg, int j) { return (seg * kSplitStatsNV + j) * 64; }
+// segments of a row of `nq` vectors, and the workgroups that take them
+__host__ __device__ inline int stats_segments(int nq) { return (nq + 64 * kSplitStatsNV - 1) / (64 * kSplitStatsNV); }
+__host__ __device__ inline int stats_parts(int segments) { return (segments + 4 * kSplitStatsSpw - 1) / (4 * kSplitStatsSpw); }
+// vectors of a row of V elements that lies off the 16-byte boundary, the most it can span: what a launch is sized for
+__host__ __device__ inline int row_vecs_max(bool bf16, int V) { return (int)(((int64_t)V * (bf16 ? 2 : 4) + 15) / 16) + 1; }
+
 template <bool BF16>
 struct ResidualGeom {
     static constexpr int N = BF16 ? 8 : 4;

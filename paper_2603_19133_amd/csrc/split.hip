@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_round_kernel(
     if (y == n_draft && x == 0 && threadIdx.x == 0)
         *header = SegHeader{kSegMagicSplit, kSplitStatsNV * kWave, seg_stride, (int32_t)gridDim.y - n_draft};
     if (x < stats_per_row)
-        row_stats_parts<BF16, kSplitStatsNV, kSplitStatsSpw>(y - n_draft, x, tgt_logits, ld_t, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
+        row_stats_parts<BF16>(y - n_draft, x, tgt_logits, ld_t, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
 }
 
 template <bool BF16>
@@ -416,7 +416,7 @@ hipError_t launch_split_round(const void* draft_logits, int dtype, int64_t ld_d,
 {
     const SplitPlan p = split_plan(dtype, n_draft, V, k);
     const StatsShape sh = split_stats_shape(dtype, V);
-    const int per_row = split_stats_parts(sh.stride);
+    const int per_row = stats_parts(sh.stride);
     const float inv_T = 1.0f / temperature;
     SplitHead* const heads = (SplitHead*)scratch;
     uint2* const lists = (uint2*)(heads + (size_t)n_draft * p.parts);

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256) void row_stats_parts_kernel(
         row = (int64_t)d0 + b + t;
         if (row < 0 || row >= n_rows) return;           // (offsets that leave the call's rows)
     }
-    row_stats_parts<BF16, kSplitStatsNV, kSplitStatsSpw>(row, (int)blockIdx.x, logits, ld, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
+    row_stats_parts<BF16>(row, (int)blockIdx.x, logits, ld, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
 }
 
 // The statistics of rows whose table stands in the split layout: one wave per row.
@@ -159,7 +159,7 @@ hipError_t launch_row_stats_parts(const void* logits, int dtype, int64_t ld, int
     if (n_rows == 0 || (seq_off && B == 0)) return hipSuccess;
     const float inv_T = 1.0f / temperature;
     const StatsShape sh = split_stats_shape(dtype, V);
-    const dim3 grid(split_stats_parts(sh.stride), n_accept ? 1 : seq_off ? gamma_max + 1 : n_rows, seq_off ? B : 1);
+    const dim3 grid(stats_parts(sh.stride), n_accept ? 1 : seq_off ? gamma_max + 1 : n_rows, seq_off ? B : 1);
     if (dtype == 1) hipLaunchKernelGGL(row_stats_parts_kernel<true>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, n_accept, (SegHeader*)seg_table);
     else            hipLaunchKernelGGL(row_stats_parts_kernel<false>, grid, dim3(256), 0, stream, logits, ld, V, inv_T, n_rows, sh.stride, seq_off, pos_begin, pos_end, n_accept, (SegHeader*)seg_table);
     return hipGetLastError();

@@ -99,3 +99,23 @@ def test_hand_issued_loads_keep_their_registers(listings, src):
             broken.append((name, op, ops))
     assert loads > 0 or src != "compress.hip"
     assert not broken, (len(broken), broken[:3])
+
+
+def test_every_range_checked_load_takes_its_place_from_the_shared_rule():
+    """What picospec_max_load_byte evaluates on the host is what the kernels address: every raw buffer load of a row names its
+    vectors through a function of rowspan.hpp (or the spread sample's, whose vectors lie inside the row)."""
+    from paper_2603_19133_amd import build as bld
+    shared = ("group_first(", "split_block(", "stats_group_first(", "sample_vec(")
+    loads = 0
+    for name in sorted(os.listdir(bld.CSRC)):
+        if name == "selfcheck.hip":              # (the probes of the range check itself)
+            continue
+        text = open(os.path.join(bld.CSRC, name)).read()
+        for m in re.finditer(r"raw_buffer_load_b128\((\w+), ([^;]*);", text):
+            loads += 1
+            where = m.group(2)
+            if where.startswith("lane * 16, first * 16"):        # (a helper whose callers pass the place)
+                assert all(any(f in call for f in shared) for call in re.findall(r"load_vec\((?!int)[^;]*", text)), name
+            else:
+                assert any(f in where for f in shared), (name, where)
+    assert loads >= 5
