@@ -188,9 +188,10 @@ int picospec_sample_residual(const void* tgt_logits, int dtype, int64_t ld, int3
                              void* workspace, size_t workspace_bytes, void* stream);
 
 /*
- * The same where no verification left a table: the workspace (optional, of the same size) is scratch, whatever it holds.  A call
- * of up to 1024 sequences and records of up to 1024 entries then forms the table of the rows it draws from, every row spread over many workgroups, in a launch of
- * its own (the sums are formed in another order and agree to rounding).
+ * The same where no verification left a table: the workspace (optional, picospec_workspace_bytes(PICOSPEC_CALL_SAMPLE_RESIDUAL,
+ * dtype, B, V, k) bytes: a row per sequence) is scratch, whatever it holds.  A call of up to 1024 sequences and records of up to
+ * 1024 entries then forms the table of the rows it draws from, every row spread over many workgroups, in a launch of its own,
+ * where that is faster (picospec_scratch_bytes; the sums are formed in another order and agree to rounding).
  */
 int picospec_sample_residual_ws(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float temperature,
                                 int32_t B, int32_t n_draft, const int32_t* seq_off, const int32_t* n_accept,

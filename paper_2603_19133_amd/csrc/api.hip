@@ -446,7 +446,8 @@ int sample_residual_impl(const void* tgt_logits, int dtype, int64_t ld, int32_t 
         return PICOSPEC_EINVAL;
     if (n_draft > 0 && (k < 1 || !q_idx || !q_prob || !q_count || !q_mass)) return PICOSPEC_EINVAL;
     if (n_draft > 0 && k > kMaxK) return PICOSPEC_EUNSUPPORTED;   // records come from picospec_compress
-    if (int rc = check_workspace(PICOSPEC_CALL_SAMPLE_RESIDUAL, dtype, rows, V, k, workspace, workspace_bytes)) return rc;
+    // (a table of the call's own: one row per sequence)
+    if (int rc = check_workspace(PICOSPEC_CALL_SAMPLE_RESIDUAL, dtype, own_table ? B : rows, V, k, workspace, workspace_bytes)) return rc;
     if (own_table && workspace && residual_split_serves(dtype, B, V, k))
         return hip_status(launch_residual_split(tgt_logits, dtype, ld, V, temperature, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass, k,
                                                 renorm, uniforms, out_tok, resid_mass, flags, workspace, rows, (hipStream_t)stream));
@@ -511,7 +512,7 @@ size_t picospec_scratch_bytes(int which_call, int dtype, int32_t n_draft, int32_
         case PICOSPEC_CALL_VERIFY_SAMPLE: return split_stats_serves(rows, V) ? seg_table_bytes(dtype, rows, V) : 0;
         case PICOSPEC_CALL_ROW_STATS: return row_stats_split_serves(dtype, rows, V) ? seg_table_bytes(dtype, rows, V) : 0;
         case PICOSPEC_CALL_SAMPLE_RESIDUAL:
-            return residual_split_serves(dtype, B, V, k) ? seg_table_bytes(dtype, rows, V) : 0;
+            return residual_split_serves(dtype, B, V, k) ? seg_table_bytes(dtype, B, V) : 0;
         case PICOSPEC_CALL_ROUND:
         {
             if (!round_split_serves(dtype, n_draft, rows, V, k)) return 0;

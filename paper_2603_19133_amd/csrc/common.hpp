@@ -498,7 +498,7 @@ __device__ __forceinline__ float tree_sum(const F& f) {
     else return tree_sum<FROM, N / 2>(f) + tree_sum<FROM + N / 2, N / 2>(f);
 }
 
-// The segment table of part `part` of a row, and nothing else (calls of few rows, whose statistics are formed from the table):
+// The segment table (its row `table_row`) of part `part` of a row, and nothing else (calls of few rows, whose statistics are formed from the table):
 // a workgroup of four waves, each wave SPW consecutive segments of NV * 64 vectors whose loads are all in flight at once.
 // Entry: (sum of 2^(z c - r), m), m = the segment's largest logit and r = split_ref(m, c); a NaN in the segment makes its sum NaN.
 // The lanes' sums are added in fp64.
@@ -508,7 +508,7 @@ __device__ __forceinline__ bool split_ref_fused(float m, float c) { return fabsf
 __device__ __forceinline__ double split_ref(float m, float c) { return split_ref_fused(m, c) ? (double)(m * c) : (double)m * (double)c; }
 template <bool BF16>
 __device__ __forceinline__ void row_stats_parts(
-    const int64_t row, const int part, const void* __restrict__ logits, int64_t ld, int V, float inv_T,
+    const int64_t row, const int64_t table_row, const int part, const void* __restrict__ logits, int64_t ld, int V, float inv_T,
     float2* __restrict__ seg, int seg_stride)
 {
     constexpr int NV = kSplitStatsNV, SPW = kSplitStatsSpw, N = Vec<BF16>::N, E = NV * N;
@@ -527,7 +527,7 @@ __device__ __forceinline__ void row_stats_parts(
             const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(row_rsrc, lane * 16, stats_group_first(stats_segment(part, wave, i), j) * 16, 2 /* non-temporal */);
             raw[i][j] = make_uint4(t.x, t.y, t.z, t.w);
         }
-    float2* const seg_row = seg + row * (int64_t)seg_stride;
+    float2* const seg_row = seg + table_row * (int64_t)seg_stride;
 #pragma unroll
     for (int i = 0; i < SPW; ++i) {
         const int s = stats_segment(part, wave, i);

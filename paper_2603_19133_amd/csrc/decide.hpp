@@ -532,6 +532,7 @@ struct __align__(16) SegResidualShared {
 };
 
 // s_stats (nullable): the target rows' statistics by position, left in LDS by accept_sequence<.., TABLE>.
+// by_sequence: the table holds one row per sequence, the one it draws from (launch_residual_split).
 // RT: threads (whole waves from thread 0 on) that run this, at least k / 4: every wave more is one more that goes through the
 // chain of scans and barriers, four instructions' time each once a SIMD holds several (residual_seg_threads).
 template <bool BF16, int RT>
@@ -542,7 +543,8 @@ __device__ __forceinline__ void residual_seg_sequence(
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
     const float* __restrict__ uniforms,
-    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ flags, const SplitStats* s_stats = nullptr)
+    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ flags, const SplitStats* s_stats = nullptr,
+    const bool by_sequence = false)
 {
     __shared__ SegResidualShared sh;
     constexpr int N = Vec<BF16>::N;
@@ -563,7 +565,7 @@ __device__ __forceinline__ void residual_seg_sequence(
     const int nq = (rv.L + N - 1) / N;
     const int seg_elems = seg_vecs * N;
     const int n_seg = (nq + seg_vecs - 1) / seg_vecs;
-    const float2* seg_row = reinterpret_cast<const float2*>(table + 1) + rt * (int64_t)stride;
+    const float2* seg_row = reinterpret_cast<const float2*>(table + 1) + (by_sequence ? (int64_t)b : rt) * (int64_t)stride;
     // Everything that depends only on the two rows is asked for at once (one trip to memory): the table's header
     // (checked below), the target row's maximum, the record's count and mass, this thread's entries of the record and
     // its entries of the segment table.

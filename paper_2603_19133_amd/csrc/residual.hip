@@ -58,10 +58,10 @@ __global__ __launch_bounds__(RT) void residual_seg_kernel(
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
     const float* __restrict__ uniforms,
-    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ flags)
+    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ flags, bool by_sequence)
 {
     residual_seg_sequence<BF16, RT>(blockIdx.x, n_accept[blockIdx.x], tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
-                                q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags);
+                                q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, nullptr, by_sequence);
 }
 
 // SPLIT: the table stands in the split layout, and the rows' statistics are formed here.
@@ -102,10 +102,10 @@ __global__ __launch_bounds__(kThreads) void decide_seg_kernel(
 static hipError_t launch_residual_seg(const void* tgt_logits, int dtype, int64_t ld, int V, float it, int B, const int32_t* seq_off,
                                       const int32_t* n_accept, const float* tgt_max, const int32_t* q_idx, const float* q_prob,
                                       const int32_t* q_count, const float* q_mass, int k, int renorm, const float* uniforms,
-                                      int32_t* out_tok, float* resid_mass, uint32_t* flags, const void* seg_table, const StatsShape& sh, hipStream_t stream)
+                                      int32_t* out_tok, float* resid_mass, uint32_t* flags, const void* seg_table, const StatsShape& sh, bool by_sequence, hipStream_t stream)
 {
 #define PICOSPEC_RESIDUAL(BF, RT) \
-    hipLaunchKernelGGL((residual_seg_kernel<BF, RT>), dim3(B), dim3(RT), 0, stream, tgt_logits, ld, V, it, seq_off, n_accept, tgt_max, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags)
+    hipLaunchKernelGGL((residual_seg_kernel<BF, RT>), dim3(B), dim3(RT), 0, stream, tgt_logits, ld, V, it, seq_off, n_accept, tgt_max, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, by_sequence)
 #define PICOSPEC_RESIDUAL_RT(BF) \
     switch (residual_seg_threads(k)) { case 256: PICOSPEC_RESIDUAL(BF, 256); break; case 512: PICOSPEC_RESIDUAL(BF, 512); break; default: PICOSPEC_RESIDUAL(BF, 1024); }
     if (dtype == 1) { PICOSPEC_RESIDUAL_RT(true) } else { PICOSPEC_RESIDUAL_RT(false) }
@@ -123,7 +123,7 @@ hipError_t launch_residual_split(const void* tgt_logits, int dtype, int64_t ld, 
     if (hipError_t e = launch_row_stats_parts(tgt_logits, dtype, ld, (int)n_rows, V, temperature, B, 0, seq_off, nullptr, nullptr, scratch, stream, n_accept))
         return e;
     return launch_residual_seg(tgt_logits, dtype, ld, V, 1.0f / temperature, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass,
-                               k, renorm, uniforms, out_tok, resid_mass, flags, scratch, split_stats_shape(dtype, V), stream);
+                               k, renorm, uniforms, out_tok, resid_mass, flags, scratch, split_stats_shape(dtype, V), true, stream);
 }
 
 hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
@@ -137,7 +137,7 @@ hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V,
         if (B == 0) return hipSuccess;
         const StatsShape sh = split_stats_serves(n_rows, V) ? split_stats_shape(dtype, V) : stats_shape(dtype, n_rows, V);   // (as the verification laid it out)
         return launch_residual_seg(tgt_logits, dtype, ld, V, 1.0f / temperature, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass,
-                                   k, renorm, uniforms, out_tok, resid_mass, flags, seg_table, sh, stream);
+                                   k, renorm, uniforms, out_tok, resid_mass, flags, seg_table, sh, false, stream);
     }
     static DeviceFlags limit_raised[2] = {};
     const size_t smem = sizeof(ResidualShared);

@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_round_kernel(
     if (y == n_draft && x == 0 && threadIdx.x == 0)
         *header = SegHeader{kSegMagicSplit, kSplitStatsNV * kWave, seg_stride, (int32_t)gridDim.y - n_draft};
     if (x < stats_per_row)
-        row_stats_parts<BF16>(y - n_draft, x, tgt_logits, ld_t, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
+        row_stats_parts<BF16>(y - n_draft, y - n_draft, x, tgt_logits, ld_t, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
 }
 
 template <bool BF16>

@@ -48,8 +48,8 @@ __global__ __launch_bounds__(THREADS) void row_stats_range_kernel(
 }
 
 // Rows that leave the chip partly idle: the segment tables alone (split layout).  Bound by the memory's latency up to some
-// 100 rows and by its rate from there (576 bf16 rows of 128,256 in 24.0 us: 6.2 TB/s).  One workgroup per row -> here: 16 sequences of 1 to 8 drafts, fp32 rows of 151,936: 17.8 -> 9.3 us; half of 24 such drafts, rows of 33,001: 8.2 -> 5.0 us.  grid: (workgroups per row, rows), or (.., gamma_max + 1, B) for the
-// target rows of a range of positions, or (.., 1, B) for every sequence's row at n_accept.
+// 100 rows and by its rate from there (224 bf16 rows of 128,256 in a verification of 16.3 us).  One workgroup per row -> here: 16 sequences of 1 to 8 drafts, fp32 rows of 151,936: 17.8 -> 9.3 us; half of 24 such drafts, rows of 33,001: 8.2 -> 5.0 us.  grid: (workgroups per row, rows), or (.., gamma_max + 1, B) for the
+// target rows of a range of positions, or (.., 1, B) for every sequence's row at n_accept (row b of the table).
 template <bool BF16>
 __global__ __launch_bounds__(256) void row_stats_parts_kernel(
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int n_rows, int seg_stride,
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256) void row_stats_parts_kernel(
         row = (int64_t)d0 + b + t;
         if (row < 0 || row >= n_rows) return;           // (offsets that leave the call's rows)
     }
-    row_stats_parts<BF16>(row, (int)blockIdx.x, logits, ld, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
+    row_stats_parts<BF16>(row, n_accept ? (int64_t)blockIdx.z : row, (int)blockIdx.x, logits, ld, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
 }
 
 // The statistics of rows whose table stands in the split layout: one wave per row.

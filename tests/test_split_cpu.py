@@ -128,3 +128,10 @@ def test_statistics_are_spread_without_a_workspace_only_where_that_was_faster(B)
     for V, f32, bf16 in ((32000, 0, 0), (62500, 64, 0), (64000, 64, 0), (128256, 128, 160), (151936, 128, 160)):
         for dt, most in ((B.F32, f32), (B.BF16, bf16)):
             assert f(B.CALL_ROW_STATS, dt, most or 1, V) == (most > 0) and not f(B.CALL_ROW_STATS, dt, most + 1, V)
+
+
+def test_a_draw_with_a_table_of_its_own_asks_for_a_row_per_sequence(B):
+    for dt in (B.F32, B.BF16):
+        for n, b in ((3, 2), (1024 * 16, 1024), (0, 300)):
+            got = B.scratch_bytes(B.CALL_SAMPLE_RESIDUAL, dt, n, b, 151936, 64)
+            assert got == B.workspace_bytes(B.CALL_SAMPLE_RESIDUAL, dt, b, 151936, 64) and got < 3000 * b + 16
