@@ -108,10 +108,14 @@ def _check(rc: int) -> None:
         raise PicoSpecError(rc)
 
 
-def alloc_workspace(dtype: torch.dtype, rows: int, V: int, device, which: int = CALL_VERIFY) -> torch.Tensor:
-    """The optional workspace of verify / sample_residual / verify_sample / round for `rows` = n_draft + B target rows."""
+def alloc_workspace(dtype: torch.dtype, rows: int, V: int, device, which: int = CALL_VERIFY, k: int = 0, n_draft: int = 0) -> torch.Tensor:
+    """The optional workspace of verify / sample_residual / verify_sample / round for `rows` = n_draft + B target rows.  With the
+    record length k and n_draft, a round's also holds the scratch that spreads its draft rows (else a round that has a use for
+    it allocates it)."""
     code = F32 if dtype == torch.float32 else BF16
     n = int(lib.picospec_workspace_bytes(which, code, rows, V, 0))
+    if k and n_draft:
+        n = max(n, int(lib.picospec_scratch_bytes(which, code, n_draft, rows - n_draft, V, k)))
     return torch.empty(max(n, 16), dtype=torch.uint8, device=device)
 
 
@@ -256,8 +260,8 @@ def round(draft_logits: torch.Tensor, tgt_logits: torch.Tensor, V: int, temperat
     q = q or alloc_compressed(n_draft, k, dev)
     ver = ver or alloc_verified(B, n_draft, dev)
     res = res or alloc_residual(B, dev)
-    # few draft rows: the call's own buffer, the segment table and the split kernels' scratch
-    own = _nat.scratch(tgt_logits, CALL_ROUND, dt, n_draft, B, V, k)
+    # few draft rows: a buffer for the segment table and the split kernels' scratch, unless the caller's holds both
+    own = _nat.scratch(tgt_logits, CALL_ROUND, dt, n_draft, B, V, k, workspace)
     _check(_nat.round(draft_logits, tgt_logits, dt, ld_d, ld_t, V, temperature, B, n_draft, seq_off, draft_tok, k, top_p, renorm,
                     uniforms, q.idx, q.prob, q.count, q.mass, q.lse,
                     ver.n_accept, ver.p_tok, ver.q_tok, ver.tgt_max, ver.tgt_sum, ver.tgt_lse, ver.flags,

@@ -132,8 +132,7 @@ PyObject* n_round(PyObject*, PyObject* const* v, Py_ssize_t n) {
         auto off = a.ptr<int32_t>(); auto tok = a.ptr<int32_t>(); auto k = a.i32(); auto top_p = a.f32(); auto renorm = a.i32(); auto uni = a.ptr<float>();
         auto idx = a.ptr<int32_t>(); auto prob = a.ptr<float>(); auto count = a.ptr<int32_t>(); auto mass = a.ptr<float>(); auto lse = a.ptr<float>();
         auto o = verdict(a); auto d = draw(a); auto ws = a.buffer(), own = a.buffer(); auto s = a.stream();
-        // (the call's own buffer in the place of the caller's, unless the library would refuse the caller's: it still does)
-        if (own.p && !(ws.p && (((uintptr_t)ws.p & 15u) || ws.bytes < picospec_workspace_bytes(PICOSPEC_CALL_ROUND, dt, N + B, V, 0)))) ws = own;
+        if (own.p) ws = own;                     // (scratch(..) brings one only where the caller's does not serve)
         return [=] { return picospec_round(zd, zt, dt, ldd, ldt, V, T, B, N, off, tok, k, top_p, renorm, uni, idx, prob, count, mass, lse,
                                            o.n, o.p, o.q, o.mx, o.sm, o.lse, o.fl, d.tok, d.mass, d.fl, ws.p, ws.bytes, s); };
     });
@@ -259,15 +258,20 @@ PyObject* n_scratch_bytes(PyObject*, PyObject* const* v, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// scratch(like, which, dtype, n_draft, B, V, k) -> uint8 tensor of picospec_scratch_bytes(...) bytes, None where that is 0
+// scratch(like, which, dtype, n_draft, B, V, k[, given]) -> uint8 tensor of picospec_scratch_bytes(...) bytes.  None where that is
+// 0, where the caller's workspace `given` holds as many, and where the library refuses that one (it still does).
 PyObject* n_scratch(PyObject*, PyObject* const* v, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     try {
-        if (n != 7 || !THPVariable_Check(v[0])) throw BadArgument("scratch(tensor, which, dtype, n_draft, B, V, k)");
+        if ((n != 7 && n != 8) || !THPVariable_Check(v[0])) throw BadArgument("scratch(tensor, which, dtype, n_draft, B, V, k[, given])");
         Args a{v, n, 1};
         const int which = a.i32(), dt = a.i32(), N = a.i32(), B = a.i32(), V = a.i32(), k = a.i32();
         const size_t bytes = picospec_scratch_bytes(which, dt, N, B, V, k);
         if (!bytes) Py_RETURN_NONE;
+        if (n == 8) {
+            const Args::Buffer given = a.buffer();
+            if (given.p && (given.bytes >= bytes || ((uintptr_t)given.p & 15u) || given.bytes < picospec_workspace_bytes(which, dt, N + B, V, 0))) Py_RETURN_NONE;
+        }
         return THPVariable_Wrap(at::empty({(int64_t)bytes}, like(v[0], at::kByte)));
     } catch (const BadArgument& e) {
         if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, e.what());

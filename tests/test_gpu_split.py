@@ -432,3 +432,29 @@ def test_offsets_beyond_the_rows_write_nothing_behind_them(gpu, ps):
     for t in (out.tgt_max, out.tgt_sum, out.tgt_lse):
         assert (t[:N + B] != -7.0).all() and (t[N + B:] == -7.0).all()
     assert int(out.flags[1]) & ps.FLAG_BAD_INPUT
+
+
+def test_a_round_takes_its_scratch_from_a_workspace_that_holds_it(gpu, ps):
+    """A caller that sizes the workspace for the round allocates once: the round spreads its rows in it and allocates nothing; what it
+    gives is what it gives without one."""
+    _announce("round in the caller's workspace")
+    V, k, B, N, T = 32000, 64, 2, 8, 0.8
+    g = torch.Generator(device=gpu)
+    g.manual_seed(5)
+    tgt = torch.randn((N + B, V), device=gpu, generator=g) * 2
+    draft = torch.randn((N, V), device=gpu, generator=g) * 2
+    off = torch.tensor([0, 4, 8], dtype=torch.int32, device=gpu)
+    u = torch.rand(N + B, device=gpu, generator=g)
+    tok = ps.compress(draft, V, T, k).idx[:, 0].contiguous()
+    ws = ps.alloc_workspace(torch.float32, N + B, V, gpu, ps.CALL_ROUND, k=k, n_draft=N)
+    assert ws.numel() > ps.alloc_workspace(torch.float32, N + B, V, gpu, ps.CALL_ROUND).numel()
+    want = ps.round(draft, tgt, V, T, off, N, tok, k, u)
+    out = dict(q=ps.alloc_compressed(N, k, gpu), ver=ps.alloc_verified(B, N, gpu), res=ps.alloc_residual(B, gpu))
+    torch.cuda.synchronize()
+    made = lambda: torch.cuda.memory_stats()["allocation.all.allocated"]
+    before = made()
+    ps.round(draft, tgt, V, T, off, N, tok, k, u, workspace=ws, **out)
+    assert made() == before
+    for a, b in zip(want, (out["q"], out["ver"], out["res"])):
+        for name, x in vars(a).items():
+            assert not torch.is_tensor(x) or torch.equal(x, getattr(b, name)), name
