@@ -17,6 +17,7 @@ larger residual mass are held to the strict criteria there as well.
 """
 from __future__ import annotations
 
+import contextlib
 from dataclasses import dataclass
 
 import numpy as np
@@ -75,9 +76,37 @@ class GpuRound:
     res: ps.Residual
 
 
+class _Bare:
+    """The binding's native part, but for the scratch that it brings: no call has a use for any."""
+    def __init__(self, native):
+        self._native = native
+
+    def __getattr__(self, name):
+        return getattr(self._native, name)
+
+    def scratch(self, *args):
+        return None
+
+    def scratch_bytes(self, *args):
+        return 0
+
+
+@contextlib.contextmanager
+def no_scratch():
+    """Calls inside pass the library the workspace that they are given and NULL where they are given none, as a C caller does that
+    has none: one workgroup per row (the binding otherwise brings scratch of its own to calls of few rows)."""
+    native = ps._nat
+    ps._nat = _Bare(native)
+    try:
+        yield
+    finally:
+        ps._nat = native
+
+
 def gpu_round(r: W.Round, tok: np.ndarray, device, renorm: int = 1, seg: bool = False) -> GpuRound:
     """The library's three calls on the same inputs; the drafted tokens are the oracle's.  seg: with the optional
-    workspace, i.e. verify leaves the target rows' segment table and the draw works from it."""
+    workspace, i.e. verify leaves the target rows' segment table and the draw works from it; without, verify and draw get
+    none, the binding's own scratch neither."""
     w = r.workload
     draft = to_device(r.draft_logits, device)
     tgt = to_device(r.tgt_logits, device)
@@ -86,8 +115,9 @@ def gpu_round(r: W.Round, tok: np.ndarray, device, renorm: int = 1, seg: bool = 
     dtok = torch.from_numpy(tok).to(device)
     q = ps.compress(draft, w.V, w.T, w.k, w.top_p)
     ws = ps.alloc_workspace(tgt.dtype, r.N + r.B, w.V, device) if seg else None
-    ver = ps.verify(tgt, w.V, w.T, seq_off, r.N, dtok, q, uni, renorm=renorm, workspace=ws)
-    res = ps.sample_residual(tgt, w.V, w.T, seq_off, r.N, ver, q, uni, renorm=renorm, workspace=ws)
+    with contextlib.nullcontext() if seg else no_scratch():
+        ver = ps.verify(tgt, w.V, w.T, seq_off, r.N, dtok, q, uni, renorm=renorm, workspace=ws)
+        res = ps.sample_residual(tgt, w.V, w.T, seq_off, r.N, ver, q, uni, renorm=renorm, workspace=ws)
     torch.cuda.synchronize()
     return GpuRound(q, ver, res)
 

@@ -1,6 +1,8 @@
 """GPU parity of the paper-literal downlink (Section 3.3, Eq. 4): the Top-K record of the target row at
 the rejected position, and the edge's local resampling against its dense draft distribution, through
 the C ABI against the oracle on the same seeded inputs."""
+import contextlib
+
 import numpy as np
 import pytest
 import torch
@@ -73,15 +75,16 @@ CASES = [("cfg1", {}, 64), ("cfg2", {}, 256), ("cfg3", {"B": 6}, 1024), ("cfg4",
          ("cfg2", {}, 10), ("cfg3", {"B": 6}, 10)]
 
 
-@pytest.mark.parametrize("renorm", [0, 1])
+@pytest.mark.parametrize("renorm,bare", [(0, False), (1, False), (1, True)])       # bare: without the binding's own scratch
 @pytest.mark.parametrize("name,scale,k", CASES)
-def test_downlink_round_matches_oracle(gpu, pu, ps, name, scale, k, renorm):
+def test_downlink_round_matches_oracle(gpu, pu, ps, name, scale, k, renorm, bare):
     w = W.WORKLOADS[name]
     if scale:
         w = w.scaled(**scale)
     _announce("downlink round", name, scale, "K", k, "renorm", renorm)
     r = W.build_round(w, 0)
-    st, _ = _downlink(pu, ps, gpu, r, k, renorm)
+    with pu.no_scratch() if bare else contextlib.nullcontext():
+        st, _ = _downlink(pu, ps, gpu, r, k, renorm)
     print("[stats]", name, {a: b for a, b in st.items() if a != "topp_excluded"}, flush=True)
 
 

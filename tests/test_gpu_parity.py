@@ -52,6 +52,11 @@ def test_round_matches_oracle(gpu, pu, name, scale, rnd, seg):
     print("[stats]", name, "seg" if seg else "", {k: v for k, v in st.items() if k != "topp_excluded"}, flush=True)
     if name in ("cfg1", "cfg2", "cfg3"):
         assert st["mismatch_accept"] == 0 and st["mismatch_draw"] == 0
+    if not seg:                                  # (the records with one workgroup per row; gpu_round's may be spread)
+        from paper_2603_19133_amd import binding as ps
+        with pu.no_scratch():
+            q = ps.compress(pu.to_device(r.draft_logits, gpu), w.V, w.T, w.k, w.top_p)
+        pu.compare_compress(q, o.q, w.top_p)
 
 
 # ---------------------------------------------------------------- compress edge cases

@@ -56,6 +56,16 @@ def test_round_call_matches_oracle_and_separate_calls(gpu, pu, ps, name, scale, 
                                       renorm=renorm, workspace=wsp)
         torch.cuda.synchronize()
         pu.compare_round(pu.GpuRound(sep.q, ver4, res4), o, r, max_excluded_frac=0.34)
+    # the same calls as a caller makes them that has no scratch: nothing at all, and the table only
+    with pu.no_scratch():
+        for wsp in (None, ws):
+            bare = pu.GpuRound(*ps.round(pu.to_device(r.draft_logits, gpu), pu.to_device(r.tgt_logits, gpu), w.V, w.T, d(r.seq_off), r.N, d(o.tok), w.k,
+                                         d(r.uniforms), top_p=w.top_p, renorm=renorm, workspace=wsp))
+            ver5, res5 = ps.verify_sample(pu.to_device(r.tgt_logits, gpu), w.V, w.T, d(r.seq_off), r.N, d(o.tok), sep.q, d(r.uniforms),
+                                          renorm=renorm, workspace=wsp)
+            torch.cuda.synchronize()
+            pu.compare_round(bare, o, r, max_excluded_frac=0.34)
+            pu.compare_round(pu.GpuRound(sep.q, ver5, res5), o, r, max_excluded_frac=0.34)
     # the records come from the same code: bit for bit; the target statistics of the two-launch schedule are summed by
     # 512 threads instead of 1024, so everything behind them agrees to rounding and the decisions wherever the oracle
     # does not call them knife-edge

@@ -458,3 +458,47 @@ def test_a_round_takes_its_scratch_from_a_workspace_that_holds_it(gpu, ps):
     for a, b in zip(want, (out["q"], out["ver"], out["res"])):
         for name, x in vars(a).items():
             assert not torch.is_tensor(x) or torch.equal(x, getattr(b, name)), name
+
+
+@pytest.mark.parametrize("dtype,N,B,V,k", [(torch.bfloat16, 160, 80, 98304, 40),       # drafts spread, statistics not, in a small round
+                                           (torch.bfloat16, 160, 80, 98303, 40),       # ... and the rule's other side
+                                           (torch.float32, 64, 450, 16384, 16), (torch.bfloat16, 16, 500, 16400, 300),   # large rounds
+                                           (torch.float32, 112, 112, 16384, 700), (torch.float32, 113, 112, 16384, 700),  # 224 rows and more
+                                           (torch.float32, 48, 4, 32768, 4096), (torch.float32, 49, 4, 32768, 4096)])
+def test_rounds_on_either_side_of_the_rule(gpu, pu, ps, dtype, N, B, V, k):
+    """Every schedule that a round's sizes can choose against the one without scratch: the same ids, sums to rounding, and the same
+    decisions but where a uniform lies within that of a step."""
+    _announce("rounds on either side of the rule", dtype, N, B, V, k)
+    T, g = 0.9, torch.Generator(device=gpu)
+    g.manual_seed(N + V)
+    off_l = [N * b // B for b in range(B + 1)]
+    at = torch.tensor([off_l[b] + b + i for b in range(B) for i in range(off_l[b + 1] - off_l[b])], device=gpu)
+    tgt = (torch.randn((N + B, V), device=gpu, generator=g) * 2).to(dtype)
+    draft = (tgt[at].float() + torch.randn((N, V), device=gpu, generator=g)).to(dtype)
+    off = torch.tensor(off_l, dtype=torch.int32, device=gpu)
+    u = torch.rand(N + B, device=gpu, generator=g)
+    tok = ps.compress(draft, V, T, k).idx[:, 0].contiguous()
+    q, v, r = ps.round(draft, tgt, V, T, off, N, tok, k, u)
+    with pu.no_scratch():
+        q0, v0, r0 = ps.round(draft, tgt, V, T, off, N, tok, k, u)
+    torch.cuda.synchronize()
+    assert torch.equal(q.idx, q0.idx) and torch.equal(q.count, q0.count) and torch.equal(v.tgt_max, v0.tgt_max)
+    for a, b in ((q.prob, q0.prob), (q.mass, q0.mass), (v.p_tok, v0.p_tok), (v.q_tok, v0.q_tok), (v.tgt_sum, v0.tgt_sum), (v.tgt_lse, v0.tgt_lse)):
+        assert torch.allclose(a, b, rtol=2e-6, atol=1e-37)
+    assert torch.equal(v.flags, v0.flags) and torch.equal(r.flags, r0.flags)
+    # (the first positions that differ: a uniform within the acceptance margin of p / q there)
+    for b in torch.nonzero(v.n_accept != v0.n_accept)[:, 0].tolist():
+        d, t = off_l[b] + int(min(v.n_accept[b], v0.n_accept[b])), off_l[b] + b + int(min(v.n_accept[b], v0.n_accept[b]))
+        assert abs(float(u[t]) * float(v.q_tok[d]) / float(v.p_tok[d]) - 1) < pu.ACCEPT_MARGIN
+    same = v.n_accept == v0.n_accept
+    assert torch.allclose(r.resid_mass[same], r0.resid_mass[same], rtol=1e-5, atol=1e-6)
+    # (tokens that differ: the uniform lies within the sums' rounding of both tokens' steps of the residual's cumulative sum)
+    for b in torch.nonzero(same & (r.out_tok != r0.out_tok))[:, 0].tolist():
+        j, n = int(v.n_accept[b]), off_l[b + 1] - off_l[b]
+        res = torch.softmax(tgt[off_l[b] + b + j].double() / T, 0)
+        if j < n:
+            res[q.idx[off_l[b] + j].long()] -= q.prob[off_l[b] + j].double() / q.mass[off_l[b] + j].double()
+        res = res.clamp_min(0)
+        cum, at_u = res.cumsum(0), float(u[off_l[b] + b + n]) * float(res.sum())
+        for x in (int(r.out_tok[b]), int(r0.out_tok[b])):
+            assert float(cum[x]) > at_u - pu.CDF_MARGIN and (x == 0 or float(cum[x - 1]) < at_u + pu.CDF_MARGIN)

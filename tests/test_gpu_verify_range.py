@@ -1,5 +1,7 @@
 """GPU parity of the verification over a range of draft positions (Section 3.2, Fast Verification; Section 3.3
 for the acceptance test) through the C ABI against the oracle, and the composition of consecutive ranges."""
+import contextlib
+
 import numpy as np
 import pytest
 import torch
@@ -52,11 +54,13 @@ def _compare_range(pu, r, g, o, begin, end):
     assert np.array_equal(pu.n(g.flags).astype(np.uint32), o.flags)
 
 
+@pytest.mark.parametrize("bare", [False, True])     # with the binding's own scratch (few rows are spread) / with none
 @pytest.mark.parametrize("name,scale,k", [("cfg1", dict(B=6), 64), ("cfg2", dict(B=8), 256), ("cfg5", dict(B=24, V=20011, k=512), 512)])
-def test_ranges_match_the_oracle_and_compose(gpu, pu, ps, name, scale, k):
-    _announce("verify_range", name, k)
+def test_ranges_match_the_oracle_and_compose(gpu, pu, ps, name, scale, k, bare):
+    _announce("verify_range", name, k, bare)
     w = W.WORKLOADS[name].scaled(**scale)
-    _ranges_case(pu, ps, gpu, W.build_round(w, 0), k, 3)
+    with pu.no_scratch() if bare else contextlib.nullcontext():
+        _ranges_case(pu, ps, gpu, W.build_round(w, 0), k, 3)
 
 
 def _ranges_case(pu, ps, gpu, r, k, seed):
