@@ -43,7 +43,11 @@
  *     (picospec_sample_residual given the SAME workspace that picospec_verify filled for the same rows, or the draw
  *     inside the fused calls) does not stream its target row a second time: it gathers one logit per record entry
  *     and reads the one segment in which the draw falls.  Size: picospec_workspace_bytes(call, dtype, n_draft + B, V, k)
- *     bytes on a 16-byte boundary (about 1.2 KB per target row at V = 152 K); its content is the library's business.
+ *     bytes on a 16-byte boundary (about 1.2 KB per target row at V = 152 K); its content is the library's business.  Calls of
+ *     few rows use theirs as scratch in which every row is spread over many workgroups (also picospec_compress,
+ *     picospec_compress_rejected, picospec_verify_range and the _ws calls, which overwrite whatever it holds): ids and
+ *     counts are the same, sums are formed in another order and agree to rounding, so the bits of a row's probabilities and
+ *     statistics depend on the number of rows in the call.
  *   - Return value: PICOSPEC_OK or a negative PICOSPEC_E* code.  Misuse that the host can see
  *     (null pointers, sizes, dtype, workspace) is rejected BEFORE anything is launched.
  *     Data-dependent conditions never fail a call; they set bits in `flags`.

@@ -3,6 +3,9 @@
 Argument marshalling only: torch supplies device memory and the current stream, every step of
 the path runs in the library's HIP kernels.  What runs on every call (tensors to pointers, outputs and
 scratch, entering the C ABI) is native code (``_native``, csrc/native.cpp); ``lib`` is the library itself through ctypes.
+Calls of few rows get scratch in which the library spreads every row over many workgroups (``scratch_bytes``): ids are the same
+as with one workgroup per row, sums (probabilities, masses, statistics) agree to rounding, so their bits depend on the number of
+rows in the call.
 There is no fallback: if the library has not been built (``python -m paper_2603_19133_amd.build``) importing this module raises.
 """
 from __future__ import annotations

@@ -44,8 +44,9 @@ __host__ __device__ inline int optimistic_rank(int k, int V, int m, int cap, flo
 // parts = 0: the call is not split.  Lines of the rule:
 //   * rows (split_max_rows): with one workgroup per row a call takes the time of one row as long as every row has a CU of its
 //     own; split, the first launch's time grows with the rows from about 40 rows on, and the second one's with k.  Measured,
-//     unsplit / split, us, fp32 (bf16) of 151,936: k = 64: 128 rows 28.2 / 23.8 (29.2 / 21.4), 192: 29.8 / 29.8 (29.1 / 25.8);
-//     k = 1024: 96 rows 29.7 / 24.4, 128: 29.6 / 27.2, 160: 29.8 / 30.3; k = 4096: 48 rows 35.4 / 29.9, 96: 35.6 / 36.1.
+//     unsplit / split, us, fp32 (bf16): k = 256: 192 rows of 151,936 30.4 / 30.5 (29.6 / 26.0), 100,000 24.4 / 24.7 (24.7 / 21.7),
+//     16,384 14.9 / 14.6 (14.7 / 14.0); k = 1024: 128 rows of 151,936 30.6 / 27.0 (30.6 / 24.0), 20,000 16.2 / 15.8 (16.7 / 15.7); k = 4096: 80
+//     rows of 151,936 36.4 / 32.9 (37.2 / 31.6), 64,000 27.3 / 27.4 (27.6 / 25.8); of 608 points one (192 x 100,000) is slower by more than 1 %.
 //   * V: two workgroups' worth, and eight times k (V = 20,000, k = 4096, 48 rows: 23.2 / 24.1).
 //   * the margin of the rank is optimistic_rank's (4.5 standard deviations of the share of the k largest that falls to one
 //     workgroup); its lists together must fit the candidate buffer of the finishing kernel with room to spare.
@@ -156,10 +157,11 @@ constexpr int32_t kSegMagic = 0x53454731;        // entries (sum of 2^(z c - r),
 constexpr int32_t kSegMagicSplit = 0x53454732;   // split layout: entries (sum of 2^(z c - r), m), m = the segment's largest logit, r = m c (split_ref)
 // Calls whose rows leave CUs idle spread every row's statistics over many workgroups: each wave leaves the entries of two
 // segments of 256 vectors, nothing else, and the kernel that needs the statistics forms them from the row's table.  One
-// workgroup per row is bound by the vector ALUs of one CU.  The line: a row for nearly every CU (256 rows x 151 936: 19.3 us per
-// row, 20.0 spread, bf16 verification; 128: 17.8, 14.1; fp32 128: 20.8, 19.1); nor below kSplitMinV, where a row is a few
-// segments.  (384 rows: 28.4, 25.1, a round's 576: 31.5, 24.0.  Not taken: the draws of such a call are many, and one in 400
-// lies so near a step of the cumulative sum that sums in another order name its neighbour.)
+// workgroup per row is bound by the vector ALUs of one CU.  The line for calls that keep the table for their draw: a row for nearly
+// every CU (verification and draw of 224 rows of 151,936, k = 64, us, one workgroup per row / spread: fp32 38.3 / 34.3, bf16 28.9 / 25.0;
+// of 16,384: 20.9 / 17.1, 19.1 / 17.2); nor below kSplitMinV, where a row is a few segments.  (More rows would gain as well, 384: 28.4 / 25.1, a
+// round's 576: 31.5 / 24.0.  Not taken: the draws of such a call are many, and one in 400 lies so near a step of the cumulative
+// sum that sums in another order name its neighbour; the spread sums are the more exact ones.)
 constexpr int kSplitStatsRows = 224;
 inline StatsShape split_stats_shape(int dtype, int V) {
     return StatsShape{256, kSplitStatsNV, 64 * kSplitStatsNV, stats_segments(row_vecs_max(dtype == 1, V))};
@@ -203,8 +205,9 @@ inline bool round_split_serves(int dtype, int64_t n_draft, int64_t rows, int V, 
 // is bound by the vector ALUs of one CU): 64 sequences x 33 001 fp32, k = 64: 17.2 -> 11.3 us; 64 x 151 936, k = 64: fp32 29.5 ->
 // 15.4, bf16 24.7 -> 13.2; 512: 73.4 -> 54.7, 50.4 -> 32.2; 1024: 139 -> 105, 98.7 -> 56.7.  The draw from a table gathers one logit per
 // record entry: long records cost more than the second pass (256 x 151 936 bf16, k = 4096: 28.0, 37.8), and so do those of up to
-// 1024 entries where the pass has the chip filled once (256 x 64 000 bf16, k = 1024: 17.8, 19.2); on rows of up to 64 KB the
-// pass is as fast as the second launch (256 x 16 384 bf16, k = 64: 10.8, 12.3).
+// 1024 entries where the pass has the chip filled once (256 x 64 000 bf16, k = 1024: 17.8, 19.2).  On rows of up to 64 KB the second
+// launch does not pay for few sequences (8 to 256 x 16 384 bf16, k = 64: 9.4 to 10.8, 10.5 to 12.3; fp32 14.3, 12.5 at 256); more
+// sequences on such rows would gain (512: 19.6, 15.0; fp32 26.2, 15.5) and keep the pass so far.
 constexpr int kResidualSplitSeqs = 1024, kResidualSplitK = 1024;
 inline bool residual_split_serves(int dtype, int64_t B, int V, int k) {
     if (B < 1 || B > kResidualSplitSeqs || k > kResidualSplitK || (int64_t)V * (dtype == 1 ? 2 : 4) <= 65536) return false;
