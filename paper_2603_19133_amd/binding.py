@@ -5,7 +5,8 @@ the path runs in the library's HIP kernels.  What runs on every call (tensors to
 scratch, entering the C ABI) is native code (``_native``, csrc/native.cpp); ``lib`` is the library itself through ctypes.
 Calls of few rows get scratch in which the library spreads every row over many workgroups (``scratch_bytes``): ids are the same
 as with one workgroup per row, sums (probabilities, masses, statistics) agree to rounding, so their bits depend on the number of
-rows in the call.
+rows in the call.  Scratch comes from torch's allocator on the current stream: capture such calls with ``torch.cuda.graph``, whose
+pool keeps it for the replays.
 There is no fallback: if the library has not been built (``python -m paper_2603_19133_amd.build``) importing this module raises.
 """
 from __future__ import annotations

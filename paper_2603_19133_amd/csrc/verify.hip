@@ -48,7 +48,7 @@ __global__ __launch_bounds__(THREADS) void row_stats_range_kernel(
 }
 
 // Rows that leave the chip partly idle: the segment tables alone (split layout).  Bound by the memory's latency up to some
-// 100 rows and by its rate from there (224 bf16 rows of 128,256 in a verification of 16.3 us).  One workgroup per row -> here: 16 sequences of 1 to 8 drafts, fp32 rows of 151,936: 17.8 -> 9.3 us; half of 24 such drafts, rows of 33,001: 8.2 -> 5.0 us.  grid: (workgroups per row, rows), or (.., gamma_max + 1, B) for the
+// 100 rows and by its rate from there (196 bf16 rows of 128,256 in 10.9 us: 4.6 TB/s).  One workgroup per row -> here: 16 sequences of 1 to 8 drafts, fp32 rows of 151,936: 17.8 -> 9.3 us; half of 24 such drafts, rows of 33,001: 8.2 -> 5.0 us.  grid: (workgroups per row, rows), or (.., gamma_max + 1, B) for the
 // target rows of a range of positions, or (.., 1, B) for every sequence's row at n_accept (row b of the table).
 template <bool BF16>
 __global__ __launch_bounds__(256) void row_stats_parts_kernel(

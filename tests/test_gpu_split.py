@@ -141,9 +141,14 @@ def test_statistics_of_degenerate_rows(gpu, ps, rows):
     want = [torch.empty(2, device=gpu) for _ in range(3)]
     ps._check(ps.lib.picospec_row_stats(z.data_ptr(), ps.F32, V, 2, V, 1.0, *[t.data_ptr() for t in want],
                                         torch.cuda.current_stream().cuda_stream))
+    # (row_stats takes one workgroup per row at this size; a verification that is given a workspace spreads them)
+    off, tok = torch.tensor([0, 1], dtype=torch.int32, device=gpu), torch.zeros(1, dtype=torch.int32, device=gpu)
+    v = ps.verify(z, V, 1.0, off, 1, tok, None, torch.rand(2, device=gpu), q_scalar=torch.rand(1, device=gpu),
+                  workspace=ps.alloc_workspace(torch.float32, 2, V, gpu))
     torch.cuda.synchronize()
-    for a, b in zip(got, want):
-        assert torch.allclose(a, b, rtol=1e-6, atol=0, equal_nan=True), (a, b)
+    for got in (got, (v.tgt_max, v.tgt_sum, v.tgt_lse)):
+        for a, b in zip(got, want):
+            assert torch.allclose(a, b, rtol=1e-6, atol=0, equal_nan=True), (a, b)
 
 
 def test_rows_behind_the_last_sequence_keep_their_statistics(gpu, ps):
