@@ -18,7 +18,7 @@ __global__ __launch_bounds__(kT, SMALL ? 6 : 4) void compress_kernel(
                                     seq_off, n_accept, ahead, rank_opt);
 }
 
-// The rows that the small variant marked with count = kRetryRow, through the general code: a few workgroups, each
+// The rows that the fast kernel with the large buffer marked with count = kRetryRow, through the general code: a few workgroups, each
 // looking through its share of the counts (one row per thread and step) and compressing the rows it finds marked.
 // (Launching one general workgroup per row just to look would cost tens of microseconds: its LDS makes the launch slow.)
 template <bool BF16>
@@ -258,12 +258,14 @@ hipError_t launch_compress(const void* logits, int dtype, int64_t ld, int n_rows
         cus = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0 ? cus : -1;
         cu_count[dev].store(cus, std::memory_order_relaxed);
     }
-    // Calls of more rows than the chip holds at a time take the fast kernels (fewer registers: the careful pass is
-    // not in them) and pay one small launch more; smaller calls are bound by that launch and take the general kernel.
-    const bool fast = cus > 0 && n_rows > 2 * cus && V > kCompressSample;
     // (fp32 rows stream faster from two workgroups per CU with the large buffer than from three with the small one,
-    //  measured at every record length; bf16 rows, which cost twice the arithmetic per byte, gain from the third)
-    const bool small = fast && bf && small_variant_serves(k, V);
+    //  measured at every record length; bf16 rows, which cost twice the arithmetic per byte, gain from the third, and calls
+    //  of any number of rows from the kernel without the careful pass: 1 to 512 rows of 33,000, 64,000 and 152,064, k = 10 to
+    //  2048, are 15 to 22, 11 to 14 and 7 to 10 % faster than from the general kernel)
+    const bool small = bf && small_variant_serves(k, V);
+    // With the large buffer, calls of more rows than the chip holds at a time take the fast kernel (fewer registers: the careful
+    // pass is not in it) and pay one small launch more; smaller calls are bound by that launch and take the general kernel.
+    const bool fast = small || (cus > 0 && n_rows > 2 * cus && V > kCompressSample);
     // rows resident at a time (2 workgroups per CU, 3 of the small variant): the distance of the look-ahead loads
     // (no look-ahead with a row map: the next row is not known from the row number)
     const int ahead = (!seq_off && cus > 0) ? (small ? 3 : 2) * cus : 0;
@@ -280,7 +282,7 @@ hipError_t launch_compress(const void* logits, int dtype, int64_t ld, int n_rows
     } else {
         if (bf) PICOSPEC_COMPRESS(true, false, false, smem_big); else PICOSPEC_COMPRESS(false, false, false, smem_big);
     }
-    if (fast) {
+    if (fast && !small) {
         if (hipError_t e = hipGetLastError()) return e;
         if (bf) PICOSPEC_RETRY(true); else PICOSPEC_RETRY(false);
     }

@@ -2,8 +2,9 @@
 // softmax statistics: one workgroup of 512 threads per row, two workgroups per CU (three with the
 // small candidate buffer), one HBM pass per row.  Three kernels per dtype share the code below
 // (launch_compress chooses): the general one (optimistic pass, then the safe pass for the rows that
-// lose it), the fast ones that hold the optimistic pass only, with the large or the small candidate
-// buffer, and mark the rows they give up, and the retry kernel that runs the general code on those.
+// lose it) and the fast ones that hold the optimistic pass only.  A row that loses it is done the safe
+// way by a function that the small-buffer kernel calls; the one with the large buffer marks it, and
+// the retry kernel runs the general code on it.
 //
 // Streaming selection.  A row is read with buffer loads (descriptor base + scalar offset + one
 // constant per-lane offset) in sub-tiles of two 16-byte vectors per thread through a ring of four
@@ -52,7 +53,7 @@ namespace {
 
 constexpr int kT = kCompressThreads;        // threads per workgroup
 constexpr int kW = kT / kWave;
-constexpr int kRetryRow = -2;               // count of a row that the small variant leaves to the general kernel
+constexpr int kRetryRow = -2;               // count of a row that the fast kernel with the large buffer leaves to the retry kernel
 constexpr int kCapBig = 8192;               // candidate slots in LDS (value + id, 8 bytes): records of up to kMaxK entries
 constexpr int kCapSmall = 5120;             // ... and the variant for records of up to kMaxK / 2: three workgroups per CU
 constexpr int kBinsLog2 = 11;
@@ -485,11 +486,11 @@ __device__ __forceinline__ int sample_vec_of(int j, int n_vec, const uint4* base
 // SMALL: records of up to kMaxK / 2 entries on rows whose expected candidates fit the smaller buffer (the host
 // decides: launch_compress) - 51 KB of LDS and at most 80 registers, so that three workgroups share a CU.
 // FAST: the optimistic pass only (what the careful pass keeps alive across it costs registers, those that the third
-// workgroup needs among them): a row whose pass fails, or to which it does not apply, gets count = kRetryRow and
-// nothing else, and a second, small launch that runs the general code on the marked rows takes it.
+// workgroup needs among them): done = false for a row whose pass fails, or to which it does not apply.
+// CAREFUL: the careful pass only, for such a row (its sample must fit the buffer as candidates: one sub-tile with the small one).
 // rank_opt: compress_rank() of the call, from the host (its square roots are a hundred instructions that every wave of every
 // row would spend on the same number).
-template <bool BF16, bool SMALL, bool FAST>
+template <bool BF16, bool SMALL, bool FAST, bool CAREFUL = false>
 __device__ __forceinline__ RowSelection select_row(
     CompressShared<SMALL ? kCapSmall : kCapBig>& sh, const int64_t row,
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float* __restrict__ lse,
@@ -501,8 +502,8 @@ __device__ __forceinline__ RowSelection select_row(
     // threshold is taken has the size of T0 sub-tiles (8192 elements) and is processed in one piece.
     using Geom = CompressGeom<BF16, SMALL>;
     constexpr int N = Vec<BF16>::N;
-    constexpr int SAMPLE = kCompressSample;
     constexpr int SV = Geom::SV, ES = SV * N, SUB = kT * ES;
+    constexpr int SAMPLE = CAREFUL && kCompressSample > kCap ? SUB : kCompressSample;
     constexpr int T0 = SAMPLE / SUB, NV0 = T0 * SV, E0 = NV0 * N;
     constexpr int RING = Geom::RING;             // sub-tile buffers: one in use, the others in flight
     static_assert(Geom::N == N, "vector width");
@@ -764,9 +765,8 @@ __device__ __forceinline__ RowSelection select_row(
     bool fill = false;                           // fewer entries above -inf than k: masked entries fill the record up
 
     bool row_done = false;
-    static_assert(FAST || !SMALL, "the small buffer cannot hold the careful pass's sample");
-    for (int attempt = r_opt > 0 ? 0 : 1; attempt < (FAST ? 1 : 2); ++attempt) {
-        const bool optimistic = FAST || attempt == 0;
+    for (int attempt = !CAREFUL && r_opt > 0 ? 0 : 1; attempt < (FAST ? 1 : 2); ++attempt) {
+        const bool optimistic = FAST || (!CAREFUL && attempt == 0);
         if (tid == 0) {
             sh.cnt = optimistic ? (int)val_addr : 0;      // (the optimistic pass's counter is the LDS address of the next slot)
             sh.overflowed = 0;
@@ -1263,6 +1263,39 @@ __device__ __forceinline__ void emit_row(
     }
 }
 
+// A value that is the same in every lane, in scalar registers (arguments of a function that is called arrive in vector ones).
+template <typename T>
+__device__ __forceinline__ T uniform(T v) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    int w[sizeof(T) / 4];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(T) / 4; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
+
+// A row that lost the optimistic pass, the careful way, in the same workgroup: a function that is called, so that what this
+// rare pass keeps alive costs the code in front of it nothing (inlined it takes the kernel from 75 registers to 128, its scalar
+// ones to 150 spills, and every row 3 to 4 us: 300 bf16 rows of 50,001, k = 777: 29.4 -> 25.1 us, 512 of 128,256, k = 1024:
+// 43.6 -> 40.4, 1 of 33,000, k = 10: 16.2 -> 13.3).
+template <bool BF16, bool SMALL>
+__device__ __attribute__((noinline)) void compress_row_again(
+    int64_t row, const void* logits, int64_t ld, int V, float inv_T, int k, float top_p,
+    int32_t* idx, float* prob, int32_t* count, float* mass, float* lse, const int32_t* seq_off, const int32_t* n_accept)
+{
+    using SH = CompressShared<SMALL ? kCapSmall : kCapBig>;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    SH& sh = *reinterpret_cast<SH*>(smem_raw);
+    row = uniform(row); logits = uniform(logits); ld = uniform(ld); V = uniform(V); inv_T = uniform(inv_T); k = uniform(k);
+    top_p = uniform(top_p); idx = uniform(idx); prob = uniform(prob); count = uniform(count); mass = uniform(mass);
+    lse = uniform(lse); seq_off = uniform(seq_off); n_accept = uniform(n_accept);
+    const RowSelection sel = select_row<BF16, SMALL, false, true>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, 0);
+    const int n = min(sel.n_held, k);
+    const uint64_t* sorted = order_top_k<BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+    emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass, u32x4_t{0u, 0u, 0u, 0u});
+}
+
 // One row of the compression: the workgroup that runs this writes record `row` of `n_rows`.
 template <bool BF16, bool SMALL, bool FAST = SMALL>
 __device__ __forceinline__ void compress_row(
@@ -1277,7 +1310,11 @@ __device__ __forceinline__ void compress_row(
     SH& sh = *reinterpret_cast<SH*>(smem_raw);
     const RowSelection sel = select_row<BF16, SMALL, FAST>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, rank_opt);
     if (FAST && !sel.done) {                     // (uniform: the verdict was read from LDS behind a barrier)
-        if (threadIdx.x == 0) count[row] = kRetryRow;
+        if constexpr (SMALL) {
+            compress_row_again<BF16, SMALL>(row, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept);
+        } else {
+            if (threadIdx.x == 0) count[row] = kRetryRow;
+        }
         return;
     }
 

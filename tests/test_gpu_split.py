@@ -90,6 +90,31 @@ def test_patterns_match_the_oracle(gpu, pu, ps, pattern, dtype, k, top_p):
     pu.compare_compress(g, oracle.compress(np.ascontiguousarray(stored[:, shift:]), V, 1.1, k, top_p), top_p)
 
 
+# (the kernel of the small candidate buffer: the shortest rows it serves, its longest record; the safe pass keeps one sub-tile of
+# 4096 elements as its first candidates there and fills the 5120 slots at once)
+@pytest.mark.parametrize("pattern", ["one_value", "few_values", "ascending", "spike", "none"])
+@pytest.mark.parametrize("V,ld,k,top_p", [(32768, 32768, 1, 0.0), (33001, 33004, 2048, 0.0), (33001, 33004, 777, 0.9)])
+def test_rows_that_lose_the_first_pass_with_one_workgroup_per_row(gpu, pu, ps, pattern, V, ld, k, top_p):
+    _announce("lost rows", pattern, V, k, top_p)
+    rng = np.random.default_rng(V + k)
+    z = _rows(rng, pattern, 5, ld)
+    if pattern == "ascending":
+        z = np.tile(np.linspace(-8, 8, ld, dtype=np.float32), (5, 1))
+    elif pattern == "spike":                     # beside the sample's runs in most rows
+        z[np.arange(5), (np.arange(5) * 6151 + 1234) % V] = 160.0
+    elif pattern == "none":
+        z[:] = -np.inf
+        z[1:, 3] = 1.0
+    stored = W.to_bf16_bits(z)
+    g = _unsplit(ps, pu.to_device(stored, gpu)[:, :V], V, 0.9, k, top_p)
+    torch.cuda.synchronize()
+    if pattern == "none":                        # (a row without a finite value has ids in ascending order and no distribution)
+        assert torch.equal(g.idx[0].cpu(), torch.arange(k, dtype=torch.int32)) or top_p
+        g = ps.Compressed(g.idx[1:], g.prob[1:], g.count[1:], g.mass[1:], g.lse[1:], k)
+        stored = stored[1:]
+    pu.compare_compress(g, oracle.compress(np.ascontiguousarray(stored[:, :V]), V, 0.9, k, top_p), top_p)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_infinities_and_nan_as_with_one_workgroup_per_row(gpu, ps, dtype):
     _announce("split infinities", dtype)
