@@ -14,8 +14,8 @@
 //     the record with the code of the unsplit kernels.  The answer is exact iff the k-th value lies above every workgroup's
 //     threshold, which is tested; a row that fails it (or whose lists overflow) is compressed from the start by the general
 //     code in the same workgroup.
-// Device time of a call, one workgroup per row -> split: one bf16 row of 128,256, k = 10: 25.5 -> 4.9 + 6.1
-// us; 64 fp32 rows of 151,936, k = 1024: 31.0 -> 13.1 + 9.5 us, of which the first launch reads 39 MB (5.8 us at 6.8 TB/s).  The line between the two is split_plan's.
+// Device time of a call, one workgroup per row -> split: one bf16 row of 128,256, k = 10: 25.5 -> 4.9 + 5.1
+// us; 64 fp32 rows of 151,936, k = 1024: 31.0 -> 12.4 + 8.4 us, of which the first launch reads 39 MB (5.8 us at 6.8 TB/s).  The line between the two is split_plan's.
 #include "compress_row.hpp"
 
 namespace picospec {
@@ -291,6 +291,19 @@ __global__ __launch_bounds__(kSplitThreads) void split_round_kernel(
         row_stats_parts<BF16>(y - n_draft, y - n_draft, x, tgt_logits, ld_t, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
 }
 
+// A row whose lists do not hold its answer, from the start.  A function that is called: inlined, what the general code keeps alive
+// costs every row 0.8 to 1.1 us (one row of 128,256 bf16, k = 10: 6.0 -> 5.1; 64 of 151,936 fp32, k = 1024: 9.5 -> 8.4).
+template <bool BF16>
+__device__ __attribute__((noinline)) void split_row_again(
+    int64_t row, const void* logits, int64_t ld, int V, float inv_T, int k, float top_p,
+    int32_t* idx, float* prob, int32_t* count, float* mass, float* lse, const int32_t* seq_off, const int32_t* n_accept, int rank_opt)
+{
+    row = uniform(row);
+    compress_row<BF16, false, false>(row, (int)row + 1, uniform(logits), uniform(ld), uniform(V), uniform(inv_T), uniform(k), uniform(top_p),
+                                     uniform(idx), uniform(prob), uniform(count), uniform(mass), uniform(lse), uniform(seq_off),
+                                     uniform(n_accept), 0, uniform(rank_opt));
+}
+
 template <bool BF16>
 __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
@@ -351,12 +364,9 @@ __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
         if (tid == kT - 1) lse[row] = (float)((double)M * (double)inv_T + log(S));
         __syncthreads();
     }
-    const uint32_t key_T = short_key<BF16>(__float_as_uint(T));
-    const uint64_t* sorted;
-    int n;
-    for (;;) {
-        if (!ok) sel = select_row<BF16, false, false>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, rank_opt);
-        n = min(sel.n_held, k);
+    if (ok) {
+        const int n = min(sel.n_held, k);
+        const uint64_t* sorted;
         if (sel.n_held <= kT)          sorted = order_top_k<BF16, 1, 1024, 128>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
         else if (sel.n_held <= 2 * kT) sorted = order_top_k<BF16, 2, 2048, 256>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
         else if (sel.n_held <= 4 * kT) sorted = order_top_k<BF16, 4>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
@@ -364,11 +374,13 @@ __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
         else                           sorted = order_top_k<BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
         // the lists hold every element above T: they hold the top k iff the k-th lies above it
         // (bf16: the short key of a T between two values is that of the lower one)
-        if (!ok || T == kNegInf || (uint32_t)(sorted[n - 1] >> kIdBits) > key_T) break;
-        ok = false;
-        __syncthreads();
+        if (T == kNegInf || (uint32_t)(sorted[n - 1] >> kIdBits) > short_key<BF16>(__float_as_uint(T))) {
+            emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass, u32x4_t{0u, 0u, 0u, 0u});
+            return;
+        }
     }
-    emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass, u32x4_t{0u, 0u, 0u, 0u});
+    __syncthreads();
+    split_row_again<BF16>(row, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, rank_opt);
 }
 
 }  // namespace
