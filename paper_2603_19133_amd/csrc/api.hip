@@ -202,14 +202,14 @@ int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, 
     if (int rc = check_workspace(PICOSPEC_CALL_ROUND, dtype, rows, V, k, workspace, workspace_bytes)) return rc;
     hipStream_t s = (hipStream_t)stream;
     // The two per-sequence kernels always go out as one (the position found by the acceptance test never leaves
-    // the workgroup).  A round that leaves most of the chip idle is bound by the serial part of each launch, so
-    // its two streaming kernels go out as one as well; a round that fills the chip streams faster with each
-    // kernel in its own launch shape.
+    // the workgroup), and the two streaming kernels as well where the target rows get a table (launch_round_wide); without
+    // one, rounds that leave most of the chip idle do so too, and those that fill it take each kernel in its own launch shape.
     const bool small_round = rows + n_draft <= kRoundSmallRows;     // (bound by its launches: two of them)
     // (a workspace that holds the split kernels' scratch behind the segment table: few draft rows are spread over many
     //  workgroups, and with few target rows their statistics as well)
     const size_t table_bytes = (round_seg_table_bytes(dtype, rows, V) + 15) / 16 * 16;
-    const bool split_draft = n_draft > 0 && workspace && workspace_bytes > table_bytes && round_split_serves(dtype, n_draft, rows, V, k) &&
+    const bool wide = workspace && round_wide_serves(dtype, n_draft, rows, V, k);
+    const bool split_draft = n_draft > 0 && workspace && !(wide && round_wide_first(dtype, n_draft)) && workspace_bytes > table_bytes && round_split_serves(dtype, n_draft, rows, V, k) &&
                              split_fits(dtype, n_draft, V, k, (char*)workspace + table_bytes, workspace_bytes - table_bytes);
     const bool split_stats = split_draft && split_stats_serves(rows, V);
     if (split_draft) {
@@ -229,7 +229,12 @@ int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, 
                                         q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok,
                                         verify_flags, out_tok, resid_mass, residual_flags, workspace, rows, false, split_stats, s));
     }
-    if (small_round) {
+    if (wide) {
+        if (hipError_t e = launch_round_wide(draft_logits, dtype, ld_draft, n_draft, V, temperature, k, top_p, q_idx,
+                                             q_prob, q_count, q_mass, q_lse, tgt_logits, ld_tgt, (int)rows, tgt_max, tgt_sum, tgt_lse,
+                                             workspace, small_round ? round_stats_shape(dtype, V) : stats_shape(dtype, rows, V), s))
+            return hip_status(e);
+    } else if (small_round) {
         if (hipError_t e = launch_round_stream(draft_logits, dtype, ld_draft, n_draft, V, temperature, k, top_p, q_idx,
                                                q_prob, q_count, q_mass, q_lse, tgt_logits, ld_tgt, (int)rows,
                                                tgt_max, tgt_sum, tgt_lse, workspace, s))

@@ -387,13 +387,15 @@ __device__ __forceinline__ void row_stats_row(
 // STAGE_GIVEN: the caller lends kSegStage float2 of LDS for the row's table (a kernel whose workgroups hold a
 // large buffer for another job); otherwise the function owns them.
 constexpr int kSegStage = 1040;                  // segments of the longest row (2^20 elements)
-template <bool BF16, int NV, int THREADS, bool STAGE_GIVEN = false>
+// FOLD: the workgroup has THREADS / FOLD threads, and each of its waves does the work of FOLD of the row's THREADS / 64 waves
+// (wave, wave + WAVES / FOLD, ..): the same sums in the same order, bit for bit, from workgroups of another size.
+template <bool BF16, int NV, int THREADS, bool STAGE_GIVEN = false, int FOLD = 1>
 __device__ __forceinline__ void row_stats_seg_row(
     const int64_t row, const void* __restrict__ logits, int64_t ld, int V, float inv_T,
     float* __restrict__ row_max, float* __restrict__ row_sum, float* __restrict__ row_lse,
     float2* __restrict__ seg, int seg_stride, float2* stage = nullptr)
 {
-    constexpr int WAVES = THREADS / kWave;
+    constexpr int WAVES = THREADS / kWave, STEP = WAVES / FOLD;
     __shared__ double red[2 * WAVES];
     // the row's table is gathered in LDS and written once, in whole lines, at the end of the row
     constexpr int kSegLds = kSegStage;
@@ -413,62 +415,76 @@ __device__ __forceinline__ void row_stats_seg_row(
     float2* const seg_row = seg + row * (int64_t)seg_stride;
 
     uint4 cur[NV], nxt[NV];
-    // vector j of this lane in trip `it`: it * TILE_VECS + wave * (NV * 64) + j * 64 + lane
+    // vector j of this lane in trip `it`, for wave + f * STEP: it * TILE_VECS + (wave + f * STEP) * (NV * 64) + j * 64 + lane
     const int q_lane = wave * (NV * kWave) + lane;
-    auto load_tile = [&](int it, uint4 (&dst)[NV]) {
+    auto load_tile = [&](int it, int f, uint4 (&dst)[NV]) {
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            const int q = it * TILE_VECS + q_lane + j * kWave;
+            const int q = it * TILE_VECS + q_lane + (f * STEP * NV + j) * kWave;
             dst[j] = make_uint4(0, 0, 0, 0);
             if (vec_in_row<BF16>(rv, q)) dst[j] = load16_stream(rv.base + q);
         }
     };
-    load_tile(0, cur);
-    float mx = kNegInf;          // this lane's largest value
-    float r_w = kNegInf;         // the wave's reference exponent (uniform)
-    float s = 0.f;               // this lane's sum of 2^(z c - r_w)
+    load_tile(0, 0, cur);
+    float mx[FOLD], r_w[FOLD], s[FOLD];
+#pragma unroll
+    for (int f = 0; f < FOLD; ++f) {
+        mx[f] = kNegInf;         // this lane's largest value
+        r_w[f] = kNegInf;        // the wave's reference exponent (uniform)
+        s[f] = 0.f;              // this lane's sum of 2^(z c - r_w)
+    }
     for (int it = 0; it < n_tiles; ++it) {
-        if (it + 1 < n_tiles) load_tile(it + 1, nxt);
-        float v[E];
+        auto trip = [&](auto f_tag) {
+            constexpr int f = decltype(f_tag)::value;
+            if constexpr (f + 1 < FOLD) load_tile(it, f + 1, nxt);
+            else if (it + 1 < n_tiles) load_tile(it + 1, 0, nxt);
+            float v[E];
 #pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            float t[N];
-            unpack<BF16>(cur[j], t);
+            for (int j = 0; j < NV; ++j) {
+                float t[N];
+                unpack<BF16>(cur[j], t);
 #pragma unroll
-            for (int e = 0; e < N; ++e) v[j * N + e] = t[e];
-        }
-        if (it == 0 || it == n_tiles - 1) {
-            unsigned vm = 0;
+                for (int e = 0; e < N; ++e) v[j * N + e] = t[e];
+            }
+            if (it == 0 || it == n_tiles - 1) {
+                unsigned vm = 0;
 #pragma unroll
-            for (int j = 0; j < NV; ++j) vm |= vec_valid_mask<BF16>(rv, it * TILE_VECS + q_lane + j * kWave) << (j * N);
+                for (int j = 0; j < NV; ++j) vm |= vec_valid_mask<BF16>(rv, it * TILE_VECS + q_lane + (f * STEP * NV + j) * kWave) << (j * N);
 #pragma unroll
-            for (int e = 0; e < E; ++e) v[e] = (vm >> e) & 1u ? v[e] : kNegInf;
-        }
-        float bm = v[0];
+                for (int e = 0; e < E; ++e) v[e] = (vm >> e) & 1u ? v[e] : kNegInf;
+            }
+            float bm = v[0];
 #pragma unroll
-        for (int e = 1; e < E; ++e) bm = fmaxf(bm, v[e]);
-        mx = fmaxf(mx, bm);
-        if (__ballot(bm * c > r_w + 64.f)) {                     // (uniform; the first trip, and outliers)
-            const float rn = ceilf(wave_max(bm) * c);
-            if (rn > r_w) { s *= __builtin_amdgcn_exp2f(r_w - rn); r_w = rn; }   // r_w = -inf: s is 0 and stays 0
-        }
-        const float nr = r_w == kNegInf ? 0.f : -r_w;           // waves that have seen only -inf so far
-        float acc = 0.f;
+            for (int e = 1; e < E; ++e) bm = fmaxf(bm, v[e]);
+            mx[f] = fmaxf(mx[f], bm);
+            if (__ballot(bm * c > r_w[f] + 64.f)) {                  // (uniform; the first trip, and outliers)
+                const float rn = ceilf(wave_max(bm) * c);
+                if (rn > r_w[f]) { s[f] *= __builtin_amdgcn_exp2f(r_w[f] - rn); r_w[f] = rn; }   // r_w = -inf: s is 0 and stays 0
+            }
+            const float nr = r_w[f] == kNegInf ? 0.f : -r_w[f];     // waves that have seen only -inf so far
+            float acc = 0.f;
 #pragma unroll
-        for (int e = 0; e < E; ++e) acc += __builtin_amdgcn_exp2f(fmaf(v[e], c, nr));
-        s += acc;
-        const float t = wave_sum_last(acc);
-        if (lane == kWave - 1 && it * WAVES + wave < kSegLds) seg_lds[it * WAVES + wave] = make_float2(t, r_w);   // (r_w = -inf with t = 0: the reader skips it)
+            for (int e = 0; e < E; ++e) acc += __builtin_amdgcn_exp2f(fmaf(v[e], c, nr));
+            s[f] += acc;
+            const float t = wave_sum_last(acc);
+            if (lane == kWave - 1 && it * WAVES + wave + f * STEP < kSegLds) seg_lds[it * WAVES + wave + f * STEP] = make_float2(t, r_w[f]);   // (r_w = -inf with t = 0: the reader skips it)
 #pragma unroll
-        for (int j = 0; j < NV; ++j) cur[j] = nxt[j];
+            for (int j = 0; j < NV; ++j) cur[j] = nxt[j];
+        };
+        static_assert(FOLD == 1 || FOLD == 2, "one call per segment of a trip");
+        trip(std::integral_constant<int, 0>{});
+        if constexpr (FOLD == 2) trip(std::integral_constant<int, 1>{});
     }
     // M = max over the block; S = sum of s 2^(r_w - M c), combined in fp64
-    const float wm = wave_max(mx);
-    if (lane == 0) red[wave] = (double)wm;
+#pragma unroll
+    for (int f = 0; f < FOLD; ++f) {
+        const float wm = wave_max(mx[f]);
+        if (lane == 0) red[wave + f * STEP] = (double)wm;
+    }
     __syncthreads();
     {   // (non-temporal stores: ordinary ones, which allocate their lines in the L2, cost this pass 5 % of its bandwidth)
         typedef float f32x2_t __attribute__((ext_vector_type(2)));
-        for (int sg = tid; sg < min(n_tiles * WAVES, min(seg_stride, kSegLds)); sg += THREADS) {
+        for (int sg = tid; sg < min(n_tiles * WAVES, min(seg_stride, kSegLds)); sg += THREADS / FOLD) {
             const float2 e = seg_lds[sg];
             const f32x2_t ev = {e.x, e.y};
             __builtin_nontemporal_store(ev, reinterpret_cast<f32x2_t*>(&seg_row[sg]));
@@ -477,9 +493,12 @@ __device__ __forceinline__ void row_stats_seg_row(
     float M = kNegInf;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) M = fmaxf(M, (float)red[w]);
-    const double mine = r_w == kNegInf ? (double)s : (double)s * exp2_split((double)r_w - (double)M * (double)c);   // (r_w = -inf: s is 0 or NaN)
-    const double ws = wave_sum(mine);
-    if (lane == 0) red[WAVES + wave] = ws;
+#pragma unroll
+    for (int f = 0; f < FOLD; ++f) {
+        const double mine = r_w[f] == kNegInf ? (double)s[f] : (double)s[f] * exp2_split((double)r_w[f] - (double)M * (double)c);   // (r_w = -inf: s is 0 or NaN)
+        const double ws = wave_sum(mine);
+        if (lane == 0) red[WAVES + wave + f * STEP] = ws;
+    }
     __syncthreads();
     double S = 0.0;
 #pragma unroll

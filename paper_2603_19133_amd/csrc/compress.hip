@@ -1,5 +1,5 @@
 // The kernels of the sparse Top-K compression (compress_row.hpp holds what a workgroup does with a row): the general
-// and the fast variants, the retry launch behind the fast ones, the small rounds' streaming kernel, and the drafter's
+// and the fast variants, the kernels that stream a round's draft and target rows at once, and the drafter's
 // draw from a record.
 #include "compress_row.hpp"
 
@@ -18,40 +18,9 @@ __global__ __launch_bounds__(kT, SMALL ? 6 : 4) void compress_kernel(
                                     seq_off, n_accept, ahead, rank_opt);
 }
 
-// The rows that the fast kernel with the large buffer marked with count = kRetryRow, through the general code: a few workgroups, each
-// looking through its share of the counts (one row per thread and step) and compressing the rows it finds marked.
-// (Launching one general workgroup per row just to look would cost tens of microseconds: its LDS makes the launch slow.)
-template <bool BF16>
-__global__ __launch_bounds__(kT, 4) void compress_retry_kernel(
-    const void* __restrict__ logits, int64_t ld, int n_rows, int V, float inv_T, int k, float top_p,
-    int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
-    float* __restrict__ mass, float* __restrict__ lse,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int rank_opt)
-{
-    __shared__ int marked[kT];
-    __shared__ int n_marked;
-    const int per = (n_rows + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int first = (int)blockIdx.x * per, last = min(first + per, n_rows);
-    for (int r0 = first; r0 < last; r0 += kT) {
-        if (threadIdx.x == 0) n_marked = 0;
-        __syncthreads();
-        const int r = r0 + (int)threadIdx.x;
-        if (r < last && count[r] == kRetryRow) marked[atomicAdd(&n_marked, 1)] = r;
-        __syncthreads();
-        const int n = n_marked;
-        for (int i = 0; i < n; ++i) {
-            const int row = marked[i];
-            compress_row<BF16, false, false>(row, n_rows, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse,
-                                      seq_off, n_accept, 0, rank_opt);
-            __syncthreads();                     // (the row's last reads of LDS are done before the next one resets it)
-        }
-        __syncthreads();
-    }
-}
-
 // Both streams of a small round in one launch (the draft rows' compression and the target rows' statistics do
 // not depend on each other): workgroups 0..n_draft-1 compress, the others take one target row each.
-// (For rounds of a few rows: registers are not held down to four waves per SIMD here.)
+// (For what round_wide_kernel does not serve: registers are not held down to four waves per SIMD here.)
 template <bool BF16>
 __global__ __launch_bounds__(kT, 2) void round_stream_kernel(
     const void* __restrict__ draft_logits, int64_t ld_d, int n_draft, int V, float inv_T, int k, float top_p,
@@ -76,6 +45,45 @@ __global__ __launch_bounds__(kT, 2) void round_stream_kernel(
                                                                 reinterpret_cast<float2*>(smem_raw));
     } else {
         row_stats_row<BF16, 2, kT>((int64_t)blockIdx.x - n_draft, tgt_logits, ld_t, V, inv_T, tgt_max, tgt_sum, tgt_lse);
+    }
+}
+
+// The same with the fast kernels' rows, for rounds of any size whose target rows get a segment table: statistics in the layout
+// and in the order of summation of whichever launch the draw expects (stats_threads: stats_shape, round_stats_shape).  `turns` times two drafts
+// and a target row, then the drafts that are left, then the target rows that are left.  The compression of a row is bound by the vector ALUs and by its serial phases,
+// the statistics by memory: 512 bf16 drafts of 128,256 (k = 1024) and 576 target rows take 59 us here, 40.4 + 31.4 in launches of their
+// own; rounds of 40 to 128 sequences, 33,000 to 152,064, k = 64 to 2048, us, two launches / here: bf16 76.5 / 55.2 (40 of 8 drafts), 134.6 /
+// 117.7 (64 of 16), 185 / 161 (100 of 14), fp32 107.7 / 82.7, 207.5 / 192.8, 299.5 / 282.7.  (More than 1000 drafts before the first target
+// row: up to 3 % slower; four segments in flight per wave of a target row: bf16 2 % faster, fp32 7 % slower.)
+template <bool BF16>
+__global__ __launch_bounds__(kT, BF16 ? 6 : 4) void round_wide_kernel(
+    const void* __restrict__ draft_logits, int64_t ld_d, int n_draft, int V, float inv_T, int k, float top_p,
+    int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
+    float* __restrict__ mass, float* __restrict__ lse,
+    const void* __restrict__ tgt_logits, int64_t ld_t,
+    float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
+    SegHeader* __restrict__ seg_header, int seg_vecs, int seg_stride, int stats_threads, int rank_opt, int ahead, int turns)
+{
+    const int n_target = (int)gridDim.x - n_draft, x = (int)blockIdx.x, turn = x / 3;
+    int draft, target;                           // (n_draft or more: none)
+    if (turn < turns) {
+        draft = x - 3 * turn < 2 ? x - turn : n_draft;
+        target = turn;
+    } else {                                     // the drafts that are left, then the target rows that are left
+        draft = x - turns;
+        target = x - n_draft;
+    }
+    if (__builtin_expect(draft < n_draft, 1)) {   // (the longer code first)
+        compress_row<BF16, BF16, true>(draft, n_draft, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr, ahead, rank_opt);
+    } else {
+        extern __shared__ __align__(16) unsigned char smem_raw[];
+        if (target == 0 && threadIdx.x == 0) *seg_header = SegHeader{kSegMagic, seg_vecs, seg_stride, n_target};
+        float2* const seg = reinterpret_cast<float2*>(seg_header + 1);
+        float2* const stage = reinterpret_cast<float2*>(smem_raw);
+        static_assert(sizeof(CompressShared<kCapSmall>) >= kSegStage * sizeof(float2), "the staged table fits the candidate buffer");
+        constexpr int NV = kRoundStatsNV<BF16>;
+        if (stats_threads == kT) row_stats_seg_row<BF16, NV, kT, true>(target, tgt_logits, ld_t, V, inv_T, tgt_max, tgt_sum, tgt_lse, seg, seg_stride, stage);
+        else                     row_stats_seg_row<BF16, NV, 2 * kT, true, 2>(target, tgt_logits, ld_t, V, inv_T, tgt_max, tgt_sum, tgt_lse, seg, seg_stride, stage);
     }
 }
 
@@ -231,50 +239,59 @@ static bool small_variant_serves(int k, int V)
            optimistic_rank(k, V, kCompressSample, kCapSmall, 4.5f) > 0;
 }
 
+// CUs of device `dev` (-1: not known)
+static int cus_of(int dev)
+{
+    static std::atomic<int> count[kMaxDevices] = {};
+    int cus = count[dev].load(std::memory_order_relaxed);
+    if (cus == 0) {                              // (first use on this device; a second thread here computes the same value)
+        cus = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0 ? cus : -1;
+        count[dev].store(cus, std::memory_order_relaxed);
+    }
+    return cus;
+}
+
+// (statistics of 2048 bf16 rows and more run in workgroups of 256 threads, which the launch for both streams has no form of)
+bool round_wide_serves(int dtype, int64_t n_draft, int64_t n_target, int V, int k)
+{
+    if (n_draft < 1 || n_draft + n_target > INT32_MAX) return false;
+    if (dtype == 1) return n_target < 2048 && small_variant_serves(k, V);
+    return compress_rank(k, V, false) > 0;
+}
+
 hipError_t launch_compress(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
                            int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass,
                            float* lse, const int32_t* seq_off, const int32_t* n_accept, hipStream_t stream)
 {
-    static DeviceFlags limit_raised[8] = {};
-    static std::atomic<int> cu_count[kMaxDevices] = {};
+    static DeviceFlags limit_raised[6] = {};
     const int bf = dtype == 1 ? 1 : 0;
-    // general (both passes in one kernel) / fast (optimistic pass only, rows it gives up marked for the retry kernel),
-    // the latter with the large or the small candidate buffer
-    const void* const kernels[8] = {(const void*)compress_kernel<false, false, false>, (const void*)compress_kernel<true, false, false>,
+    // general (both passes in one kernel) / fast (optimistic pass, rows it gives up by a call), the latter with the large or the
+    // small candidate buffer
+    const void* const kernels[6] = {(const void*)compress_kernel<false, false, false>, (const void*)compress_kernel<true, false, false>,
                                     (const void*)compress_kernel<false, false, true>, (const void*)compress_kernel<true, false, true>,
-                                    nullptr /* (the small buffer serves bf16 rows only) */, (const void*)compress_kernel<true, true, true>,
-                                    (const void*)compress_retry_kernel<false>, (const void*)compress_retry_kernel<true>};
+                                    nullptr /* (the small buffer serves bf16 rows only) */, (const void*)compress_kernel<true, true, true>};
     const size_t smem_big = sizeof(CompressShared<kCapBig>), smem_small = sizeof(CompressShared<kCapSmall>);
     int dev = 0;
     {   // (every variant of the dtype: which of them a call takes depends on its sizes)
         hipError_t e = hipSuccess;
-        for (int v = 0; v < 4 && e == hipSuccess; ++v)
+        for (int v = 0; v < 3 && e == hipSuccess; ++v)
             if (kernels[2 * v + bf]) e = raise_lds_limit_once(kernels[2 * v + bf], v == 2 ? smem_small : smem_big, limit_raised[2 * v + bf], dev);
         if (e != hipSuccess) return e;
     }
     if (n_rows == 0) return hipSuccess;
-    int cus = cu_count[dev].load(std::memory_order_relaxed);
-    if (cus == 0) {                              // (first use on this device; a second thread here computes the same value)
-        cus = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0 ? cus : -1;
-        cu_count[dev].store(cus, std::memory_order_relaxed);
-    }
+    const int cus = cus_of(dev);
     // (fp32 rows stream faster from two workgroups per CU with the large buffer than from three with the small one,
-    //  measured at every record length; bf16 rows, which cost twice the arithmetic per byte, gain from the third, and calls
-    //  of any number of rows from the kernel without the careful pass: 1 to 512 rows of 33,000, 64,000 and 152,064, k = 10 to
-    //  2048, are 15 to 22, 11 to 14 and 7 to 10 % faster than from the general kernel)
+    //  measured at every record length; bf16 rows, which cost twice the arithmetic per byte, gain from the third)
     const bool small = bf && small_variant_serves(k, V);
-    // With the large buffer, calls of more rows than the chip holds at a time take the fast kernel (fewer registers: the careful
-    // pass is not in it) and pay one small launch more; smaller calls are bound by that launch and take the general kernel.
-    const bool fast = small || (cus > 0 && n_rows > 2 * cus && V > kCompressSample);
+    // the general kernel takes what the optimistic pass does not serve (rows of up to its sample's length, records it has no rank for)
+    const int rank_opt = compress_rank(k, V, small);
+    const bool fast = rank_opt > 0;
     // rows resident at a time (2 workgroups per CU, 3 of the small variant): the distance of the look-ahead loads
     // (no look-ahead with a row map: the next row is not known from the row number)
     const int ahead = (!seq_off && cus > 0) ? (small ? 3 : 2) * cus : 0;
     const float inv_T = 1.0f / temperature;
-    const int rank_opt = compress_rank(k, V, small);
 #define PICOSPEC_COMPRESS(BF, SM, FA, SMEM) \
     hipLaunchKernelGGL((compress_kernel<BF, SM, FA>), dim3(n_rows), dim3(kT), SMEM, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, ahead, rank_opt)
-#define PICOSPEC_RETRY(BF) \
-    hipLaunchKernelGGL((compress_retry_kernel<BF>), dim3(min(64, (n_rows + kT - 1) / kT)), dim3(kT), smem_big, stream, logits, ld, n_rows, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, compress_rank(k, V, false))
     if (small) {
         PICOSPEC_COMPRESS(true, true, true, smem_small);
     } else if (fast) {
@@ -282,12 +299,31 @@ hipError_t launch_compress(const void* logits, int dtype, int64_t ld, int n_rows
     } else {
         if (bf) PICOSPEC_COMPRESS(true, false, false, smem_big); else PICOSPEC_COMPRESS(false, false, false, smem_big);
     }
-    if (fast && !small) {
-        if (hipError_t e = hipGetLastError()) return e;
-        if (bf) PICOSPEC_RETRY(true); else PICOSPEC_RETRY(false);
-    }
-#undef PICOSPEC_RETRY
 #undef PICOSPEC_COMPRESS
+    return hipGetLastError();
+}
+
+hipError_t launch_round_wide(const void* draft_logits, int dtype, int64_t ld_d, int n_draft, int V, float temperature,
+                             int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass, float* lse,
+                             const void* tgt_logits, int64_t ld_t, int n_target,
+                             float* tgt_max, float* tgt_sum, float* tgt_lse, void* seg_table, const StatsShape& sh, hipStream_t stream)
+{
+    static DeviceFlags limit_raised[2] = {};
+    const int bf = dtype == 1;
+    const size_t smem = bf ? sizeof(CompressShared<kCapSmall>) : sizeof(CompressShared<kCapBig>);
+    const void* const kernel = bf ? (const void*)round_wide_kernel<true> : (const void*)round_wide_kernel<false>;
+    int dev = 0;
+    if (hipError_t e = raise_lds_limit_once(kernel, smem, limit_raised[bf], dev)) return e;
+    const float inv_T = 1.0f / temperature;
+    const int rank_opt = compress_rank(k, V, bf);
+    const int cus = cus_of(dev), ahead = cus > 0 ? 2 * cus : 0;      // (fp32: two workgroups per CU, bf16: two of three)
+    // (a draft's row is the longer job: up to two per CU start at once, each on a CU of its own as long as there are any - 182 fp32
+    //  drafts of 33,000, k = 2048, with 196 target rows: 42.4 us in turns, 36.5 drafts first)
+    const int turns = n_draft > 2 * cus ? min(n_draft / 2, n_target) : 0;
+#define PICOSPEC_WIDE(BF) \
+    hipLaunchKernelGGL(round_wide_kernel<BF>, dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, (SegHeader*)seg_table, sh.seg_vecs, sh.stride, sh.threads, rank_opt, ahead, turns)
+    if (bf) PICOSPEC_WIDE(true); else PICOSPEC_WIDE(false);
+#undef PICOSPEC_WIDE
     return hipGetLastError();
 }
 

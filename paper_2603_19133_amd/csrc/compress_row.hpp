@@ -2,9 +2,9 @@
 // softmax statistics: one workgroup of 512 threads per row, two workgroups per CU (three with the
 // small candidate buffer), one HBM pass per row.  Three kernels per dtype share the code below
 // (launch_compress chooses): the general one (optimistic pass, then the safe pass for the rows that
-// lose it) and the fast ones that hold the optimistic pass only.  A row that loses it is done the safe
-// way by a function that the small-buffer kernel calls; the one with the large buffer marks it, and
-// the retry kernel runs the general code on it.
+// lose it) for rows and records that the optimistic pass does not serve, and the fast ones, with the
+// large or the small candidate buffer, that hold the optimistic pass only and call a function for a
+// row that loses it.
 //
 // Streaming selection.  A row is read with buffer loads (descriptor base + scalar offset + one
 // constant per-lane offset) in sub-tiles of two 16-byte vectors per thread through a ring of four
@@ -53,7 +53,6 @@ namespace {
 
 constexpr int kT = kCompressThreads;        // threads per workgroup
 constexpr int kW = kT / kWave;
-constexpr int kRetryRow = -2;               // count of a row that the fast kernel with the large buffer leaves to the retry kernel
 constexpr int kCapBig = 8192;               // candidate slots in LDS (value + id, 8 bytes): records of up to kMaxK entries
 constexpr int kCapSmall = 5120;             // ... and the variant for records of up to kMaxK / 2: three workgroups per CU
 constexpr int kBinsLog2 = 11;
@@ -1278,7 +1277,7 @@ __device__ __forceinline__ T uniform(T v) {
 // A row that lost the optimistic pass, the careful way, in the same workgroup: a function that is called, so that what this
 // rare pass keeps alive costs the code in front of it nothing (inlined it takes the kernel from 75 registers to 128, its scalar
 // ones to 150 spills, and every row 3 to 4 us: 300 bf16 rows of 50,001, k = 777: 29.4 -> 25.1 us, 512 of 128,256, k = 1024:
-// 43.6 -> 40.4, 1 of 33,000, k = 10: 16.2 -> 13.3).
+// 43.6 -> 40.4, 1 of 33,000, k = 10: 16.2 -> 13.3; calls that fill the chip spared it by a second launch for the lost rows, 4.7 us).
 template <bool BF16, bool SMALL>
 __device__ __attribute__((noinline)) void compress_row_again(
     int64_t row, const void* logits, int64_t ld, int V, float inv_T, int k, float top_p,
@@ -1310,11 +1309,7 @@ __device__ __forceinline__ void compress_row(
     SH& sh = *reinterpret_cast<SH*>(smem_raw);
     const RowSelection sel = select_row<BF16, SMALL, FAST>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, rank_opt);
     if (FAST && !sel.done) {                     // (uniform: the verdict was read from LDS behind a barrier)
-        if constexpr (SMALL) {
-            compress_row_again<BF16, SMALL>(row, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept);
-        } else {
-            if (threadIdx.x == 0) count[row] = kRetryRow;
-        }
+        compress_row_again<BF16, SMALL>(row, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept);
         return;
     }
 

@@ -14,8 +14,8 @@ namespace picospec {
 
 constexpr int kMaxK = 4096;          // candidate buffer in LDS holds 16384 entries; k beyond this is refused
 constexpr int kMaxV = 1 << 20;
-// picospec_round: draft + target rows up to which the two-launch schedule is used (the chip holds 512 compress
-// workgroups at a time; beyond that the separate kernels, each with its own launch shape, are as fast or faster)
+// picospec_round: draft + target rows up to which the target rows' statistics take the layout of round_stats_shape, and rounds
+// without a table stream both kinds of rows in one launch (the chip holds 512 compress workgroups at a time)
 constexpr int kRoundSmallRows = 512;
 
 // The optimistic pass of the compress kernel takes its threshold from a sample of m elements of a row of V: the value
@@ -151,6 +151,18 @@ inline StatsShape round_stats_shape(int dtype, int V) {
     sh.stride = (int)((nq_max + tile_vecs - 1) / tile_vecs) * (sh.threads / 64);
     return sh;
 }
+// launch_round_stream's work for rounds with a segment table, in the layout `sh`, where the compression's first pass applies
+// (round_wide_serves)
+bool round_wide_serves(int dtype, int64_t n_draft, int64_t n_target, int V, int k);
+// ... and goes before the spread rows (round_split_serves): bf16 rounds from 160 drafts on.  us, drafts spread / one launch for both
+// streams: 180 drafts and 240 target rows of 100,000, k = 64: 42.4 / 33.0; 180 and 200 of 64,000, k = 256: 33.1 / 29.8, of 152,064, k = 64:
+// 40.8 / 38.9; 192 and 224, k = 256: 44.2 / 39.5; with fewer drafts 128 and 144 of 152,064, k = 1024: 42.3 / 42.3, 100 and 200, k = 64: 34.6 / 37.3, 96
+// and 112, k = 256: 33.2 / 38.2.  (fp32, two workgroups per CU: 180 and 200: 53.8 / 54.5, 192 and 224: 59.0 / 55.7.)
+inline bool round_wide_first(int dtype, int64_t n_draft) { return dtype == 1 && n_draft >= 160; }
+hipError_t launch_round_wide(const void* draft_logits, int dtype, int64_t ld_d, int n_draft, int V, float temperature,
+                             int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass, float* lse,
+                             const void* tgt_logits, int64_t ld_t, int n_target,
+                             float* tgt_max, float* tgt_sum, float* tgt_lse, void* seg_table, const StatsShape& sh, hipStream_t stream);
 // bytes of the segment table of `rows` rows (16-byte header in front: see SegHeader)
 struct SegHeader { int32_t magic, seg_vecs, stride, rows; };
 constexpr int32_t kSegMagic = 0x53454731;        // entries (sum of 2^(z c - r), r)
@@ -184,10 +196,10 @@ inline bool row_stats_split_serves(int dtype, int64_t rows, int V) {
     const int64_t row_bytes = (int64_t)V * (dtype == 1 ? 2 : 4);
     return split_stats_serves(rows, V) && row_bytes >= 250000 && rows <= (dtype == 1 ? 160 : row_bytes >= 500000 ? 128 : 64);
 }
-// Whether a round spreads its draft rows (with scratch at hand): where picospec_compress would (the records of a round are then
+// Whether a round has a use for scratch that spreads its draft rows: where picospec_compress would (the records of a round are then
 // those of a call of its own, bit for bit), unless the launch that otherwise streams the draft and the target rows at once, and
-// hides most of the drafts' serial phases, is faster.  us, one launch for both / spread:
-//   * rounds beyond kRoundSmallRows, which launch their streams one after the other: always (64 + 450 sequences of 16,384 fp32,
+// hides most of the drafts' serial phases, is faster (see round_wide_first too).  us, round_stream_kernel's launch for both / spread:
+//   * rounds beyond kRoundSmallRows: always (64 + 450 sequences of 16,384 fp32,
 //     k = 64: 34.6 / 31.9; 16 + 500 of 151,936, k = 4096: 117.6 / 108.5);
 //   * smaller rounds whose statistics are spread with them: up to 48 drafts for the longest records (48 and 48 of 151,936 fp32, k =
 //     4096: 52.6 / 53.1, 64 and 64: 53.6 / 58.0, bf16 of 64,000 80 and 80: 41.3 / 45.7), else always (192 and 32, k = 256: 64.0 / 58.3;

@@ -84,6 +84,40 @@ def test_round_call_matches_oracle_and_separate_calls(gpu, pu, ps, name, scale, 
     assert np.array_equal(pu.n(res.out_tok)[sure], pu.n(sep.res.out_tok)[sure])
 
 
+# (drafts and target rows take turns, two to one: one draft, an odd number of them, more targets than turns, drafts left over; the layouts
+# of the statistics change at 1024 and 2048 target rows, the last of which bf16 rounds take in launches of their own)
+@pytest.mark.parametrize("dtype,N,B,V,pad,k", [(torch.bfloat16, 1, 520, 32768, 0, 40), (torch.bfloat16, 301, 222, 33001, 3, 2048),
+                                               (torch.bfloat16, 1001, 22, 32768, 0, 64), (torch.bfloat16, 1001, 23, 32768, 0, 64),
+                                               (torch.bfloat16, 2000, 47, 32768, 0, 64), (torch.bfloat16, 2000, 48, 32768, 0, 64),
+                                               (torch.float32, 1, 520, 16385, 0, 4), (torch.float32, 301, 222, 33001, 3, 4096),
+                                               (torch.float32, 700, 2, 20000, 0, 1024)])
+def test_both_streams_in_one_launch_match_the_separate_calls(gpu, pu, ps, dtype, N, B, V, pad, k):
+    """Bit for bit, with rows among them that lose the first pass of the compression."""
+    _announce("both streams in one launch", dtype, N, B, V, k)
+    T, g = 0.9, torch.Generator(device=gpu)
+    g.manual_seed(N + B)
+    off_l = [N * b // B for b in range(B + 1)]
+    at = torch.tensor([off_l[b] + b + i for b in range(B) for i in range(off_l[b + 1] - off_l[b])], device=gpu)
+    tgt = (torch.randn((N + B, V + pad), device=gpu, generator=g) * 2).to(dtype)[:, :V]
+    draft = (tgt[at].float() + torch.randn((N, V), device=gpu, generator=g)).to(dtype)
+    draft[3::7] = 0.5
+    draft[4::7, (V // 3):] = -20.0
+    draft[5::7] = torch.linspace(-8, 8, V, device=gpu).to(dtype)
+    off = torch.tensor(off_l, dtype=torch.int32, device=gpu)
+    u = torch.rand(N + B, device=gpu, generator=g)
+    tok = draft.float().argmax(1).to(torch.int32)
+    ws = ps.alloc_workspace(dtype, N + B, V, gpu, ps.CALL_ROUND)
+    with pu.no_scratch():
+        q, v, r = ps.round(draft, tgt, V, T, off, N, tok, k, u, workspace=ws)
+        q0 = ps.compress(draft, V, T, k)
+        v0 = ps.verify(tgt, V, T, off, N, tok, q0, u, workspace=ws)
+        r0 = ps.sample_residual(tgt, V, T, off, N, v0, q0, u, workspace=ws)
+    torch.cuda.synchronize()
+    for a, b in ((q, q0), (v, v0), (r, r0)):
+        for name, x in vars(a).items():
+            assert not torch.is_tensor(x) or torch.equal(x, getattr(b, name)), name
+
+
 def test_round_call_empty_and_misuse(gpu, ps):
     _announce("picospec_round empty")
     V = 64
