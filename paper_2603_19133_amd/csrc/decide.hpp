@@ -21,29 +21,35 @@ __device__ __forceinline__ bool clamp_range(const int32_t* pos_begin, const int3
 }
 
 // The statistics of one target row from its segment table in the split layout (row_stats_parts_kernel): M = the largest of
-// the segments' maxima, S = their sums brought to M in fp64.  One wave, the result in every lane.
-template <bool BF16>
-__device__ __forceinline__ void row_stats_of_table(const float2* __restrict__ seg_row, int n_seg, float c, float& M, double& S) {
-    const int lane = threadIdx.x & (kWave - 1);
-    constexpr int kAhead = 5;                        // entries per lane in flight (rows of up to 320 segments: one trip)
+// the segments' maxima, S = their sums brought to M in fp64.  One wave, the result in every lane; the entries are asked for (load)
+// apart from what is made of them.
+struct TableStats {
+    static constexpr int kAhead = 5;                 // entries per lane in flight (rows of up to 320 segments: one trip)
     float2 e[kAhead];
+    __device__ __forceinline__ void load(const float2* __restrict__ seg_row, int n_seg) {
+        const int lane = threadIdx.x & (kWave - 1);
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-        e[u] = make_float2(0.f, kNegInf);
-        if (u * kWave < n_seg && u * kWave + lane < n_seg) e[u] = seg_row[u * kWave + lane];
+        for (int u = 0; u < kAhead; ++u) {
+            e[u] = make_float2(0.f, kNegInf);
+            if (u * kWave < n_seg && u * kWave + lane < n_seg) e[u] = seg_row[u * kWave + lane];
+        }
     }
-    float m = kNegInf;
+    __device__ __forceinline__ void combine(const float2* __restrict__ seg_row, int n_seg, float c, float& M, double& S) const {
+        const int lane = threadIdx.x & (kWave - 1);
+        float m = kNegInf;
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) m = fmaxf(m, e[u].y);
-    for (int s = kAhead * kWave + lane; s < n_seg; s += kWave) m = fmaxf(m, seg_row[s].y);
-    M = wave_max(m);
-    auto term = [&](float2 t) { return t.x > 0.f || t.x != t.x ? (double)t.x * exp2_split(split_ref(t.y, c) - (double)M * (double)c) : 0.0; };
-    double s = 0.0;
+        for (int u = 0; u < kAhead; ++u) m = fmaxf(m, e[u].y);
+        for (int s = kAhead * kWave + lane; s < n_seg; s += kWave) m = fmaxf(m, seg_row[s].y);
+        M = wave_max(m);
+        const double top = (double)M * (double)c;
+        auto term = [&](float2 t) { return t.x > 0.f || t.x != t.x ? (double)t.x * exp2_split(split_ref(t.y, c) - top) : 0.0; };
+        double s = 0.0;
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) if (u * kWave < n_seg) s += term(e[u]);
-    for (int q = kAhead * kWave + lane; q < n_seg; q += kWave) s += term(seg_row[q]);
-    S = wave_sum(s);
-}
+        for (int u = 0; u < kAhead; ++u) if (u * kWave < n_seg) s += term(e[u]);
+        for (int q = kAhead * kWave + lane; q < n_seg; q += kWave) s += term(seg_row[q]);
+        S = wave_sum(s);
+    }
+};
 
 struct SplitStats { double S; float M; };
 // tgt_lse of the positions rows.x .. rows.y - 1 from what accept_sequence<.., TABLE> left in LDS, by `n` threads from thread
@@ -57,7 +63,7 @@ __device__ __forceinline__ void write_split_lse(const SplitStats* s_stats, int2 
 // token up in the position's sparse record with 16-byte loads (four in flight per lane), front
 // first, and stops once it is found.  What a position needs is asked for in two trips to memory: everything that depends
 // only on the position (token, uniform, statistics, the record's first 1024 ids), then the target's logit and the
-// record's probability of the token.
+// record's probability of the token.  (Twelve loads in flight for a token behind the first 1024 ids: 10.4 -> 18 us at 512 sequences, k = 2048.)
 // Returns the sequence's first rejected position (in every thread; a barrier stands behind the decision).
 // TABLE: the rows' statistics are not known yet; their sums stand in the segment table (split layout,
 // split_stats_serves): they are formed here and written to tgt_max / tgt_sum / tgt_lse.  s_stats (nullable, LDS): they
@@ -140,24 +146,21 @@ __device__ __forceinline__ int accept_sequence(
                 }
             }
         }
+        const float2* table_row = nullptr;
+        int n_seg = 0;
+        TableStats stats;
         if constexpr (TABLE) {
             const RowView rv = row_view<BF16>(tgt_logits, ld, rt, V);
-            const int nq = (rv.L + Vec<BF16>::N - 1) / Vec<BF16>::N, n_seg = (nq + seg_vecs - 1) / seg_vecs;
-            double S;
-            row_stats_of_table<BF16>(reinterpret_cast<const float2*>(table + 1) + rt * (int64_t)stride, n_seg, c, M_t, S);
-            S_t = (float)S;
-            if (lane == 0) {
-                tgt_max[rt] = M_t;
-                tgt_sum[rt] = S_t;
-                if (s_stats && i >= begin && i < kSplitStatsRows) s_stats[i] = SplitStats{S, M_t};
-                else if (tgt_lse) tgt_lse[rt] = (float)((double)M_t * (double)inv_T + log(S));
-                if (i >= begin && i <= end && nonfinite(M_t, S_t)) fl |= 2u;
-            }
-            if (!decides) continue;
+            const int nq = (rv.L + Vec<BF16>::N - 1) / Vec<BF16>::N;
+            n_seg = (nq + seg_vecs - 1) / seg_vecs;
+            table_row = reinterpret_cast<const float2*>(table + 1) + rt * (int64_t)stride;
+            stats.load(table_row, n_seg);
         }
         const bool bad = x < 0 || x >= V;
-        const float z_t = bad ? 0.f : logit_at<BF16>(tgt_logits, ld, rt, x);
-        if (!q_scalar) {
+        const float z_t = bad || !decides ? 0.f : logit_at<BF16>(tgt_logits, ld, rt, x);
+        float q_at = 0.f;                             // the record's probability of the token
+        bool in_record = false;
+        if (decides && !q_scalar) {
             cnt = cnt < 0 ? 0 : (cnt > k ? k : cnt);
             int slot = -1;
             // The record is ordered by probability and the token was drawn from it, so it sits near the
@@ -207,8 +210,26 @@ __device__ __forceinline__ int accept_sequence(
             }
             const unsigned long long found = __ballot(slot >= 0);    // (one lane: the ids of a record are distinct)
             slot = found ? __builtin_amdgcn_readlane(slot, 63 - __clzll((long long)found)) : -1;
-            if (slot >= 0 && !bad) {
-                qh = (double)q_prob[rd * k + slot];
+            in_record = slot >= 0 && !bad;
+            if (in_record) q_at = q_prob[rd * k + slot];
+        }
+        // (the row's statistics are formed while the last two loads are on their way)
+        if constexpr (TABLE) {
+            double S;
+            stats.combine(table_row, n_seg, c, M_t, S);
+            S_t = (float)S;
+            if (lane == 0) {
+                tgt_max[rt] = M_t;
+                tgt_sum[rt] = S_t;
+                if (s_stats && i >= begin && i < kSplitStatsRows) s_stats[i] = SplitStats{S, M_t};
+                else if (tgt_lse) tgt_lse[rt] = (float)((double)M_t * (double)inv_T + log(S));
+                if (i >= begin && i <= end && nonfinite(M_t, S_t)) fl |= 2u;
+            }
+            if (!decides) continue;
+        }
+        if (!q_scalar) {
+            if (in_record) {
+                qh = (double)q_at;
                 if (renorm) qh /= (double)mass_d;
             } else if (lane == 0) {
                 fl |= 1u;
@@ -517,6 +538,9 @@ __device__ __forceinline__ void residual_sequence(
 // T = sum over the record's entries in the segment of min(P(x), qhat(x)): one gathered logit per record entry.  The
 // segment in which the cumulative residual crosses u R is then read (one to four KB) and the token named as before.
 // T is summed in 2^-62 fixed point (integer LDS atomics: the order of the additions does not change the result).
+// Bound by latency: three dependent trips to memory and a chain of scans and barriers of 0.3 to 0.6 us each - one scan for the total and
+// the place, the sum taken from the acceptance where that has it, no logarithm: 9.0 -> 8.3 us with the acceptance for one sequence of 32,000,
+// 6.7 -> 6.25 alone for 24 of 33,001 - and for many sequences by the gathered logits (256 of 4096 entries: 13.7 of 24.5 us at 8 TB/s of lines).
 
 constexpr int kMaxSegTable = 1040;                               // segments of the longest row (2^20 elements: 1025 of 4 KB or of 2 KB)
 constexpr int kMaxSegElems = 256 * 8;                            // elements of the largest segment (256 vectors of bf16)
@@ -571,6 +595,8 @@ __device__ __forceinline__ void residual_seg_sequence(
     // its entries of the segment table.
     const SegHeader hd = *table;
     const float M = s_stats ? s_stats[min(j, kSplitStatsRows - 1)].M : tgt_max[rt];
+    double S = s_stats ? s_stats[min(j, kSplitStatsRows - 1)].S : 0.0;
+    const bool known = S > 0.0 && S < (double)__builtin_huge_valf();       // (else: the sum over the table's rows below)
     int cnt = 0;
     float mass_d = 1.f;
     int my_id[SP];
@@ -629,15 +655,19 @@ __device__ __forceinline__ void residual_seg_sequence(
             part += p;
         }
     }
-    part = wave_sum(part);
-    if (lane == 0) sh.red[wave] = part;
-    if (tid == 0) { sh.seg_pick = 0x7FFFFFFF; sh.seg_last = -1; sh.before = 0.0; }
+    for (int i = tid; i < seg_elems; i += RT) sh.qimg[i] = 0.f;
+    if (tid == 0) { sh.seg_pick = 0x7FFFFFFF; sh.seg_last = -1; sh.before = 0.0; sh.tok = 0x7FFFFFFF; sh.last_tok = -1; }
+    if (!known) {                                 // (uniform)
+        part = wave_sum(part);
+        if (lane == 0) sh.red[wave] = part;
+    }
     __syncthreads();
-    double S = 0.0;
+    if (!known) {
+        S = 0.0;
 #pragma unroll
-    for (int w = 0; w < RW; ++w) S += sh.red[w];
+        for (int w = 0; w < RW; ++w) S += sh.red[w];
+    }
     const double invS = 1.0 / S;
-    __syncthreads();
 
     // this thread's share of the record: qhat and min(P, qhat) into the segment's T
     float my_q[SP];
@@ -657,38 +687,30 @@ __device__ __forceinline__ void residual_seg_sequence(
     // residual mass of every segment, the total, and the segment in which the cumulative residual crosses u R
     const int per = (n_seg + RT - 1) / RT;        // contiguous segments per thread
     const int s0 = min(n_seg, tid * per), s1 = min(n_seg, s0 + per);
-    double R = 0.0, mine = 0.0;
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        mine = 0.0;
-        for (int s = s0; s < s1; ++s) {
-            double r = sh.pseg[s] * invS;
-            if (has_q) { r -= (double)sh.tfix[s] * (1.0 / 4611686018427387904.0); r = r > 0.0 ? r : 0.0; }
-            mine += r;
-        }
-        const double tot = wave_sum(mine);
-        __syncthreads();
-        if (lane == 0) sh.red[wave] = tot;
-        __syncthreads();
-        R = 0.0;
-#pragma unroll
-        for (int w = 0; w < RW; ++w) R += sh.red[w];
-        if (R > 0.0 || !has_q) break;
-        fl |= 4u;                                              // P == qhat numerically: draw from P itself
-        has_q = false;
-    }
     auto seg_mass = [&](int s) {
         double r = sh.pseg[s] * invS;
         if (has_q) { r -= (double)sh.tfix[s] * (1.0 / 4611686018427387904.0); r = r > 0.0 ? r : 0.0; }
         return r;
     };
-    const double target = (double)uniforms[(int64_t)d0 + b + g] * R;
-    const double incl = wave_scan_incl(mine);
-    __syncthreads();
-    if (lane == kWave - 1) sh.red[RW + wave] = incl;
-    __syncthreads();
-    double cum = incl - mine;
+    // (one scan serves the total and the place: a wave's last lane holds its sum, and each attempt has words of its own for them)
+    double R = 0.0, mine = 0.0, incl = 0.0, cum = 0.0;
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        mine = 0.0;
+        for (int s = s0; s < s1; ++s) mine += seg_mass(s);
+        incl = wave_scan_incl(mine);
+        double* const sums = sh.red + attempt * RW;
+        if (lane == kWave - 1) sums[wave] = incl;
+        __syncthreads();
+        R = 0.0;
+        double before = 0.0;
 #pragma unroll
-    for (int w = 0; w < RW; ++w) if (w < wave) cum += sh.red[RW + w];
+        for (int w = 0; w < RW; ++w) { const double t = sums[w]; if (w < wave) before += t; R += t; }
+        cum = before + incl - mine;
+        if (R > 0.0 || !has_q) break;
+        fl |= 4u;                                              // P == qhat numerically: draw from P itself
+        has_q = false;
+    }
+    const double target = (double)uniforms[(int64_t)d0 + b + g] * R;
     int my_pick = 0x7FFFFFFF, my_last = -1;
     for (int s = s0; s < s1; ++s) {
         const double v = seg_mass(s);
@@ -712,8 +734,6 @@ __device__ __forceinline__ void residual_seg_sequence(
     const int ql = wave * kWave + lane, q = seg_vec + ql;
     uint4 raw = make_uint4(0, 0, 0, 0);
     if (reads && vec_in_row<BF16>(rv, q)) raw = load16_stream(rv.base + q);
-    for (int i = tid; i < seg_elems; i += RT) sh.qimg[i] = 0.f;
-    __syncthreads();
     if (has_q) {
 #pragma unroll
         for (int z = 0; z < SP; ++z) {
@@ -721,19 +741,17 @@ __device__ __forceinline__ void residual_seg_sequence(
             if (my_id[z] >= 0 && off >= 0 && off < seg_elems) sh.qimg[off] = my_q[z];
         }
     }
-    if (tid == 0) { sh.tok = 0x7FFFFFFF; sh.last_tok = -1; }
     __syncthreads();
 
     // the token: ids ascend with (wave, lane, element)
     double r[N], sum = 0.0, inc = 0.0;
     if (reads) {
-        const double kappa = -(double)M * cd - log2(S);
         float v[N];
         unpack<BF16>(raw, v);
         const unsigned vm = vec_valid_mask<BF16>(rv, q);
 #pragma unroll
         for (int e = 0; e < N; ++e) {
-            const double d = exp2_split((double)v[e] * cd + kappa) - (double)sh.qimg[ql * N + e];
+            const double d = exp_emit(v[e], M, cd) * invS - (double)sh.qimg[ql * N + e];
             r[e] = ((vm >> e) & 1u) && d > 0.0 ? d : 0.0;
             sum += r[e];
         }
