@@ -294,6 +294,24 @@ def test_compress_kernels_keep_claimed_slots_in_registers():
     assert all(claiming[k]["scratch"] == 0 for k in hot), {k: claiming[k] for k in hot}
 
 
+def test_outputs_of_one_allocation_do_not_meet(B):
+    """The binding's outputs: sizes, types and order as asked for, each on a 512-byte boundary of the allocation they share."""
+    import torch
+    like = torch.zeros(1)
+    out = B._nat.empty(like, "iiififflb", 5, 6, (3, 7), (0, 7), 200, 1, 0, 4, 3)
+    assert [tuple(t.shape) for t in out] == [(5,), (6,), (3, 7), (0, 7), (200,), (1,), (0,), (4,), (3,)]
+    assert [t.dtype for t in out] == [torch.int32] * 3 + [torch.float32, torch.int32] + [torch.float32] * 2 + [torch.int64, torch.uint8]
+    at = [t.storage_offset() * t.element_size() for t in out]
+    assert all(a % 512 == 0 and t.is_contiguous() for a, t in zip(at, out))
+    for i, t in enumerate(out):
+        t.fill_(i + 1)
+    assert all(bool((t == i + 1).all()) for i, t in enumerate(out))
+    assert B._nat.empty(like, "f", 0)[0].numel() == 0
+    for bad in (-1, (2, -3), (1 << 62, 1 << 20)):
+        with pytest.raises(RuntimeError):
+            B._nat.empty(like, "f", bad)
+
+
 def test_streaming_loads_stay_inside_the_row(B):
     """The row loads of the compress and residual kernels, look-ahead included, never address a byte behind the aligned
     16-byte block that holds the row's last byte, whatever the row length and its alignment: the library's own
