@@ -51,7 +51,7 @@ __global__ __launch_bounds__(kT, 2) void round_stream_kernel(
 // The same with the fast kernels' rows, for rounds of any size whose target rows get a segment table: statistics in the layout
 // and in the order of summation of whichever launch the draw expects (stats_threads: stats_shape, round_stats_shape).  `turns` times two drafts
 // and a target row, then the drafts that are left, then the target rows that are left.  The compression of a row is bound by the vector ALUs and by its serial phases,
-// the statistics by memory: 512 bf16 drafts of 128,256 (k = 1024) and 576 target rows take 59 us here, 40.4 + 31.4 in launches of their
+// the statistics by memory: 512 bf16 drafts of 128,256 (k = 1024) and 576 target rows take 55 us here, 36.5 + 31.4 in launches of their
 // own; rounds of 40 to 128 sequences, 33,000 to 152,064, k = 64 to 2048, us, two launches / here: bf16 76.5 / 55.2 (40 of 8 drafts), 134.6 /
 // 117.7 (64 of 16), 185 / 161 (100 of 14), fp32 107.7 / 82.7, 207.5 / 192.8, 299.5 / 282.7.  (More than 1000 drafts before the first target
 // row: up to 3 % slower; four segments in flight per wave of a target row: bf16 2 % faster, fp32 7 % slower.)
@@ -317,9 +317,9 @@ hipError_t launch_round_wide(const void* draft_logits, int dtype, int64_t ld_d, 
     const float inv_T = 1.0f / temperature;
     const int rank_opt = compress_rank(k, V, bf);
     const int cus = cus_of(dev), ahead = cus > 0 ? 2 * cus : 0;      // (fp32: two workgroups per CU, bf16: two of three)
-    // (a draft's row is the longer job: up to two per CU start at once, each on a CU of its own as long as there are any - 182 fp32
-    //  drafts of 33,000, k = 2048, with 196 target rows: 42.4 us in turns, 36.5 drafts first)
-    const int turns = n_draft > 2 * cus ? min(n_draft / 2, n_target) : 0;
+    // (a draft's row is the longer job: up to one per CU start at once, each on a CU of its own - 182 fp32 drafts of 33,000, k = 2048, with 196
+    //  target rows: 42.4 us in turns, 36.5 drafts first; 200 bf16 of 100,000: 38.1 / 32.8; 288 of 152,064 64.0 / 64.6, 512 of 128,256 69.7 / 73.7)
+    const int turns = n_draft > cus ? min(n_draft / 2, n_target) : 0;
 #define PICOSPEC_WIDE(BF) \
     hipLaunchKernelGGL(round_wide_kernel<BF>, dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, (SegHeader*)seg_table, sh.seg_vecs, sh.stride, sh.threads, rank_opt, ahead, turns)
     if (bf) PICOSPEC_WIDE(true); else PICOSPEC_WIDE(false);

@@ -16,8 +16,9 @@
 //   * Optimistic pass: the sample is 256 runs of 128 bytes spread evenly over the row (logits trend with
 //     the vocabulary id, so the head of a row would misplace the threshold); it is only looked at.  r is
 //     chosen (optimistic_rank, kernels.hpp) so that the row is expected to hold k plus a safety margin at or above the
-//     threshold.  The row is then streamed from its start: every element at or above the threshold
-//     claims a slot of the candidate buffer in LDS with an atomic of its own and writes (value, id)
+//     threshold.  The row is then streamed from its start: every 32-bit word of the row (one element, two
+//     of a bf16 row) that holds an element at or above the threshold
+//     claims a slot of the candidate buffer in LDS with an atomic of its own and writes (word, id)
 //     there; the softmax arithmetic sits between claim and write, and runs against a reference exponent
 //     fixed from the sample (no running maximum: the row's maximum is its largest candidate).  If the row ends with at least k
 //     candidates that fit the buffer, the exact top k is among them, because nothing at or above the
@@ -683,8 +684,8 @@ __device__ __forceinline__ RowSelection select_row(
     using nv0_t = std::integral_constant<int, NV0>;
     using e0_t = std::integral_constant<int, E0>;
 
-    // Optimistic pass: every element above the threshold claims a slot with an LDS atomic of its own (a
-    // few lanes per instruction) and later writes (value, id) there.  Both steps are hand-issued so
+    // Optimistic pass: every word with an element above the threshold claims a slot with an LDS atomic of its own (a
+    // few lanes per instruction) and later writes (word, id) there.  Both steps are hand-issued so
     // that they stay straight-line code (predication by EXEC, no branches for the compiler to lay
     // out): claim_asm forms the lane mask, claims under it and hands the mask on; put_asm waits for
     // the claimed slots and writes under the same masks.  The counter
@@ -693,64 +694,102 @@ __device__ __forceinline__ RowSelection select_row(
     typedef __attribute__((address_space(3))) unsigned lds_u32;
     const unsigned cnt_addr = (unsigned)(uintptr_t)(lds_u32*)&sh.cnt;
     const unsigned val_addr = (unsigned)(uintptr_t)(lds_u32*)&sh.cand_val[0];
-    unsigned four = 4u, last_slot = val_addr + (unsigned)(kCap * 4 - 4);
-    asm volatile("" : "+v"(four), "+v"(last_slot));
-    auto claim_asm = [&, four](auto ee_tag, const float* v, float tau, int* slot, unsigned long long* passed) {
-        constexpr int EE = decltype(ee_tag)::value;
+    unsigned four = 4u;
+    asm volatile("" : "+v"(four));
+    // Claims go by the row's 32-bit words: one element each, or two of a bf16 row, whose word is claimed if either lies above the
+    // threshold and taken apart at the end of the pass (split_words).  The pass over bf16 rows is bound by the LDS's instructions: with a claim and
+    // a write per element 4352 rows of 152,064 (k = 2048) took 233 us to its end, 196 (the memory's time) without the writes, and the whole launch
+    // 321; by words it takes 281.  300 rows of 50,001, k = 777: 25.1 -> 22.7.
+    // returns the counter behind this wave's claims (in flight like the slots)
+    constexpr int kWordsPerVec = 4;
+    auto claim_asm = [&, four](auto nvv_tag, const float* v, float tau, int* slot, unsigned long long* passed) {
+        constexpr int W = decltype(nvv_tag)::value * kWordsPerVec;
         unsigned ca = cnt_addr;
         asm volatile("" : "+v"(ca));
 #pragma unroll
-        for (int e = 0; e < EE; ++e) {
+        for (int i = 0; i < W; ++i) {
             unsigned long long saved;
-            asm volatile("v_cmp_gt_f32_e64 %[m], %[x], %[t]\n\t"
-                         "s_and_saveexec_b64 %[sv], %[m]\n\t"
-                         "ds_add_rtn_u32 %[slot], %[ca], %[four]\n\t"
-                         "s_mov_b64 exec, %[sv]"
-                         : [slot] "+v"(slot[e]), [m] "=&s"(passed[e]), [sv] "=&s"(saved)
-                         : [x] "v"(v[e]), [t] "v"(tau), [ca] "v"(ca), [four] "v"(four)
-                         : "memory", "scc");
-        }
-    };
-    auto put_asm = [&, last_slot](auto nvv_tag, const float* v, int* slot, const unsigned long long* passed, int x0) {
-        constexpr int NVV = decltype(nvv_tag)::value;
-        static_assert(NVV * N == 8 || NVV * N == 16, "the wait names every slot");
-        // the claimed slots have arrived (the running sum is named so that the statistics stay in front)
-        if constexpr (NVV * N == 8)
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(slot[0]), "+v"(slot[1]), "+v"(slot[2]), "+v"(slot[3]),
-                         "+v"(slot[4]), "+v"(slot[5]), "+v"(slot[6]), "+v"(slot[7]), "+v"(os.s));
-        else {
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(slot[0]), "+v"(slot[1]), "+v"(slot[2]), "+v"(slot[3]),
-                         "+v"(slot[4]), "+v"(slot[5]), "+v"(slot[6]), "+v"(slot[7]), "+v"(os.s));
-            asm volatile("" : "+v"(slot[8]), "+v"(slot[9]), "+v"(slot[10]), "+v"(slot[11]),
-                         "+v"(slot[12]), "+v"(slot[13]), "+v"(slot[14]), "+v"(slot[15]));
-        }
-        // A slot behind the buffer's end: the pass is lost, nothing is written any more (the counter says so at the end).  Looked
-        // at once per sub-tile and wave; a lane that claimed nothing holds its last claim, or the buffer's start.
-        unsigned top = (unsigned)slot[0];
-#pragma unroll
-        for (int i = 1; i < NVV * N; ++i) top = max(top, (unsigned)slot[i]);
-        if (__ballot(top > last_slot)) return;
-        // eight columns at a time: their ids first (every lane, back to back), then only the write under each column's mask
-        static_assert((NVV * N) % 8 == 0, "writes go in blocks of eight columns");
-#pragma unroll
-        for (int i0 = 0; i0 < NVV * N; i0 += 8) {
-            unsigned id[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u;
-                id[u] = (unsigned)(x0 + (i / N) * kT * N + i % N);
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                unsigned long long saved;
-                asm volatile("s_and_saveexec_b64 %[sv], %[m]\n\t"
-                             "ds_write2st64_b32 %[at], %[x], %[id] offset1:%c[o1]\n\t"
+            if constexpr (BF16) {
+                float larger;                    // (v_max skips the NaN of elements outside the row)
+                asm volatile("v_max_f32_e32 %[l], %[x], %[y]\n\t"
+                             "v_cmp_gt_f32_e64 %[m], %[l], %[t]\n\t"
+                             "s_and_saveexec_b64 %[sv], %[m]\n\t"
+                             "ds_add_rtn_u32 %[slot], %[ca], %[four]\n\t"
                              "s_mov_b64 exec, %[sv]"
-                             : [sv] "=&s"(saved)
-                             : [m] "s"(passed[i0 + u]), [at] "v"(slot[i0 + u]), [id] "v"(id[u]), [x] "v"(v[i0 + u]), [o1] "n"(kCap / 64)
+                             : [slot] "+v"(slot[i]), [m] "=&s"(passed[i]), [sv] "=&s"(saved), [l] "=&v"(larger)
+                             : [x] "v"(v[2 * i]), [y] "v"(v[2 * i + 1]), [t] "v"(tau), [ca] "v"(ca), [four] "v"(four)
+                             : "memory", "scc");
+            } else {
+                asm volatile("v_cmp_gt_f32_e64 %[m], %[x], %[t]\n\t"
+                             "s_and_saveexec_b64 %[sv], %[m]\n\t"
+                             "ds_add_rtn_u32 %[slot], %[ca], %[four]\n\t"
+                             "s_mov_b64 exec, %[sv]"
+                             : [slot] "+v"(slot[i]), [m] "=&s"(passed[i]), [sv] "=&s"(saved)
+                             : [x] "v"(v[i]), [t] "v"(tau), [ca] "v"(ca), [four] "v"(four)
                              : "memory", "scc");
             }
         }
+        unsigned next;
+        asm volatile("ds_read_b32 %0, %1" : "=&v"(next) : "v"(ca) : "memory");
+        return next;
+    };
+    auto put_asm = [&](auto nvv_tag, const uint4* raw, int* slot, const unsigned long long* passed, unsigned next, int x0) {
+        constexpr int W = decltype(nvv_tag)::value * kWordsPerVec;
+        static_assert(W == 4 || W == 8, "the wait names every slot");
+        // the claimed slots have arrived (the running sum is named so that the statistics stay in front)
+        if constexpr (W == 4)
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(slot[0]), "+v"(slot[1]), "+v"(slot[2]), "+v"(slot[3]), "+v"(next), "+v"(os.s));
+        else
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(slot[0]), "+v"(slot[1]), "+v"(slot[2]), "+v"(slot[3]),
+                         "+v"(slot[4]), "+v"(slot[5]), "+v"(slot[6]), "+v"(slot[7]), "+v"(next), "+v"(os.s));
+        // Slots claimed behind the buffer's end: the pass is lost, nothing is written any more (the counter says so at the end).  The
+        // counter is looked at, once per sub-tile and wave: it lies behind every claim of this wave (and of others, whose overflow
+        // loses the pass as well).  (The largest of the lane's own slots: a vector instruction per column.)
+        if ((unsigned)__builtin_amdgcn_readfirstlane((int)next) > val_addr + (unsigned)(kCap * 4)) return;
+        // the ids first (every lane, back to back), then only the write under each column's mask
+        unsigned id[W];
+#pragma unroll
+        for (int i = 0; i < W; ++i) id[i] = (unsigned)(x0 + (i / kWordsPerVec) * kT * N + (i % kWordsPerVec) * (N / kWordsPerVec));
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            const uint4& r = raw[i / kWordsPerVec];
+            const unsigned word = i % kWordsPerVec == 0 ? r.x : i % kWordsPerVec == 1 ? r.y : i % kWordsPerVec == 2 ? r.z : r.w;
+            unsigned long long saved;
+            asm volatile("s_and_saveexec_b64 %[sv], %[m]\n\t"
+                         "ds_write2st64_b32 %[at], %[x], %[id] offset1:%c[o1]\n\t"
+                         "s_mov_b64 exec, %[sv]"
+                         : [sv] "=&s"(saved)
+                         : [m] "s"(passed[i]), [at] "v"(slot[i]), [id] "v"(id[i]), [x] "v"(word), [o1] "n"(kCap / 64)
+                         : "memory", "scc");
+        }
+    };
+    // The words held, `words` of them: each is given up for the element of it that lies above the threshold (and inside the row); where both do, the
+    // second one claims a slot of its own.  Returns the largest of this thread's candidates.
+    auto split_words = [&](int words, float tau) {
+        float cm = kNegInf;
+#pragma unroll
+        for (int j = 0; j < kCap / kT; ++j) {
+            const int i = tid + j * kT;
+            if (i < words) {
+                const unsigned raw = sh.cand_val[i];
+                if constexpr (BF16) {
+                    const unsigned x = sh.cand_id[i];
+                    const float lo = __uint_as_float(raw << 16), hi = __uint_as_float(raw & 0xFFFF0000u);
+                    const bool pl = lo > tau && x < (unsigned)V, ph = hi > tau && x + 1u < (unsigned)V;     // (x = -1: a word that begins in front of the row)
+                    sh.cand_val[i] = __float_as_uint(pl ? lo : hi);
+                    sh.cand_id[i] = pl ? x : x + 1u;
+                    cm = pl ? fmaxf(cm, lo) : cm;
+                    cm = ph ? fmaxf(cm, hi) : cm;
+                    if (pl && ph) {
+                        const int at = (int)(atomicAdd((unsigned*)&sh.cnt, 4u) - val_addr) >> 2;
+                        if (at < kCap) { sh.cand_val[at] = __float_as_uint(hi); sh.cand_id[at] = x + 1u; }
+                    }
+                } else {
+                    cm = fmaxf(cm, __uint_as_float(raw));
+                }
+            }
+        }
+        return cm;
     };
     static_assert(offsetof(SH, cand_id) - offsetof(SH, cand_val) == (kCap / 64) * 64 * 4,
                   "ds_write2st64 offset1 reaches cand_id from cand_val");
@@ -948,36 +987,37 @@ __device__ __forceinline__ RowSelection select_row(
             if (applies) {
 #pragma unroll
                 for (int t = 0; t < T0; ++t) load_sub(RING - T0 + t, rb[t]);
-                int slot[ES];                    // per column: this lane's last claim
+                constexpr int WS = SV * kWordsPerVec;
+                int slot[WS];                    // per word: this lane's claim
 #pragma unroll
-                for (int e = 0; e < ES; ++e) slot[e] = (int)val_addr;
+                for (int i = 0; i < WS; ++i) slot[i] = (int)val_addr;
                 auto full = [&](int sub, uint4 (&buf)[SV]) {        // a sub-tile wholly inside the row
                     float v[ES];
-                    unsigned long long passed[ES];
+                    unsigned long long passed[WS];
                     unpack_vecs(sv_t{}, 0, buf, v, false);
-                    claim_asm(es_t{}, v, tau, slot, passed);
+                    const unsigned next = claim_asm(sv_t{}, v, tau, slot, passed);
                     add_sum(es_t{}, v, false, nr);
-                    put_asm(sv_t{}, v, slot, passed, sub * SUB - rv.o + tid * N);
+                    put_asm(sv_t{}, buf, slot, passed, next, sub * SUB - rv.o + tid * N);
                     load_sub(sub + RING, buf);
                 };
                 auto ragged = [&](int sub, uint4 (&buf)[SV]) {      // the last sub-tiles: what lies behind the row is masked
                     if (sub < n_sub) {
                         float v[ES];
-                        unsigned long long passed[ES];
+                        unsigned long long passed[WS];
                         const bool edge = sub + 1 == n_sub;
                         unpack_vecs(sv_t{}, sub * (kT * SV) + tid, buf, v, edge);
-                        claim_asm(es_t{}, v, tau, slot, passed);
+                        const unsigned next = claim_asm(sv_t{}, v, tau, slot, passed);
                         add_sum(es_t{}, v, edge, nr);
-                        put_asm(sv_t{}, v, slot, passed, sub * SUB - rv.o + tid * N);
+                        put_asm(sv_t{}, buf, slot, passed, next, sub * SUB - rv.o + tid * N);
                     }
                 };
                 {   // sub-tile 0 may begin in front of the row (rows off the 16-byte boundary): masked like an edge
                     float v[ES];
-                    unsigned long long passed[ES];
+                    unsigned long long passed[WS];
                     unpack_vecs(sv_t{}, tid, rb[T0], v, rv.o > 0);
-                    claim_asm(es_t{}, v, tau, slot, passed);
+                    const unsigned next = claim_asm(sv_t{}, v, tau, slot, passed);
                     add_sum(es_t{}, v, rv.o > 0, nr);
-                    put_asm(sv_t{}, v, slot, passed, tid * N - rv.o);
+                    put_asm(sv_t{}, rb[T0], slot, passed, next, tid * N - rv.o);
                     load_sub(RING, rb[T0]);
                 }
                 // the hot loop holds nothing but the common case, RING times (one copy per buffer role)
@@ -990,20 +1030,20 @@ __device__ __forceinline__ RowSelection select_row(
                 for (int r = 0; r < RING; ++r) ragged(sub + r, rb[(T0 + 1 + r) % RING]);
             }
             __syncthreads();
-            const int held = (int)((unsigned)sh.cnt - val_addr) >> 2;   // (this pass's counter is an LDS byte address)
+            const int words = (int)((unsigned)sh.cnt - val_addr) >> 2;  // (this pass's counter is an LDS byte address)
+            const bool fits = applies && !sh.overflowed && words <= kCap;
+            if constexpr (BF16) __syncthreads();     // (everyone has read the counter before it moves on)
+            // the row's largest value is its largest candidate (slots behind the last one hold stale values)
+            const float cm = fits ? split_words(words, tau) : kNegInf;
+            int held = words;
+            if constexpr (BF16) {
+                __syncthreads();
+                held = (int)((unsigned)sh.cnt - val_addr) >> 2;
+            }
             // (a threshold of -inf: every entry above -inf is held, so fewer than k of them are still the whole answer)
-            enough = applies && !sh.overflowed && held <= kCap && (held >= k || (tau == kNegInf && held >= 1));
+            enough = fits && held <= kCap && (held >= k || (tau == kNegInf && held >= 1));
             n_held = enough ? held : -1;
             fill = enough && held < k;
-            // the row's largest value is its largest candidate (slots behind the last one hold stale values)
-            float cm = kNegInf;
-            if (enough) {
-#pragma unroll
-                for (int j = 0; j < kCap / kT; ++j) {
-                    const float x = __uint_as_float(sh.cand_val[tid + j * kT]);
-                    cm = tid + j * kT < held ? fmaxf(cm, x) : cm;
-                }
-            }
             os.mx = cm;
             __syncthreads();                     // everyone has read the verdict before the next attempt resets it
         } else {
@@ -1078,16 +1118,17 @@ __device__ __forceinline__ RowSelection select_row(
             S = 0.0;
 #pragma unroll
             for (int w = 0; w < kW; ++w) S += sh.red[kW + w];
-            if (tid == kT - 1) {                 // (off the last wave's critical path later on)
-                float it = inv_T;
-                asm volatile("" : "+s"(it));     // widened here: hoisted to the top of the kernel it would hold two registers throughout
-                lse[row] = (float)((double)M * (double)it + log(S));     // (rewritten by the pass that follows a pass given up here)
-            }
         }
         if (!enough) continue;
         key_hi = short_key<BF16>(__float_as_uint(M));
         row_done = true;
         break;
+    }
+    // (behind the loop: inside it the logarithm's constants are held in registers across the passes)
+    if (row_done && tid == kT - 1) {             // (off the last wave's critical path later on)
+        float it = inv_T;
+        asm volatile("" : "+s"(it));             // widened here: hoisted to the top of the kernel it would hold two registers throughout
+        lse[row] = (float)((double)M * (double)it + log(S));
     }
     return RowSelection{n_held, fill, row_done, M, S, key_lo, key_hi};
 }

@@ -115,6 +115,27 @@ def test_rows_that_lose_the_first_pass_with_one_workgroup_per_row(gpu, pu, ps, p
     pu.compare_compress(g, oracle.compress(np.ascontiguousarray(stored[:, :V]), V, 0.9, k, top_p), top_p)
 
 
+# (candidates are claimed by 32-bit words, two elements of a bf16 row: words that begin in front of a row or end behind it, with values there that
+# would head the record, and rows whose candidates come in pairs)
+@pytest.mark.parametrize("V,ld,k", [(33001, 33003, 300), (33000, 33001, 2048), (33001, 33002, 3000), (12001, 12001, 64)])
+def test_words_on_the_rows_edges_and_pairs_with_one_workgroup_per_row(gpu, pu, ps, V, ld, k):
+    _announce("words on the edges", V, ld, k)
+    rng = np.random.default_rng(V + ld)
+    R = 6
+    flat = np.full(R * ld + 8, 50.0, np.float32)                 # (what lies between the rows)
+    rows = _rows(rng, "normal", R, V)
+    rows[1::2, 1:] = np.maximum(rows[1::2, 1:], rows[1::2, :-1])   # neighbours share their larger value: ties in pairs
+    for r in range(R):
+        flat[1 + r * ld:1 + r * ld + V] = rows[r]
+    bits = W.to_bf16_bits(flat)
+    dev = pu.to_device(bits, gpu)
+    z = torch.as_strided(dev, (R, V), (ld, 1), 1)
+    g = _unsplit(ps, z, V, 0.9, k)
+    torch.cuda.synchronize()
+    stored = np.stack([bits[1 + r * ld:1 + r * ld + V] for r in range(R)])
+    pu.compare_compress(g, oracle.compress(np.ascontiguousarray(stored), V, 0.9, k), 0.0)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_infinities_and_nan_as_with_one_workgroup_per_row(gpu, ps, dtype):
     _announce("split infinities", dtype)
