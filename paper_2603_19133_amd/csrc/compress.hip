@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kT, BF16 ? 6 : 4) void round_wide_kernel(
     float* __restrict__ mass, float* __restrict__ lse,
     const void* __restrict__ tgt_logits, int64_t ld_t,
     float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
-    SegHeader* __restrict__ seg_header, int seg_vecs, int seg_stride, int stats_threads, int rank_opt, int ahead, int turns)
+    SegHeader* __restrict__ seg_header, int seg_vecs, int seg_stride, int stats_threads, int rank_opt, int turns)
 {
     const int n_target = (int)gridDim.x - n_draft, x = (int)blockIdx.x, turn = x / 3;
     int draft, target;                           // (n_draft or more: none)
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kT, BF16 ? 6 : 4) void round_wide_kernel(
         target = x - n_draft;
     }
     if (__builtin_expect(draft < n_draft, 1)) {   // (the longer code first)
-        compress_row<BF16, BF16, true>(draft, n_draft, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr, ahead, rank_opt);
+        compress_row<BF16, BF16, true>(draft, n_draft, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr, 0, rank_opt);
     } else {
         extern __shared__ __align__(16) unsigned char smem_raw[];
         if (target == 0 && threadIdx.x == 0) *seg_header = SegHeader{kSegMagic, seg_vecs, seg_stride, n_target};
@@ -286,9 +286,9 @@ hipError_t launch_compress(const void* logits, int dtype, int64_t ld, int n_rows
     // the general kernel takes what the optimistic pass does not serve (rows of up to its sample's length, records it has no rank for)
     const int rank_opt = compress_rank(k, V, small);
     const bool fast = rank_opt > 0;
-    // rows resident at a time (2 workgroups per CU, 3 of the small variant): the distance of the look-ahead loads
-    // (no look-ahead with a row map: the next row is not known from the row number)
-    const int ahead = (!seq_off && cus > 0) ? (small ? 3 : 2) * cus : 0;
+    // rows resident at a time: the distance of the general kernel's look-ahead loads (none with a row map: the next row is not known
+    // from the row number)
+    const int ahead = (!seq_off && cus > 0) ? 2 * cus : 0;
     const float inv_T = 1.0f / temperature;
 #define PICOSPEC_COMPRESS(BF, SM, FA, SMEM) \
     hipLaunchKernelGGL((compress_kernel<BF, SM, FA>), dim3(n_rows), dim3(kT), SMEM, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, ahead, rank_opt)
@@ -316,12 +316,12 @@ hipError_t launch_round_wide(const void* draft_logits, int dtype, int64_t ld_d, 
     if (hipError_t e = raise_lds_limit_once(kernel, smem, limit_raised[bf], dev)) return e;
     const float inv_T = 1.0f / temperature;
     const int rank_opt = compress_rank(k, V, bf);
-    const int cus = cus_of(dev), ahead = cus > 0 ? 2 * cus : 0;      // (fp32: two workgroups per CU, bf16: two of three)
+    const int cus = cus_of(dev);
     // (a draft's row is the longer job: up to one per CU start at once, each on a CU of its own - 182 fp32 drafts of 33,000, k = 2048, with 196
     //  target rows: 42.4 us in turns, 36.5 drafts first; 200 bf16 of 100,000: 38.1 / 32.8; 288 of 152,064 64.0 / 64.6, 512 of 128,256 69.7 / 73.7)
     const int turns = n_draft > cus ? min(n_draft / 2, n_target) : 0;
 #define PICOSPEC_WIDE(BF) \
-    hipLaunchKernelGGL(round_wide_kernel<BF>, dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, (SegHeader*)seg_table, sh.seg_vecs, sh.stride, sh.threads, rank_opt, ahead, turns)
+    hipLaunchKernelGGL(round_wide_kernel<BF>, dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, (SegHeader*)seg_table, sh.seg_vecs, sh.stride, sh.threads, rank_opt, turns)
     if (bf) PICOSPEC_WIDE(true); else PICOSPEC_WIDE(false);
 #undef PICOSPEC_WIDE
     return hipGetLastError();

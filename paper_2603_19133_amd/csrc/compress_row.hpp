@@ -300,9 +300,15 @@ __device__ __forceinline__ void order_prepare(SH& sh, int n) {
 //     candidates of the bins up to that one are gathered bin by bin, each one's position inside
 //     its bin is the number of larger bin-mates, and the positions below k are kept.
 // A bin too crowded for that sends the row through the radix select and a sorting network.
+// LINEAR (bf16 rows): places on a linear scale of the values.  Keys are logarithmic in the magnitude: candidates that reach across zero
+// leave most of the keys' range empty and crowd into a few coarse ranges and bins, whose atomics wait for each other (4352 rows of
+// 152,064 with Zipf-like values: 20 of the launch's 280 us went into that).  p = (M - w) 2^32 / span with w = v - id 2^-(8 + vb) |v|:
+// the gap from v to the next lower bf16 value is at least 2^-8 |v| and v - 2^-8 |v| is an fp32 value, so w, rounded, stays
+// between the two and falls with the id, and p never decreases along the wanted order.  Equal values next to zero share a place; a row
+// with a bin too crowded comes back as nullptr, for the careful code.
 // CAND_PER * kT >= n slots of candidates, FINE fine bins and COARSE ranges: the whole buffer's by default; a caller that
 // knows n to be small has less to clear, scan and skip (split.hip).
-template <bool BF16, int CAND_PER = 0, int FINE = kFine, int COARSE = kCoarse, class SH>
+template <bool BF16, int CAND_PER = 0, int FINE = kFine, int COARSE = kCoarse, bool LINEAR = false, class SH>
 __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int V, uint32_t key_lo, uint32_t key_hi) {
     constexpr int kFine = FINE, kCoarse = COARSE, kBinsPer = FINE / 2 / kT;       // (two 16-bit fine bins to a word)
     static_assert(FINE % (2 * kT) == 0 && FINE <= 2 * kBins && COARSE <= kCoarseAll, "the histograms of the buffer");
@@ -320,7 +326,16 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
     // as the high word of p times a 0.32 fixed-point factor; the low word is the position inside the range.  (Ranges
     // that tile the next power of two leave up to half of them, and of the fine bins of the range that holds the
     // threshold - the most crowded one - to places that do not occur.)  Few places: one range per place.
-    const uint64_t n_places = ((uint64_t)kr + 1u) << ib;           // <= 2^32
+    float lin = 0.f, lin_max = 0.f, id_step = 0.f;
+    bool linear = false;
+    if constexpr (LINEAR) {
+        const float v_max = __uint_as_float(bits_of_short_key<BF16>(key_hi)), v_low = __uint_as_float(bits_of_short_key<BF16>(key_lo));
+        lin = 4294900000.f * __builtin_amdgcn_rcpf((v_max - v_low) + fabsf(v_low) * 0.0078125f);
+        lin_max = v_max * lin;
+        id_step = __uint_as_float((unsigned)(127 - 8 - vb) << 23);
+        linear = v_low > kNegInf && v_max > v_low && lin < __builtin_huge_valf() && fabsf(lin_max) < __builtin_huge_valf();
+    }
+    const uint64_t n_places = LINEAR && linear ? 1ull << 32 : ((uint64_t)kr + 1u) << ib;           // <= 2^32
     const bool one_each = n_places <= (uint64_t)kCoarse;
     // (kCoarse * 2^32 / n_places from a float reciprocal, two parts in a million low so that rounding never takes it above:
     //  the ranges then tile the places but for a sliver at the end, and no 64-bit division is run per row)
@@ -339,7 +354,12 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
         if (i < n) {
             const uint32_t bits = sh.cand_val[i], id = sh.cand_id[i];
             c[j] = composite<BF16>(bits, id);
-            place[j] = ib < 32 ? ((key_hi - short_key<BF16>(bits)) << ib) | (id >> id_drop) : (id >> id_drop);
+            if (LINEAR && linear) {
+                const float v = __uint_as_float(bits), w = fmaf(-(float)id, fabsf(v) * id_step, v);
+                asm("v_cvt_u32_f32 %0, %1" : "=v"(place[j]) : "v"(fmaf(w, -lin, lin_max)));     // (saturates)
+            } else {
+                place[j] = ib < 32 ? ((key_hi - short_key<BF16>(bits)) << ib) | (id >> id_drop) : (id >> id_drop);
+            }
             atomicAdd(&sh.coarse[range_of(place[j])], 1u);
         }
     }
@@ -413,6 +433,7 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
     }
     if (big > kSortMaxBin) atomicMax(&sh.maxbin, big);
     __syncthreads();
+    if (LINEAR && linear && sh.maxbin > kSortMaxBin) return nullptr;     // (uniform)
     if (sh.maxbin > kSortMaxBin) {
         __syncthreads();                     // (prune_to_k writes the words read above)
         if (n > k) { prune_to_k<BF16>(sh, n, k, key_lo, key_hi); n = k; }
@@ -1360,7 +1381,9 @@ __device__ __forceinline__ void compress_row(
     //      for HBM: what its first loads will ask for, i.e. its spread sample (if it takes the optimistic pass)
     //      and the sub-tiles behind it.  One register quadruple takes all of them (tied operand: loads return in order).
     u32x4_t dropped = {0u, 0u, 0u, 0u};
-    if (ahead > 0 && row + ahead < (int64_t)n_rows) {
+    // (The general code only: behind the fast kernels it costs what it gives or more: 4096 fp32 rows of 151,936, k = 4096, 449 us with it, 444
+    // without, 4352 bf16 rows of 152,064 280 and 279.)
+    if (!FAST && ahead > 0 && row + ahead < (int64_t)n_rows) {
         using Geom = CompressGeom<BF16, SMALL>;
         constexpr int N = Vec<BF16>::N, SV = Geom::SV, RING = Geom::RING;
         constexpr int NV0 = kCompressSample / (kT * N), PIECES = NV0 * (kT / 8);
@@ -1377,7 +1400,12 @@ __device__ __forceinline__ void compress_row(
     }
 
     const int n = min(sel.n_held, k);
-    const uint64_t* sorted = order_top_k<BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+    const uint64_t* sorted = order_top_k<BF16, 0, kFine, kCoarse, BF16 && FAST>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+    if (BF16 && FAST && !sorted) {
+        __syncthreads();                         // (the careful code starts on the words read above)
+        compress_row_again<BF16, SMALL>(row, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept);
+        return;
+    }
     emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass, dropped);
 }
 

@@ -136,6 +136,39 @@ def test_words_on_the_rows_edges_and_pairs_with_one_workgroup_per_row(gpu, pu, p
     pu.compare_compress(g, oracle.compress(np.ascontiguousarray(stored), V, 0.9, k), 0.0)
 
 
+# (bf16 candidates are ordered by places on a linear scale: equal values spread by id between two neighbours of the type, also where the
+# neighbours' distance changes - powers of two, next to zero - and where the scale ends; hundreds of zeros at the cut share one place)
+@pytest.mark.parametrize("pattern", ["across_zero", "zeros_at_the_cut", "powers_of_two", "tiny", "subnormal", "huge", "few_across_zero", "zipf"])
+@pytest.mark.parametrize("V,k", [(32768, 2048), (131072, 2048), (40001, 3000), (33001, 10)])
+def test_orders_of_bf16_values_with_one_workgroup_per_row(gpu, pu, ps, pattern, V, k):
+    _announce("bf16 orders", pattern, V, k)
+    rng = np.random.default_rng(V + k)
+    R = 4
+    z = rng.standard_normal((R, V))
+    share = 1.1 * k / V                                          # of the values above the middle of the pattern
+    if pattern == "across_zero":
+        z = z - np.quantile(z, 1 - share / 2)
+    elif pattern == "zeros_at_the_cut":
+        z = np.where(rng.random((R, V)) < share / 2, np.abs(z), np.where(rng.random((R, V)) < share, 0.0, -1.0 - np.abs(z)))
+    elif pattern == "powers_of_two":
+        z = np.sign(z) * np.exp2(np.round(np.abs(z) * 4) - 4)
+    elif pattern == "tiny":
+        z = (z - np.quantile(z, 1 - share)) * 1e-20
+    elif pattern == "subnormal":
+        z = z * 2e-39
+    elif pattern == "huge":
+        z = z * 3e37
+    elif pattern == "few_across_zero":
+        z = np.round((z - np.quantile(z, 1 - share / 2)) * 4) / 4
+    else:
+        z = 0.5 * z - 1.2 * np.log(np.floor(rng.random((R, V)) * V) + 1) + rng.standard_normal((R, V))
+    stored = W.to_bf16_bits(z.astype(np.float32))
+    T = 1e-20 if pattern == "tiny" else 1e37 if pattern == "huge" else 0.9
+    g = _unsplit(ps, pu.to_device(stored, gpu), V, T, k)
+    torch.cuda.synchronize()
+    pu.compare_compress(g, oracle.compress(stored, V, T, k), 0.0)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_infinities_and_nan_as_with_one_workgroup_per_row(gpu, ps, dtype):
     _announce("split infinities", dtype)
