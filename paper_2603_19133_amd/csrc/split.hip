@@ -14,8 +14,9 @@
 //     the record with the code of the unsplit kernels.  The answer is exact iff the k-th value lies above every workgroup's
 //     threshold, which is tested; a row that fails it (or whose lists overflow) is compressed from the start by the general
 //     code in the same workgroup.
-// Device time of a call, one workgroup per row -> split: one bf16 row of 128,256, k = 10: 25.5 -> 4.9 + 5.1
-// us; 64 fp32 rows of 151,936, k = 1024: 31.0 -> 12.4 + 8.4 us, of which the first launch reads 39 MB (5.8 us at 6.8 TB/s).  The line between the two is split_plan's.
+// Device time of a call, one workgroup per row -> split: one bf16 row of 128,256, k = 10: 25.5 -> 4.8 + 5.1 us; 64 fp32 rows of
+// 151,936, k = 1024: 31.0 -> 10.5 + 8.4 us, of which the first launch reads 39 MB (5.8 us at 6.8 TB/s).  The line between the two
+// is split_plan's.
 #include "compress_row.hpp"
 
 namespace picospec {
@@ -46,7 +47,7 @@ static_assert(sizeof(SplitHead) == 32, "two 16-byte loads");
 template <bool BF16>
 __device__ __forceinline__ void split_select(
     const int64_t row, const int part, const int P,
-    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int rank, int cap, int narrow,
+    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int rank, int cap, int narrow, int lanes,
     SplitHead* __restrict__ heads, uint2* __restrict__ lists,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
 {
@@ -145,15 +146,25 @@ __device__ __forceinline__ void split_select(
         }
         return true;
     };
+    const double ws = wave_sum((double)acc);
+    unsigned marks = 0;
+    int at = 0, held = 0;
+    // First (lanes > 0) by the lanes' largest values alone, one bin and atomic per lane instead of 32: with n of 256 lanes at or above it, a
+    // threshold has some -256 ln(1 - n / 256) elements above it, as the host chose n (split_plan); a list that comes out too long for
+    // its slots, a crowded pivot bin or too few lanes with a value (masks, values that trend within a lane) fall to the elements.
+    // 64 fp32 rows of 151,936, k = 1024: 12.2 -> 10.5 us, 32 bf16 of 128,256, k = 256: 7.5 -> 6.7, one, k = 10: 5.1 -> 4.8.
+    for (int by_lanes = lanes;; by_lanes = 0) {
+    bool again = false;
     if (finite && !(hi > lo)) {
         if (hi == lo) tau = float_below(lo);     // one value
     } else if (finite) {
-        int need = rank;
+        int need = by_lanes ? by_lanes : rank;
         bool open = true;                        // the threshold is not fine enough yet
         bool counted = false;                    // the histogram holds a pass
         uint32_t top = key_of_bits(__float_as_uint(hi)), bottom = key_of_bits(__float_as_uint(lo));
         const float width = (hi - lo) * (1.0f / (float)kSplitBins);
-        const float scale = __builtin_amdgcn_rcpf(width);
+        float scale = __builtin_amdgcn_rcpf(width);
+        asm volatile("" : "+v"(scale));          // (the elements' bins are formed in each round, not held from in front of it)
         if (scale < __builtin_huge_valf() && width < __builtin_huge_valf()) {
             const float at0 = hi * scale;
             // bin 0 holds the largest values; what lies below lo goes to the lane's own slot behind the bins
@@ -162,12 +173,22 @@ __device__ __forceinline__ void split_select(
                 asm("v_cvt_u32_f32 %0, %1" : "=v"(b) : "v"(fmaf(x, -scale, at0)));     // (saturates: below 0 and NaN 0, large 2^32 - 1)
                 return b;
             };
+            if (by_lanes) {
+                atomicAdd(&hist[min(bin_of(bm), (unsigned)(kSplitBins + lane))], 1u);
+            } else {
 #pragma unroll
-            for (int e = 0; e < E; ++e) atomicAdd(&hist[min(bin_of(v[e]), (unsigned)(kSplitBins + lane))], 1u);
+                for (int e = 0; e < E; ++e) atomicAdd(&hist[min(bin_of(v[e]), (unsigned)(kSplitBins + lane))], 1u);
+            }
             __syncthreads();
             counted = true;
-            if (!find_pivot(need)) open = false; // fewer than `need` elements above -inf (a masked row): tau stays -inf, all of them are listed
-            else {
+            if (!find_pivot(need)) {
+                if (by_lanes) again = true;      // (too few lanes with an element above -inf)
+                open = false;                    // fewer than `need` elements above -inf (a masked row): tau stays -inf, all of them are listed
+            } else if (by_lanes) {
+                tau = float_below(hi - ((float)(bin + 1) + 0.02f) * width);
+                open = false;
+                again = cnt > crowd;
+            } else {
                 const float edge = hi - ((float)(bin + 1) + 0.02f) * width;    // below every element of the bins up to the pivot
                 tau = float_below(edge);
                 open = cnt > crowd;
@@ -176,7 +197,8 @@ __device__ __forceinline__ void split_select(
                 bottom = max(bottom, key_of_bits(__float_as_uint(edge)));
             }
         }
-        for (int pass = 0; open && pass < 4; ++pass) {       // (a pass too many for the widest bin: one bin is one value by then)
+        if (by_lanes && !counted) again = true;
+        for (int pass = 0; open && !by_lanes && pass < 4; ++pass) {       // (a pass too many for the widest bin: one bin is one value by then)
             if (counted) {
                 __syncthreads();
                 *reinterpret_cast<uint2*>(&hist[2 * tid]) = make_uint2(0u, 0u);
@@ -206,18 +228,25 @@ __device__ __forceinline__ void split_select(
 
     // ---- the list: the elements above the threshold, in any order.  A lane marks its elements in a word, a scan over the
     //      counts gives it its slots, and it takes the few it marked from the image.
-    unsigned marks = 0;                          // bit 31 - e: element e
+    marks = 0;                                   // bit 31 - e: element e
     // (the sign of tau - v, shifted in; -inf below a threshold of -inf gives the positive NaN)
 #pragma unroll
     for (int e = 0; e < E; ++e) marks = __builtin_amdgcn_alignbit(marks, __float_as_uint(tau - v[e]), 31);
     const int mine = __popc(marks);
     const int incl = wave_scan_incl(mine);
-    const double ws = wave_sum((double)acc);
-    if (lane == kWave - 1) { wave_held[wave] = incl; wave_s[wave] = ws; }
+    if (lane == kWave - 1) wave_held[wave] = incl;
+    if (lane == 0) wave_s[wave] = ws;
     __syncthreads();
-    int at = incl - mine, held = 0;
+    at = incl - mine;
+    held = 0;
 #pragma unroll
     for (int w = 0; w < kSplitWaves; ++w) { at += w < wave ? wave_held[w] : 0; held += wave_held[w]; }
+    if (!by_lanes || (!again && held <= cap)) break;
+    // the elements themselves, then (the histogram is cleared; every wave has read the counts)
+    tau = kNegInf;
+    *reinterpret_cast<uint2*>(&hist[2 * tid]) = make_uint2(0u, 0u);
+    __syncthreads();
+    }
     const int64_t list = row * P + part;
     uint2* const out = lists + list * cap;
     const typename G::elem_t* const my_image = reinterpret_cast<const typename G::elem_t*>(image) + tid * N;
@@ -265,24 +294,24 @@ __device__ __forceinline__ void split_select(
 
 template <bool BF16>
 __global__ __launch_bounds__(kSplitThreads) void split_select_kernel(
-    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int rank, int cap, int narrow,
+    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int rank, int cap, int narrow, int lanes,
     SplitHead* __restrict__ heads, uint2* __restrict__ lists,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
 {
-    split_select<BF16>(blockIdx.y, (int)blockIdx.x, (int)gridDim.x, logits, ld, V, inv_T, rank, cap, narrow, heads, lists, seq_off, n_accept);
+    split_select<BF16>(blockIdx.y, (int)blockIdx.x, (int)gridDim.x, logits, ld, V, inv_T, rank, cap, narrow, lanes, heads, lists, seq_off, n_accept);
 }
 
 // A small round's draft rows and, in the same launch, the segment tables of its target rows: workgroups (x, y) with
 // y < n_draft and x < parts select, those with y >= n_draft and x < stats_per_row sum.
 template <bool BF16>
 __global__ __launch_bounds__(kSplitThreads) void split_round_kernel(
-    const void* __restrict__ draft_logits, int64_t ld_d, int n_draft, int V, float inv_T, int rank, int cap, int narrow,
+    const void* __restrict__ draft_logits, int64_t ld_d, int n_draft, int V, float inv_T, int rank, int cap, int narrow, int lanes,
     SplitHead* __restrict__ heads, uint2* __restrict__ lists, int parts,
     const void* __restrict__ tgt_logits, int64_t ld_t, int stats_per_row, SegHeader* __restrict__ header, int seg_stride)
 {
     const int x = blockIdx.x, y = blockIdx.y;
     if (y < n_draft) {
-        if (x < parts) split_select<BF16>(y, x, parts, draft_logits, ld_d, V, inv_T, rank, cap, narrow, heads, lists, nullptr, nullptr);
+        if (x < parts) split_select<BF16>(y, x, parts, draft_logits, ld_d, V, inv_T, rank, cap, narrow, lanes, heads, lists, nullptr, nullptr);
         return;
     }
     if (y == n_draft && x == 0 && threadIdx.x == 0)
@@ -416,8 +445,8 @@ hipError_t launch_split_compress(const void* logits, int dtype, int64_t ld, int 
     uint2* const lists = (uint2*)(heads + (size_t)n_rows * p.parts);
     const int narrow = p.rank <= kSplitNarrowRank;
     const dim3 grid(p.parts, n_rows);
-    if (dtype == 1) hipLaunchKernelGGL(split_select_kernel<true>, grid, dim3(kSplitThreads), 0, stream, logits, ld, V, inv_T, p.rank, p.cap, narrow, heads, lists, seq_off, n_accept);
-    else            hipLaunchKernelGGL(split_select_kernel<false>, grid, dim3(kSplitThreads), 0, stream, logits, ld, V, inv_T, p.rank, p.cap, narrow, heads, lists, seq_off, n_accept);
+    if (dtype == 1) hipLaunchKernelGGL(split_select_kernel<true>, grid, dim3(kSplitThreads), 0, stream, logits, ld, V, inv_T, p.rank, p.cap, narrow, p.lanes, heads, lists, seq_off, n_accept);
+    else            hipLaunchKernelGGL(split_select_kernel<false>, grid, dim3(kSplitThreads), 0, stream, logits, ld, V, inv_T, p.rank, p.cap, narrow, p.lanes, heads, lists, seq_off, n_accept);
     if (hipError_t e = hipGetLastError()) return e;
     return launch_split_finish(logits, dtype, ld, n_rows, V, temperature, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, p, heads, lists, stream);
 }
@@ -434,8 +463,8 @@ hipError_t launch_split_round(const void* draft_logits, int dtype, int64_t ld_d,
     uint2* const lists = (uint2*)(heads + (size_t)n_draft * p.parts);
     const int narrow = p.rank <= kSplitNarrowRank;
     const dim3 grid(p.parts > per_row ? p.parts : per_row, n_draft + n_target);
-    if (dtype == 1) hipLaunchKernelGGL(split_round_kernel<true>, grid, dim3(kSplitThreads), 0, stream, draft_logits, ld_d, n_draft, V, inv_T, p.rank, p.cap, narrow, heads, lists, p.parts, tgt_logits, ld_t, per_row, (SegHeader*)seg_table, sh.stride);
-    else            hipLaunchKernelGGL(split_round_kernel<false>, grid, dim3(kSplitThreads), 0, stream, draft_logits, ld_d, n_draft, V, inv_T, p.rank, p.cap, narrow, heads, lists, p.parts, tgt_logits, ld_t, per_row, (SegHeader*)seg_table, sh.stride);
+    if (dtype == 1) hipLaunchKernelGGL(split_round_kernel<true>, grid, dim3(kSplitThreads), 0, stream, draft_logits, ld_d, n_draft, V, inv_T, p.rank, p.cap, narrow, p.lanes, heads, lists, p.parts, tgt_logits, ld_t, per_row, (SegHeader*)seg_table, sh.stride);
+    else            hipLaunchKernelGGL(split_round_kernel<false>, grid, dim3(kSplitThreads), 0, stream, draft_logits, ld_d, n_draft, V, inv_T, p.rank, p.cap, narrow, p.lanes, heads, lists, p.parts, tgt_logits, ld_t, per_row, (SegHeader*)seg_table, sh.stride);
     if (hipError_t e = hipGetLastError()) return e;
     return launch_split_finish(draft_logits, dtype, ld_d, n_draft, V, temperature, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr, p, heads, lists, stream);
 }

@@ -186,6 +186,33 @@ def test_infinities_and_nan_as_with_one_workgroup_per_row(gpu, ps, dtype):
     assert torch.allclose(g.lse, u.lse, rtol=1e-6, atol=0, equal_nan=True)
 
 
+# (ranks up to 100 find their threshold by the lanes' largest values first: k = 308 and 1129 are the last that do in 5 and 19 parts)
+@pytest.mark.parametrize("pattern", ["normal", "one_lane", "few_lanes", "masked_but_a_lane", "masked_but_many", "crowded"])
+@pytest.mark.parametrize("V,k", [(16384, 1), (33001, 308), (33001, 309), (151936, 1129), (151936, 1130)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_thresholds_by_lanes_match_the_oracle_and_one_workgroup_per_row(gpu, pu, ps, pattern, V, k, dtype):
+    """Large values in one lane or few of every wave (lists too long for the lanes' threshold), masks that leave too few lanes, equal values."""
+    _announce("thresholds by lanes", pattern, V, k, dtype)
+    z = np.random.default_rng(k).standard_normal((3, V)).astype(np.float32) * 3
+    lane = np.arange(V) // (4 if dtype == "f32" else 8) % 64
+    if pattern == "one_lane":
+        z += np.float32(20) * (lane == 17)
+    elif pattern == "few_lanes":
+        z += np.float32(20) * (lane % 16 == 5)
+    elif pattern == "masked_but_a_lane":
+        z[:, lane != 63] = -np.inf
+    elif pattern == "masked_but_many":
+        z[:, lane % 3 > 0] = -np.inf
+    elif pattern == "crowded":
+        z = np.minimum(z, np.float32(2))
+    stored = z if dtype == "f32" else W.to_bf16_bits(z)
+    dev = pu.to_device(stored, gpu)
+    g, u = ps.compress(dev, V, 0.9, k), _unsplit(ps, dev, V, 0.9, k)
+    torch.cuda.synchronize()
+    pu.compare_compress(g, oracle.compress(stored, V, 0.9, k), 0.0)
+    assert torch.equal(g.idx, u.idx) and torch.equal(g.count, u.count)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("V,R,T", [(16384, 3, 1.0), (33001, 224, 0.7), (128256, 5, 0.05), ((1 << 20) - 5, 2, 1.0)])
 def test_row_statistics(gpu, pu, ps, dtype, V, R, T):
