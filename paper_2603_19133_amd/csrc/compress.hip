@@ -251,12 +251,17 @@ static int cus_of(int dev)
     return cus;
 }
 
-// (statistics of 2048 bf16 rows and more run in workgroups of 256 threads, which the launch for both streams has no form of)
+// bf16: statistics of 2048 rows and more run in workgroups of 256 threads, which the launch for both streams has no form of.  fp32: the more of the time
+// both streams are bound by memory, the less one hides in the other, and each then has its better launch shape alone.  us, a round in three
+// launches / two, drafts of 151,936: 1000 257 / 252, 1400 348 / 338, 1600 385 / 382 and 376 / 377, 1760 (k = 4096) 405 / 413, (k = 64) 360 / 349, 2048 462 / 474,
+// 4096 876 / 940; of 100,000: 1900 296 / 289, 2048 298 / 296; of 64,000: 2048 258 / 245; of 33,000: 1350 111 / 104, 4000 245 / 246.
+constexpr int64_t kWideRowsF32 = 4608, kWideBytesF32 = 1800000000;
 bool round_wide_serves(int dtype, int64_t n_draft, int64_t n_target, int V, int k)
 {
     if (n_draft < 1 || n_draft + n_target > INT32_MAX) return false;
     if (dtype == 1) return n_target < 2048 && small_variant_serves(k, V);
-    return compress_rank(k, V, false) > 0;
+    const int64_t rows = n_draft + n_target;
+    return rows <= kWideRowsF32 && rows * V * 4 <= kWideBytesF32 && compress_rank(k, V, false) > 0;
 }
 
 hipError_t launch_compress(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,

@@ -90,7 +90,8 @@ def test_round_call_matches_oracle_and_separate_calls(gpu, pu, ps, name, scale, 
                                                (torch.bfloat16, 1001, 22, 32768, 0, 64), (torch.bfloat16, 1001, 23, 32768, 0, 64),
                                                (torch.bfloat16, 2000, 47, 32768, 0, 64), (torch.bfloat16, 2000, 48, 32768, 0, 64),
                                                (torch.float32, 1, 520, 16385, 0, 4), (torch.float32, 301, 222, 33001, 3, 4096),
-                                               (torch.float32, 700, 2, 20000, 0, 1024)])
+                                               (torch.float32, 700, 2, 20000, 0, 1024),
+                                               (torch.float32, 4300, 308, 16385, 0, 64), (torch.float32, 4300, 309, 16385, 0, 64)])     # the most rows, and one more
 def test_both_streams_in_one_launch_match_the_separate_calls(gpu, pu, ps, dtype, N, B, V, pad, k):
     """Bit for bit, with rows among them that lose the first pass of the compression."""
     _announce("both streams in one launch", dtype, N, B, V, k)
