@@ -305,7 +305,7 @@ __device__ __forceinline__ void order_prepare(SH& sh, int n) {
 // 152,064 with Zipf-like values: 20 of the launch's 280 us went into that).  p = (M - w) 2^32 / span with w = v - id 2^-(8 + vb) |v|:
 // the gap from v to the next lower bf16 value is at least 2^-8 |v| and v - 2^-8 |v| is an fp32 value, so w, rounded, stays
 // between the two and falls with the id, and p never decreases along the wanted order.  Equal values next to zero share a place; a row
-// with a bin too crowded comes back as nullptr, for the careful code.
+// with a bin too crowded comes back as nullptr, its candidates where they were, to be ordered by keys.
 // CAND_PER * kT >= n slots of candidates, FINE fine bins and COARSE ranges: the whole buffer's by default; a caller that
 // knows n to be small has less to clear, scan and skip (split.hip).
 template <bool BF16, int CAND_PER = 0, int FINE = kFine, int COARSE = kCoarse, bool LINEAR = false, class SH>
@@ -1357,6 +1357,28 @@ __device__ __attribute__((noinline)) void compress_row_again(
     emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass, u32x4_t{0u, 0u, 0u, 0u});
 }
 
+// A row whose candidates crowd the linear places: ordered again by keys, from the candidates in LDS, and written.  Called for the same
+// reason.  (4000 bf16 rows of 152,064, k = 2048, with 1500 zeros among the candidates, us: 368 with keys only, 1356 when such a row was
+// compressed from the start, 413 so; 400 of 128,256, k = 1024: 47.5, 149, 45.9.)
+template <bool BF16, bool SMALL>
+__device__ __attribute__((noinline)) void order_row_again(
+    int64_t row, int n_held, int fill, uint32_t key_lo, uint32_t key_hi, float M, double S, int V, float inv_T, int k, float top_p,
+    int32_t* idx, float* prob, int32_t* count, float* mass)
+{
+    using SH = CompressShared<SMALL ? kCapSmall : kCapBig>;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    SH& sh = *reinterpret_cast<SH*>(smem_raw);
+    row = uniform(row); n_held = uniform(n_held); fill = uniform(fill); key_lo = uniform(key_lo); key_hi = uniform(key_hi); M = uniform(M); S = uniform(S);
+    V = uniform(V); inv_T = uniform(inv_T); k = uniform(k); top_p = uniform(top_p); idx = uniform(idx); prob = uniform(prob);
+    count = uniform(count); mass = uniform(mass);
+    __syncthreads();                             // (the words that sent the row here have been read)
+    order_prepare(sh, n_held);
+    __syncthreads();
+    const int n = min(n_held, k);
+    const uint64_t* sorted = order_top_k<BF16>(sh, n_held, n, V, key_lo, key_hi);
+    emit_row<BF16>(sh, sorted, row, n, fill != 0, M, S, inv_T, k, top_p, idx, prob, count, mass, u32x4_t{0u, 0u, 0u, 0u});
+}
+
 // One row of the compression: the workgroup that runs this writes record `row` of `n_rows`.
 template <bool BF16, bool SMALL, bool FAST = SMALL>
 __device__ __forceinline__ void compress_row(
@@ -1402,8 +1424,7 @@ __device__ __forceinline__ void compress_row(
     const int n = min(sel.n_held, k);
     const uint64_t* sorted = order_top_k<BF16, 0, kFine, kCoarse, BF16 && FAST>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
     if (BF16 && FAST && !sorted) {
-        __syncthreads();                         // (the careful code starts on the words read above)
-        compress_row_again<BF16, SMALL>(row, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept);
+        order_row_again<BF16, SMALL>(row, sel.n_held, sel.fill, sel.key_lo, sel.key_hi, sel.M, sel.S, V, inv_T, k, top_p, idx, prob, count, mass);
         return;
     }
     emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass, dropped);

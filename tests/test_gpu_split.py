@@ -169,6 +169,26 @@ def test_orders_of_bf16_values_with_one_workgroup_per_row(gpu, pu, ps, pattern, 
     pu.compare_compress(g, oracle.compress(stored, V, T, k), 0.0)
 
 
+@pytest.mark.parametrize("V,k,top_p", [(33001, 1, 0.0), (33001, 777, 0.9), (152064, 2048, 0.0)])
+@pytest.mark.parametrize("zeros,masked", [(129, False), (900, False), (900, True), (1, True)])
+def test_equal_values_next_to_zero_with_one_workgroup_per_row(gpu, pu, ps, V, k, top_p, zeros, masked):
+    """Zeros (of either sign) among the candidates of bf16 rows, which a linear scale of the values cannot tell apart; also in rows that
+    hold fewer entries above -inf than the record is long."""
+    _announce("equal values next to zero", V, k, top_p, zeros, masked)
+    rng = np.random.default_rng(zeros)
+    z = (rng.standard_normal((5, V)) - 6).astype(np.float32)
+    if masked:
+        z[:, rng.random(V) < 0.995] = -np.inf
+    for r in range(5):
+        at = rng.permutation(V)[:zeros]
+        z[r, at] = np.where(rng.random(zeros) < 0.5 * (r % 3), np.float32(-0.0), np.float32(0.0))
+        z[r, rng.permutation(V)[:20]] = 3.0
+    stored = W.to_bf16_bits(z)
+    u = _unsplit(ps, pu.to_device(stored, gpu), V, 1.0, k, top_p)
+    torch.cuda.synchronize()
+    pu.compare_compress(u, oracle.compress(stored, V, 1.0, k, top_p), top_p)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_infinities_and_nan_as_with_one_workgroup_per_row(gpu, ps, dtype):
     _announce("split infinities", dtype)
