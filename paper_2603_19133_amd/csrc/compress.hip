@@ -1,5 +1,5 @@
-// The kernels of the sparse Top-K compression (compress_row.hpp holds what a workgroup does with a row): the general
-// and the fast variants, the kernels that stream a round's draft and target rows at once, and the drafter's
+// The kernels of the sparse Top-K compression (compress_row.hpp holds what a workgroup does with a row): the fast
+// variants and the careful one, the kernels that stream a round's draft and target rows at once, and the drafter's
 // draw from a record.
 #include "compress_row.hpp"
 
@@ -7,22 +7,35 @@ namespace picospec {
 
 namespace {
 
-template <bool BF16, bool SMALL, bool FAST>
+template <bool BF16, bool SMALL>
 __global__ __launch_bounds__(kT, SMALL ? 6 : 4) void compress_kernel(
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
     int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
     float* __restrict__ mass, float* __restrict__ lse,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int ahead, int rank_opt)
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int rank_opt)
 {
-    compress_row<BF16, SMALL, FAST>(blockIdx.x, (int)gridDim.x, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse,
-                                    seq_off, n_accept, ahead, rank_opt);
+    compress_row<BF16, SMALL>(blockIdx.x, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, rank_opt);
+}
+
+// What the optimistic pass does not serve: rows of up to its sample's length, records it has no rank for.  (3000 fp32 rows of 8000, us: k = 10
+// 104.8, k = 4096 159.0 when one kernel held both passes, at 128 registers and some 150 scalar spills; 89.8 and 145.2 so.)
+template <bool BF16>
+__global__ __launch_bounds__(kT, 4) void compress_careful_kernel(
+    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
+    int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
+    float* __restrict__ mass, float* __restrict__ lse,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
+{
+    compress_row_careful<BF16, false>(blockIdx.x, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept);
 }
 
 // Both streams of a small round in one launch (the draft rows' compression and the target rows' statistics do
 // not depend on each other): workgroups 0..n_draft-1 compress, the others take one target row each.
-// (For what round_wide_kernel does not serve: registers are not held down to four waves per SIMD here.)
-template <bool BF16>
-__global__ __launch_bounds__(kT, 2) void round_stream_kernel(
+// (For what round_wide_kernel does not serve: rounds without a table, and rows and records that the optimistic pass does not serve:
+// CAREFUL.  With the rows' function of the fast kernels, us of a round without a workspace: 200 drafts and 240 target rows of 151,936, k = 256: fp32 88.9 -> 75.4,
+// bf16 64.2 -> 49.9; of 6000, CAREFUL: 32.4 -> 30.4, 30.8 -> 29.1.)
+template <bool BF16, bool CAREFUL>
+__global__ __launch_bounds__(kT, 4) void round_stream_kernel(
     const void* __restrict__ draft_logits, int64_t ld_d, int n_draft, int V, float inv_T, int k, float top_p,
     int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
     float* __restrict__ mass, float* __restrict__ lse,
@@ -31,8 +44,8 @@ __global__ __launch_bounds__(kT, 2) void round_stream_kernel(
     SegHeader* __restrict__ seg_header, int seg_stride, int rank_opt)
 {
     if ((int)blockIdx.x < n_draft) {
-        compress_row<BF16, false, false>(blockIdx.x, n_draft, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse,
-                                  nullptr, nullptr, 0, rank_opt);
+        if constexpr (CAREFUL) compress_row_careful<BF16, false>(blockIdx.x, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr);
+        else                   compress_row<BF16, false>(blockIdx.x, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr, rank_opt);
     } else if (seg_header) {
         // with the target rows' segment table (the draw then needs no second pass over its row); the row's table is
         // staged in the LDS that a compressing workgroup uses for its candidates
@@ -74,7 +87,7 @@ __global__ __launch_bounds__(kT, BF16 ? 6 : 4) void round_wide_kernel(
         target = x - n_draft;
     }
     if (__builtin_expect(draft < n_draft, 1)) {   // (the longer code first)
-        compress_row<BF16, BF16, true>(draft, n_draft, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr, 0, rank_opt);
+        compress_row<BF16, BF16>(draft, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr, rank_opt);
     } else {
         extern __shared__ __align__(16) unsigned char smem_raw[];
         if (target == 0 && threadIdx.x == 0) *seg_header = SegHeader{kSegMagic, seg_vecs, seg_stride, n_target};
@@ -270,40 +283,29 @@ hipError_t launch_compress(const void* logits, int dtype, int64_t ld, int n_rows
 {
     static DeviceFlags limit_raised[6] = {};
     const int bf = dtype == 1 ? 1 : 0;
-    // general (both passes in one kernel) / fast (optimistic pass, rows it gives up by a call), the latter with the large or the
-    // small candidate buffer
-    const void* const kernels[6] = {(const void*)compress_kernel<false, false, false>, (const void*)compress_kernel<true, false, false>,
-                                    (const void*)compress_kernel<false, false, true>, (const void*)compress_kernel<true, false, true>,
-                                    nullptr /* (the small buffer serves bf16 rows only) */, (const void*)compress_kernel<true, true, true>};
+    // the optimistic pass with the large or the small candidate buffer, and the careful pass
+    const void* const kernels[6] = {(const void*)compress_kernel<false, false>, (const void*)compress_kernel<true, false>,
+                                    nullptr /* (the small buffer serves bf16 rows only) */, (const void*)compress_kernel<true, true>,
+                                    (const void*)compress_careful_kernel<false>, (const void*)compress_careful_kernel<true>};
     const size_t smem_big = sizeof(CompressShared<kCapBig>), smem_small = sizeof(CompressShared<kCapSmall>);
-    int dev = 0;
     {   // (every variant of the dtype: which of them a call takes depends on its sizes)
         hipError_t e = hipSuccess;
+        int dev = 0;
         for (int v = 0; v < 3 && e == hipSuccess; ++v)
-            if (kernels[2 * v + bf]) e = raise_lds_limit_once(kernels[2 * v + bf], v == 2 ? smem_small : smem_big, limit_raised[2 * v + bf], dev);
+            if (kernels[2 * v + bf]) e = raise_lds_limit_once(kernels[2 * v + bf], v == 1 ? smem_small : smem_big, limit_raised[2 * v + bf], dev);
         if (e != hipSuccess) return e;
     }
     if (n_rows == 0) return hipSuccess;
-    const int cus = cus_of(dev);
     // (fp32 rows stream faster from two workgroups per CU with the large buffer than from three with the small one,
     //  measured at every record length; bf16 rows, which cost twice the arithmetic per byte, gain from the third)
     const bool small = bf && small_variant_serves(k, V);
-    // the general kernel takes what the optimistic pass does not serve (rows of up to its sample's length, records it has no rank for)
     const int rank_opt = compress_rank(k, V, small);
-    const bool fast = rank_opt > 0;
-    // rows resident at a time: the distance of the general kernel's look-ahead loads (none with a row map: the next row is not known
-    // from the row number)
-    const int ahead = (!seq_off && cus > 0) ? 2 * cus : 0;
     const float inv_T = 1.0f / temperature;
-#define PICOSPEC_COMPRESS(BF, SM, FA, SMEM) \
-    hipLaunchKernelGGL((compress_kernel<BF, SM, FA>), dim3(n_rows), dim3(kT), SMEM, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, ahead, rank_opt)
-    if (small) {
-        PICOSPEC_COMPRESS(true, true, true, smem_small);
-    } else if (fast) {
-        if (bf) PICOSPEC_COMPRESS(true, false, true, smem_big); else PICOSPEC_COMPRESS(false, false, true, smem_big);
-    } else {
-        if (bf) PICOSPEC_COMPRESS(true, false, false, smem_big); else PICOSPEC_COMPRESS(false, false, false, smem_big);
-    }
+#define PICOSPEC_COMPRESS(KERNEL, SMEM, ...) \
+    hipLaunchKernelGGL(KERNEL, dim3(n_rows), dim3(kT), SMEM, stream, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, ##__VA_ARGS__)
+    if (small) PICOSPEC_COMPRESS((compress_kernel<true, true>), smem_small, rank_opt);
+    else if (rank_opt > 0) { if (bf) PICOSPEC_COMPRESS((compress_kernel<true, false>), smem_big, rank_opt); else PICOSPEC_COMPRESS((compress_kernel<false, false>), smem_big, rank_opt); }
+    else                   { if (bf) PICOSPEC_COMPRESS((compress_careful_kernel<true>), smem_big); else PICOSPEC_COMPRESS((compress_careful_kernel<false>), smem_big); }
 #undef PICOSPEC_COMPRESS
     return hipGetLastError();
 }
@@ -337,23 +339,25 @@ hipError_t launch_round_stream(const void* draft_logits, int dtype, int64_t ld_d
                                const void* tgt_logits, int64_t ld_t, int n_target,
                                float* tgt_max, float* tgt_sum, float* tgt_lse, void* seg_table, hipStream_t stream)
 {
-    static DeviceFlags limit_raised[2] = {};
+    static DeviceFlags limit_raised[4] = {};
     const size_t smem = sizeof(CompressShared<kCapBig>);
-    auto f32 = round_stream_kernel<false>;
-    auto b16 = round_stream_kernel<true>;
-    const int which = dtype == 1;
-    {
+    const void* const kernels[4] = {(const void*)round_stream_kernel<false, false>, (const void*)round_stream_kernel<true, false>,
+                                    (const void*)round_stream_kernel<false, true>, (const void*)round_stream_kernel<true, true>};
+    const int bf = dtype == 1, rank_opt = compress_rank(k, V, false);
+    for (int v = 0; v < 2; ++v) {                // (both variants of the dtype: which of them a call takes depends on its sizes)
         int dev = 0;
-        hipError_t e = raise_lds_limit_once(which ? (const void*)b16 : (const void*)f32, smem, limit_raised[which], dev);
-        if (e != hipSuccess) return e;
+        if (hipError_t e = raise_lds_limit_once(kernels[2 * v + bf], smem, limit_raised[2 * v + bf], dev)) return e;
     }
     if (n_draft + n_target == 0) return hipSuccess;
     const float inv_T = 1.0f / temperature;
     if (n_target == 0) seg_table = nullptr;
     SegHeader* const header = (SegHeader*)seg_table;
     const int stride = round_stats_shape(dtype, V).stride;
-    if (which) hipLaunchKernelGGL(b16, dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, header, stride, compress_rank(k, V, false));
-    else       hipLaunchKernelGGL(f32, dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, header, stride, compress_rank(k, V, false));
+#define PICOSPEC_STREAM(BF, CA) \
+    hipLaunchKernelGGL((round_stream_kernel<BF, CA>), dim3(n_draft + n_target), dim3(kT), smem, stream, draft_logits, ld_d, n_draft, V, inv_T, k, top_p, idx, prob, count, mass, lse, tgt_logits, ld_t, tgt_max, tgt_sum, tgt_lse, header, stride, rank_opt)
+    if (rank_opt > 0) { if (bf) PICOSPEC_STREAM(true, false); else PICOSPEC_STREAM(false, false); }
+    else              { if (bf) PICOSPEC_STREAM(true, true); else PICOSPEC_STREAM(false, true); }
+#undef PICOSPEC_STREAM
     return hipGetLastError();
 }
 

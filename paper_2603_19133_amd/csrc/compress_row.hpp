@@ -1,10 +1,9 @@
 // Sparse Top-K compression of vocabulary distributions (paper Section 3.3, Eq. 4) fused with the
 // softmax statistics: one workgroup of 512 threads per row, two workgroups per CU (three with the
-// small candidate buffer), one HBM pass per row.  Three kernels per dtype share the code below
-// (launch_compress chooses): the general one (optimistic pass, then the safe pass for the rows that
-// lose it) for rows and records that the optimistic pass does not serve, and the fast ones, with the
-// large or the small candidate buffer, that hold the optimistic pass only and call a function for a
-// row that loses it.
+// small candidate buffer), one HBM pass per row.  The kernels share the code below (launch_compress
+// chooses): the careful one, the safe pass only, for rows and records that the optimistic pass does
+// not serve, and the fast ones, with the large or the small candidate buffer, that hold the
+// optimistic pass only and call a function for a row that loses it.
 //
 // Streaming selection.  A row is read with buffer loads (descriptor base + scalar offset + one
 // constant per-lane offset) in sub-tiles of two 16-byte vectors per thread through a ring of four
@@ -24,7 +23,7 @@
 //     candidates that fit the buffer, the exact top k is among them, because nothing at or above the
 //     threshold was dropped.  Waves run free in this pass; too many or too few candidates give the
 //     pass up.
-//   * Safe pass (only after a failed optimistic pass, or when the optimistic rank would not pay):
+//   * Safe pass (only for a row that lost the optimistic pass, or when the optimistic rank would not pay):
 //     the sample is the row's first 8192 elements, which are kept as candidates, and r = k, so the
 //     threshold is at or below the k-th largest of the sample.  The waves meet after
 //     every sub-tile; when the buffer is full it is pruned to the exact top k of everything seen,
@@ -89,8 +88,8 @@ struct __align__(16) CompressShared {
     int piv_bin, piv_before, piv_count;     // radix-select broadcast
     int maxbin;
     int overflowed;                         // a reservation of the sample did not fit (cannot happen: kept as a guard)
-    int epoch_overflow[3];                  // safe pass, per attempt epoch: some wave did not fit
-    int epoch_valid[3];                     // safe pass, per attempt epoch: first reservation that did not fit
+    int epoch_overflow[3];                  // safe pass, per epoch: some wave did not fit
+    int epoch_valid[3];                     // safe pass, per epoch: first reservation that did not fit
 };
 
 static_assert(sizeof(CompressShared<kCapBig>) <= 80 * 1024, "two workgroups share the 160 KB of LDS of a gfx950 CU");
@@ -484,7 +483,7 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
 }
 
 // What the selection leaves for the ordering: the candidates in LDS (n_held of them, every short key in [key_lo, key_hi])
-// and the row's statistics.  done = false: a FAST selection that gave the row up.
+// and the row's statistics.  done = false: an optimistic selection that gave the row up.
 struct RowSelection {
     int n_held;
     bool fill, done;                             // fill: fewer entries above -inf than k, masked entries fill the record up
@@ -506,12 +505,12 @@ __device__ __forceinline__ int sample_vec_of(int j, int n_vec, const uint4* base
 // The selection of one row (the streaming passes): candidates into LDS, statistics combined, lse[row] written.
 // SMALL: records of up to kMaxK / 2 entries on rows whose expected candidates fit the smaller buffer (the host
 // decides: launch_compress) - 51 KB of LDS and at most 80 registers, so that three workgroups share a CU.
-// FAST: the optimistic pass only (what the careful pass keeps alive across it costs registers, those that the third
-// workgroup needs among them): done = false for a row whose pass fails, or to which it does not apply.
-// CAREFUL: the careful pass only, for such a row (its sample must fit the buffer as candidates: one sub-tile with the small one).
+// The optimistic pass (what the careful pass keeps alive across it costs registers, those that the third workgroup needs among
+// them, so no code holds both): done = false for a row whose pass fails, or to which it does not apply.
+// CAREFUL: the careful pass, for such a row (its sample must fit the buffer as candidates: one sub-tile with the small one).
 // rank_opt: compress_rank() of the call, from the host (its square roots are a hundred instructions that every wave of every
 // row would spend on the same number).
-template <bool BF16, bool SMALL, bool FAST, bool CAREFUL = false>
+template <bool BF16, bool SMALL, bool CAREFUL>
 __device__ __forceinline__ RowSelection select_row(
     CompressShared<SMALL ? kCapSmall : kCapBig>& sh, const int64_t row,
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float* __restrict__ lse,
@@ -528,7 +527,7 @@ __device__ __forceinline__ RowSelection select_row(
     constexpr int T0 = SAMPLE / SUB, NV0 = T0 * SV, E0 = NV0 * N;
     constexpr int RING = Geom::RING;             // sub-tile buffers: one in use, the others in flight
     static_assert(Geom::N == N, "vector width");
-    static_assert(T0 >= 1 && T0 < RING && E0 <= 16 && (FAST || SAMPLE <= kCap), "sample geometry (the careful pass keeps its sample as candidates)");
+    static_assert(T0 >= 1 && T0 < RING && E0 <= 16 && (!CAREFUL || SAMPLE <= kCap), "sample geometry (the careful pass keeps its sample as candidates)");
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);   // uniform: what is indexed by it is addressed from a scalar
     // Row read: the same one, or (downlink record, Section 3.3) the target row of sequence `row` at its
@@ -824,8 +823,8 @@ __device__ __forceinline__ RowSelection select_row(
     bool fill = false;                           // fewer entries above -inf than k: masked entries fill the record up
 
     bool row_done = false;
-    for (int attempt = !CAREFUL && r_opt > 0 ? 0 : 1; attempt < (FAST ? 1 : 2); ++attempt) {
-        const bool optimistic = FAST || (!CAREFUL && attempt == 0);
+    constexpr bool optimistic = !CAREFUL;
+    if (CAREFUL || r_opt > 0) do {               // (left early by a row that is given up)
         if (tid == 0) {
             sh.cnt = optimistic ? (int)val_addr : 0;      // (the optimistic pass's counter is the LDS address of the next slot)
             sh.overflowed = 0;
@@ -1066,7 +1065,7 @@ __device__ __forceinline__ RowSelection select_row(
             n_held = enough ? held : -1;
             fill = enough && held < k;
             os.mx = cm;
-            __syncthreads();                     // everyone has read the verdict before the next attempt resets it
+            __syncthreads();                     // everyone has read the verdict before what follows a row given up resets it
         } else {
             // ---- behind the sample, safe: all waves meet after every sub-tile; a full buffer is pruned back to
             //      the exact top k of everything seen, after which admission is strict for the sub-tiles that follow.
@@ -1118,7 +1117,7 @@ __device__ __forceinline__ RowSelection select_row(
                 }
             }
         }
-        if (!enough) continue;                   // optimistic threshold too high, or buffer full: stream again, safely
+        if (!enough) break;                      // optimistic threshold too high, or buffer full: the caller streams it again, safely
 
         // ---- end of row
         if (n_held < 0) n_held = sh.cnt;
@@ -1140,12 +1139,11 @@ __device__ __forceinline__ RowSelection select_row(
 #pragma unroll
             for (int w = 0; w < kW; ++w) S += sh.red[kW + w];
         }
-        if (!enough) continue;
+        if (!enough) break;
         key_hi = short_key<BF16>(__float_as_uint(M));
         row_done = true;
-        break;
-    }
-    // (behind the loop: inside it the logarithm's constants are held in registers across the passes)
+    } while (false);
+    // (behind the pass: inside it the logarithm's constants are held in registers across the passes)
     if (row_done && tid == kT - 1) {             // (off the last wave's critical path later on)
         float it = inv_T;
         asm volatile("" : "+s"(it));             // widened here: hoisted to the top of the kernel it would hold two registers throughout
@@ -1154,14 +1152,12 @@ __device__ __forceinline__ RowSelection select_row(
     return RowSelection{n_held, fill, row_done, M, S, key_lo, key_hi};
 }
 
-// The record of a row from its ordered composites (the n = min(n_held, k) largest), written once.  `dropped`: the
-// look-ahead loads in flight, which have landed before the record's stores go out.
+// The record of a row from its ordered composites (the n = min(n_held, k) largest), written once.
 template <bool BF16, class SH>
 __device__ __forceinline__ void emit_row(
     SH& sh, const uint64_t* sorted, const int64_t row, const int n, const bool fill, const float M, const double S,
     float inv_T, int k, float top_p,
-    int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count, float* __restrict__ mass,
-    u32x4_t dropped)
+    int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count, float* __restrict__ mass)
 {
     constexpr int kRecMax = SH::kRecMax, kSortPer = kRecMax / kT;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -1204,10 +1200,6 @@ __device__ __forceinline__ void emit_row(
         for (int r = j - (int)free_before[lo]; r > 0; --r) free &= free - 1u;
         return lo * 32 + __ffs((int)free) - 1;
     };
-
-    // the dropped loads have landed (they were issued a whole ordering ago); waiting here, in front of the
-    // record's stores, keeps the wave from waiting for those at its end
-    asm volatile("s_waitcnt vmcnt(0)" : "+v"(dropped));
 
     const double cd = 1.4426950408889634 * (double)inv_T;
     const double invS = 1.0 / S;
@@ -1336,6 +1328,23 @@ __device__ __forceinline__ T uniform(T v) {
     return v;
 }
 
+// A row the careful way.
+template <bool BF16, bool SMALL>
+__device__ __forceinline__ void compress_row_careful(
+    const int64_t row, const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
+    int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
+    float* __restrict__ mass, float* __restrict__ lse,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
+{
+    using SH = CompressShared<SMALL ? kCapSmall : kCapBig>;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    SH& sh = *reinterpret_cast<SH*>(smem_raw);
+    const RowSelection sel = select_row<BF16, SMALL, true>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, 0);
+    const int n = min(sel.n_held, k);
+    const uint64_t* sorted = order_top_k<BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+    emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass);
+}
+
 // A row that lost the optimistic pass, the careful way, in the same workgroup: a function that is called, so that what this
 // rare pass keeps alive costs the code in front of it nothing (inlined it takes the kernel from 75 registers to 128, its scalar
 // ones to 150 spills, and every row 3 to 4 us: 300 bf16 rows of 50,001, k = 777: 29.4 -> 25.1 us, 512 of 128,256, k = 1024:
@@ -1345,16 +1354,8 @@ __device__ __attribute__((noinline)) void compress_row_again(
     int64_t row, const void* logits, int64_t ld, int V, float inv_T, int k, float top_p,
     int32_t* idx, float* prob, int32_t* count, float* mass, float* lse, const int32_t* seq_off, const int32_t* n_accept)
 {
-    using SH = CompressShared<SMALL ? kCapSmall : kCapBig>;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    SH& sh = *reinterpret_cast<SH*>(smem_raw);
-    row = uniform(row); logits = uniform(logits); ld = uniform(ld); V = uniform(V); inv_T = uniform(inv_T); k = uniform(k);
-    top_p = uniform(top_p); idx = uniform(idx); prob = uniform(prob); count = uniform(count); mass = uniform(mass);
-    lse = uniform(lse); seq_off = uniform(seq_off); n_accept = uniform(n_accept);
-    const RowSelection sel = select_row<BF16, SMALL, false, true>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, 0);
-    const int n = min(sel.n_held, k);
-    const uint64_t* sorted = order_top_k<BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
-    emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass, u32x4_t{0u, 0u, 0u, 0u});
+    compress_row_careful<BF16, SMALL>(uniform(row), uniform(logits), uniform(ld), uniform(V), uniform(inv_T), uniform(k), uniform(top_p),
+                                      uniform(idx), uniform(prob), uniform(count), uniform(mass), uniform(lse), uniform(seq_off), uniform(n_accept));
 }
 
 // A row whose candidates crowd the linear places: ordered again by keys, from the candidates in LDS, and written.  Called for the same
@@ -1376,58 +1377,33 @@ __device__ __attribute__((noinline)) void order_row_again(
     __syncthreads();
     const int n = min(n_held, k);
     const uint64_t* sorted = order_top_k<BF16>(sh, n_held, n, V, key_lo, key_hi);
-    emit_row<BF16>(sh, sorted, row, n, fill != 0, M, S, inv_T, k, top_p, idx, prob, count, mass, u32x4_t{0u, 0u, 0u, 0u});
+    emit_row<BF16>(sh, sorted, row, n, fill != 0, M, S, inv_T, k, top_p, idx, prob, count, mass);
 }
 
-// One row of the compression: the workgroup that runs this writes record `row` of `n_rows`.
-template <bool BF16, bool SMALL, bool FAST = SMALL>
+// One row of the compression: the workgroup that runs this writes record `row`.
+template <bool BF16, bool SMALL>
 __device__ __forceinline__ void compress_row(
-    const int64_t row, const int n_rows,
+    const int64_t row,
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
     int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
     float* __restrict__ mass, float* __restrict__ lse,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int ahead, int rank_opt)
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int rank_opt)
 {
     using SH = CompressShared<SMALL ? kCapSmall : kCapBig>;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     SH& sh = *reinterpret_cast<SH*>(smem_raw);
-    const RowSelection sel = select_row<BF16, SMALL, FAST>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, rank_opt);
-    if (FAST && !sel.done) {                     // (uniform: the verdict was read from LDS behind a barrier)
+    const RowSelection sel = select_row<BF16, SMALL, false>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, rank_opt);
+    if (!sel.done) {                             // (uniform: the verdict was read from LDS behind a barrier)
         compress_row_again<BF16, SMALL>(row, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept);
         return;
     }
-
-    // While this row is ordered and emitted, the first sub-tiles of the row that will take a slot like
-    //      this one next (`ahead` rows further: as many rows as the chip holds at a time, same XCD) are pulled
-    //      into the caches with ordinary loads whose data is dropped, so that row does not start by waiting
-    //      for HBM: what its first loads will ask for, i.e. its spread sample (if it takes the optimistic pass)
-    //      and the sub-tiles behind it.  One register quadruple takes all of them (tied operand: loads return in order).
-    u32x4_t dropped = {0u, 0u, 0u, 0u};
-    // (The general code only: behind the fast kernels it costs what it gives or more: 4096 fp32 rows of 151,936, k = 4096, 449 us with it, 444
-    // without, 4352 bf16 rows of 152,064 280 and 279.)
-    if (!FAST && ahead > 0 && row + ahead < (int64_t)n_rows) {
-        using Geom = CompressGeom<BF16, SMALL>;
-        constexpr int N = Vec<BF16>::N, SV = Geom::SV, RING = Geom::RING;
-        constexpr int NV0 = kCompressSample / (kT * N), PIECES = NV0 * (kT / 8);
-        const RowView nv = row_view<BF16>(logits, ld, row + ahead, V);
-        const int nq2 = (nv.L + N - 1) / N;
-        const bool spread = V > kCompressSample && rank_opt > 0;
-        const int n_spread = (spread && nq2 >= 8 * PIECES + 8) ? NV0 : 0;
-#pragma unroll
-        for (int j = 0; j < RING * SV; ++j) {
-            const int q = j < n_spread ? sample_vec_of(j, nq2, nv.base, PIECES) : (j - n_spread) * kT + (int)threadIdx.x;
-            const uint4* p = nv.base + min(q, nq2 - 1);
-            asm volatile("global_load_dwordx4 %0, %1, off" : "+v"(dropped) : "v"(p));
-        }
-    }
-
     const int n = min(sel.n_held, k);
-    const uint64_t* sorted = order_top_k<BF16, 0, kFine, kCoarse, BF16 && FAST>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
-    if (BF16 && FAST && !sorted) {
+    const uint64_t* sorted = order_top_k<BF16, 0, kFine, kCoarse, BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+    if (BF16 && !sorted) {
         order_row_again<BF16, SMALL>(row, sel.n_held, sel.fill, sel.key_lo, sel.key_hi, sel.M, sel.S, V, inv_T, k, top_p, idx, prob, count, mass);
         return;
     }
-    emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass, dropped);
+    emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass);
 }
 
 }  // namespace

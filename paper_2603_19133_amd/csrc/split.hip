@@ -12,8 +12,8 @@
 //     them to a list of its own in the scratch, and its share of the statistics in front of it.
 //   * split_finish_kernel: one workgroup per row gathers the lists (about k plus the ranks' margins), orders them and writes
 //     the record with the code of the unsplit kernels.  The answer is exact iff the k-th value lies above every workgroup's
-//     threshold, which is tested; a row that fails it (or whose lists overflow) is compressed from the start by the general
-//     code in the same workgroup.
+//     threshold, which is tested; a row that fails it (or whose lists overflow) is compressed from the start by the
+//     unsplit kernels' code in the same workgroup.
 // Device time of a call, one workgroup per row -> split: one bf16 row of 128,256, k = 10: 25.5 -> 4.8 + 5.1 us; 64 fp32 rows of
 // 151,936, k = 1024: 31.0 -> 10.5 + 8.4 us, of which the first launch reads 39 MB (5.8 us at 6.8 TB/s).  The line between the two
 // is split_plan's.
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_round_kernel(
         row_stats_parts<BF16>(y - n_draft, y - n_draft, x, tgt_logits, ld_t, V, inv_T, reinterpret_cast<float2*>(header + 1), seg_stride);
 }
 
-// A row whose lists do not hold its answer, from the start.  A function that is called: inlined, what the general code keeps alive
+// A row whose lists do not hold its answer, from the start.  A function that is called: inlined, what that code keeps alive
 // costs every row 0.8 to 1.1 us (one row of 128,256 bf16, k = 10: 6.0 -> 5.1; 64 of 151,936 fp32, k = 1024: 9.5 -> 8.4).
 // (It is the fast kernels' code, which calls the careful pass in turn: a call, us, of 40 rows of 128,256, k = 512, that all come here, 13 entries above -inf in
 // each: fp32 49.2 with both passes in the one function, 42.6 so, bf16 40.2 and 37.5; inlined, at every other row's cost, 37 and 36 to 38.)
@@ -329,10 +329,9 @@ __device__ __attribute__((noinline)) void split_row_again(
     int64_t row, const void* logits, int64_t ld, int V, float inv_T, int k, float top_p,
     int32_t* idx, float* prob, int32_t* count, float* mass, float* lse, const int32_t* seq_off, const int32_t* n_accept, int rank_opt)
 {
-    row = uniform(row);
-    compress_row<BF16, false, true>(row, (int)row + 1, uniform(logits), uniform(ld), uniform(V), uniform(inv_T), uniform(k), uniform(top_p),
-                                     uniform(idx), uniform(prob), uniform(count), uniform(mass), uniform(lse), uniform(seq_off),
-                                     uniform(n_accept), 0, uniform(rank_opt));
+    compress_row<BF16, false>(uniform(row), uniform(logits), uniform(ld), uniform(V), uniform(inv_T), uniform(k), uniform(top_p),
+                              uniform(idx), uniform(prob), uniform(count), uniform(mass), uniform(lse), uniform(seq_off),
+                              uniform(n_accept), uniform(rank_opt));
 }
 
 template <bool BF16>
@@ -406,7 +405,7 @@ __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
         // the lists hold every element above T: they hold the top k iff the k-th lies above it
         // (bf16: the short key of a T between two values is that of the lower one)
         if (T == kNegInf || (uint32_t)(sorted[n - 1] >> kIdBits) > short_key<BF16>(__float_as_uint(T))) {
-            emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass, u32x4_t{0u, 0u, 0u, 0u});
+            emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass);
             return;
         }
     }

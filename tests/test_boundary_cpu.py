@@ -289,7 +289,7 @@ def test_compress_kernels_keep_claimed_slots_in_registers():
             kernels[name]["in_window"] += pending
     claiming = {k: v for k, v in kernels.items() if v["atomics"] >= 8}
     hot = [k for k in claiming if "compress_kernel" in k or "round_stream_kernel" in k]
-    assert len(hot) == 7 and len(claiming) == 9, sorted(claiming)      # + the two instantiations of round_wide_kernel
+    assert len(hot) == 5 and len(claiming) == 7, sorted(claiming)      # + the two instantiations of round_wide_kernel
     assert all(v["in_window"] == 0 for v in claiming.values()), claiming
     assert all(claiming[k]["scratch"] == 0 for k in hot), {k: claiming[k] for k in hot}
 
