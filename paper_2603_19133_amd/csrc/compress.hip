@@ -14,7 +14,7 @@ __global__ __launch_bounds__(kT, SMALL ? 6 : 4) void compress_kernel(
     float* __restrict__ mass, float* __restrict__ lse,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int rank_opt)
 {
-    compress_row<BF16, SMALL>(blockIdx.x, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, rank_opt);
+    compress_row<BF16, SMALL>(blockIdx.x, record_source<BF16>(blockIdx.x, logits, ld, V, seq_off, n_accept), V, inv_T, k, top_p, idx, prob, count, mass, lse, rank_opt);
 }
 
 // What the optimistic pass does not serve: rows of up to its sample's length, records it has no rank for.  (3000 fp32 rows of 8000, us: k = 10
@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kT, 4) void compress_careful_kernel(
     float* __restrict__ mass, float* __restrict__ lse,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
 {
-    compress_row_careful<BF16, false>(blockIdx.x, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept);
+    compress_row_careful<BF16, false>(blockIdx.x, record_source<BF16>(blockIdx.x, logits, ld, V, seq_off, n_accept), V, inv_T, k, top_p, idx, prob, count, mass, lse);
 }
 
 // Both streams of a small round in one launch (the draft rows' compression and the target rows' statistics do
@@ -44,8 +44,9 @@ __global__ __launch_bounds__(kT, 4) void round_stream_kernel(
     SegHeader* __restrict__ seg_header, int seg_stride, int rank_opt)
 {
     if ((int)blockIdx.x < n_draft) {
-        if constexpr (CAREFUL) compress_row_careful<BF16, false>(blockIdx.x, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr);
-        else                   compress_row<BF16, false>(blockIdx.x, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr, rank_opt);
+        const RowView rv = row_view<BF16>(draft_logits, ld_d, blockIdx.x, V);
+        if constexpr (CAREFUL) compress_row_careful<BF16, false>(blockIdx.x, rv, V, inv_T, k, top_p, idx, prob, count, mass, lse);
+        else                   compress_row<BF16, false>(blockIdx.x, rv, V, inv_T, k, top_p, idx, prob, count, mass, lse, rank_opt);
     } else if (seg_header) {
         // with the target rows' segment table (the draw then needs no second pass over its row); the row's table is
         // staged in the LDS that a compressing workgroup uses for its candidates
@@ -87,7 +88,7 @@ __global__ __launch_bounds__(kT, BF16 ? 6 : 4) void round_wide_kernel(
         target = x - n_draft;
     }
     if (__builtin_expect(draft < n_draft, 1)) {   // (the longer code first)
-        compress_row<BF16, BF16>(draft, draft_logits, ld_d, V, inv_T, k, top_p, idx, prob, count, mass, lse, nullptr, nullptr, rank_opt);
+        compress_row<BF16, BF16>(draft, row_view<BF16>(draft_logits, ld_d, draft, V), V, inv_T, k, top_p, idx, prob, count, mass, lse, rank_opt);
     } else {
         extern __shared__ __align__(16) unsigned char smem_raw[];
         if (target == 0 && threadIdx.x == 0) *seg_header = SegHeader{kSegMagic, seg_vecs, seg_stride, n_target};

@@ -495,11 +495,28 @@ struct RowSelection {
 // vector of thread tid in run j*(kT/8) + tid/8 of the spread sample (n_pieces runs) of a row of n_vec vectors at `base`:
 // the runs start on 128-byte lines of memory (one line fetched per run), at least 8 vectors apart once
 // n_vec >= 8*n_pieces + 8
+__device__ __forceinline__ int sample_run_first(int run, int n_vec, const uint4* base, int n_pieces) {     // first vector of a run
+    const int shift = (int)(((uintptr_t)base >> 4) & 7u);
+    const int a = (run * (n_vec - 16)) / (n_pieces - 1) + shift;
+    return ((a + 7) & ~7) - shift;
+}
 __device__ __forceinline__ int sample_vec_of(int j, int n_vec, const uint4* base, int n_pieces) {
     const int tid = threadIdx.x;
-    const int shift = (int)(((uintptr_t)base >> 4) & 7u);
-    const int a = ((j * (kT / 8) + (tid >> 3)) * (n_vec - 16)) / (n_pieces - 1) + shift;
-    return ((a + 7) & ~7) - shift + (tid & 7);
+    return sample_run_first(j * (kT / 8) + (tid >> 3), n_vec, base, n_pieces) + (tid & 7);
+}
+
+// The row that record `row` is read from: the same one, or (downlink record, Section 3.3) the target row of sequence `row` at its
+// first rejected or bonus position, seq_off[b] + b + n_accept[b] (n_accept clamped to 0..gamma_b).
+template <bool BF16>
+__device__ __forceinline__ RowView record_source(
+    const int64_t row, const void* __restrict__ logits, int64_t ld, int V, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
+{
+    int64_t in_row = row;
+    if (seq_off) {
+        const int d0 = seq_off[row], g = max(seq_off[row + 1] - d0, 0);
+        in_row = (int64_t)d0 + row + min(max(n_accept[row], 0), g);
+    }
+    return row_view<BF16>(logits, ld, in_row, V);
 }
 
 // The selection of one row (the streaming passes): candidates into LDS, statistics combined, lse[row] written.
@@ -513,8 +530,7 @@ __device__ __forceinline__ int sample_vec_of(int j, int n_vec, const uint4* base
 template <bool BF16, bool SMALL, bool CAREFUL>
 __device__ __forceinline__ RowSelection select_row(
     CompressShared<SMALL ? kCapSmall : kCapBig>& sh, const int64_t row,
-    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float* __restrict__ lse,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, const int rank_opt)
+    const RowView rv, int V, float inv_T, int k, float* __restrict__ lse, const int rank_opt)
 {
     using SH = CompressShared<SMALL ? kCapSmall : kCapBig>;
     constexpr int kCap = SH::kCap;
@@ -530,14 +546,6 @@ __device__ __forceinline__ RowSelection select_row(
     static_assert(T0 >= 1 && T0 < RING && E0 <= 16 && (!CAREFUL || SAMPLE <= kCap), "sample geometry (the careful pass keeps its sample as candidates)");
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);   // uniform: what is indexed by it is addressed from a scalar
-    // Row read: the same one, or (downlink record, Section 3.3) the target row of sequence `row` at its
-    // first rejected or bonus position, seq_off[b] + b + n_accept[b] (n_accept clamped to 0..gamma_b).
-    int64_t in_row = row;
-    if (seq_off) {
-        const int d0 = seq_off[row], g = max(seq_off[row + 1] - d0, 0);
-        in_row = (int64_t)d0 + row + min(max(n_accept[row], 0), g);
-    }
-    const RowView rv = row_view<BF16>(logits, ld, in_row, V);
     const int n_sub = (rv.L + SUB - 1) / SUB;
     const int nq = (rv.L + N - 1) / N;           // 16-byte vectors that overlap the row
     const float c = 1.4426950408889634f * inv_T;
@@ -787,6 +795,8 @@ __device__ __forceinline__ RowSelection select_row(
     // second one claims a slot of its own.  Returns the largest of this thread's candidates.
     auto split_words = [&](int words, float tau) {
         float cm = kNegInf;
+        unsigned V_here = (unsigned)V;
+        asm volatile("" : "+s"(V_here));         // (fetched once from where the arguments are kept, not for every word)
 #pragma unroll
         for (int j = 0; j < kCap / kT; ++j) {
             const int i = tid + j * kT;
@@ -795,7 +805,7 @@ __device__ __forceinline__ RowSelection select_row(
                 if constexpr (BF16) {
                     const unsigned x = sh.cand_id[i];
                     const float lo = __uint_as_float(raw << 16), hi = __uint_as_float(raw & 0xFFFF0000u);
-                    const bool pl = lo > tau && x < (unsigned)V, ph = hi > tau && x + 1u < (unsigned)V;     // (x = -1: a word that begins in front of the row)
+                    const bool pl = lo > tau && x < V_here, ph = hi > tau && x + 1u < V_here;     // (x = -1: a word that begins in front of the row)
                     sh.cand_val[i] = __float_as_uint(pl ? lo : hi);
                     sh.cand_id[i] = pl ? x : x + 1u;
                     cm = pl ? fmaxf(cm, lo) : cm;
@@ -848,6 +858,7 @@ __device__ __forceinline__ RowSelection select_row(
         // ---- the sample: the first threshold (and, in the safe pass, the statistics of its elements)
         float tau = kNegInf;                     // elements are admitted iff > tau ...
         bool admit_all = true;                   // ... or, before a threshold exists, all of them
+        int cut_sub = 0x7FFFFFFF;                // optimistic pass, bf16: sub-tile from which on they must exceed the next larger float
         {
             float v[E0];
             float bm;
@@ -984,6 +995,29 @@ __device__ __forceinline__ RowSelection select_row(
                 }
                 const float t = __uint_as_float(bits_of_short_key<BF16>(lo));   // lower edge of the pivot bin
                 if (t > kNegInf) { tau = float_below(t); admit_all = false; key_lo = lo; }
+                if constexpr (BF16 && optimistic) {
+                    // Values on a coarse grid: the key found is one value, and where the row is expected to hold more of it than there are slots,
+                    // only those of the lowest ids can be of use.  It is counted by the sample's runs, which ascend with the id: the run by whose end as
+                    // many as are needed have been seen ends the ids whose ties are admitted (in whole sub-tiles; a row that finds too few or too many
+                    // of them is given up like any other).  Calls, us, of rows that gave the pass up for it / so: 400 of 128,256 in steps of two, k =
+                    // 1024: 153 / 43 (not on a grid: 32), 512 of 152,064 in whole numbers, k = 2048: 180 / 49 (41), 2000: 380 / 148 (130).
+                    const float per = (float)V * (1.0f / (float)SAMPLE), held = (float)(target - need + sh.piv_count) * per, room = (float)kCap - held;
+                    if (t > kNegInf && (room < 0.f || room * room < 20.f * held * per)) {      // (4.5 standard deviations are asked for)
+                        __syncthreads();         // (the pivot's words have been read)
+                        zero_hist(sh);
+                        __syncthreads();
+#pragma unroll
+                        for (int e = 0; e < E0; ++e) if (v[e] == t) atomicAdd(&sh.hist[(e / N) * (kT / 8) + (tid >> 3)], 1u);
+                        __syncthreads();
+                        static_assert(PIECES % kWave == 0 && PIECES <= kBins, "as many runs for every lane");
+                        int mine = 0;
+#pragma unroll
+                        for (int u = 0; u < PIECES / kWave; ++u) mine += (int)sh.hist[lane * (PIECES / kWave) + u];
+                        const unsigned long long reach = __ballot(wave_scan_incl(mine) >= need);
+                        const int run = (__ffsll((long long)reach) - 1) * (PIECES / kWave) + PIECES / kWave - 1;
+                        cut_sub = __builtin_amdgcn_readfirstlane(sample_run_first(run, nq, rv.base, PIECES) + 7) / (kT * SV) + 1;
+                    }
+                }
             }
             if (admit_all && more) key_lo = 0;   // later sub-tiles may go below the sample's minimum
             if (!have_tau) __syncthreads();      // (with a one-pass threshold the barrier behind the pivot stands here already)
@@ -1011,8 +1045,12 @@ __device__ __forceinline__ RowSelection select_row(
                 int slot[WS];                    // per word: this lane's claim
 #pragma unroll
                 for (int i = 0; i < WS; ++i) slot[i] = (int)val_addr;
+                auto cut_at = [&](int sub) {     // (float_below undone)
+                    if (BF16 && __builtin_expect(sub == cut_sub, 0)) tau = __uint_as_float(__float_as_uint(tau) + (tau < 0.f ? -1u : 1u));
+                };
                 auto full = [&](int sub, uint4 (&buf)[SV]) {        // a sub-tile wholly inside the row
                     float v[ES];
+                    cut_at(sub);
                     unsigned long long passed[WS];
                     unpack_vecs(sv_t{}, 0, buf, v, false);
                     const unsigned next = claim_asm(sv_t{}, v, tau, slot, passed);
@@ -1025,6 +1063,7 @@ __device__ __forceinline__ RowSelection select_row(
                         float v[ES];
                         unsigned long long passed[WS];
                         const bool edge = sub + 1 == n_sub;
+                        cut_at(sub);
                         unpack_vecs(sv_t{}, sub * (kT * SV) + tid, buf, v, edge);
                         const unsigned next = claim_asm(sv_t{}, v, tau, slot, passed);
                         add_sum(es_t{}, v, edge, nr);
@@ -1052,6 +1091,19 @@ __device__ __forceinline__ RowSelection select_row(
             __syncthreads();
             const int words = (int)((unsigned)sh.cnt - val_addr) >> 2;  // (this pass's counter is an LDS byte address)
             const bool fits = applies && !sh.overflowed && words <= kCap;
+            if (BF16 && __builtin_expect(cut_sub < n_sub, 0)) {
+                // (rare: elements of words behind the cut that their sub-tiles did not admit are masked, then all go by the lower threshold)
+#pragma unroll 1
+                for (int i = tid; i < min(words, kCap); i += kT) {
+                    unsigned raw = sh.cand_val[i];
+                    if ((int)sh.cand_id[i] >= cut_sub * SUB - rv.o) {
+                        if (!(__uint_as_float(raw << 16) > tau)) raw = (raw & 0xFFFF0000u) | 0xFF80u;
+                        if (!(__uint_as_float(raw & 0xFFFF0000u) > tau)) raw = (raw & 0xFFFFu) | 0xFF800000u;
+                        sh.cand_val[i] = raw;
+                    }
+                }
+                tau = float_below(tau);
+            }
             if constexpr (BF16) __syncthreads();     // (everyone has read the counter before it moves on)
             // the row's largest value is its largest candidate (slots behind the last one hold stale values)
             const float cm = fits ? split_words(words, tau) : kNegInf;
@@ -1331,15 +1383,14 @@ __device__ __forceinline__ T uniform(T v) {
 // A row the careful way.
 template <bool BF16, bool SMALL>
 __device__ __forceinline__ void compress_row_careful(
-    const int64_t row, const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
+    const int64_t row, const RowView rv, int V, float inv_T, int k, float top_p,
     int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
-    float* __restrict__ mass, float* __restrict__ lse,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
+    float* __restrict__ mass, float* __restrict__ lse)
 {
     using SH = CompressShared<SMALL ? kCapSmall : kCapBig>;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     SH& sh = *reinterpret_cast<SH*>(smem_raw);
-    const RowSelection sel = select_row<BF16, SMALL, true>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, 0);
+    const RowSelection sel = select_row<BF16, SMALL, true>(sh, row, rv, V, inv_T, k, lse, 0);
     const int n = min(sel.n_held, k);
     const uint64_t* sorted = order_top_k<BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
     emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass);
@@ -1351,11 +1402,12 @@ __device__ __forceinline__ void compress_row_careful(
 // 43.6 -> 40.4, 1 of 33,000, k = 10: 16.2 -> 13.3; calls that fill the chip spared it by a second launch for the lost rows, 4.7 us).
 template <bool BF16, bool SMALL>
 __device__ __attribute__((noinline)) void compress_row_again(
-    int64_t row, const void* logits, int64_t ld, int V, float inv_T, int k, float top_p,
-    int32_t* idx, float* prob, int32_t* count, float* mass, float* lse, const int32_t* seq_off, const int32_t* n_accept)
+    int64_t row, const uint4* base, int o, int V, float inv_T, int k, float top_p,
+    int32_t* idx, float* prob, int32_t* count, float* mass, float* lse)
 {
-    compress_row_careful<BF16, SMALL>(uniform(row), uniform(logits), uniform(ld), uniform(V), uniform(inv_T), uniform(k), uniform(top_p),
-                                      uniform(idx), uniform(prob), uniform(count), uniform(mass), uniform(lse), uniform(seq_off), uniform(n_accept));
+    V = uniform(V); o = uniform(o);
+    compress_row_careful<BF16, SMALL>(uniform(row), RowView{uniform(base), o, o + V}, V, uniform(inv_T), uniform(k), uniform(top_p),
+                                      uniform(idx), uniform(prob), uniform(count), uniform(mass), uniform(lse));
 }
 
 // A row whose candidates crowd the linear places: ordered again by keys, from the candidates in LDS, and written.  Called for the same
@@ -1383,18 +1435,16 @@ __device__ __attribute__((noinline)) void order_row_again(
 // One row of the compression: the workgroup that runs this writes record `row`.
 template <bool BF16, bool SMALL>
 __device__ __forceinline__ void compress_row(
-    const int64_t row,
-    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
+    const int64_t row, const RowView rv, int V, float inv_T, int k, float top_p,
     int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
-    float* __restrict__ mass, float* __restrict__ lse,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, int rank_opt)
+    float* __restrict__ mass, float* __restrict__ lse, int rank_opt)
 {
     using SH = CompressShared<SMALL ? kCapSmall : kCapBig>;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     SH& sh = *reinterpret_cast<SH*>(smem_raw);
-    const RowSelection sel = select_row<BF16, SMALL, false>(sh, row, logits, ld, V, inv_T, k, lse, seq_off, n_accept, rank_opt);
+    const RowSelection sel = select_row<BF16, SMALL, false>(sh, row, rv, V, inv_T, k, lse, rank_opt);
     if (!sel.done) {                             // (uniform: the verdict was read from LDS behind a barrier)
-        compress_row_again<BF16, SMALL>(row, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept);
+        compress_row_again<BF16, SMALL>(row, rv.base, rv.o, V, inv_T, k, top_p, idx, prob, count, mass, lse);
         return;
     }
     const int n = min(sel.n_held, k);

@@ -60,12 +60,7 @@ __device__ __forceinline__ void split_select(
     __shared__ int wave_held[kSplitWaves];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    int64_t in_row = row;
-    if (seq_off) {
-        const int d0 = seq_off[row], g = max(seq_off[row + 1] - d0, 0);
-        in_row = (int64_t)d0 + row + min(max(n_accept[row], 0), g);
-    }
-    const RowView rv = row_view<BF16>(logits, ld, in_row, V);
+    const RowView rv = record_source<BF16>(row, logits, ld, V, seq_off, n_accept);
     const int nq = (rv.L + N - 1) / N;
     const int n_blocks = (nq + kWave - 1) / kWave;
     const float c = 1.4426950408889634f * inv_T;
@@ -329,9 +324,9 @@ __device__ __attribute__((noinline)) void split_row_again(
     int64_t row, const void* logits, int64_t ld, int V, float inv_T, int k, float top_p,
     int32_t* idx, float* prob, int32_t* count, float* mass, float* lse, const int32_t* seq_off, const int32_t* n_accept, int rank_opt)
 {
-    compress_row<BF16, false>(uniform(row), uniform(logits), uniform(ld), uniform(V), uniform(inv_T), uniform(k), uniform(top_p),
-                              uniform(idx), uniform(prob), uniform(count), uniform(mass), uniform(lse), uniform(seq_off),
-                              uniform(n_accept), uniform(rank_opt));
+    row = uniform(row); V = uniform(V);
+    compress_row<BF16, false>(row, record_source<BF16>(row, uniform(logits), uniform(ld), V, uniform(seq_off), uniform(n_accept)), V, uniform(inv_T),
+                              uniform(k), uniform(top_p), uniform(idx), uniform(prob), uniform(count), uniform(mass), uniform(lse), uniform(rank_opt));
 }
 
 template <bool BF16>
