@@ -224,9 +224,14 @@ __device__ __forceinline__ void split_select(
     // ---- the list: the elements above the threshold, in any order.  A lane marks its elements in a word, a scan over the
     //      counts gives it its slots, and it takes the few it marked from the image.
     marks = 0;                                   // bit 31 - e: element e
-    // (the sign of tau - v, shifted in; -inf below a threshold of -inf gives the positive NaN)
+    // (the sign of tau - v, shifted in; below a threshold of -inf a masked entry's difference is a NaN, of either sign, which the minimum drops)
+    if (tau > kNegInf) {                         // (uniform)
 #pragma unroll
-    for (int e = 0; e < E; ++e) marks = __builtin_amdgcn_alignbit(marks, __float_as_uint(tau - v[e]), 31);
+        for (int e = 0; e < E; ++e) marks = __builtin_amdgcn_alignbit(marks, __float_as_uint(tau - v[e]), 31);
+    } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) marks = __builtin_amdgcn_alignbit(marks, __float_as_uint(fminf(tau - v[e], 0.f)), 31);
+    }
     const int mine = __popc(marks);
     const int incl = wave_scan_incl(mine);
     if (lane == kWave - 1) wave_held[wave] = incl;

@@ -90,6 +90,47 @@ def test_patterns_match_the_oracle(gpu, pu, ps, pattern, dtype, k, top_p):
     pu.compare_compress(g, oracle.compress(np.ascontiguousarray(stored[:, shift:]), V, 1.1, k, top_p), top_p)
 
 
+def _share_heads(ps, z, V, k):
+    """A compression in scratch of its own: the record, and per row and workgroup its threshold, the length of its list (what the
+    selecting workgroups leave first in the scratch: 32 bytes each, third to last words unread here) and how many entries above -inf its
+    share has (every P-th kilobyte of the row)."""
+    dt, R = ps._dtype_code(z), z.shape[0]
+    out = ps.alloc_compressed(R, k, z.device)
+    ws = torch.zeros(ps.workspace_bytes(ps.CALL_COMPRESS, dt, R, V, k), dtype=torch.uint8, device=z.device)
+    p = lambda t: t.data_ptr()
+    ps._check(ps.lib.picospec_compress(p(z), dt, z.stride(0), R, V, 1.0, k, 0.0, p(out.idx), p(out.prob), p(out.count), p(out.mass), p(out.lse),
+                                       p(ws), ws.numel(), torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    esz = z.element_size()
+    per_block, blocks = 1024 // esz, ((V * esz + 15) // 16 + 1 + 63) // 64
+    P = -(-blocks // (8192 // per_block))
+    head = ws[:R * P * 32].view(R, P, 32)
+    share = torch.zeros((R, blocks * per_block), dtype=torch.bool, device=z.device)
+    share[:, :V] = z[:, :V] > float("-inf")
+    share = share.view(R, blocks, per_block).sum(2)
+    held = torch.stack([share[:, q::P].sum(1) for q in range(P)], 1)
+    return out, head[:, :, 4:8].contiguous().view(torch.float32)[:, :, 0], head[:, :, 12:16].contiguous().view(torch.int32)[:, :, 0], held
+
+
+@pytest.mark.parametrize("k", [10, 512, 1100])           # (ranks that are looked for among the lanes' largest values, and one that is not)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_a_share_with_fewer_entries_than_its_rank_lists_those_alone(gpu, pu, ps, dtype, k):
+    """Vocabulary masks: a list of a share's entries above -inf holds none of the masked ones, and the row keeps its lists."""
+    _announce("few entries in a share", dtype, k)
+    V, rng = 128256, np.random.default_rng(k)
+    z = np.full((4, V), -np.inf, np.float32)
+    for r, n in enumerate((200, 60, 3000, 2)):
+        at = rng.permutation(V)[:n]
+        z[r, at] = rng.standard_normal(n)
+    z[3, 100:103] = (1.0, 2.0, 3.0)              # (all in one share: the others have nothing)
+    stored = z if dtype == torch.float32 else W.to_bf16_bits(z)
+    out, tau, count, held = _share_heads(ps, pu.to_device(stored, gpu), V, k)
+    pu.compare_compress(out, oracle.compress(stored, V, 1.0, k), 0.0)
+    open_ = tau == float("-inf")
+    assert open_[[0, 1, 3]].any(1).all() and torch.equal(count[open_].long(), held[open_].long())
+    assert bool((count <= held).all())
+
+
 def _grid_rows(rng, pattern, R, V):
     """Rows whose k-th value is shared by more entries than there are candidate slots."""
     z = rng.standard_normal((R, V)) * 3
