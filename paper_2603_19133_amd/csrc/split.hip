@@ -148,10 +148,15 @@ __device__ __forceinline__ void split_select(
     // threshold has some -256 ln(1 - n / 256) elements above it, as the host chose n (split_plan); a list that comes out too long for
     // its slots, a crowded pivot bin or too few lanes with a value (masks, values that trend within a lane) fall to the elements.
     // 64 fp32 rows of 151,936, k = 1024: 12.2 -> 10.5 us, 32 bf16 of 128,256, k = 256: 7.5 -> 6.7, one, k = 10: 5.1 -> 4.8.
-    for (int by_lanes = lanes;; by_lanes = 0) {
+    // A share with no two values to tell apart (narrow: whose lanes have none) lists everything above -inf, as a share with fewer entries
+    // than the rank does: a vocabulary mask may leave it one.  If that is too much, what lies below the one value goes.  (40 rows of 128,256
+    // with 13 entries above -inf, k = 512, us: cut at their one value, which sends the row to split_row_again, fp32 39.6, bf16 34.2; so 15.3 and 14.8.)
+    const bool one = finite && !(hi > lo);
+    bool whole = one;
+    for (int by_lanes = lanes;; by_lanes = 0, whole = false) {
     bool again = false;
-    if (finite && !(hi > lo)) {
-        if (hi == lo) tau = float_below(lo);     // one value
+    if (one) {
+        if (!whole && hi == lo) tau = float_below(lo);
     } else if (finite) {
         int need = by_lanes ? by_lanes : rank;
         bool open = true;                        // the threshold is not fine enough yet
@@ -224,14 +229,12 @@ __device__ __forceinline__ void split_select(
     // ---- the list: the elements above the threshold, in any order.  A lane marks its elements in a word, a scan over the
     //      counts gives it its slots, and it takes the few it marked from the image.
     marks = 0;                                   // bit 31 - e: element e
-    // (the sign of tau - v, shifted in; below a threshold of -inf a masked entry's difference is a NaN, of either sign, which the minimum drops)
-    if (tau > kNegInf) {                         // (uniform)
+    // (v > tau is v >= the next larger float: the sign of v - that, shifted in and turned over.  It is finite also for a tau of -inf, whose own
+    //  difference to a masked entry is a NaN)
+    const float least = __uint_as_float(__float_as_uint(tau) + (tau < 0.f ? -1u : 1u));
 #pragma unroll
-        for (int e = 0; e < E; ++e) marks = __builtin_amdgcn_alignbit(marks, __float_as_uint(tau - v[e]), 31);
-    } else {
-#pragma unroll
-        for (int e = 0; e < E; ++e) marks = __builtin_amdgcn_alignbit(marks, __float_as_uint(fminf(tau - v[e], 0.f)), 31);
-    }
+    for (int e = 0; e < E; ++e) marks = __builtin_amdgcn_alignbit(marks, __float_as_uint(v[e] - least), 31);
+    marks = ~marks;
     const int mine = __popc(marks);
     const int incl = wave_scan_incl(mine);
     if (lane == kWave - 1) wave_held[wave] = incl;
@@ -241,7 +244,7 @@ __device__ __forceinline__ void split_select(
     held = 0;
 #pragma unroll
     for (int w = 0; w < kSplitWaves; ++w) { at += w < wave ? wave_held[w] : 0; held += wave_held[w]; }
-    if (!by_lanes || (!again && held <= cap)) break;
+    if (!(by_lanes || whole) || (!again && held <= cap)) break;
     // the elements themselves, then (the histogram is cleared; every wave has read the counts)
     tau = kNegInf;
     *reinterpret_cast<uint2*>(&hist[2 * tid]) = make_uint2(0u, 0u);
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_round_kernel(
 
 // A row whose lists do not hold its answer, from the start.  A function that is called: inlined, what that code keeps alive
 // costs every row 0.8 to 1.1 us (one row of 128,256 bf16, k = 10: 6.0 -> 5.1; 64 of 151,936 fp32, k = 1024: 9.5 -> 8.4).
-// (It is the fast kernels' code, which calls the careful pass in turn: a call, us, of 40 rows of 128,256, k = 512, that all come here, 13 entries above -inf in
+// (It is the fast kernels' code, which calls the careful pass in turn: a call, us, of 40 rows of 128,256, k = 512, that all came here, 13 entries above -inf in
 // each: fp32 49.2 with both passes in the one function, 42.6 so, bf16 40.2 and 37.5; inlined, at every other row's cost, 37 and 36 to 38.)
 template <bool BF16>
 __device__ __attribute__((noinline)) void split_row_again(

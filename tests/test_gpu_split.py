@@ -131,6 +131,27 @@ def test_a_share_with_fewer_entries_than_its_rank_lists_those_alone(gpu, pu, ps,
     assert bool((count <= held).all())
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("k", [10, 40, 1100])
+def test_a_share_of_one_value_lists_what_it_has(gpu, pu, ps, dtype, k):
+    """One entry above -inf in every share, equal ones, and one value in all lanes but for smaller ones beside it: the lists hold the
+    whole answer and say so; a share of nothing but one value is cut there."""
+    _announce("one value in a share", dtype, k)
+    V, rng = 128256, np.random.default_rng(k)
+    block = 256 if dtype == torch.float32 else 512
+    z = np.full((4, V), -np.inf, np.float32)
+    z[0, np.arange(7, 16 * block, block)] = rng.standard_normal(16)               # (16 workgroups: the first block of each)
+    z[1, np.arange(3, V - 1, 997)] = 0.5
+    z[2, np.arange(8, 16 * block, block)] = 2.0
+    z[2, np.arange(9, 16 * block, block)] = 1.0  # (the same lane's second entry)
+    z[3] = -1.5
+    stored = z if dtype == torch.float32 else W.to_bf16_bits(z)
+    out, tau, count, held = _share_heads(ps, pu.to_device(stored, gpu), V, k)
+    pu.compare_compress(out, oracle.compress(stored, V, 1.0, k), 0.0)
+    assert bool((tau[:3] == float("-inf")).all()) and torch.equal(count[:3].long(), held[:3].long())
+    assert bool((tau[3] > -2.0).all()) and bool((tau[3] < -1.5).all())
+
+
 def _grid_rows(rng, pattern, R, V):
     """Rows whose k-th value is shared by more entries than there are candidate slots."""
     z = rng.standard_normal((R, V)) * 3
