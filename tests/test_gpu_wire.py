@@ -192,6 +192,26 @@ def test_uplink_pack_and_unpack(gpu, ps, pu, fmt, B, gmax):
         assert int(st.item()) == o.status != 0, name
 
 
+@pytest.mark.parametrize("B,g,fmt", [(32, 6, 0), (64, 4, 1), (256, 1, 2), (257, 1, 0), (1, 1024, 1), (20000, 2, 0)])
+def test_room_for_many_more_positions_than_the_message_has(gpu, ps, pu, B, g, fmt):
+    """Workgroups whose positions lie behind the message's end, from the first one behind its last token on, write nothing."""
+    _announce("uplink with room", B, g, fmt)
+    seq_off = (np.arange(B + 1) * g).astype(np.int32)
+    N, rng = B * g, np.random.default_rng(B + fmt)
+    tok = rng.integers(0, 152064, N).astype(np.int32)
+    want, n = oracle.pack_uplink(seq_off, tok, rng.random(N).astype(np.float32), fmt)
+    wire = torch.from_numpy(want).to(gpu)
+    for n_max in (N + 255, N + 256, 1 << 20):
+        o = oracle.unpack_uplink(want, B, n_max)
+        so, t, q, st = (torch.full((m,), -7, dtype=dt, device=gpu) for m, dt in ((B + 1, torch.int32), (n_max, torch.int32), (n_max, torch.float32), (1, torch.int32)))
+        ps._check(ps.lib.picospec_unpack_uplink(wire.data_ptr(), n, B, n_max, so.data_ptr(), t.data_ptr(), q.data_ptr(), st.data_ptr(),
+                                                torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+        assert int(st.item()) == o.status == 0 and np.array_equal(pu.n(so), o.seq_off)
+        assert np.array_equal(pu.n(t)[:N], o.draft_tok[:N]) and np.array_equal(pu.n(q)[:N].astype(np.float64), o.q_scalar[:N])
+        assert bool((t[N:] == -7).all()) and bool((q[N:] == -7).all())
+
+
 @pytest.mark.parametrize("cfg,k", [("cfg1", 64), ("cfg3", 1024)])
 def test_round_over_the_wire(gpu, ps, pu, cfg, k):
     """One round as the paper ships it, both messages through the library: the edge's scalars go up, the
