@@ -7,6 +7,9 @@ Calls of few rows get scratch in which the library spreads every row over many w
 as with one workgroup per row, sums (probabilities, masses, statistics) agree to rounding, so their bits depend on the number of
 rows in the call.  Scratch comes from torch's allocator on the current stream: capture such calls with ``torch.cuda.graph``, whose
 pool keeps it for the replays.
+Outputs that a call allocates by itself (the wire messages', sample_draft's, row_stats') share one allocation as far as they are
+small (64 KB each): one that is kept keeps the other small ones of its call, torch.save writes them with it, and an in-place resize_
+beyond its size runs into them; clone() it for any of these.  Larger outputs stand alone.
 There is no fallback: if the library has not been built (``python -m paper_2603_19133_amd.build``) importing this module raises.
 """
 from __future__ import annotations

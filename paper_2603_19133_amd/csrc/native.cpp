@@ -281,37 +281,45 @@ PyObject* n_scratch(PyObject*, PyObject* const* v, Py_ssize_t n) {
 }
 
 // empty(like, codes, size, ...) -> one tensor per letter of `codes` (i int32, l int64, f float32, b uint8) on the device of
-// `like`; a size is an int (1-d) or a tuple of two.  The outputs of one call share one allocation, each from a 512-byte boundary of it on, as
-// slices of a tensor do (the whole of it lives as long as any of them; record_stream on one covers all): an allocation costs 0.85 us,
-// a slice 0.15 (the eight outputs of an unpacked downlink message: 6.8 -> 2.1 us).
+// `like`; a size is an int (1-d) or a tuple of two.  Outputs of up to kShared bytes share one allocation, each from a 512-byte boundary of it
+// on, as slices of a tensor do: an allocation costs 0.45 to 0.85 us, a slice 0.15 (the eight outputs of an unpacked downlink message of 32
+// records of 256: 2.1 us, each from torch.empty 6.8).  All of it lives as long as any of them, so larger ones, next to which an allocation is cheap to make and
+// dear to keep, have their own.
 PyObject* n_empty(PyObject*, PyObject* const* v, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     constexpr Py_ssize_t kMost = 16;
+    constexpr int64_t kShared = 64 * 1024;
     Py_ssize_t len = 0;
     const char* codes = n >= 2 && THPVariable_Check(v[0]) ? PyUnicode_AsUTF8AndSize(v[1], &len) : nullptr;
     if (!codes || n != len + 2 || len > kMost) { if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "empty(tensor, codes, size, ...)"); return nullptr; }
-    int64_t dims[kMost][2], at_byte[kMost + 1];
+    int64_t dims[kMost][2], bytes[kMost], shared = 0;
     int nd[kMost];
-    at_byte[0] = 0;
     for (Py_ssize_t i = 0; i < len; ++i) {
         PyObject* s = v[2 + i];
         nd[i] = PyTuple_Check(s) && PyTuple_GET_SIZE(s) == 2 ? 2 : 1;
         dims[i][0] = PyLong_AsLongLong(nd[i] == 2 ? PyTuple_GET_ITEM(s, 0) : s);
         dims[i][1] = nd[i] == 2 ? PyLong_AsLongLong(PyTuple_GET_ITEM(s, 1)) : 1;
         if (PyErr_Occurred()) return nullptr;
-        int64_t bytes;
-        if (dims[i][0] < 0 || dims[i][1] < 0 || __builtin_mul_overflow(dims[i][0], dims[i][1], &bytes) || bytes > (int64_t(1) << 56)) { PyErr_SetString(PyExc_RuntimeError, "empty: a size is out of range"); return nullptr; }
-        bytes *= codes[i] == 'l' ? 8 : codes[i] == 'b' ? 1 : 4;
-        at_byte[i + 1] = at_byte[i] + (bytes + 511) / 512 * 512;
+        if (dims[i][0] < 0 || dims[i][1] < 0 || __builtin_mul_overflow(dims[i][0], dims[i][1], &bytes[i]) || bytes[i] > (int64_t(1) << 56)) { PyErr_SetString(PyExc_RuntimeError, "empty: a size is out of range"); return nullptr; }
+        bytes[i] *= codes[i] == 'l' ? 8 : codes[i] == 'b' ? 1 : 4;
+        if (bytes[i] <= kShared) shared += (bytes[i] + 511) / 512 * 512;
     }
     THPObjectPtr out(PyTuple_New(len));
     if (!out) return nullptr;
-    const at::Tensor block = at::empty({at_byte[len]}, like(v[0], at::kByte));
+    at::Tensor block;
+    int64_t at_byte = 0;
     for (Py_ssize_t i = 0; i < len; ++i) {
         const at::ScalarType type = codes[i] == 'i' ? at::kInt : codes[i] == 'l' ? at::kLong : codes[i] == 'b' ? at::kByte : at::kFloat;
-        at::Tensor piece = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(block.storage()), block.key_set(), c10::scalarTypeToTypeMeta(type));
-        piece.unsafeGetTensorImpl()->set_storage_offset(at_byte[i] / (int64_t)c10::elementSize(type));
-        piece.unsafeGetTensorImpl()->set_sizes_contiguous(at::IntArrayRef(dims[i], nd[i]));
+        at::Tensor piece;
+        if (bytes[i] > kShared) {
+            piece = at::empty(at::IntArrayRef(dims[i], nd[i]), like(v[0], type));
+        } else {
+            if (!block.defined()) block = at::empty({shared}, like(v[0], at::kByte));
+            piece = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(block.storage()), block.key_set(), c10::scalarTypeToTypeMeta(type));
+            piece.unsafeGetTensorImpl()->set_storage_offset(at_byte / (int64_t)c10::elementSize(type));
+            piece.unsafeGetTensorImpl()->set_sizes_contiguous(at::IntArrayRef(dims[i], nd[i]));
+            at_byte += (bytes[i] + 511) / 512 * 512;
+        }
         PyObject* t = THPVariable_Wrap(piece);
         if (!t) return nullptr;
         PyTuple_SET_ITEM(out.get(), i, t);

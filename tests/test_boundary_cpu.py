@@ -312,6 +312,19 @@ def test_outputs_of_one_allocation_do_not_meet(B):
             B._nat.empty(like, "f", bad)
 
 
+def test_a_small_output_keeps_no_large_one(B):
+    """Outputs of up to 64 KB share an allocation; what is larger lives, and is resized and saved, on its own."""
+    import torch
+    out = B._nat.empty(torch.zeros(1), "iififib", 7, (512, 2048), (512, 2048), 16384, 16385, 1, 65537)
+    own = [t.untyped_storage().nbytes() == t.numel() * t.element_size() and t.storage_offset() == 0 for t in out]
+    assert own == [False, True, True, False, True, False, True]
+    together = {t.untyped_storage().data_ptr() for t, o in zip(out, own) if not o}
+    assert len(together) == 1 and out[0].untyped_storage().nbytes() == 512 + 65536 + 512
+    for i, t in enumerate(out):
+        t.fill_(i + 1)
+    assert all(bool((t == i + 1).all()) for i, t in enumerate(out))
+
+
 def test_streaming_loads_stay_inside_the_row(B):
     """The row loads of the compress and residual kernels, look-ahead included, never address a byte behind the aligned
     16-byte block that holds the row's last byte, whatever the row length and its alignment: the library's own

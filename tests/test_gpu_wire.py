@@ -212,6 +212,25 @@ def test_room_for_many_more_positions_than_the_message_has(gpu, ps, pu, B, g, fm
         assert bool((t[N:] == -7).all()) and bool((q[N:] == -7).all())
 
 
+def test_a_kept_status_word_keeps_no_records(gpu, ps):
+    """A program that keeps an unpacked message's status keeps at most the small outputs with it, from the allocator's own memory
+    (record_stream covers it)."""
+    _announce("a kept status word")
+    wire = torch.zeros(4096, dtype=torch.uint8, device=gpu)
+    before = torch.cuda.memory_allocated()
+    out = ps.unpack_downlink(wire, 4096, 512, 2048)
+    assert torch.cuda.memory_allocated() - before >= 2 * 512 * 2048 * 4
+    kept = out.status
+    del out
+    assert torch.cuda.memory_allocated() - before <= 8 * 2048
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        kept.record_stream(side)
+        kept.fill_(3)
+    torch.cuda.synchronize()
+    assert int(kept.item()) == 3
+
+
 @pytest.mark.parametrize("cfg,k", [("cfg1", 64), ("cfg3", 1024)])
 def test_round_over_the_wire(gpu, ps, pu, cfg, k):
     """One round as the paper ships it, both messages through the library: the edge's scalars go up, the
