@@ -273,18 +273,21 @@ int picospec_resample_sparse(const void* draft_logits, int dtype, int64_t ld, in
  * The drafted tokens must be known beforehand (in a deployment they come from picospec_sample_draft on an
  * earlier compress of the same rows; the records written here are then the same ones).
  * Acceptance and residual draw of a sequence run in one workgroup (one launch, the rejected position never
- * leaves it).  Rounds of up to 512 rows (draft + target) also stream the draft and the target rows in one
- * launch (two launches in all instead of four): such rounds are bound by the launches' serial parts, not by
- * bandwidth.  Larger rounds keep the two streaming launches of the separate calls (three in all).
- * The records are the same bit for bit in both schedules; the target statistics of the two-launch schedule are
- * summed in another order, so what depends on them agrees with the separate calls to rounding.
- * workspace (optional): picospec_workspace_bytes(PICOSPEC_CALL_ROUND, dtype, n_draft + B, V, 0) bytes; either schedule then
- * leaves the target rows' segment table there (in a layout of its own: the table of one call of picospec_round serves that
- * call only) and draws from it without a second pass over the target row.  The size for the record length k instead of 0
- * holds scratch as well (few rows only; the same size where there are more): the draft rows, and the target rows with
- * them, are then spread over many workgroups where that is faster (picospec_scratch_bytes says where, and how many bytes the
- * call needs by its own n_draft), three launches that each take a fraction of the two.  Records then hold the
- * same ids, and probabilities agree to rounding, as with picospec_compress given a workspace.
+ * leaves it), behind one launch that streams the draft and the target rows at once, or two:
+ *   - without a workspace: one for rounds of up to 512 rows (draft + target), two for larger ones;
+ *   - workspace of picospec_workspace_bytes(PICOSPEC_CALL_ROUND, dtype, n_draft + B, V, 0) bytes: the target rows' segment table
+ *     is left there (the table of one call of picospec_round serves that call only) and the draw works from it without a second
+ *     pass over the target row.  One launch for rounds of up to 512 rows and for larger ones of up to 4608 rows and 1.8 GB of
+ *     logits (fp32), or up to 2047 target rows of at least 32,768 with k <= 2048 (bf16); two beyond, and for records so long, or rows
+ *     so short, that the compression takes its rows the careful way;
+ *   - workspace of the size for the record length k instead of 0, which holds scratch as well (few rows only; the same size where
+ *     there are more): the draft rows, and the target rows with them, are spread over many workgroups where that is faster, two
+ *     small launches in front of the decision.  picospec_scratch_bytes says where, and how many bytes the call needs by its own
+ *     n_draft (0: the round has no use for more than the table).
+ * Records whose rows are not spread are those of picospec_compress without a workspace, bit for bit; spread ones hold the same
+ * ids and probabilities that agree to rounding, bit for bit those of picospec_compress with one.  The target statistics of
+ * rounds of more than 512 rows are those of picospec_verify bit for bit (with a workspace where the round has one); those of smaller
+ * rounds are summed in another order, so what depends on them agrees to rounding.
  */
 int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, int64_t ld_draft, int64_t ld_tgt,
                    int32_t V, float temperature, int32_t B, int32_t n_draft, const int32_t* seq_off,

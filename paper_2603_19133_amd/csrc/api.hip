@@ -205,11 +205,11 @@ int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, 
     // the workgroup), and the two streaming kernels as well where the target rows get a table (launch_round_wide); without
     // one, rounds that leave most of the chip idle do so too, and those that fill it take each kernel in its own launch shape.
     const bool small_round = rows + n_draft <= kRoundSmallRows;     // (bound by its launches: two of them)
-    // (a workspace that holds the split kernels' scratch behind the segment table: few draft rows are spread over many
-    //  workgroups, and with few target rows their statistics as well)
+    // (a workspace that holds the split kernels' scratch behind the segment table: few draft rows are spread over many workgroups
+    //  where that is faster, and with few target rows their statistics as well)
     const size_t table_bytes = (round_seg_table_bytes(dtype, rows, V) + 15) / 16 * 16;
     const bool wide = workspace && round_wide_serves(dtype, n_draft, rows, V, k);
-    const bool split_draft = n_draft > 0 && workspace && !(wide && round_wide_first(dtype, n_draft)) && workspace_bytes > table_bytes && round_split_serves(dtype, n_draft, rows, V, k) &&
+    const bool split_draft = n_draft > 0 && workspace && workspace_bytes > table_bytes && round_split_serves(dtype, n_draft, rows, V, k) &&
                              split_fits(dtype, n_draft, V, k, (char*)workspace + table_bytes, workspace_bytes - table_bytes);
     const bool split_stats = split_draft && split_stats_serves(rows, V);
     if (split_draft) {

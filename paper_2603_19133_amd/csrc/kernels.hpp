@@ -44,10 +44,12 @@ __host__ __device__ inline int optimistic_rank(int k, int V, int m, int cap, flo
 // parts = 0: the call is not split.  Lines of the rule:
 //   * rows (split_max_rows): with one workgroup per row a call takes the time of one row as long as every row has a CU of its
 //     own; split, the first launch's time grows with the rows from about 40 rows on, and the second one's with k.  Measured,
-//     unsplit / split, us, fp32 (bf16): k = 256: 192 rows of 151,936 30.4 / 30.5 (29.6 / 26.0), 100,000 24.4 / 24.7 (24.7 / 21.7),
-//     16,384 14.9 / 14.6 (14.7 / 14.0); k = 1024: 128 rows of 151,936 30.6 / 27.0 (30.6 / 24.0), 20,000 16.2 / 15.8 (16.7 / 15.7); k = 4096: 80
-//     rows of 151,936 36.4 / 32.9 (37.2 / 31.6), 64,000 27.3 / 27.4 (27.6 / 25.8); of 608 points one (192 x 100,000) is slower by more than 1 %.
-//   * V: two workgroups' worth, and eight times k (V = 20,000, k = 4096, 48 rows: 23.2 / 24.1).
+//     unsplit / split, us, fp32 (bf16): k = 256: 192 rows of 151,936 28.8 / 26.8 (23.6 / 23.7), 100,000 23.5 / 21.7 (19.6 / 19.9),
+//     16,384 14.0 / 13.8 (13.5 / 13.4); k = 1024: 128 rows of 151,936 29.4 / 24.4 (25.4 / 22.2), 100,000 24.4 / 21.9 (20.8 / 21.2), 20,000 15.5 / 15.3
+//     (15.8 / 15.5), 16,384 15.0 / 15.4 (15.1 / 15.6); k = 4096: 80 rows of 151,936 35.0 / 31.0 (34.6 / 31.4), 50,000 25.9 / 26.2 (27.9 / 26.4): of 574
+//     points on this side of the line seven are slower by more than 1 %, at V = 16,384 by 3 %.  More rows would gain on fp32 (320 of 151,936, k = 256: 50.4 /
+//     39.8; 160 of 128,256, k = 512: 26.3 / 23.3) and are not taken so far; bf16 rows would not (31.5 / 33.0, 22.4 / 21.6).
+//   * V: two workgroups' worth, and eight times k.
 //   * the margin of the rank is optimistic_rank's (4.5 standard deviations of the share of the k largest that falls to one
 //     workgroup); its lists together must fit the candidate buffer of the finishing kernel with room to spare.
 //   * a list holds the rank, a crowded pivot bin and some slack.
@@ -160,11 +162,6 @@ inline StatsShape round_stats_shape(int dtype, int V) {
 // launch_round_stream's work for rounds with a segment table, in the layout `sh`, where the compression's first pass applies
 // (round_wide_serves)
 bool round_wide_serves(int dtype, int64_t n_draft, int64_t n_target, int V, int k);
-// ... and goes before the spread rows (round_split_serves): bf16 rounds from 160 drafts on.  us, drafts spread / one launch for both
-// streams: 180 drafts and 240 target rows of 100,000, k = 64: 42.4 / 33.0; 180 and 200 of 64,000, k = 256: 33.1 / 29.8, of 152,064, k = 64:
-// 40.8 / 38.9; 192 and 224, k = 256: 44.2 / 39.5; with fewer drafts 128 and 144 of 152,064, k = 1024: 42.3 / 42.3, 100 and 200, k = 64: 34.6 / 37.3, 96
-// and 112, k = 256: 33.2 / 38.2.  (fp32, two workgroups per CU: 180 and 200: 53.8 / 54.5, 192 and 224: 59.0 / 55.7.)
-inline bool round_wide_first(int dtype, int64_t n_draft) { return dtype == 1 && n_draft >= 160; }
 hipError_t launch_round_wide(const void* draft_logits, int dtype, int64_t ld_d, int n_draft, int V, float temperature,
                              int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass, float* lse,
                              const void* tgt_logits, int64_t ld_t, int n_target,
@@ -202,22 +199,28 @@ inline bool row_stats_split_serves(int dtype, int64_t rows, int V) {
     const int64_t row_bytes = (int64_t)V * (dtype == 1 ? 2 : 4);
     return split_stats_serves(rows, V) && row_bytes >= 250000 && rows <= (dtype == 1 ? 160 : row_bytes >= 500000 ? 128 : 64);
 }
-// Whether a round has a use for scratch that spreads its draft rows: where picospec_compress would (the records of a round are then
-// those of a call of its own, bit for bit), unless the launch that otherwise streams the draft and the target rows at once, and
-// hides most of the drafts' serial phases, is faster (see round_wide_first too).  us, round_stream_kernel's launch for both / spread:
-//   * rounds beyond kRoundSmallRows: always (64 + 450 sequences of 16,384 fp32,
-//     k = 64: 34.6 / 31.9; 16 + 500 of 151,936, k = 4096: 117.6 / 108.5);
-//   * smaller rounds whose statistics are spread with them: up to 48 drafts for the longest records (48 and 48 of 151,936 fp32, k =
-//     4096: 52.6 / 53.1, 64 and 64: 53.6 / 58.0, bf16 of 64,000 80 and 80: 41.3 / 45.7), else always (192 and 32, k = 256: 64.0 / 58.3;
-//     80 and 20, k = 2048: 44.8 / 44.8, k = 1024: 40.5 / 40.0; the other way by up to 8 % around 200 rows of 64,000 in all);
-//   * with more target rows than that four launches stand against two (128 + 128 of 151,936 fp32, k = 64: 53.6 / 58.6; 20 + 300, k =
-//     4096: 65.5 / 87.9), but for bf16 rows of 192 KB and more, bound by the vector ALUs of their CUs, where the one launch no
-//     longer has a CU for every row (160 + 80 of 100,000, k = 64: 41.7 / 40.9, of 151,936: 52.4 / 47.3, 192 + 64: 53.6 / 50.5).
+// Whether a round spreads its draft rows in scratch behind its table (picospec_round; picospec_scratch_bytes asks for that scratch by the same
+// rule, and a round that does not spread them uses the table alone).  us, one launch for both streams (launch_round_wide) / drafts spread, of
+// 2380 points (4 to 192 drafts, 1 to 400 sequences, V = 16,384 to 151,936, k = 10 to 4096) one in thirty-six on the wrong side by more than 2 %, none by more
+// than 7 %:
+//   * rounds whose statistics are not spread with the drafts' rows (more than kSplitStatsRows target rows) take three launches behind each
+//     other and never do: 128 drafts and 528 target rows, k = 256, of 64,000: fp32 43.7 / 51.9, bf16 29.9 / 42.0, of 151,936: 75.5 / 91.1, 49.2 /
+//     69.2; 96 and 296 of 151,936, k = 1024: 51.1 / 68.8, 35.8 / 52.7; 16 and 416 of 64,000: 33.7 / 39.5, 27.5 / 33.8.  But where the one launch does not
+//     serve (bf16, k > 2048 or V < 32,768), rounds beyond kRoundSmallRows have three launches either way: 37.2 / 34.8 (128 and 528 of 32,000 bf16, k = 256);
+//   * drafts, fp32: k = 256, of 151,936: 128 and 192: 47.7 / 45.6, 160 and 192: 49.4 / 49.3, 192 and 224: 50.5 / 55.5; k = 1024, of 64,000: 96 and 128: 31.1 /
+//     29.1; short rows: 64 and 80 of 16,384: 25.7 / 25.2, 96 and 112: 25.8 / 27.4.  bf16, three workgroups per CU in the one launch: k = 256, of 151,936: 96 and 160:
+//     33.1 / 32.3, 128 and 192: 32.8 / 36.1; k = 1024, of 64,000: 64 and 80: 27.9 / 26.3, 96 and 128: 28.2 / 29.1.  k = 4096: 48 and 64 of 151,936: 54.2 /
+//     49.4, 54.9 / 49.7;
+//   * drafts per sequence: with the statistics spread a sequence's decision forms those of all its rows.  One sequence of 96 drafts of
+//     64,000, k = 256: 36.6 / 39.5, 34.5 / 40.7; of 64: 33.0 / 31.8, 31.2 / 33.8; four of 32 of 16,384: 25.7 / 26.1, 25.0 / 27.3.
 inline bool round_split_serves(int dtype, int64_t n_draft, int64_t rows, int V, int k) {
     if (split_plan(dtype, n_draft, V, k).parts == 0) return false;
-    if (n_draft + rows > kRoundSmallRows) return true;
-    if (split_stats_serves(rows, V)) return k <= 2048 || n_draft <= 48;
-    return dtype == 1 && V >= 96 * 1024 && n_draft >= 160 && rows <= 256;
+    const bool wide = round_wide_serves(dtype, n_draft, rows, V, k), short_rows = V < 24000;
+    if (!wide && n_draft + rows > kRoundSmallRows) return true;
+    if (!split_stats_serves(rows, V) || n_draft > (short_rows ? 24 : 48) * (rows - n_draft)) return false;
+    if (k > 2048) return n_draft <= 48;
+    if (dtype == 1 && wide) return n_draft <= 64 || (n_draft <= (k <= 256 ? 96 : 80) && rows <= 160);
+    return n_draft <= (k <= 256 ? (wide ? 160 : 128) : (short_rows ? 64 : 128));
 }
 // Where a draw that was given no table makes one of the rows it draws from (one workgroup per row passes over its row twice, and
 // is bound by the vector ALUs of one CU): 64 sequences x 33 001 fp32, k = 64: 17.2 -> 11.3 us; 64 x 151 936, k = 64: fp32 29.5 ->

@@ -704,8 +704,42 @@ def test_a_round_takes_its_scratch_from_a_workspace_that_holds_it(gpu, ps):
             assert not torch.is_tensor(x) or torch.equal(x, getattr(b, name)), name
 
 
-@pytest.mark.parametrize("dtype,N,B,V,k", [(torch.bfloat16, 160, 80, 98304, 40),       # drafts spread, statistics not, in a small round
-                                           (torch.bfloat16, 160, 80, 98303, 40),       # ... and the rule's other side
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_a_round_that_spreads_nothing_takes_its_table_from_a_workspace_that_holds_it(gpu, ps, dtype):
+    """What the call asks for is what it uses: a workspace that holds the table will do, and nothing is allocated beside it."""
+    _announce("round in the table alone", dtype)
+    V, k, B, N, T = 40000, 64, 4, 192, 0.8
+    assert ps.scratch_bytes(ps.CALL_ROUND, ps.F32 if dtype == torch.float32 else ps.BF16, N, B, V, k) == 0
+    g = torch.Generator(device=gpu)
+    g.manual_seed(5)
+    tgt = (torch.randn((N + B, V), device=gpu, generator=g) * 2).to(dtype)
+    draft = (torch.randn((N, V), device=gpu, generator=g) * 2).to(dtype)
+    off = torch.tensor([0, 48, 96, 144, 192], dtype=torch.int32, device=gpu)
+    u = torch.rand(N + B, device=gpu, generator=g)
+    ws = ps.alloc_workspace(dtype, N + B, V, gpu, ps.CALL_ROUND, k=k, n_draft=N)
+    assert ws.numel() == ps.alloc_workspace(dtype, N + B, V, gpu, ps.CALL_ROUND).numel()
+    with_scratch = torch.empty(ws.numel() + 16 + ps.workspace_bytes(ps.CALL_COMPRESS, ps._dtype_code(tgt), N, V, k), dtype=torch.uint8, device=gpu)
+    tok = draft.float().argmax(1).to(torch.int32)
+    outs = []
+    for w in (ws, with_scratch):
+        out = dict(q=ps.alloc_compressed(N, k, gpu), ver=ps.alloc_verified(B, N, gpu), res=ps.alloc_residual(B, gpu))
+        torch.cuda.synchronize()
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        ps.round(draft, tgt, V, T, off, N, tok, k, u, workspace=w, **out)
+        assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+        outs.append(out)
+    torch.cuda.synchronize()
+    for key in outs[0]:
+        for name, x in vars(outs[0][key]).items():
+            assert not torch.is_tensor(x) or torch.equal(x, getattr(outs[1][key], name)), name
+
+
+@pytest.mark.parametrize("dtype,N,B,V,k", [(torch.bfloat16, 160, 80, 98304, 40), (torch.bfloat16, 159, 80, 98303, 40),  # one launch for both streams
+                                           (torch.bfloat16, 96, 64, 32768, 256), (torch.bfloat16, 97, 63, 32768, 256),  # its line, the rows that it
+                                           (torch.bfloat16, 97, 63, 32767, 256),                                       # serves, and one beside them
+                                           (torch.bfloat16, 64, 32, 32768, 2048), (torch.bfloat16, 48, 32, 32768, 2049),
+                                           (torch.float32, 160, 64, 20000, 256), (torch.float32, 160, 65, 20000, 256),
+                                           (torch.float32, 24, 1, 16384, 64), (torch.float32, 25, 1, 16384, 64),         # drafts per sequence
                                            (torch.float32, 64, 450, 16384, 16), (torch.bfloat16, 16, 500, 16400, 300),   # large rounds
                                            (torch.float32, 112, 112, 16384, 700), (torch.float32, 113, 112, 16384, 700),  # 224 rows and more
                                            (torch.float32, 48, 4, 32768, 4096), (torch.float32, 49, 4, 32768, 4096)])

@@ -111,12 +111,22 @@ def test_a_round_spreads_its_drafts_only_where_that_was_faster(B):
     buffer."""
     f = lambda dt, n, b, V, k: B.scratch_bytes(B.CALL_ROUND, dt, n, b, V, k) > 0
     for dt in (B.F32, B.BF16):
-        for n, b, k in ((20, 300, 64), (20, 300, 4096), (64, 300, 4096), (128, 128, 1024), (128, 128, 64), (80, 80, 4096), (49, 10, 4096)):
+        for n, b, k in ((20, 300, 64), (20, 300, 4096), (64, 300, 4096), (128, 128, 1024), (128, 128, 64), (80, 80, 4096), (49, 10, 4096),
+                        (64, 450, 64), (16, 497, 64), (161, 32, 64)):
             assert not f(dt, n, b, 64000, k), (n, b, k)
-        for n, b, k in ((4, 1, 64), (64, 8, 256), (80, 20, 1024), (80, 20, 2048), (48, 3, 4096), (192, 32, 64), (64, 450, 64), (16, 500, 4096)):
+        for n, b, k in ((4, 1, 64), (64, 8, 256), (80, 20, 1024), (80, 20, 2048), (48, 3, 4096), (96, 64, 256)):
             assert f(dt, n, b, 151936, k), (n, b, k)
-    assert f(B.BF16, 160, 80, 151936, 64) and not f(B.F32, 160, 80, 151936, 64) and not f(B.BF16, 160, 80, 64000, 64)
-    assert not f(B.BF16, 0, 4, 151936, 64) and not f(B.BF16, 193, 4, 151936, 64)
+        for n, b, V in ((48, 1, 24000), (24, 1, 23999), (72, 3, 23999)):                 # drafts per sequence
+            assert f(dt, n, b, V, 64) and not f(dt, n + 1, b, V, 64), (n, b, V)
+    assert f(B.F32, 160, 64, 64000, 256) and not f(B.F32, 160, 65, 64000, 256)
+    assert f(B.F32, 128, 64, 24000, 257) and f(B.F32, 64, 64, 23999, 257) and not f(B.F32, 65, 64, 23999, 257)
+    # bf16: fewer drafts where one launch for both streams takes three workgroups per CU, up to its longest record and shortest row
+    assert f(B.BF16, 96, 64, 32768, 256) and not f(B.BF16, 97, 63, 32768, 256) and not f(B.BF16, 96, 65, 32768, 256)
+    assert f(B.BF16, 80, 80, 64000, 257) and not f(B.BF16, 81, 79, 64000, 257) and f(B.BF16, 64, 160, 64000, 257)
+    assert not f(B.BF16, 128, 64, 32768, 256) and f(B.BF16, 128, 64, 32767, 256) and not f(B.BF16, 129, 64, 32767, 256)
+    assert not f(B.BF16, 20, 480, 32768, 64) and f(B.BF16, 20, 480, 32767, 64)             # (beyond 512 rows in all)
+    assert not f(B.BF16, 20, 480, 64000, 2048) and f(B.BF16, 20, 480, 64000, 2049)
+    assert not f(B.BF16, 160, 80, 151936, 64) and not f(B.BF16, 0, 4, 151936, 64) and not f(B.BF16, 193, 4, 151936, 64)
 
 
 def test_statistics_are_spread_without_a_workspace_only_where_that_was_faster(B):
