@@ -119,6 +119,47 @@ def test_both_streams_in_one_launch_match_the_separate_calls(gpu, pu, ps, dtype,
             assert not torch.is_tensor(x) or torch.equal(x, getattr(b, name)), name
 
 
+# (up to 512 rows in all: statistics in a layout of their own, by workgroups of 512 threads; drafts first up to the number of CUs, in turns beyond)
+@pytest.mark.parametrize("dtype,N,B,V,pad,k", [(torch.bfloat16, 1, 1, 32768, 0, 1), (torch.bfloat16, 200, 100, 33001, 3, 2048), (torch.bfloat16, 256, 0, 64000, 0, 777),
+                                               (torch.float32, 1, 1, 8185, 0, 4), (torch.float32, 200, 100, 33001, 3, 4096), (torch.float32, 253, 3, 100000, 1, 64)])
+def test_both_streams_of_a_small_round_in_one_launch(gpu, pu, ps, dtype, N, B, V, pad, k):
+    """Records bit for bit those of the call of its own, statistics to rounding, with rows among them that lose the first pass; the segment sums
+    of every target row add up to its sum."""
+    B = B or N
+    _announce("both streams of a small round", dtype, N, B, V, k)
+    T, g = 0.9, torch.Generator(device=gpu)
+    g.manual_seed(N + B)
+    off_l = [N * b // B for b in range(B + 1)]
+    tgt = (torch.randn((N + B, V + pad), device=gpu, generator=g) * 2).to(dtype)[:, :V]
+    draft = (torch.randn((N, V + pad), device=gpu, generator=g) * 2).to(dtype)[:, :V]
+    draft[3::7] = 0.5
+    draft[5::7] = torch.linspace(-8, 8, V, device=gpu).to(dtype)
+    off = torch.tensor(off_l, dtype=torch.int32, device=gpu)
+    u = torch.rand(N + B, device=gpu, generator=g)
+    tok = draft.float().argmax(1).to(torch.int32)
+    ws = ps.alloc_workspace(dtype, N + B, V, gpu, ps.CALL_ROUND)
+    with pu.no_scratch():
+        q, v, r = ps.round(draft, tgt, V, T, off, N, tok, k, u, workspace=ws)
+        q0 = ps.compress(draft, V, T, k)
+        v0 = ps.verify(tgt, V, T, off, N, tok, q0, u)
+    torch.cuda.synchronize()
+    for name, x in vars(q).items():
+        assert not torch.is_tensor(x) or torch.equal(x, getattr(q0, name)), name
+    exact = torch.logsumexp(tgt.double() / T, 1)
+    assert torch.equal(v.tgt_max, v0.tgt_max) and torch.allclose(v.tgt_lse.double(), exact, rtol=0, atol=2e-6)
+    assert torch.allclose(v.tgt_sum.double(), torch.exp(exact - v.tgt_max.double() / T), rtol=2e-6)
+    magic, seg_vecs, stride, rows = ws[:16].view(torch.int32).tolist()
+    n_vec = 16 // tgt.element_size()
+    assert rows == N + B and stride >= -(-V // (seg_vecs * n_vec))
+    table = ws[16:16 + rows * stride * 8].view(torch.float32).view(rows, stride, 2)
+    first = (tgt.data_ptr() // tgt.element_size() + torch.arange(rows, device=gpu) * tgt.stride(0)) % n_vec     # elements in front of a row's first vector
+    n_seg = (first + V + seg_vecs * n_vec - 1) // (seg_vecs * n_vec)
+    used = torch.arange(stride, device=gpu)[None, :] < n_seg[:, None]
+    total = torch.where(used & (table[:, :, 0] > 0), table[:, :, 0].double() * torch.exp2(table[:, :, 1].double()), torch.zeros((), dtype=torch.float64, device=gpu)).sum(1)
+    assert torch.allclose(torch.log(total), exact, rtol=0, atol=2e-6)
+    assert torch.equal(v.flags, v0.flags)
+
+
 def test_round_call_empty_and_misuse(gpu, ps):
     _announce("picospec_round empty")
     V = 64
