@@ -250,7 +250,7 @@ def test_compress_kernels_keep_claimed_slots_in_registers():
     """The compress kernels issue LDS atomics by hand and read their results later (after an explicit wait); a
     register spilled in between would carry a stale value.  The generated code (cross-compiled here, no GPU needed)
     must therefore hold no scratch access between a hand-issued atomic and the wait that follows it, in any kernel;
-    the kernels that run the hot path (the variants of the compress kernel, the small rounds' streaming kernel) must
+    the kernels that run the hot path (the variants of the compress kernel, the rounds' two streaming kernels) must
     not touch scratch memory at all."""
     import subprocess
     import tempfile
@@ -288,8 +288,8 @@ def test_compress_kernels_keep_claimed_slots_in_registers():
             kernels[name]["scratch"] += 1
             kernels[name]["in_window"] += pending
     claiming = {k: v for k, v in kernels.items() if v["atomics"] >= 8}
-    hot = [k for k in claiming if "compress_kernel" in k or "round_stream_kernel" in k]
-    assert len(hot) == 5 and len(claiming) == 7, sorted(claiming)      # + the two instantiations of round_wide_kernel
+    hot = [k for k in claiming if "compress_kernel" in k or "round_stream_kernel" in k or "round_wide_kernel" in k]
+    assert len(hot) == 7 == len(claiming), sorted(claiming)
     assert all(v["in_window"] == 0 for v in claiming.values()), claiming
     assert all(claiming[k]["scratch"] == 0 for k in hot), {k: claiming[k] for k in hot}
 

@@ -99,6 +99,29 @@ def test_hand_issued_loads_keep_their_registers(listings, src):
     assert not broken, (len(broken), broken[:3])
 
 
+@pytest.mark.parametrize("src,claiming", [("compress.hip", 7), ("split.hip", 2)])
+def test_hand_issued_lds_results_keep_their_registers(listings, src, claiming):
+    """The slots that an asm statement claims in LDS, and the counter it reads behind them, land behind the compiler's back as well: between
+    the instruction and the wait nothing names their registers, nor moves them to scratch memory or another register."""
+    broken, kernel, flying, claims, reads = [], None, set(), {}, {}
+    for name, hand, op, ops in listings[src]:
+        if name != kernel:
+            assert not flying, kernel
+            kernel = name
+        if hand and (op.startswith("ds_add_rtn") or op.startswith("ds_read")):
+            if _regs(" ".join(ops), "v") & flying:
+                broken.append((name, op, ops))
+            flying |= _regs(ops[0], "v")
+            (claims if op.startswith("ds_add") else reads)[name] = (claims if op.startswith("ds_add") else reads).get(name, 0) + 1
+        elif op == "s_waitcnt" and "lgkmcnt(0)" in " ".join(ops):
+            flying = set()
+        elif flying & _regs(" ".join(ops), "v"):
+            broken.append((name, op, ops))
+    assert len(claims) == claiming and all(n >= 8 for n in claims.values()), claims
+    assert reads.keys() == claims.keys() and all(claims[k] in (4 * n, 8 * n) for k, n in reads.items()), (claims, reads)
+    assert not broken, (len(broken), broken[:3])
+
+
 def test_every_range_checked_load_takes_its_place_from_the_shared_rule():
     """What picospec_max_load_byte evaluates on the host is what the kernels address: every raw buffer load of a row names its
     vectors through a function of rowspan.hpp (or the spread sample's, whose vectors lie inside the row)."""
