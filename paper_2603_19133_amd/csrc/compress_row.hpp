@@ -1213,6 +1213,7 @@ __device__ __forceinline__ void emit_row(
 {
     constexpr int kRecMax = SH::kRecMax, kSortPer = kRecMax / kT;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    asm volatile("" : "+s"(k));                  // (fetched once from where the arguments are kept, not for every slot)
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     // A mostly masked row with fewer entries above -inf than k (all of them are held): the record goes on with
     // masked entries (probability 0), lowest ids first, i.e. with the lowest ids that are not held.  There are
