@@ -9,7 +9,7 @@
  *   picospec_verify          parallel verification: acceptance test, first rejection (Section 3.3)
  *   picospec_verify_range    the same for a range of each draft's positions (Section 3.2, Fast Verification)
  *   picospec_sample_residual correction token ~ norm(max(0, P_j - Q_j)), or the bonus token
- *   picospec_round           the three calls above as one (two launches for small rounds)
+ *   picospec_round           the three calls above as one (two or three launches)
  *   picospec_row_stats / picospec_compress_rejected / picospec_resample_sparse
  *                            the paper's own downlink: Top-K record of the target row at the
  *                            rejected position, local resampling at the edge (Section 3.3, Eq. 4)

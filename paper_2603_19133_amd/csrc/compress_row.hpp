@@ -21,7 +21,8 @@
 //     there; the softmax arithmetic sits between claim and write, and runs against a reference exponent
 //     fixed from the sample (no running maximum: the row's maximum is its largest candidate).  If the row ends with at least k
 //     candidates that fit the buffer, the exact top k is among them, because nothing at or above the
-//     threshold was dropped.  Waves run free in this pass; too many or too few candidates give the
+//     threshold was dropped (of a bf16 row's ties with it, those of the highest ids may be, once
+//     as many as are needed have been seen).  Waves run free in this pass; too many or too few candidates give the
 //     pass up.
 //   * Safe pass (only for a row that lost the optimistic pass, or when the optimistic rank would not pay):
 //     the sample is the row's first 8192 elements, which are kept as candidates, and r = k, so the

@@ -84,8 +84,9 @@ def test_compress_sizes_and_tails(gpu, pu, ps, V, k, dtype):
                                      "two_values", "sawtooth", "trend_down", "trend_up", "head_hot", "head_cold",
                                      "hot_cluster", "period_of_the_sample", "masked_3pct", "masked_block", "masked_few",
                                      "masked_half", "spike"])
-# (three rows: the general kernel at two record lengths; 600 rows of a short record on long rows: the variant with three
-#  workgroups per CU, which leaves the rows its optimistic pass cannot take to a second launch of the general kernel)
+# (three rows: at two record lengths, the longer one with the large buffer; 600 rows of a short record on long rows: more than
+#  the chip holds at a time.  bf16 rows with k = 777 take the variant with three workgroups per CU.  The rows that the optimistic
+#  pass cannot take are finished by the careful pass in the same launch)
 @pytest.mark.parametrize("R,k", [(3, 777), (3, 2500), (600, 777)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_compress_adversarial_rows(gpu, pu, ps, pattern, dtype, R, k):
@@ -173,7 +174,7 @@ def test_compress_unaligned_rows(gpu, pu, ps, shift, dtype, V):
 @pytest.mark.parametrize("pattern", ["trend", "masked_above_k", "masked_below_k", "few_values", "mixed"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_compress_every_pass_with_the_chip_full(gpu, pu, ps, pattern, dtype):
-    """1100 rows (two generations of workgroups, look-ahead loads live) of the kinds that steer the selector through
+    """1100 rows (two generations of workgroups) of the kinds that steer the selector through
     its other passes: values that trend with the id, masks that leave more or fewer ids than k, rows of a few
     distinct values whose buffer fills, and all of them mixed row by row."""
     _chip_full_case(gpu, pu, ps, pattern, dtype, 1100, 12300, 600)
@@ -219,8 +220,8 @@ def _chip_full_case(gpu, pu, ps, pattern, dtype, rows, V, k):
 @pytest.mark.parametrize("shape", [(1237, 9001, 9003, 70), (1741, 33001, 33003, 70)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_compress_more_rows_than_resident_workgroups(gpu, pu, ps, dtype, shape):
-    """More rows than the chip holds at a time (the look-ahead loads of the next generation of rows are
-    live), odd leading dimension so that most rows start off a 16-byte boundary, and a row count that is
+    """More rows than the chip holds at a time (two generations of workgroups),
+    odd leading dimension so that most rows start off a 16-byte boundary, and a row count that is
     not a multiple of anything; also the same through the row statistics."""
     _announce("compress many rows", dtype, shape)
     rows, V, ld, k = shape
