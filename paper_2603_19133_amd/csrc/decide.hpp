@@ -26,17 +26,18 @@ __device__ __forceinline__ bool clamp_range(const int32_t* pos_begin, const int3
 struct TableStats {
     static constexpr int kAhead = 5;                 // entries per lane in flight (rows of up to 320 segments: one trip)
     float2 e[kAhead];
+    // (lanes behind the last segment read that one again and are masked in combine: a load under a condition is waited for where the
+    //  branch ends, and the next one is asked for behind it)
     __device__ __forceinline__ void load(const float2* __restrict__ seg_row, int n_seg) {
         const int lane = threadIdx.x & (kWave - 1);
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            e[u] = make_float2(0.f, kNegInf);
-            if (u * kWave < n_seg && u * kWave + lane < n_seg) e[u] = seg_row[u * kWave + lane];
-        }
+        for (int u = 0; u < kAhead; ++u) e[u] = seg_row[min(u * kWave + lane, n_seg - 1)];
     }
-    __device__ __forceinline__ void combine(const float2* __restrict__ seg_row, int n_seg, float c, float& M, double& S) const {
+    __device__ __forceinline__ void combine(const float2* __restrict__ seg_row, int n_seg, float c, float& M, double& S) {
         const int lane = threadIdx.x & (kWave - 1);
         float m = kNegInf;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) if (u * kWave + lane >= n_seg) e[u] = make_float2(0.f, kNegInf);
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) m = fmaxf(m, e[u].y);
         for (int s = kAhead * kWave + lane; s < n_seg; s += kWave) m = fmaxf(m, seg_row[s].y);
@@ -790,6 +791,268 @@ __device__ __forceinline__ void residual_seg_sequence(
         resid_mass[b] = (fl & 4u) ? 0.f : (float)R;
         flags[b] = fl;
     }
+}
+
+// ---------------------------------------------------------------- both decisions of a short draft, one wave per position
+//
+// The two functions above behind each other make five dependent trips to memory: offsets; the positions' tokens, ids and table rows; their
+// logits; then the chosen row's record and table again; its gathered logits; the segment.  Here the wave of a position asks for its
+// record's probabilities with the ids, and for the target's logits at all of them together with the token's, so that when the first
+// rejection is known its wave holds all the draw needs in registers, its entries with their logits and its row's segments.  It
+// sums, scans and picks the segment alone, without a barrier, and the whole workgroup names the token, one dword of the segment per thread.
+// For records of up to 256 entries (kDecideRowsK) and drafts of up to 15 positions in a call whose table stands in the split layout: the
+// gathers of the positions that are not drawn from are what longer records would pay for.  Bound by the chain of latencies: of 5.8 us
+// for one sequence of 32,000 fp32, k = 64, the three trips are 0.7, 0.7 and 0.5, the scan of the segments and the token 1.0 each.
+// General code / here, us a call: that round 18.7 / 16.4, 8 sequences of 8 drafts of 32,000 bf16, k = 256: 21.8 / 19.7, verification and draw of 16 of
+// 151,936 fp32, k = 64: 18.9 / 17.1.
+constexpr int kDecideRowsK = 256, kDecideRowsSegs = TableStats::kAhead * kWave;
+
+// Whether sequence b can be decided so (uniform in the workgroup); rows of the call in front of the first and behind the last sequence,
+// whose statistics accept_sequence writes, and offsets that leave the call's rows stay with the general code.
+__device__ __forceinline__ bool decide_rows_serves(int b, int B, int d0, int d1, int n_rows) {
+    const int g = d1 - d0, t0 = d0 + b;
+    return g >= 0 && g < kWaves && d0 >= 0 && d1 <= n_rows - B && (b > 0 || t0 == 0) && (b + 1 < B || d1 + b + 1 == n_rows);
+}
+
+template <bool BF16>
+__device__ __forceinline__ void decide_rows(
+    const int b, const int d0, const int d1, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
+    const int32_t* __restrict__ draft_tok, const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
+    const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
+    const float* __restrict__ uniforms, float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
+    const SegHeader* __restrict__ table, int stride,
+    int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
+    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags)
+{
+    constexpr int N = Vec<BF16>::N, SP = kDecideRowsK / kWave, U = TableStats::kAhead;
+    constexpr int kSegVecs = kSplitStatsNV * kWave, kSegElems = kSegVecs * N;
+    constexpr double kFix = 4611686018427387904.0;                 // 2^62
+    static_assert(kSegVecs * 4 == kThreads, "one dword of the segment per thread");
+    __shared__ unsigned long long tfix[kDecideRowsSegs];           // T of each segment of the chosen row, 2^-62 fixed point
+    __shared__ float qimg[kSegElems];                              // qhat image of the chosen segment
+    __shared__ double wave_mass[kWaves];
+    __shared__ double s_before, s_target, s_R, s_invS;
+    __shared__ float s_M;
+    __shared__ int s_first, s_pick;                                // (s_pick: -1 - segment where the sum is not crossed)
+    __shared__ unsigned s_flags, s_res_flags;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int g = d1 - d0;
+    const int64_t t0 = (int64_t)d0 + b;
+    const int i = min(wave, g);                                    // this wave's position; the last one is the bonus row's
+    const bool mine = wave <= g, drafted = wave < g;
+    const int64_t rt = t0 + i, rd = (int64_t)d0 + (drafted ? i : 0);
+    const RowView rv = row_view<BF16>(tgt_logits, ld, rt, V);
+    const int nq = (rv.L + N - 1) / N, n_seg = stats_segments(nq);
+    const float2* const table_row = reinterpret_cast<const float2*>(table + 1) + rt * (int64_t)stride;
+    const float c = 1.4426950408889634f * inv_T;
+    const double cd = 1.4426950408889634 * (double)inv_T;
+    // ---- one trip: what depends on the position alone.  Without a condition anywhere, since a load under one is waited for where its
+    //      branch ends: the bonus row's wave asks for the first position's values and uses none, a sequence without drafts reads some float.
+    TableStats stats;
+    int my_id[SP];
+    float my_p[SP];
+    const float u_draw = uniforms[t0 + g];
+    const bool any_q = g > 0;
+    const int32_t* const ids = any_q ? q_idx + rd * k : (const int32_t*)uniforms;
+    const float* const qp = any_q ? q_prob + rd * k : uniforms;
+    const int last = any_q ? k - 1 : 0;
+    const int tok_x = *(any_q ? draft_tok + rd : (const int32_t*)uniforms), count_d = *(any_q ? q_count + rd : (const int32_t*)uniforms);
+    const float u_t = uniforms[rt], q_mass_d = *(any_q ? q_mass + rd : uniforms);
+    stats.load(table_row, n_seg);
+#pragma unroll
+    for (int z = 0; z < SP; ++z) {
+        const int sl = min(z * kWave + lane, last);
+        my_id[z] = ids[sl];
+        my_p[z] = qp[sl];
+    }
+    for (int s = tid; s < n_seg; s += kThreads) tfix[s] = 0ull;
+    for (int s = tid; s < kSegElems; s += kThreads) qimg[s] = 0.f;
+    if (tid == 0) { s_first = g; s_flags = 0; }
+    __syncthreads();
+    const int x = drafted ? tok_x : -1, cnt = !drafted || count_d < 0 ? 0 : (count_d > k ? k : count_d);
+    const float mass_d = renorm ? q_mass_d : 1.f;
+    float M = 0.f;
+    double S = 0.0;
+    float my_z[SP];
+    if (mine) {
+        // ---- one more: the target's logits at the record's ids and at the token
+        unsigned fl = 0;
+        bool found = false;
+        float q_at = 0.f;
+#pragma unroll
+        for (int z = 0; z < SP; ++z) {
+            const bool held = z * kWave + lane < cnt;
+            if (held && my_id[z] == x) { found = true; q_at = my_p[z]; }
+            if (!(held && my_id[z] >= 0 && my_id[z] < V)) my_id[z] = -1;
+            my_z[z] = logit_at<BF16>(tgt_logits, ld, rt, max(my_id[z], 0));
+        }
+        const bool bad = x < 0 || x >= V;
+        int x_at = bad ? 0 : x;
+        asm("" : "+v"(x_at));                                      // (a vector load: a scalar one would be waited for here)
+        const float z_t = logit_at<BF16>(tgt_logits, ld, rt, x_at);
+        const unsigned long long at = __ballot(found);             // (one lane: the ids of a record are distinct)
+        const bool in_record = at != 0ull && !bad;
+        stats.combine(table_row, n_seg, c, M, S);
+        const float S_t = (float)S;
+        if (!(fabsf(M) < __builtin_huge_valf()) || !(S_t > 0.f) || !(S_t < __builtin_huge_valf())) fl |= 2u;
+        if (drafted) {
+            double qh = 0.0;
+            if (in_record) {
+                qh = (double)read_lane(q_at, 63 - __clzll((long long)at));
+                if (renorm) qh /= (double)mass_d;
+            } else {
+                fl |= 1u;
+            }
+            if (bad) fl |= 8u;
+            const double p = bad ? 0.0 : exp_emit(z_t, M, cd) / (double)S_t;
+            const double u = (double)u_t;
+            const bool accept = !bad && (u < 1.0) && (qh > 0.0 ? (u * qh < p) : true);   // (accept_sequence's test)
+            if (lane == 0) {
+                if (!accept) atomicMin(&s_first, i);
+                if (p_tok) p_tok[rd] = (float)p;
+                if (q_tok) q_tok[rd] = (float)qh;
+            }
+        }
+        if (lane == 0) {
+            tgt_max[rt] = M;
+            tgt_sum[rt] = S_t;
+            if (fl) atomicOr(&s_flags, fl);
+        }
+    }
+    __syncthreads();
+    const int j = s_first;
+    if (tid == kThreads - 1) { n_accept[b] = j; flags[b] = s_flags; }
+    if (wave == j) {                                               // (j <= g: this wave holds row j)
+        // ---- the chosen row: residual mass of its segments, the total, and the segment in which the cumulative residual crosses u R
+        // (as the draw from a table takes it: a sum that is no number is formed again from the segments that have one)
+        double Sd = S;
+        if (!(S > 0.0 && S < (double)__builtin_huge_valf())) {
+            double s = 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) s += stats.e[u].x > 0.f ? (double)stats.e[u].x * exp2_split(split_ref(stats.e[u].y, c) - (double)M * (double)c) : 0.0;
+            Sd = wave_sum(s);
+        }
+        const double invS = 1.0 / Sd, q_scale = 1.0 / (double)mass_d;
+        float my_q[SP];
+#pragma unroll
+        for (int z = 0; z < SP; ++z) {
+            my_q[z] = 0.f;
+            if (z * kWave < k && my_id[z] >= 0) {
+                const double qh = (double)my_p[z] * q_scale, p = exp_emit(my_z[z], M, cd) * invS;
+                my_q[z] = (float)qh;
+                atomicAdd(&tfix[(my_id[z] + rv.o) / kSegElems], (unsigned long long)llrint((p < qh ? p : qh) * kFix));
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // (LDS serves a wave in order)
+        double p[U], r[U], incl[U], R = 0.0;
+        const double top = (double)M * (double)c;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float2 e = stats.e[u];
+            p[u] = u * kWave < n_seg && e.x > 0.f ? (double)e.x * exp2_split(split_ref(e.y, c) - top) * invS : 0.0;
+        }
+        bool has_q = drafted;
+        unsigned fl = 0;
+        for (int attempt = 0; attempt < 2; ++attempt) {
+            R = 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                r[u] = p[u];
+                if (has_q && u * kWave < n_seg && u * kWave + lane < n_seg) {
+                    r[u] -= (double)tfix[u * kWave + lane] * (1.0 / kFix);
+                    r[u] = r[u] > 0.0 ? r[u] : 0.0;
+                }
+                incl[u] = 0.0;
+                if (u * kWave < n_seg) incl[u] = R + wave_scan_incl(r[u]);
+                if (u * kWave < n_seg) R = read_lane(incl[u], kWave - 1);
+            }
+            if (R > 0.0 || !has_q) break;
+            fl |= 4u;                                              // P == qhat numerically: draw from P itself
+            has_q = false;
+        }
+        const double target = (double)u_draw * R;
+        int pick = -1, last = 0;
+        double before = 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u * kWave >= n_seg) break;
+            const unsigned long long over = __ballot(incl[u] > target), any = __ballot(r[u] > 0.0);
+            if (any) last = u * kWave + 63 - __clzll((long long)any);
+            if (pick < 0 && over) {
+                const int owner = __ffsll((long long)over) - 1;
+                pick = u * kWave + owner;
+                before = read_lane(incl[u] - r[u], owner);
+            }
+        }
+        const int seg = pick >= 0 ? pick : last;                   // rounding: the last segment with mass
+        const int seg_lo = seg * kSegElems - rv.o;
+        if (has_q)
+#pragma unroll
+            for (int z = 0; z < SP; ++z) {
+                const int off = my_id[z] - seg_lo;
+                if (my_id[z] >= 0 && off >= 0 && off < kSegElems) qimg[off] = my_q[z];
+            }
+        if (lane == 0) {
+            s_pick = pick >= 0 ? seg : -1 - seg;
+            s_before = before;
+            s_target = target;
+            s_R = R;
+            s_invS = invS;
+            s_M = M;
+            s_res_flags = fl;
+        }
+    }
+    __syncthreads();
+    // ---- the token: one dword of the segment per thread, ids ascend with (wave, lane, element)
+    const bool crossed = s_pick >= 0;
+    const int seg = __builtin_amdgcn_readfirstlane(crossed ? s_pick : -1 - s_pick);
+    const RowView rj = row_view<BF16>(tgt_logits, ld, t0 + j, V);
+    const int q = seg * kSegVecs + tid / 4, seg_lo = seg * kSegElems - rj.o;
+    uint32_t raw = 0;
+    if (vec_in_row<BF16>(rj, q)) raw = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(rj.base) + (int64_t)seg * kThreads + tid);
+    if (mine && lane == 0 && tgt_lse) tgt_lse[rt] = (float)((double)M * (double)inv_T + log(S));     // (while that load is on its way)
+    constexpr int E = BF16 ? 2 : 1;
+    const double target = s_target, inv = s_invS;
+    const float Mj = s_M;
+    double r[E], sum = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int id = seg_lo + tid * E + e;
+        const float v = BF16 ? __uint_as_float(e ? raw & 0xFFFF0000u : raw << 16) : __uint_as_float(raw);
+        const double d = exp_emit(v, Mj, cd) * inv - (double)qimg[tid * E + e];
+        r[e] = id >= 0 && id < V && d > 0.0 ? d : 0.0;
+        sum += r[e];
+    }
+    const double inc = wave_scan_incl(sum);
+    if (lane == kWave - 1) wave_mass[wave] = inc;
+    __syncthreads();
+    // every wave places the crossing for itself, by the waves' sums; the one it falls to names the token
+    const double w_sum = lane < kWaves ? wave_mass[lane] : 0.0, w_incl = s_before + wave_scan_incl(w_sum);
+    const unsigned long long over = crossed ? __ballot(lane < kWaves && w_incl > target) : 0ull, any = __ballot(w_sum > 0.0);
+    const int owner = over ? __ffsll((long long)over) - 1 : any ? 63 - __clzll((long long)any) : 0;
+    if (wave != owner) return;
+    const double base = owner ? read_lane(w_incl, owner - 1) : s_before;
+    const unsigned long long hit = over ? __ballot(base + inc > target) : 0ull, some = __ballot(sum > 0.0);
+    const int who = hit ? __ffsll((long long)hit) - 1 : some ? 63 - __clzll((long long)some) : 0;
+    if (lane != who) return;
+    int tok = -1;
+    if (hit) {
+        double cu = base + inc - sum;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            cu += r[e];
+            if (tok < 0 && cu > target) tok = seg_lo + tid * E + e;
+        }
+        if (tok < 0) tok = seg_lo + tid * E + E - 1;
+    } else {                                                       // rounding fallback: the last id of the segment with mass
+#pragma unroll
+        for (int e = 0; e < E; ++e) if (r[e] > 0.0) tok = seg_lo + tid * E + e;
+        if (tok < 0) tok = min(max(seg_lo, 0), V - 1);
+    }
+    out_tok[b] = tok;
+    resid_mass[b] = s_res_flags & 4u ? 0.f : (float)s_R;
+    res_flags[b] = s_res_flags;
 }
 
 }  // namespace

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(RT) void residual_seg_kernel(
 
 // SPLIT: the table stands in the split layout, and the rows' statistics are formed here.
 template <bool BF16, bool SPLIT, int RT>
-__global__ __launch_bounds__(kThreads) void decide_seg_kernel(
+__device__ __forceinline__ void decide_seg(
     const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
@@ -95,6 +95,42 @@ __global__ __launch_bounds__(kThreads) void decide_seg_kernel(
     residual_seg_sequence<BF16, RT>(blockIdx.x, first, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
                                     q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, res_flags,
                                     SPLIT ? s_stats : nullptr);
+}
+
+template <bool BF16, bool SPLIT, int RT>
+__global__ __launch_bounds__(kThreads) void decide_seg_kernel(
+    const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
+    const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
+    const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
+    const float* __restrict__ uniforms, float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
+    const SegHeader* __restrict__ table, int seg_vecs, int stride,
+    int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
+    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags, int n_rows)
+{
+    decide_seg<BF16, SPLIT, RT>(tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse,
+                                table, seg_vecs, stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags, n_rows);
+}
+
+// Short records on a table in the split layout: decide_rows, and the kernel above's code for the sequences that it leaves.
+template <bool BF16>
+__global__ __launch_bounds__(kThreads) void decide_rows_kernel(
+    const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
+    const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
+    const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
+    const float* __restrict__ uniforms, float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
+    const SegHeader* __restrict__ table, int seg_vecs, int stride,
+    int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
+    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags, int n_rows)
+{
+    const int b = blockIdx.x, d0 = seq_off[b], d1 = seq_off[b + 1];
+    if (decide_rows_serves(b, (int)gridDim.x, d0, d1, n_rows))
+        decide_rows<BF16>(b, d0, d1, tgt_logits, ld, V, inv_T, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum,
+                          tgt_lse, table, stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags);
+    else
+        decide_seg<BF16, true, 256>(tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum,
+                                    tgt_lse, table, seg_vecs, stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags, n_rows);
 }
 
 }  // namespace
@@ -168,14 +204,20 @@ hipError_t launch_decide(const void* tgt_logits, int dtype, int64_t ld, int V, f
         if (B == 0) return hipSuccess;
         const float it = 1.0f / temperature;
         const StatsShape sh = split_table ? split_stats_shape(dtype, V) : small_round_table ? round_stats_shape(dtype, V) : stats_shape(dtype, n_rows, V);
-#define PICOSPEC_DECIDE(BF, SP, RT) \
-        hipLaunchKernelGGL((decide_seg_kernel<BF, SP, RT>), dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, it, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags, (int)n_rows)
+#define PICOSPEC_DECIDE_ARGS dim3(B), dim3(kThreads), 0, stream, tgt_logits, ld, V, it, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags, (int)n_rows
+#define PICOSPEC_DECIDE(BF, SP, RT) hipLaunchKernelGGL((decide_seg_kernel<BF, SP, RT>), PICOSPEC_DECIDE_ARGS)
 #define PICOSPEC_DECIDE_RT(BF, SP) \
         switch (residual_seg_threads(k)) { case 256: PICOSPEC_DECIDE(BF, SP, 256); break; case 512: PICOSPEC_DECIDE(BF, SP, 512); break; default: PICOSPEC_DECIDE(BF, SP, 1024); }
-        if (split_table) { if (dtype == 1) { PICOSPEC_DECIDE_RT(true, true) } else { PICOSPEC_DECIDE_RT(false, true) } }
+        // (the table of a row has to fit the registers of one wave: fp32 rows of up to 327,680, bf16 of up to 655,360)
+        if (split_table && k <= kDecideRowsK && sh.stride <= kDecideRowsSegs) {
+            if (dtype == 1) hipLaunchKernelGGL(decide_rows_kernel<true>, PICOSPEC_DECIDE_ARGS);
+            else            hipLaunchKernelGGL(decide_rows_kernel<false>, PICOSPEC_DECIDE_ARGS);
+        }
+        else if (split_table) { if (dtype == 1) { PICOSPEC_DECIDE_RT(true, true) } else { PICOSPEC_DECIDE_RT(false, true) } }
         else             { if (dtype == 1) { PICOSPEC_DECIDE_RT(true, false) } else { PICOSPEC_DECIDE_RT(false, false) } }
 #undef PICOSPEC_DECIDE_RT
 #undef PICOSPEC_DECIDE
+#undef PICOSPEC_DECIDE_ARGS
         return hipGetLastError();
     }
     static DeviceFlags limit_raised[2] = {};
