@@ -455,6 +455,11 @@ size_t picospec_workspace_bytes(int which_call, int dtype, int32_t rows, int32_t
  * which calls are spread stand in the library only: a caller that keeps its buffers asks here which call has a use for one. */
 size_t picospec_scratch_bytes(int which_call, int dtype, int32_t n_draft, int32_t B, int32_t V, int32_t k);
 
+/* The same, and behind it what lets the call go out in one launch where that is the faster way (few rows; verify, verify_range, row_stats and the
+ * draw that makes its own table).  A call that is given picospec_scratch_bytes() alone takes two launches.  Calls that overlap in time must not
+ * share scratch. */
+size_t picospec_one_launch_bytes(int which_call, int dtype, int32_t n_draft, int32_t B, int32_t V, int32_t k);
+
 /* host: largest supported k (PICOSPEC_LIMIT_MAX_K) or V (PICOSPEC_LIMIT_MAX_V); -1 for an unknown id. */
 int64_t picospec_limit(int which);
 

@@ -36,7 +36,7 @@ EXPORTS = ("picospec_round", "picospec_verify_sample", "picospec_verify_sample_s
            "picospec_row_stats", "picospec_row_stats_ws", "picospec_compress_rejected", "picospec_resample_sparse",
            "picospec_pack_downlink", "picospec_unpack_downlink", "picospec_pack_uplink", "picospec_unpack_uplink",
            "picospec_downlink_bytes_max", "picospec_uplink_bytes", "picospec_max_load_byte", "picospec_check_device", "picospec_probe_clock",
-           "picospec_workspace_bytes", "picospec_scratch_bytes", "picospec_limit", "picospec_strerror", "picospec_version")
+           "picospec_workspace_bytes", "picospec_scratch_bytes", "picospec_one_launch_bytes", "picospec_limit", "picospec_strerror", "picospec_version")
 
 if not os.path.exists(LIB_PATH):
     raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2603_19133_amd.build` "
@@ -93,6 +93,8 @@ lib.picospec_workspace_bytes.argtypes = [C.c_int, C.c_int, _i32, _i32, _i32]
 lib.picospec_workspace_bytes.restype = _sz
 lib.picospec_scratch_bytes.argtypes = [C.c_int, C.c_int, _i32, _i32, _i32, _i32]
 lib.picospec_scratch_bytes.restype = _sz
+lib.picospec_one_launch_bytes.argtypes = [C.c_int, C.c_int, _i32, _i32, _i32, _i32]
+lib.picospec_one_launch_bytes.restype = _sz
 lib.picospec_limit.argtypes = [C.c_int]
 lib.picospec_limit.restype = _i64
 lib.picospec_strerror.argtypes = [C.c_int]

@@ -130,6 +130,9 @@ int picospec_row_stats_ws(const void* logits, int dtype, int64_t ld, int32_t n_r
     hipStream_t s = (hipStream_t)stream;
     if (!workspace || !row_stats_split_serves(dtype, n_rows, V))
         return hip_status(launch_row_stats(logits, dtype, ld, n_rows, V, temperature, row_max, row_sum, row_lse, nullptr, s));
+    // (a workspace that holds the table alone: two launches)
+    if (workspace_bytes >= row_stats_scratch_bytes(dtype, n_rows, V))
+        return hip_status(launch_row_stats_spread(logits, dtype, ld, n_rows, V, temperature, workspace, row_max, row_sum, row_lse, s));
     if (hipError_t e = launch_row_stats_parts(logits, dtype, ld, n_rows, V, temperature, 0, 0, nullptr, nullptr, nullptr, workspace, s))
         return hip_status(e);
     return hip_status(launch_row_stats_finish(logits, dtype, ld, n_rows, V, temperature, workspace, row_max, row_sum, row_lse, s));
@@ -390,6 +393,10 @@ int verify_impl(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float 
     if (int rc = check_workspace(PICOSPEC_CALL_VERIFY, dtype, rows, V, k, workspace, workspace_bytes)) return rc;
     hipStream_t s = (hipStream_t)stream;
     const bool split = workspace && B > 0 && split_stats_serves(rows, V);
+    if (split && verify_one_launch(ranged, dtype, rows, V) && workspace_bytes >= verify_scratch_bytes(dtype, rows, B, V))      // (one that holds the table alone: two launches)
+        return hip_status(launch_verify_spread(tgt_logits, dtype, ld, V, temperature, B, rows, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k,
+                                               renorm, q_scalar, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok, flags,
+                                               ranged, ranged ? pos_begin : nullptr, ranged ? pos_end : nullptr, gamma_max, workspace, s));
     const hipError_t e = split
         ? launch_row_stats_parts(tgt_logits, dtype, ld, (int)rows, V, temperature, B, gamma_max, ranged ? seq_off : nullptr,
                                  pos_begin, pos_end, workspace, s)
@@ -455,7 +462,7 @@ int sample_residual_impl(const void* tgt_logits, int dtype, int64_t ld, int32_t 
     if (int rc = check_workspace(PICOSPEC_CALL_SAMPLE_RESIDUAL, dtype, own_table ? B : rows, V, k, workspace, workspace_bytes)) return rc;
     if (own_table && workspace && residual_split_serves(dtype, B, V, k))
         return hip_status(launch_residual_split(tgt_logits, dtype, ld, V, temperature, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass, k,
-                                                renorm, uniforms, out_tok, resid_mass, flags, workspace, rows, (hipStream_t)stream));
+                                                renorm, uniforms, out_tok, resid_mass, flags, workspace, workspace_bytes, rows, (hipStream_t)stream));
     if (own_table) workspace = nullptr;
     return hip_status(launch_residual(tgt_logits, dtype, ld, V, temperature, B, seq_off, n_accept, tgt_max, tgt_sum,
                                       q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass,
@@ -524,6 +531,19 @@ size_t picospec_scratch_bytes(int which_call, int dtype, int32_t n_draft, int32_
             return (round_seg_table_bytes(dtype, rows, V) + 15) / 16 * 16 + split_scratch_bytes(dtype, n_draft, V, k);
         }
         default: return 0;
+    }
+}
+
+size_t picospec_one_launch_bytes(int which_call, int dtype, int32_t n_draft, int32_t B, int32_t V, int32_t k)
+{
+    const size_t scratch = picospec_scratch_bytes(which_call, dtype, n_draft, B, V, k);
+    if (!scratch) return 0;
+    const int64_t rows = (int64_t)n_draft + B;
+    switch (which_call) {
+        case PICOSPEC_CALL_VERIFY: return verify_one_launch(true, dtype, rows, V) ? std::max(scratch, verify_scratch_bytes(dtype, rows, B, V)) : scratch;
+        case PICOSPEC_CALL_ROW_STATS: return std::max(scratch, row_stats_scratch_bytes(dtype, rows, V));
+        case PICOSPEC_CALL_SAMPLE_RESIDUAL: return residual_one_launch(dtype, B, V, k) ? std::max(scratch, residual_scratch_bytes(dtype, B, V)) : scratch;
+        default: return scratch;
     }
 }
 

@@ -194,6 +194,69 @@ __device__ __forceinline__ double exp2_split(double a) {
     return ldexp((double)__builtin_amdgcn_exp2f((float)(a - n)), (int)n);
 }
 
+// ---------------------------------------------------------------- the last workgroup of a group goes on
+//
+// What a group of workgroups hands to the last of them that arrives, without a launch between: every workgroup writes its share with
+// put_shared, arrives, and the last one reads all of it with get_shared.  These are accesses at device scope, which pass by the
+// L2s (each XCD has its own): a store that has returned (vmcnt) is visible to the whole device, and a load reads past what an L2 may hold,
+// so no cache is written back or invalidated.  Against a second launch the hand-over saves 0.5 us on the device (of 1.5 to 2) and a
+// launch on the host (2.5 to 3.6 us); with a release and an acquire fence instead, which write back and invalidate whole L2s, it is
+// 1 us slower with 32 workgroups and 15 to 50 with 256 and 1024.  The waves never wait for another workgroup.
+//
+// The group's word lies in the caller's scratch and need not be cleared: whoever opens it first, early in the kernel, replaces what it finds
+// by kArrivalMark with a count of 0, which is also what the last to arrive leaves: a call that is given the same scratch again, or a
+// captured one, finds its words open.
+constexpr unsigned long long kArrivalMark = 0x5A9C31E7D24Bull << 16;         // (behind it 16 bits of count)
+constexpr unsigned kArrivalMost = 0xFFFFu;
+
+__device__ __forceinline__ void put_shared(unsigned long long* p, unsigned long long v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ unsigned long long get_shared(const unsigned long long* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void put_shared(float2* p, float2 v) {
+    put_shared(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__float_as_uint(v.x) | (unsigned long long)__float_as_uint(v.y) << 32);
+}
+__device__ __forceinline__ float2 get_shared(const float2* p) {
+    const unsigned long long v = get_shared(reinterpret_cast<const unsigned long long*>(p));
+    return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
+}
+
+__device__ __forceinline__ unsigned long long* arrival_word(unsigned long long* words, int64_t i) { return words + i * (int64_t)(kArrivalStride / 8); }
+
+// One thread of every workgroup, before the workgroup arrives; best behind the loads that the workgroup waits for anyway.
+__device__ __forceinline__ void open_arrival(unsigned long long* word) {
+    unsigned long long seen = get_shared(word);
+    if ((seen & ~(unsigned long long)kArrivalMost) != kArrivalMark)       // (fails only where another workgroup has just opened it)
+        __hip_atomic_compare_exchange_strong(word, &seen, kArrivalMark, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The whole workgroup, by the thread that opened the word for the workgroup first (opener): true in the last of `total` workgroups.
+__device__ __forceinline__ bool arrive_last(unsigned long long* word, unsigned total, bool opener) {
+    __shared__ int s_last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // (every wave: its stores are where all can see them)
+    __syncthreads();
+    if (opener) {
+        const unsigned long long seen = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool last = (unsigned)(seen & kArrivalMost) + 1u == total;
+        if (last) put_shared(word, kArrivalMark);
+        s_last = last;
+    }
+    __syncthreads();
+    return s_last != 0;
+}
+
+// A kernel with many arguments of which each part of it uses few takes them as one structure, its only argument, and reads them through
+// args_here<A>(): from where they are kept, at that place.  (As parameters all of them are fetched at the kernel's start and held across it, in
+// lanes of vector registers where there are more than scalar ones: 117 writes and as many reads in verify_spread_kernel.)  Pointers in the
+// structure name their address space, which the compiler otherwise knows of parameters only.
+template <class T> using global_ptr = T __attribute__((address_space(1)))*;
+template <class T> __device__ __forceinline__ T* plain(global_ptr<T> p) { return (T*)p; }
+#define PICOSPEC_ARGS __attribute__((address_space(4)))
+template <class A>
+__device__ __forceinline__ const A PICOSPEC_ARGS* args_here() {
+    auto p = (const A PICOSPEC_ARGS*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 // ---------------------------------------------------------------- row streaming
 //
 // A row of V elements is read as 16-byte vectors.  If the row does not start on a 16-byte
@@ -525,63 +588,110 @@ __device__ __forceinline__ bool split_ref_fused(float m, float c) { return fabsf
 // m c as the sums' reference: rounded to fp32 as in the fused form of their terms; exact where that overflows (a segment of
 // nothing but masked entries of the type's lowest value), whose terms are formed as (z - m) c
 __device__ __forceinline__ double split_ref(float m, float c) { return split_ref_fused(m, c) ? (double)(m * c) : (double)m * (double)c; }
+// The entry of segment s, whose vectors are raw, in every lane of the wave that holds them.
+template <bool BF16>
+__device__ __forceinline__ float2 segment_entry(const RowView& rv, const int n_seg, const int s, const uint4 (&raw)[kSplitStatsNV], const float c)
+{
+    constexpr int NV = kSplitStatsNV, N = Vec<BF16>::N, E = NV * N;
+    const int lane = threadIdx.x & (kWave - 1);
+    float v[E];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        float t[N];
+        unpack<BF16>(raw[j], t);
+#pragma unroll
+        for (int e = 0; e < N; ++e) v[j * N + e] = t[e];
+    }
+    if (s == 0 || s + 1 == n_seg) {               // (elements outside the row)
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const unsigned vm = vec_valid_mask<BF16>(rv, stats_group_first(s, j) + lane);
+#pragma unroll
+            for (int e = 0; e < N; ++e) v[j * N + e] = (vm >> e) & 1u ? v[j * N + e] : kNegInf;
+        }
+    }
+    float bm = v[0];
+#pragma unroll
+    for (int e = 1; e < E; ++e) bm = fmaxf(bm, v[e]);
+    const float m = wave_max(bm);
+    float acc;
+    if (split_ref_fused(m, c)) {                  // (uniform)
+        const float nr = -(m * c);
+        acc = tree_sum<0, E>([&](int e) { return __builtin_amdgcn_exp2f(fmaf(v[e], c, nr)); });
+    } else {
+        // (no value above -inf: the sum is 0, or NaN if the segment holds one - the maxima skip NaN, so only the sum can carry it)
+        const float ref = m > kNegInf ? m : 0.f;
+        acc = tree_sum<0, E>([&](int e) { return exp_stream(v[e], ref, c); });
+    }
+    return make_float2((float)wave_sum((double)acc), m > kNegInf ? m : kNegInf);
+}
+
+// A row's vectors by segment.  (The range rule of the other row kernels, rowspan.hpp: vectors behind the row read as zero and touch no memory.)
+template <bool BF16>
+struct RowSegments {
+    RowView rv;
+    int nq, n_seg;
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ RowSegments(const void* __restrict__ logits, int64_t ld, int64_t row, int V) : rv(row_view<BF16>(logits, ld, row, V)) {
+        nq = (rv.L + Vec<BF16>::N - 1) / Vec<BF16>::N;
+        n_seg = stats_segments(nq);
+        rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)rv.base, 0, nq * 16, 0x00020000);
+    }
+    __device__ __forceinline__ void load(int s, uint4 (&raw)[kSplitStatsNV]) const {
+        const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+        for (int j = 0; j < kSplitStatsNV; ++j) {
+            const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, stats_group_first(s, j) * 16, 2 /* non-temporal */);
+            raw[j] = make_uint4(t.x, t.y, t.z, t.w);
+        }
+    }
+};
+
 template <bool BF16>
 __device__ __forceinline__ void row_stats_parts(
     const int64_t row, const int64_t table_row, const int part, const void* __restrict__ logits, int64_t ld, int V, float inv_T,
     float2* __restrict__ seg, int seg_stride)
 {
-    constexpr int NV = kSplitStatsNV, SPW = kSplitStatsSpw, N = Vec<BF16>::N, E = NV * N;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const RowView rv = row_view<BF16>(logits, ld, row, V);
-    const int nq = (rv.L + N - 1) / N, n_seg = stats_segments(nq);
+    const RowSegments<BF16> segs(logits, ld, row, V);
+    uint4 raw[kSplitStatsSpw][kSplitStatsNV];
+#pragma unroll
+    for (int i = 0; i < kSplitStatsSpw; ++i) segs.load(stats_segment(part, wave, i), raw[i]);
     const float c = 1.4426950408889634f * inv_T;
-    // (the range rule of the other row kernels, rowspan.hpp: vectors behind the row read as zero and touch no memory)
-    const __amdgpu_buffer_rsrc_t row_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)rv.base, 0, nq * 16, 0x00020000);
-    uint4 raw[SPW][NV];
-#pragma unroll
-    for (int i = 0; i < SPW; ++i)
-#pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(row_rsrc, lane * 16, stats_group_first(stats_segment(part, wave, i), j) * 16, 2 /* non-temporal */);
-            raw[i][j] = make_uint4(t.x, t.y, t.z, t.w);
-        }
     float2* const seg_row = seg + table_row * (int64_t)seg_stride;
 #pragma unroll
-    for (int i = 0; i < SPW; ++i) {
+    for (int i = 0; i < kSplitStatsSpw; ++i) {
         const int s = stats_segment(part, wave, i);
-        if (s >= n_seg) return;                       // (uniform)
-        float v[E];
+        if (s >= segs.n_seg) return;                      // (uniform)
+        const float2 e = segment_entry<BF16>(segs.rv, segs.n_seg, s, raw[i], c);
+        if (lane == 0) seg_row[s] = e;
+    }
+}
+
+// The entries of a row from workgroup `part` of `parts`, WAVES waves each, for another workgroup of the same launch to read: as many parts as
+// keep all workgroups of the call on the chip at once, each wave a segment per trip and the next one's loads in flight.  `meanwhile`
+// is run behind the first loads.
+template <bool BF16, int WAVES, class F>
+__device__ __forceinline__ void row_stats_shared(
+    const int64_t row, const int64_t table_row, const int part, const int parts, const void* __restrict__ logits, int64_t ld, int V, float inv_T,
+    float2* __restrict__ seg, int seg_stride, const F& meanwhile)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const RowSegments<BF16> segs(logits, ld, row, V);
+    const float c = 1.4426950408889634f * inv_T;
+    float2* const seg_row = seg + table_row * (int64_t)seg_stride;
+    int s = part * WAVES + wave;
+    uint4 cur[kSplitStatsNV], next[kSplitStatsNV];
+    segs.load(s, cur);
+    meanwhile();
+    for (; s < segs.n_seg; s += parts * WAVES) {
+        segs.load(s + parts * WAVES, next);
+        const float2 e = segment_entry<BF16>(segs.rv, segs.n_seg, s, cur, c);
+        if (lane == 0) put_shared(&seg_row[s], e);
 #pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            float t[N];
-            unpack<BF16>(raw[i][j], t);
-#pragma unroll
-            for (int e = 0; e < N; ++e) v[j * N + e] = t[e];
-        }
-        if (s == 0 || s + 1 == n_seg) {               // (elements outside the row)
-#pragma unroll
-            for (int j = 0; j < NV; ++j) {
-                const unsigned vm = vec_valid_mask<BF16>(rv, stats_group_first(s, j) + lane);
-#pragma unroll
-                for (int e = 0; e < N; ++e) v[j * N + e] = (vm >> e) & 1u ? v[j * N + e] : kNegInf;
-            }
-        }
-        float bm = v[0];
-#pragma unroll
-        for (int e = 1; e < E; ++e) bm = fmaxf(bm, v[e]);
-        const float m = wave_max(bm);
-        float acc;
-        if (split_ref_fused(m, c)) {                  // (uniform)
-            const float nr = -(m * c);
-            acc = tree_sum<0, E>([&](int e) { return __builtin_amdgcn_exp2f(fmaf(v[e], c, nr)); });
-        } else {
-            // (no value above -inf: the sum is 0, or NaN if the segment holds one - the maxima skip NaN, so only the sum can carry it)
-            const float ref = m > kNegInf ? m : 0.f;
-            acc = tree_sum<0, E>([&](int e) { return exp_stream(v[e], ref, c); });
-        }
-        const float t = (float)wave_sum((double)acc);
-        if (lane == 0) seg_row[s] = make_float2(t, m > kNegInf ? m : kNegInf);
+        for (int j = 0; j < kSplitStatsNV; ++j) cur[j] = next[j];
     }
 }
 

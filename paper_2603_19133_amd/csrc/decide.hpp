@@ -28,11 +28,16 @@ struct TableStats {
     float2 e[kAhead];
     // (lanes behind the last segment read that one again and are masked in combine: a load under a condition is waited for where the
     //  branch ends, and the next one is asked for behind it)
+    template <bool SHARED = false>
     __device__ __forceinline__ void load(const float2* __restrict__ seg_row, int n_seg) {
         const int lane = threadIdx.x & (kWave - 1);
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) e[u] = seg_row[min(u * kWave + lane, n_seg - 1)];
+        for (int u = 0; u < kAhead; ++u) {
+            const float2* const p = &seg_row[min(u * kWave + lane, n_seg - 1)];
+            e[u] = SHARED ? get_shared(p) : *p;
+        }
     }
+    template <bool SHARED = false>
     __device__ __forceinline__ void combine(const float2* __restrict__ seg_row, int n_seg, float c, float& M, double& S) {
         const int lane = threadIdx.x & (kWave - 1);
         float m = kNegInf;
@@ -40,15 +45,84 @@ struct TableStats {
         for (int u = 0; u < kAhead; ++u) if (u * kWave + lane >= n_seg) e[u] = make_float2(0.f, kNegInf);
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) m = fmaxf(m, e[u].y);
-        for (int s = kAhead * kWave + lane; s < n_seg; s += kWave) m = fmaxf(m, seg_row[s].y);
+        for (int s = kAhead * kWave + lane; s < n_seg; s += kWave) m = fmaxf(m, (SHARED ? get_shared(&seg_row[s]) : seg_row[s]).y);
         M = wave_max(m);
         const double top = (double)M * (double)c;
         auto term = [&](float2 t) { return t.x > 0.f || t.x != t.x ? (double)t.x * exp2_split(split_ref(t.y, c) - top) : 0.0; };
         double s = 0.0;
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) if (u * kWave < n_seg) s += term(e[u]);
-        for (int q = kAhead * kWave + lane; q < n_seg; q += kWave) s += term(seg_row[q]);
+        for (int q = kAhead * kWave + lane; q < n_seg; q += kWave) s += term(SHARED ? get_shared(&seg_row[q]) : seg_row[q]);
         S = wave_sum(s);
+    }
+};
+
+// Where one wave finds a token in a position's record: the first 1024 ids (512 where the record is off the 16-byte boundary) are asked for apart
+// from the search.
+struct RecordScan {
+    int4 front[4];
+    bool aligned;
+    __device__ __forceinline__ void load(const int32_t* __restrict__ ids, int k) {
+        const int lane = threadIdx.x & (kWave - 1);
+        aligned = ((uintptr_t)ids & 15u) == 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = u * kWave + lane;
+            if (aligned) { if (s < (k >> 2)) front[u] = reinterpret_cast<const int4*>(ids)[s]; }
+            else { if (s < k) front[u].x = ids[s]; if (s + 4 * kWave < k) front[u].y = ids[s + 4 * kWave]; }
+        }
+    }
+    // the slot among the record's first cnt that holds x, or -1; in every lane
+    __device__ __forceinline__ int find(const int32_t* __restrict__ ids, int cnt, int x) const {
+        const int lane = threadIdx.x & (kWave - 1);
+        int slot = -1;
+        // The record is ordered by probability and the token was drawn from it, so it sits near the
+        // front more often than not: the scan goes in rounds of 1024 ids and stops at the round
+        // that holds it.
+        if (aligned) {
+            const int4* ids4 = reinterpret_cast<const int4*>(ids);
+            const int n4 = cnt >> 2;
+            auto look = [&](int s, const int4& q) {
+                if (s < n4) {
+                    if (q.x == x) slot = 4 * s;
+                    if (q.y == x) slot = 4 * s + 1;
+                    if (q.z == x) slot = 4 * s + 2;
+                    if (q.w == x) slot = 4 * s + 3;
+                }
+            };
+#pragma unroll
+            for (int u = 0; u < 4; ++u) look(u * kWave + lane, front[u]);
+            if (!__ballot(slot >= 0))
+                for (int s0 = 4 * kWave; s0 < n4; s0 += 4 * kWave) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int s = s0 + u * kWave + lane;
+                        if (s < n4) look(s, ids4[s]);
+                    }
+                    if (__ballot(slot >= 0)) break;
+                }
+            if (!__ballot(slot >= 0))
+                for (int s = 4 * n4 + lane; s < cnt; s += kWave)
+                    if (ids[s] == x) slot = s;
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int s = u * kWave + lane;
+                if (s < cnt && front[u].x == x) slot = s;
+                if (s + 4 * kWave < cnt && front[u].y == x) slot = s + 4 * kWave;
+            }
+            if (!__ballot(slot >= 0))
+                for (int s0 = 8 * kWave; s0 < cnt; s0 += 8 * kWave) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int s = s0 + u * kWave + lane;
+                        if (s < cnt && ids[s] == x) slot = s;
+                    }
+                    if (__ballot(slot >= 0)) break;
+                }
+        }
+        const unsigned long long found = __ballot(slot >= 0);    // (one lane: the ids of a record are distinct)
+        return found ? __builtin_amdgcn_readlane(slot, 63 - __clzll((long long)found)) : -1;
     }
 };
 
@@ -70,9 +144,10 @@ __device__ __forceinline__ void write_split_lse(const SplitStats* s_stats, int2 
 // split_stats_serves): they are formed here and written to tgt_max / tgt_sum / tgt_lse.  s_stats (nullable, LDS): they
 // are left there by position as well, and tgt_lse is not written: the caller does that off the critical path
 // (write_split_lse), for the positions that come back in `rows`.
-template <bool BF16, bool TABLE = false>
+// WAVES: waves of the workgroup.  SHARED: the table was written by other workgroups of this launch.
+template <bool BF16, bool TABLE = false, int WAVES = kWaves, bool SHARED = false>
 __device__ __forceinline__ int accept_sequence(
-    const int b, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
+    const int b, const int B, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
@@ -102,7 +177,7 @@ __device__ __forceinline__ int accept_sequence(
 
     // every target row of the range must have finite statistics
     if constexpr (!TABLE) {
-        for (int t = begin + tid; t <= end; t += kThreads)
+        for (int t = begin + tid; t <= end; t += WAVES * kWave)
             if (nonfinite(tgt_max[t0 + t], tgt_sum[t0 + t])) fl |= 2u;
     }
 
@@ -112,9 +187,9 @@ __device__ __forceinline__ int accept_sequence(
     int rows_begin = begin, rows_end = end;           // positions rows_begin .. rows_end - 1
     if constexpr (TABLE) {
         rows_begin = all_rows && b == 0 ? min(begin, -(int)t0) : begin;
-        rows_end = all_rows && b + 1 == (int)gridDim.x ? max(end + 1, (int)(n_rows - t0)) : end + 1;
+        rows_end = all_rows && b + 1 == B ? max(end + 1, (int)(n_rows - t0)) : end + 1;
     }
-    for (int i = rows_begin + wave; i < rows_end; i += kWaves) {
+    for (int i = rows_begin + wave; i < rows_end; i += WAVES) {
         const int64_t rt = t0 + i;
         const bool decides = !TABLE || (i >= begin && i < end);       // (the other rows have statistics only)
         if (TABLE && (rt < 0 || rt >= n_rows)) {      // (offsets that leave the call's rows: nothing is written for such a row)
@@ -127,8 +202,7 @@ __device__ __forceinline__ int accept_sequence(
         float u_t = 0.f, mass_d = 1.f, M_t = 0.f, S_t = 1.f;
         double qh = 0.0;
         const int32_t* ids = q_idx;
-        const bool ids_aligned = !q_scalar && ((((uintptr_t)(q_idx + rd * k)) & 15u) == 0);
-        int4 q4[4];                                   // the record's first 1024 ids (512 where it is off the 16-byte boundary)
+        RecordScan scan;
         if (decides) {
             x = draft_tok[rd];
             u_t = uniforms[rt];
@@ -139,12 +213,7 @@ __device__ __forceinline__ int accept_sequence(
                 cnt = q_count[rd];
                 if (renorm) mass_d = q_mass[rd];
                 ids = q_idx + rd * k;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int s = u * kWave + lane;
-                    if (ids_aligned) { if (s < (k >> 2)) q4[u] = reinterpret_cast<const int4*>(ids)[s]; }
-                    else { if (s < k) q4[u].x = ids[s]; if (s + 4 * kWave < k) q4[u].y = ids[s + 4 * kWave]; }
-                }
+                scan.load(ids, k);
             }
         }
         const float2* table_row = nullptr;
@@ -155,7 +224,7 @@ __device__ __forceinline__ int accept_sequence(
             const int nq = (rv.L + Vec<BF16>::N - 1) / Vec<BF16>::N;
             n_seg = (nq + seg_vecs - 1) / seg_vecs;
             table_row = reinterpret_cast<const float2*>(table + 1) + rt * (int64_t)stride;
-            stats.load(table_row, n_seg);
+            stats.template load<SHARED>(table_row, n_seg);
         }
         const bool bad = x < 0 || x >= V;
         const float z_t = bad || !decides ? 0.f : logit_at<BF16>(tgt_logits, ld, rt, x);
@@ -163,61 +232,14 @@ __device__ __forceinline__ int accept_sequence(
         bool in_record = false;
         if (decides && !q_scalar) {
             cnt = cnt < 0 ? 0 : (cnt > k ? k : cnt);
-            int slot = -1;
-            // The record is ordered by probability and the token was drawn from it, so it sits near the
-            // front more often than not: the scan goes in rounds of 1024 ids and stops at the round
-            // that holds it.
-            if (ids_aligned) {
-                const int4* ids4 = reinterpret_cast<const int4*>(ids);
-                const int n4 = cnt >> 2;
-                auto look = [&](int s, const int4& q) {
-                    if (s < n4) {
-                        if (q.x == x) slot = 4 * s;
-                        if (q.y == x) slot = 4 * s + 1;
-                        if (q.z == x) slot = 4 * s + 2;
-                        if (q.w == x) slot = 4 * s + 3;
-                    }
-                };
-#pragma unroll
-                for (int u = 0; u < 4; ++u) look(u * kWave + lane, q4[u]);
-                if (!__ballot(slot >= 0))
-                    for (int s0 = 4 * kWave; s0 < n4; s0 += 4 * kWave) {
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int s = s0 + u * kWave + lane;
-                            if (s < n4) look(s, ids4[s]);
-                        }
-                        if (__ballot(slot >= 0)) break;
-                    }
-                if (!__ballot(slot >= 0))
-                    for (int s = 4 * n4 + lane; s < cnt; s += kWave)
-                        if (ids[s] == x) slot = s;
-            } else {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int s = u * kWave + lane;
-                    if (s < cnt && q4[u].x == x) slot = s;
-                    if (s + 4 * kWave < cnt && q4[u].y == x) slot = s + 4 * kWave;
-                }
-                if (!__ballot(slot >= 0))
-                    for (int s0 = 8 * kWave; s0 < cnt; s0 += 8 * kWave) {
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            const int s = s0 + u * kWave + lane;
-                            if (s < cnt && ids[s] == x) slot = s;
-                        }
-                        if (__ballot(slot >= 0)) break;
-                    }
-            }
-            const unsigned long long found = __ballot(slot >= 0);    // (one lane: the ids of a record are distinct)
-            slot = found ? __builtin_amdgcn_readlane(slot, 63 - __clzll((long long)found)) : -1;
+            const int slot = scan.find(ids, cnt, x);
             in_record = slot >= 0 && !bad;
             if (in_record) q_at = q_prob[rd * k + slot];
         }
         // (the row's statistics are formed while the last two loads are on their way)
         if constexpr (TABLE) {
             double S;
-            stats.combine(table_row, n_seg, c, M_t, S);
+            stats.template combine<SHARED>(table_row, n_seg, c, M_t, S);
             S_t = (float)S;
             if (lane == 0) {
                 tgt_max[rt] = M_t;
@@ -258,6 +280,123 @@ __device__ __forceinline__ int accept_sequence(
         flags[b] = s_flags;
     }
     return first;
+}
+
+
+// What the acceptance of a sequence's positions needs besides the rows' statistics, looked up by a workgroup of its own while others stream
+// the rows: entry rt of `found` holds the target's logit at the token and flags (1: not in the record, 8: no id), then qhat (fp64).  One
+// wave per position; for the workgroup that decides to read (get_shared).
+template <bool BF16, int WAVES>
+__device__ __forceinline__ void look_up_positions(
+    const int b, const int d0, const int begin, const int end, const void* __restrict__ tgt_logits, int64_t ld, int V, int n_rows, int n_draft,
+    const int32_t* __restrict__ draft_tok, const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
+    const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm, const float* __restrict__ q_scalar,
+    unsigned long long* __restrict__ found)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (int i = begin + wave; i < end; i += WAVES) {
+        const int64_t rd = (int64_t)d0 + i, rt = rd + b;
+        if (rt < 0 || rt >= n_rows || rd >= n_draft) continue;      // (offsets that leave the call's rows or drafts)
+        const int x = draft_tok[rd];
+        double qh = 0.0;
+        float mass_d = 1.f;
+        int cnt = 0;
+        const int32_t* ids = q_idx;
+        RecordScan scan;
+        if (q_scalar) {
+            qh = (double)q_scalar[rd];
+        } else {
+            cnt = q_count[rd];
+            if (renorm) mass_d = q_mass[rd];
+            ids = q_idx + rd * k;
+            scan.load(ids, k);
+        }
+        const bool bad = x < 0 || x >= V;
+        unsigned fl = bad ? 8u : 0u;
+        const float z_t = bad ? 0.f : logit_at<BF16>(tgt_logits, ld, rt, x);
+        if (!q_scalar) {
+            const int slot = scan.find(ids, cnt < 0 ? 0 : (cnt > k ? k : cnt), x);
+            if (slot >= 0 && !bad) {
+                qh = (double)q_prob[rd * k + slot];
+                if (renorm) qh /= (double)mass_d;
+            } else {
+                fl |= 1u;
+            }
+        }
+        if (lane == 0) {
+            put_shared(found + 2 * rt, (unsigned long long)__float_as_uint(z_t) | (unsigned long long)fl << 32);
+            put_shared(found + 2 * rt + 1, (unsigned long long)__double_as_longlong(qh));
+        }
+    }
+}
+
+// accept_sequence<.., TABLE> of a sequence whose table rows and lookups other workgroups of this launch have left: one wave per row, one trip
+// to memory.  rows_begin .. rows_end - 1: the positions whose rows get statistics.
+template <bool BF16, int WAVES>
+__device__ __forceinline__ void decide_spread(
+    const int b, const int d0, unsigned fl, const int begin, const int end, const int rows_begin, const int rows_end,
+    const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T, int n_rows, int n_draft, const float* __restrict__ uniforms,
+    float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
+    int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
+    const SegHeader* __restrict__ table, int stride, const unsigned long long* __restrict__ found)
+{
+    __shared__ int s_first;
+    __shared__ unsigned s_flags;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int64_t t0 = (int64_t)d0 + b;
+    const float c = 1.4426950408889634f * inv_T;
+    const double cd = 1.4426950408889634 * (double)inv_T;
+    if (tid == 0) { s_first = end; s_flags = 0; }
+    __syncthreads();
+    float M = 0.f;
+    double S = 1.0;
+    int64_t wait_lse = -1;                            // the row whose log-sum-exp is still to be written
+    auto write_lse = [&] { if (wait_lse >= 0 && tgt_lse && lane == 0) tgt_lse[wait_lse] = (float)((double)M * (double)inv_T + log(S)); };
+    for (int i = rows_begin + wave; i < rows_end; i += WAVES) {
+        const int64_t rt = t0 + i, rd = (int64_t)d0 + i;
+        const bool decides = i >= begin && i < end;
+        const bool outside = rt < 0 || rt >= n_rows;
+        if (outside || (decides && rd >= n_draft)) {  // (offsets that leave the call's rows, or its drafts: nothing is read or written there)
+            fl |= 8u;
+            if (decides && lane == 0) atomicMin(&s_first, i);
+            if (outside) continue;
+        }
+        const RowView rv = row_view<BF16>(tgt_logits, ld, rt, V);
+        const int n_seg = stats_segments((rv.L + Vec<BF16>::N - 1) / Vec<BF16>::N);
+        const float2* const table_row = reinterpret_cast<const float2*>(table + 1) + rt * (int64_t)stride;
+        const unsigned long long at = get_shared(found + 2 * rt), qh_bits = get_shared(found + 2 * rt + 1);    // (used where the row decides)
+        const float u_t = uniforms[rt];
+        TableStats stats;
+        stats.load<true>(table_row, n_seg);
+        write_lse();
+        stats.combine<true>(table_row, n_seg, c, M, S);
+        wait_lse = rt;
+        const float S_t = (float)S;
+        if (lane == 0) {
+            tgt_max[rt] = M;
+            tgt_sum[rt] = S_t;
+            if (i >= begin && i <= end && (!(fabsf(M) < __builtin_huge_valf()) || !(S_t > 0.f) || !(S_t < __builtin_huge_valf()))) fl |= 2u;
+            if (decides && rd < n_draft) {
+                const unsigned f = (unsigned)(at >> 32);
+                const bool bad = f & 8u;
+                const double qh = __longlong_as_double((long long)qh_bits), u = (double)u_t;
+                const double p = bad ? 0.0 : exp_emit(__uint_as_float((unsigned)at), M, cd) / (double)S_t;
+                fl |= f;
+                if (bad || !(u < 1.0) || !(qh > 0.0 ? (u * qh < p) : true)) atomicMin(&s_first, i);            // (accept_sequence's test)
+                if (p_tok) p_tok[rd] = (float)p;
+                if (q_tok) q_tok[rd] = (float)qh;
+            }
+        }
+    }
+    if (fl) atomicOr(&s_flags, fl);
+    __syncthreads();
+    if (tid == 0) {
+        n_accept[b] = s_first;
+        flags[b] = s_flags;
+    }
+    write_lse();
 }
 
 
@@ -560,7 +699,8 @@ struct __align__(16) SegResidualShared {
 // by_sequence: the table holds one row per sequence, the one it draws from (launch_residual_split).
 // RT: threads (whole waves from thread 0 on) that run this, at least k / 4: every wave more is one more that goes through the
 // chain of scans and barriers, four instructions' time each once a SIMD holds several (residual_seg_threads).
-template <bool BF16, int RT>
+// SHARED: the table was written by other workgroups of this launch (and has no header).
+template <bool BF16, int RT, bool SHARED = false>
 __device__ __forceinline__ void residual_seg_sequence(
     const int b, const int j_in, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const float* __restrict__ tgt_max, const SegHeader* __restrict__ table,
@@ -594,7 +734,8 @@ __device__ __forceinline__ void residual_seg_sequence(
     // Everything that depends only on the two rows is asked for at once (one trip to memory): the table's header
     // (checked below), the target row's maximum, the record's count and mass, this thread's entries of the record and
     // its entries of the segment table.
-    const SegHeader hd = *table;
+    SegHeader hd{kSegMagicSplit, seg_vecs, stride, 0x7FFFFFFF};
+    if (!SHARED) hd = *table;
     const float M = s_stats ? s_stats[min(j, kSplitStatsRows - 1)].M : tgt_max[rt];
     double S = s_stats ? s_stats[min(j, kSplitStatsRows - 1)].S : 0.0;
     const bool known = S > 0.0 && S < (double)__builtin_huge_valf();       // (else: the sum over the table's rows below)
@@ -623,7 +764,7 @@ __device__ __forceinline__ void residual_seg_sequence(
     for (int u = 0; u < (kMaxSegTable + RT - 1) / RT; ++u) {
         const int sg = u * RT + tid;
         my_seg[u] = make_float2(0.f, 0.f);
-        if (table_ok && sg < n_seg) my_seg[u] = seg_row[sg];
+        if (table_ok && sg < n_seg) my_seg[u] = SHARED ? get_shared(&seg_row[sg]) : seg_row[sg];
     }
     // ... and, one trip later, the target's logit at each of this thread's record entries
     float my_z[SP];

@@ -183,14 +183,15 @@ inline StatsShape split_stats_shape(int dtype, int V) {
 }
 inline bool split_stats_serves(int64_t rows, int V) { return rows >= 1 && rows <= kSplitStatsRows && V >= kSplitMinV; }
 // Calls that are given no workspace and would need one for their statistics alone.  A verification without a draw gains less
-// (its second launch is there either way; the draw that the table serves is another call's), row_stats pays a second launch.  us, one
+// (its second launch is there either way; the draw that the table serves is another call's).  us, one
 // workgroup per row / spread, device time:
 //   * verification, fp32: rows of 16,384: 9.4 / 10.6 (160 rows), 20,000: 10.6 / 9.8 (64), 10.8 / 11.0 (192), 32,000: 10.9 / 10.5 (128),
 //     12.0 / 12.3 (224), 64,000: 13.6 / 12.9 (128), 14.5 / 14.8 (192), 151,936: 22.5 / 21.9 (160), 24.4 / 24.7 (192);
 //     bf16: 16,384: 9.6 / 10.9 (160), 20,000: 10.2 / 9.8 (128), 10.3 / 10.5 (224), 32,000: 10.3 / 10.7 (160), 64,000: 12.6 / 12.3 (192),
 //     151,936: 18.6 / 16.8 (192), 18.7 / 18.3 (224);
-//   * row_stats: fp32: 32,000: 6.5 / 8.1 (64), 64,000: 9.2 / 8.4 (64), 9.4 / 10.2 (128), 151,936: 17.4 / 16.9 (128), 18.6 / 19.6 (160);
-//     bf16: 64,000: 8.1 / 8.3 (64), 151,936: 14.5 / 13.4 (160), 14.6 / 14.8 (192).
+//   * row_stats (launch_row_stats_spread), on the device alone and called in a row: fp32: 33,001: 6.4 / 4.5, 6.4 / 7.5 (8 rows), 64,000: 6.9 / 5.8, 9.7 / 7.4 (64),
+//     151,936: 14.3 / 14.7, 14.5 / 14.5 (128); bf16: 33,001: 6.5 / 5.3, 6.5 / 7.6 (96), 64,000: 6.9 / 4.4, 6.9 / 7.6 (8), 151,936: 11.4 / 11.1 (160), 14.6 / 14.3 (192).
+//     (Where calls in a row are the slower ones it is the host, which allocates the scratch.)
 inline bool verify_scratch_serves(int dtype, int64_t rows, int V) {
     if (!split_stats_serves(rows, V) || V < 20000) return false;
     return rows <= (dtype != 1 ? 160 : V >= 64000 ? kSplitStatsRows : 128);
@@ -243,6 +244,41 @@ inline size_t round_seg_table_bytes(int dtype, int64_t rows, int V) {
     return small > seg_table_bytes(dtype, rows, V) ? small : seg_table_bytes(dtype, rows, V);
 }
 
+// Scratch of the calls whose last workgroups go on (arrive_last): a table in the split layout and behind it, on a 16-byte boundary, the
+// groups' words, kArrivalStride bytes apart, one per row (row_stats), per sequence and one more (verify), per sequence (the draw without a table).
+// Workgroups per row, of `waves` waves, of these launches: no more of them in all than are on the chip at once, two of eight waves per CU (a
+// workgroup that waits for its arrival, 0.7 us, holds its place: with a workgroup for every eight segments a verification of 144 rows of 151,936
+// fp32 took 28.3 us, with these 19.5).
+constexpr int kSpreadGroups = 512;
+inline int spread_parts(int segments, int waves, int64_t rows) {
+    const int64_t most = (segments + waves - 1) / waves, fit = (int64_t)kSpreadGroups * 8 / waves / (rows > 0 ? rows : 1);
+    return (int)(fit < 1 ? 1 : fit < most ? fit : most);
+}
+// Where they serve, by the segments (4 KB) of the rows in all.  With few, two launches are a boundary of 1.5 us on the device and 2.5 to 3.5 us on the
+// host; with more, the rows stream faster from many small workgroups that wait for nothing.  us a call, two launches / one, on the device
+// alone and called in a row:
+//   * verification of a range of positions, up to 5500: fp32: 24 rows of 24,576: 6.6 / 6.1, 9.8 / 6.4; 48 of 64,000 (3024): 7.6 / 7.5, 10.1 / 7.5; 144 of 33,001
+//     (4752): 8.5 / 9.1, 10.1 / 8.8; 96 of 64,000 (6048): 8.4 / 9.5, 10.1 / 9.2; 144 of 151,936: 13.8 / 17.8, 14.1 / 17.8; bf16: 48 of 128,256 (3024): 8.2 /
+//     7.5, 10.2 / 7.6; 144 of 64,000 (4608): 9.4 / 9.6, 10.5 / 9.0;
+//   * of all positions, whose workgroups look their sequences up and all have rows to sum, up to 2000: fp32: 24 of 64,000 (1512): 6.8 / 7.2, 9.9 / 7.2; 48 of
+//     33,001: 7.3 / 7.3, 10.0 / 7.3; 24 of 128,256 (3024): 8.0 / 9.7, 9.9 / 9.4; bf16: 96 of 33,001 (1632): 8.2 / 8.6, 9.9 / 8.3; 48 of 128,256 (3024): 8.3 / 8.6;
+//   * the draw, up to 2500: fp32: 24 sequences of 33,001, k = 64: 8.3 / 7.5, 8.5 / 7.5; 64, k = 256 (2112): 9.7 / 9.0; 64 of 64,000 (4032): 10.1 / 10.8; bf16: 64 of 64,000
+//     (2048): 9.9 / 9.1; 64 of 151,936 (4800): 11.8 / 13.6.  And from 512 sequences on for records of 513 entries or more, whose workgroups sum a row alone:
+//     512 of 33,001, k = 700: 24.1 / 20.8, bf16 18.9 / 16.3, of 151,936 60.8 / 60.3, 39.2 / 34.3; shorter records (k = 64: 18.0 / 20.1) do not gain.
+constexpr int kOneLaunchRange = 5500, kOneLaunchVerify = 2000, kOneLaunchDraw = 2500;
+inline bool verify_one_launch(bool ranged, int dtype, int64_t rows, int V) { return rows * split_stats_shape(dtype, V).stride <= (ranged ? kOneLaunchRange : kOneLaunchVerify); }
+inline bool residual_one_launch(int dtype, int64_t B, int V, int k) {
+    return B * split_stats_shape(dtype, V).stride <= kOneLaunchDraw || (k > 512 && B >= 512);
+}
+inline size_t split_table_end(int dtype, int64_t rows, int V) { return (sizeof(SegHeader) + (size_t)rows * (size_t)split_stats_shape(dtype, V).stride * 8 + 15) / 16 * 16; }
+inline size_t row_stats_words_at(int dtype, int64_t rows, int V) { return split_table_end(dtype, rows, V); }
+inline size_t row_stats_scratch_bytes(int dtype, int64_t rows, int V) { return row_stats_words_at(dtype, rows, V) + (size_t)rows * kArrivalStride; }
+inline size_t verify_words_at(int dtype, int64_t rows, int V) { return split_table_end(dtype, rows, V); }
+inline size_t verify_found_at(int dtype, int64_t rows, int64_t B, int V) { return verify_words_at(dtype, rows, V) + (size_t)(B + 1) * kArrivalStride; }
+inline size_t verify_scratch_bytes(int dtype, int64_t rows, int64_t B, int V) { return verify_found_at(dtype, rows, B, V) + (size_t)rows * 16; }   // (16 bytes per position looked up)
+inline size_t residual_words_at(int dtype, int64_t B, int V) { return split_table_end(dtype, B, V); }
+inline size_t residual_scratch_bytes(int dtype, int64_t B, int V) { return residual_words_at(dtype, B, V) + (size_t)B * kArrivalStride; }
+
 // seg (nullable): the segment table, seg_stride entries per row
 hipError_t launch_row_stats(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
                             float* row_max, float* row_sum, float* row_lse, void* seg_table, hipStream_t stream);
@@ -254,6 +290,20 @@ hipError_t launch_row_stats_parts(const void* logits, int dtype, int64_t ld, int
 // ... and the statistics from it
 hipError_t launch_row_stats_finish(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
                                    const void* seg_table, float* row_max, float* row_sum, float* row_lse, hipStream_t stream);
+
+// both in one launch; scratch holds row_stats_scratch_bytes(...)
+hipError_t launch_row_stats_spread(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
+                                   void* scratch, float* row_max, float* row_sum, float* row_lse, hipStream_t stream);
+
+// launch_row_stats_parts and launch_accept in one launch; scratch holds verify_scratch_bytes(...)
+hipError_t launch_verify_spread(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
+                                int B, int64_t n_rows, const int32_t* seq_off, const int32_t* draft_tok,
+                                const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
+                                int k, int renorm, const float* q_scalar, const float* uniforms,
+                                float* tgt_max, float* tgt_sum, float* tgt_lse,
+                                int32_t* n_accept, float* p_tok, float* q_tok, uint32_t* flags,
+                                bool ranged, const int32_t* pos_begin, const int32_t* pos_end, int gamma_max,
+                                void* scratch, hipStream_t stream);
 
 // the same for the target rows pos_begin[b]..pos_end[b] of every sequence only (nullable: 0 / gamma_b)
 hipError_t launch_row_stats_range(const void* logits, int dtype, int64_t ld, int V, float temperature, int B,
@@ -280,13 +330,13 @@ hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V,
                            const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
                            int k, int renorm, const float* uniforms,
                            int32_t* out_tok, float* resid_mass, uint32_t* flags, const void* seg_table, int64_t n_rows, hipStream_t stream);
-// the same with a scratch table of its own (residual_split_serves): one launch spreads the sequences' rows at n_accept over
-// many workgroups, and the draw reads their segments
+// the same with a scratch table of its own (residual_split_serves): the sequences' rows at n_accept are spread over many workgroups, and the
+// draw reads their segments: in one launch where the scratch holds residual_scratch_bytes(...), in two where it holds the table alone
 hipError_t launch_residual_split(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
                                  int B, const int32_t* seq_off, const int32_t* n_accept, const float* tgt_max,
                                  const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
                                  int k, int renorm, const float* uniforms,
-                                 int32_t* out_tok, float* resid_mass, uint32_t* flags, void* scratch, int64_t n_rows, hipStream_t stream);
+                                 int32_t* out_tok, float* resid_mass, uint32_t* flags, void* scratch, size_t scratch_bytes, int64_t n_rows, hipStream_t stream);
 
 // (launch_accept: split_table non-null: the rows' statistics are formed from that table, tgt_max / tgt_sum / tgt_lse written;
 // all_rows: those of all n_rows rows of the call, else of the sequences' positions in the range)

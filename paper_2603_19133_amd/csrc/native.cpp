@@ -258,7 +258,7 @@ PyObject* n_scratch_bytes(PyObject*, PyObject* const* v, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// scratch(like, which, dtype, n_draft, B, V, k[, given]) -> uint8 tensor of picospec_scratch_bytes(...) bytes.  None where that is
+// scratch(like, which, dtype, n_draft, B, V, k[, given]) -> uint8 tensor of picospec_one_launch_bytes(...) bytes.  None where that is
 // 0, where the caller's workspace `given` holds as many, and where the library refuses that one (it still does).
 PyObject* n_scratch(PyObject*, PyObject* const* v, Py_ssize_t n) {
     HANDLE_TH_ERRORS
@@ -272,7 +272,7 @@ PyObject* n_scratch(PyObject*, PyObject* const* v, Py_ssize_t n) {
             const Args::Buffer given = a.buffer();
             if (given.p && (given.bytes >= bytes || ((uintptr_t)given.p & 15u) || given.bytes < picospec_workspace_bytes(which, dt, N + B, V, 0))) Py_RETURN_NONE;
         }
-        return THPVariable_Wrap(at::empty({(int64_t)bytes}, like(v[0], at::kByte)));
+        return THPVariable_Wrap(at::empty({(int64_t)picospec_one_launch_bytes(which, dt, N, B, V, k)}, like(v[0], at::kByte)));
     } catch (const BadArgument& e) {
         if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, e.what());
         return nullptr;

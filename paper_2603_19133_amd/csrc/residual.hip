@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
     int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags)
 {
-    const int first = accept_sequence<BF16>(blockIdx.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
+    const int first = accept_sequence<BF16>(blockIdx.x, (int)gridDim.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
                                             q_count, q_mass, k, renorm, nullptr, uniforms, tgt_max, tgt_sum,
                                             n_accept, p_tok, q_tok, flags, nullptr, nullptr);
     residual_sequence<BF16>(blockIdx.x, first, tgt_logits, ld, V, inv_T, seq_off, tgt_max, tgt_sum,
@@ -64,6 +64,29 @@ __global__ __launch_bounds__(RT) void residual_seg_kernel(
                                 q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, nullptr, by_sequence);
 }
 
+// The draw that is given no table in one launch: the workgroups that sum a sequence's row (row b of the table) arrive at its word, and the last
+// of them draws.
+template <bool BF16, int RT>
+__global__ __launch_bounds__(RT) void residual_spread_kernel(
+    const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T, int n_rows,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept,
+    const float* __restrict__ tgt_max, SegHeader* __restrict__ table, int seg_vecs, int stride, unsigned long long* __restrict__ words,
+    const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
+    const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
+    const float* __restrict__ uniforms,
+    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ flags)
+{
+    const int b = blockIdx.y, d0 = seq_off[b], g = max(seq_off[b + 1] - d0, 0), j = n_accept[b];
+    const int64_t row = (int64_t)d0 + b + min(max(j, 0), g);          // (as the draw takes it)
+    const bool streams = row >= 0 && row < n_rows;                    // (offsets that leave the call's rows)
+    auto open = [&] { if (threadIdx.x == 0) open_arrival(arrival_word(words, b)); };
+    if (streams) row_stats_shared<BF16, RT / kWave>(row, b, (int)blockIdx.x, (int)gridDim.x, tgt_logits, ld, V, inv_T, reinterpret_cast<float2*>(table + 1), stride, open);
+    else open();
+    if (!arrive_last(arrival_word(words, b), gridDim.x, threadIdx.x == 0)) return;
+    residual_seg_sequence<BF16, RT, true>(b, j, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
+                                          q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, nullptr, true);
+}
+
 // SPLIT: the table stands in the split layout, and the rows' statistics are formed here.
 template <bool BF16, bool SPLIT, int RT>
 __device__ __forceinline__ void decide_seg(
@@ -78,7 +101,7 @@ __device__ __forceinline__ void decide_seg(
 {
     __shared__ SplitStats s_stats[SPLIT ? kSplitStatsRows : 1];
     int2 rows = make_int2(0, 0);
-    const int first = accept_sequence<BF16, SPLIT>(blockIdx.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
+    const int first = accept_sequence<BF16, SPLIT>(blockIdx.x, (int)gridDim.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
                                                    q_count, q_mass, k, renorm, nullptr, uniforms, tgt_max, tgt_sum,
                                                    n_accept, p_tok, q_tok, flags, nullptr, nullptr,
                                                    tgt_lse, table, seg_vecs, stride, n_rows, true, SPLIT ? s_stats : nullptr, &rows);
@@ -154,12 +177,25 @@ hipError_t launch_residual_split(const void* tgt_logits, int dtype, int64_t ld, 
                                  int B, const int32_t* seq_off, const int32_t* n_accept, const float* tgt_max,
                                  const int32_t* q_idx, const float* q_prob, const int32_t* q_count, const float* q_mass,
                                  int k, int renorm, const float* uniforms,
-                                 int32_t* out_tok, float* resid_mass, uint32_t* flags, void* scratch, int64_t n_rows, hipStream_t stream)
+                                 int32_t* out_tok, float* resid_mass, uint32_t* flags, void* scratch, size_t scratch_bytes, int64_t n_rows, hipStream_t stream)
 {
+    const StatsShape sh = split_stats_shape(dtype, V);
+    const float inv_T = 1.0f / temperature;
+    if (residual_one_launch(dtype, B, V, k) && scratch_bytes >= residual_scratch_bytes(dtype, B, V)) {
+        const dim3 grid(spread_parts(sh.stride, residual_seg_threads(k) / 64, B), B);
+        unsigned long long* const words = (unsigned long long*)((char*)scratch + residual_words_at(dtype, B, V));
+#define PICOSPEC_RESIDUAL_SPREAD(BF, RT) \
+        hipLaunchKernelGGL((residual_spread_kernel<BF, RT>), grid, dim3(RT), 0, stream, tgt_logits, ld, V, inv_T, (int)n_rows, seq_off, n_accept, tgt_max, (SegHeader*)scratch, sh.seg_vecs, sh.stride, words, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags)
+        static_assert(kResidualSplitK <= 2048, "records for 512 threads");
+        if (residual_seg_threads(k) == 256) { if (dtype == 1) PICOSPEC_RESIDUAL_SPREAD(true, 256); else PICOSPEC_RESIDUAL_SPREAD(false, 256); }
+        else                                { if (dtype == 1) PICOSPEC_RESIDUAL_SPREAD(true, 512); else PICOSPEC_RESIDUAL_SPREAD(false, 512); }
+#undef PICOSPEC_RESIDUAL_SPREAD
+        return hipGetLastError();
+    }
     if (hipError_t e = launch_row_stats_parts(tgt_logits, dtype, ld, (int)n_rows, V, temperature, B, 0, seq_off, nullptr, nullptr, scratch, stream, n_accept))
         return e;
-    return launch_residual_seg(tgt_logits, dtype, ld, V, 1.0f / temperature, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass,
-                               k, renorm, uniforms, out_tok, resid_mass, flags, scratch, split_stats_shape(dtype, V), true, stream);
+    return launch_residual_seg(tgt_logits, dtype, ld, V, inv_T, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass,
+                               k, renorm, uniforms, out_tok, resid_mass, flags, scratch, sh, true, stream);
 }
 
 hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,

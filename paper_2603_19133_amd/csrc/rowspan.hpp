@@ -76,6 +76,10 @@ __host__ __device__ inline int stats_parts(int segments) { return (segments + 4 
 // vectors of a row of V elements that lies off the 16-byte boundary, the most it can span: what a launch is sized for
 __host__ __device__ inline int row_vecs_max(bool bf16, int V) { return (int)(((int64_t)V * (bf16 ? 2 : 4) + 15) / 16) + 1; }
 
+// Bytes between the words at which groups of workgroups arrive (common.hpp): atomics on one line are done one after the other, and with
+// the words side by side 32 groups of 48 workgroups took 50 us.
+constexpr size_t kArrivalStride = 256;
+
 template <bool BF16>
 struct ResidualGeom {
     static constexpr int N = BF16 ? 8 : 4;
