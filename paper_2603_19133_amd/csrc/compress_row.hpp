@@ -65,7 +65,6 @@ constexpr unsigned kIdMask = (1u << kIdBits) - 1u;
 constexpr int kSortMaxBin = 128;            // beyond this bin size the ordering falls back to a sorting network
 constexpr int kCoarseLog2 = 9;
 constexpr int kCoarse = 1 << kCoarseLog2;   // coarse ranges that steer the fine bins of the rank sort
-constexpr int kCoarseAll = kCoarse;
 
 static_assert(kMaxK <= kCapBig && (kMaxK & (kMaxK - 1)) == 0, "the sorting network pads to a power of two inside the buffer");
 static_assert(kFine <= 32768, "bin and arrival order of a candidate share one register");
@@ -306,12 +305,11 @@ __device__ __forceinline__ void order_prepare(SH& sh, int n) {
 // the gap from v to the next lower bf16 value is at least 2^-8 |v| and v - 2^-8 |v| is an fp32 value, so w, rounded, stays
 // between the two and falls with the id, and p never decreases along the wanted order.  Equal values next to zero share a place; a row
 // with a bin too crowded comes back as nullptr, its candidates where they were, to be ordered by keys.
-// CAND_PER * kT >= n slots of candidates, FINE fine bins and COARSE ranges: the whole buffer's by default; a caller that
-// knows n to be small has less to clear, scan and skip (split.hip).
-template <bool BF16, int CAND_PER = 0, int FINE = kFine, int COARSE = kCoarse, bool LINEAR = false, class SH>
+// CAND_PER * kT >= n slots of candidates: the whole buffer's by default; a caller that knows n to be small has less to skip
+// (split.hip).
+template <bool BF16, int CAND_PER = 0, bool LINEAR = false, class SH>
 __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int V, uint32_t key_lo, uint32_t key_hi) {
-    constexpr int kFine = FINE, kCoarse = COARSE, kBinsPer = FINE / 2 / kT;       // (two 16-bit fine bins to a word)
-    static_assert(FINE % (2 * kT) == 0 && FINE <= 2 * kBins && COARSE <= kCoarseAll, "the histograms of the buffer");
+    static_assert(kFine / 2 / kT == kBinsPer, "two 16-bit fine bins to a word");
     constexpr int kCap = SH::kCap, kCandPer = CAND_PER ? CAND_PER : kCap / kT;
     constexpr int kSortPer = kCandPer < SH::kRecMax / kT ? kCandPer : SH::kRecMax / kT;
     static_assert((kSortPer & (kSortPer - 1)) == 0, "the sorting network's padded length fits the slots");
@@ -1450,7 +1448,7 @@ __device__ __forceinline__ void compress_row(
         return;
     }
     const int n = min(sel.n_held, k);
-    const uint64_t* sorted = order_top_k<BF16, 0, kFine, kCoarse, BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+    const uint64_t* sorted = order_top_k<BF16, 0, BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
     if (BF16 && !sorted) {
         order_row_again<BF16, SMALL>(row, sel.n_held, sel.fill, sel.key_lo, sel.key_hi, sel.M, sel.S, V, inv_T, k, top_p, idx, prob, count, mass);
         return;

@@ -14,8 +14,8 @@
 //     the record with the code of the unsplit kernels.  The answer is exact iff the k-th value lies above every workgroup's
 //     threshold, which is tested; a row that fails it (or whose lists overflow) is compressed from the start by the
 //     unsplit kernels' code in the same workgroup.
-// Device time of a call, one workgroup per row -> split: one bf16 row of 128,256, k = 10: 25.5 -> 4.8 + 5.1 us; 64 fp32 rows of
-// 151,936, k = 1024: 31.0 -> 10.5 + 8.4 us, of which the first launch reads 39 MB (5.8 us at 6.8 TB/s).  The line between the two
+// Device time of a call, one workgroup per row -> split: one bf16 row of 128,256, k = 10: 25.5 -> 4.8 + 4.3 us; 64 fp32 rows of
+// 151,936, k = 1024: 31.0 -> 10.5 + 6.6 us, of which the first launch reads 39 MB (5.8 us at 6.8 TB/s).  The line between the two
 // is split_plan's.
 #include "compress_row.hpp"
 
@@ -337,6 +337,120 @@ __device__ __attribute__((noinline)) void split_row_again(
                               uniform(k), uniform(top_p), uniform(idx), uniform(prob), uniform(count), uniform(mass), uniform(lse), uniform(rank_opt));
 }
 
+// The record of a row whose candidates are few enough to stay in the registers they were loaded into: SLOTS per thread, those of them valid
+// of which `valid` has the bit.  As order_top_k and emit_row, with less between: one histogram, on a linear scale of the values (bf16: with
+// the id, as its LINEAR places), whose bins hold one or two candidates of the upper end of any smooth distribution; the candidates of the
+// bins up to the one that holds the n-th are laid out bin by bin, and whoever reads position i of that ranks it in its bin and writes it:
+// positions i and their ranks are a bin apart, so the stores are as good as in order.  Returns false with nothing written if a bin is too
+// crowded (values on a grid, an outlier that stretches the scale); else whether the n-th lies above `above`, below which candidates are missing.
+// `meanwhile` forms the row's sum of exponentials while the histogram's atomics are on their way.
+// Bound by the chain of barriers, six of them (ten before): the finish of one row of 32,000 fp32, k = 64: 4.5 -> 3.6 us from its first instruction, of 64 of
+// 151,936, k = 1024: 7.4 -> 5.6; a round of that row 16.4 -> 15.6, the draft of those 22.0 -> 20.0.
+constexpr int kFewBins = kBins, kFewMost = 32;          // (a bin per word of the histogram; entries of a bin that are ranked by comparing all)
+enum class Few { crowded, missing, done };
+template <bool BF16, int SLOTS, class SH, class F>
+__device__ __forceinline__ Few finish_few(
+    SH& sh, const uint2 (&e)[SLOTS], const unsigned valid, const int n, const int V, const float low, const float M, const uint32_t above,
+    const int64_t row, const int k, const bool direct, const float inv_T, int32_t* __restrict__ idx, float* __restrict__ prob,
+    int32_t* __restrict__ count, float* __restrict__ mass, const F& meanwhile)
+{
+    static_assert(kFewBins == 4 * kT, "four bins per thread");
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    uint64_t* const buf = reinterpret_cast<uint64_t*>(sh.cand_val);
+    const float id_step = __uint_as_float((unsigned)(127 - 8 - (32 - __clz(V - 1))) << 23);
+    const float scale = (float)(kFewBins - 1) * __builtin_amdgcn_rcpf((M - low) + (BF16 ? fabsf(low) * 0.0078125f : 0.f));
+    const float top = M * scale;
+    auto bin_of = [&](float v, unsigned id) {
+        const float w = BF16 ? fmaf(-(float)id, fabsf(v) * id_step, v) : v;
+        unsigned b;
+        asm("v_cvt_u32_f32 %0, %1" : "=v"(b) : "v"(fmaf(w, -scale, top)));       // (saturates)
+        return min(b, (unsigned)(kFewBins - 1));
+    };
+    unsigned meta[SLOTS];                              // (bin << 16) | arrival order within the bin
+#pragma unroll
+    for (int u = 0; u < SLOTS; ++u) {
+        meta[u] = 0;
+        if (valid >> u & 1u) {
+            const unsigned b = bin_of(__uint_as_float(e[u].x), e[u].y);
+            meta[u] = b << 16 | atomicAdd(&sh.hist[b], 1u);
+        }
+    }
+    const double S = meanwhile();
+    __syncthreads();
+    const uint4 h4 = *reinterpret_cast<const uint4*>(&sh.hist[4 * tid]);
+    const int h[4] = {(int)h4.x, (int)h4.y, (int)h4.z, (int)h4.w};
+    const int loc = (h[0] + h[1]) + (h[2] + h[3]), incl = wave_scan_incl(loc);
+    if (lane == kWave - 1) sh.wtot[wave] = incl;
+    __syncthreads();
+    int at = incl - loc;
+#pragma unroll
+    for (int w = 0; w < kW; ++w) at += w < wave ? sh.wtot[w] : 0;
+    int big = 0;
+    unsigned first[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        first[j] = (unsigned)at;
+        if (at < n) {
+            big = max(big, h[j]);
+            if (at + h[j] >= n) { sh.piv_bin = 4 * tid + j; sh.piv_before = at + h[j]; }
+        }
+        at += h[j];
+    }
+    *reinterpret_cast<uint4*>(&sh.hist[4 * tid]) = make_uint4(first[0], first[1], first[2], first[3]);
+    if (big > kFewMost) sh.maxbin = big;
+    __syncthreads();
+    if (sh.maxbin > kFewMost) return Few::crowded;     // (uniform)
+    const int piv = sh.piv_bin, n_keep = sh.piv_before;
+#pragma unroll
+    for (int u = 0; u < SLOTS; ++u)
+        if ((valid >> u & 1u) && (int)(meta[u] >> 16) <= piv) buf[sh.hist[meta[u] >> 16] + (meta[u] & 0xFFFFu)] = composite<BF16>(e[u].x, e[u].y);
+    __syncthreads();
+    uint64_t* const ordered = buf + SH::kCap / 2;
+    const double cd = 1.4426950408889634 * (double)inv_T, invS = 1.0 / S;
+    int32_t* const idx_row = idx + row * (int64_t)k;
+    float* const prob_row = prob + row * (int64_t)k;
+    double my_mass = 0.0;
+    for (int i = tid; i < n_keep; i += kT) {
+        const uint64_t c = buf[i];
+        const float v = __uint_as_float(bits_of_short_key<BF16>((uint32_t)(c >> kIdBits)));
+        const unsigned id = kIdMask - ((uint32_t)c & kIdMask), b = bin_of(v, id);
+        const int s = (int)sh.hist[b], end = (int)b < piv ? (int)sh.hist[b + 1] : n_keep;
+        int larger = 0;
+        for (int q = s; q < end; q += 4) {             // (four bin-mates per round trip to LDS)
+            uint64_t m[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m[u] = buf[min(q + u, SH::kCap / 2 - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) larger += (q + u < end && m[u] > c) ? 1 : 0;
+        }
+        const int pos = s + larger;
+        if (pos >= n) continue;
+        if (pos == n - 1 && (uint32_t)(c >> kIdBits) <= above) sh.overflowed = 1;
+        if (direct) {
+            const float p = (float)(exp_emit(v, M, cd) * invS);
+            idx_row[pos] = (int)id;
+            prob_row[pos] = p;
+            my_mass += (double)p;
+        } else {
+            ordered[pos] = c;
+        }
+    }
+    if (direct) {
+        const double wm = wave_sum(my_mass);
+        if (lane == 0) sh.red[wave] = wm;
+    }
+    __syncthreads();
+    if (direct && tid == 0) {
+        double tm = 0.0;
+#pragma unroll
+        for (int w = 0; w < kW; ++w) tm += sh.red[w];
+        mass[row] = (float)tm;
+        count[row] = n;
+    }
+    return sh.overflowed ? Few::missing : Few::done;
+}
+
 template <bool BF16>
 __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
@@ -354,61 +468,97 @@ __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
     const uint2* const list = lists + row * n_lists * (int64_t)cap;
     const float c = 1.4426950408889634f * inv_T;
     // ---- Everything is asked for at once: the lists' heads (by every wave for itself, one per lane) and the first kAhead * kT
-    //      slots of the row's lists, whatever those turn out to hold.  Slot f of the row's array: position f mod cap of list
-    //      f / cap.
+    //      slots of the row's lists, whatever those turn out to hold.  Slot f of the row's lists: position f / n_lists of list f mod n_lists,
+    //      so that what the lists do not fill are the last slots.
     constexpr int kAhead = 8;
     const int n_slots = n_lists * cap;
-    const float per_list = 1.0f / (float)cap;
-    uint4 h = make_uint4(0xFF800000u, 0xFF800000u, 0xFF800000u, 0u);
-    double s = 0.0;
-    if (lane < n_lists) {
-        h = *reinterpret_cast<const uint4*>(head + lane);
-        s = head[lane].s;
-    }
+    const float per_round = 1.0f / (float)n_lists;
+    auto place_of = [&](int f, int& l, int& q) { q = (int)(((float)f + 0.5f) * per_round); l = f - q * n_lists; };     // (f < 2^15: exact)
+    const uint4 h = *reinterpret_cast<const uint4*>(head + min(lane, n_lists - 1));
+    const double s_head = head[min(lane, n_lists - 1)].s;
     uint2 e[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
-        e[u] = make_uint2(0u, 0u);
-        if (u * kT < n_slots && u * kT + tid < n_slots) e[u] = list[u * kT + tid];
+        int l, q;
+        place_of(min(u * kT + tid, n_slots - 1), l, q);
+        if (u * kT < n_slots) e[u] = list[l * cap + q];
     }
-    const float mx = __uint_as_float(h.x), tau = __uint_as_float(h.y), ref = mx > kNegInf ? __uint_as_float(h.z) : kNegInf;
-    const int held = (int)h.w;
-    const float M = wave_max(mx), T = wave_max(tau), R = wave_max(ref);
-    const float low = -wave_max(lane < n_lists ? -tau : kNegInf);
+    zero_hist(sh);
+    if (tid == 0) { sh.maxbin = 0; sh.overflowed = 0; }
+    const bool mine = lane < n_lists;
+    const float mx = mine ? __uint_as_float(h.x) : kNegInf, tau = mine ? __uint_as_float(h.y) : kNegInf;
+    const float ref = mx > kNegInf ? __uint_as_float(h.z) : kNegInf;
+    const int held = mine ? (int)h.w : 0;
+    const float M = wave_max(mx), T = wave_max(tau);
+    const float low = -wave_max(mine ? -tau : kNegInf);
     const bool over = __ballot(held > cap) != 0ull;
     const int incl = wave_scan_incl(held), total = read_lane(incl, kWave - 1);
-    const int first = incl - held;               // first slot, in the ordering's buffer, of list `lane`
-    double S = wave_sum(ref > kNegInf ? ldexp(s, max((int)(ref - R), -2000)) : 0.0);     // (whole exponents: exact)
-    S *= exp2_split((double)R - (double)M * (double)c);
-
-    RowSelection sel{total, total < k, true, M, S, short_key<BF16>(__float_as_uint(low)), short_key<BF16>(__float_as_uint(M))};
-    bool ok = !over && total <= SH::kCap && total >= 1 && M > kNegInf && M < __builtin_huge_valf() && S > 0.0 && S < 1e300 &&
+    // (the share's sums meet in fp64; whole exponents: exact)
+    auto sum_of_lists = [&] {
+        const float R = wave_max(ref);
+        const double S = wave_sum(ref > kNegInf ? ldexp(s_head, max((int)(ref - R), -2000)) : 0.0);
+        return S * exp2_split((double)R - (double)M * (double)c);
+    };
+    const int n = min(total, k);
+    const bool fill = total < k;
+    bool ok = !over && total <= SH::kCap && total >= 1 && M > kNegInf && M < __builtin_huge_valf() &&
               (total >= k || T == kNegInf);      // (a threshold of -inf: every entry above -inf is listed)
-    if (ok) {
-        auto take = [&](int f, uint2 t) {
-            const int l = (int)(((float)f + 0.5f) * per_list), q = f - l * cap;     // (f < 2^15: exact)
-            const int n = __shfl(held, l, kWave), s0 = __shfl(first, l, kWave);
-            if (f < n_slots && q < n) { sh.cand_val[s0 + q] = t.x; sh.cand_id[s0 + q] = t.y; }
-        };
+    double S = 0.0;
+    auto sound = [&] { return S > 0.0 && S < 1e300; };
+    const float spread = (float)(kFewBins - 1) / (M - low);
+    if (ok && n_slots <= kAhead * kT && low > kNegInf && M > low && spread < __builtin_huge_valf() && fabsf(M) * spread < 1e9f) {
+        const bool use_top_p = top_p > 0.f && top_p < 1.f;
+        unsigned valid = 0;
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) if (u * kT < n_slots) take(u * kT + tid, e[u]);
-        for (int f0 = kAhead * kT; f0 < n_slots; f0 += kT) take(f0 + tid, f0 + tid < n_slots ? list[f0 + tid] : make_uint2(0u, 0u));
-        order_prepare(sh, total);
-        if (tid == kT - 1) lse[row] = (float)((double)M * (double)inv_T + log(S));
+        for (int u = 0; u < kAhead; ++u) {
+            int l, q;
+            const int f = u * kT + tid;
+            place_of(f, l, q);
+            if (u * kT < n_slots) valid |= f < n_slots && q < __shfl(held, l, kWave) ? 1u << u : 0u;
+        }
+        __syncthreads();
+        const Few did = finish_few<BF16>(sh, e, valid, n, V, low, M, T == kNegInf ? 0u : short_key<BF16>(__float_as_uint(T)), row, k,
+                                         !use_top_p && !fill, inv_T, idx, prob, count, mass, [&] { S = sum_of_lists(); return S; });
+        if (did == Few::done && sound()) {
+            if (tid == kT - 1) lse[row] = (float)((double)M * (double)inv_T + log(S));
+            if (use_top_p || fill) emit_row<BF16>(sh, reinterpret_cast<uint64_t*>(sh.cand_val) + SH::kCap / 2, row, n, fill, M, S, inv_T, k, top_p, idx, prob, count, mass);
+            return;
+        }
+        ok = did == Few::crowded;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // (what was written is written again)
         __syncthreads();
     }
     if (ok) {
-        const int n = min(sel.n_held, k);
+        S = sum_of_lists();
+        ok = sound();
+    }
+    if (ok) {
+        const int first = incl - held;           // first slot, in the ordering's buffer, of list `lane`
+        auto take = [&](int f, uint2 t) {
+            int l, q;
+            place_of(f, l, q);
+            const int m = __shfl(held, l, kWave), s0 = __shfl(first, l, kWave);
+            if (f < n_slots && q < m) { sh.cand_val[s0 + q] = t.x; sh.cand_id[s0 + q] = t.y; }
+        };
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) if (u * kT < n_slots) take(u * kT + tid, e[u]);
+        for (int f0 = kAhead * kT; f0 < n_slots; f0 += kT) {
+            int l, q;
+            place_of(min(f0 + tid, n_slots - 1), l, q);
+            take(f0 + tid, list[l * cap + q]);
+        }
+        order_prepare(sh, total);
+        if (tid == kT - 1) lse[row] = (float)((double)M * (double)inv_T + log(S));
+        __syncthreads();
+        const uint32_t key_lo = short_key<BF16>(__float_as_uint(low)), key_hi = short_key<BF16>(__float_as_uint(M));
         const uint64_t* sorted;
-        if (sel.n_held <= kT)          sorted = order_top_k<BF16, 1, 1024, 128>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
-        else if (sel.n_held <= 2 * kT) sorted = order_top_k<BF16, 2, 2048, 256>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
-        else if (sel.n_held <= 4 * kT) sorted = order_top_k<BF16, 4>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
-        else if (sel.n_held <= 8 * kT) sorted = order_top_k<BF16, 8>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
-        else                           sorted = order_top_k<BF16>(sh, sel.n_held, n, V, sel.key_lo, sel.key_hi);
+        if (total <= 4 * kT)      sorted = order_top_k<BF16, 4>(sh, total, n, V, key_lo, key_hi);
+        else if (total <= 8 * kT) sorted = order_top_k<BF16, 8>(sh, total, n, V, key_lo, key_hi);
+        else                      sorted = order_top_k<BF16>(sh, total, n, V, key_lo, key_hi);
         // the lists hold every element above T: they hold the top k iff the k-th lies above it
         // (bf16: the short key of a T between two values is that of the lower one)
         if (T == kNegInf || (uint32_t)(sorted[n - 1] >> kIdBits) > short_key<BF16>(__float_as_uint(T))) {
-            emit_row<BF16>(sh, sorted, row, n, sel.fill, sel.M, sel.S, inv_T, k, top_p, idx, prob, count, mass);
+            emit_row<BF16>(sh, sorted, row, n, fill, M, S, inv_T, k, top_p, idx, prob, count, mass);
             return;
         }
     }
