@@ -63,6 +63,7 @@ constexpr int kFine = 2 * kBins;            // fine bins of the rank sort: 16-bi
 constexpr int kIdBits = 20;                 // ids < 2^20 (kMaxV)
 constexpr unsigned kIdMask = (1u << kIdBits) - 1u;
 constexpr int kSortMaxBin = 128;            // beyond this bin size the ordering falls back to a sorting network
+constexpr int kDirectMaxBin = 24;           // ... and beyond this one a row whose bins were not steered by the coarse ranges is counted again with them
 constexpr int kCoarseLog2 = 9;
 constexpr int kCoarse = 1 << kCoarseLog2;   // coarse ranges that steer the fine bins of the rank sort
 
@@ -344,93 +345,134 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
     static_assert(kCap < 65536, "positions and bin counts are kept in 16 bits");
     // (order_prepare and a barrier behind it have cleared the histograms)
     uint64_t c[kCandPer];
-    uint32_t place[kCandPer];
-#pragma unroll
-    for (int j = 0; j < kCandPer; ++j) {
-        const int i = tid + j * kT;
-        c[j] = 0; place[j] = 0;
-        if (i < n) {
-            const uint32_t bits = sh.cand_val[i], id = sh.cand_id[i];
-            c[j] = composite<BF16>(bits, id);
-            if (LINEAR && linear) {
-                const float v = __uint_as_float(bits), w = fmaf(-(float)id, fabsf(v) * id_step, v);
-                asm("v_cvt_u32_f32 %0, %1" : "=v"(place[j]) : "v"(fmaf(w, -lin, lin_max)));     // (saturates)
-            } else {
-                place[j] = ib < 32 ? ((key_hi - short_key<BF16>(bits)) << ib) | (id >> id_drop) : (id >> id_drop);
-            }
-            atomicAdd(&sh.coarse[range_of(place[j])], 1u);
-        }
-    }
-    __syncthreads();
-    // fine bins per coarse range, in proportion to its count (at least one where there is a candidate); one
-    // wave builds the table, kCoarse / 64 consecutive ranges per lane
-    if (wave == 0) {
-        constexpr int kPerLane = kCoarse / kWave;
-        constexpr int kShared = kFine - kCoarse - kCoarse / 2;      // leaves room for the "at least one" and for rounding
-        const float share = (float)kShared / (float)n;
-        unsigned nf[kPerLane], loc = 0;
-#pragma unroll
-        for (int u = 0; u < kPerLane; ++u) {
-            const unsigned cnt = sh.coarse[lane * kPerLane + u];
-            nf[u] = cnt ? max(1u, (unsigned)((float)cnt * share)) : 0u;
-            loc += nf[u];
-        }
-        unsigned first = wave_scan_incl(loc) - loc;                 // first fine bin of this lane's ranges
-#pragma unroll
-        for (int u = 0; u < kPerLane; ++u) { sh.coarse[lane * kPerLane + u] = (nf[u] << 16) | first; first += nf[u]; }
-    }
-    __syncthreads();
     int meta[kCandPer];                      // (fine bin << 16) | arrival order within the bin; -1: no candidate
+    // (bin 2w in the low half of word w, bin 2w+1 in the high half: a bin holds fewer than 2^16 candidates, so
+    //  the low half never carries into the high one)
+    auto enter = [&](int bin) {
+        const int half = (bin & 1) * 16;
+        return (bin << 16) | (int)((atomicAdd(&sh.hist[bin >> 1], 1u << half) >> half) & 0xFFFFu);
+    };
+    auto by_ranges = [&](bool held) {        // the fine bins by way of the coarse ranges; held: the composites are formed already
+        uint32_t place[kCandPer];
 #pragma unroll
-    for (int j = 0; j < kCandPer; ++j) {
-        const int i = tid + j * kT;
-        meta[j] = -1;
-        if (i < n) {
-            const unsigned t = sh.coarse[range_of(place[j])];
-            const uint32_t frac = within_range(place[j]);
-            const int bin = (int)(t & 0xFFFFu) + (int)__umulhi(frac, t >> 16);
-            // (bin 2w in the low half of word w, bin 2w+1 in the high half: a bin holds fewer than 2^16 candidates, so
-            //  the low half never carries into the high one)
-            const int half = (bin & 1) * 16;
-            meta[j] = (bin << 16) | (int)((atomicAdd(&sh.hist[bin >> 1], 1u << half) >> half) & 0xFFFFu);
-        }
-    }
-    __syncthreads();
-    // exclusive prefix over the bins, in place (16 bits each: at most kCap candidates); the bin that holds the k-th
-    // largest; the most crowded bin in front of it
-    constexpr int kFinePer = kFine / kT;
-    int h[kFinePer], loc = 0;
-#pragma unroll
-    for (int j = 0; j < kBinsPer; ++j) {
-        const unsigned w = sh.hist[tid * kBinsPer + j];
-        h[2 * j] = (int)(w & 0xFFFFu); h[2 * j + 1] = (int)(w >> 16);
-        loc += h[2 * j] + h[2 * j + 1];
-    }
-    const int incl = wave_scan_incl(loc);
-    if (lane == kWave - 1) sh.wtot[wave] = incl;
-    __syncthreads();   // every thread has read its counters
-    int excl = incl - loc;
-#pragma unroll
-    for (int w = 0; w < kW; ++w) excl += (w < wave) ? sh.wtot[w] : 0;
-    int big = 0;
-    const uint16_t* const start_of = reinterpret_cast<const uint16_t*>(sh.hist);    // first position of a fine bin, below
-#pragma unroll
-    for (int j = 0; j < kBinsPer; ++j) {
-        unsigned w = 0;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int b = 2 * j + u;
-            w |= (unsigned)excl << (16 * u);
-            if (excl < k) {
-                big = max(big, h[b]);
-                if (excl + h[b] >= k) { sh.piv_bin = tid * kFinePer + b; sh.piv_before = excl + h[b]; }
+        for (int j = 0; j < kCandPer; ++j) {
+            const int i = tid + j * kT;
+            place[j] = 0;
+            if (!held) c[j] = 0;
+            if (i < n) {
+                const uint32_t bits = sh.cand_val[i], id = sh.cand_id[i];
+                if (!held) c[j] = composite<BF16>(bits, id);
+                if (LINEAR && linear) {
+                    const float v = __uint_as_float(bits), w = fmaf(-(float)id, fabsf(v) * id_step, v);
+                    asm("v_cvt_u32_f32 %0, %1" : "=v"(place[j]) : "v"(fmaf(w, -lin, lin_max)));     // (saturates)
+                } else {
+                    place[j] = ib < 32 ? ((key_hi - short_key<BF16>(bits)) << ib) | (id >> id_drop) : (id >> id_drop);
+                }
+                atomicAdd(&sh.coarse[range_of(place[j])], 1u);
             }
-            excl += h[b];
         }
-        sh.hist[tid * kBinsPer + j] = w;
+        __syncthreads();
+        // fine bins per coarse range, in proportion to its count (at least one where there is a candidate); one
+        // wave builds the table, kCoarse / 64 consecutive ranges per lane
+        if (wave == 0) {
+            constexpr int kPerLane = kCoarse / kWave;
+            constexpr int kShared = kFine - kCoarse - kCoarse / 2;      // leaves room for the "at least one" and for rounding
+            const float share = (float)kShared / (float)n;
+            unsigned nf[kPerLane], loc = 0;
+#pragma unroll
+            for (int u = 0; u < kPerLane; ++u) {
+                const unsigned cnt = sh.coarse[lane * kPerLane + u];
+                nf[u] = cnt ? max(1u, (unsigned)((float)cnt * share)) : 0u;
+                loc += nf[u];
+            }
+            unsigned first = wave_scan_incl(loc) - loc;                 // first fine bin of this lane's ranges
+#pragma unroll
+            for (int u = 0; u < kPerLane; ++u) { sh.coarse[lane * kPerLane + u] = (nf[u] << 16) | first; first += nf[u]; }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kCandPer; ++j) {
+            const int i = tid + j * kT;
+            meta[j] = -1;
+            if (i < n) {
+                const unsigned t = sh.coarse[range_of(place[j])];
+                const uint32_t frac = within_range(place[j]);
+                meta[j] = enter((int)(t & 0xFFFFu) + (int)__umulhi(frac, t >> 16));
+            }
+        }
+    };
+    const uint16_t* const start_of = reinterpret_cast<const uint16_t*>(sh.hist);    // first position of a fine bin, behind the prefix
+    auto prefix = [&] {
+        __syncthreads();
+        // exclusive prefix over the bins, in place (16 bits each: at most kCap candidates); the bin that holds the k-th
+        // largest; the most crowded bin in front of it
+        constexpr int kFinePer = kFine / kT;
+        int h[kFinePer], loc = 0;
+#pragma unroll
+        for (int j = 0; j < kBinsPer; ++j) {
+            const unsigned w = sh.hist[tid * kBinsPer + j];
+            h[2 * j] = (int)(w & 0xFFFFu); h[2 * j + 1] = (int)(w >> 16);
+            loc += h[2 * j] + h[2 * j + 1];
+        }
+        const int incl = wave_scan_incl(loc);
+        if (lane == kWave - 1) sh.wtot[wave] = incl;
+        __syncthreads();   // every thread has read its counters
+        int excl = incl - loc;
+#pragma unroll
+        for (int w = 0; w < kW; ++w) excl += (w < wave) ? sh.wtot[w] : 0;
+        int big = 0;
+#pragma unroll
+        for (int j = 0; j < kBinsPer; ++j) {
+            unsigned w = 0;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int b = 2 * j + u;
+                w |= (unsigned)excl << (16 * u);
+                if (excl < k) {
+                    big = max(big, h[b]);
+                    if (excl + h[b] >= k) { sh.piv_bin = tid * kFinePer + b; sh.piv_before = excl + h[b]; }
+                }
+                excl += h[b];
+            }
+            sh.hist[tid * kBinsPer + j] = w;
+        }
+        if (big > kDirectMaxBin) atomicMax(&sh.maxbin, big);
+        __syncthreads();
+    };
+    // Linear places need no ranges where the values thin out towards the largest as any tail does.  With t = the distance from the
+    // largest value in parts of the whole, the bin is kFine t (1 + 3 t^3) / 4: exponential and Gaussian tails (a few thousand candidates:
+    // density about e^(8 t)) leave one or two entries in every bin, an even distribution up to three.  (Rounded, each product is
+    // monotone, so the bins never decrease along the order.)  A row with a more crowded bin - values on a grid, an outlier - takes the ranges.
+    // us: 300 rows of 50,001, k = 777, top-p 25.6 -> 24.4; 512 drafts beside 576 target rows of 128,256, k = 1024 67.6 -> 66.9; 4352 of 152,064 532 -> 530 the round.
+    bool placed = false;
+    if (LINEAR && linear) {
+        const float part = lin * (1.0f / 4294967296.0f), top = lin_max * (1.0f / 4294967296.0f);
+#pragma unroll
+        for (int j = 0; j < kCandPer; ++j) {
+            const int i = tid + j * kT;
+            c[j] = 0; meta[j] = -1;
+            if (i < n) {
+                const uint32_t bits = sh.cand_val[i], id = sh.cand_id[i];
+                c[j] = composite<BF16>(bits, id);
+                const float v = __uint_as_float(bits), w = fmaf(-(float)id, fabsf(v) * id_step, v);
+                const float t = fmaxf(fmaf(w, -part, top), 0.f);
+                unsigned bin;
+                asm("v_cvt_u32_f32 %0, %1" : "=v"(bin) : "v"(t * fmaf(0.75f * (float)kFine, t * t * t, 0.25f * (float)kFine)));
+                meta[j] = enter((int)min(bin, (unsigned)(kFine - 1)));
+            }
+        }
+        prefix();
+        placed = sh.maxbin <= kDirectMaxBin;         // (uniform)
+        if (!placed) {
+            __syncthreads();
+            order_prepare(sh, n);
+            __syncthreads();
+        }
     }
-    if (big > kSortMaxBin) atomicMax(&sh.maxbin, big);
-    __syncthreads();
+    if (!placed) {
+        by_ranges(LINEAR && linear);
+        prefix();
+    }
     if (LINEAR && linear && sh.maxbin > kSortMaxBin) return nullptr;     // (uniform)
     if (sh.maxbin > kSortMaxBin) {
         __syncthreads();                     // (prune_to_k writes the words read above)
@@ -450,6 +492,44 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
         return buf;
     }
     const int piv = sh.piv_bin, n_keep = sh.piv_before;
+    if constexpr (BF16) {
+        // gather bin by bin (every candidate is in registers: the buffer may be overwritten), the bin in the bits in front of the composite
+        static_assert(kIdBits + 32 + 12 == 64 && kFine <= 1 << 12, "a bin fits in front of a composite");
+#pragma unroll
+        for (int j = 0; j < kCandPer; ++j)
+            if (meta[j] >= 0 && (meta[j] >> 16) <= piv) buf[(int)start_of[meta[j] >> 16] + (meta[j] & 0xFFFF)] = c[j] | (uint64_t)(unsigned)(meta[j] >> 16) << (kIdBits + 32);
+        __syncthreads();
+        // Whoever reads position i ranks it in its bin.  (Not whoever brought it there: a wave's 64 positions and their bin-mates then lie
+        // side by side, and its reads meet in no bank; those of candidates in order of arrival are spread over the whole buffer.)
+        constexpr int kKeepPer = (SH::kRecMax + kSortMaxBin + kT - 1) / kT < kCandPer ? (SH::kRecMax + kSortMaxBin + kT - 1) / kT : kCandPer;
+        uint64_t kept[kKeepPer];
+        int pos[kKeepPer];
+#pragma unroll
+        for (int j = 0; j < kKeepPer; ++j) {
+            pos[j] = k;
+            const int i = tid + j * kT;
+            if (i < n_keep) {
+                kept[j] = buf[i];
+                const int bin = (int)(kept[j] >> (kIdBits + 32));
+                const int s = (int)start_of[bin];
+                const int e = bin < piv ? (int)start_of[bin + 1] : n_keep;
+                int larger = 0;
+                for (int q = s; q < e; q += 4) {         // four bin-mates per round trip to LDS
+                    uint64_t m[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) m[u] = buf[min(q + u, kCap - 1)];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) larger += (q + u < e && m[u] > kept[j]) ? 1 : 0;
+                }
+                pos[j] = s + larger;
+            }
+        }
+        __syncthreads();                         // all positions are known before the ordered list overwrites the bins
+#pragma unroll
+        for (int j = 0; j < kKeepPer; ++j) if (pos[j] < k) buf[pos[j]] = kept[j] & (((uint64_t)1 << (kIdBits + 32)) - 1);
+        __syncthreads();
+        return buf;
+    }
     // gather bin by bin (every candidate is in registers: the buffer may be overwritten)
 #pragma unroll
     for (int j = 0; j < kCandPer; ++j)

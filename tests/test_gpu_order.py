@@ -1,5 +1,5 @@
-"""The ordering of a row's candidates by one histogram on a linear scale: spread rows whose candidates stay in registers, against the
-oracle where bins are as full as may be, fuller, or hold equal values."""
+"""The ordering of a row's candidates by one histogram on a linear scale: spread rows whose candidates stay in registers, and bf16 rows of the calls
+with one workgroup per row, against the oracle where bins are as full as may be, fuller, or hold equal values."""
 import numpy as np
 import pytest
 import torch
@@ -60,4 +60,16 @@ def test_spread_rows(gpu, pu, ps, pattern, dtype, V, R, k, top_p):
     z = W.to_bf16_bits(z) if dtype == "bf16" else z
     o = oracle.compress(z, V, 0.9, k, top_p)
     g = ps.compress(pu.to_device(z, gpu), V, 0.9, k, top_p)
+    pu.compare_compress(g, o, top_p)
+
+
+@pytest.mark.parametrize("pattern", ["normal", "below_zero", "around_zero", "even", "equal24", "equal25", "equal200", "outlier", "steep"])
+@pytest.mark.parametrize("V,k,top_p", [(32768, 10, 0.0), (33001, 777, 0.9), (152064, 2048, 0.0), (131072, 3000, 0.0)])
+def test_rows_of_one_workgroup(gpu, pu, ps, pattern, V, k, top_p):
+    print("[case]", pattern, V, k, top_p, flush=True)
+    z = W.to_bf16_bits(_rows(np.random.default_rng(V + k), pattern, 2, V, "bf16"))
+    o = oracle.compress(z, V, 1.0, k, top_p)
+    t = pu.to_device(z, gpu)
+    with pu.no_scratch():
+        g = ps.compress(t, V, 1.0, k, top_p)
     pu.compare_compress(g, o, top_p)
