@@ -63,7 +63,7 @@ constexpr int kFine = 2 * kBins;            // fine bins of the rank sort: 16-bi
 constexpr int kIdBits = 20;                 // ids < 2^20 (kMaxV)
 constexpr unsigned kIdMask = (1u << kIdBits) - 1u;
 constexpr int kSortMaxBin = 128;            // beyond this bin size the ordering falls back to a sorting network
-constexpr int kDirectMaxBin = 24;           // ... and beyond this one a row whose bins were not steered by the coarse ranges is counted again with them
+constexpr int kDirectMaxBin = 64;           // ... and beyond this one a row whose bins were not steered by the coarse ranges is counted again with them
 constexpr int kCoarseLog2 = 9;
 constexpr int kCoarse = 1 << kCoarseLog2;   // coarse ranges that steer the fine bins of the rank sort
 
@@ -88,6 +88,7 @@ struct __align__(16) CompressShared {
     int n_holes, n_fills;                   // compaction of a prune
     int piv_bin, piv_before, piv_count;     // radix-select broadcast
     int maxbin;
+    int on_grid;                            // bf16, optimistic pass: the threshold's value occurs more often than the buffer has room for
     int overflowed;                         // a reservation of the sample did not fit (cannot happen: kept as a guard)
     int epoch_overflow[3];                  // safe pass, per epoch: some wave did not fit
     int epoch_valid[3];                     // safe pass, per epoch: first reservation that did not fit
@@ -402,8 +403,7 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
         }
     };
     const uint16_t* const start_of = reinterpret_cast<const uint16_t*>(sh.hist);    // first position of a fine bin, behind the prefix
-    auto prefix = [&] {
-        __syncthreads();
+    auto prefix = [&] {                      // (behind a barrier)
         // exclusive prefix over the bins, in place (16 bits each: at most kCap candidates); the bin that holds the k-th
         // largest; the most crowded bin in front of it
         constexpr int kFinePer = kFine / kT;
@@ -436,7 +436,7 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
             }
             sh.hist[tid * kBinsPer + j] = w;
         }
-        if (big > kDirectMaxBin) atomicMax(&sh.maxbin, big);
+        if (big > kSortMaxBin) atomicMax(&sh.maxbin, big);
         __syncthreads();
     };
     // Linear places need no ranges where the values thin out towards the largest as any tail does.  With t = the distance from the
@@ -445,7 +445,9 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
     // monotone, so the bins never decrease along the order.)  A row with a more crowded bin - values on a grid, an outlier - takes the ranges.
     // us: 300 rows of 50,001, k = 777, top-p 25.6 -> 24.4; 512 drafts beside 576 target rows of 128,256, k = 1024 67.6 -> 66.9; 4352 of 152,064 532 -> 530 the round.
     bool placed = false;
-    if (LINEAR && linear) {
+    if (LINEAR && linear && !sh.on_grid) {
+        unsigned seen = 0;                           // (an arrival of kDirectMaxBin or later leaves a bit)
+        static_assert((kDirectMaxBin & (kDirectMaxBin - 1)) == 0, "one bit and those above it");
         const float part = lin * (1.0f / 4294967296.0f), top = lin_max * (1.0f / 4294967296.0f);
 #pragma unroll
         for (int j = 0; j < kCandPer; ++j) {
@@ -459,10 +461,12 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
                 unsigned bin;
                 asm("v_cvt_u32_f32 %0, %1" : "=v"(bin) : "v"(t * fmaf(0.75f * (float)kFine, t * t * t, 0.25f * (float)kFine)));
                 meta[j] = enter((int)min(bin, (unsigned)(kFine - 1)));
+                seen |= (unsigned)meta[j];
             }
         }
-        prefix();
-        placed = sh.maxbin <= kDirectMaxBin;         // (uniform)
+        if (seen & (0xFFFFu & ~(unsigned)(kDirectMaxBin - 1))) sh.maxbin = 1;
+        __syncthreads();
+        placed = sh.maxbin == 0;                     // (uniform)
         if (!placed) {
             __syncthreads();
             order_prepare(sh, n);
@@ -470,9 +474,10 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
         }
     }
     if (!placed) {
-        by_ranges(LINEAR && linear);
-        prefix();
+        by_ranges(LINEAR && linear && !sh.on_grid);
+        __syncthreads();
     }
+    prefix();
     if (LINEAR && linear && sh.maxbin > kSortMaxBin) return nullptr;     // (uniform)
     if (sh.maxbin > kSortMaxBin) {
         __syncthreads();                     // (prune_to_k writes the words read above)
@@ -916,7 +921,7 @@ __device__ __forceinline__ RowSelection select_row(
     if (CAREFUL || r_opt > 0) do {               // (left early by a row that is given up)
         if (tid == 0) {
             sh.cnt = optimistic ? (int)val_addr : 0;      // (the optimistic pass's counter is the LDS address of the next slot)
-            sh.overflowed = 0;
+            sh.overflowed = 0; sh.on_grid = 0;
             for (int e = 0; e < 3; ++e) { sh.epoch_overflow[e] = 0; sh.epoch_valid[e] = 0x7FFFFFFF; }
         }
         os.mx = kNegInf; os.r = kNegInf; os.s = 0.f;
@@ -1172,6 +1177,7 @@ __device__ __forceinline__ RowSelection select_row(
             const bool fits = applies && !sh.overflowed && words <= kCap;
             if (BF16 && __builtin_expect(cut_sub < n_sub, 0)) {
                 // (rare: elements of words behind the cut that their sub-tiles did not admit are masked, then all go by the lower threshold)
+                sh.on_grid = 1;
 #pragma unroll 1
                 for (int i = tid; i < min(words, kCap); i += kT) {
                     unsigned raw = sh.cand_val[i];

@@ -346,7 +346,7 @@ __device__ __attribute__((noinline)) void split_row_again(
 // `meanwhile` forms the row's sum of exponentials while the histogram's atomics are on their way.
 // Bound by the chain of barriers, six of them (ten before): the finish of one row of 32,000 fp32, k = 64: 4.5 -> 3.6 us from its first instruction, of 64 of
 // 151,936, k = 1024: 7.4 -> 5.6; a round of that row 16.4 -> 15.6, the draft of those 22.0 -> 20.0.
-constexpr int kFewBins = kBins, kFewMost = 32;          // (a bin per word of the histogram; entries of a bin that are ranked by comparing all)
+constexpr int kFewBins = kBins, kFewMost = 64;          // (a bin per word of the histogram; entries of a bin that are ranked by comparing all)
 enum class Few { crowded, missing, done };
 template <bool BF16, int SLOTS, class SH, class F>
 __device__ __forceinline__ Few finish_few(
@@ -368,16 +368,21 @@ __device__ __forceinline__ Few finish_few(
         return min(b, (unsigned)(kFewBins - 1));
     };
     unsigned meta[SLOTS];                              // (bin << 16) | arrival order within the bin
+    unsigned seen = 0;                                 // (an arrival of kFewMost or later leaves a bit)
+    static_assert((kFewMost & (kFewMost - 1)) == 0, "one bit and those above it");
 #pragma unroll
     for (int u = 0; u < SLOTS; ++u) {
         meta[u] = 0;
         if (valid >> u & 1u) {
             const unsigned b = bin_of(__uint_as_float(e[u].x), e[u].y);
             meta[u] = b << 16 | atomicAdd(&sh.hist[b], 1u);
+            seen |= meta[u];
         }
     }
     const double S = meanwhile();
+    if (seen & (0xFFFFu & ~(unsigned)(kFewMost - 1))) sh.maxbin = 1;
     __syncthreads();
+    if (sh.maxbin) return Few::crowded;                // (uniform)
     const uint4 h4 = *reinterpret_cast<const uint4*>(&sh.hist[4 * tid]);
     const int h[4] = {(int)h4.x, (int)h4.y, (int)h4.z, (int)h4.w};
     const int loc = (h[0] + h[1]) + (h[2] + h[3]), incl = wave_scan_incl(loc);
@@ -386,21 +391,15 @@ __device__ __forceinline__ Few finish_few(
     int at = incl - loc;
 #pragma unroll
     for (int w = 0; w < kW; ++w) at += w < wave ? sh.wtot[w] : 0;
-    int big = 0;
     unsigned first[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         first[j] = (unsigned)at;
-        if (at < n) {
-            big = max(big, h[j]);
-            if (at + h[j] >= n) { sh.piv_bin = 4 * tid + j; sh.piv_before = at + h[j]; }
-        }
+        if (at < n && at + h[j] >= n) { sh.piv_bin = 4 * tid + j; sh.piv_before = at + h[j]; }
         at += h[j];
     }
     *reinterpret_cast<uint4*>(&sh.hist[4 * tid]) = make_uint4(first[0], first[1], first[2], first[3]);
-    if (big > kFewMost) sh.maxbin = big;
     __syncthreads();
-    if (sh.maxbin > kFewMost) return Few::crowded;     // (uniform)
     const int piv = sh.piv_bin, n_keep = sh.piv_before;
 #pragma unroll
     for (int u = 0; u < SLOTS; ++u)

@@ -50,7 +50,7 @@ def _rows(rng, pattern, R, V, dtype):
     return z.astype(np.float32)
 
 
-@pytest.mark.parametrize("pattern", ["normal", "below_zero", "around_zero", "even", "equal32", "equal33", "equal200", "outlier", "steep", "late", "masked"])
+@pytest.mark.parametrize("pattern", ["normal", "below_zero", "around_zero", "even", "equal64", "equal65", "equal200", "outlier", "steep", "late", "masked"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("V,R,k,top_p", [(16384, 2, 1, 0.0), (33001, 3, 64, 0.0), (33001, 2, 777, 0.9), (151936, 2, 1024, 0.0), (100003, 2, 1700, 0.0),
                                          (65536, 2, 2049, 0.0)])      # (slots of all lists on either side of 4096)
@@ -63,7 +63,7 @@ def test_spread_rows(gpu, pu, ps, pattern, dtype, V, R, k, top_p):
     pu.compare_compress(g, o, top_p)
 
 
-@pytest.mark.parametrize("pattern", ["normal", "below_zero", "around_zero", "even", "equal24", "equal25", "equal200", "outlier", "steep"])
+@pytest.mark.parametrize("pattern", ["normal", "below_zero", "around_zero", "even", "equal64", "equal65", "equal200", "outlier", "steep"])
 @pytest.mark.parametrize("V,k,top_p", [(32768, 10, 0.0), (33001, 777, 0.9), (152064, 2048, 0.0), (131072, 3000, 0.0)])
 def test_rows_of_one_workgroup(gpu, pu, ps, pattern, V, k, top_p):
     print("[case]", pattern, V, k, top_p, flush=True)
