@@ -54,14 +54,15 @@ __host__ __device__ inline int optimistic_rank(int k, int V, int m, int cap, flo
 //     workgroup); its lists together must fit the candidate buffer of the finishing kernel with room to spare.
 //   * a list holds the rank, a crowded pivot bin and some slack.
 //   * lanes: of a workgroup's 256 lanes, 256 (1 - exp(-rank / 256)) hold one of its `rank` largest elements on average, so a threshold with that
-//     many lanes' maxima at or above it has about `rank` elements above it, with a standard deviation of 4.3 at rank 93 and 4.7 at
-//     100 (20,000 simulated orders).  Together with the share's own that leaves 4.7 and 4.8 deviations (k = 1024 and 1100 in 19 parts),
-//     of the 4.5 asked for; at 128 it would be 4.5.  Ranks beyond kSplitLanesRank (lanes = 0) count the elements.
+//     many lanes' maxima at or above it has about `rank` elements above it, with a standard deviation of 4.3 at rank 93, 4.7 at
+//     100 and 4.9 at 103 (simulated orders).  Together with the share's own that leaves 4.6 to 4.7 deviations (k = 1024 and 1100 in 19 parts, 256 in
+//     4), of the 4.5 asked for; at 125 (k = 330 in 4) it would be 4.3.  Ranks beyond kSplitLanesRank (lanes = 0) count the elements: 8 sequences of 8
+//     drafts of 32,000 bf16, k = 256 (rank 102), a round 18.9 us so, 18.3 by lanes.
 constexpr int kSplitMaxRows = 192;
 inline int split_max_rows(int k) { return k <= 256 ? kSplitMaxRows : k <= 1024 ? 128 : 80; }
 constexpr int kSplitMinV = 16384;                // (two workgroups per row)
 constexpr int kSplitNarrowRank = 240;            // ranks for which 256 elements above the histogram's lower end suffice
-constexpr int kSplitLanesRank = 100;             // ... for which the threshold is looked for among the lanes' largest values first
+constexpr int kSplitLanesRank = 104;             // ... for which the threshold is looked for among the lanes' largest values first
 constexpr int kSplitMaxParts = 64;               // lists per row (one per lane of a finishing wave): rows of up to half a million elements
 struct SplitPlan { int parts, rank, cap, lanes; };
 inline SplitPlan split_plan(int dtype, int64_t rows, int V, int k) {
