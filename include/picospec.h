@@ -194,8 +194,9 @@ int picospec_sample_residual(const void* tgt_logits, int dtype, int64_t ld, int3
 /*
  * The same where no verification left a table: the workspace (optional, picospec_workspace_bytes(PICOSPEC_CALL_SAMPLE_RESIDUAL,
  * dtype, B, V, k) bytes: a row per sequence) is scratch, whatever it holds.  A call of up to 1024 sequences and records of up to
- * 1024 entries then forms the table of the rows it draws from, every row spread over many workgroups, in a launch of its own,
- * where that is faster (picospec_scratch_bytes; the sums are formed in another order and agree to rounding).
+ * 1024 entries then forms the table of the rows it draws from, every row spread over many workgroups, in a launch of its own
+ * or in the draw's (picospec_one_launch_bytes), where that is faster (picospec_scratch_bytes; the sums are formed in another
+ * order and agree to rounding).
  */
 int picospec_sample_residual_ws(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float temperature,
                                 int32_t B, int32_t n_draft, const int32_t* seq_off, const int32_t* n_accept,
@@ -455,8 +456,8 @@ size_t picospec_workspace_bytes(int which_call, int dtype, int32_t rows, int32_t
  * which calls are spread stand in the library only: a caller that keeps its buffers asks here which call has a use for one. */
 size_t picospec_scratch_bytes(int which_call, int dtype, int32_t n_draft, int32_t B, int32_t V, int32_t k);
 
-/* The same, and behind it what lets the call go out in one launch where that is the faster way (few rows; verify, verify_range, row_stats and the
- * draw that makes its own table).  A call that is given picospec_scratch_bytes() alone takes two launches.  Calls that overlap in time must not
+/* The same, and behind it what lets the call go out in one launch where that is the faster way (few rows; compress, compress_rejected, verify,
+ * verify_range, row_stats and the draw that makes its own table).  A call that is given picospec_scratch_bytes() alone takes two launches.  Calls that overlap in time must not
  * share scratch. */
 size_t picospec_one_launch_bytes(int which_call, int dtype, int32_t n_draft, int32_t B, int32_t V, int32_t k);
 

@@ -107,7 +107,7 @@ int picospec_compress(const void* logits, int dtype, int64_t ld, int32_t n_rows,
     if ((uintptr_t)workspace & 15u) return PICOSPEC_EWORKSPACE;
     if (split_fits(dtype, n_rows, V, k, workspace, workspace_bytes))
         return hip_status(launch_split_compress(logits, dtype, ld, n_rows, V, temperature, k, top_p, idx, prob, count,
-                                                mass, lse, nullptr, nullptr, workspace, (hipStream_t)stream));
+                                                mass, lse, nullptr, nullptr, workspace, workspace_bytes, (hipStream_t)stream));
     return hip_status(launch_compress(logits, dtype, ld, n_rows, V, temperature, k, top_p, idx, prob, count,
                                       mass, lse, nullptr, nullptr, (hipStream_t)stream));
 }
@@ -154,7 +154,7 @@ int picospec_compress_rejected(const void* tgt_logits, int dtype, int64_t ld, in
     if ((uintptr_t)workspace & 15u) return PICOSPEC_EWORKSPACE;
     if (split_fits(dtype, B, V, k, workspace, workspace_bytes))
         return hip_status(launch_split_compress(tgt_logits, dtype, ld, B, V, temperature, k, top_p, idx, prob, count,
-                                                mass, lse, seq_off, n_accept, workspace, (hipStream_t)stream));
+                                                mass, lse, seq_off, n_accept, workspace, workspace_bytes, (hipStream_t)stream));
     return hip_status(launch_compress(tgt_logits, dtype, ld, B, V, temperature, k, top_p, idx, prob, count,
                                       mass, lse, seq_off, n_accept, (hipStream_t)stream));
 }
@@ -223,7 +223,7 @@ int picospec_round(const void* draft_logits, const void* tgt_logits, int dtype, 
                                    q_lse, tgt_logits, ld_tgt, (int)rows, workspace, scratch, s);
         } else {
             e = launch_split_compress(draft_logits, dtype, ld_draft, n_draft, V, temperature, k, top_p, q_idx, q_prob, q_count,
-                                      q_mass, q_lse, nullptr, nullptr, scratch, s);
+                                      q_mass, q_lse, nullptr, nullptr, scratch, 0, s);      // (beside the statistics' launch)
             if (e == hipSuccess)
                 e = launch_row_stats(tgt_logits, dtype, ld_tgt, (int)rows, V, temperature, tgt_max, tgt_sum, tgt_lse, workspace, s);
         }
@@ -540,6 +540,8 @@ size_t picospec_one_launch_bytes(int which_call, int dtype, int32_t n_draft, int
     if (!scratch) return 0;
     const int64_t rows = (int64_t)n_draft + B;
     switch (which_call) {
+        case PICOSPEC_CALL_COMPRESS: return split_one_launch(dtype, n_draft, V, k) ? split_one_launch_bytes(dtype, n_draft, V, k) : scratch;
+        case PICOSPEC_CALL_COMPRESS_REJECTED: return split_one_launch(dtype, B, V, k) ? split_one_launch_bytes(dtype, B, V, k) : scratch;
         case PICOSPEC_CALL_VERIFY: return verify_one_launch(true, dtype, rows, V) ? std::max(scratch, verify_scratch_bytes(dtype, rows, B, V)) : scratch;
         case PICOSPEC_CALL_ROW_STATS: return std::max(scratch, row_stats_scratch_bytes(dtype, rows, V));
         case PICOSPEC_CALL_SAMPLE_RESIDUAL: return residual_one_launch(dtype, B, V, k) ? std::max(scratch, residual_scratch_bytes(dtype, B, V)) : scratch;

@@ -83,6 +83,15 @@ inline size_t split_scratch_bytes(int dtype, int64_t rows, int V, int k) {
     return (size_t)rows * (size_t)p.parts * (32 + 8 * (size_t)p.cap);
 }
 
+// ... in one launch, whose last workgroup of a row finishes it (split_compress_kernel; behind the lists, on a 16-byte boundary, a word per row).  It
+// spares the host a launch, 2.5 to 3 us of the 12.6 in which it issues a row's record and draw; on the device it is 0.5 us slower for one row (of 11.0),
+// even from four rows on and up to 0.5 us faster around 64 workgroups; beyond 128 it loses (bf16, 32 rows of 128,256, k = 256, 512 workgroups: 14.7
+// against 13.5; 16 of 151,936, k = 1024, 304: 17.7 against 15.4): its workgroups have the finish's LDS, two to a CU.
+constexpr int kOneLaunchSplit = 128;
+inline bool split_one_launch(int dtype, int64_t rows, int V, int k) { return rows * split_plan(dtype, rows, V, k).parts <= kOneLaunchSplit; }
+inline size_t split_words_at(int dtype, int64_t rows, int V, int k) { return (split_scratch_bytes(dtype, rows, V, k) + 15) / 16 * 16; }
+inline size_t split_one_launch_bytes(int dtype, int64_t rows, int V, int k) { return split_words_at(dtype, rows, V, k) + (size_t)rows * kArrivalStride; }
+
 // Kernels whose dynamic LDS exceeds the 64 KB default need their limit raised once per device and kernel.
 // `done` is the caller's per-device record for that kernel; the current device's ordinal comes back in `dev`.
 // The record is atomic and the attribute call idempotent: two threads that meet here on a kernel's first use
@@ -107,11 +116,11 @@ hipError_t launch_compress(const void* logits, int dtype, int64_t ld, int n_rows
                            int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass,
                            float* lse, const int32_t* seq_off, const int32_t* n_accept, hipStream_t stream);
 
-// the same in two launches that spread every row over several workgroups (split_plan(...).parts > 0); scratch holds
-// split_scratch_bytes(...) bytes on a 16-byte boundary
+// the same with every row spread over several workgroups (split_plan(...).parts > 0), in two launches, or in one (split_one_launch) where the
+// scratch, on a 16-byte boundary, holds split_one_launch_bytes(...) and not only split_scratch_bytes(...)
 hipError_t launch_split_compress(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
                                  int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass,
-                                 float* lse, const int32_t* seq_off, const int32_t* n_accept, void* scratch, hipStream_t stream);
+                                 float* lse, const int32_t* seq_off, const int32_t* n_accept, void* scratch, size_t scratch_bytes, hipStream_t stream);
 
 // ... and besides it, in the first of the two launches, the target rows' segment table in the split layout
 hipError_t launch_split_round(const void* draft_logits, int dtype, int64_t ld_d, int n_draft, int V, float temperature,

@@ -23,15 +23,20 @@ namespace picospec {
 
 namespace {
 
-constexpr int kSplitThreads = 256, kSplitWaves = kSplitThreads / kWave;
+constexpr int kSplitThreads = 256;
 constexpr int kSplitBins = 512;                // histogram of a workgroup's values: eight bins per lane in the pivot scan
 constexpr int kImageVecs = 4;                  // vectors per lane that pass through LDS at a time
-template <bool BF16> struct SplitGeom {
+// THREADS: 256, or 512 of which wave w + 4 holds the second half of what wave w holds otherwise.
+template <bool BF16, int THREADS> struct SplitGeom {
     using elem_t = typename std::conditional<BF16, uint16_t, uint32_t>::type;
     static constexpr int N = Vec<BF16>::N;
-    static constexpr int NV = kSplitElems / (kSplitThreads * N);           // vectors per lane
+    static constexpr int NV = kSplitElems / (THREADS * N);                 // vectors per lane
     static constexpr int E = NV * N;                                  // elements per lane
-    static_assert(NV % kImageVecs == 0 && E == 32, "one bit of a word per element");
+    static constexpr int IV = NV < kImageVecs ? NV : kImageVecs;
+    static constexpr int WAVES = THREADS / kWave;
+    static constexpr int HIST = kSplitBins + kWave, IMAGE = 4 * IV * THREADS;      // words of LDS; behind the bins: a slot per lane for what lies below them
+    static_assert(NV % IV == 0 && E <= 32 && THREADS % 256 == 0 && kSplitBins % THREADS == 0, "one bit of a word per element");
+    __device__ static __forceinline__ int nth(int j, int wave) { return (wave >> 2) * NV + j; }       // a wave's block j: split_block(nth(j, wave), wave & 3, ..)
 };
 
 // What a workgroup leaves of its share of the row; its list of (value, id) pairs stands in an array of its own.
@@ -43,19 +48,20 @@ struct __align__(16) SplitHead {
 };
 static_assert(sizeof(SplitHead) == 32, "two 16-byte loads");
 
-// Workgroup `part` of the P workgroups of row `row` of the call.
-template <bool BF16>
+// Workgroup `part` of the P workgroups of row `row` of the call.  hist, image: LDS on 16-byte boundaries.  SHARED: for another workgroup of this
+// launch to read.  `meanwhile` is run behind the loads.  The share's sum is formed in the same order by workgroups of either size.
+template <bool BF16, int THREADS, bool SHARED, class F>
 __device__ __forceinline__ void split_select(
+    unsigned* const hist, unsigned* const image,
     const int64_t row, const int part, const int P,
     const void* __restrict__ logits, int64_t ld, int V, float inv_T, int rank, int cap, int narrow, int lanes,
     SplitHead* __restrict__ heads, uint2* __restrict__ lists,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept, const F& meanwhile)
 {
-    using G = SplitGeom<BF16>;
-    constexpr int N = G::N, NV = G::NV, E = G::E;
-    __shared__ __align__(16) unsigned hist[kSplitBins + kWave];       // (behind the bins: a slot per lane for what lies below them)
-    __shared__ __align__(16) unsigned image[4 * kImageVecs * kSplitThreads];
+    using G = SplitGeom<BF16, THREADS>;
+    constexpr int N = G::N, NV = G::NV, E = G::E, kSplitWaves = G::WAVES;
     __shared__ float red[2 * kSplitWaves];
+    __shared__ float lane_s[THREADS > 256 ? THREADS : 1];
     __shared__ double wave_s[kSplitWaves];
     __shared__ int wave_held[kSplitWaves];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -69,11 +75,15 @@ __device__ __forceinline__ void split_select(
     uint4 raw[NV];
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-        const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(row_rsrc, lane * 16, split_block(j, wave, part, P) * (kWave * 16), 2 /* non-temporal */);
+        const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(row_rsrc, lane * 16, split_block(G::nth(j, wave), wave & 3, part, P) * (kWave * 16), 2 /* non-temporal */);
         raw[j] = make_uint4(t.x, t.y, t.z, t.w);
     }
-    *reinterpret_cast<uint2*>(&hist[2 * tid]) = make_uint2(0u, 0u);
-    static_assert(kSplitBins == 2 * kSplitThreads, "one store clears the histogram");
+    auto clear = [&] {
+#pragma unroll
+        for (int i = 0; i < kSplitBins / THREADS; ++i) hist[i * THREADS + tid] = 0u;
+    };
+    clear();
+    meanwhile();
     float v[E];
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
@@ -84,10 +94,10 @@ __device__ __forceinline__ void split_select(
     }
     // elements outside the row (in front of its first, behind its last) count as masked ones: -inf.  Only the row's first and
     // last blocks hold any.
-    if ((part == 0 && wave == 0) || split_block(NV - 1, wave, part, P) >= n_blocks - 1) {
+    if ((part == 0 && wave == 0) || split_block(G::nth(NV - 1, wave), wave & 3, part, P) >= n_blocks - 1) {
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            const unsigned vm = vec_valid_mask<BF16>(rv, split_block(j, wave, part, P) * kWave + lane);
+            const unsigned vm = vec_valid_mask<BF16>(rv, split_block(G::nth(j, wave), wave & 3, part, P) * kWave + lane);
 #pragma unroll
             for (int e = 0; e < N; ++e) v[j * N + e] = (vm >> e) & 1u ? v[j * N + e] : kNegInf;
         }
@@ -141,7 +151,7 @@ __device__ __forceinline__ void split_select(
         }
         return true;
     };
-    const double ws = wave_sum((double)acc);
+    const double ws = THREADS > 256 ? 0.0 : wave_sum((double)acc);
     unsigned marks = 0;
     int at = 0, held = 0;
     // First (lanes > 0) by the lanes' largest values alone, one bin and atomic per lane instead of 32: with n of 256 lanes at or above it, a
@@ -201,7 +211,7 @@ __device__ __forceinline__ void split_select(
         for (int pass = 0; open && !by_lanes && pass < 4; ++pass) {       // (a pass too many for the widest bin: one bin is one value by then)
             if (counted) {
                 __syncthreads();
-                *reinterpret_cast<uint2*>(&hist[2 * tid]) = make_uint2(0u, 0u);
+                clear();
                 __syncthreads();
             }
             const uint32_t span = top - bottom;
@@ -234,11 +244,12 @@ __device__ __forceinline__ void split_select(
     const float least = __uint_as_float(__float_as_uint(tau) + (tau < 0.f ? -1u : 1u));
 #pragma unroll
     for (int e = 0; e < E; ++e) marks = __builtin_amdgcn_alignbit(marks, __float_as_uint(v[e] - least), 31);
-    marks = ~marks;
+    marks = ~marks << (32 - E);
     const int mine = __popc(marks);
     const int incl = wave_scan_incl(mine);
     if (lane == kWave - 1) wave_held[wave] = incl;
-    if (lane == 0) wave_s[wave] = ws;
+    if (THREADS > 256) lane_s[tid] = acc;
+    else if (lane == 0) wave_s[wave] = ws;
     __syncthreads();
     at = incl - mine;
     held = 0;
@@ -247,20 +258,19 @@ __device__ __forceinline__ void split_select(
     if (!(by_lanes || whole) || (!again && held <= cap)) break;
     // the elements themselves, then (the histogram is cleared; every wave has read the counts)
     tau = kNegInf;
-    *reinterpret_cast<uint2*>(&hist[2 * tid]) = make_uint2(0u, 0u);
+    clear();
     __syncthreads();
     }
     const int64_t list = row * P + part;
     uint2* const out = lists + list * cap;
     const typename G::elem_t* const my_image = reinterpret_cast<const typename G::elem_t*>(image) + tid * N;
-    const int first_block = wave * P + part;
     if (held <= cap) {
         // (a lane's vectors go through LDS four at a time, so that it picks its marked elements by a computed address)
 #pragma unroll
-        for (int j0 = 0; j0 < NV; j0 += kImageVecs) {
+        for (int j0 = 0; j0 < NV; j0 += G::IV) {
 #pragma unroll
-            for (int j = 0; j < kImageVecs; ++j) {
-                unsigned* const dst = &image[(j * kSplitThreads + tid) * 4];
+            for (int j = 0; j < G::IV; ++j) {
+                unsigned* const dst = &image[(j * THREADS + tid) * 4];
                 if constexpr (BF16) {                // (packed again: the vectors as they were read would hold registers throughout)
                     unsigned p[4];
 #pragma unroll
@@ -269,31 +279,45 @@ __device__ __forceinline__ void split_select(
                     *reinterpret_cast<uint4*>(dst) = make_uint4(p[0], p[1], p[2], p[3]);
                 } else *reinterpret_cast<float4*>(dst) = make_float4(v[(j0 + j) * N], v[(j0 + j) * N + 1], v[(j0 + j) * N + 2], v[(j0 + j) * N + 3]);
             }
-            constexpr int kPer = kImageVecs * N;     // elements per batch
-            unsigned m = (marks << (j0 * N)) & (0xFFFFFFFFu << (E - kPer));
+            constexpr int kPer = G::IV * N;          // elements per batch
+            unsigned m = (marks << (j0 * N)) & (0xFFFFFFFFu << (32 - kPer));
             while (m) {
                 const int e = __clz((int)m);
                 m &= ~(0x80000000u >> e);
                 const int j = e / N, el = e % N;
-                const unsigned bits = (unsigned)my_image[j * (kSplitThreads * N) + el] << (BF16 ? 16 : 0);
-                const int x = ((first_block + (j0 + j) * (kSplitWaves * P)) * kWave + lane) * N - rv.o + el;
-                out[at++] = make_uint2(bits, (unsigned)x);
+                const unsigned bits = (unsigned)my_image[j * (THREADS * N) + el] << (BF16 ? 16 : 0);
+                const int x = (split_block(G::nth(j0 + j, wave), wave & 3, part, P) * kWave + lane) * N - rv.o + el;
+                if (SHARED) put_shared(reinterpret_cast<unsigned long long*>(&out[at++]), (unsigned long long)bits | (unsigned long long)(unsigned)x << 32);
+                else out[at++] = make_uint2(bits, (unsigned)x);
             }
         }
+    }
+    if (THREADS > 256 && wave == 0) {                // (the two halves of what a lane of four waves holds, then its wave's lanes)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) wave_s[w] = wave_sum((double)(lane_s[w * kWave + lane] + lane_s[(THREADS > 256 ? 256 : 0) + w * kWave + lane]));
     }
     if (tid == 0) {
         // (+inf in the row: given up, as by the other kernels' first pass; so is a share of NaN and nothing above -inf, whose sum the
         //  finishing kernel leaves out with its reference: any other NaN it finds in the row's sum)
         double s = 0.0;
 #pragma unroll
-        for (int w = 0; w < kSplitWaves; ++w) s += wave_s[w];
+        for (int w = 0; w < 4; ++w) s += wave_s[w];
         SplitHead h{mx, tau, ref, finite || (!(mx > kNegInf) && s == s) ? held : cap + 1, s, 0.0};
-        uint4* dst = reinterpret_cast<uint4*>(heads + list);
-        const uint4* src = reinterpret_cast<const uint4*>(&h);
-        dst[0] = src[0];
-        dst[1] = src[1];
+        if (SHARED) {
+            const unsigned long long* src = reinterpret_cast<const unsigned long long*>(&h);
+            unsigned long long* dst = reinterpret_cast<unsigned long long*>(heads + list);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) put_shared(dst + i, src[i]);
+        } else {
+            uint4* dst = reinterpret_cast<uint4*>(heads + list);
+            const uint4* src = reinterpret_cast<const uint4*>(&h);
+            dst[0] = src[0];
+            dst[1] = src[1];
+        }
     }
 }
+
+template <bool BF16> using SplitGeom256 = SplitGeom<BF16, kSplitThreads>;
 
 template <bool BF16>
 __global__ __launch_bounds__(kSplitThreads) void split_select_kernel(
@@ -301,7 +325,8 @@ __global__ __launch_bounds__(kSplitThreads) void split_select_kernel(
     SplitHead* __restrict__ heads, uint2* __restrict__ lists,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept)
 {
-    split_select<BF16>(blockIdx.y, (int)blockIdx.x, (int)gridDim.x, logits, ld, V, inv_T, rank, cap, narrow, lanes, heads, lists, seq_off, n_accept);
+    __shared__ __align__(16) unsigned hist[SplitGeom256<BF16>::HIST], image[SplitGeom256<BF16>::IMAGE];
+    split_select<BF16, kSplitThreads, false>(hist, image, blockIdx.y, (int)blockIdx.x, (int)gridDim.x, logits, ld, V, inv_T, rank, cap, narrow, lanes, heads, lists, seq_off, n_accept, [] {});
 }
 
 // A small round's draft rows and, in the same launch, the segment tables of its target rows: workgroups (x, y) with
@@ -312,9 +337,10 @@ __global__ __launch_bounds__(kSplitThreads) void split_round_kernel(
     SplitHead* __restrict__ heads, uint2* __restrict__ lists, int parts,
     const void* __restrict__ tgt_logits, int64_t ld_t, int stats_per_row, SegHeader* __restrict__ header, int seg_stride)
 {
+    __shared__ __align__(16) unsigned hist[SplitGeom256<BF16>::HIST], image[SplitGeom256<BF16>::IMAGE];
     const int x = blockIdx.x, y = blockIdx.y;
     if (y < n_draft) {
-        if (x < parts) split_select<BF16>(y, x, parts, draft_logits, ld_d, V, inv_T, rank, cap, narrow, lanes, heads, lists, nullptr, nullptr);
+        if (x < parts) split_select<BF16, kSplitThreads, false>(hist, image, y, x, parts, draft_logits, ld_d, V, inv_T, rank, cap, narrow, lanes, heads, lists, nullptr, nullptr, [] {});
         return;
     }
     if (y == n_draft && x == 0 && threadIdx.x == 0)
@@ -450,19 +476,17 @@ __device__ __forceinline__ Few finish_few(
     return sh.overflowed ? Few::missing : Few::done;
 }
 
-template <bool BF16>
-__global__ __launch_bounds__(kT, 4) void split_finish_kernel(
-    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
+// SHARED: the lists were written by other workgroups of this launch.
+template <bool BF16, bool SHARED>
+__device__ __forceinline__ void split_finish(
+    CompressShared<kCapBig>& sh, const int64_t row, const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
     int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
     float* __restrict__ mass, float* __restrict__ lse,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept,
     const SplitHead* __restrict__ heads, const uint2* __restrict__ lists, int n_lists, int cap, int rank_opt)
 {
     using SH = CompressShared<kCapBig>;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    SH& sh = *reinterpret_cast<SH*>(smem_raw);
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int64_t row = blockIdx.x;
     const SplitHead* const head = heads + row * n_lists;
     const uint2* const list = lists + row * n_lists * (int64_t)cap;
     const float c = 1.4426950408889634f * inv_T;
@@ -473,14 +497,32 @@ __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
     const int n_slots = n_lists * cap;
     const float per_round = 1.0f / (float)n_lists;
     auto place_of = [&](int f, int& l, int& q) { q = (int)(((float)f + 0.5f) * per_round); l = f - q * n_lists; };     // (f < 2^15: exact)
-    const uint4 h = *reinterpret_cast<const uint4*>(head + min(lane, n_lists - 1));
-    const double s_head = head[min(lane, n_lists - 1)].s;
+    auto entry = [&](int l, int q) {
+        const uint2* const at = &list[l * cap + q];
+        if (!SHARED) return *at;
+        const unsigned long long t = get_shared(reinterpret_cast<const unsigned long long*>(at));
+        return make_uint2((unsigned)t, (unsigned)(t >> 32));
+    };
+    uint4 h;
+    double s_head;
+    {
+        const SplitHead* const my = head + min(lane, n_lists - 1);
+        if (SHARED) {
+            const unsigned long long* const w = reinterpret_cast<const unsigned long long*>(my);
+            const unsigned long long h0 = get_shared(w), h1 = get_shared(w + 1), h2 = get_shared(w + 2);
+            h = make_uint4((unsigned)h0, (unsigned)(h0 >> 32), (unsigned)h1, (unsigned)(h1 >> 32));
+            s_head = __longlong_as_double((long long)h2);
+        } else {
+            h = *reinterpret_cast<const uint4*>(my);
+            s_head = my->s;
+        }
+    }
     uint2 e[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
         int l, q;
         place_of(min(u * kT + tid, n_slots - 1), l, q);
-        if (u * kT < n_slots) e[u] = list[l * cap + q];
+        if (u * kT < n_slots) e[u] = entry(l, q);
     }
     zero_hist(sh);
     if (tid == 0) { sh.maxbin = 0; sh.overflowed = 0; }
@@ -544,7 +586,7 @@ __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
         for (int f0 = kAhead * kT; f0 < n_slots; f0 += kT) {
             int l, q;
             place_of(min(f0 + tid, n_slots - 1), l, q);
-            take(f0 + tid, list[l * cap + q]);
+            take(f0 + tid, entry(l, q));
         }
         order_prepare(sh, total);
         if (tid == kT - 1) lse[row] = (float)((double)M * (double)inv_T + log(S));
@@ -563,6 +605,42 @@ __global__ __launch_bounds__(kT, 4) void split_finish_kernel(
     }
     __syncthreads();
     split_row_again<BF16>(row, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, rank_opt);
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kT, 4) void split_finish_kernel(
+    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int k, float top_p,
+    int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
+    float* __restrict__ mass, float* __restrict__ lse,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept,
+    const SplitHead* __restrict__ heads, const uint2* __restrict__ lists, int n_lists, int cap, int rank_opt)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    split_finish<BF16, false>(*reinterpret_cast<CompressShared<kCapBig>*>(smem_raw), blockIdx.x, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse,
+                              seq_off, n_accept, heads, lists, n_lists, cap, rank_opt);
+}
+
+// Both in one launch: the last workgroup of a row to arrive (arrive_last) finishes it.  512 threads do the selection as well, half of a lane's
+// elements each, and form the share's sum in the order of 256 (the same bits).  What it gives and the calls it serves: split_one_launch.
+template <bool BF16>
+__global__ __launch_bounds__(kT, 4) void split_compress_kernel(
+    const void* __restrict__ logits, int64_t ld, int V, float inv_T, int rank, int cap, int narrow, int lanes, int k, float top_p,
+    int32_t* __restrict__ idx, float* __restrict__ prob, int32_t* __restrict__ count,
+    float* __restrict__ mass, float* __restrict__ lse,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ n_accept,
+    SplitHead* __restrict__ heads, uint2* __restrict__ lists, unsigned long long* __restrict__ words, int rank_opt)
+{
+    using G = SplitGeom<BF16, kT>;
+    using SH = CompressShared<kCapBig>;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    SH& sh = *reinterpret_cast<SH*>(smem_raw);
+    static_assert(G::IMAGE <= SH::kCap && G::HIST <= SH::kCap, "the selection's arrays lie where the candidates will");
+    const int64_t row = blockIdx.y;
+    unsigned long long* const word = arrival_word(words, row);
+    split_select<BF16, kT, true>(sh.cand_id, sh.cand_val, row, (int)blockIdx.x, (int)gridDim.x, logits, ld, V, inv_T, rank, cap, narrow, lanes, heads, lists,
+                                 seq_off, n_accept, [&] { if (threadIdx.x == 0) open_arrival(word); });
+    if (!arrive_last(word, gridDim.x, threadIdx.x == 0)) return;
+    split_finish<BF16, true>(sh, row, logits, ld, V, inv_T, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, heads, lists, (int)gridDim.x, cap, rank_opt);
 }
 
 }  // namespace
@@ -590,7 +668,7 @@ hipError_t launch_split_finish(const void* logits, int dtype, int64_t ld, int n_
 
 hipError_t launch_split_compress(const void* logits, int dtype, int64_t ld, int n_rows, int V, float temperature,
                                  int k, float top_p, int32_t* idx, float* prob, int32_t* count, float* mass,
-                                 float* lse, const int32_t* seq_off, const int32_t* n_accept, void* scratch, hipStream_t stream)
+                                 float* lse, const int32_t* seq_off, const int32_t* n_accept, void* scratch, size_t scratch_bytes, hipStream_t stream)
 {
     const SplitPlan p = split_plan(dtype, n_rows, V, k);
     const float inv_T = 1.0f / temperature;
@@ -598,6 +676,21 @@ hipError_t launch_split_compress(const void* logits, int dtype, int64_t ld, int 
     uint2* const lists = (uint2*)(heads + (size_t)n_rows * p.parts);
     const int narrow = p.rank <= kSplitNarrowRank;
     const dim3 grid(p.parts, n_rows);
+    if (split_one_launch(dtype, n_rows, V, k) && scratch_bytes >= split_one_launch_bytes(dtype, n_rows, V, k)) {
+        static DeviceFlags limit_raised[2] = {};
+        const int bf = dtype == 1;
+        const size_t smem = sizeof(CompressShared<kCapBig>);
+        int dev = 0;
+        if (hipError_t e = raise_lds_limit_once(bf ? (const void*)split_compress_kernel<true> : (const void*)split_compress_kernel<false>, smem, limit_raised[bf], dev)) return e;
+        unsigned long long* const words = (unsigned long long*)((char*)scratch + split_words_at(dtype, n_rows, V, k));
+        // (twice the lanes, each with half as many elements)
+        const int lanes = p.lanes ? (int)ceilf(512.f * (1.f - expf((float)p.rank * (-1.f / 512.f)))) : 0;
+#define PICOSPEC_SPLIT(BF) \
+        hipLaunchKernelGGL(split_compress_kernel<BF>, grid, dim3(kT), smem, stream, logits, ld, V, inv_T, p.rank, p.cap, narrow, lanes, k, top_p, idx, prob, count, mass, lse, seq_off, n_accept, heads, lists, words, compress_rank(k, V, false))
+        if (bf) PICOSPEC_SPLIT(true); else PICOSPEC_SPLIT(false);
+#undef PICOSPEC_SPLIT
+        return hipGetLastError();
+    }
     if (dtype == 1) hipLaunchKernelGGL(split_select_kernel<true>, grid, dim3(kSplitThreads), 0, stream, logits, ld, V, inv_T, p.rank, p.cap, narrow, p.lanes, heads, lists, seq_off, n_accept);
     else            hipLaunchKernelGGL(split_select_kernel<false>, grid, dim3(kSplitThreads), 0, stream, logits, ld, V, inv_T, p.rank, p.cap, narrow, p.lanes, heads, lists, seq_off, n_accept);
     if (hipError_t e = hipGetLastError()) return e;
