@@ -367,8 +367,8 @@ __device__ __attribute__((noinline)) void split_row_again(
 // of which `valid` has the bit.  As order_top_k and emit_row, with less between: one histogram, on a linear scale of the values (bf16: with
 // the id, as its LINEAR places), whose bins hold one or two candidates of the upper end of any smooth distribution; the candidates of the
 // bins up to the one that holds the n-th are laid out bin by bin, and whoever reads position i of that ranks it in its bin and writes it:
-// positions i and their ranks are a bin apart, so the stores are as good as in order.  Returns false with nothing written if a bin is too
-// crowded (values on a grid, an outlier that stretches the scale); else whether the n-th lies above `above`, below which candidates are missing.
+// positions i and their ranks are a bin apart, so the stores are as good as in order.  Few::crowded, with nothing written: a
+// bin is too crowded (values on a grid, an outlier that stretches the scale); missing: the n-th does not lie above `above`, below which candidates are missing.
 // `meanwhile` forms the row's sum of exponentials while the histogram's atomics are on their way.
 // Bound by the chain of barriers, six of them (ten before): the finish of one row of 32,000 fp32, k = 64: 4.5 -> 3.6 us from its first instruction, of 64 of
 // 151,936, k = 1024: 7.4 -> 5.6; a round of that row 16.4 -> 15.6, the draft of those 22.0 -> 20.0.
