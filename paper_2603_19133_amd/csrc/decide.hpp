@@ -1007,7 +1007,9 @@ __device__ __forceinline__ void decide_rows(
         my_id[z] = ids[sl];
         my_p[z] = qp[sl];
     }
-    for (int s = tid; s < n_seg; s += kThreads) tfix[s] = 0ull;
+    // (all of it: which row is drawn from is not known yet, and rows at other offsets of a 16-byte block differ by a segment)
+    static_assert(kDecideRowsSegs <= kThreads, "one word per thread");
+    if (tid < kDecideRowsSegs) tfix[tid] = 0ull;
     for (int s = tid; s < kSegElems; s += kThreads) qimg[s] = 0.f;
     if (tid == 0) { s_first = g; s_flags = 0; }
     __syncthreads();

@@ -83,3 +83,36 @@ def test_one_wave_per_position_matches_the_general_kernel(gpu, ps, V, ld, k, gam
                 np.testing.assert_allclose(got[name], w, rtol=1.2e-7, err_msg=name)
             else:
                 np.testing.assert_array_equal(got[name], w, err_msg=name)
+
+
+def _uncleared(V, ld, N, gammas):
+    """Sequences whose row at position 1 has a segment more than the row of the wave that would clear it by its own row's count."""
+    segs = lambda r: -(-(-(-((r * ld) % N + V) // N)) // 256)
+    first = np.concatenate([[0], np.cumsum(gammas)])
+    return [b for b, g in enumerate(gammas)
+            if segs(first[b] + b + 1) > segs(first[b] + b + min((segs(first[b] + b + 1) - 1) // 64, g))]
+
+
+@pytest.mark.parametrize("dtype,V,ld", [(torch.float32, 32768, 32769), (torch.float32, 32767, 32767), (torch.bfloat16, 65535, 65535)])
+def test_the_drawn_row_may_have_a_segment_more(gpu, ps, dtype, V, ld):
+    """Rows at other offsets of a 16-byte block can be a segment longer than the sequence's first row: most of the target's mass on the last
+    ids, the first position accepted, the second rejected, LDS that holds what another kernel left there."""
+    print("[case]", V, ld, dtype, flush=True)
+    dev, k, gammas = torch.device("cuda"), 64, [3] * 24
+    assert len(_uncleared(V, ld, 4 if dtype == torch.float32 else 8, gammas)) >= 4
+    c = _case(V, V, ld, k, gammas, dtype, "normal", dev)
+    c["tgt"][:, V - 2:] += 30.0
+    c["uni"].fill_(0.5)
+    for b in range(len(gammas)):
+        c["uni"][4 * b] = 0.0
+        c["uni"][4 * b + 1:4 * b + 3] = 0.9999
+    dirty = torch.randn((1024, 40000), device=dev)
+    ps.compress(dirty, 40000, 1.0, 2048)                   # (every CU, 73 KB of LDS each)
+    got = _run(ps, c, V, k, k, 1)
+    want = _run(ps, c, V, k, 257, 1)
+    assert (want["n_accept"] == 1).mean() > 0.9 and (want["out_tok"] >= V - 2).mean() > 0.9
+    for name, w in want.items():
+        if name == "resid_mass":
+            np.testing.assert_allclose(got[name], w, rtol=1.2e-7, err_msg=name)
+        else:
+            np.testing.assert_array_equal(got[name], w, err_msg=name)
