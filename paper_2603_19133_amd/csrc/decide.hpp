@@ -700,9 +700,10 @@ struct __align__(16) SegResidualShared {
 // RT: threads (whole waves from thread 0 on) that run this, at least k / 4: every wave more is one more that goes through the
 // chain of scans and barriers, four instructions' time each once a SIMD holds several (residual_seg_threads).
 // SHARED: the table was written by other workgroups of this launch (and has no header).
+// A row outside the call's n_rows, or a record outside its n_draft (offsets that leave them), is flagged and gives token 0; nothing of it is read.
 template <bool BF16, int RT, bool SHARED = false>
 __device__ __forceinline__ void residual_seg_sequence(
-    const int b, const int j_in, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
+    const int b, const int j_in, const int n_rows, const int n_draft, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const float* __restrict__ tgt_max, const SegHeader* __restrict__ table,
     const int seg_vecs, const int stride,
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
@@ -726,6 +727,10 @@ __device__ __forceinline__ void residual_seg_sequence(
     const int64_t rt = (int64_t)d0 + b + j;
     const int64_t rd = (int64_t)d0 + j;
     bool has_q = j < g;
+    if (rt < 0 || rt >= n_rows || (has_q && (rd < 0 || rd >= n_draft))) {
+        if (tid == 0) { out_tok[b] = 0; resid_mass[b] = 0.f; flags[b] = fl | 8u; }
+        return;
+    }
     const RowView rv = row_view<BF16>(tgt_logits, ld, rt, V);
     const int nq = (rv.L + N - 1) / N;
     const int seg_elems = seg_vecs * N;

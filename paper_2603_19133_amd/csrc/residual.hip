@@ -58,9 +58,9 @@ __global__ __launch_bounds__(RT) void residual_seg_kernel(
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
     const float* __restrict__ uniforms,
-    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ flags, bool by_sequence)
+    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ flags, bool by_sequence, int n_rows)
 {
-    residual_seg_sequence<BF16, RT>(blockIdx.x, n_accept[blockIdx.x], tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
+    residual_seg_sequence<BF16, RT>(blockIdx.x, n_accept[blockIdx.x], n_rows, n_rows - (int)gridDim.x, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
                                 q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, nullptr, by_sequence);
 }
 
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(RT) void residual_spread_kernel(
     if (streams) row_stats_shared<BF16, RT / kWave>(row, b, (int)blockIdx.x, (int)gridDim.x, tgt_logits, ld, V, inv_T, reinterpret_cast<float2*>(table + 1), stride, open);
     else open();
     if (!arrive_last(arrival_word(words, b), gridDim.x, threadIdx.x == 0)) return;
-    residual_seg_sequence<BF16, RT, true>(b, j, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
+    residual_seg_sequence<BF16, RT, true>(b, j, n_rows, n_rows - (int)gridDim.y, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
                                           q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, nullptr, true);
 }
 
@@ -115,7 +115,7 @@ __device__ __forceinline__ void decide_seg(
     } else if (SPLIT) {
         write_split_lse(s_stats, rows, t0, inv_T, tgt_lse, 0, kThreads);
     }
-    residual_seg_sequence<BF16, RT>(blockIdx.x, first, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
+    residual_seg_sequence<BF16, RT>(blockIdx.x, first, n_rows, n_rows - (int)gridDim.x, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
                                     q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, res_flags,
                                     SPLIT ? s_stats : nullptr);
 }
@@ -161,10 +161,10 @@ __global__ __launch_bounds__(kThreads) void decide_rows_kernel(
 static hipError_t launch_residual_seg(const void* tgt_logits, int dtype, int64_t ld, int V, float it, int B, const int32_t* seq_off,
                                       const int32_t* n_accept, const float* tgt_max, const int32_t* q_idx, const float* q_prob,
                                       const int32_t* q_count, const float* q_mass, int k, int renorm, const float* uniforms,
-                                      int32_t* out_tok, float* resid_mass, uint32_t* flags, const void* seg_table, const StatsShape& sh, bool by_sequence, hipStream_t stream)
+                                      int32_t* out_tok, float* resid_mass, uint32_t* flags, const void* seg_table, const StatsShape& sh, bool by_sequence, int64_t n_rows, hipStream_t stream)
 {
 #define PICOSPEC_RESIDUAL(BF, RT) \
-    hipLaunchKernelGGL((residual_seg_kernel<BF, RT>), dim3(B), dim3(RT), 0, stream, tgt_logits, ld, V, it, seq_off, n_accept, tgt_max, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, by_sequence)
+    hipLaunchKernelGGL((residual_seg_kernel<BF, RT>), dim3(B), dim3(RT), 0, stream, tgt_logits, ld, V, it, seq_off, n_accept, tgt_max, (const SegHeader*)seg_table, sh.seg_vecs, sh.stride, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, by_sequence, (int)n_rows)
 #define PICOSPEC_RESIDUAL_RT(BF) \
     switch (residual_seg_threads(k)) { case 256: PICOSPEC_RESIDUAL(BF, 256); break; case 512: PICOSPEC_RESIDUAL(BF, 512); break; default: PICOSPEC_RESIDUAL(BF, 1024); }
     if (dtype == 1) { PICOSPEC_RESIDUAL_RT(true) } else { PICOSPEC_RESIDUAL_RT(false) }
@@ -195,7 +195,7 @@ hipError_t launch_residual_split(const void* tgt_logits, int dtype, int64_t ld, 
     if (hipError_t e = launch_row_stats_parts(tgt_logits, dtype, ld, (int)n_rows, V, temperature, B, 0, seq_off, nullptr, nullptr, scratch, stream, n_accept))
         return e;
     return launch_residual_seg(tgt_logits, dtype, ld, V, inv_T, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass,
-                               k, renorm, uniforms, out_tok, resid_mass, flags, scratch, sh, true, stream);
+                               k, renorm, uniforms, out_tok, resid_mass, flags, scratch, sh, true, n_rows, stream);
 }
 
 hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V, float temperature,
@@ -209,7 +209,7 @@ hipError_t launch_residual(const void* tgt_logits, int dtype, int64_t ld, int V,
         if (B == 0) return hipSuccess;
         const StatsShape sh = split_stats_serves(n_rows, V) ? split_stats_shape(dtype, V) : stats_shape(dtype, n_rows, V);   // (as the verification laid it out)
         return launch_residual_seg(tgt_logits, dtype, ld, V, 1.0f / temperature, B, seq_off, n_accept, tgt_max, q_idx, q_prob, q_count, q_mass,
-                                   k, renorm, uniforms, out_tok, resid_mass, flags, seg_table, sh, false, stream);
+                                   k, renorm, uniforms, out_tok, resid_mass, flags, seg_table, sh, false, n_rows, stream);
     }
     static DeviceFlags limit_raised[2] = {};
     const size_t smem = sizeof(ResidualShared);

@@ -144,6 +144,45 @@ def test_draw(gpu, ps, dtype, V, B, k):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("off,n,outside", [([0, 3, 6, 12], [1, 3, 5], [2]),          # the drawn row lies behind the call's
+                                           ([0, 3, 6, 12], [1, 3, 3], [2]),          # ... its draft's record alone
+                                           ([0, 3, 12, 9], [3, 7, 0], [1, 2]),       # offsets that descend
+                                           ([0, -1, 2, 9], [0, 0, 2], [1]),          # a record in front of the call's
+                                           ([-2, -1, 2, 9], [0, 0, 2], [0, 1])])
+def test_a_draw_that_leaves_the_call(gpu, ps, dtype, off, n, outside):
+    """The drawn row or the record lies outside the call's (inside the tensors, which are larger): token 0, flagged, in one launch, in two and from a
+    verification's table; the other sequences draw as ever."""
+    V, k, front = 33001, 64, 8
+    print("[case]", off, n, dtype, flush=True)
+    c = _Case(ps, 5, dtype, V, V + 1, [3, 3, 3], k)
+    mx, sm, _ = ps.row_stats(c.z, V, 0.9)
+    # (everything once more with room in front of it)
+    z = torch.cat([c.z[:front], c.z])
+    pad = lambda t: torch.cat([t[:front], t])[front:]
+    z, mx, sm, uni, idx, prob, count, mass = z[front:], *[pad(t) for t in (mx, sm, c.uni, c.q.idx, c.q.prob, c.q.count, c.q.mass)]
+    seq, na = torch.tensor(off, dtype=torch.int32, device=z.device), torch.tensor(n, dtype=torch.int32, device=z.device)
+    def draw(ws, call, seq=seq, na=na):
+        _, res = c.fresh()
+        ps._check(call(z, c.code, z.stride(0), V, 0.9, c.B, c.N, seq, na, mx, sm, idx, prob, count, mass, k, 1, uni,
+                       res.out_tok, res.resid_mass, res.flags, ws, ps._stream()))
+        return [t.cpu().numpy() for t in vars(res).values()]
+    room = torch.randint(0, 256, (max(_scratch_bytes(dtype, c.B, c.B, V), _table_bytes(ps, dtype, c.B, V)) + 65536,), dtype=torch.uint8, device=z.device)
+    one, two = draw(room, ps._nat.sample_residual_ws), draw(room[:_table_bytes(ps, dtype, c.B, V)], ps._nat.sample_residual_ws)
+    ws = ps.alloc_workspace(dtype, c.rows, V, z.device)
+    ver, _ = c.fresh()
+    c.z = z
+    c.verify(ws, ver, False)
+    table = draw(ws, ps._nat.sample_residual)
+    inside = [b for b in range(c.B) if b not in outside]
+    for tok, resid, flags in (one, two, table):
+        assert all(tok[b] == 0 and resid[b] == 0 and flags[b] & 8 for b in outside), (tok, resid, flags)
+        assert all(0 < resid[b] <= 1.0 and 0 <= tok[b] < V and (flags[b] & 8 == 0 or off[b + 1] < off[b]) for b in inside), (tok, resid, flags)
+        np.testing.assert_array_equal(tok, one[0])
+        np.testing.assert_array_equal(flags, one[2])
+        np.testing.assert_allclose(resid, one[1], rtol=1e-6)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("V,rows", [(62500, 1), (125003, 3), (64000, 128), (128256, 160), (1048576, 2)])
 def test_row_statistics(gpu, ps, dtype, V, rows):
     print("[case]", V, rows, dtype, flush=True)
