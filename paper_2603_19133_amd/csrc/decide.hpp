@@ -144,8 +144,7 @@ __device__ __forceinline__ void write_split_lse(const SplitStats* s_stats, int2 
 // split_stats_serves): they are formed here and written to tgt_max / tgt_sum / tgt_lse.  s_stats (nullable, LDS): they
 // are left there by position as well, and tgt_lse is not written: the caller does that off the critical path
 // (write_split_lse), for the positions that come back in `rows`.
-// WAVES: waves of the workgroup.  SHARED: the table was written by other workgroups of this launch.
-template <bool BF16, bool TABLE = false, int WAVES = kWaves, bool SHARED = false>
+template <bool BF16, bool TABLE = false>
 __device__ __forceinline__ int accept_sequence(
     const int b, const int B, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
@@ -177,7 +176,7 @@ __device__ __forceinline__ int accept_sequence(
 
     // every target row of the range must have finite statistics
     if constexpr (!TABLE) {
-        for (int t = begin + tid; t <= end; t += WAVES * kWave)
+        for (int t = begin + tid; t <= end; t += kThreads)
             if (nonfinite(tgt_max[t0 + t], tgt_sum[t0 + t])) fl |= 2u;
     }
 
@@ -189,7 +188,7 @@ __device__ __forceinline__ int accept_sequence(
         rows_begin = all_rows && b == 0 ? min(begin, -(int)t0) : begin;
         rows_end = all_rows && b + 1 == B ? max(end + 1, (int)(n_rows - t0)) : end + 1;
     }
-    for (int i = rows_begin + wave; i < rows_end; i += WAVES) {
+    for (int i = rows_begin + wave; i < rows_end; i += kWaves) {
         const int64_t rt = t0 + i;
         const bool decides = !TABLE || (i >= begin && i < end);       // (the other rows have statistics only)
         if (TABLE && (rt < 0 || rt >= n_rows)) {      // (offsets that leave the call's rows: nothing is written for such a row)
@@ -224,7 +223,7 @@ __device__ __forceinline__ int accept_sequence(
             const int nq = (rv.L + Vec<BF16>::N - 1) / Vec<BF16>::N;
             n_seg = (nq + seg_vecs - 1) / seg_vecs;
             table_row = reinterpret_cast<const float2*>(table + 1) + rt * (int64_t)stride;
-            stats.template load<SHARED>(table_row, n_seg);
+            stats.load(table_row, n_seg);
         }
         const bool bad = x < 0 || x >= V;
         const float z_t = bad || !decides ? 0.f : logit_at<BF16>(tgt_logits, ld, rt, x);
@@ -239,7 +238,7 @@ __device__ __forceinline__ int accept_sequence(
         // (the row's statistics are formed while the last two loads are on their way)
         if constexpr (TABLE) {
             double S;
-            stats.template combine<SHARED>(table_row, n_seg, c, M_t, S);
+            stats.combine(table_row, n_seg, c, M_t, S);
             S_t = (float)S;
             if (lane == 0) {
                 tgt_max[rt] = M_t;

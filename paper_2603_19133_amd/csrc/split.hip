@@ -44,9 +44,8 @@ struct __align__(16) SplitHead {
     float mx, tau, r;                          // largest value; threshold (every element above it is in the list); reference exponent
     int count;                                 // entries of the list (more than the list holds: the row is given up)
     double s;                                  // sum of 2^(z c - r) over the share
-    double unused;
 };
-static_assert(sizeof(SplitHead) == 32, "two 16-byte loads");
+static_assert(sizeof(SplitHead) == 32, "a 16-byte load and one of eight");
 
 // Workgroup `part` of the P workgroups of row `row` of the call.  hist, image: LDS on 16-byte boundaries.  SHARED: for another workgroup of this
 // launch to read.  `meanwhile` is run behind the loads.  The share's sum is formed in the same order by workgroups of either size.
@@ -302,17 +301,14 @@ __device__ __forceinline__ void split_select(
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < 4; ++w) s += wave_s[w];
-        SplitHead h{mx, tau, ref, finite || (!(mx > kNegInf) && s == s) ? held : cap + 1, s, 0.0};
+        SplitHead h{mx, tau, ref, finite || (!(mx > kNegInf) && s == s) ? held : cap + 1, s};
         if (SHARED) {
             const unsigned long long* src = reinterpret_cast<const unsigned long long*>(&h);
             unsigned long long* dst = reinterpret_cast<unsigned long long*>(heads + list);
 #pragma unroll
             for (int i = 0; i < 3; ++i) put_shared(dst + i, src[i]);
         } else {
-            uint4* dst = reinterpret_cast<uint4*>(heads + list);
-            const uint4* src = reinterpret_cast<const uint4*>(&h);
-            dst[0] = src[0];
-            dst[1] = src[1];
+            heads[list] = h;
         }
     }
 }
