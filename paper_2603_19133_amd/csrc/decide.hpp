@@ -144,9 +144,11 @@ __device__ __forceinline__ void write_split_lse(const SplitStats* s_stats, int2 
 // split_stats_serves): they are formed here and written to tgt_max / tgt_sum / tgt_lse.  s_stats (nullable, LDS): they
 // are left there by position as well, and tgt_lse is not written: the caller does that off the critical path
 // (write_split_lse), for the positions that come back in `rows`.
+// Positions whose row lies outside the call's n_rows, or whose draft outside its n_rows - B drafts (offsets that leave them), are flagged and
+// rejected; nothing is read or written for them.
 template <bool BF16, bool TABLE = false>
 __device__ __forceinline__ int accept_sequence(
-    const int b, const int B, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
+    const int b, const int B, const int n_rows, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
     const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob,
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
@@ -155,7 +157,7 @@ __device__ __forceinline__ int accept_sequence(
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok,
     uint32_t* __restrict__ flags, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end,
     float* __restrict__ tgt_lse = nullptr, const SegHeader* __restrict__ table = nullptr, int seg_vecs = 0, int stride = 0,
-    int n_rows = 0, bool all_rows = false, SplitStats* s_stats = nullptr, int2* rows = nullptr)
+    bool all_rows = false, SplitStats* s_stats = nullptr, int2* rows = nullptr)
 {
     __shared__ int s_first;
     __shared__ unsigned s_flags;
@@ -177,7 +179,8 @@ __device__ __forceinline__ int accept_sequence(
     // every target row of the range must have finite statistics
     if constexpr (!TABLE) {
         for (int t = begin + tid; t <= end; t += kThreads)
-            if (nonfinite(tgt_max[t0 + t], tgt_sum[t0 + t])) fl |= 2u;
+            if (t0 + t < 0 || t0 + t >= n_rows) fl |= 8u;
+            else if (nonfinite(tgt_max[t0 + t], tgt_sum[t0 + t])) fl |= 2u;
     }
 
     // (TABLE: the row behind the last position as well, and, where all of the call's rows get statistics, by the first and the last
@@ -190,13 +193,15 @@ __device__ __forceinline__ int accept_sequence(
     }
     for (int i = rows_begin + wave; i < rows_end; i += kWaves) {
         const int64_t rt = t0 + i;
-        const bool decides = !TABLE || (i >= begin && i < end);       // (the other rows have statistics only)
-        if (TABLE && (rt < 0 || rt >= n_rows)) {      // (offsets that leave the call's rows: nothing is written for such a row)
+        bool decides = !TABLE || (i >= begin && i < end);             // (the other rows have statistics only)
+        const int64_t rd = (int64_t)d0 + (decides ? i : 0);
+        const bool outside = rt < 0 || rt >= n_rows;
+        if (outside || (decides && (rd < 0 || rd >= n_rows - B))) {
             fl |= 8u;
             if (decides && lane == 0) atomicMin(&s_first, i);
-            continue;
+            decides = false;
+            if (outside || !TABLE) continue;
         }
-        const int64_t rd = (int64_t)d0 + (decides ? i : 0);
         int x = -1, cnt = 0;
         float u_t = 0.f, mass_d = 1.f, M_t = 0.f, S_t = 1.f;
         double qh = 0.0;
@@ -296,7 +301,7 @@ __device__ __forceinline__ void look_up_positions(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     for (int i = begin + wave; i < end; i += WAVES) {
         const int64_t rd = (int64_t)d0 + i, rt = rd + b;
-        if (rt < 0 || rt >= n_rows || rd >= n_draft) continue;      // (offsets that leave the call's rows or drafts)
+        if (rt < 0 || rt >= n_rows || rd < 0 || rd >= n_draft) continue;      // (offsets that leave the call's rows or drafts)
         const int x = draft_tok[rd];
         double qh = 0.0;
         float mass_d = 1.f;
@@ -356,8 +361,8 @@ __device__ __forceinline__ void decide_spread(
     for (int i = rows_begin + wave; i < rows_end; i += WAVES) {
         const int64_t rt = t0 + i, rd = (int64_t)d0 + i;
         const bool decides = i >= begin && i < end;
-        const bool outside = rt < 0 || rt >= n_rows;
-        if (outside || (decides && rd >= n_draft)) {  // (offsets that leave the call's rows, or its drafts: nothing is read or written there)
+        const bool outside = rt < 0 || rt >= n_rows, drafted = rd >= 0 && rd < n_draft;
+        if (outside || (decides && !drafted)) {       // (offsets that leave the call's rows, or its drafts: nothing is read or written there)
             fl |= 8u;
             if (decides && lane == 0) atomicMin(&s_first, i);
             if (outside) continue;
@@ -377,7 +382,7 @@ __device__ __forceinline__ void decide_spread(
             tgt_max[rt] = M;
             tgt_sum[rt] = S_t;
             if (i >= begin && i <= end && (!(fabsf(M) < __builtin_huge_valf()) || !(S_t > 0.f) || !(S_t < __builtin_huge_valf()))) fl |= 2u;
-            if (decides && rd < n_draft) {
+            if (decides && drafted) {
                 const unsigned f = (unsigned)(at >> 32);
                 const bool bad = f & 8u;
                 const double qh = __longlong_as_double((long long)qh_bits), u = (double)u_t;

@@ -40,9 +40,9 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(
     const int32_t* __restrict__ q_count, const float* __restrict__ q_mass, int k, int renorm,
     const float* __restrict__ uniforms, float* __restrict__ tgt_max, float* __restrict__ tgt_sum,
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
-    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags)
+    int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags, int n_rows)
 {
-    const int first = accept_sequence<BF16>(blockIdx.x, (int)gridDim.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
+    const int first = accept_sequence<BF16>(blockIdx.x, (int)gridDim.x, n_rows, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
                                             q_count, q_mass, k, renorm, nullptr, uniforms, tgt_max, tgt_sum,
                                             n_accept, p_tok, q_tok, flags, nullptr, nullptr);
     residual_sequence<BF16>(blockIdx.x, first, tgt_logits, ld, V, inv_T, seq_off, tgt_max, tgt_sum,
@@ -101,10 +101,10 @@ __device__ __forceinline__ void decide_seg(
 {
     __shared__ SplitStats s_stats[SPLIT ? kSplitStatsRows : 1];
     int2 rows = make_int2(0, 0);
-    const int first = accept_sequence<BF16, SPLIT>(blockIdx.x, (int)gridDim.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
+    const int first = accept_sequence<BF16, SPLIT>(blockIdx.x, (int)gridDim.x, n_rows, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
                                                    q_count, q_mass, k, renorm, nullptr, uniforms, tgt_max, tgt_sum,
                                                    n_accept, p_tok, q_tok, flags, nullptr, nullptr,
-                                                   tgt_lse, table, seg_vecs, stride, n_rows, true, SPLIT ? s_stats : nullptr, &rows);
+                                                   tgt_lse, table, seg_vecs, stride, true, SPLIT ? s_stats : nullptr, &rows);
     const int64_t t0 = (int64_t)seq_off[blockIdx.x] + blockIdx.x;
     // the waves that the draw has no use for write the log-sum-exps and end here (a barrier waits for those that are left)
     if (RT < kThreads) {
@@ -268,8 +268,8 @@ hipError_t launch_decide(const void* tgt_logits, int dtype, int64_t ld, int V, f
     }
     if (B == 0) return hipSuccess;
     const float inv_T = 1.0f / temperature;
-    if (which) hipLaunchKernelGGL(b16, dim3(B), dim3(kThreads), smem, stream, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags);
-    else       hipLaunchKernelGGL(f32, dim3(B), dim3(kThreads), smem, stream, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags);
+    if (which) hipLaunchKernelGGL(b16, dim3(B), dim3(kThreads), smem, stream, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags, (int)n_rows);
+    else       hipLaunchKernelGGL(f32, dim3(B), dim3(kThreads), smem, stream, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags, (int)n_rows);
     return hipGetLastError();
 }
 

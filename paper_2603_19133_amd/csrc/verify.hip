@@ -290,9 +290,9 @@ __global__ __launch_bounds__(kThreads, TABLE ? 4 : 8) void accept_kernel(
     uint32_t* __restrict__ flags, const int32_t* __restrict__ pos_begin, const int32_t* __restrict__ pos_end,
     const SegHeader* __restrict__ table, int seg_vecs, int stride, int n_rows, bool all_rows)
 {
-    accept_sequence<BF16, TABLE>(blockIdx.x, (int)gridDim.x, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k,
+    accept_sequence<BF16, TABLE>(blockIdx.x, (int)gridDim.x, n_rows, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k,
                                  renorm, q_scalar, uniforms, tgt_max, tgt_sum, n_accept, p_tok, q_tok, flags, pos_begin, pos_end,
-                                 tgt_lse, table, seg_vecs, stride, n_rows, all_rows);
+                                 tgt_lse, table, seg_vecs, stride, all_rows);
 }
 
 }  // namespace

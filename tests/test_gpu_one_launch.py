@@ -14,7 +14,7 @@ def ps():
     return binding
 
 
-NV, WORD = 4, 256
+NV, WORD, FRONT = 4, 256, 4
 
 
 def _segments(dtype, V):
@@ -48,11 +48,16 @@ class _Case:
         pick = torch.randint(0, min(3, k), (room,), device=dev, generator=g)
         self.tok = self.q.idx.gather(1, pick.unsqueeze(1).long())[:, 0].contiguous()
         self.scalar = torch.rand(room, device=dev, generator=g)
+        behind = lambda t: torch.cat([t[:FRONT], t])[FRONT:]      # (room in front of what is read by draft row)
+        self.q = ps.Compressed(*[behind(t) for t in (self.q.idx, self.q.prob, self.q.count, self.q.mass, self.q.lse)], k)
+        self.tok, self.scalar = behind(self.tok), behind(self.scalar)
         self.code = ps._dtype_code(self.z)
 
     def fresh(self):
         ver, res = self.ps.alloc_verified(self.B, self.N + 8, self.z.device), self.ps.alloc_residual(self.B, self.z.device)
-        for t in list(vars(ver).values()) + list(vars(res).values()):
+        self.fronts = [torch.empty(FRONT + self.N + 8, device=self.z.device) for _ in range(2)]
+        ver.p_tok, ver.q_tok = [t[FRONT:] for t in self.fronts]
+        for t in list(vars(ver).values()) + list(vars(res).values()) + self.fronts:
             t.fill_(-7)
         return ver, res
 
@@ -78,7 +83,8 @@ def _same(a, b):
 CASES = [(16384, 16384, [1], 64, 0, None), (20000, 20003, [0, 3, 15, 0, 16], 70, 0, None), (33001, 33001, [4] * 9, 257, 3, None),
          (40000, 40001, [2, 2, 2], 10, 2, [2, 4, 6, 8]),          # rows in front of the first sequence
          (33000, 33000, [3, 3, 3], 10, 0, [0, 5, 3, 9]),          # offsets that descend
-         (33000, 33000, [3, 3, 3], 10, 0, [0, 3, 6, 12])]         # ... and that leave the call's rows
+         (33000, 33000, [3, 3, 3], 10, 0, [0, 3, 6, 12]),         # ... that leave the call's rows
+         (33000, 33000, [3, 3, 3], 10, 0, [0, -1, 2, 9])]         # ... and whose drafts lie in front of the call's
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
@@ -100,12 +106,16 @@ def test_verification(gpu, ps, dtype, V, ld, gammas, k, extra, off, q_scalar):
         want, _ = c.fresh()
         with pytest.MonkeyPatch.context() as m:                   # two launches: statistics and acceptance from a table of their own
             c.verify(None, want, q_scalar, r)
+            assert all(bool((t[:FRONT] == -7).all()) for t in c.fronts)
         for fill in ("random", "ones", "again"):
             if fill == "ones":
                 garbage.fill_(255)
             got, _ = c.fresh()
             c.verify(garbage, got, q_scalar, r)
             torch.cuda.synchronize()
+            assert all(bool((t[:FRONT] == -7).all()) for t in c.fronts)
+            if off is not None and min(off) < 0:
+                assert got.n_accept[1] == 0 and got.flags[1] & 8
             a, w = [{n: t.cpu().numpy() for n, t in vars(v).items()} for v in (got, want)]
             if off is not None and off[-1] > c.N:
                 # rows behind the call's are neither read nor written here: flagged and rejected
