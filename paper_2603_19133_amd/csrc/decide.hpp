@@ -74,7 +74,8 @@ struct RecordScan {
     }
     // the slot among the record's first cnt that holds x, or -1; in every lane
     __device__ __forceinline__ int find(const int32_t* __restrict__ ids, int cnt, int x) const {
-        const int lane = threadIdx.x & (kWave - 1);
+        int lane = threadIdx.x & (kWave - 1);
+        asm volatile("" : "+v"(lane));           // (the slots are formed here, not held from in front of a caller's loop)
         int slot = -1;
         // The record is ordered by probability and the token was drawn from it, so it sits near the
         // front more often than not: the scan goes in rounds of 1024 ids and stops at the round
@@ -286,10 +287,69 @@ __device__ __forceinline__ int accept_sequence(
     return first;
 }
 
+// What the acceptance of a position needs besides its row's statistics: qhat, the target's logit at the token, and flags (1: not in the record,
+// 8: no id).  One wave, in every lane.
+struct Looked { double qh; float z; unsigned fl; };
+template <bool BF16>
+__device__ __forceinline__ Looked look_up_position(
+    const int64_t rd, const int64_t rt, const void* __restrict__ tgt_logits, int64_t ld, int V, const int32_t* __restrict__ draft_tok,
+    const int32_t* __restrict__ q_idx, const float* __restrict__ q_prob, const int32_t* __restrict__ q_count, const float* __restrict__ q_mass,
+    int k, int renorm, const float* __restrict__ q_scalar)
+{
+    const int x = draft_tok[rd];
+    const bool bad = x < 0 || x >= V;
+    Looked at{0.0, 0.f, bad ? 8u : 0u};
+    float mass_d = 1.f;
+    int cnt = 0;
+    const int32_t* ids = q_idx;
+    RecordScan scan;
+    if (q_scalar) {
+        at.qh = (double)q_scalar[rd];
+    } else {
+        cnt = q_count[rd];
+        if (renorm) mass_d = q_mass[rd];
+        ids = q_idx + rd * k;
+        scan.load(ids, k);
+    }
+    at.z = bad ? 0.f : logit_at<BF16>(tgt_logits, ld, rt, x);
+    if (!q_scalar) {
+        const int slot = scan.find(ids, cnt < 0 ? 0 : (cnt > k ? k : cnt), x);
+        if (slot >= 0 && !bad) {
+            at.qh = (double)q_prob[rd * k + slot];
+            if (renorm) at.qh /= (double)mass_d;
+        } else {
+            at.fl |= 1u;
+        }
+    }
+    return at;
+}
 
-// What the acceptance of a sequence's positions needs besides the rows' statistics, looked up by a workgroup of its own while others stream
-// the rows: entry rt of `found` holds the target's logit at the token and flags (1: not in the record, 8: no id), then qhat (fp64).  One
-// wave per position; for the workgroup that decides to read (get_shared).
+// The lookups of a sequence's positions by a workgroup of its own while others stream the rows, one wave per position: entry rt of `found` is kFoundWords
+// words for the workgroup that decides to read (get_shared), the logit and the halves of qhat, each with the sequence it was looked up for and the first
+// with the flags.  (Where offsets descend, positions of two sequences share a target row and its entry, which then holds words of
+// either: the sequence that does not find its own looks up again.)
+__device__ __forceinline__ void put_found(unsigned long long* entry, int b, const Looked& at) {
+    const unsigned long long tag = (unsigned long long)(b + 1) << 40, qh = (unsigned long long)__double_as_longlong(at.qh);
+    put_shared(entry, tag | (unsigned long long)at.fl << 32 | __float_as_uint(at.z));
+    put_shared(entry + 1, tag | (qh & 0xFFFFFFFFull));
+    put_shared(entry + 2, tag | qh >> 32);
+}
+struct Found {
+    unsigned long long w[kFoundWords];
+    __device__ __forceinline__ explicit Found(const unsigned long long* entry) {
+#pragma unroll
+        for (int i = 0; i < kFoundWords; ++i) w[i] = get_shared(entry + i);
+    }
+    // (uniform: every lane reads the same entry)
+    __device__ __forceinline__ bool of(int b) const {
+        const auto tag = [](unsigned long long v) { return (int)(v >> 40) - 1; };
+        return __builtin_amdgcn_readfirstlane(tag(w[0]) == b && tag(w[1]) == b && tag(w[2]) == b);
+    }
+    __device__ __forceinline__ Looked looked() const {
+        return Looked{__longlong_as_double((long long)(w[2] << 32 | (w[1] & 0xFFFFFFFFull))), __uint_as_float((unsigned)w[0]), (unsigned)(w[0] >> 32) & 0xFFu};
+    }
+};
+
 template <bool BF16, int WAVES>
 __device__ __forceinline__ void look_up_positions(
     const int b, const int d0, const int begin, const int end, const void* __restrict__ tgt_logits, int64_t ld, int V, int n_rows, int n_draft,
@@ -302,48 +362,20 @@ __device__ __forceinline__ void look_up_positions(
     for (int i = begin + wave; i < end; i += WAVES) {
         const int64_t rd = (int64_t)d0 + i, rt = rd + b;
         if (rt < 0 || rt >= n_rows || rd < 0 || rd >= n_draft) continue;      // (offsets that leave the call's rows or drafts)
-        const int x = draft_tok[rd];
-        double qh = 0.0;
-        float mass_d = 1.f;
-        int cnt = 0;
-        const int32_t* ids = q_idx;
-        RecordScan scan;
-        if (q_scalar) {
-            qh = (double)q_scalar[rd];
-        } else {
-            cnt = q_count[rd];
-            if (renorm) mass_d = q_mass[rd];
-            ids = q_idx + rd * k;
-            scan.load(ids, k);
-        }
-        const bool bad = x < 0 || x >= V;
-        unsigned fl = bad ? 8u : 0u;
-        const float z_t = bad ? 0.f : logit_at<BF16>(tgt_logits, ld, rt, x);
-        if (!q_scalar) {
-            const int slot = scan.find(ids, cnt < 0 ? 0 : (cnt > k ? k : cnt), x);
-            if (slot >= 0 && !bad) {
-                qh = (double)q_prob[rd * k + slot];
-                if (renorm) qh /= (double)mass_d;
-            } else {
-                fl |= 1u;
-            }
-        }
-        if (lane == 0) {
-            put_shared(found + 2 * rt, (unsigned long long)__float_as_uint(z_t) | (unsigned long long)fl << 32);
-            put_shared(found + 2 * rt + 1, (unsigned long long)__double_as_longlong(qh));
-        }
+        const Looked at = look_up_position<BF16>(rd, rt, tgt_logits, ld, V, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, q_scalar);
+        if (lane == 0) put_found(found + kFoundWords * rt, b, at);
     }
 }
 
 // accept_sequence<.., TABLE> of a sequence whose table rows and lookups other workgroups of this launch have left: one wave per row, one trip
-// to memory.  rows_begin .. rows_end - 1: the positions whose rows get statistics.
-template <bool BF16, int WAVES>
+// to memory.  rows_begin .. rows_end - 1: the positions whose rows get statistics.  look_again(rd, rt) is look_up_position.
+template <bool BF16, int WAVES, class F>
 __device__ __forceinline__ void decide_spread(
     const int b, const int d0, unsigned fl, const int begin, const int end, const int rows_begin, const int rows_end,
     const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T, int n_rows, int n_draft, const float* __restrict__ uniforms,
     float* __restrict__ tgt_max, float* __restrict__ tgt_sum, float* __restrict__ tgt_lse,
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
-    const SegHeader* __restrict__ table, int stride, const unsigned long long* __restrict__ found)
+    const SegHeader* __restrict__ table, int stride, const unsigned long long* __restrict__ found, const F& look_again)
 {
     __shared__ int s_first;
     __shared__ unsigned s_flags;
@@ -358,19 +390,30 @@ __device__ __forceinline__ void decide_spread(
     double S = 1.0;
     int64_t wait_lse = -1;                            // the row whose log-sum-exp is still to be written
     auto write_lse = [&] { if (wait_lse >= 0 && tgt_lse && lane == 0) tgt_lse[wait_lse] = (float)((double)M * (double)inv_T + log(S)); };
+    auto is_draft = [&](int i, int64_t rd) { return i >= begin && i < end && rd >= 0 && rd < n_draft; };
+    // (one lane: the acceptance test of accept_sequence)
+    auto decide = [&](int i, int64_t rd, const Looked& at, float M_t, float S_t, float u_t) {
+        const bool bad = at.fl & 8u;
+        const double u = (double)u_t, qh = at.qh;
+        const double p = bad ? 0.0 : exp_emit(at.z, M_t, cd) / (double)S_t;
+        fl |= at.fl;
+        if (bad || !(u < 1.0) || !(qh > 0.0 ? (u * qh < p) : true)) atomicMin(&s_first, i);
+        if (p_tok) p_tok[rd] = (float)p;
+        if (q_tok) q_tok[rd] = (float)qh;
+    };
+    bool again = false;                               // some position's entry is another sequence's
     for (int i = rows_begin + wave; i < rows_end; i += WAVES) {
         const int64_t rt = t0 + i, rd = (int64_t)d0 + i;
-        const bool decides = i >= begin && i < end;
-        const bool outside = rt < 0 || rt >= n_rows, drafted = rd >= 0 && rd < n_draft;
-        if (outside || (decides && !drafted)) {       // (offsets that leave the call's rows, or its drafts: nothing is read or written there)
+        const bool outside = rt < 0 || rt >= n_rows, decides = is_draft(i, rd);
+        if (outside || (i >= begin && i < end && !decides)) {        // (offsets that leave the call's rows, or its drafts: nothing is read or written there)
             fl |= 8u;
-            if (decides && lane == 0) atomicMin(&s_first, i);
+            if (i >= begin && i < end && lane == 0) atomicMin(&s_first, i);
             if (outside) continue;
         }
         const RowView rv = row_view<BF16>(tgt_logits, ld, rt, V);
         const int n_seg = stats_segments((rv.L + Vec<BF16>::N - 1) / Vec<BF16>::N);
         const float2* const table_row = reinterpret_cast<const float2*>(table + 1) + rt * (int64_t)stride;
-        const unsigned long long at = get_shared(found + 2 * rt), qh_bits = get_shared(found + 2 * rt + 1);    // (used where the row decides)
+        const Found entry(found + kFoundWords * rt);                 // (used where the row decides)
         const float u_t = uniforms[rt];
         TableStats stats;
         stats.load<true>(table_row, n_seg);
@@ -378,20 +421,23 @@ __device__ __forceinline__ void decide_spread(
         stats.combine<true>(table_row, n_seg, c, M, S);
         wait_lse = rt;
         const float S_t = (float)S;
+        const bool mine = entry.of(b);
+        again = again || (decides && !mine);
         if (lane == 0) {
             tgt_max[rt] = M;
             tgt_sum[rt] = S_t;
             if (i >= begin && i <= end && (!(fabsf(M) < __builtin_huge_valf()) || !(S_t > 0.f) || !(S_t < __builtin_huge_valf()))) fl |= 2u;
-            if (decides && drafted) {
-                const unsigned f = (unsigned)(at >> 32);
-                const bool bad = f & 8u;
-                const double qh = __longlong_as_double((long long)qh_bits), u = (double)u_t;
-                const double p = bad ? 0.0 : exp_emit(__uint_as_float((unsigned)at), M, cd) / (double)S_t;
-                fl |= f;
-                if (bad || !(u < 1.0) || !(qh > 0.0 ? (u * qh < p) : true)) atomicMin(&s_first, i);            // (accept_sequence's test)
-                if (p_tok) p_tok[rd] = (float)p;
-                if (q_tok) q_tok[rd] = (float)qh;
-            }
+            if (decides && mine) decide(i, rd, entry.looked(), M, S_t, u_t);
+        }
+    }
+    if (again) {                                      // (uniform; a pass of its own, which holds no row's statistics in registers: each wave reads those it wrote)
+        write_lse();
+        wait_lse = -1;
+        for (int i = rows_begin + wave; i < rows_end; i += WAVES) {
+            const int64_t rt = t0 + i, rd = (int64_t)d0 + i;
+            if (rt < 0 || rt >= n_rows || !is_draft(i, rd) || Found(found + kFoundWords * rt).of(b)) continue;
+            const Looked at = look_again(rd, rt);
+            if (lane == 0) decide(i, rd, at, tgt_max[rt], tgt_sum[rt], uniforms[rt]);
         }
     }
     if (fl) atomicOr(&s_flags, fl);

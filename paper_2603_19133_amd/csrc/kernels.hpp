@@ -284,8 +284,9 @@ inline size_t split_table_end(int dtype, int64_t rows, int V) { return (sizeof(S
 inline size_t row_stats_words_at(int dtype, int64_t rows, int V) { return split_table_end(dtype, rows, V); }
 inline size_t row_stats_scratch_bytes(int dtype, int64_t rows, int V) { return row_stats_words_at(dtype, rows, V) + (size_t)rows * kArrivalStride; }
 inline size_t verify_words_at(int dtype, int64_t rows, int V) { return split_table_end(dtype, rows, V); }
+constexpr int kFoundWords = 3;                   // 64-bit words per position looked up
 inline size_t verify_found_at(int dtype, int64_t rows, int64_t B, int V) { return verify_words_at(dtype, rows, V) + (size_t)(B + 1) * kArrivalStride; }
-inline size_t verify_scratch_bytes(int dtype, int64_t rows, int64_t B, int V) { return verify_found_at(dtype, rows, B, V) + (size_t)rows * 16; }   // (16 bytes per position looked up)
+inline size_t verify_scratch_bytes(int dtype, int64_t rows, int64_t B, int V) { return verify_found_at(dtype, rows, B, V) + (size_t)rows * kFoundWords * 8; }
 inline size_t residual_words_at(int dtype, int64_t B, int V) { return split_table_end(dtype, B, V); }
 inline size_t residual_scratch_bytes(int dtype, int64_t B, int V) { return residual_words_at(dtype, B, V) + (size_t)B * kArrivalStride; }
 

@@ -259,6 +259,11 @@ __global__ __launch_bounds__(512, 6) void verify_spread_kernel(const VerifySprea
     const bool ranged = a->ranged;
     int d0 = here(s_d0), begin = here(s_begin), end = here(s_end);
     unsigned wrong = (unsigned)here((int)s_wrong);
+    auto look_again = [](int64_t rd, int64_t rt) {
+        const auto a = args_here<VerifySpreadArgs>();
+        return look_up_position<BF16>(rd, rt, plain(a->tgt_logits), a->ld, a->V, plain(a->draft_tok), plain(a->q_idx), plain(a->q_prob), plain(a->q_count),
+                                      plain(a->q_mass), a->k, a->renorm, plain(a->q_scalar));
+    };
     for (int s = group < B ? group : 0, n = group < B ? 1 : B; n > 0; --n, ++s) {
         if (group == B) {
             d0 = plain(a->seq_off)[s];
@@ -271,7 +276,7 @@ __global__ __launch_bounds__(512, 6) void verify_spread_kernel(const VerifySprea
         decide_spread<BF16, kWavesHere>(s, d0, wrong, begin, end, !ranged && s == 0 ? min(begin, -t0) : begin,
                                         !ranged && s + 1 == B ? max(end + 1, a->n_rows - t0) : end + 1, plain(a->tgt_logits), a->ld, a->V, a->inv_T, a->n_rows, a->n_rows - B,
                                         plain(a->uniforms), plain(a->tgt_max), plain(a->tgt_sum), plain(a->tgt_lse), plain(a->n_accept), plain(a->p_tok), plain(a->q_tok), plain(a->flags),
-                                        plain(a->table), a->stride, plain(a->found));
+                                        plain(a->table), a->stride, plain(a->found), look_again);
         __syncthreads();
     }
 }

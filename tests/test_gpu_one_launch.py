@@ -83,6 +83,8 @@ def _same(a, b):
 CASES = [(16384, 16384, [1], 64, 0, None), (20000, 20003, [0, 3, 15, 0, 16], 70, 0, None), (33001, 33001, [4] * 9, 257, 3, None),
          (40000, 40001, [2, 2, 2], 10, 2, [2, 4, 6, 8]),          # rows in front of the first sequence
          (33000, 33000, [3, 3, 3], 10, 0, [0, 5, 3, 9]),          # offsets that descend
+         (33000, 33000, [3, 3, 3], 10, 0, [0, 6, 2, 9]),          # ... so far that positions of two sequences share a target row
+         (16384, 16387, [4] * 8, 64, 0, [0, 9, 1, 10, 2, 11, 3, 12, 32]),
          (33000, 33000, [3, 3, 3], 10, 0, [0, 3, 6, 12]),         # ... that leave the call's rows
          (33000, 33000, [3, 3, 3], 10, 0, [0, -1, 2, 9])]         # ... and whose drafts lie in front of the call's
 
@@ -93,14 +95,14 @@ CASES = [(16384, 16384, [1], 64, 0, None), (20000, 20003, [0, 3, 15, 0, 16], 70,
 def test_verification(gpu, ps, dtype, V, ld, gammas, k, extra, off, q_scalar):
     print("[case]", V, gammas, k, extra, off, dtype, q_scalar, flush=True)
     c = _Case(ps, V + k, dtype, V, ld, gammas, k, extra, off)
-    full = _scratch_bytes(dtype, c.rows, c.B + 1, V) + c.rows * 16
+    full = _scratch_bytes(dtype, c.rows, c.B + 1, V) + c.rows * 24
     asked = ps.lib.picospec_one_launch_bytes(ps.CALL_VERIFY, c.code, c.N, c.B, V, 0)
     assert asked == 0 or asked == max(full, ps.scratch_bytes(ps.CALL_VERIFY, c.code, c.N, c.B, V, 0))
     garbage = torch.randint(0, 256, (max(full, _table_bytes(ps, dtype, c.rows, V)),), dtype=torch.uint8, device=c.z.device)
     ranges = [None]
-    if off is None:
-        g = (c.off[1:] - c.off[:-1])
-        top = max(max(gammas), 0)
+    if off is None or off[-1] <= c.N:
+        g = (c.off[1:] - c.off[:-1]).clamp_min(0)
+        top = int(g.max())
         ranges += [(None, None, top), ((g + 1) // 2, g, top), (torch.zeros_like(g), (g + 1) // 2, top), (g, g, top), (g + 5, g - 9, top)]
     for r in ranges:
         want, _ = c.fresh()
@@ -114,7 +116,7 @@ def test_verification(gpu, ps, dtype, V, ld, gammas, k, extra, off, q_scalar):
             c.verify(garbage, got, q_scalar, r)
             torch.cuda.synchronize()
             assert all(bool((t[:FRONT] == -7).all()) for t in c.fronts)
-            if off is not None and min(off) < 0:
+            if off is not None and min(off) < 0 and r is None:
                 assert got.n_accept[1] == 0 and got.flags[1] & 8
             a, w = [{n: t.cpu().numpy() for n, t in vars(v).items()} for v in (got, want)]
             if off is not None and off[-1] > c.N:
@@ -213,7 +215,7 @@ def test_row_statistics(gpu, ps, dtype, V, rows):
 def test_captured_calls_replay(gpu, ps):
     c = _Case(ps, 3, torch.float32, 33001, 33001, [4, 0, 7, 2], 64)
     ver, res = c.fresh()
-    ws = torch.empty(_scratch_bytes(torch.float32, c.rows, c.B + 1, 33001) + c.rows * 16 + 65536, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(_scratch_bytes(torch.float32, c.rows, c.B + 1, 33001) + c.rows * 24 + 65536, dtype=torch.uint8, device="cuda")
     ws2 = torch.empty(_scratch_bytes(torch.float32, c.B, c.B, 33001) + 65536, dtype=torch.uint8, device="cuda")
     def both(v, r):
         c.verify(ws, v, False)
