@@ -123,6 +123,8 @@ def alloc_workspace(dtype: torch.dtype, rows: int, V: int, device, which: int = 
     it allocates it)."""
     code = F32 if dtype == torch.float32 else BF16
     n = int(lib.picospec_workspace_bytes(which, code, rows, V, 0))
+    if which == CALL_VERIFY:                     # (with what lets a verification of few rows go out in one launch, however many sequences)
+        n = max(n, int(lib.picospec_one_launch_bytes(which, code, 0, rows, V, 0)))
     if k and n_draft:
         n = max(n, int(lib.picospec_scratch_bytes(which, code, n_draft, rows - n_draft, V, k)))
     return torch.empty(max(n, 16), dtype=torch.uint8, device=device)

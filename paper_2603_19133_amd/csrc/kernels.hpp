@@ -254,8 +254,7 @@ inline size_t round_seg_table_bytes(int dtype, int64_t rows, int V) {
     return small > seg_table_bytes(dtype, rows, V) ? small : seg_table_bytes(dtype, rows, V);
 }
 
-// Scratch of the calls whose last workgroups go on (arrive_last): a table in the split layout and behind it, on a 16-byte boundary, the
-// groups' words, kArrivalStride bytes apart, one per row (row_stats), per sequence and one more (verify), per sequence (the draw without a table).
+// Scratch of the calls whose last workgroups go on (arrive_last): a table in the split layout and behind it (split_table_end) the groups' words, kArrivalStride bytes apart, one per row (row_stats), per sequence and one more (verify), per sequence (the draw without a table).
 // Workgroups per row, of `waves` waves, of these launches: no more of them in all than are on the chip at once, two of eight waves per CU (a
 // workgroup that waits for its arrival, 0.7 us, holds its place: with a workgroup for every eight segments a verification of 144 rows of 151,936
 // fp32 took 28.3 us, with these 19.5).
@@ -280,7 +279,12 @@ inline bool verify_one_launch(bool ranged, int dtype, int64_t rows, int V) { ret
 inline bool residual_one_launch(int dtype, int64_t B, int V, int k) {
     return B * split_stats_shape(dtype, V).stride <= kOneLaunchDraw || (k > 512 && B >= 512);
 }
-inline size_t split_table_end(int dtype, int64_t rows, int V) { return (sizeof(SegHeader) + (size_t)rows * (size_t)split_stats_shape(dtype, V).stride * 8 + 15) / 16 * 16; }
+// (behind the larger of the two layouts' tables: a buffer of picospec_scratch_bytes or picospec_workspace_bytes, which holds either, never reaches the words,
+// so that its owner gets two launches, and one of picospec_one_launch_bytes one)
+inline size_t split_table_end(int dtype, int64_t rows, int V) {
+    const size_t split = sizeof(SegHeader) + (size_t)rows * (size_t)split_stats_shape(dtype, V).stride * 8, table = seg_table_bytes(dtype, rows, V);
+    return ((split > table ? split : table) + 15) / 16 * 16;
+}
 inline size_t row_stats_words_at(int dtype, int64_t rows, int V) { return split_table_end(dtype, rows, V); }
 inline size_t row_stats_scratch_bytes(int dtype, int64_t rows, int V) { return row_stats_words_at(dtype, rows, V) + (size_t)rows * kArrivalStride; }
 inline size_t verify_words_at(int dtype, int64_t rows, int V) { return split_table_end(dtype, rows, V); }

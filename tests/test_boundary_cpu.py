@@ -357,3 +357,26 @@ def test_check_device_rejects_misuse(B):
 def test_probe_clock_rejects_misuse(B):
     assert B.lib.picospec_probe_clock(None, None) == B.EINVAL
     assert B.lib.picospec_probe_clock(FAKE + 4, None) == B.EINVAL
+
+
+def test_the_size_of_a_buffer_chooses_one_launch_or_two(B):
+    """picospec_scratch_bytes and picospec_workspace_bytes never hold what one launch needs, wherever it is a choice."""
+    one = B.lib.picospec_one_launch_bytes
+    choices = 0
+    for which in (B.CALL_COMPRESS, B.CALL_COMPRESS_REJECTED, B.CALL_VERIFY, B.CALL_ROW_STATS, B.CALL_SAMPLE_RESIDUAL):
+        for dt in (B.F32, B.BF16):
+            for V in (16384, 20003, 33001, 64000, 128256, 151936, 524288, 1 << 20):
+                for n, b in ((1, 0), (0, 1), (3, 1), (8, 24), (48, 12), (96, 32), (100, 0), (0, 512), (160, 0), (1000, 600)):
+                    for k in (10, 256, 700):
+                        scratch = B.scratch_bytes(which, dt, n, b, V, k)
+                        bytes = one(which, dt, n, b, V, k)
+                        assert bytes == 0 if scratch == 0 else bytes >= scratch
+                        segments = -(-(V * (4 if dt == B.F32 else 2) + 16) // 4096) * (b if which == B.CALL_SAMPLE_RESIDUAL else n + b)
+                        table = which in (B.CALL_VERIFY, B.CALL_SAMPLE_RESIDUAL) and segments < 1500 or which == B.CALL_ROW_STATS
+                        if scratch == 0 or (bytes == scratch and not table):
+                            continue
+                        choices += 1
+                        rows = {B.CALL_COMPRESS: n, B.CALL_COMPRESS_REJECTED: b, B.CALL_SAMPLE_RESIDUAL: b}.get(which, n + b)
+                        call = B.CALL_VERIFY if which == B.CALL_ROW_STATS else which
+                        assert bytes > max(scratch, B.workspace_bytes(call, dt, rows, V, k)), (which, dt, n, b, V, k)
+    assert choices > 100

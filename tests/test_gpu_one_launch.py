@@ -1,6 +1,6 @@
 """Calls whose last workgroup goes on (verification, the draw without a table, row statistics in one launch) against the same calls in two, which
-a workspace that holds the table alone still takes: the same bits.  Scratch that holds anything, offsets of every kind, repeated use and
-captured launches.  (The verification is compared with one workgroup per row.)"""
+a workspace that holds the table alone takes: the same bits.  Scratch that holds anything, offsets of every kind, repeated use and
+captured launches.  (The verification is compared with one workgroup per row as well, the statistics with 64 bits.)"""
 import numpy as np
 import pytest
 import torch
@@ -23,12 +23,12 @@ def _segments(dtype, V):
 
 
 def _table_bytes(ps, dtype, rows, V):
-    """What picospec_workspace_bytes asks for, without a byte to spare for more than the table."""
+    """What picospec_workspace_bytes asks for: two launches (test_boundary_cpu.py holds that it is less than one launch needs)."""
     return ps.workspace_bytes(ps.CALL_VERIFY, ps.BF16 if dtype == torch.bfloat16 else ps.F32, rows, V, 0)
 
 
-def _scratch_bytes(dtype, rows, groups, V):
-    return (16 + rows * 8 * _segments(dtype, V) + 15) // 16 * 16 + groups * WORD
+def _scratch_bytes(ps, dtype, rows, groups, V):
+    return (max(16 + rows * 8 * _segments(dtype, V), _table_bytes(ps, dtype, rows, V)) + 15) // 16 * 16 + groups * WORD
 
 
 class _Case:
@@ -95,10 +95,12 @@ CASES = [(16384, 16384, [1], 64, 0, None), (20000, 20003, [0, 3, 15, 0, 16], 70,
 def test_verification(gpu, ps, dtype, V, ld, gammas, k, extra, off, q_scalar):
     print("[case]", V, gammas, k, extra, off, dtype, q_scalar, flush=True)
     c = _Case(ps, V + k, dtype, V, ld, gammas, k, extra, off)
-    full = _scratch_bytes(dtype, c.rows, c.B + 1, V) + c.rows * 24
+    full = _scratch_bytes(ps, dtype, c.rows, c.B + 1, V) + c.rows * 24
     asked = ps.lib.picospec_one_launch_bytes(ps.CALL_VERIFY, c.code, c.N, c.B, V, 0)
-    assert asked == 0 or asked == max(full, ps.scratch_bytes(ps.CALL_VERIFY, c.code, c.N, c.B, V, 0))
-    garbage = torch.randint(0, 256, (max(full, _table_bytes(ps, dtype, c.rows, V)),), dtype=torch.uint8, device=c.z.device)
+    assert asked in (0, full)
+    assert _table_bytes(ps, dtype, c.rows, V) < full
+    garbage = torch.randint(0, 256, (full,), dtype=torch.uint8, device=c.z.device)
+    table = garbage.clone()[:_table_bytes(ps, dtype, c.rows, V)]
     ranges = [None]
     if off is None or off[-1] <= c.N:
         g = (c.off[1:] - c.off[:-1]).clamp_min(0)
@@ -106,14 +108,14 @@ def test_verification(gpu, ps, dtype, V, ld, gammas, k, extra, off, q_scalar):
         ranges += [(None, None, top), ((g + 1) // 2, g, top), (torch.zeros_like(g), (g + 1) // 2, top), (g, g, top), (g + 5, g - 9, top)]
     for r in ranges:
         want, _ = c.fresh()
-        with pytest.MonkeyPatch.context() as m:                   # two launches: statistics and acceptance from a table of their own
-            c.verify(None, want, q_scalar, r)
-            assert all(bool((t[:FRONT] == -7).all()) for t in c.fronts)
-        for fill in ("random", "ones", "again"):
+        c.verify(None, want, q_scalar, r)
+        assert all(bool((t[:FRONT] == -7).all()) for t in c.fronts)
+        two = None
+        for fill in ("two launches", "random", "ones", "again"):
             if fill == "ones":
                 garbage.fill_(255)
             got, _ = c.fresh()
-            c.verify(garbage, got, q_scalar, r)
+            c.verify(table if fill == "two launches" else garbage, got, q_scalar, r)
             torch.cuda.synchronize()
             assert all(bool((t[:FRONT] == -7).all()) for t in c.fronts)
             if off is not None and min(off) < 0 and r is None:
@@ -124,11 +126,15 @@ def test_verification(gpu, ps, dtype, V, ld, gammas, k, extra, off, q_scalar):
                 assert (a["p_tok"][c.N:] == -7).all() and (a["tgt_sum"][c.rows:] == -7).all()
                 assert a["flags"][-1] & 8 and a["n_accept"][-1] <= 3
                 continue
+            two = two or a
             np.testing.assert_array_equal(a["n_accept"], w["n_accept"])
             np.testing.assert_array_equal(a["flags"], w["flags"])
             shared = off is not None and (np.diff(off) < 0).any()     # (positions of two sequences: whose p comes last is anyone's)
             if not shared:
                 np.testing.assert_array_equal(a["q_tok"], w["q_tok"])
+                np.testing.assert_array_equal(a["p_tok"], two["p_tok"])
+            for name in ("tgt_max", "tgt_sum", "tgt_lse"):
+                np.testing.assert_array_equal(a[name], two[name], err_msg=name)
             for name in ("tgt_max", "tgt_sum", "tgt_lse") + (() if shared else ("p_tok",)):
                 # (two fp32 sums of up to 40,000 terms, by 1024 threads and by segments: a few 2^-24 each)
                 np.testing.assert_allclose(a[name], w[name], rtol=2e-6, err_msg=name)
@@ -148,7 +154,7 @@ def test_draw(gpu, ps, dtype, V, B, k):
         ps._check(ps._nat.sample_residual_ws(c.z, c.code, c.z.stride(0), V, 0.9, B, c.N, c.off, n, mx, sm, c.q.idx, c.q.prob, c.q.count, c.q.mass, k, 1, c.uni,
                                              res.out_tok, res.resid_mass, res.flags, ws, ps._stream()))
         return res
-    room = torch.randint(0, 256, (max(_scratch_bytes(dtype, B, B, V), _table_bytes(ps, dtype, B, V)),), dtype=torch.uint8, device=c.z.device)
+    room = torch.randint(0, 256, (_scratch_bytes(ps, dtype, B, B, V),), dtype=torch.uint8, device=c.z.device)
     table = room.clone()[:_table_bytes(ps, dtype, B, V)]
     want = draw(table)
     for _ in range(3):
@@ -178,7 +184,7 @@ def test_a_draw_that_leaves_the_call(gpu, ps, dtype, off, n, outside):
         ps._check(call(z, c.code, z.stride(0), V, 0.9, c.B, c.N, seq, na, mx, sm, idx, prob, count, mass, k, 1, uni,
                        res.out_tok, res.resid_mass, res.flags, ws, ps._stream()))
         return [t.cpu().numpy() for t in vars(res).values()]
-    room = torch.randint(0, 256, (max(_scratch_bytes(dtype, c.B, c.B, V), _table_bytes(ps, dtype, c.B, V)) + 65536,), dtype=torch.uint8, device=z.device)
+    room = torch.randint(0, 256, (_scratch_bytes(ps, dtype, c.B, c.B, V),), dtype=torch.uint8, device=z.device)
     one, two = draw(room, ps._nat.sample_residual_ws), draw(room[:_table_bytes(ps, dtype, c.B, V)], ps._nat.sample_residual_ws)
     ws = ps.alloc_workspace(dtype, c.rows, V, z.device)
     ver, _ = c.fresh()
@@ -194,19 +200,29 @@ def test_a_draw_that_leaves_the_call(gpu, ps, dtype, off, n, outside):
         np.testing.assert_allclose(resid, one[1], rtol=1e-6)
 
 
-@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("V,rows", [(62500, 1), (125003, 3), (64000, 128), (128256, 160), (1048576, 2)])
+@pytest.mark.parametrize("dtype,V,rows", [(torch.float32, 62500, 1), (torch.float32, 125003, 100), (torch.float32, 64000, 64), (torch.float32, 128256, 128),
+                                          (torch.float32, 1048576, 2), (torch.bfloat16, 125001, 1), (torch.bfloat16, 128256, 160), (torch.bfloat16, 151937, 37),
+                                          (torch.bfloat16, 1048576, 2)])
 def test_row_statistics(gpu, ps, dtype, V, rows):
     print("[case]", V, rows, dtype, flush=True)
     z = (torch.randn((rows, V + 1), device="cuda") * 3).to(dtype)[:, :V]
-    z[0, 7], z[rows - 1, V // 2:] = float("inf") if rows > 1 else 0.0, float("-inf")
-    code = ps._dtype_code(z)
+    code, T = ps._dtype_code(z), 0.9
+    one, two = ps.lib.picospec_one_launch_bytes(ps.CALL_ROW_STATS, code, rows, 0, V, 0), _table_bytes(ps, dtype, rows, V)
+    assert one == _scratch_bytes(ps, dtype, rows, rows, V) > two > 0            # (spread, in one launch and in two)
+    z[rows - 1, V // 2:] = float("-inf")
     def stats(ws):
         out = [torch.full((rows,), -7.0, device="cuda") for _ in range(3)]
-        ps._check(ps._nat.row_stats(z, code, z.stride(0), rows, V, 0.9, *out, ws, ps._stream()))
+        ps._check(ps._nat.row_stats(z, code, z.stride(0), rows, V, T, *out, ws, ps._stream()))
         return [o.cpu().numpy() for o in out]
-    room = torch.randint(0, 256, (max(_scratch_bytes(dtype, rows, rows, V), _table_bytes(ps, dtype, rows, V)),), dtype=torch.uint8, device="cuda")
-    want = stats(room.clone()[:_table_bytes(ps, dtype, rows, V)])
+    room = torch.randint(0, 256, (one,), dtype=torch.uint8, device="cuda")
+    x = z.double() / T
+    top, lse = x.max(1).values, torch.logsumexp(x, 1)
+    # each term 2^e, e of up to 2^6 rounded to fp32, so 2^-18 ln 2 at most and 2^-22 for the terms that matter (e > -2^2); the log-sum-exp is rounded once
+    exact = [z.float().max(1).values, torch.exp(lse - top), lse]
+    for name, got, want, tol in zip("max sum lse".split(), stats(room), exact, (0.0, 2e-6, 3e-7)):
+        np.testing.assert_allclose(got, want.double().cpu().numpy(), rtol=tol, err_msg=name)
+    z[0, 7] = float("inf")
+    want = stats(room.clone()[:two])
     for _ in range(3):
         for got, w in zip(stats(room), want):
             np.testing.assert_array_equal(got, w)
@@ -215,8 +231,8 @@ def test_row_statistics(gpu, ps, dtype, V, rows):
 def test_captured_calls_replay(gpu, ps):
     c = _Case(ps, 3, torch.float32, 33001, 33001, [4, 0, 7, 2], 64)
     ver, res = c.fresh()
-    ws = torch.empty(_scratch_bytes(torch.float32, c.rows, c.B + 1, 33001) + c.rows * 24 + 65536, dtype=torch.uint8, device="cuda")
-    ws2 = torch.empty(_scratch_bytes(torch.float32, c.B, c.B, 33001) + 65536, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(_scratch_bytes(ps, torch.float32, c.rows, c.B + 1, 33001) + c.rows * 24 + 65536, dtype=torch.uint8, device="cuda")
+    ws2 = torch.empty(_scratch_bytes(ps, torch.float32, c.B, c.B, 33001) + 65536, dtype=torch.uint8, device="cuda")
     def both(v, r):
         c.verify(ws, v, False)
         ps._check(ps._nat.sample_residual_ws(c.z, c.code, c.z.stride(0), c.V, 0.9, c.B, c.N, c.off, v.n_accept, v.tgt_max, v.tgt_sum, c.q.idx, c.q.prob, c.q.count,
