@@ -87,6 +87,15 @@ int64_t max_load_end(int which, int V, int o)
                     for (int j = 0; j < kSplitStatsNV; ++j)
                         for (int lane = 0; lane < 64; ++lane)
                             end = std::max(end, buffer_lane_read_end(size, (int64_t)stats_group_first(stats_segment(part, w, i), j) * 16, (int64_t)lane * 16));
+        const int segments = stats_segments(nq);                                 // ... by the workgroups of a row, as few or many as the call has, that share them
+        for (int waves : {4, 8})
+            for (int shared : {1, 2, (stats_segments(row_vecs_max(BF16, V)) + waves - 1) / waves})
+                for (int part = 0; part < shared; ++part)
+                    for (int w = 0; w < waves; ++w)
+                        for (int trip = 0; trip == 0 || shared_segment(part, w, trip - 1, shared, waves) < segments; ++trip)
+                            for (int j = 0; j < kSplitStatsNV; ++j)
+                                for (int lane = 0; lane < 64; ++lane)
+                                    end = std::max(end, buffer_lane_read_end(size, (int64_t)stats_group_first(shared_segment(part, w, trip, shared, waves), j) * 16, (int64_t)lane * 16));
     }
     return end;
 }

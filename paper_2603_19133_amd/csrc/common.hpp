@@ -682,12 +682,11 @@ __device__ __forceinline__ void row_stats_shared(
     const RowSegments<BF16> segs(logits, ld, row, V);
     const float c = 1.4426950408889634f * inv_T;
     float2* const seg_row = seg + table_row * (int64_t)seg_stride;
-    int s = part * WAVES + wave;
     uint4 cur[kSplitStatsNV], next[kSplitStatsNV];
-    segs.load(s, cur);
+    segs.load(shared_segment(part, wave, 0, parts, WAVES), cur);
     meanwhile();
-    for (; s < segs.n_seg; s += parts * WAVES) {
-        segs.load(s + parts * WAVES, next);
+    for (int trip = 0, s; (s = shared_segment(part, wave, trip, parts, WAVES)) < segs.n_seg; ++trip) {
+        segs.load(shared_segment(part, wave, trip + 1, parts, WAVES), next);
         const float2 e = segment_entry<BF16>(segs.rv, segs.n_seg, s, cur, c);
         if (lane == 0) put_shared(&seg_row[s], e);
 #pragma unroll

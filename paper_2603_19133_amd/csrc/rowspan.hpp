@@ -68,6 +68,9 @@ __host__ __device__ inline int split_parts(bool bf16, int nq) {
 constexpr int kSplitStatsNV = 4, kSplitStatsSpw = 2;
 // segment i of wave `wave` of workgroup `part`
 __host__ __device__ inline int stats_segment(int part, int wave, int i) { return (part * 4 + wave) * kSplitStatsSpw + i; }
+// ... where a row's `parts` workgroups of `waves` waves take a segment per trip each (row_stats_shared); every trip's loads are asked for in the one before
+// it, so trips go one further than the row
+__host__ __device__ inline int shared_segment(int part, int wave, int trip, int parts, int waves) { return (trip * parts + part) * waves + wave; }
 // first vector of group j of a segment
 __host__ __device__ inline int stats_group_first(int seg, int j) { return (seg * kSplitStatsNV + j) * 64; }
 // segments of a row of `nq` vectors, and the workgroups that take them

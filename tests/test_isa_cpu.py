@@ -140,3 +140,8 @@ def test_every_range_checked_load_takes_its_place_from_the_shared_rule():
             else:
                 assert any(f in where for f in shared), (name, where)
     assert loads >= 5
+    # ... and a row's segments are chosen by functions of it as well
+    text = open(os.path.join(bld.CSRC, "common.hpp")).read()
+    chosen = re.findall(r"segs\.load\(([^;]*);", text)
+    assert len(chosen) >= 3 and all("stats_segment(" in c or "shared_segment(" in c for c in chosen), chosen
+    assert "shared_segment(" in open(os.path.join(bld.CSRC, "api.hip")).read()
