@@ -458,9 +458,9 @@ size_t picospec_scratch_bytes(int which_call, int dtype, int32_t n_draft, int32_
 
 /* The same, and behind it what lets the call go out in one launch where that is the faster way (few rows; compress, compress_rejected, verify,
  * verify_range, row_stats and the draw that makes its own table).  Larger than picospec_scratch_bytes() and, for these calls, than
- * picospec_workspace_bytes() wherever there is a choice: a call that is given either of those alone takes two launches.  In one, a call costs the host a launch
- * less (2.5 to 3.5 us); on the device alone it takes between 0.8 us less and 0.6 us more (a replayed graph, a queue that is ahead), so a caller
- * whose host is not the one that waits may give the smaller buffer.  Calls that overlap in time must not share scratch. */
+ * picospec_workspace_bytes() wherever there is a choice: a call that is given either of those alone takes two launches.  One launch spares the host 2.5 to 3.5 us.
+ * On the device alone it is the slower form for some sizes: a call that is being captured, whose replays no host bounds, takes two there all the
+ * same, and a caller whose queue is always ahead may give the smaller buffer.  Calls that overlap in time must not share scratch. */
 size_t picospec_one_launch_bytes(int which_call, int dtype, int32_t n_draft, int32_t B, int32_t V, int32_t k);
 
 /* host: largest supported k (PICOSPEC_LIMIT_MAX_K) or V (PICOSPEC_LIMIT_MAX_V); -1 for an unknown id. */

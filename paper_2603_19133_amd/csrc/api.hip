@@ -402,7 +402,9 @@ int verify_impl(const void* tgt_logits, int dtype, int64_t ld, int32_t V, float 
     if (int rc = check_workspace(PICOSPEC_CALL_VERIFY, dtype, rows, V, k, workspace, workspace_bytes)) return rc;
     hipStream_t s = (hipStream_t)stream;
     const bool split = workspace && B > 0 && split_stats_serves(rows, V);
-    if (split && verify_one_launch(ranged, dtype, rows, V) && workspace_bytes >= verify_scratch_bytes(dtype, rows, B, V))      // (one that holds the table alone: two launches)
+    // (a workspace that holds the table alone: two launches; so does a captured call that replays faster so)
+    if (split && verify_one_launch(ranged, dtype, rows, V) && workspace_bytes >= verify_scratch_bytes(dtype, rows, B, V) &&
+        !(ranged && rows * split_stats_shape(dtype, V).stride > kOneLaunchRangeReplayed && is_captured(s)))
         return hip_status(launch_verify_spread(tgt_logits, dtype, ld, V, temperature, B, rows, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k,
                                                renorm, q_scalar, uniforms, tgt_max, tgt_sum, tgt_lse, n_accept, p_tok, q_tok, flags,
                                                ranged, ranged ? pos_begin : nullptr, ranged ? pos_end : nullptr, gamma_max, workspace, s));

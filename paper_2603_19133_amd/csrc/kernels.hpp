@@ -84,10 +84,13 @@ inline size_t split_scratch_bytes(int dtype, int64_t rows, int V, int k) {
 }
 
 // ... in one launch, whose last workgroup of a row finishes it (split_compress_kernel; behind the lists, on a 16-byte boundary, a word per row).  It
-// spares the host a launch, 2.5 to 3 us of the 12.6 in which it issues a row's record and draw; on the device it is 0.5 us slower for one row (of 11.0),
-// even from four rows on and up to 0.5 us faster around 64 workgroups; beyond 128 it loses (bf16, 32 rows of 128,256, k = 256, 512 workgroups: 14.7
-// against 13.5; 16 of 151,936, k = 1024, 304: 17.7 against 15.4): its workgroups have the finish's LDS, two to a CU.
-constexpr int kOneLaunchSplit = 128;
+// spares the host a launch, 2.5 to 3 us of the 12.6 in which it issues a row's record and draw.  us a call in a replayed graph and called in a row, two
+// launches / one: one row of 32,000 fp32, k = 64: 9.0 / 9.3, 8.9 / 9.0 (record and draw, which the host bounds: 13.9 / 11.2); one of 128,256 bf16, k = 10: 9.0 /
+// 9.2, 8.9 / 8.9; 2 of 151,936 fp32, k = 64: 9.7 / 9.9, 9.6 / 9.6; 4 of 128,256 bf16, k = 64: 9.6 / 9.6, 9.5 / 9.3; 8, k = 256: 10.5 / 10.2, 10.9 / 9.9; 24 of
+// 33,001 fp32, k = 70: 9.6 / 9.6, 10.2 / 9.2.  So captured calls of fewer than kOneLaunchSplitReplayed rows, whose replays no host bounds, take two; all
+// calls beyond 128 workgroups do (bf16, 32 rows of 128,256, k = 256, 512 workgroups: 14.7 against 13.5; 16 of 151,936, k = 1024, 304: 17.7
+// against 15.4): those of the one launch have the finish's LDS, two to a CU.
+constexpr int kOneLaunchSplit = 128, kOneLaunchSplitReplayed = 4;
 inline bool split_one_launch(int dtype, int64_t rows, int V, int k) { return rows * split_plan(dtype, rows, V, k).parts <= kOneLaunchSplit; }
 inline size_t split_words_at(int dtype, int64_t rows, int V, int k) { return (split_scratch_bytes(dtype, rows, V, k) + 15) / 16 * 16; }
 inline size_t split_one_launch_bytes(int dtype, int64_t rows, int V, int k) { return split_words_at(dtype, rows, V, k) + (size_t)rows * kArrivalStride; }
@@ -264,18 +267,27 @@ inline int spread_parts(int segments, int waves, int64_t rows) {
     return (int)(fit < 1 ? 1 : fit < most ? fit : most);
 }
 // Where they serve, by the segments (4 KB) of the rows in all.  With few, two launches are a boundary of 1.5 us on the device and 2.5 to 3.5 us on the
-// host; with more, the rows stream faster from many small workgroups that wait for nothing.  us a call, two launches / one, on the device
-// alone and called in a row:
-//   * verification of a range of positions, up to 5500: fp32: 24 rows of 24,576: 6.6 / 6.1, 9.8 / 6.4; 48 of 64,000 (3024): 7.6 / 7.5, 10.1 / 7.5; 144 of 33,001
-//     (4752): 8.5 / 9.1, 10.1 / 8.8; 96 of 64,000 (6048): 8.4 / 9.5, 10.1 / 9.2; 144 of 151,936: 13.8 / 17.8, 14.1 / 17.8; bf16: 48 of 128,256 (3024): 8.2 /
-//     7.5, 10.2 / 7.6; 144 of 64,000 (4608): 9.4 / 9.6, 10.5 / 9.0;
-//   * of all positions, whose workgroups look their sequences up and all have rows to sum, up to 2000: fp32: 24 of 64,000 (1512): 6.8 / 7.2, 9.9 / 7.2; 48 of
-//     33,001: 7.3 / 7.3, 10.0 / 7.3; 24 of 128,256 (3024): 8.0 / 9.7, 9.9 / 9.4; bf16: 96 of 33,001 (1632): 8.2 / 8.6, 9.9 / 8.3; 48 of 128,256 (3024): 8.3 / 8.6;
-//   * the draw, up to 2500: fp32: 24 sequences of 33,001, k = 64: 8.3 / 7.5, 8.5 / 7.5; 64, k = 256 (2112): 9.7 / 9.0; 64 of 64,000 (4032): 10.1 / 10.8; bf16: 64 of 64,000
-//     (2048): 9.9 / 9.1; 64 of 151,936 (4800): 11.8 / 13.6.  And from 512 sequences on for records of 513 entries or more, whose workgroups sum a row alone:
-//     512 of 33,001, k = 700: 24.1 / 20.8, bf16 18.9 / 16.3, of 151,936 60.8 / 60.3, 39.2 / 34.3; shorter records (k = 64: 18.0 / 20.1) do not gain.
-constexpr int kOneLaunchRange = 5500, kOneLaunchVerify = 2000, kOneLaunchDraw = 2500;
+// host; with more, the rows stream faster from many small workgroups that wait for nothing.  us a call, two launches / one, in a replayed graph
+// and called in a row:
+//   * verification of a range of positions, up to 5500: fp32: 24 rows of 24,576: 8.0 / 7.2, 8.2 / 7.2; 48 of 64,000 (3024): 9.0 / 8.3, 9.3 / 8.1; 76 of 64,000 (4788): 10.2 /
+//     10.1, 11.1 / 9.6; 144 of 33,001 (4752): 10.1 / 10.6, 10.3 / 9.8; 32 of 151,936 (4768): 10.2 / 11.8, 11.3 / 11.2; 108 of 50,000 (5292): 10.4 / 11.4, 11.2 / 10.8;
+//     bf16: 48 of 128,256 (3024): 9.4 / 8.3, 9.6 / 8.0; 144 of 64,000 (4608): 10.9 / 10.8, 10.9 / 10.1; 64 of 151,936 (4800): 10.1 / 12.7, 11.3 / 11.9.  That is, of 74 points from 2300 to
+//     5500 one launch is the faster in 72 called in a row (1 to 29 %), and in a replayed graph, where no host waits, in 25 of 26 up to 3300 and in 16 of 48
+//     beyond (9 % faster to 20 % slower): captured calls take two there;
+//   * of all positions, whose workgroups look their sequences up and all have rows to sum, up to 2000: fp32: 24 of 64,000 (1512): 7.8 / 7.5, 8.0 / 7.4; 48 of
+//     33,001: 8.1 / 7.5, 8.3 / 7.4; bf16: 24 of 128,256: 8.1 / 7.5, 8.3 / 7.5; 96 of 33,001 (1632): 9.1 / 8.2, 9.3 / 8.0;
+//   * the draw, up to 2500: fp32: 24 sequences of 33,001, k = 70: 9.0 / 8.0, 9.8 / 7.8; 64, k = 256 (2112): 9.9 / 9.1, 10.6 / 8.9; bf16: 64 of 64,000 (2048): 9.8 / 9.4, 11.0 / 9.0; beyond
+//     (on the device alone) fp32 64 of 64,000 (4032): 10.1 / 10.8, bf16 64 of 151,936 (4800): 11.8 / 13.6.  And from 512 sequences on for records of 513 entries or more, whose
+//     workgroups sum a row alone: 512 of 33,001, k = 700: 23.6 / 19.9, bf16 18.7 / 16.5, of 151,936 bf16 38.5 / 34.6; shorter records (k = 64: 18.0 / 20.1) do not gain.
+constexpr int kOneLaunchRange = 5500, kOneLaunchRangeReplayed = 3300, kOneLaunchVerify = 2000, kOneLaunchDraw = 2500;
 inline bool verify_one_launch(bool ranged, int dtype, int64_t rows, int V) { return rows * split_stats_shape(dtype, V).stride <= (ranged ? kOneLaunchRange : kOneLaunchVerify); }
+// (asked only where it makes a difference: `stream` is being captured.  A stream that cannot be asked is not.)
+inline bool is_captured(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status == hipStreamCaptureStatusActive;
+    (void)hipGetLastError();
+    return false;
+}
 inline bool residual_one_launch(int dtype, int64_t B, int V, int k) {
     return B * split_stats_shape(dtype, V).stride <= kOneLaunchDraw || (k > 512 && B >= 512);
 }

@@ -672,7 +672,7 @@ hipError_t launch_split_compress(const void* logits, int dtype, int64_t ld, int 
     uint2* const lists = (uint2*)(heads + (size_t)n_rows * p.parts);
     const int narrow = p.rank <= kSplitNarrowRank;
     const dim3 grid(p.parts, n_rows);
-    if (split_one_launch(dtype, n_rows, V, k) && scratch_bytes >= split_one_launch_bytes(dtype, n_rows, V, k)) {
+    if (split_one_launch(dtype, n_rows, V, k) && scratch_bytes >= split_one_launch_bytes(dtype, n_rows, V, k) && !(n_rows < kOneLaunchSplitReplayed && is_captured(stream))) {
         static DeviceFlags limit_raised[2] = {};
         const int bf = dtype == 1;
         const size_t smem = sizeof(CompressShared<kCapBig>);

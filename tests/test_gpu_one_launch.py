@@ -1,6 +1,8 @@
 """Calls whose last workgroup goes on (verification, the draw without a table, row statistics in one launch) against the same calls in two, which
 a workspace that holds the table alone takes: the same bits.  Scratch that holds anything, offsets of every kind, repeated use and
 captured launches.  (The verification is compared with one workgroup per row as well, the statistics with 64 bits.)"""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -254,3 +256,34 @@ def test_captured_calls_replay(gpu, ps):
         torch.cuda.synchronize()
         _same(ver, want_v)
         _same(res, want_r)
+
+
+def _kernels(graph):
+    """Kernels of a captured graph (its only nodes)."""
+    n = ctypes.c_size_t(0)
+    assert ctypes.CDLL("libamdhip64.so").hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,V,launches", [(24, 33001, 1), (112, 64000, 2)])     # (up to 3300 segments of a range's rows, and beyond)
+def test_a_captured_range_takes_the_launches_that_replay_faster(gpu, ps, dtype, rows, V, launches):
+    V *= 1 if dtype == torch.float32 else 2
+    c = _Case(ps, 4, dtype, V, V, [3] * (rows // 8), 64, extra=rows // 2)
+    assert ps.lib.picospec_one_launch_bytes(ps.CALL_VERIFY, c.code, c.N, c.B, V, 0) > ps.scratch_bytes(ps.CALL_VERIFY, c.code, c.N, c.B, V, 0) or launches == 2
+    ws = torch.empty(_scratch_bytes(ps, dtype, c.rows, c.B + 1, V) + c.rows * 24, dtype=torch.uint8, device="cuda")
+    r = (None, None, 3)
+    want, _ = c.fresh()
+    c.verify(ws, want, False, r)
+    ver, _ = c.fresh()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        c.verify(ws, ver, False, r)
+    assert _kernels(graph) == launches
+    graph.instantiate()
+    for _ in range(3):
+        ws.random_(0, 256)
+        graph.replay()
+        torch.cuda.synchronize()
+        _same(ver, want)

@@ -98,3 +98,25 @@ def test_captured_calls_replay(gpu, ps):
         graph.replay()
         torch.cuda.synchronize()
         _same(out, want)
+
+
+@pytest.mark.parametrize("rows,launches", [(1, 2), (3, 2), (4, 1)])
+def test_captured_calls_of_very_few_rows_take_two_launches(gpu, ps, rows, launches):
+    import ctypes
+    V, k = 33001, 64
+    z = torch.randn((rows, V), device="cuda")
+    out, want = ps.alloc_compressed(rows, k, z.device), ps.alloc_compressed(rows, k, z.device)
+    ws = torch.empty(ps.lib.picospec_one_launch_bytes(ps.CALL_COMPRESS, ps.F32, rows, 0, V, k), dtype=torch.uint8, device="cuda")
+    _compress(ps, z, V, k, 0.0, ws, want)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        ps._check(ps._nat.compress(z, ps.F32, V, rows, V, 0.9, k, 0.0, out.idx, out.prob, out.count, out.mass, out.lse, ws, ps._stream()))
+    n = ctypes.c_size_t(0)
+    assert ctypes.CDLL("libamdhip64.so").hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0 and n.value == launches
+    graph.instantiate()
+    for _ in range(3):
+        ws.random_(0, 256)
+        graph.replay()
+        torch.cuda.synchronize()
+        _same(out, want)
