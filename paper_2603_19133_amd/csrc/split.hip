@@ -155,7 +155,9 @@ __device__ __forceinline__ void split_select(
     int at = 0, held = 0;
     // First (lanes > 0) by the lanes' largest values alone, one bin and atomic per lane instead of 32: with n of 256 lanes at or above it, a
     // threshold has some -256 ln(1 - n / 256) elements above it, as the host chose n (split_plan); a list that comes out too long for
-    // its slots, a crowded pivot bin or too few lanes with a value (masks, values that trend within a lane) fall to the elements.
+    // its slots or too few lanes with a value (masks, values that trend within a lane) fall to the elements.  (A crowded pivot bin alone does not: where
+    // values tie its elements are one value, which no finer bins divide.  24 fp32 rows of 33,001 on quarters, k = 70, 11.0 -> 9.9 us in two
+    // launches, in one, whose 512 lanes meet more ties, 14.4 -> 9.9; 8 bf16 of 128,256, k = 256: 16.2 -> 10.3.)
     // 64 fp32 rows of 151,936, k = 1024: 12.2 -> 10.5 us, 32 bf16 of 128,256, k = 256: 7.5 -> 6.7, one, k = 10: 5.1 -> 4.8.
     // A share with no two values to tell apart (narrow: whose lanes have none) lists everything above -inf, as a share with fewer entries
     // than the rank does: a vocabulary mask may leave it one.  If that is too much, what lies below the one value goes.  (40 rows of 128,256
@@ -196,7 +198,7 @@ __device__ __forceinline__ void split_select(
             } else if (by_lanes) {
                 tau = float_below(hi - ((float)(bin + 1) + 0.02f) * width);
                 open = false;
-                again = cnt > crowd;
+                again = before + cnt > cap;      // (a lane's largest is an element: more than the list has slots for)
             } else {
                 const float edge = hi - ((float)(bin + 1) + 0.02f) * width;    // below every element of the bins up to the pivot
                 tau = float_below(edge);
@@ -363,16 +365,20 @@ __device__ __attribute__((noinline)) void split_row_again(
 // of which `valid` has the bit.  As order_top_k and emit_row, with less between: one histogram, on a linear scale of the values (bf16: with
 // the id, as its LINEAR places), whose bins hold one or two candidates of the upper end of any smooth distribution; the candidates of the
 // bins up to the one that holds the n-th are laid out bin by bin, and whoever reads position i of that ranks it in its bin and writes it:
-// positions i and their ranks are a bin apart, so the stores are as good as in order.  Few::crowded, with nothing written: a
-// bin is too crowded (values on a grid, an outlier that stretches the scale); missing: the n-th does not lie above `above`, below which candidates are missing.
+// positions i and their ranks are a bin apart, so the stores are as good as in order.  The scale goes from `low` to `high`; what lies above shares bin 0.
+// Few::crowded, with nothing written: a bin is too crowded (values on a coarse grid); missing: the n-th does not lie above `above`, below which candidates are missing.
 // `meanwhile` forms the row's sum of exponentials while the histogram's atomics are on their way.
 // Bound by the chain of barriers, six of them (ten before): the finish of one row of 32,000 fp32, k = 64: 4.5 -> 3.6 us from its first instruction, of 64 of
 // 151,936, k = 1024: 7.4 -> 5.6; a round of that row 16.4 -> 15.6, the draft of those 22.0 -> 20.0.
-constexpr int kFewBins = kBins, kFewMost = 64;          // (a bin per word of the histogram; entries of a bin that are ranked by comparing all)
+constexpr int kFewBins = kBins;                         // (a bin per word of the histogram)
+// Entries of a bin that are ranked by comparing all: as many as values on a grid put there, which order_top_k, where fp32 values tie, would sort by a network.
+// (64 rows of 151,936, k = 1024, us, in front of finish_few / up to 64 / so: fp32 on eighths 40.0 / 42.0 / 26.3, sixths 41.2 / 43.2 / 30.0, quarters 46.6 / 48.8 /
+// 43.5; bf16 on sixths 22.0 / 23.4 / 21.8, whose places the ids spread: with up to 512 24.6.)
+template <bool BF16> constexpr int kFewMost = BF16 ? 256 : 512;
 enum class Few { crowded, missing, done };
 template <bool BF16, int SLOTS, class SH, class F>
 __device__ __forceinline__ Few finish_few(
-    SH& sh, const uint2 (&e)[SLOTS], const unsigned valid, const int n, const int V, const float low, const float M, const uint32_t above,
+    SH& sh, const uint2 (&e)[SLOTS], const unsigned valid, const int n, const int V, const float low, const float high, const float M, const uint32_t above,
     const int64_t row, const int k, const bool direct, const float inv_T, int32_t* __restrict__ idx, float* __restrict__ prob,
     int32_t* __restrict__ count, float* __restrict__ mass, const F& meanwhile)
 {
@@ -381,8 +387,8 @@ __device__ __forceinline__ Few finish_few(
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     uint64_t* const buf = reinterpret_cast<uint64_t*>(sh.cand_val);
     const float id_step = __uint_as_float((unsigned)(127 - 8 - (32 - __clz(V - 1))) << 23);
-    const float scale = (float)(kFewBins - 1) * __builtin_amdgcn_rcpf((M - low) + (BF16 ? fabsf(low) * 0.0078125f : 0.f));
-    const float top = M * scale;
+    const float scale = (float)(kFewBins - 1) * __builtin_amdgcn_rcpf((high - low) + (BF16 ? fabsf(low) * 0.0078125f : 0.f));
+    const float top = high * scale;
     auto bin_of = [&](float v, unsigned id) {
         const float w = BF16 ? fmaf(-(float)id, fabsf(v) * id_step, v) : v;
         unsigned b;
@@ -391,7 +397,7 @@ __device__ __forceinline__ Few finish_few(
     };
     unsigned meta[SLOTS];                              // (bin << 16) | arrival order within the bin
     unsigned seen = 0;                                 // (an arrival of kFewMost or later leaves a bit)
-    static_assert((kFewMost & (kFewMost - 1)) == 0, "one bit and those above it");
+    static_assert((kFewMost<BF16> & (kFewMost<BF16> - 1)) == 0, "one bit and those above it");
 #pragma unroll
     for (int u = 0; u < SLOTS; ++u) {
         meta[u] = 0;
@@ -402,7 +408,7 @@ __device__ __forceinline__ Few finish_few(
         }
     }
     const double S = meanwhile();
-    if (seen & (0xFFFFu & ~(unsigned)(kFewMost - 1))) sh.maxbin = 1;
+    if (seen & (0xFFFFu & ~(unsigned)(kFewMost<BF16> - 1))) sh.maxbin = 1;
     __syncthreads();
     if (sh.maxbin) return Few::crowded;                // (uniform)
     const uint4 h4 = *reinterpret_cast<const uint4*>(&sh.hist[4 * tid]);
@@ -542,8 +548,14 @@ __device__ __forceinline__ void split_finish(
               (total >= k || T == kNegInf);      // (a threshold of -inf: every entry above -inf is listed)
     double S = 0.0;
     auto sound = [&] { return S > 0.0 && S < 1e300; };
-    const float spread = (float)(kFewBins - 1) / (M - low);
-    if (ok && n_slots <= kAhead * kT && low > kNegInf && M > low && spread < __builtin_huge_valf() && fabsf(M) * spread < 1e9f) {
+    // finish_few's scale ends at the row's largest value, unless at least a quarter of the lists have theirs in the lowest eighth below it; then at the
+    // largest of those: a few values far above the others would leave the others a few bins.  (us, in front of finish_few / with it, its scale up to M / so:
+    // 64 rows of 151,936 fp32, k = 1024, one value of 200 in each 20.9 / 22.6 / 19.4; 8 of 128,256 bf16, k = 256: 14.4 / 15.6 / 13.0.)
+    float high = M;
+    const float near = fmaf(0.125f, M - low, low);
+    if (4 * __popcll(__ballot(mx > near)) <= 3 * n_lists) high = wave_max(mx > near ? kNegInf : mx);
+    const float spread = (float)(kFewBins - 1) / (high - low);
+    if (ok && n_slots <= kAhead * kT && low > kNegInf && high > low && spread < __builtin_huge_valf() && fabsf(high) * spread < 1e9f) {
         const bool use_top_p = top_p > 0.f && top_p < 1.f;
         unsigned valid = 0;
 #pragma unroll
@@ -554,7 +566,7 @@ __device__ __forceinline__ void split_finish(
             if (u * kT < n_slots) valid |= f < n_slots && q < __shfl(held, l, kWave) ? 1u << u : 0u;
         }
         __syncthreads();
-        const Few did = finish_few<BF16>(sh, e, valid, n, V, low, M, T == kNegInf ? 0u : short_key<BF16>(__float_as_uint(T)), row, k,
+        const Few did = finish_few<BF16>(sh, e, valid, n, V, low, high, M, T == kNegInf ? 0u : short_key<BF16>(__float_as_uint(T)), row, k,
                                          !use_top_p && !fill, inv_T, idx, prob, count, mass, [&] { S = sum_of_lists(); return S; });
         if (did == Few::done && sound()) {
             if (tid == kT - 1) lse[row] = (float)((double)M * (double)inv_T + log(S));

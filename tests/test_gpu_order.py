@@ -41,6 +41,12 @@ def _rows(rng, pattern, R, V, dtype):
             z = np.minimum(z, 0.0)
     elif pattern == "outlier":
         z[:, V // 3] = 1e6
+    elif pattern.startswith("far"):                        # that many values far above the others, in as many places, some in turn above the rest of them
+        m = int(pattern[3:])
+        z[:, 100:100 + (V // (m + 1)) * m:V // (m + 1)] = 300.0
+        z[0, 100] = 1e6
+    elif pattern.startswith("grid"):                       # values on a grid: bins of some ten to some hundred
+        z = np.round(z * int(pattern[4:])) / int(pattern[4:])
     elif pattern == "steep":                               # a few far above, many close together
         z = np.sign(z) * np.abs(z) ** 4
     elif pattern == "late":                                # the largest ones in one workgroup's share: its list does not hold them
@@ -50,7 +56,8 @@ def _rows(rng, pattern, R, V, dtype):
     return z.astype(np.float32)
 
 
-@pytest.mark.parametrize("pattern", ["normal", "below_zero", "around_zero", "even", "equal64", "equal65", "equal200", "outlier", "steep", "late", "masked"])
+@pytest.mark.parametrize("pattern", ["normal", "below_zero", "around_zero", "even", "equal64", "equal65", "equal200", "equal256", "equal257", "outlier", "far1", "far2",
+                                     "far9", "far40", "grid2", "grid4", "grid8", "grid16", "steep", "late", "masked"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("V,R,k,top_p", [(16384, 2, 1, 0.0), (33001, 3, 64, 0.0), (33001, 2, 777, 0.9), (151936, 2, 1024, 0.0), (100003, 2, 1700, 0.0),
                                          (65536, 2, 2049, 0.0)])      # (slots of all lists on either side of 4096)
