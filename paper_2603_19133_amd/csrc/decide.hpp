@@ -996,8 +996,11 @@ __device__ __forceinline__ void residual_seg_sequence(
 // record's probabilities with the ids, and for the target's logits at all of them together with the token's, so that when the first
 // rejection is known its wave holds all the draw needs in registers, its entries with their logits and its row's segments.  It
 // sums, scans and picks the segment alone, without a barrier, and the whole workgroup names the token, one dword of the segment per thread.
-// For records of up to 256 entries (kDecideRowsK) and drafts of up to 15 positions in a call whose table stands in the split layout: the
-// gathers of the positions that are not drawn from are what longer records would pay for.  Bound by the chain of latencies: of 5.8 us
+// For records of up to 256 entries (kDecideRowsK) and drafts of up to 15 positions in a call whose table stands in the split layout: longer records
+// pay for the gathers of the positions that are not drawn from, and with registers for 512 entries all calls take 0.9 us more.  Verification and draw in a replayed graph, us,
+// general code / 256 entries / 512: 8 sequences of 8 drafts of 32,000 fp32, k = 64 12.5 / 10.8 / 11.9, 256 12.4 / 11.2 / 12.3, 320 13.0 / - / 12.4, 512 13.0 / - / 13.0; 16 of 8 of
+// 151,936, k = 256 22.2 / 21.6 / 22.7, 320 22.5 / - / 23.0, 512 22.6 / - / 25.1; 12 of 14 of 128,256, k = 256 23.7 / 23.9 / 25.1, 320 24.5 / - / 26.9; bf16 17.9 / 17.4 / 18.4, 18.4 / - / 19.5.
+// Bound by the chain of latencies: of 5.8 us
 // for one sequence of 32,000 fp32, k = 64, the three trips are 0.7, 0.7 and 0.5, the scan of the segments and the token 1.0 each.
 // General code / here, us a call: that round 18.7 / 16.4, 8 sequences of 8 drafts of 32,000 bf16, k = 256: 21.8 / 19.7, verification and draw of 16 of
 // 151,936 fp32, k = 64: 18.9 / 17.1.

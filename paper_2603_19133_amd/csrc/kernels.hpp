@@ -54,10 +54,12 @@ __host__ __device__ inline int optimistic_rank(int k, int V, int m, int cap, flo
 //     workgroup); its lists together must fit the candidate buffer of the finishing kernel with room to spare.
 //   * a list holds the rank, a crowded pivot bin and some slack.
 //   * lanes: of a workgroup's 256 lanes, 256 (1 - exp(-rank / 256)) hold one of its `rank` largest elements on average, so a threshold with that
-//     many lanes' maxima at or above it has about `rank` elements above it, with a standard deviation of 4.3 at rank 93, 4.7 at
-//     100 and 4.9 at 103 (simulated orders).  Together with the share's own that leaves 4.6 to 4.7 deviations (k = 1024 and 1100 in 19 parts, 256 in
-//     4), of the 4.5 asked for; at 125 (k = 330 in 4) it would be 4.3.  Ranks beyond kSplitLanesRank (lanes = 0) count the elements: 8 sequences of 8
-//     drafts of 32,000 bf16, k = 256 (rank 102), a round 18.9 us so, 18.3 by lanes.
+//     many lanes' maxima at or above it has about `rank` elements above it, with a standard deviation of 4.3 at rank 93, 4.8 at 104 and
+//     5.1 at 110 (simulated orders, 4000 a point).  Together with the share's own that leaves of the 4.5 deviations asked for 4.5 to 4.7 up to rank 104 in rows of three
+//     parts and more, 4.46 at 106 (3 and 4 parts) and 4.2 at 125 (4), and 4.3 to 4.4 in rows of two parts from 100 on; of 512 lanes, with which calls in one launch
+//     select, 4.9 at 102 to 113, 4.7 at 125.  So ranks beyond kSplitLanesRank (lanes = 0) count the elements, which is slower everywhere: us, elements / lanes, fp32 (bf16):
+//     8 rows of 32,000, k = 256 (rank 102) 9.9 / 9.6 (9.7 / 9.4), 290 (113) 9.9 / 9.6 (9.7 / 9.4); 48 of 131,072, k = 975 (102) 15.1 / 14.3 (14.5 / 13.7), 1050 (108)
+//     15.6 / 14.9 (15.0 / 14.2).
 constexpr int kSplitMaxRows = 192;
 inline int split_max_rows(int k) { return k <= 256 ? kSplitMaxRows : k <= 1024 ? 128 : 80; }
 constexpr int kSplitMinV = 16384;                // (two workgroups per row)

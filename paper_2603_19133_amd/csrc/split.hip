@@ -1,5 +1,5 @@
 // Sparse Top-K compression of few rows (paper Section 3.3, Eq. 4): a call that leaves most of the chip idle spreads every
-// row over many small workgroups and finishes it in a second launch.
+// row over many small workgroups and finishes it in a second launch, or in the same one by the last of the row's workgroups.
 //
 // One workgroup per row (compress_row.hpp) is a chain of phases on one CU: 25 us for a bf16 row of 128,256 whatever k is, of
 // which 13 us are the streaming of the row by eight waves and the rest serial phases that issue one instruction per wave
@@ -11,9 +11,10 @@
 //     row's k largest, so the elements above it hold the row's top k but for a chance of some 1e-6.  The workgroup writes
 //     them to a list of its own in the scratch, and its share of the statistics in front of it.
 //   * split_finish_kernel: one workgroup per row gathers the lists (about k plus the ranks' margins), orders them and writes
-//     the record with the code of the unsplit kernels.  The answer is exact iff the k-th value lies above every workgroup's
+//     the record: from registers (finish_few), or with the code of the unsplit kernels.  The answer is exact iff the k-th value lies above every workgroup's
 //     threshold, which is tested; a row that fails it (or whose lists overflow) is compressed from the start by the
 //     unsplit kernels' code in the same workgroup.
+//   * split_compress_kernel: both, for calls of up to 128 workgroups whose scratch has room for the rows' words (split_one_launch).
 // Device time of a call, one workgroup per row -> split: one bf16 row of 128,256, k = 10: 25.5 -> 4.8 + 4.3 us; 64 fp32 rows of
 // 151,936, k = 1024: 31.0 -> 10.5 + 6.6 us, of which the first launch reads 39 MB (5.8 us at 6.8 TB/s).  The line between the two
 // is split_plan's.
