@@ -72,10 +72,11 @@ struct RecordScan {
             else { if (s < k) front[u].x = ids[s]; if (s + 4 * kWave < k) front[u].y = ids[s + 4 * kWave]; }
         }
     }
-    // the slot among the record's first cnt that holds x, or -1; in every lane
+    // the slot among the record's first cnt that holds x, or -1; in every lane.  PIN: fewer registers, some instructions more
+    template <bool PIN = true>
     __device__ __forceinline__ int find(const int32_t* __restrict__ ids, int cnt, int x) const {
         int lane = threadIdx.x & (kWave - 1);
-        asm volatile("" : "+v"(lane));           // (the slots are formed here, not held from in front of a caller's loop)
+        if (PIN) asm volatile("" : "+v"(lane));           // (the slots are formed here, not held from in front of a caller's loop)
         int slot = -1;
         // The record is ordered by probability and the token was drawn from it, so it sits near the
         // front more often than not: the scan goes in rounds of 1024 ids and stops at the round
@@ -147,7 +148,8 @@ __device__ __forceinline__ void write_split_lse(const SplitStats* s_stats, int2 
 // (write_split_lse), for the positions that come back in `rows`.
 // Positions whose row lies outside the call's n_rows, or whose draft outside its n_rows - B drafts (offsets that leave them), are flagged and
 // rejected; nothing is read or written for them.
-template <bool BF16, bool TABLE = false>
+// PIN: RecordScan::find's.
+template <bool BF16, bool TABLE = false, bool PIN = true>
 __device__ __forceinline__ int accept_sequence(
     const int b, const int B, const int n_rows, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
@@ -179,9 +181,10 @@ __device__ __forceinline__ int accept_sequence(
 
     // every target row of the range must have finite statistics
     if constexpr (!TABLE) {
-        for (int t = begin + tid; t <= end; t += kThreads)
-            if (t0 + t < 0 || t0 + t >= n_rows) fl |= 8u;
-            else if (nonfinite(tgt_max[t0 + t], tgt_sum[t0 + t])) fl |= 2u;
+        if (t0 + begin < 0 || t0 + end >= n_rows) fl |= 8u;
+        const int64_t row_end = min(t0 + end + 1, (int64_t)n_rows);
+        for (int64_t r = max(t0 + begin, (int64_t)0) + tid; r < row_end; r += kThreads)
+            if (nonfinite(tgt_max[r], tgt_sum[r])) fl |= 2u;
     }
 
     // (TABLE: the row behind the last position as well, and, where all of the call's rows get statistics, by the first and the last
@@ -196,12 +199,12 @@ __device__ __forceinline__ int accept_sequence(
         const int64_t rt = t0 + i;
         bool decides = !TABLE || (i >= begin && i < end);             // (the other rows have statistics only)
         const int64_t rd = (int64_t)d0 + (decides ? i : 0);
-        const bool outside = rt < 0 || rt >= n_rows;
+        const bool outside = (PIN || !decides) && (rt < 0 || rt >= n_rows);           // (a draft of the call's has its row there)
         if (outside || (decides && (rd < 0 || rd >= n_rows - B))) {
             fl |= 8u;
             if (decides && lane == 0) atomicMin(&s_first, i);
             decides = false;
-            if (outside || !TABLE) continue;
+            if (outside || !TABLE || rt < 0 || rt >= n_rows) continue;
         }
         int x = -1, cnt = 0;
         float u_t = 0.f, mass_d = 1.f, M_t = 0.f, S_t = 1.f;
@@ -237,7 +240,7 @@ __device__ __forceinline__ int accept_sequence(
         bool in_record = false;
         if (decides && !q_scalar) {
             cnt = cnt < 0 ? 0 : (cnt > k ? k : cnt);
-            const int slot = scan.find(ids, cnt, x);
+            const int slot = scan.template find<PIN>(ids, cnt, x);
             in_record = slot >= 0 && !bad;
             if (in_record) q_at = q_prob[rd * k + slot];
         }
@@ -751,7 +754,8 @@ struct __align__(16) SegResidualShared {
 // chain of scans and barriers, four instructions' time each once a SIMD holds several (residual_seg_threads).
 // SHARED: the table was written by other workgroups of this launch (and has no header).
 // A row outside the call's n_rows, or a record outside its n_draft (offsets that leave them), is flagged and gives token 0; nothing of it is read.
-template <bool BF16, int RT, bool SHARED = false>
+// GUARD: the place is looked at behind a branch.
+template <bool BF16, int RT, bool SHARED = false, bool GUARD = false>
 __device__ __forceinline__ void residual_seg_sequence(
     const int b, const int j_in, const int n_rows, const int n_draft, const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const float* __restrict__ tgt_max, const SegHeader* __restrict__ table,
@@ -774,12 +778,14 @@ __device__ __forceinline__ void residual_seg_sequence(
     if (g < 0) { fl |= 8u; g = 0; }
     int j = j_in;
     if (j < 0 || j > g) { fl |= 8u; j = j < 0 ? 0 : g; }
-    const int64_t rt = (int64_t)d0 + b + j;
+    int64_t rt = (int64_t)d0 + b + j;
     const int64_t rd = (int64_t)d0 + j;
     bool has_q = j < g;
-    if (rt < 0 || rt >= n_rows || (has_q && (rd < 0 || rd >= n_draft))) {
-        if (tid == 0) { out_tok[b] = 0; resid_mass[b] = 0.f; flags[b] = fl | 8u; }
-        return;
+    // (the answer is given where the table's header is looked at: a branch in front of the loads below costs 0.3 us.  The call's first row is read instead)
+    bool outside = false;
+    if (!GUARD || __builtin_expect(d0 < 0 || (int64_t)d0 + g > n_draft, 0)) {       // (uniform: whether some position of the sequence may be)
+        outside = rt < 0 || rt >= n_rows || (has_q && (rd < 0 || rd >= n_draft));
+        if (outside) { rt = 0; has_q = false; }
     }
     const RowView rv = row_view<BF16>(tgt_logits, ld, rt, V);
     const int nq = (rv.L + N - 1) / N;
@@ -832,7 +838,7 @@ __device__ __forceinline__ void residual_seg_sequence(
     const float c = 1.4426950408889634f * inv_T;
     const double cd = 1.4426950408889634 * (double)inv_T;
     const double q_scale = 1.0 / (double)mass_d;
-    if (!table_ok || (hd.magic != kSegMagic && hd.magic != kSegMagicSplit) || rt >= hd.rows || hd.stride != stride || hd.seg_vecs != seg_vecs) {
+    if (outside || !table_ok || (hd.magic != kSegMagic && hd.magic != kSegMagicSplit) || rt >= hd.rows || hd.stride != stride || hd.seg_vecs != seg_vecs) {
         if (tid == 0) { out_tok[b] = 0; resid_mass[b] = 0.f; flags[b] = fl | 8u; }     // (not the table of these rows)
         return;
     }

@@ -87,8 +87,10 @@ __global__ __launch_bounds__(RT) void residual_spread_kernel(
                                           q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, flags, nullptr, true);
 }
 
-// SPLIT: the table stands in the split layout, and the rows' statistics are formed here.
-template <bool BF16, bool SPLIT, int RT>
+// SPLIT: the table stands in the split layout, and the rows' statistics are formed here.  PIN: RecordScan::find's, and no GUARD in the draw: 0.2 us faster in
+// decide_rows_kernel, whose registers this code sets (a round of one sequence 15.7 us, 16.0 without), 0.4 slower in kernels of its own (64 sequences of 8 drafts of 128,256
+// bf16 67.0, 67.5 with).
+template <bool BF16, bool SPLIT, int RT, bool PIN>
 __device__ __forceinline__ void decide_seg(
     const void* __restrict__ tgt_logits, int64_t ld, int V, float inv_T,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ draft_tok,
@@ -101,7 +103,7 @@ __device__ __forceinline__ void decide_seg(
 {
     __shared__ SplitStats s_stats[SPLIT ? kSplitStatsRows : 1];
     int2 rows = make_int2(0, 0);
-    const int first = accept_sequence<BF16, SPLIT>(blockIdx.x, (int)gridDim.x, n_rows, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
+    const int first = accept_sequence<BF16, SPLIT, PIN>(blockIdx.x, (int)gridDim.x, n_rows, tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob,
                                                    q_count, q_mass, k, renorm, nullptr, uniforms, tgt_max, tgt_sum,
                                                    n_accept, p_tok, q_tok, flags, nullptr, nullptr,
                                                    tgt_lse, table, seg_vecs, stride, true, SPLIT ? s_stats : nullptr, &rows);
@@ -115,7 +117,7 @@ __device__ __forceinline__ void decide_seg(
     } else if (SPLIT) {
         write_split_lse(s_stats, rows, t0, inv_T, tgt_lse, 0, kThreads);
     }
-    residual_seg_sequence<BF16, RT>(blockIdx.x, first, n_rows, n_rows - (int)gridDim.x, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
+    residual_seg_sequence<BF16, RT, false, !PIN>(blockIdx.x, first, n_rows, n_rows - (int)gridDim.x, tgt_logits, ld, V, inv_T, seq_off, tgt_max, table, seg_vecs, stride,
                                     q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, out_tok, resid_mass, res_flags,
                                     SPLIT ? s_stats : nullptr);
 }
@@ -131,7 +133,7 @@ __global__ __launch_bounds__(kThreads) void decide_seg_kernel(
     int32_t* __restrict__ n_accept, float* __restrict__ p_tok, float* __restrict__ q_tok, uint32_t* __restrict__ flags,
     int32_t* __restrict__ out_tok, float* __restrict__ resid_mass, uint32_t* __restrict__ res_flags, int n_rows)
 {
-    decide_seg<BF16, SPLIT, RT>(tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse,
+    decide_seg<BF16, SPLIT, RT, false>(tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum, tgt_lse,
                                 table, seg_vecs, stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags, n_rows);
 }
 
@@ -152,7 +154,7 @@ __global__ __launch_bounds__(kThreads) void decide_rows_kernel(
         decide_rows<BF16>(b, d0, d1, tgt_logits, ld, V, inv_T, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum,
                           tgt_lse, table, stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags);
     else
-        decide_seg<BF16, true, 256>(tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum,
+        decide_seg<BF16, true, 256, true>(tgt_logits, ld, V, inv_T, seq_off, draft_tok, q_idx, q_prob, q_count, q_mass, k, renorm, uniforms, tgt_max, tgt_sum,
                                     tgt_lse, table, seg_vecs, stride, n_accept, p_tok, q_tok, flags, out_tok, resid_mass, res_flags, n_rows);
 }
 
