@@ -443,7 +443,7 @@ __device__ __forceinline__ const uint64_t* order_top_k(SH& sh, int n, int k, int
     // largest value in parts of the whole, the bin is kFine t (1 + 3 t^3) / 4: exponential and Gaussian tails (a few thousand candidates:
     // density about e^(8 t)) leave one or two entries in every bin, an even distribution up to three.  (Rounded, each product is
     // monotone, so the bins never decrease along the order.)  A row with a more crowded bin - values on a grid, an outlier - takes the ranges.
-    // us: 300 rows of 50,001, k = 777, top-p 25.6 -> 24.4; 512 drafts beside 576 target rows of 128,256, k = 1024 67.6 -> 66.9; 4352 of 152,064 532 -> 530 the round.
+    // us: 300 rows of 50,001, k = 777, top-p 25.6 -> 24.4; 512 drafts beside 576 target rows of 128,256, k = 1024 67.6 -> 66.9; 4352 of 152,064, the round, 533 and 530, which is no more than its runs differ.
     bool placed = false;
     if (LINEAR && linear && !sh.on_grid) {
         unsigned seen = 0;                           // (an arrival of kDirectMaxBin or later leaves a bit)

@@ -373,8 +373,8 @@ __device__ __attribute__((noinline)) void split_row_again(
 // 151,936, k = 1024: 7.4 -> 5.6; a round of that row 16.4 -> 15.6, the draft of those 22.0 -> 20.0.
 constexpr int kFewBins = kBins;                         // (a bin per word of the histogram)
 // Entries of a bin that are ranked by comparing all: as many as values on a grid put there, which order_top_k, where fp32 values tie, would sort by a network.
-// (64 rows of 151,936, k = 1024, us, in front of finish_few / up to 64 / so: fp32 on eighths 40.0 / 42.0 / 26.3, sixths 41.2 / 43.2 / 30.0, quarters 46.6 / 48.8 /
-// 43.5; bf16 on sixths 22.0 / 23.4 / 21.8, whose places the ids spread: with up to 512 24.6.)
+// (64 rows of 151,936, k = 1024, us, in front of finish_few / up to 64 / so, with the selection as it is: fp32 on eighths 40.0 / 42.0 / 22.2, sixths 41.2 / 43.2 / 24.8,
+// quarters 46.6 / 48.8 / 39.0; bf16 on sixths 22.0 / 23.4 / 16.7, whose places the ids spread: with up to 512, and the selection as it was, 24.6 for 21.8.)
 template <bool BF16> constexpr int kFewMost = BF16 ? 256 : 512;
 enum class Few { crowded, missing, done };
 template <bool BF16, int SLOTS, class SH, class F>
@@ -551,7 +551,7 @@ __device__ __forceinline__ void split_finish(
     auto sound = [&] { return S > 0.0 && S < 1e300; };
     // finish_few's scale ends at the row's largest value, unless at least a quarter of the lists have theirs in the lowest eighth below it; then at the
     // largest of those: a few values far above the others would leave the others a few bins.  (us, in front of finish_few / with it, its scale up to M / so:
-    // 64 rows of 151,936 fp32, k = 1024, one value of 200 in each 20.9 / 22.6 / 19.4; 8 of 128,256 bf16, k = 256: 14.4 / 15.6 / 13.0.)
+    // 64 rows of 151,936 fp32, k = 1024, one value of 200 in each 20.8 / 22.6 / 15.7; 8 of 128,256 bf16, k = 256: 14.4 / 15.8 / 10.1.)
     float high = M;
     const float near = fmaf(0.125f, M - low, low);
     if (4 * __popcll(__ballot(mx > near)) <= 3 * n_lists) high = wave_max(mx > near ? kNegInf : mx);
