@@ -21,6 +21,10 @@ def _rows(g, pattern, rows, ld):
     z = torch.randn((rows, ld), device="cuda", generator=g) * 3
     if pattern == "masked":
         z[torch.rand((rows, ld), device="cuda", generator=g) < 0.999] = float("-inf")
+    elif pattern == "grid":                      # values that tie: the two forms' lanes find other thresholds
+        z = torch.round(z * 4) / 4
+    elif pattern == "far":                       # a few values far above the others
+        z[:, 7:ld:ld // 3] = 300.0
     elif pattern == "lost":                      # +-inf, NaN, one value: rows that the lists cannot give
         z[0, 5] = float("inf")
         z[rows - 1] = 0.25
@@ -43,7 +47,7 @@ def _same(a, b):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("V,ld,rows,k", CASES)
-@pytest.mark.parametrize("pattern", ["normal", "masked", "lost"])
+@pytest.mark.parametrize("pattern", ["normal", "masked", "grid", "far", "lost"])
 def test_one_launch_is_two(gpu, ps, dtype, V, ld, rows, k, pattern):
     print("[case]", V, rows, k, dtype, pattern, flush=True)
     g = torch.Generator(device="cuda"); g.manual_seed(V + k)
